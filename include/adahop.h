@@ -131,8 +131,7 @@ int adahop_foid_topk_noalloc(const adahop_operand_t *x, int axis, int k, int32_t
  * codes / scales in the canonical layout above; codes 16-byte aligned, K % 32 == 0.
  * workspace: device scratch of at least adahop_gemm_mx_workspace_bytes(M, N, K) bytes, 256-byte
  * aligned (the kernel keeps a re-ordered copy of the scales there); contents undefined on return.
- * With K % 256 == 0 and K >= 768 the whole 256x256 tiles of C take the tiled, LDS-pipelined kernel
- * and only the ragged edges a slower bounds-checked kernel; any other K takes the latter throughout.
+ * Products with M, N >= 256 and K > 512 take the tiled, LDS-pipelined kernels, smaller ones a bounds-checked kernel.
  * ------------------------------------------------------------------------------------------- */
 size_t adahop_gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int adahop_gemm_mx(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales,
@@ -330,7 +329,7 @@ int adahop_probe_mfma_rate(int random_operands, int idle_sleeps, int workgroups,
 
 /* Measurement aid: which tiled kernel the MXFP4 product uses from now on (process-wide).  0 = chosen by shape (the
  * default), 1 = always the 256 x 256 tile kernel, 2 = the 256 x 128 tile kernel with two accumulator sets wherever it
- * can run (fp32 C, K % 256 == 0, K >= 2048, no K-channel extraction).  3 .. 6 = kernel chosen by shape, and the
+ * can run (fp32 C, K > 1792, no K-channel extraction).  3 .. 6 = kernel chosen by shape, and the
  * 256 x 256 kernel walks its tiles in a forced order: 3 = bands of A in XCD-contiguous runs, 4 = bands of A swept
  * over B, 5 / 6 = the same two with the roles of A and B exchanged (a sweep that the shape does not allow falls back
  * to the contiguous runs).  By default the bands run along the operand with more tiles, swept where more of it would

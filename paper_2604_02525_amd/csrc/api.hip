@@ -9,8 +9,7 @@ static thread_local int g_last_hip_error = 0;
 void set_last_hip_error(int e) { g_last_hip_error = e; }
 
 // Largest operand extents.  They keep every launch legal: the second grid dimension of a launch may not exceed
-// 65535, and the kernels put K / 256 (fast quantisers), K / 128 (general K-strided quantiser: K / 32 blocks over
-// 4 waves) and stored rows / 256 (pattern detector) there.  The OHT kernels put outer / block there and check it
+// 65535, and the kernels put K / 256 (quantisers) and stored rows / 256 (pattern detector) there.  The OHT kernels put outer / block there and check it
 // themselves (oht_grid_ok).
 static const int64_t MAX_OUTER = (int64_t)1 << 21;
 static const int64_t MAX_K = (int64_t)1 << 21;
@@ -65,7 +64,7 @@ int adahop_prepare_device(void)
     int rc;
     if ((rc = configure_gemm_mx(nullptr)) != ADAHOP_OK || (rc = configure_gemm_mx_dual(nullptr)) != ADAHOP_OK ||
         (rc = configure_oe_rowcol()) != ADAHOP_OK || (rc = configure_oht()) != ADAHOP_OK ||
-        (rc = configure_quantizers()) != ADAHOP_OK || (rc = configure_foid()) != ADAHOP_OK)
+        (rc = configure_foid()) != ADAHOP_OK)
         return rc;
     float *scores = nullptr;
     return foid_static_scores(&scores); // the address of the built-in score scratch, looked up once per device
@@ -421,8 +420,7 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // The tiled GEMM kernel reads the scales in a stage-major copy; the quantisers that run here write it
     // beside the canonical one, which saves the product its two re-ordering launches.
     const int kpad_planned = oe && strategy == ADAHOP_IHT_OE_K ? kpad_of(k) : 0;
-    int64_t Mi = 0, Ni = 0;
-    gemm_mx_tiled_part(M, N, K, kpad_planned, a_scales, b_scales, C, ldc, c_bf16, &Mi, &Ni);
+    const bool sm_wanted = !oht && gemm_mx_tiled(M, N, K, kpad_planned, C, ldc, c_bf16);
     // K-channel extraction: a quantiser that runs here on a K-contiguous operand also copies the extracted channels
     // out (it has the row in registers); the position of a channel in the index list comes from a 16-bit table that
     // takes the place of the scores, which nobody reads after the selection.
@@ -442,21 +440,21 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     int sm_ready = 0;
     if (!a_given) {
         uint8_t *c = reinterpret_cast<uint8_t *>(ws + L.a_codes), *s = reinterpret_cast<uint8_t *>(ws + L.a_scales);
-        const scales_sm_t sm = {Mi > 0 && !oht ? gemm_mx_scales_sm(ws + L.gemm, M, K, 0) : nullptr, Mi};
+        const scales_sm_t sm = {sm_wanted ? gemm_mx_scales_sm(ws + L.gemm, M, K, 0) : nullptr, M};
         rc = oht ? launch_oht_quantize(*A, b, c, s, st)
                  : launch_iht_quantize(*A, b, a_kind == 1 ? mask : nullptr, a_kind == 2 ? mask : nullptr, c, s, st,
                                        opts && opts->sr_a ? &opts->sr_seed_a : nullptr, &sm, &ga);
         if (rc != ADAHOP_OK) return rc;
-        if (sm.out && iht_quantize_writes_scales_sm(*A)) sm_ready |= 1;
+        if (sm.out) sm_ready |= 1;
     }
     if (!b_given) {
         uint8_t *c = reinterpret_cast<uint8_t *>(ws + L.b_codes), *s = reinterpret_cast<uint8_t *>(ws + L.b_scales);
-        const scales_sm_t sm = {Ni > 0 && !oht ? gemm_mx_scales_sm(ws + L.gemm, M, K, 1) : nullptr, Ni};
+        const scales_sm_t sm = {sm_wanted ? gemm_mx_scales_sm(ws + L.gemm, M, K, 1) : nullptr, N};
         rc = oht ? launch_oht_quantize(*B, b, c, s, st)
                  : launch_iht_quantize(*B, b, b_kind == 1 ? mask : nullptr, b_kind == 2 ? mask : nullptr, c, s, st,
                                        opts && opts->sr_b ? &opts->sr_seed_b : nullptr, &sm, &gb);
         if (rc != ADAHOP_OK) return rc;
-        if (sm.out && iht_quantize_writes_scales_sm(*B)) sm_ready |= 2;
+        if (sm.out) sm_ready |= 2;
     }
     // 3. MXFP4 product, with the K-channel BF16 product fused in front; 4. row / column BF16 product
     if (oe_k) {

@@ -34,18 +34,14 @@ int configure_gemm_mx(int *ncu_out);
 int configure_gemm_mx_dual(int *ncu_out);
 int configure_oe_rowcol();
 int configure_oht();
-int configure_quantizers();
 int configure_foid();
 
 // Launchers (one per kernel family); each validates nothing and returns a status.
-// Stage-major copy of the scales for the tiled GEMM kernel (see gemm_mx_tiled_part): [K/256][rows][8].
+// Stage-major copy of the scales for the tiled GEMM kernels (see gemm_mx_tiled_part): [ceil(K/256)][rows][8].
 struct scales_sm_t {
     uint8_t *out; // stage-major copy, or nullptr
-    int64_t rows; // rows [0, rows) are written
+    int64_t rows; // rows of the operand
 };
-// Whether launch_iht_quantize honours a scales_sm_t for this operand (only its kernels for K % 256 == 0 write the
-// copy); a caller may tell the product that the copy is there only if this holds.
-bool iht_quantize_writes_scales_sm(const adahop_operand_t &x);
 // The extracted K-channels of an operand, copied out by the quantiser that reads the operand anyway (Eq. 7 with
 // S a set of K-channels): out[o, pos1[c] - 1] = x(o, c) for every channel c with pos1[c] != 0, out[o, k .. kpad) = 0.
 // out is [outer, kpad] bf16; pos1[c] = t + 1 for the channel c = idx[t], 0 for a channel that is not extracted.
@@ -75,15 +71,14 @@ int launch_gemm_mx(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, cons
                    const uint16_t *Ag, const uint16_t *Bg, int kpad, void *workspace, hipStream_t st,
                    int sm_ready = 0);
 size_t gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K);
-// The tiled kernel reads the scales in a stage-major copy, [K/256][rows][8] over the rows it takes.  A caller
+// Whether a tiled kernel takes the product; it reads the scales in a stage-major copy, [ceil(K/256)][rows][8].  A caller
 // that quantises right before the product lets the quantiser write that copy as well (scales_sm_t above) and
 // says so with sm_ready (bit 0: A, bit 1: B); otherwise launch_gemm_mx re-orders the canonical scales itself.
-void gemm_mx_tiled_part(int64_t M, int64_t N, int64_t K, int kpad, const uint8_t *a_scales, const uint8_t *b_scales,
-                        const void *C, int64_t ldc, int c_bf16, int64_t *Mi, int64_t *Ni);
+bool gemm_mx_tiled(int64_t M, int64_t N, int64_t K, int kpad, const void *C, int64_t ldc, int c_bf16);
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which);
-// The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): fp32 C, no gathered K-channels, K >= 2048.
+// The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): fp32 C, no gathered K-channels, K > 1792.
 bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K);
-int launch_gemm_mx_dual(int64_t Mi, int64_t Ni, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
+int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
                         const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, hipStream_t st);
 // Diagnostics: 0 = choose by shape, 1 = always the 256 x 256 kernel, 2 = the 256 x 128 kernel wherever it can run.
 void gemm_mx_force_kernel(int which);

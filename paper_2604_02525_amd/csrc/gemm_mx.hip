@@ -39,7 +39,7 @@ __device__ __forceinline__ float load_c(const uint16_t *p) { return bf16_one(*p)
 // ------------------------------------------------------------------------------------------------
 // Generic kernel: any M, N, any K % 32 == 0.  Workgroup tile 128x128, four waves as 2x2, each wave
 // 64x64 (2x2 matrix-core tiles), operands read straight from global memory with bounds checks.
-// It is the reference for the layout assumptions above and the fallback for ragged shapes.
+// For products too small for a tile of the kernels below (and the accumulating form of the K-channel product).
 // ------------------------------------------------------------------------------------------------
 template <bool ACCUMULATE, typename OUT>
 __global__ __launch_bounds__(256) void k_gemm_mx_generic(int64_t M, int64_t N, int64_t K,
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void k_gemm_mx_generic(int64_t M, int64_t N, i
 
 
 // ------------------------------------------------------------------------------------------------
-// Tiled kernel for M % 256 == 0, N % 256 == 0, K % 256 == 0 (and kpad % 64 == 0).
+// Tiled kernel for M >= 256, N >= 256, K > 512 (K % 32 == 0, kpad % 64 == 0).
 //
 // A workgroup (4 waves, 2x2) computes 256x256 tiles of C, one after the other; each wave owns 128x128 =
 // 4x4 matrix-core tiles, i.e. 256 fp32 accumulators per lane, and the workgroup is alone on its compute
@@ -147,22 +147,40 @@ __global__ __launch_bounds__(256) void k_gemm_mx_generic(int64_t M, int64_t N, i
 // Scales reach LDS by DMA as well, so the main loop has no register-targeted global loads and only
 // waits where the kernel says so.  Fetching 8 bytes per row from the canonical [rows, K/32] array
 // would cost one cache-line request per row and stage -- as many requests as the codes need -- so the
-// kernel reads a stage-major copy, [K/256][rows][8], where the 256 rows of a slab are 2 KiB contiguous:
+// kernel reads a stage-major copy, [ceil(K/256)][rows][8], where the 256 rows of a slab are 2 KiB contiguous:
 // written by the quantiser beside the canonical scales, or by a small pre-pass (k_stage_major_scales).
+//
+// Ragged shapes take whole tiles and whole stages all the same.  The last tile of a dimension starts at M - 256
+// (N - 256): it overlaps the tile before it, computes the shared elements of C a second time from the same bytes in
+// the same order, and stores the same bits.  The last stage of a K that is no multiple of 256 starts at K - 256: its
+// leading MX blocks are those that the stage before has already used, and their scale bytes are 0 in both operands of
+// the stage-major copy, 2^-127 each, so that their products are below every fp32 number.  That costs the matrix-core
+// work of at most one tile row, tile column and stage; the edges as a launch of a bounds-checked kernel of their own took
+// more than the tiles themselves (2016 x 11008 x 4096: 65 + 67 us, now 65), and so did the whole product for any other
+// K % 256 (11008 x 4096 x 2016: 266 us, now 67).
 // ------------------------------------------------------------------------------------------------
 constexpr int TM = 256, TN = 256, TKB = 128, NSTAGE = 2;
 constexpr int SLAB_BYTES = (TM + TN) * TKB;             // codes (or gathered bf16) of one stage
 constexpr int STAGE_BYTES = SLAB_BYTES + (TM + TN) * 8; // + 8 scale bytes per row
 constexpr int TILED_LDS_BYTES = NSTAGE * STAGE_BYTES;
 
-// out[s][row][0..7] = in[row][8s .. 8s+7]   (8-byte units; KB8 = K/256 units per row)
-__global__ __launch_bounds__(256) void k_stage_major_scales(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
-                                                            int64_t rows, int64_t KB8)
+// out[s][row][0..7] = in[row][8s .. 8s+7]; of a last stage with t < 8 blocks the last t bytes, behind zeros (see above).
+// WORDS: K % 256 == 0 and the scales 8-byte aligned, so that a row's eight bytes are one word.
+template <bool WORDS>
+__global__ __launch_bounds__(256) void k_stage_major_scales(const uint8_t *__restrict__ in, uint64_t *__restrict__ out,
+                                                            int64_t rows, int64_t KB)
 {
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= rows * KB8) return;
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x, stages = (KB + 7) >> 3;
+    if (g >= rows * stages) return;
     const int64_t s = g / rows, r = g - s * rows; // consecutive threads: consecutive rows (coalesced writes)
-    out[g] = in[r * KB8 + s];
+    if constexpr (WORDS) {
+        out[g] = reinterpret_cast<const uint64_t *>(in)[r * stages + s];
+    } else {
+        const int t = (int)(KB - 8 * s < 8 ? KB - 8 * s : 8);
+        uint64_t v = 0;
+        for (int j = 0; j < t; ++j) v |= (uint64_t)in[r * KB + 8 * s + j] << (8 * (j + 8 - t));
+        out[g] = v;
+    }
 }
 
 struct frags_t {
@@ -191,6 +209,7 @@ struct tile_state_t {
     uint32_t lrow, c_even, c_odd, vs;        // per-lane: row within an 8-row group, byte of its chunk in even / odd
                                              // groups, offset of the scale copy
     uint32_t pitch, gpitch;                  // bytes between rows of the codes / of the gathered bf16 operands
+    int last_off;                            // byte offset in a row of the last FP4 stage: the row's last 128 bytes
     int64_t s_stride;
     uint32_t lds_w;                          // LDS address of this wave's 64 rows of the A slab, buffer 0
     uint32_t lds_s;                          // LDS address of this wave's 1 KiB of scales, buffer 0
@@ -255,8 +274,9 @@ __device__ __forceinline__ void issue_copies(const tile_state_t &t, const copy_s
     const uint32_t boff = buf * STAGE_BYTES;
     const int cs = stage - t.nbf;                      // index among the FP4 stages
     const uint32_t rp = TBF ? t.gpitch : t.pitch;      // row pitch of this stage's operands
-    const uint8_t *pa = TBF ? src.gga + (int64_t)stage * TKB : src.ga + (int64_t)cs * TKB;
-    const uint8_t *pb = TBF ? src.ggb + (int64_t)stage * TKB : src.gb + (int64_t)cs * TKB;
+    const int coff = TBF ? stage * TKB : min(cs * TKB, t.last_off);
+    const uint8_t *pa = (TBF ? src.gga : src.ga) + coff;
+    const uint8_t *pb = (TBF ? src.ggb : src.gb) + coff;
     // row group g starts 8 g rows further: a wave-uniform term that goes into the base address
     const uint32_t v_even = t.lrow * rp + t.c_even, v_odd = t.lrow * rp + t.c_odd;
 #pragma unroll
@@ -460,8 +480,8 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
 // workgroup walks the tile sequence with the stride of the grid.  The stage pipeline of a tile runs over
 // the gathered bf16 K-channels first (OEK), then over the FP4 stages, and on into the next tile: while a
 // tile's accumulators are stored, the first two stages of the next one are already in LDS or on the way.
-// Host side guarantees K >= 512 (two FP4 stages), so that every bf16 stage has two successors and the
-// last two stages of a tile are FP4 stages, and at least three stages per tile (K >= 768 when there are
+// Host side guarantees K > 256 (two FP4 stages), so that every bf16 stage has two successors and the
+// last two stages of a tile are FP4 stages, and at least three stages per tile (K > 512 when there are
 // no bf16 stages).
 template <bool OEK, typename OUT>
 __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_t *__restrict__ a_codes,
@@ -509,8 +529,8 @@ __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_
             major = first + (tix % band) % gsz;
             minor = (tix % band) / gsz;
         }
-        m0 = (int64_t)(b_major ? minor : major) * TM;
-        n0 = (int64_t)(b_major ? major : minor) * TN;
+        m0 = min((int64_t)(b_major ? minor : major) * TM, M - TM); // the last tile of a ragged dimension ends with it
+        n0 = min((int64_t)(b_major ? major : minor) * TN, N - TN);
     };
 
     tile_state_t t;
@@ -530,7 +550,8 @@ __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_
         t.lds_s = smem_base + SLAB_BYTES + w * 1024;
     }
     t.nbf = OEK ? (kpad >> 6) : 0;
-    t.n = t.nbf + (int)(K >> 8);
+    t.n = t.nbf + (int)((K + 255) >> 8);
+    t.last_off = (int)(K >> 1) - TKB;
     auto tile_source = [&](int64_t m0, int64_t n0) {
         const int64_t pitch = t.pitch, gpitch = t.gpitch;
         copy_src_t c;
@@ -613,12 +634,10 @@ __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_
 
 size_t gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
-    return align_up((size_t)M * (K / 32), 256) + align_up((size_t)N * (K / 32), 256);
+    const size_t per_row = (size_t)ceil_div(K, 256) * 8;
+    return align_up((size_t)M * per_row, 256) + align_up((size_t)N * per_row, 256);
 }
 
-// Which part of the product the tiled kernel takes: whole 256x256 tiles (rows [0, Mi), columns [0, Ni)), or
-// nothing.  At least three pipeline stages are needed (64 gathered channels or 256 K-elements each, two of
-// them FP4 stages); the bf16 epilogue stores 16 bytes per lane.
 static std::atomic<int> g_kernel_choice{0};
 static std::atomic<int> g_force_walk{-1}; // -1: the order of the tile walk chosen by shape; 0 .. 3: forced
 
@@ -642,28 +661,25 @@ static bool takes_dual_kernel(int64_t M, int64_t N, int64_t K, int kpad, int c_b
     if (forced == 2) return true;
     if (K <= 2048) return true;
     if (K <= 4096) return M * N <= (int64_t)8192 * 11008;
-    const double units = 256.0, t256 = (double)(M / 256) * (double)(N / 256), t128 = (double)(M / 256) * (double)(N / 128);
-    if (t256 < 1.0) return true; // N in [128, 256): only the smaller tile exists
+    if (N < 256) return true; // only the narrower tile fits
+    const double units = 256.0, t256 = (double)ceil_div(M, 256) * ceil_div(N, 256), t128 = (double)ceil_div(M, 256) * ceil_div(N, 128);
     const double waste256 = std::ceil(t256 / units) * units / t256, waste128 = std::ceil(t128 / units) * units / t128;
     return waste256 >= 1.10 && waste128 + 0.08 <= waste256;
 }
 
-void gemm_mx_tiled_part(int64_t M, int64_t N, int64_t K, int kpad, const uint8_t *a_scales, const uint8_t *b_scales,
-                        const void *C, int64_t ldc, int c_bf16, int64_t *Mi, int64_t *Ni)
+// Whether a tiled kernel takes the product.  At least three pipeline stages are needed (64 gathered channels or 256
+// K-elements each, two of them FP4 stages); the bf16 epilogue stores 16 bytes per lane.
+bool gemm_mx_tiled(int64_t M, int64_t N, int64_t K, int kpad, const void *C, int64_t ldc, int c_bf16)
 {
-    const bool fast_c = !c_bf16 || (aligned(C, 16) && ldc % 8 == 0);
-    const bool fast_k = fast_c && K % 256 == 0 && K >= (kpad > 0 ? 512 : 768) && kpad % 64 == 0 &&
-                        aligned(a_scales, 8) && aligned(b_scales, 8);
-    const int64_t tn = fast_k && takes_dual_kernel(M, N, K, kpad, c_bf16) ? 128 : TN;
-    *Mi = fast_k ? M / TM * TM : 0;
-    *Ni = fast_k ? N / tn * tn : 0;
-    if (*Mi == 0 || *Ni == 0 || (*Mi / TM) * (*Ni / tn) >= (1 << 30)) *Mi = *Ni = 0;
+    if (c_bf16 && !(aligned(C, 16) && ldc % 8 == 0 && N % 8 == 0)) return false;
+    if (M < TM || K <= (kpad > 0 ? 256 : 512) || kpad % 64 != 0) return false;
+    return (N >= TN || takes_dual_kernel(M, N, K, kpad, c_bf16)) && ceil_div(M, TM) * ceil_div(N, 128) < (1 << 30);
 }
 
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which)
 {
     uint8_t *a_sm = static_cast<uint8_t *>(workspace);
-    return which == 0 ? a_sm : a_sm + align_up((size_t)M * (K / 32), 256);
+    return which == 0 ? a_sm : a_sm + align_up((size_t)M * ceil_div(K, 256) * 8, 256);
 }
 
 // Once per device: the compute-unit count, and for every instance of the tiled kernel the LDS size (more than a
@@ -702,37 +718,37 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
                      const uint16_t *Bg, int kpad, void *workspace, int sm_ready, hipStream_t st)
 {
     if (M == 0 || N == 0) return ADAHOP_OK;
-    auto generic = [&](int64_t m, int64_t n, const uint8_t *ac, const uint8_t *as, const uint8_t *bc, const uint8_t *bs,
-                       OUT *c, const uint16_t *ag, const uint16_t *bg) {
-        dim3 grid((unsigned)ceil_div(n, 128), (unsigned)ceil_div(m, 128));
-        hipLaunchKernelGGL((k_gemm_mx_generic<false, OUT>), grid, dim3(256), 0, st, m, n, K, ac, as, bc, bs, c, ldc, ag, bg,
-                           kpad);
+    if (!gemm_mx_tiled(M, N, K, kpad, C, ldc, sizeof(OUT) == 2)) {
+        const dim3 grid((unsigned)ceil_div(N, 128), (unsigned)ceil_div(M, 128));
+        hipLaunchKernelGGL((k_gemm_mx_generic<false, OUT>), grid, dim3(256), 0, st, M, N, K, a_codes, a_scales, b_codes,
+                           b_scales, C, ldc, Ag, Bg, kpad);
         return check_launch();
-    };
-    // The tiled kernel takes the whole 256x256 tiles; ragged edges (and shapes it cannot take at all) go to
-    // the bounds-checked kernel.
-    int64_t Mi, Ni;
-    gemm_mx_tiled_part(M, N, K, kpad, a_scales, b_scales, C, ldc, sizeof(OUT) == 2, &Mi, &Ni);
-    if (Mi == 0) return generic(M, N, a_codes, a_scales, b_codes, b_scales, C, Ag, Bg);
+    }
 
     int ncu = 0;
     const int rc0 = configure_gemm_mx(&ncu); // once per device: the compute-unit count and the kernels' LDS size
     if (rc0 != ADAHOP_OK) return rc0;
     ncu = ncu / 8 * 8; // keep a workgroup's tiles on one XCD
     if (ncu < 8) ncu = 8;
-    // scales of the tiled part, stage-major, in the caller's workspace (sm_ready bit 0 / 1: the quantiser of A / B
-    // has already written them there)
+    // stage-major scales in the caller's workspace (sm_ready bit 0 / 1: the quantiser of A / B has already written them)
     uint8_t *a_sm = gemm_mx_scales_sm(workspace, M, K, 0), *b_sm = gemm_mx_scales_sm(workspace, M, K, 1);
-    const int64_t KB8 = K / 256;
-    if (!(sm_ready & 1))
-        hipLaunchKernelGGL(k_stage_major_scales, dim3((unsigned)ceil_div(Mi * KB8, 256)), dim3(256), 0, st,
-                           reinterpret_cast<const uint64_t *>(a_scales), reinterpret_cast<uint64_t *>(a_sm), Mi, KB8);
-    if (!(sm_ready & 2))
-        hipLaunchKernelGGL(k_stage_major_scales, dim3((unsigned)ceil_div(Ni * KB8, 256)), dim3(256), 0, st,
-                           reinterpret_cast<const uint64_t *>(b_scales), reinterpret_cast<uint64_t *>(b_sm), Ni, KB8);
+    const int64_t KB = K / 32;
+    auto reorder = [&](const uint8_t *in, uint8_t *out, int64_t rows) {
+        const dim3 g((unsigned)ceil_div(rows * ceil_div(KB, 8), 256));
+        if (KB % 8 == 0 && aligned(in, 8))
+            hipLaunchKernelGGL(k_stage_major_scales<true>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
+        else
+            hipLaunchKernelGGL(k_stage_major_scales<false>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
+    };
+    if (!(sm_ready & 1)) reorder(a_scales, a_sm, M);
+    if (!(sm_ready & 2)) reorder(b_scales, b_sm, N);
     int rc = check_launch();
     if (rc != ADAHOP_OK) return rc;
-    const int tiles_m = (int)(Mi / TM), tiles_n = (int)(Ni / TN);
+    if constexpr (sizeof(OUT) == 4) {
+        if (takes_dual_kernel(M, N, K, kpad, 0))
+            return launch_gemm_mx_dual(M, N, K, a_codes, a_sm, b_codes, b_sm, reinterpret_cast<float *>(C), ldc, st);
+    }
+    const int tiles_m = (int)ceil_div(M, TM), tiles_n = (int)ceil_div(N, TN);
     const int group_m = 8;
     // one workgroup per compute unit walks the tiles (each workgroup fills a compute unit's LDS and registers)
     const int ntiles = tiles_m * tiles_n;
@@ -751,7 +767,7 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
     constexpr int64_t STAYS = 192ll << 20;
     const bool b_major = tiles_n > tiles_m;
     const int64_t a_in_use = (int64_t)(tiles_m < 64 ? tiles_m : 64) * TM * (K / 2);
-    const bool sweep_a = !b_major && a_in_use > STAYS && Ni * (K / 2) <= STAYS && grid.x == 256 && tiles_m % 8 == 0 &&
+    const bool sweep_a = !b_major && a_in_use > STAYS && N * (K / 2) <= STAYS && grid.x == 256 && tiles_m % 8 == 0 &&
                          tiles_n % 32 == 0;
     int order = b_major ? 2 : sweep_a ? 1 : 0;
     const int forced = g_force_walk.load();
@@ -760,30 +776,13 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
         const bool ok = !(forced & 1) || (grid.x == 256 && (fb ? tiles_n : tiles_m) % 8 == 0 && (fb ? tiles_m : tiles_n) % 32 == 0);
         order = ok ? forced : (forced & 2);
     }
-    if constexpr (sizeof(OUT) == 4) {
-        if (takes_dual_kernel(M, N, K, kpad, 0)) {
-            rc = launch_gemm_mx_dual(Mi, Ni, K, a_codes, a_sm, b_codes, b_sm, reinterpret_cast<float *>(C), ldc, st);
-            goto edges;
-        }
-    }
     if (kpad > 0)
         hipLaunchKernelGGL((k_gemm_mx_tile256<true, OUT>), grid, dim3(256), KERNEL_LDS_BYTES, st, K, a_codes, a_sm, b_codes,
-                           b_sm, Mi, Ni, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
+                           b_sm, M, N, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
     else
         hipLaunchKernelGGL((k_gemm_mx_tile256<false, OUT>), grid, dim3(256), KERNEL_LDS_BYTES, st, K, a_codes, a_sm, b_codes,
-                           b_sm, Mi, Ni, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
-    rc = check_launch();
-edges:
-    if (rc != ADAHOP_OK) return rc;
-    if (Mi < M) { // bottom strip: rows [Mi, M), all columns
-        rc = generic(M - Mi, N, a_codes + Mi * (K / 2), a_scales + Mi * (K / 32), b_codes, b_scales, C + Mi * ldc,
-                     Ag ? Ag + Mi * kpad : nullptr, Bg);
-        if (rc != ADAHOP_OK) return rc;
-    }
-    if (Ni < N) // right strip: rows [0, Mi), columns [Ni, N)
-        rc = generic(Mi, N - Ni, a_codes, a_scales, b_codes + Ni * (K / 2), b_scales + Ni * (K / 32), C + Ni, Ag,
-                     Bg ? Bg + Ni * kpad : nullptr);
-    return rc;
+                           b_sm, M, N, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
+    return check_launch();
 }
 
 } // namespace

@@ -10,7 +10,7 @@
 //     128 fp32 accumulators per lane and set; tile t of a workgroup accumulates into set t % 2;
 //   - while tile t is computed, the 128 stores per lane of tile t - 1 (the other set) are issued one after a
 //     matrix-core instruction each, during the first 8 pipeline stages of tile t (16 stores per stage: one
-//     32 x 32 accumulator tile); the product therefore needs K >= 2048 (8 stages of 256 K-elements);
+//     32 x 32 accumulator tile); the product therefore needs K > 1792 (8 stages of 256 K-elements);
 //   - a stage is 256 K-elements of the 256 A rows and 128 B rows (48 KiB) plus their scales (3 KiB); THREE
 //     stages rotate in LDS, copies run two to three stages ahead of the matrix cores.  A wave waits for its
 //     own copies with a counted wait: vector memory operations of a wave complete in the order issued, so
@@ -59,6 +59,7 @@ struct state_t {
     // copy cursor: the stage being fetched, two to three stages ahead of the one being computed
     const uint8_t *pa, *pb, *ps;
     int left;          // stages of the cursor's tile that are not yet completely issued
+    int last_step;     // bytes from the last stage but one to the last, which ends with the row (TKB if K % 256 == 0)
     uint32_t cbuf;     // byte offset of the cursor's LDS buffer
     src_t nxt;         // the tile after the cursor's
     int n;             // stages per tile
@@ -97,8 +98,9 @@ __device__ __forceinline__ const uint8_t *pick(bool c, const uint8_t *a, const u
 __device__ __forceinline__ void advance(state_t &t)
 {
     const bool wrap = t.left == 1;
-    t.pa = pick(wrap, t.nxt.ga, t.pa + TKB);
-    t.pb = pick(wrap, t.nxt.gb, t.pb + TKB);
+    const int ahead = t.left == 2 ? t.last_step : TKB;
+    t.pa = pick(wrap, t.nxt.ga, t.pa + ahead);
+    t.pb = pick(wrap, t.nxt.gb, t.pb + ahead);
     t.ps = pick(wrap, t.nxt.gs, t.ps + t.s_stride);
     t.left = wrap ? t.n : t.left - 1;
     t.cbuf = next_buf(t.cbuf);
@@ -231,7 +233,8 @@ template <int SET> __device__ __forceinline__ void store_all(const state_t &t, f
 } // namespace dual
 
 // Persistent kernel, one workgroup per compute unit walking the tile sequence with the stride of the grid.
-// M % 256 == 0, N % 128 == 0, K % 256 == 0, K >= 2048 (host side).
+// M >= 256, N >= 128, K % 32 == 0, K > 1792 (host side).  The last tile of a ragged dimension ends with it and overlaps
+// its neighbour, and so does the last stage of a ragged K (see the 256 x 256 kernel).
 __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *__restrict__ a_codes,
                                                       const uint8_t *__restrict__ a_scales_sm,
                                                       const uint8_t *__restrict__ b_codes,
@@ -264,8 +267,8 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
         const int gsz = min(group_m, tiles_m - first_m);
         int tn = (tix % band) / gsz + shift;
         if (tn >= tiles_n) tn -= tiles_n;
-        m0 = (int64_t)(first_m + (tix % band) % gsz) * TM;
-        n0 = (int64_t)tn * TN;
+        m0 = min((int64_t)(first_m + (tix % band) % gsz) * TM, M - TM);
+        n0 = min((int64_t)tn * TN, N - TN);
     };
 
     state_t t;
@@ -286,7 +289,8 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
         t.lds_b = base + A_SLAB + w * 32 * TKB;
         t.lds_s = base + (w == 0 ? SA_OFF : (w == 1 ? SA_OFF + 1024 : SB_OFF)); // waves 2 and 3 both bring B's scales
     }
-    t.n = (int)(K >> 8);
+    t.n = (int)((K + 255) >> 8);
+    t.last_step = (int)(K >> 1) - TKB - (t.n - 2) * TKB;
     auto tile_source = [&](int64_t m0, int64_t n0) {
         const int64_t pitch = t.pitch;
         src_t c;
@@ -373,10 +377,9 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
 
 bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K)
 {
-    return K % 256 == 0 && K >= 256 * dual::STORE_STAGES && M >= dual::TM && N >= dual::TN;
+    return K > 256 * (dual::STORE_STAGES - 1) && M >= dual::TM && N >= dual::TN;
 }
 
-// Launches the kernel on rows [0, Mi), columns [0, Ni) (multiples of 256 and 128); scales stage-major over those rows.
 // Once per device: the compute-unit count and the kernel's LDS size.  Host-side calls, nothing queued.
 int configure_gemm_mx_dual(int *ncu_out)
 {
@@ -399,7 +402,7 @@ int configure_gemm_mx_dual(int *ncu_out)
     return ADAHOP_OK;
 }
 
-int launch_gemm_mx_dual(int64_t Mi, int64_t Ni, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
+int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
                         const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, hipStream_t st)
 {
     int ncu = 0;
@@ -407,11 +410,11 @@ int launch_gemm_mx_dual(int64_t Mi, int64_t Ni, int64_t K, const uint8_t *a_code
     if (rc != ADAHOP_OK) return rc;
     ncu = ncu / 8 * 8;
     if (ncu < 8) ncu = 8;
-    const int tiles_m = (int)(Mi / dual::TM), tiles_n = (int)(Ni / dual::TN);
+    const int tiles_m = (int)ceil_div(M, dual::TM), tiles_n = (int)ceil_div(N, dual::TN);
     const int ntiles = tiles_m * tiles_n;
     const int group_m = tiles_m < 4 ? tiles_m : 4; // the 32 tiles an XCD runs at a time: 4 x 8, a 1024 x 1024 block of C
     const dim3 grid((unsigned)(ntiles < ncu ? ntiles : ncu));
-    hipLaunchKernelGGL(k_gemm_mx_dual, grid, dim3(256), dual::LDS_BYTES, st, K, a_codes, a_sm, b_codes, b_sm, Mi, Ni, C, ldc,
+    hipLaunchKernelGGL(k_gemm_mx_dual, grid, dim3(256), dual::LDS_BYTES, st, K, a_codes, a_sm, b_codes, b_sm, M, N, C, ldc,
                        tiles_m, tiles_n, group_m);
     return check_launch();
 }

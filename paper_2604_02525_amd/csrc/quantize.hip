@@ -11,15 +11,11 @@
 // with saturation at 6; a transformed value that is exactly zero is stored as +0.  The file is
 // compiled with -ffp-contract=off.
 //
-// Two kernels, one per storage order of the operand:
-//   k_quant_kc  K contiguous: a lane owns 8 consecutive K-elements (one 16-byte load); strides
-//               1,2,4 are register butterflies, strides 8..B/2 exchange lanes (DPP / swizzle).
-//               Reads and writes are fully coalesced.  HBM-bound: 2 + 1/2 + 1/32 bytes / element.
-//   k_quant_ks  K strided (outer contiguous): a lane owns two neighbouring columns and one MX block
-//               (32 K-elements) of each, so strides 1..16 are register butterflies with no lane
-//               traffic; strides 32..B/2 pair whole MX blocks held by different waves of the
-//               workgroup and go through LDS.  Loads are coalesced along `outer`.
+// One kernel per storage order of the operand (k_quant_kc16, k_quant_ks16, for every K % 32 == 0) and a variant of the
+// first that also copies the extracted K-channels out; what bounds them and how the work is split stands at each.
 #include "common.h"
+
+#include <type_traits>
 
 namespace adahop {
 
@@ -30,16 +26,6 @@ __device__ __forceinline__ int e8m0_of_amax(float amax)
     int e = (int)((__float_as_uint(amax) >> 23) & 0xffu);
     int s = e - 2;
     return s < 0 ? 0 : s; // zero and subnormal amax -> 0
-}
-
-// E2M1 code of v / 2^(s-127): sign in bit 3, magnitude index 0..7, RNE, saturating.
-__device__ __forceinline__ uint32_t e2m1_code(float v, int s)
-{
-    float q = ldexpf(v, 127 - s);
-    float a = fabsf(q);
-    uint32_t m = (uint32_t)(a > 0.25f) + (uint32_t)(a >= 0.75f) + (uint32_t)(a > 1.25f) + (uint32_t)(a >= 1.75f) +
-                 (uint32_t)(a > 2.5f) + (uint32_t)(a >= 3.5f) + (uint32_t)(a > 5.0f);
-    return m | ((__float_as_uint(v) >> 28) & 8u);
 }
 
 // ---- optional stochastic rounding of the elements (the paper cites it as prior work for unbiased
@@ -68,7 +54,7 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, sr_key_
 }
 
 // E2M1 code of v / 2^(s-127) rounded stochastically with the 16-bit draw r16: up to the next magnitude
-// iff r16 / 65536 < (|q| - lo) / (hi - lo); |q| >= 6 saturates; sign as in e2m1_code.
+// iff r16 / 65536 < (|q| - lo) / (hi - lo); |q| >= 6 saturates; the sign bit of v is kept.
 __device__ __forceinline__ uint32_t e2m1_code_sr(float v, int s, uint32_t r16)
 {
     const float a = fabsf(ldexpf(v, 127 - s));
@@ -99,244 +85,9 @@ template <> __device__ __forceinline__ float hadamard_norm<64>() { return 0.125f
 template <> __device__ __forceinline__ float hadamard_norm<128>() { return 0x1.6a09e6p-4f; }
 template <> __device__ __forceinline__ float hadamard_norm<256>() { return 0.0625f; }
 
-// Value held by lane (lane ^ XM); XM in {1, 2, 4, 8, 16}.
-template <int XM> __device__ __forceinline__ float lane_xor(float v)
-{
-    int i = __float_as_int(v);
-    if constexpr (XM == 1)
-        i = __builtin_amdgcn_mov_dpp(i, 0xB1, 0xf, 0xf, true); // quad_perm [1,0,3,2]
-    else if constexpr (XM == 2)
-        i = __builtin_amdgcn_mov_dpp(i, 0x4E, 0xf, 0xf, true); // quad_perm [2,3,0,1]
-    else
-        i = __builtin_amdgcn_ds_swizzle(i, (XM << 10) | 0x1f); // bit mode: and 0x1f, or 0, xor XM
-    return __int_as_float(i);
-}
-
-template <int XM, int B> __device__ __forceinline__ void lane_stage(float (&v)[8], int lane)
-{
-    if constexpr (8 * XM < B) {
-        const bool upper = (lane & XM) != 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float p = lane_xor<XM>(v[i]);
-            v[i] = upper ? p - v[i] : v[i] + p;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// K-contiguous operand.  One lane = 8 consecutive K-elements; 4 lanes = one MX block; B/8 lanes =
-// one transform block.  FLAT = 0: blockIdx.x is the row, blockIdx.y*256+tid the 8-element chunk.
-// FLAT = 1 (short rows): chunks of all rows are numbered consecutively.
-// ------------------------------------------------------------------------------------------------
-template <int B, int FLAT, bool SR>
-__global__ __launch_bounds__(256) void k_quant_kc(const uint16_t *__restrict__ x, int64_t outer, int64_t K,
-                                                  int64_t ld, const uint8_t *__restrict__ zero_outer,
-                                                  const uint8_t *__restrict__ zero_k,
-                                                  uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
-                                                  sr_key_t key)
-{
-    const uint32_t cpr = (uint32_t)(K >> 3);
-    int64_t row;
-    uint32_t chunk;
-    bool active;
-    if constexpr (FLAT) {
-        const uint32_t c = blockIdx.x * 256u + threadIdx.x;
-        const uint32_t r = c / cpr;
-        row = r;
-        chunk = c - r * cpr;
-        active = row < outer;
-    } else {
-        row = blockIdx.x;
-        chunk = blockIdx.y * 256u + threadIdx.x;
-        active = chunk < cpr;
-    }
-    const int lane = threadIdx.x & 63;
-    const int64_t kk = (int64_t)chunk * 8;
-
-    uint4 raw = make_uint4(0, 0, 0, 0);
-    if (active) {
-        raw = load_once16(x + row * ld + kk);
-        if (zero_outer && zero_outer[row]) raw = make_uint4(0, 0, 0, 0);
-    }
-    float v[8] = {bf16_lo(raw.x), bf16_hi(raw.x), bf16_lo(raw.y), bf16_hi(raw.y),
-                  bf16_lo(raw.z), bf16_hi(raw.z), bf16_lo(raw.w), bf16_hi(raw.w)};
-    if (zero_k && active) {
-        const uint64_t zm = *reinterpret_cast<const uint64_t *>(zero_k + kk);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if ((zm >> (8 * i)) & 0xffu) v[i] = 0.0f;
-    }
-
-    if constexpr (B > 0) {
-#pragma unroll
-        for (int h = 1; h < 8; h *= 2)
-#pragma unroll
-            for (int i = 0; i < 8; i += 2 * h)
-#pragma unroll
-                for (int j = i; j < i + h; ++j) {
-                    float a = v[j], b = v[j + h];
-                    v[j] = a + b;
-                    v[j + h] = a - b;
-                }
-        lane_stage<1, B>(v, lane);
-        lane_stage<2, B>(v, lane);
-        lane_stage<4, B>(v, lane);
-        lane_stage<8, B>(v, lane);
-        lane_stage<16, B>(v, lane);
-        const float c = hadamard_norm<B>();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = __builtin_fmaf(v[i], c, 0.0f); // exact zeros become +0
-    }
-
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
-    amax = fmaxf(amax, lane_xor<1>(amax));
-    amax = fmaxf(amax, lane_xor<2>(amax));
-    const int s = e8m0_of_amax(amax);
-
-    uint32_t packed = 0;
-    if constexpr (SR) {
-        packed = pack8_sr(v, s, key, row, kk);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) packed |= e2m1_code(v[i], s) << (4 * i);
-    }
-
-    if (active) {
-        *reinterpret_cast<uint32_t *>(codes + row * (K >> 1) + (kk >> 1)) = packed;
-        if ((lane & 3) == 0) scales[row * (K >> 5) + (kk >> 5)] = (uint8_t)s;
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// K-strided operand: element (o, kk) at x[kk*ld + o].  Workgroup = NW waves; wave w owns MX block
-// (blockIdx.y*NW + w) of 128 columns (two per lane).
-// ------------------------------------------------------------------------------------------------
-template <int B> struct ks_cfg {
-    static constexpr int NCH = (B <= 32) ? 1 : B / 32; // MX blocks per transform block
-    static constexpr int NW = (NCH > 4) ? NCH : 4;     // waves per workgroup
-};
-
-template <int B, bool SR>
-__global__ __launch_bounds__(ks_cfg<B>::NW * 64) void k_quant_ks(const uint16_t *__restrict__ x, int64_t outer,
-                                                                  int64_t K, int64_t ld,
-                                                                  const uint8_t *__restrict__ zero_outer,
-                                                                  const uint8_t *__restrict__ zero_k,
-                                                                  uint8_t *__restrict__ codes,
-                                                                  uint8_t *__restrict__ scales, sr_key_t key)
-{
-    constexpr int NCH = ks_cfg<B>::NCH;
-    constexpr int NW = ks_cfg<B>::NW;
-    extern __shared__ float2 xchg[]; // [NW][32][64], only touched when NCH > 1
-
-    const int w = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
-    const int64_t o = ((int64_t)blockIdx.x * 64 + lane) * 2;
-    const int64_t blk = (int64_t)blockIdx.y * NW + w;
-    const bool valid = (blk < (K >> 5)) && (o < outer);
-    const bool valid1 = valid && (o + 1 < outer);
-
-    float2 v[32];
-    {
-        bool z0 = false, z1 = false;
-        if (zero_outer && valid) {
-            z0 = zero_outer[o] != 0;
-            z1 = valid1 ? (zero_outer[o + 1] != 0) : true;
-        }
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            uint32_t pair = 0;
-            if (valid) {
-                const int64_t kk = blk * 32 + i;
-                pair = load_once4(x + kk * ld + o);
-                if (zero_k && zero_k[kk]) pair = 0;
-            }
-            v[i].x = z0 ? 0.0f : bf16_lo(pair);
-            v[i].y = (z1 || !valid1) ? 0.0f : bf16_hi(pair);
-        }
-    }
-
-    if constexpr (B > 0) {
-#pragma unroll
-        for (int h = 1; h < 32; h *= 2)
-#pragma unroll
-            for (int i = 0; i < 32; i += 2 * h)
-#pragma unroll
-                for (int j = i; j < i + h; ++j) {
-                    float2 a = v[j], b = v[j + h];
-                    v[j].x = a.x + b.x;
-                    v[j].y = a.y + b.y;
-                    v[j + h].x = a.x - b.x;
-                    v[j + h].y = a.y - b.y;
-                }
-        if constexpr (NCH > 1) {
-            const int c = w % NCH; // index of this MX block inside its transform block
-#pragma unroll
-            for (int d = 1; d < NCH; d *= 2) {
-#pragma unroll
-                for (int i = 0; i < 32; ++i) xchg[(w * 32 + i) * 64 + lane] = v[i];
-                __syncthreads();
-                const int pw = w ^ d;
-                const bool upper = (c & d) != 0;
-#pragma unroll
-                for (int i = 0; i < 32; ++i) {
-                    const float2 p = xchg[(pw * 32 + i) * 64 + lane];
-                    v[i].x = upper ? p.x - v[i].x : v[i].x + p.x;
-                    v[i].y = upper ? p.y - v[i].y : v[i].y + p.y;
-                }
-                __syncthreads();
-            }
-        }
-        const float cn = hadamard_norm<(B >= 32 ? B : 32)>();
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            v[i].x = __builtin_fmaf(v[i].x, cn, 0.0f); // exact zeros become +0
-            v[i].y = __builtin_fmaf(v[i].y, cn, 0.0f);
-        }
-    }
-
-    float ax = 0.0f, ay = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        ax = fmaxf(ax, fabsf(v[i].x));
-        ay = fmaxf(ay, fabsf(v[i].y));
-    }
-    const int sx = e8m0_of_amax(ax), sy = e8m0_of_amax(ay);
-    uint32_t px[4] = {0, 0, 0, 0}, py[4] = {0, 0, 0, 0};
-    if constexpr (SR) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float wx[8], wy[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                wx[i] = v[8 * g + i].x;
-                wy[i] = v[8 * g + i].y;
-            }
-            px[g] = pack8_sr(wx, sx, key, o, blk * 32 + 8 * g);
-            py[g] = pack8_sr(wy, sy, key, o + 1, blk * 32 + 8 * g);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            px[i >> 3] |= e2m1_code(v[i].x, sx) << (4 * (i & 7));
-            py[i >> 3] |= e2m1_code(v[i].y, sy) << (4 * (i & 7));
-        }
-    }
-    if (valid) {
-        *reinterpret_cast<uint4 *>(codes + o * (K >> 1) + blk * 16) = make_uint4(px[0], px[1], px[2], px[3]);
-        scales[o * (K >> 5) + blk] = (uint8_t)sx;
-    }
-    if (valid1) {
-        *reinterpret_cast<uint4 *>(codes + (o + 1) * (K >> 1) + blk * 16) = make_uint4(py[0], py[1], py[2], py[3]);
-        scales[(o + 1) * (K >> 5) + blk] = (uint8_t)sy;
-    }
-}
-
 // ================================================================================================
-// Fast kernels for K % 256 == 0.  Both quantisers are bound by vector-ALU work long before HBM unless
-// the per-element instruction count is kept near 12, so these kernels
+// Both quantisers are bound by vector-ALU work long before HBM unless the per-element instruction count is kept
+// near 12, so these kernels
 //   - let the hardware convert: v_cvt_scalef32_pk_fp4_f32 rounds two fp32 values / 2^(s-127) to E2M1
 //     (nearest even, saturating, first value in the low nibble) in one instruction;
 //   - do every cross-lane butterfly as ONE fused multiply-add whose first operand comes through DPP:
@@ -344,6 +95,11 @@ __global__ __launch_bounds__(ks_cfg<B>::NW * 64) void k_quant_ks(const uint16_t 
 //     yields L+U on the lower lane and -(L-U) on the upper lane; the stray sign is not fixed up but
 //     tracked (it only depends on the lane) and folded into the final 1/sqrt(B) multiply.  Negation
 //     commutes with rounding, so the stored bits are exactly those of the plain butterflies.
+//
+// Rows are cut into units of 256 K-elements; K need only be a multiple of 32: the lanes past the end of a row's last,
+// shorter unit hold zeros and store nothing (no transform block reaches across that end, because K is a multiple of
+// the block).  On [5000][3040] bf16 that takes 13.7 us, against 17.6 us for a kernel of its own with eight elements per lane
+// and the conversion in compares, and on K-strided [2016][11008] 17.2 against 26.2 us.
 //
 // Work split: 16 lanes (one DPP row) own 256 consecutive K-elements of one row; a lane holds two
 // groups of 8 consecutive elements, 128 apart (chunk c of each half).  Strides 1, 2, 4 are register
@@ -524,35 +280,51 @@ __device__ __forceinline__ uint4 clear_extracted(uint4 r, uint4 pos)
     return make_uint4(r.x & keep(pos.x), r.y & keep(pos.y), r.z & keep(pos.z), r.w & keep(pos.w));
 }
 
-// k0: start of the lane group's 256 K-elements (a multiple of 256).  sm: optional second copy of the scales in
-// the order the tiled GEMM kernel reads them, [K/256][sm.rows][8].
+// Slot of MX block j (0 .. 7) of unit u in the stage-major copy of the scales: the last unit of a row holds
+// t = K / 32 - 8 u blocks if K is no multiple of 256, and the tiled GEMM kernels read that stage so that it ends with the
+// row (see there): its blocks then are the last t of 8, and the slots before them, which stand for blocks that the
+// stage before has already used, hold scale 0.  Rotating by 8 - t puts the zeros of the missing blocks there.
+__device__ __forceinline__ int tail_rotation(int64_t K, int64_t k0)
+{
+    const int64_t left = (K - k0) >> 5;
+    return left < 8 ? 8 - (int)left : 0;
+}
+
+// k0: start of the lane group's 256 K-elements (a multiple of 256); in0 / in1: the lane's chunk of the first / second
+// half lies inside the row.  sm: optional second copy of the scales in the order the tiled GEMM kernels read them,
+// [ceil(K/256)][sm.rows][8].
+template <bool TAIL>
 __device__ __forceinline__ void store_codes_scales(uint8_t *codes, uint8_t *scales, int64_t row, int64_t K, int64_t k0,
-                                                   int chunk, uint32_t c0, uint32_t c1, int s0, int s1, scales_sm_t sm)
+                                                   int chunk, bool in0, bool in1, uint32_t c0, uint32_t c1, int s0, int s1,
+                                                   scales_sm_t sm)
 {
     uint8_t *crow = codes + row * (K >> 1) + ((k0 + chunk * 8) >> 1);
-    *reinterpret_cast<uint32_t *>(crow) = c0;
-    *reinterpret_cast<uint32_t *>(crow + 64) = c1;
+    if (!TAIL || in0) *reinterpret_cast<uint32_t *>(crow) = c0;
+    if (!TAIL || in1) *reinterpret_cast<uint32_t *>(crow + 64) = c1;
     if ((chunk & 3) == 0) {
         uint8_t *srow = scales + row * (K >> 5) + ((k0 + chunk * 8) >> 5);
-        srow[0] = (uint8_t)s0;
-        srow[4] = (uint8_t)s1;
-        if (sm.out && row < sm.rows) {
-            uint8_t *q = sm.out + ((k0 >> 8) * sm.rows + row) * 8 + (chunk >> 2);
-            q[0] = (uint8_t)s0;
-            q[4] = (uint8_t)s1;
+        if (!TAIL || in0) srow[0] = (uint8_t)s0;
+        if (!TAIL || in1) srow[4] = (uint8_t)s1;
+        if (sm.out) {
+            uint8_t *q = sm.out + ((k0 >> 8) * sm.rows + row) * 8;
+            const int j = (chunk >> 2) + (TAIL ? tail_rotation(K, k0) : 0);
+            q[j & 7] = (uint8_t)s0; // (0 where the block is missing)
+            q[(j + 4) & 7] = (uint8_t)s1;
         }
     }
 }
 
-// K-contiguous operand: 16 lanes per 256 K-elements of a row.  FLAT as in k_quant_kc.
-template <int B, int FLAT, bool SR>
+// K-contiguous operand: 16 lanes per 256 K-elements of a row.  FLAT = 0: blockIdx.x is the row, blockIdx.y and the
+// thread its units; FLAT = 1 (short rows): the units of all rows are numbered consecutively.  TAIL: K % 256 != 0 (an
+// instance of its own, because the conditions of a shorter last unit cost the others 2 %).
+template <int B, int FLAT, bool SR, bool TAIL>
 __global__ __launch_bounds__(256) void k_quant_kc16(const uint16_t *__restrict__ x, int64_t outer, int64_t K,
                                                     int64_t ld, const uint8_t *__restrict__ zero_outer,
                                                     const uint8_t *__restrict__ zero_k,
                                                     uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
                                                     sr_key_t key, scales_sm_t sm)
 {
-    const uint32_t upr = (uint32_t)(K >> 8); // 256-element units per row
+    const uint32_t upr = (uint32_t)((K + 255) >> 8); // 256-element units per row
     int64_t row;
     uint32_t unit;
     bool active;
@@ -569,12 +341,13 @@ __global__ __launch_bounds__(256) void k_quant_kc16(const uint16_t *__restrict__
     }
     const lane_plan_t plan = make_plan<B>(threadIdx.x & 63);
     const int64_t k0 = (int64_t)unit * 256, kk = k0 + plan.chunk * 8;
+    const bool in0 = active && (!TAIL || kk < K), in1 = active && (!TAIL || kk + 128 < K);
 
     uint4 r0 = make_uint4(0, 0, 0, 0), r1 = make_uint4(0, 0, 0, 0);
     if (active) { // the row's mask byte travels with the data (1 % of the rows are read for nothing) instead of ahead of it
         const uint16_t *src = x + row * ld + kk;
-        r0 = load_once16(src);
-        r1 = load_once16(src + 128);
+        if (!TAIL || in0) r0 = load_once16(src);
+        if (!TAIL || in1) r1 = load_once16(src + 128);
         if (zero_outer && zero_outer[row]) r0 = r1 = make_uint4(0, 0, 0, 0);
     }
     float w0[8] = {bf16_lo(r0.x), bf16_hi(r0.x), bf16_lo(r0.y), bf16_hi(r0.y),
@@ -582,15 +355,16 @@ __global__ __launch_bounds__(256) void k_quant_kc16(const uint16_t *__restrict__
     float w1[8] = {bf16_lo(r1.x), bf16_hi(r1.x), bf16_lo(r1.y), bf16_hi(r1.y),
                    bf16_lo(r1.z), bf16_hi(r1.z), bf16_lo(r1.w), bf16_hi(r1.w)};
     if (zero_k && active) {
-        const uint64_t z0 = *reinterpret_cast<const uint64_t *>(zero_k + kk);
-        const uint64_t z1 = *reinterpret_cast<const uint64_t *>(zero_k + kk + 128);
+        uint64_t z0 = 0, z1 = 0;
+        if (!TAIL || in0) z0 = *reinterpret_cast<const uint64_t *>(zero_k + kk);
+        if (!TAIL || in1) z1 = *reinterpret_cast<const uint64_t *>(zero_k + kk + 128);
         apply_k_mask(w0, z0);
         apply_k_mask(w1, z1);
     }
     uint32_t c0, c1;
     int s0, s1;
     transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, key, row, kk, kk + 128);
-    if (active) store_codes_scales(codes, scales, row, K, k0, plan.chunk, c0, c1, s0, s1, sm);
+    if (active) store_codes_scales<TAIL>(codes, scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, sm);
 }
 
 // The same with the extracted K-channels copied out on the way (Eq. 7 with S a set of K-channels).  One workgroup
@@ -641,7 +415,7 @@ __global__ __launch_bounds__(256) void k_quant_kc16_gather(const uint16_t *__res
         uint32_t c0, c1;
         int s0, s1;
         transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, key, row, kk, kk + 128);
-        if (active) store_codes_scales(codes, scales, row, K, k0, plan.chunk, c0, c1, s0, s1, sm);
+        if (active) store_codes_scales<false>(codes, scales, row, K, k0, plan.chunk, true, true, c0, c1, s0, s1, sm);
     }
     __syncthreads();
     uint16_t *dst = gk.out + row * gk.kpad;
@@ -650,8 +424,8 @@ __global__ __launch_bounds__(256) void k_quant_kc16_gather(const uint16_t *__res
 }
 
 // ------------------------------------------------------------------------------------------------
-// K-strided operand (element (o, kk) at x[kk*ld + o]), K % 256 == 0.  A workgroup takes a tile of 256 K-rows x 64
-// columns: coalesced 16-byte loads (8 columns of one K-row per lane) go to LDS as they are, and the LDS
+// K-strided operand (element (o, kk) at x[kk*ld + o]).  A workgroup takes a tile of 256 K-rows (fewer in the last
+// one, filled up with zeros) x 64 columns: coalesced 16-byte loads (8 columns of one K-row per lane) go to LDS as they are, and the LDS
 // transposing read of gfx950 (ds_read_b64_tr_b16) hands every lane 4 consecutive K-elements of one column per
 // instruction -- the transposition costs a quarter of an LDS instruction per element.
 //
@@ -770,11 +544,11 @@ __global__ __launch_bounds__(256) void k_quant_ks16(const uint16_t *__restrict__
         // K-mask: one byte of the tile's 256 per thread, loaded ahead of the data and handed round through LDS (eight
         // byte loads per lane, one for each of its K-rows, made the masked call 15 % slower than the plain one)
         uint8_t my_kz = 0;
-        if (zero_k) my_kz = zero_k[k0 + tid];
+        if (zero_k && k0 + tid < K) my_kz = zero_k[k0 + tid];
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
+        for (int it = 0; it < 8; ++it) { // (a pass is one MX block of K: inside the operand or not as a whole)
             const int64_t kk = k0 + it * 32 + rw;
-            v[it] = ok ? load_once16(x + kk * ld + oc) : make_uint4(0, 0, 0, 0);
+            v[it] = ok && k0 + it * 32 < K ? load_once16(x + kk * ld + oc) : make_uint4(0, 0, 0, 0);
         }
         uint32_t zk = 0; // bit it: the lane's K-row of pass it is masked out
         if (zero_k) {    // (uniform: a kernel argument)
@@ -876,8 +650,8 @@ __global__ __launch_bounds__(256) void k_quant_ks16(const uint16_t *__restrict__
     }
     if (active) {
         uint8_t *crow = codes + o * (K >> 1) + ((k0 + 64 * m) >> 1);
-        *reinterpret_cast<uint4 *>(crow) = make_uint4(c[0], c[1], c[2], c[3]);
-        *reinterpret_cast<uint4 *>(crow + 16) = make_uint4(c[4], c[5], c[6], c[7]);
+        if (k0 + 64 * m < K) *reinterpret_cast<uint4 *>(crow) = make_uint4(c[0], c[1], c[2], c[3]);
+        if (k0 + 64 * m + 32 < K) *reinterpret_cast<uint4 *>(crow + 16) = make_uint4(c[4], c[5], c[6], c[7]);
     }
     // The column's 8 scale bytes of this tile sit in the four lanes m = 0 .. 3 of the column, which are 4 apart in
     // the row of 16 lanes: the lane m = 0 collects them (two DPP shifts) and stores them at once.  Byte stores, four
@@ -890,17 +664,17 @@ __global__ __launch_bounds__(256) void k_quant_ks16(const uint16_t *__restrict__
     const uint32_t upper = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)pair, 0x108 /* row_shl:8 */, 0xf, 0xf, true);
     if (active && m == 0) {
         uint8_t *srow = scales + o * (K >> 5) + (k0 >> 5);
-        if ((reinterpret_cast<uintptr_t>(srow) & 7) == 0) {
+        const int rot = tail_rotation(K, k0);
+        if (rot == 0 && (reinterpret_cast<uintptr_t>(srow) & 7) == 0) {
             *reinterpret_cast<uint2 *>(srow) = make_uint2(pair, upper);
-        } else { // the canonical array has no alignment rule
+        } else { // the canonical array has no alignment rule, and the last tile may hold fewer blocks
+            const uint64_t all = (uint64_t)upper << 32 | pair;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                srow[i] = (uint8_t)(pair >> (8 * i));
-                srow[4 + i] = (uint8_t)(upper >> (8 * i));
-            }
+            for (int i = 0; i < 8; ++i)
+                if (i < 8 - rot) srow[i] = (uint8_t)(all >> (8 * i));
         }
-        if (sm.out && o < sm.rows)
-            *reinterpret_cast<uint2 *>(sm.out + ((k0 >> 8) * sm.rows + o) * 8) = make_uint2(pair, upper);
+        if (sm.out)
+            *reinterpret_cast<uint64_t *>(sm.out + ((k0 >> 8) * sm.rows + o) * 8) = ((uint64_t)upper << 32 | pair) << (8 * rot);
     }
 }
 
@@ -909,73 +683,32 @@ int launch_kc(const adahop_operand_t &x, const uint8_t *zo, const uint8_t *zk, u
               sr_key_t key, scales_sm_t sm, k_gather_t gk, hipStream_t st)
 {
     const uint16_t *d = static_cast<const uint16_t *>(x.data);
-    if (x.K % 256 == 0) {
-        const int64_t tpr = x.K / 16; // threads per row
-        if (gk.out) {
-            hipLaunchKernelGGL((k_quant_kc16_gather<B, SR>), dim3((unsigned)x.outer), dim3(256), 0, st, d, x.K, x.ld, codes,
-                               scales, key, sm, gk);
-            return check_launch();
-        }
-        if (tpr >= 128) {
-            dim3 grid((unsigned)x.outer, (unsigned)ceil_div(tpr, 256));
-            hipLaunchKernelGGL((k_quant_kc16<B, 0, SR>), grid, dim3(256), 0, st, d, x.outer, x.K, x.ld, zo, zk, codes,
-                               scales, key, sm);
-        } else {
-            dim3 grid((unsigned)ceil_div(x.outer * tpr, 256));
-            hipLaunchKernelGGL((k_quant_kc16<B, 1, SR>), grid, dim3(256), 0, st, d, x.outer, x.K, x.ld, zo, zk, codes,
-                               scales, key, sm);
-        }
+    if (gk.out) {
+        hipLaunchKernelGGL((k_quant_kc16_gather<B, SR>), dim3((unsigned)x.outer), dim3(256), 0, st, d, x.K, x.ld, codes,
+                           scales, key, sm, gk);
         return check_launch();
     }
-    const int64_t cpr = x.K / 8;
-    if (cpr >= 128) {
-        dim3 grid((unsigned)x.outer, (unsigned)ceil_div(cpr, 256));
-        hipLaunchKernelGGL((k_quant_kc<B, 0, SR>), grid, dim3(256), 0, st, d, x.outer, x.K, x.ld, zo, zk, codes, scales,
-                           key);
-    } else {
-        dim3 grid((unsigned)ceil_div(x.outer * cpr, 256));
-        hipLaunchKernelGGL((k_quant_kc<B, 1, SR>), grid, dim3(256), 0, st, d, x.outer, x.K, x.ld, zo, zk, codes, scales,
-                           key);
-    }
-    return check_launch();
-}
-
-template <int B> constexpr size_t ks_lds_bytes()
-{
-    return ks_cfg<B>::NCH > 1 ? (size_t)ks_cfg<B>::NW * 32 * 64 * sizeof(float2) : 0;
-}
-
-template <int B> int allow_ks_lds()
-{
-    if (ks_lds_bytes<B>() <= 48 * 1024) return ADAHOP_OK;
-    int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_quant_ks<B, false>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_lds_bytes<B>()));
-    if (rc != ADAHOP_OK) return rc;
-    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_quant_ks<B, true>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)ks_lds_bytes<B>()));
+    const int64_t tpr = ceil_div(x.K, 256) * 16; // threads per row
+    auto launch = [&](auto flat, auto tail, dim3 grid) {
+        hipLaunchKernelGGL((k_quant_kc16<B, decltype(flat)::value, SR, decltype(tail)::value>), grid, dim3(256), 0, st, d,
+                           x.outer, x.K, x.ld, zo, zk, codes, scales, key, sm);
+        return check_launch();
+    };
+    auto pick_tail = [&](auto flat, dim3 grid) {
+        return x.K % 256 ? launch(flat, std::true_type(), grid) : launch(flat, std::false_type(), grid);
+    };
+    if (tpr >= 128) return pick_tail(std::integral_constant<int, 0>(), dim3((unsigned)x.outer, (unsigned)ceil_div(tpr, 256)));
+    return pick_tail(std::integral_constant<int, 1>(), dim3((unsigned)ceil_div(x.outer * tpr, 256)));
 }
 
 template <int B, bool SR>
 int launch_ks(const adahop_operand_t &x, const uint8_t *zo, const uint8_t *zk, uint8_t *codes, uint8_t *scales,
               sr_key_t key, scales_sm_t sm, hipStream_t st)
 {
-    if (iht_quantize_writes_scales_sm(x)) {
-        dim3 grid((unsigned)ceil_div(x.outer, KS_COLS), (unsigned)(x.K / 256));
-        const unsigned group = grid.x > KS_GROUP_FROM ? KS_GROUP : 0u;
-        hipLaunchKernelGGL((k_quant_ks16<B, SR>), grid, dim3(256), 0, st, static_cast<const uint16_t *>(x.data), x.outer,
-                           x.K, x.ld, zo, zk, codes, scales, key, sm, group);
-        return check_launch();
-    }
-    constexpr int NW = ks_cfg<B>::NW;
-    constexpr int NCH = ks_cfg<B>::NCH;
-    const size_t lds = ks_lds_bytes<B>();
-    if (lds > 48 * 1024) { // more LDS than a launch may ask for by default: allowed once per device
-        const int rc = configure_quantizers();
-        if (rc != ADAHOP_OK) return rc;
-    }
-    dim3 grid((unsigned)ceil_div(x.outer, 128), (unsigned)ceil_div(x.K / 32, NW));
-    hipLaunchKernelGGL((k_quant_ks<B, SR>), grid, dim3(NW * 64), lds, st, static_cast<const uint16_t *>(x.data),
-                       x.outer, x.K, x.ld, zo, zk, codes, scales, key);
+    dim3 grid((unsigned)ceil_div(x.outer, KS_COLS), (unsigned)ceil_div(x.K, 256));
+    const unsigned group = grid.x > KS_GROUP_FROM ? KS_GROUP : 0u;
+    hipLaunchKernelGGL((k_quant_ks16<B, SR>), grid, dim3(256), 0, st, static_cast<const uint16_t *>(x.data), x.outer, x.K,
+                       x.ld, zo, zk, codes, scales, key, sm, group);
     return check_launch();
 }
 
@@ -1001,28 +734,8 @@ int dispatch_block(const adahop_operand_t &x, int b, const uint8_t *zo, const ui
 
 } // namespace
 
-// The instances of the general K-strided quantiser that need more LDS than the default, once per device (host-side
-// calls, nothing queued).
-int configure_quantizers()
-{
-    static device_once_t once;
-    int dev = 0;
-    int rc = check_hip(hipGetDevice(&dev));
-    if (rc != ADAHOP_OK || !once.need(dev)) return rc;
-    if ((rc = allow_ks_lds<0>()) != ADAHOP_OK || (rc = allow_ks_lds<32>()) != ADAHOP_OK || (rc = allow_ks_lds<64>()) != ADAHOP_OK ||
-        (rc = allow_ks_lds<128>()) != ADAHOP_OK || (rc = allow_ks_lds<256>()) != ADAHOP_OK)
-        return rc;
-    once.mark(dev);
-    return ADAHOP_OK;
-}
-
-// The kernels for K % 256 == 0 (K / 256 is a grid dimension of the K-strided one) are the ones that also write
-// the stage-major copy of the scales.
-bool iht_quantize_writes_scales_sm(const adahop_operand_t &x) { return x.K % 256 == 0 && x.K / 256 <= 65535; }
-
 // sr_seed: NULL for round-to-nearest-even, else the seed of the stochastic rounding of the elements.
-// sm: NULL, or where a stage-major copy of the scales goes; honoured by the kernels for K % 256 == 0 only,
-// which is also the only case in which the tiled GEMM kernel asks for it.
+// sm: NULL, or where a stage-major copy of the scales goes.
 // A whole row per workgroup pays from 4096 K-elements on (one pass of all its lanes); the copy is staged in LDS.
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad)
 {
@@ -1036,7 +749,7 @@ int launch_iht_quantize(const adahop_operand_t &x, int b, const uint8_t *zo, con
                         const k_gather_t *gather)
 {
     if (x.outer == 0 || x.K == 0) return ADAHOP_OK;
-    const scales_sm_t smv = sm && iht_quantize_writes_scales_sm(x) ? *sm : scales_sm_t{nullptr, 0};
+    const scales_sm_t smv = sm ? *sm : scales_sm_t{nullptr, 0};
     const k_gather_t gk = gather && gather->out && zk && !zo && iht_quantize_gathers_k(x, gather->kpad)
                               ? *gather
                               : k_gather_t{nullptr, nullptr, 0, 0};

@@ -9,7 +9,8 @@ import numpy as np
 import pytest
 
 from oracle import reference as orc
-from test_gpu_parity import ah, host, rel_fro, say  # noqa: F401  (ah is a fixture)
+from paper_2604_02525_amd import inputs
+from test_gpu_parity import ah, check_c, host, rel_fro, say, stored  # noqa: F401  (ah is a fixture)
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -87,3 +88,49 @@ def test_tiled_kernels_single_nonzero_positions(ah, force, kernel):
         ref = orc.mx_gemm(a_codes, a_scales, b_codes, b_scales)
         assert np.count_nonzero(ref) == 1
         assert np.array_equal(C.astype(np.float64), ref)
+
+
+RAGGED = [(257, 256, 544), (511, 383, 1056), (300, 130, 1824), (1000, 650, 2016), (769, 513, 2080), (2305, 1100, 2912)]
+
+
+@pytest.mark.parametrize("kernel", [TILE256, DUAL])
+@pytest.mark.parametrize("shape", RAGGED)
+def test_ragged_shapes_in_whole_tiles(ah, force, kernel, shape):
+    """Rows, columns and K one past, one short of and between whole tiles and stages: the last tile of a dimension and the
+    last stage of K overlap the ones before them (scales re-ordered by the pre-pass).  The allowance is the one above."""
+    M, N, K = shape
+    rng = np.random.default_rng(5 * M + 3 * N + K)
+    a_codes = rng.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
+    b_codes = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    a_scales = rng.integers(117, 137, size=(M, K // 32), dtype=np.uint8)
+    b_scales = rng.integers(100, 120, size=(N, K // 32), dtype=np.uint8)
+    say("ragged", kernel, shape)
+    force(kernel)
+    got = host(ah.adahop_gemm_mx(*(torch.from_numpy(t).cuda() for t in (a_codes, a_scales, b_codes, b_scales)))).astype(np.float64)
+    ref = orc.mx_gemm(a_codes, a_scales, b_codes, b_scales)
+    bar = 2.0 ** -20 * np.outer(dequant_norms(a_codes, a_scales), dequant_norms(b_codes, b_scales))
+    assert rel_fro(got, ref) < 1e-5
+    assert float((np.abs(got - ref) / bar).max()) <= 1.0
+
+
+@pytest.mark.parametrize("layouts", [(True, True), (True, False), (False, False)])
+@pytest.mark.parametrize("M,N,K", [(301, 270, 1120), (520, 264, 800), (257, 512, 2272)])
+@pytest.mark.parametrize("strategy,k", [(inputs.IHT, 0), (inputs.IHT_OE_K, 40), (inputs.IHT_OE_ROW, 5)])
+def test_ragged_whole_path(ah, layouts, M, N, K, strategy, k):
+    """The same with the stage-major scales written by the quantisers of both layouts, and gathered K-channels in front."""
+    A = inputs.Operand(inputs.matrix(M, K, 1.0, 70, col_outliers=(5, 50.0, 50.0)), True)
+    B = inputs.Operand(inputs.matrix(N, K, 0.02, 71), True)
+    A, B = (op if kc else inputs.Operand(stored(op.bits, False)[0], False) for op, kc in zip((A, B), layouts))
+    say("ragged whole path", (M, N, K), layouts, inputs.STRATEGY_NAMES[strategy])
+    ta, tb = (torch.from_numpy(op.bits.view(np.int16)).cuda() for op in (A, B))
+    opa = ah.Operand(ta if layouts[0] else ta[:, :M], layouts[0])
+    opb = ah.Operand(tb if layouts[1] else tb[:, :N], layouts[1])
+    out = ah.adahop_gemm(opa, opb, strategy, 32, k)
+    torch.cuda.synchronize()
+    bits_a = A.bits if layouts[0] else np.ascontiguousarray(A.bits[:, :M])
+    bits_b = B.bits if layouts[1] else np.ascontiguousarray(B.bits[:, :N])
+    ref = orc.adahop_gemm(bits_a, layouts[0], bits_b, layouts[1], strategy, 32, k)
+    for name in ("a_codes", "a_scales", "b_codes", "b_scales"):
+        assert np.array_equal(host(out[name]), ref[name]), name
+    g = inputs.Gemm("ragged", inputs.Operand(bits_a, layouts[0]), inputs.Operand(bits_b, layouts[1]), strategy, 32, k)
+    check_c(host(out["C"]), ref["C"], g, extracted=ref["idx"] if k else None, tol=1e-5)
