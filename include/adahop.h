@@ -131,7 +131,8 @@ int adahop_foid_topk_noalloc(const adahop_operand_t *x, int axis, int k, int32_t
  * codes / scales in the canonical layout above; codes 16-byte aligned, K % 32 == 0.
  * workspace: device scratch of at least adahop_gemm_mx_workspace_bytes(M, N, K) bytes, 256-byte
  * aligned (the kernel keeps a re-ordered copy of the scales there); contents undefined on return.
- * Products with M, N >= 256 and K > 512 take the tiled, LDS-pipelined kernels, smaller ones a bounds-checked kernel.
+ * Products whose tiles of 256 rows fill most of the compute units take the kernels with these tiles, the others one with tiles of
+ * 32 .. 128 rows.
  * ------------------------------------------------------------------------------------------- */
 size_t adahop_gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int adahop_gemm_mx(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales,
@@ -139,8 +140,8 @@ int adahop_gemm_mx(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, cons
                    size_t workspace_bytes, void *stream);
 
 /* The same product with C rounded to bf16 (round to nearest even from the fp32 accumulators; the
- * paper's kernels also emit bf16): C is bf16 [M, ldc], 2-byte aligned.  The tiled kernel needs
- * ldc % 8 == 0 and C 16-byte aligned; otherwise the bounds-checked kernel runs. */
+ * paper's kernels also emit bf16): C is bf16 [M, ldc], 2-byte aligned.  Stores are 16 bytes wide
+ * where N % 8 == 0, ldc % 8 == 0 and C is 16-byte aligned. */
 int adahop_gemm_mx_bf16out(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales,
                            const uint8_t *b_codes, const uint8_t *b_scales, uint16_t *C, int64_t ldc,
                            void *workspace, size_t workspace_bytes, void *stream);
@@ -333,8 +334,9 @@ int adahop_probe_mfma_rate(int random_operands, int idle_sleeps, int workgroups,
  * 256 x 256 kernel walks its tiles in a forced order: 3 = bands of A in XCD-contiguous runs, 4 = bands of A swept
  * over B, 5 / 6 = the same two with the roles of A and B exchanged (a sweep that the shape does not allow falls back
  * to the contiguous runs).  By default the bands run along the operand with more tiles, swept where more of it would
- * be in use at a time than stays in the Infinity Cache.  Results are the same up to fp32 summation order (3 .. 6: the
- * same bits).  Returns ADAHOP_E_INVALID_ARG for any other value. */
+ * be in use at a time than stays in the Infinity Cache.  7 .. 11 = always the kernel with small tiles: 128 x 128 (two
+ * workgroups per compute unit), 128 x 128 (one, more stages in flight), 64 x 64, 32 x 64, 32 x 32.  Results are the same up to
+ * fp32 summation order (1 .. 8: the same bits).  Returns ADAHOP_E_INVALID_ARG for any other value. */
 int adahop_debug_force_gemm_kernel(int which);
 
 #ifdef __cplusplus

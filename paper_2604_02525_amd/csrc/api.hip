@@ -54,7 +54,7 @@ int adahop_abi_version(void) { return 1; }
 
 int adahop_debug_force_gemm_kernel(int which)
 {
-    if (which < 0 || which > 6) return ADAHOP_E_INVALID_ARG;
+    if (which < 0 || which > 11) return ADAHOP_E_INVALID_ARG;
     gemm_mx_force_kernel(which);
     return ADAHOP_OK;
 }
@@ -63,6 +63,7 @@ int adahop_prepare_device(void)
 {
     int rc;
     if ((rc = configure_gemm_mx(nullptr)) != ADAHOP_OK || (rc = configure_gemm_mx_dual(nullptr)) != ADAHOP_OK ||
+        (rc = configure_gemm_mx_small()) != ADAHOP_OK ||
         (rc = configure_oe_rowcol()) != ADAHOP_OK || (rc = configure_oht()) != ADAHOP_OK ||
         (rc = configure_foid()) != ADAHOP_OK)
         return rc;
@@ -417,10 +418,10 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const uint8_t *a_scales = a_given ? opts->a_scales : reinterpret_cast<uint8_t *>(ws + L.a_scales);
     const uint8_t *b_codes = b_given ? opts->b_codes : reinterpret_cast<uint8_t *>(ws + L.b_codes);
     const uint8_t *b_scales = b_given ? opts->b_scales : reinterpret_cast<uint8_t *>(ws + L.b_scales);
-    // The tiled GEMM kernel reads the scales in a stage-major copy; the quantisers that run here write it
+    // The GEMM kernels read the scales in a stage-major copy; the quantisers that run here write it
     // beside the canonical one, which saves the product its two re-ordering launches.
     const int kpad_planned = oe && strategy == ADAHOP_IHT_OE_K ? kpad_of(k) : 0;
-    const bool sm_wanted = !oht && gemm_mx_tiled(M, N, K, kpad_planned, C, ldc, c_bf16);
+    const bool sm_wanted = !oht;
     // K-channel extraction: a quantiser that runs here on a K-contiguous operand also copies the extracted channels
     // out (it has the row in registers); the position of a channel in the index list comes from a 16-bit table that
     // takes the place of the scores, which nobody reads after the selection.

@@ -32,12 +32,13 @@ bool valid_iht_block(int b);
 // launchers call them, adahop_prepare_device calls them all.
 int configure_gemm_mx(int *ncu_out);
 int configure_gemm_mx_dual(int *ncu_out);
+int configure_gemm_mx_small();
 int configure_oe_rowcol();
 int configure_oht();
 int configure_foid();
 
 // Launchers (one per kernel family); each validates nothing and returns a status.
-// Stage-major copy of the scales for the tiled GEMM kernels (see gemm_mx_tiled_part): [ceil(K/256)][rows][8].
+// Stage-major copy of the scales for the tiled GEMM kernels [ceil(K/256)][rows][8].
 struct scales_sm_t {
     uint8_t *out; // stage-major copy, or nullptr
     int64_t rows; // rows of the operand
@@ -71,16 +72,22 @@ int launch_gemm_mx(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, cons
                    const uint16_t *Ag, const uint16_t *Bg, int kpad, void *workspace, hipStream_t st,
                    int sm_ready = 0);
 size_t gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K);
-// Whether a tiled kernel takes the product; it reads the scales in a stage-major copy, [ceil(K/256)][rows][8].  A caller
-// that quantises right before the product lets the quantiser write that copy as well (scales_sm_t above) and
-// says so with sm_ready (bit 0: A, bit 1: B); otherwise launch_gemm_mx re-orders the canonical scales itself.
-bool gemm_mx_tiled(int64_t M, int64_t N, int64_t K, int kpad, const void *C, int64_t ldc, int c_bf16);
+// The kernels read the scales in a stage-major copy, [ceil(K/256)][rows][8].  A caller that quantises right before the
+// product lets the quantiser write that copy as well (scales_sm_t above) and says so with sm_ready (bit 0: A, bit 1: B);
+// otherwise launch_gemm_mx re-orders the canonical scales itself where the chosen kernel needs that.
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which);
 // The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): fp32 C, no gathered K-channels, K > 1792.
 bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K);
 int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
                         const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, hipStream_t st);
-// Diagnostics: 0 = choose by shape, 1 = always the 256 x 256 kernel, 2 = the 256 x 128 kernel wherever it can run.
+// Any shape, tiles of 32 .. 128 (gemm_mx_small.hip).  a_sm / b_sm: the scales are the stage-major copy, else the canonical
+// array (only for K % 256 == 0 and 4-byte aligned).
+int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,
+                         const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
+                         const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);
+int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us); // the variant for a shape and its expected time
+// Diagnostics: 0 = choose by shape, 1 = always the 256 x 256 kernel, 2 = the 256 x 128 kernel wherever it can run,
+// 3 .. 6 = by shape with a forced tile walk, 7 .. 11 = a variant of the kernel with small tiles.
 void gemm_mx_force_kernel(int which);
 int launch_gather_k(const adahop_operand_t &x, const int32_t *idx, int k, int kpad, uint16_t *out, hipStream_t st);
 // C is float[M, ldc], or bf16[M, ldc] when c_bf16 is set (here and in launch_oe_rowcol).

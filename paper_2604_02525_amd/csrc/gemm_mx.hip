@@ -23,32 +23,14 @@ namespace adahop {
 
 namespace {
 
-// fp32 -> bf16 bits, round to nearest even (finite values and infinities).
-__device__ __forceinline__ uint32_t bf16_bits(float x)
-{
-    const uint32_t u = __float_as_uint(x);
-    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-}
-
-// Output element types of C: float, or bf16 held as its 16 bits.
-__device__ __forceinline__ void store_c(float *p, float v) { *p = v; }
-__device__ __forceinline__ void store_c(uint16_t *p, float v) { *p = (uint16_t)bf16_bits(v); }
-__device__ __forceinline__ float load_c(const float *p) { return *p; }
-__device__ __forceinline__ float load_c(const uint16_t *p) { return bf16_one(*p); }
-
 // ------------------------------------------------------------------------------------------------
-// Generic kernel: any M, N, any K % 32 == 0.  Workgroup tile 128x128, four waves as 2x2, each wave
-// 64x64 (2x2 matrix-core tiles), operands read straight from global memory with bounds checks.
-// For products too small for a tile of the kernels below (and the accumulating form of the K-channel product).
+// C += Ag Bg^T on the gathered K-channels alone (bf16, K-contiguous, zero padded to kpad % 16 == 0), for callers that add the
+// outlier part to a product of their own.  Workgroup tile 128x128, four waves as 2x2, each wave 64x64 (2x2 matrix-core
+// tiles), operands read straight from global memory with bounds checks.
 // ------------------------------------------------------------------------------------------------
-template <bool ACCUMULATE, typename OUT>
-__global__ __launch_bounds__(256) void k_gemm_mx_generic(int64_t M, int64_t N, int64_t K,
-                                                         const uint8_t *__restrict__ a_codes,
-                                                         const uint8_t *__restrict__ a_scales,
-                                                         const uint8_t *__restrict__ b_codes,
-                                                         const uint8_t *__restrict__ b_scales, OUT *__restrict__ C,
-                                                         int64_t ldc, const uint16_t *__restrict__ Ag,
-                                                         const uint16_t *__restrict__ Bg, int kpad)
+__global__ __launch_bounds__(256) void k_oe_k_accumulate(int64_t M, int64_t N, float *__restrict__ C, int64_t ldc,
+                                                         const uint16_t *__restrict__ Ag, const uint16_t *__restrict__ Bg,
+                                                         int kpad)
 {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int l32 = lane & 31, h = lane >> 5;
@@ -78,27 +60,6 @@ __global__ __launch_bounds__(256) void k_gemm_mx_generic(int64_t M, int64_t N, i
             for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(a[i], b[j], acc[i][j]);
     }
 
-    const int64_t KB = K >> 5;
-    for (int64_t kb = 0; kb < KB; kb += 2) {
-        const int64_t blk = kb + h;
-        const bool kok = blk < KB;
-        uint4 a[2], b[2];
-        int sa[2], sb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const bool oka = kok && rowA[i] < M;
-            const bool okb = kok && rowB[i] < N;
-            a[i] = oka ? *reinterpret_cast<const uint4 *>(a_codes + rowA[i] * (K >> 1) + blk * 16) : make_uint4(0, 0, 0, 0);
-            b[i] = okb ? *reinterpret_cast<const uint4 *>(b_codes + rowB[i] * (K >> 1) + blk * 16) : make_uint4(0, 0, 0, 0);
-            sa[i] = oka ? (int)a_scales[rowA[i] * KB + blk] : 127;
-            sb[i] = okb ? (int)b_scales[rowB[i] * KB + blk] : 127;
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = mfma_fp4(a[i], b[j], acc[i][j], sa[i], sb[j]);
-    }
-
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -107,17 +68,10 @@ __global__ __launch_bounds__(256) void k_gemm_mx_generic(int64_t M, int64_t N, i
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int64_t row = m0 + i * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
-                if (row < M && col < N) {
-                    OUT *p = C + row * ldc + col;
-                    if constexpr (ACCUMULATE)
-                        store_c(p, load_c(p) + acc[i][j][r]);
-                    else
-                        store_c(p, acc[i][j][r]);
-                }
+                if (row < M && col < N) C[row * ldc + col] += acc[i][j][r];
             }
         }
 }
-
 
 // ------------------------------------------------------------------------------------------------
 // Tiled kernel for M >= 256, N >= 256, K > 512 (K % 32 == 0, kpad % 64 == 0).
@@ -413,12 +367,13 @@ template <int NBFC> __device__ __forceinline__ void run_tile(tile_state_t &t, co
 
 // The accumulators of a finished tile -> C.  The two stage buffers may already hold the next tile, so the
 // bf16 path, which has to transpose through LDS, uses a small patch private to the wave beyond them; LDS
-// operations of one wave execute in order, so the patch needs no barrier.  For bf16 the host side
-// guarantees a 16-byte aligned C and ldc % 8 == 0.
+// operations of one wave execute in order, so the patch needs no barrier.  VEC (bf16): the host side found a 16-byte
+// aligned C, ldc % 8 == 0 and N % 8 == 0; any other C is stored element by element as fp32 is, 64-byte row segments
+// (8752 x 4025 x 4096: 536 us by a kernel without LDS, now 145, with aligned rows 94).
 constexpr int PATCH_BYTES = 5120;                                  // per wave
 constexpr int KERNEL_LDS_BYTES = TILED_LDS_BYTES + 4 * PATCH_BYTES; // 159744 of the 163840 of a compute unit
 
-template <typename OUT>
+template <typename OUT, bool VEC>
 __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *__restrict__ C, int64_t ldc, int64_t m0,
                                            int64_t n0, int w, int lane)
 {
@@ -434,6 +389,16 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     __builtin_nontemporal_store(t.acc[i][j][r],
+                                                &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+    } else if constexpr (!VEC) {
+        OUT *crow = C + (m0 + wm * 128 + h * 4) * ldc + n0 + wn * 128 + l32;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    __builtin_nontemporal_store(__builtin_bit_cast(uint16_t, (__bf16)t.acc[i][j][r]),
                                                 &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
     } else {
         // bf16: a lane converts two consecutive accumulator rows into one packed pair, trades pairs with its
@@ -483,7 +448,7 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
 // Host side guarantees K > 256 (two FP4 stages), so that every bf16 stage has two successors and the
 // last two stages of a tile are FP4 stages, and at least three stages per tile (K > 512 when there are
 // no bf16 stages).
-template <bool OEK, typename OUT>
+template <bool OEK, typename OUT, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_t *__restrict__ a_codes,
                                                          const uint8_t *__restrict__ a_scales_sm,
                                                          const uint8_t *__restrict__ b_codes,
@@ -610,7 +575,7 @@ __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_
             tile_origin(more ? vn : v, m0n, n0n);
             t.nxt = tile_source(m0n, n0n);
             run_tile<decltype(nbfc)::value>(t, smem, f);
-            store_tile(t, smem, C, ldc, m0, n0, w, lane);
+            store_tile<OUT, VEC>(t, smem, C, ldc, m0, n0, w, lane);
             if (!more) break;
             v = vn;
             m0 = m0n;
@@ -643,19 +608,19 @@ static std::atomic<int> g_force_walk{-1}; // -1: the order of the tile walk chos
 
 void gemm_mx_force_kernel(int which)
 {
-    g_kernel_choice.store(which <= 2 ? which : 0);
-    g_force_walk.store(which >= 3 ? which - 3 : -1);
+    g_kernel_choice.store(which <= 2 || which >= 7 ? which : 0);
+    g_force_walk.store(which >= 3 && which <= 6 ? which - 3 : -1);
 }
 
-// Which tiled kernel takes a product (fp32 C, no gathered K-channels; otherwise always the 256 x 256 kernel).  The
+// Which of the two kernels with tiles of 256 rows (fp32 C, no gathered K-channels; otherwise always the 256 x 256 kernel).  The
 // 256 x 128 kernel with two accumulator sets hides the C stores behind the next tile but moves 1.5 times the operand
 // bytes per flop from L2 into LDS and out of LDS; measured on MI355X it wins where the stores are a large part of a
 // tile's time -- K = 2048: 1.2x; K = 4096: 1.04 .. 1.13x up to about 90 M elements of C, 0.97x at 8192 x 12288 -- and
 // loses 4 .. 15 % from K = 8192 on, except where the 256 x 256 tiles fill the last round of the compute units badly
 // (14336 x 4096: 896 tiles on 256 units, 3.5 rounds; 1.1x with 7 rounds of the smaller tiles).
-static bool takes_dual_kernel(int64_t M, int64_t N, int64_t K, int kpad, int c_bf16)
+static bool takes_dual_kernel(int64_t M, int64_t N, int64_t K, int kpad)
 {
-    if (c_bf16 || kpad > 0 || !gemm_mx_dual_eligible(M, N, K)) return false;
+    if (kpad > 0 || !gemm_mx_dual_eligible(M, N, K)) return false;
     const int forced = g_kernel_choice.load();
     if (forced == 1) return false;
     if (forced == 2) return true;
@@ -667,13 +632,35 @@ static bool takes_dual_kernel(int64_t M, int64_t N, int64_t K, int kpad, int c_b
     return waste256 >= 1.10 && waste128 + 0.08 <= waste256;
 }
 
-// Whether a tiled kernel takes the product.  At least three pipeline stages are needed (64 gathered channels or 256
-// K-elements each, two of them FP4 stages); the bf16 epilogue stores 16 bytes per lane.
-bool gemm_mx_tiled(int64_t M, int64_t N, int64_t K, int kpad, const void *C, int64_t ldc, int c_bf16)
+// Which kernel takes a product: one of the two with tiles of 256 rows (LARGE; they need at least three pipeline stages of
+// 64 gathered channels or 256 K-elements each, two of them FP4 stages) or a variant of the one with small tiles (gemm_mx_small.hip).
+// Both sides' times are estimated from the rounds of tiles on the 256 compute units: a round of 256 x 256 (256 x 128) tiles takes
+// 6.2 + 1.21 (5.3 + 0.66) us per stage of K, as fitted to the products that gemm_mx_small.hip names.  The line lies where less
+// than about half of the chip gets a tile, or the last round is short: measured, large against small tiles, 256 x 4096 x 4096 13.4
+// / 8.2 us, 1000 x 11008 x 4096 31 / 37 us, 594 x 4096 x 28672 71 / 57 us, 2016 x 20000 x 4096 78 / 137 us.
+// The output type has no part in it: a product has the same sums, bit for bit, whichever type they are rounded to.
+struct kernel_choice_t {
+    bool large, dual;
+    int variant;
+};
+
+static kernel_choice_t choose_kernel(int64_t M, int64_t N, int64_t K, int kpad)
 {
-    if (c_bf16 && !(aligned(C, 16) && ldc % 8 == 0 && N % 8 == 0)) return false;
-    if (M < TM || K <= (kpad > 0 ? 256 : 512) || kpad % 64 != 0) return false;
-    return (N >= TN || takes_dual_kernel(M, N, K, kpad, c_bf16)) && ceil_div(M, TM) * ceil_div(N, 128) < (1 << 30);
+    const int forced = g_kernel_choice.load();
+    const bool dual = takes_dual_kernel(M, N, K, kpad);
+    const bool can = M >= TM && K > (kpad > 0 ? 256 : 512) && kpad % 64 == 0 && (N >= TN || dual) &&
+                     ceil_div(M, TM) * ceil_div(N, 128) < (1 << 30);
+    const int64_t stages = ceil_div(K, 256) + kpad / 64;
+    double us_small = 0.0;
+    kernel_choice_t c = {false, dual, gemm_mx_small_pick(M, N, stages, &us_small)};
+    if (forced >= 7) {
+        c.variant = forced - 7;
+    } else if (can) {
+        const double rounds = (double)ceil_div(ceil_div(M, TM) * ceil_div(N, dual ? 128 : TN), 256);
+        const double us_large = rounds * (dual ? 5.3 + 0.66 * (double)stages : 6.2 + 1.21 * (double)stages);
+        c.large = forced == 1 || forced == 2 || us_large <= us_small;
+    }
+    return c;
 }
 
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which)
@@ -695,10 +682,12 @@ int configure_gemm_mx(int *ncu_out)
     if (once.need(dev) || ncu == 0) {
         rc = check_hip(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
         if (rc != ADAHOP_OK) return rc;
-        const void *kernels[4] = {reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, float>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, float>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t>)};
+        const void *kernels[6] = {reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, float, true>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, float, true>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, true>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, true>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, false>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, false>)};
         for (const void *f : kernels) {
             rc = check_hip(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS_BYTES));
             if (rc != ADAHOP_OK) return rc;
@@ -718,19 +707,17 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
                      const uint16_t *Bg, int kpad, void *workspace, int sm_ready, hipStream_t st)
 {
     if (M == 0 || N == 0) return ADAHOP_OK;
-    if (!gemm_mx_tiled(M, N, K, kpad, C, ldc, sizeof(OUT) == 2)) {
-        const dim3 grid((unsigned)ceil_div(N, 128), (unsigned)ceil_div(M, 128));
-        hipLaunchKernelGGL((k_gemm_mx_generic<false, OUT>), grid, dim3(256), 0, st, M, N, K, a_codes, a_scales, b_codes,
-                           b_scales, C, ldc, Ag, Bg, kpad);
-        return check_launch();
+    kernel_choice_t c = choose_kernel(M, N, K, kpad);
+    if (c.large && c.dual && sizeof(OUT) == 2) { // (the kernel with two accumulator sets stores fp32 only)
+        c.dual = false;
+        if (N < TN) { // its sums are those of the 128 x 128 tiles, which add in the same order
+            c.large = false;
+            c.variant = 1;
+        }
     }
-
-    int ncu = 0;
-    const int rc0 = configure_gemm_mx(&ncu); // once per device: the compute-unit count and the kernels' LDS size
-    if (rc0 != ADAHOP_OK) return rc0;
-    ncu = ncu / 8 * 8; // keep a workgroup's tiles on one XCD
-    if (ncu < 8) ncu = 8;
-    // stage-major scales in the caller's workspace (sm_ready bit 0 / 1: the quantiser of A / B has already written them)
+    // Stage-major scales in the caller's workspace (sm_ready bit 0 / 1: the quantiser of A / B has already written them).
+    // The kernel with small tiles can read canonical ones too, at twice the requests to the caches (0.1 us per stage more);
+    // re-ordering them takes a launch, 3 us.
     uint8_t *a_sm = gemm_mx_scales_sm(workspace, M, K, 0), *b_sm = gemm_mx_scales_sm(workspace, M, K, 1);
     const int64_t KB = K / 32;
     auto reorder = [&](const uint8_t *in, uint8_t *out, int64_t rows) {
@@ -740,14 +727,26 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
         else
             hipLaunchKernelGGL(k_stage_major_scales<false>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
     };
-    if (!(sm_ready & 1)) reorder(a_scales, a_sm, M);
-    if (!(sm_ready & 2)) reorder(b_scales, b_sm, N);
+    const bool canonical_ok = !c.large && KB % 8 == 0 && KB <= 8 * 24;
+    const bool a_canonical = !(sm_ready & 1) && canonical_ok && aligned(a_scales, 4);
+    const bool b_canonical = !(sm_ready & 2) && canonical_ok && aligned(b_scales, 4);
+    if (!(sm_ready & 1) && !a_canonical) reorder(a_scales, a_sm, M);
+    if (!(sm_ready & 2) && !b_canonical) reorder(b_scales, b_sm, N);
     int rc = check_launch();
     if (rc != ADAHOP_OK) return rc;
+    if (!c.large)
+        return launch_gemm_mx_small(c.variant, M, N, K, a_codes, a_canonical ? a_scales : a_sm, !a_canonical, b_codes,
+                                    b_canonical ? b_scales : b_sm, !b_canonical, C, ldc, sizeof(OUT) == 2, Ag, Bg, kpad, st);
     if constexpr (sizeof(OUT) == 4) {
-        if (takes_dual_kernel(M, N, K, kpad, 0))
+        if (c.dual)
             return launch_gemm_mx_dual(M, N, K, a_codes, a_sm, b_codes, b_sm, reinterpret_cast<float *>(C), ldc, st);
     }
+
+    int ncu = 0;
+    rc = configure_gemm_mx(&ncu); // once per device: the compute-unit count and the kernels' LDS size
+    if (rc != ADAHOP_OK) return rc;
+    ncu = ncu / 8 * 8; // keep a workgroup's tiles on one XCD
+    if (ncu < 8) ncu = 8;
     const int tiles_m = (int)ceil_div(M, TM), tiles_n = (int)ceil_div(N, TN);
     const int group_m = 8;
     // one workgroup per compute unit walks the tiles (each workgroup fills a compute unit's LDS and registers)
@@ -776,12 +775,19 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
         const bool ok = !(forced & 1) || (grid.x == 256 && (fb ? tiles_n : tiles_m) % 8 == 0 && (fb ? tiles_m : tiles_n) % 32 == 0);
         order = ok ? forced : (forced & 2);
     }
-    if (kpad > 0)
-        hipLaunchKernelGGL((k_gemm_mx_tile256<true, OUT>), grid, dim3(256), KERNEL_LDS_BYTES, st, K, a_codes, a_sm, b_codes,
-                           b_sm, M, N, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
-    else
-        hipLaunchKernelGGL((k_gemm_mx_tile256<false, OUT>), grid, dim3(256), KERNEL_LDS_BYTES, st, K, a_codes, a_sm, b_codes,
-                           b_sm, M, N, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
+    auto launch = [&](auto oek, auto vec) {
+        hipLaunchKernelGGL((k_gemm_mx_tile256<decltype(oek)::value, OUT, decltype(vec)::value>), grid, dim3(256), KERNEL_LDS_BYTES,
+                           st, K, a_codes, a_sm, b_codes, b_sm, M, N, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
+    };
+    auto launch_vec = [&](auto vec) { kpad > 0 ? launch(std::true_type(), vec) : launch(std::false_type(), vec); };
+    if constexpr (sizeof(OUT) == 2) {
+        if (!(aligned(C, 16) && ldc % 8 == 0 && N % 8 == 0))
+            launch_vec(std::false_type());
+        else
+            launch_vec(std::true_type());
+    } else {
+        launch_vec(std::true_type());
+    }
     return check_launch();
 }
 
@@ -803,8 +809,7 @@ int launch_oe_k_accumulate(int64_t M, int64_t N, const uint16_t *Ag, const uint1
 {
     if (M == 0 || N == 0 || kpad == 0) return ADAHOP_OK;
     dim3 grid((unsigned)ceil_div(N, 128), (unsigned)ceil_div(M, 128));
-    hipLaunchKernelGGL((k_gemm_mx_generic<true, float>), grid, dim3(256), 0, st, M, N, (int64_t)0, nullptr, nullptr, nullptr,
-                       nullptr, C, ldc, Ag, Bg, kpad);
+    hipLaunchKernelGGL(k_oe_k_accumulate, grid, dim3(256), 0, st, M, N, C, ldc, Ag, Bg, kpad);
     return check_launch();
 }
 

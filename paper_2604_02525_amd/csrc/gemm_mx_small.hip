@@ -1,0 +1,432 @@
+// Block-scaled FP4 GEMM (the MXFP4 term of paper Eq. 4 / 5 / 7 / 8, with the K-channel outlier product in front of it),
+// for products that the tiles of 256 rows do not fill the chip with or do not fit: few rows, few tiles, short K.  Any M, N,
+// any K % 32 == 0, any alignment of C.
+//
+//   C[m, n] = sum_t Ag[m, t] Bg[n, t]                                   (bf16, optional, t < kpad)
+//           + sum_blk 2^(sa[m,blk]-127) 2^(sb[n,blk]-127) sum_{i<32} a[m,32blk+i] b[n,32blk+i]
+//
+// Same instructions, operand layout and LDS slab layout as the 256 x 256 kernel (gemm_mx.hip); what differs:
+//   - tiles of 32 .. 128 rows and columns, four waves.  A wave owns at most 64 x 64 of C (64 accumulators per lane), which
+//     leaves registers for a second workgroup on the compute unit;
+//   - WK waves share a part of C and take the four matrix-core steps of every stage between them (WK = 2: two steps
+//     each, WK = 4: one); their sums are added through LDS at the end, in wave order.  A tile of 64 x 64 by four waves then reads
+//     every operand byte from LDS once, and four times as many workgroups share a product of few tiles;
+//   - NST stages of 256 K-elements rotate in LDS, NST - 1 of them on the way: such a product is bound by the latency of
+//     its operands (a tile's own share of the copy rate is 64 bytes per cycle and compute unit, reached with 64 .. 96 KiB
+//     in flight), not by the matrix cores.  One barrier per stage, at its head: the stage has landed (a counted
+//     wait for all but the copies of the younger stages) and every wave has left the buffer that is refilled next;
+//   - rows past the end of an operand repeat its last row and are not stored.  A last stage of K that is no multiple of
+//     256 starts at K - 256 as in the 256 x 256 kernel, its leading blocks with scale 0; of a K below 256 the missing
+//     blocks are the first block again, with scale 0.
+//   - what it replaced, a kernel that read its operands straight from global memory, took 420 us on 128 x 1248 x 28672 (now 28),
+//     63 us on 128 x 11008 x 4096 (15) and 78 us on 4096 x 11008 x 512 (50); 256 rows of 4096 x 4096 took 13.4 us in tiles of
+//     256 x 128 (now 7.8);
+//   - the scales come from the stage-major copy or, where K % 256 == 0, straight from the canonical array (8 bytes per row
+//     and stage: two 4-byte copies), which saves a product of packed operands the launch that re-orders them.
+#include "common.h"
+#include "gemm_mx_common.h"
+
+#include <type_traits>
+
+namespace adahop {
+
+namespace {
+
+namespace small {
+
+constexpr int TKB = 128; // bytes of K per row and stage
+
+// Where the scale bytes of a stage lie: row r of stage s at p + r * row + s * stage, 8 bytes, 4-byte aligned.
+struct scale_src_t {
+    const uint8_t *p;
+    int64_t row, stage;
+};
+
+__device__ __forceinline__ void dma4(const uint8_t *base, uint32_t voff, uint32_t lds_addr)
+{ // as dma16, 4 bytes per lane
+    base = uniform_ptr(base);
+    lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :
+                 : "v"(voff), "s"(base), "s"(lds_addr)
+                 : "memory", "m0");
+}
+
+template <int T, int I = 0, typename F> __device__ __forceinline__ void for_each_index(F &&f)
+{
+    if constexpr (I < T) {
+        f(std::integral_constant<int, I>());
+        for_each_index<T, I + 1>(f);
+    }
+}
+
+template <int X> __device__ __forceinline__ void wait_and_meet()
+{
+    // my copies of the stage have landed and my LDS reads are done; then every wave's
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(X) : "memory");
+}
+
+__device__ __forceinline__ void put(float *p, float v) { *p = v; }
+__device__ __forceinline__ void put(uint16_t *p, float v)
+{
+    const __bf16 b = (__bf16)v; // nearest even
+    *p = __builtin_bit_cast(uint16_t, b);
+}
+
+template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct shape_t {
+    static constexpr int TM = 32 * TMB * WM, TN = 32 * TNB * WN;
+    static constexpr int SLAB = (TM + TN) * TKB, STAGE = SLAB + (TM + TN) * 8;
+    static constexpr int RED = WK > 1 ? 4 * TMB * TNB * 16 * 64 * 4 : 0;
+    static constexpr int LDS = NST * STAGE > RED ? NST * STAGE : RED;
+    static constexpr int NC = (TM + TN) / 32;      // 16-byte copies per wave and stage (a copy: 8 rows; 4 waves)
+    static constexpr int NS = ((TM + TN) / 32 + 3) / 4; // 4-byte copies of scales per wave and stage (a copy: 32 rows)
+};
+
+template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool OEK, typename OUT>
+__global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8_t *__restrict__ a_codes, scale_src_t a_sc,
+                                                          const uint8_t *__restrict__ b_codes, scale_src_t b_sc, int64_t M,
+                                                          int64_t N, OUT *__restrict__ C, int64_t ldc,
+                                                          const uint16_t *__restrict__ Ag, const uint16_t *__restrict__ Bg,
+                                                          int kpad, int tiles_m)
+{
+    typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU> S;
+    constexpr int TM = S::TM, TN = S::TN, NC = S::NC, NS = S::NS, CPS = NC + NS; // CPS: copies per wave and stage
+    static_assert(WM * WN * WK == 4 && TM % 32 == 0 && TN % 32 == 0 && 4 % WK == 0, "four waves");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = w % WK, wmn = w / WK, wm = wmn / WN, wn = wmn % WN;
+
+    // Workgroup v -> tile, row tiles fastest: consecutive ids land on the 8 XCDs in turn, and every XCD takes a contiguous run,
+    // so that the workgroups that read the same rows of B share an L2.
+    int tix = blockIdx.x;
+    {
+        const int nt = gridDim.x, per = nt >> 3, rest = nt & 7, x = tix & 7;
+        tix = x * per + min(x, rest) + (tix >> 3);
+    }
+    const int64_t m0 = (int64_t)(tix % tiles_m) * TM, n0 = (int64_t)(tix / tiles_m) * TN;
+
+    // ---- copy engine.  Copy d of wave w: rows 8 (w + 4 d) .. + 7 of the tile's TM rows of A and TN rows of B; lane i writes
+    // LDS row i / 8 of them, chunk position i % 8, which holds logical chunk (i % 8) ^ ((row / 2) & 7).
+    const int nbf = OEK ? kpad >> 6 : 0, nfp = (int)((K + 255) >> 8), n = nbf + nfp;
+    const uint32_t chunk16 = (uint32_t)(((lane & 7) ^ (4 * (w & 1) + (lane >> 4))) * 16);
+    const int last_off = K >= 256 ? (int)(K >> 1) - TKB : 0;
+    const int short_by = K >= 256 ? 0 : TKB - (int)(K >> 1); // bytes that a row lacks of a whole stage
+    const uint32_t pitch = (uint32_t)(K >> 1), gpitch = (uint32_t)kpad * 2;
+    uint32_t vo[NC]; // byte offset of the lane's chunk (OEK: its row, of which the offset is made for either pitch)
+    const uint32_t chunk_fp4 = (uint32_t)max((int)chunk16 - short_by, 0);
+#pragma unroll
+    for (int d = 0; d < NC; ++d) {
+        const int r = 8 * (w + 4 * d) + (lane >> 3);
+        const int64_t left = d < TM / 32 ? M - 1 - m0 : N - 1 - n0;
+        const uint32_t row = (uint32_t)min((int64_t)(d < TM / 32 ? r : r - TM), left);
+        vo[d] = OEK ? row : row * pitch + chunk_fp4;
+    }
+    uint32_t so[NS];      // scales: lane i copies half i % 2 of row i / 2 of 32
+    bool s_is_a[NS];      // (wave-uniform)
+    int s_at[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int q = (w + 4 * j) % ((TM + TN) / 32); // (a wave without a copy of its own repeats another's: same bytes)
+        s_at[j] = q;
+        s_is_a[j] = q < TM / 32;
+        const int r = 32 * (s_is_a[j] ? q : q - TM / 32) + (lane >> 1);
+        const uint32_t row = (uint32_t)min((int64_t)r, s_is_a[j] ? M - 1 - m0 : N - 1 - n0);
+        so[j] = row * (uint32_t)(s_is_a[j] ? a_sc.row : b_sc.row) + (lane & 1) * 4;
+    }
+    const uint64_t ga = reinterpret_cast<uint64_t>(a_codes) + m0 * pitch, gb = reinterpret_cast<uint64_t>(b_codes) + n0 * pitch;
+    const uint64_t gga = reinterpret_cast<uint64_t>(Ag) + m0 * gpitch, ggb = reinterpret_cast<uint64_t>(Bg) + n0 * gpitch;
+    // scale copies: base and stage stride of the operand that copy j of this wave serves
+    const uint8_t *sp[NS];
+    int64_t sstep[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        sp[j] = s_is_a[j] ? a_sc.p + m0 * a_sc.row : b_sc.p + n0 * b_sc.row;
+        sstep[j] = s_is_a[j] ? a_sc.stage : b_sc.stage;
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+
+    // Copies D0 .. D1-1 of the CPS of a stage, into LDS buffer b: NC of codes (or gathered bf16), then NS of scales.
+    auto issue = [&](int stage, int b, auto d0_c, auto d1_c) {
+        constexpr int D0 = decltype(d0_c)::value, D1 = decltype(d1_c)::value;
+        if constexpr (D0 < D1) {
+            const uint32_t buf = lds0 + (uint32_t)b * S::STAGE;
+            // (The choices between a bf16 and an FP4 stage are made with a mask: written as selections of the variables that this
+            // function captures, they put those into memory, and the K-channel products ran at half the speed.)
+            const bool bf = OEK && stage < nbf;
+            const uint64_t m = bf ? ~(uint64_t)0 : 0;
+            const uint32_t rp = pitch ^ ((pitch ^ gpitch) & (uint32_t)m), ch = chunk_fp4 ^ ((chunk_fp4 ^ chunk16) & (uint32_t)m);
+            const int fs = bf ? 0 : stage - nbf; // (a bf16 stage copies the scales of the first FP4 stage: the count stays the same)
+            const int off = bf ? stage * TKB : min(fs * TKB, last_off);
+            const uint8_t *pa = reinterpret_cast<const uint8_t *>(ga ^ ((ga ^ gga) & m)) + off;
+            const uint8_t *pb = reinterpret_cast<const uint8_t *>(gb ^ ((gb ^ ggb) & m)) + off;
+#pragma unroll
+            for (int d = D0; d < D1; ++d) {
+                if (d < NC) {
+                    uint32_t v = vo[d];
+                    if constexpr (OEK) v = __umul24(v, rp) + ch;
+                    dma16(d < TM / 32 ? pa : pb, v, buf + (uint32_t)(w + 4 * d) * 1024);
+                } else {
+                    const int j = d - NC;
+                    dma4(sp[j] + fs * sstep[j], so[j], buf + S::SLAB + s_at[j] * 256);
+                }
+            }
+        }
+    };
+    auto issue_all = [&](int stage, int b) { issue(stage, b, std::integral_constant<int, 0>(), std::integral_constant<int, CPS>()); };
+
+    // ---- fragment reads: row l32 (+ 32 i) of the wave's part, logical chunk 4 h + s in step s
+    const int rx = (l32 >> 1) & 7;
+    const int a_row = (wm * TMB * 32 + l32) * TKB, b_row = (TM + wn * TNB * 32 + l32) * TKB;
+    const int sa_row = S::SLAB + (wm * TMB * 32 + l32) * 8 + 4 * h, sb_row = S::SLAB + (TM + wn * TNB * 32 + l32) * 8 + 4 * h;
+
+    v16f acc[TMB][TNB];
+#pragma unroll
+    for (int i = 0; i < TMB; ++i)
+#pragma unroll
+        for (int j = 0; j < TNB; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+    // One stage: its matrix-core instructions, the fragment reads of the next step ahead of those of a step, and between them
+    // (ISSUE) the copies of stage `which` into buffer `wb`, spread evenly: a wave issues in order, and all copies at the head
+    // of the stage kept it from the matrix cores for half of its time (0.67 us per stage of 128 x 128 where the matrix
+    // cores need 0.2).
+    auto stage = [&](const uint8_t *st, auto bf_c, auto issue_c, int which, int wb) {
+        constexpr bool BF = decltype(bf_c)::value, ISSUE = decltype(issue_c)::value;
+        constexpr int STEPS = 4 / WK, T = TMB * TNB * STEPS;
+        int sa[TMB], sb[TNB];
+        uint4 a[2][TMB], b[2][TNB];
+        auto read = [&](int q) {
+            const int at = ((4 * h + STEPS * wk + q) ^ rx) * 16;
+#pragma unroll
+            for (int i = 0; i < TMB; ++i) a[q & 1][i] = *reinterpret_cast<const uint4 *>(st + a_row + i * 32 * TKB + at);
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) b[q & 1][j] = *reinterpret_cast<const uint4 *>(st + b_row + j * 32 * TKB + at);
+        };
+        if constexpr (!BF) {
+#pragma unroll
+            for (int i = 0; i < TMB; ++i) sa[i] = *reinterpret_cast<const int *>(st + sa_row + i * 256);
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) sb[j] = *reinterpret_cast<const int *>(st + sb_row + j * 256);
+        }
+        read(0);
+        ADAHOP_PIN();
+        if constexpr (!BF && WK > 1) {
+#pragma unroll
+            for (int i = 0; i < TMB; ++i) sa[i] >>= 8 * STEPS * wk;
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) sb[j] >>= 8 * STEPS * wk;
+        }
+        auto one = [&](auto k_c) { // matrix-core instruction k of the stage: step k / (TMB TNB), row-major over the wave's tiles
+            constexpr int k = decltype(k_c)::value, q = k / (TMB * TNB), e = k % (TMB * TNB), i = e / TNB, j = e % TNB;
+            if constexpr (e == 0 && q + 1 < STEPS) {
+                read(q + 1);
+                ADAHOP_PIN();
+            }
+            if constexpr (BF) {
+                acc[i][j] = mfma_bf16(a[q & 1][i], b[q & 1][j], acc[i][j]);
+            } else {
+                const uint4 x = a[q & 1][i], y = b[q & 1][j];
+                v8i av = {(int)x.x, (int)x.y, (int)x.z, (int)x.w, 0, 0, 0, 0};
+                v8i bv = {(int)y.x, (int)y.y, (int)y.z, (int)y.w, 0, 0, 0, 0};
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[i][j], 4, 4, q, sa[i], q, sb[j]);
+            }
+            if constexpr (ISSUE) {
+                ADAHOP_PIN();
+                issue(which, wb, std::integral_constant<int, CPS * k / T>(), std::integral_constant<int, CPS *(k + 1) / T>());
+                ADAHOP_PIN();
+            }
+        };
+        for_each_index<T>(one);
+    };
+    auto run = [&](int t, int b, auto issue_c, int which, int wb) {
+        const uint8_t *st = smem + b * S::STAGE;
+        if (OEK && t < nbf)
+            stage(st, std::true_type(), issue_c, which, wb);
+        else
+            stage(st, std::false_type(), issue_c, which, wb);
+    };
+
+    for (int s = 0; s < NST - PU && s < n; ++s) issue_all(s, s);
+    int t = 0, b = 0; // stage t lies in buffer b = t % NST
+    auto at = [&](int x) { return x < NST ? x : x - NST; };
+    // PU stages with the copies of PU more, into the buffers of stages t - PU .. t - 1, which every wave has left
+    auto full = [&](auto &&body) {
+        wait_and_meet<CPS *(NST - 2 * PU)>(); // stages t + PU .. t + NST - PU - 1 may still be on the way
+#pragma unroll
+        for (int u = 0; u < PU; ++u) body(t + u, at(b + u), t + NST - PU + u, at(b + NST - PU + u));
+        t += PU;
+        b = at(b + PU);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if constexpr (OEK) { // loops of their own: a branch around the matrix-core instructions moves the accumulators at every stage
+        while (t + NST <= n && t + PU <= nbf) full([&](int, int rb, int which, int wb) { stage(smem + rb * S::STAGE, yes, yes, which, wb); });
+        if (PU > 1 && t + NST <= n && t < nbf) full([&](int s, int rb, int which, int wb) { run(s, rb, yes, which, wb); });
+    }
+    while (t + NST <= n) full([&](int, int rb, int which, int wb) { stage(smem + rb * S::STAGE, no, yes, which, wb); });
+    for (; t < n; t += PU, b = at(b + PU)) {
+        wait_and_meet<0>();
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+            if (t + NST - PU + u < n) issue_all(t + NST - PU + u, at(b + NST - PU + u));
+        run(t, b, std::false_type(), 0, 0);
+#pragma unroll
+        for (int u = 1; u < PU; ++u)
+            if (t + u < n) run(t + u, at(b + u), std::false_type(), 0, 0);
+    }
+
+    // ---- the waves that share a part of C add up, each wave the sums of its share of the accumulator tile
+    if constexpr (WK > 1) {
+        constexpr int E = TMB * TNB * 16, SH = E / WK;
+        float *red = reinterpret_cast<float *>(smem);
+        wait_and_meet<0>(); // every wave has read its last fragments
+#pragma unroll
+        for (int i = 0; i < TMB; ++i)
+#pragma unroll
+            for (int j = 0; j < TNB; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) red[(w * E + (i * TNB + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+        wait_and_meet<0>();
+#pragma unroll
+        for (int e0 = 0; e0 < SH; ++e0) {
+            const int e = wk * SH + e0, t = e >> 4, r = e & 15, i = t / TNB, j = t % TNB;
+            float v = red[((wmn * WK) * E + e) * 64 + lane];
+#pragma unroll
+            for (int q = 1; q < WK; ++q) v += red[((wmn * WK + q) * E + e) * 64 + lane];
+            const int64_t row = m0 + (wm * TMB + i) * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+            const int64_t col = n0 + (wn * TNB + j) * 32 + l32;
+            if (row < M && col < N) put(C + row * ldc + col, v);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < TMB; ++i)
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) {
+                const int64_t col = n0 + (wn * TNB + j) * 32 + l32;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t row = m0 + (wm * TMB + i) * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+                    if (row < M && col < N) put(C + row * ldc + col, acc[i][j][r]);
+                }
+            }
+    }
+}
+
+template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct variant_t {
+    typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU> S;
+    template <bool OEK, typename OUT> static int allow()
+    {
+        return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, OEK, OUT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS));
+    }
+    static int configure()
+    {
+        int rc;
+        if ((rc = allow<false, float>()) != ADAHOP_OK || (rc = allow<true, float>()) != ADAHOP_OK ||
+            (rc = allow<false, uint16_t>()) != ADAHOP_OK)
+            return rc;
+        return allow<true, uint16_t>();
+    }
+    template <typename OUT>
+    static int launch(int64_t M, int64_t N, int64_t K, const uint8_t *a, scale_src_t as, const uint8_t *b, scale_src_t bs, OUT *C,
+                      int64_t ldc, const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st)
+    {
+        const int64_t tm = ceil_div(M, S::TM), tn = ceil_div(N, S::TN);
+        const dim3 grid((unsigned)(tm * tn));
+        if (kpad > 0)
+            hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, true, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b, bs,
+                               M, N, C, ldc, Ag, Bg, kpad, (int)tm);
+        else
+            hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, false, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b, bs,
+                               M, N, C, ldc, Ag, Bg, kpad, (int)tm);
+        return check_launch();
+    }
+};
+
+typedef variant_t<2, 2, 2, 2, 1, 2, 1> v128_t;    // 128 x 128, two workgroups per compute unit
+typedef variant_t<2, 2, 2, 2, 1, 3, 1> v128deep_t; // 128 x 128, one workgroup, two stages on the way
+typedef variant_t<2, 2, 1, 1, 4, 4, 1> v64_t;     // 64 x 64
+typedef variant_t<1, 2, 1, 1, 4, 4, 1> v32x64_t;  // 32 x 64
+typedef variant_t<1, 1, 1, 1, 4, 8, 2> v32_t;     // 32 x 32
+
+// What a variant takes, in us: start + stages max(alone, busy L) + tile L, L = tiles on the fullest of the 256 compute units.
+// Fitted on MI355X to 330 products (16 .. 4096 rows, 320 .. 20000 columns, K 512 .. 28672; mean error 8 .. 15 %); the choice that
+// the figures give is within 2 % of the fastest variant in the geometric mean over them.
+struct cost_t {
+    int tm, tn;
+    double start, alone, busy, tile;
+};
+constexpr cost_t COST[5] = {{128, 128, 0.9, 0.743, 0.521, 3.2},
+                            {128, 128, 0.2, 0.448, 0.500, 5.0},
+                            {64, 64, 2.8, 0.138, 0.222, 1.4},
+                            {32, 64, 3.0, 0.172, 0.153, 0.6},
+                            {32, 32, 2.5, 0.135, 0.111, 0.6}};
+
+} // namespace small
+
+} // namespace
+
+int configure_gemm_mx_small()
+{
+    static device_once_t once;
+    int dev = 0;
+    int rc = check_hip(hipGetDevice(&dev));
+    if (rc != ADAHOP_OK || !once.need(dev)) return rc;
+    using namespace small;
+    if ((rc = v128_t::configure()) != ADAHOP_OK || (rc = v128deep_t::configure()) != ADAHOP_OK ||
+        (rc = v64_t::configure()) != ADAHOP_OK || (rc = v32x64_t::configure()) != ADAHOP_OK ||
+        (rc = v32_t::configure()) != ADAHOP_OK)
+        return rc;
+    once.mark(dev);
+    return ADAHOP_OK;
+}
+
+template <typename OUT>
+static int launch_small_t(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a, small::scale_src_t as, const uint8_t *b,
+                          small::scale_src_t bs, OUT *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg, int kpad,
+                          hipStream_t st)
+{
+    using namespace small;
+    switch (variant) {
+    case 0: return v128_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    case 1: return v128deep_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    case 2: return v64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    case 3: return v32x64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    case 4: return v32_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    }
+    return ADAHOP_E_INVALID_ARG;
+}
+
+// The fastest variant for a product of `stages` pipeline stages, and what it is expected to take.
+int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us)
+{
+    int best = 0;
+    for (int v = 0; v < 5; ++v) {
+        const small::cost_t &c = small::COST[v];
+        const double L = (double)ceil_div(ceil_div(M, c.tm) * ceil_div(N, c.tn), 256);
+        const double each = c.alone > c.busy * L ? c.alone : c.busy * L;
+        const double t = c.start + (double)stages * each + c.tile * L;
+        if (v == 0 || t < *us) {
+            *us = t;
+            best = v;
+        }
+    }
+    return best;
+}
+
+int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,
+                         const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
+                         const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st)
+{
+    const int rc = configure_gemm_mx_small();
+    if (rc != ADAHOP_OK) return rc;
+    const int64_t KB = K / 32;
+    const small::scale_src_t as = {a_scales, a_sm ? 8 : KB, a_sm ? M * 8 : 8}, bs = {b_scales, b_sm ? 8 : KB, b_sm ? N * 8 : 8};
+    if (c_bf16)
+        return launch_small_t(variant, M, N, K, a_codes, as, b_codes, bs, static_cast<uint16_t *>(C), ldc, Ag, Bg, kpad, st);
+    return launch_small_t(variant, M, N, K, a_codes, as, b_codes, bs, static_cast<float *>(C), ldc, Ag, Bg, kpad, st);
+}
+
+} // namespace adahop

@@ -1,7 +1,7 @@
 """The two tiled kernels of the MXFP4 product against the oracle's emulated product, each forced through the
 diagnostics switch: the 256 x 256 tile kernel and the 256 x 128 tile kernel with two accumulator sets (C stores of a
 tile issued during the next tile).  Shapes cover one tile, several tiles per workgroup (both accumulator sets, an odd
-and an even count of tiles per workgroup), ragged edges that go to the bounds-checked kernel, tile counts whose
+and an even count of tiles per workgroup), ragged edges, tile counts whose
 split over the eight XCDs does and does not fall on whole bands of the tile order, and stage counts from the minimum of
 the two-set kernel (8) up.  Every element is compared (1e-5 relative Frobenius and the per-element
 accumulation allowance of test_gpu_parity)."""
@@ -134,3 +134,67 @@ def test_ragged_whole_path(ah, layouts, M, N, K, strategy, k):
         assert np.array_equal(host(out[name]), ref[name]), name
     g = inputs.Gemm("ragged", inputs.Operand(bits_a, layouts[0]), inputs.Operand(bits_b, layouts[1]), strategy, 32, k)
     check_c(host(out["C"]), ref["C"], g, extracted=ref["idx"] if k else None, tol=1e-5)
+
+
+SMALL = (7, 8, 9, 10, 11)           # 128 x 128 shallow and deep, 64 x 64, 32 x 64, 32 x 32
+
+
+@pytest.mark.parametrize("kernel", SMALL)
+@pytest.mark.parametrize("shape", [(1, 1, 32), (31, 33, 64), (33, 65, 224), (64, 64, 256), (65, 127, 288), (129, 130, 512),
+                                   (96, 1000, 1056), (300, 257, 2304), (130, 640, 4064), (17, 4100, 768)])
+def test_small_tiles(ah, force, kernel, shape):
+    """Rows and columns one past and one short of a tile, K from one block over less than a stage to more stages than
+    rotate in LDS, an odd and an even count of them, canonical (K % 256 == 0) and re-ordered scales, a C with a gap behind
+    its rows that must stay as it was; both output types.  The allowance is the one above, plus half a bf16 step."""
+    M, N, K = shape
+    rng = np.random.default_rng(M + 5 * N + 11 * K)
+    a_codes = rng.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
+    b_codes = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    a_scales = rng.integers(117, 137, size=(M, K // 32), dtype=np.uint8)
+    b_scales = rng.integers(100, 120, size=(N, K // 32), dtype=np.uint8)
+    say("small tiles", kernel, shape)
+    force(kernel)
+    ref = orc.mx_gemm(a_codes, a_scales, b_codes, b_scales)
+    bar = 2.0 ** -20 * np.outer(dequant_norms(a_codes, a_scales), dequant_norms(b_codes, b_scales))
+    dev = [torch.from_numpy(t).cuda() for t in (a_codes, a_scales, b_codes, b_scales)]
+    for dtype in (torch.float32, torch.bfloat16):
+        room = torch.full((M + 1, N + 3), 7.0, dtype=dtype, device="cuda")
+        ah.adahop_gemm_mx(*dev, Cout=room[:M, :N])
+        torch.cuda.synchronize()
+        got = host(room.float()).astype(np.float64)
+        assert (got[M] == 7.0).all() and (got[:, N:] == 7.0).all()
+        step = 0.0 if dtype == torch.float32 else 2.0 ** -8
+        assert float((np.abs(got[:M, :N] - ref) - step * np.abs(ref) - bar * (1.0 + step)).max()) <= 0.0
+
+
+@pytest.mark.parametrize("kernel", SMALL)
+@pytest.mark.parametrize("M,N,K,k", [(40, 70, 96, 9), (96, 264, 1120, 70), (150, 129, 2048, 200)])
+def test_small_tiles_with_k_channels(ah, force, kernel, M, N, K, k):
+    """One, two and four gathered bf16 stages in front of one to nine FP4 stages, scales written by the quantisers."""
+    A = inputs.Operand(inputs.matrix(M, K, 1.0, 80, col_outliers=(5, 50.0, 50.0)), True)
+    B = inputs.Operand(inputs.matrix(N, K, 0.02, 81), True)
+    say("small tiles with K-channels", kernel, (M, N, K, k))
+    force(kernel)
+    out = ah.adahop_gemm(*(ah.Operand.from_bits(op.bits, True) for op in (A, B)), inputs.IHT_OE_K, 32, k)
+    torch.cuda.synchronize()
+    ref = orc.adahop_gemm(A.bits, True, B.bits, True, inputs.IHT_OE_K, 32, k)
+    assert np.array_equal(np.sort(host(out["idx"])), ref["idx"])
+    check_c(host(out["C"]), ref["C"], inputs.Gemm("small", A, B, inputs.IHT_OE_K, 32, k), extracted=ref["idx"], tol=1e-5)
+
+
+@pytest.mark.parametrize("kernel", [0, TILE256])
+@pytest.mark.parametrize("M,N,K,k,gap", [(2305, 1027, 4096, 0, 0), (2048, 2048, 2048, 0, 1), (1024, 1001, 1024, 20, 0),
+                                         (300, 130, 2080, 0, 3)])
+def test_bf16_output_of_any_alignment(ah, force, kernel, M, N, K, k, gap):
+    """Widths and row strides that are no multiples of 16 bytes: the bits of the fp32 product rounded to nearest even."""
+    A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 90, col_outliers=(5, 50.0, 50.0)), True)
+    B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 91), True)
+    say("bf16 output of any alignment", kernel, (M, N, K, k, gap))
+    force(kernel)
+    strategy = inputs.IHT_OE_K if k else inputs.IHT
+    full = ah.adahop_gemm(A, B, strategy, 32, k)["C"].to(torch.bfloat16)
+    room = torch.full((M, N + gap), 7.0, dtype=torch.bfloat16, device="cuda")
+    ah.adahop_gemm(A, B, strategy, 32, k, Cout=room[:, :N])
+    torch.cuda.synchronize()
+    assert torch.equal(room[:, :N].view(torch.int16), full.view(torch.int16))
+    assert bool((room[:, N:] == 7.0).all())

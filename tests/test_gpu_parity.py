@@ -411,8 +411,7 @@ def test_whole_path_small_all_layouts(ah, strategy, kind):
                                         (inputs.IHT_OE_ROW, 6), (inputs.IHT_OE_COL, 3)])
 @pytest.mark.parametrize("M,N", [(768, 512), (840, 600)])
 def test_whole_path_tile_aligned_shape(ah, strategy, k, M, N):
-    """K a multiple of 256: the tiled GEMM kernel (LDS-staged, K-channel part fused) takes the whole 256x256
-    tiles, the bounds-checked kernel the ragged edges of the second shape."""
+    """K a multiple of 256, whole tiles and (second shape) ragged edges, K-channel part fused."""
     K = 1024
     A = inputs.Operand(inputs.matrix(M, K, 1.0, 60, row_outliers=(4, 100.0, 100.0), col_outliers=(5, 50.0, 50.0)), True)
     B = inputs.Operand(np.ascontiguousarray(inputs.matrix(N, K, 0.02, 61).T), False)

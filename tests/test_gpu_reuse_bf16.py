@@ -110,8 +110,7 @@ def test_bf16_output_small_ragged(ah, strategy, kind):
                                         (inputs.IHT_OE_COL, 3)])
 @pytest.mark.parametrize("M,N", [(768, 512), (840, 600)])
 def test_bf16_output_tiled_kernel(ah, strategy, k, M, N):
-    """K % 256 == 0: the LDS-pipelined kernel writes the whole 256x256 tiles (packed column pairs), the
-    bounds-checked kernel the ragged edges of the second shape."""
+    """K % 256 == 0, whole tiles and (second shape) ragged edges: the bits of the fp32 product rounded."""
     K = 1024
     A = inputs.Operand(inputs.matrix(M, K, 1.0, 72, row_outliers=(4, 100.0, 100.0), col_outliers=(5, 50.0, 50.0)), True)
     B = inputs.Operand(np.ascontiguousarray(inputs.matrix(N, K, 0.02, 73).T), False)
@@ -126,9 +125,8 @@ def test_bf16_output_tiled_kernel(ah, strategy, k, M, N):
 
 
 def test_bf16_output_odd_leading_dimension_and_untouched_padding(ah):
-    """A ldc that is no multiple of 8 (or a C that is not 16-byte aligned) rules out the 16-byte stores of the
-    tiled kernel: the bounds-checked kernel takes the whole product; the last case is a padded C that the tiled
-    kernel does take.  Nothing outside [M, N] may be written."""
+    """A ldc that is no multiple of 8 (or a C that is not 16-byte aligned) rules out 16-byte stores; the last case is a
+    padded C that allows them.  Nothing outside [M, N] may be written."""
     M, N, K = 512, 512, 512
     A = inputs.Operand(inputs.matrix(M, K, 1.0, 74, col_outliers=(3, 40.0, 40.0)), True)
     B = inputs.Operand(inputs.matrix(N, K, 0.02, 75), True)
