@@ -2,8 +2,7 @@
 
 Both sides implement the same counter-based generator (Philox4x32-10 keyed by the seed, counted by the
 element's position), so the bar is the usual one: codes and scales bit for bit, whatever the layout, the
-transform block, the masks or the kernel the launcher picks (K % 256 == 0 takes the 16-wide kernels, other K
-the general ones); the product within 1e-3 relative Frobenius of the oracle's.
+transform block or the masks; the product within 1e-3 relative Frobenius of the oracle's.
 """
 import numpy as np
 import pytest
@@ -31,6 +30,29 @@ def ah():
 
 def host(t):
     return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("k_contig", [True, False])
+def test_sr_quantiser_at_the_edges_of_the_range(ah, k_contig):
+    """No transform; every block has its largest magnitude at one exponent of the whole bf16 range (zero and subnormal
+    blocks among them) and the other elements anywhere from there down to the smallest subnormal, magnitudes on and next
+    to the E2M1 values, both zeros."""
+    rng = np.random.default_rng(4)
+    outer, K = 264, 512
+    top = rng.integers(0, 255, size=(outer, K // 32, 1))
+    exp = np.maximum(top - np.where(rng.random((outer, K // 32, 32)) < 0.8, rng.integers(0, 5, size=(outer, K // 32, 32)),
+                                    rng.integers(0, 255, size=(outer, K // 32, 32))), 0)
+    exp[:, :, 0] = top[:, :, 0]
+    mant = np.where(rng.random(exp.shape) < 0.5, rng.choice([0, 1, 63, 64, 65, 127], size=exp.shape), rng.integers(0, 128, size=exp.shape))
+    bits = (rng.integers(0, 2, size=exp.shape) << 15 | exp << 7 | mant).astype(np.uint16).reshape(outer, K)
+    bits[5, :64] &= 0x8000
+    stored = bits if k_contig else np.ascontiguousarray(bits.T)
+    say("SR quantiser, edges of the range", "K-contiguous" if k_contig else "K-strided")
+    codes, scales = ah.adahop_iht_quantize(ah.Operand(torch.from_numpy(stored.view(np.int16)).cuda(), k_contig), 0, sr_seed=77)
+    torch.cuda.synchronize()
+    rc, rs = orc.iht_quantize(stored, k_contig, 0, sr_seed=77)
+    assert np.array_equal(host(scales), rs)
+    assert np.array_equal(host(codes), rc)
 
 
 @pytest.mark.parametrize("k_contig", [True, False])
