@@ -15,9 +15,9 @@
 //   k_pattern_partial  one pass over the stored matrix S[R][C]: a workgroup takes 256 rows x 512
 //                      columns and writes, per row, its sum / sum of squares over the 512 columns,
 //                      and per column over the 256 rows (no atomics);
-//   k_pattern_fold     adds the partials of every row and every column in a fixed order (one thread each);
-//   k_pattern_finish   one workgroup forms both variance vectors and their statistics and writes the class and
-//                      the four CV figures.
+//   k_pattern_fold     adds the partials of every row and every column in a fixed order, forms the variances and
+//                      sums them and their squares over 32 neighbours;
+//   k_pattern_finish   one workgroup adds these and writes the class and the four CV figures.
 #include "common.h"
 
 namespace adahop {
@@ -33,107 +33,193 @@ __device__ __forceinline__ double wave_sum(double v)
     return v; // valid in lane 0
 }
 
-// rowpart[cb][r] = (sum, sumsq) of row r over column block cb; colpart[rb][c] likewise.
-__global__ __launch_bounds__(256) void k_pattern_partial(const uint16_t *__restrict__ S, int64_t ld, int64_t R, int64_t C,
-                                                         double2 *__restrict__ rowpart, double2 *__restrict__ colpart)
+// x and y of the pair handed on: the lower half of the wave (MASK = 32; of a pair of rows of 16: the even one, MASK = 16) ends
+// with x summed over both halves, the other with y.
+template <int MASK> __device__ __forceinline__ double halve(double x, double y)
 {
-    __shared__ double2 scol[4][PT_COLS];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const uint64_t xb = (uint64_t)__double_as_longlong(x), yb = (uint64_t)__double_as_longlong(y);
+    u32x2 lo, hi;
+    if constexpr (MASK == 32) {
+        lo = __builtin_amdgcn_permlane32_swap((unsigned)xb, (unsigned)yb, false, false);
+        hi = __builtin_amdgcn_permlane32_swap((unsigned)(xb >> 32), (unsigned)(yb >> 32), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap((unsigned)xb, (unsigned)yb, false, false);
+        hi = __builtin_amdgcn_permlane16_swap((unsigned)(xb >> 32), (unsigned)(yb >> 32), false, false);
+    }
+    return __longlong_as_double((long long)((uint64_t)hi.x << 32 | lo.x)) + __longlong_as_double((long long)((uint64_t)hi.y << 32 | lo.y));
+}
+
+template <int CTRL> __device__ __forceinline__ double dpp_double(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// rowpart[cb][r] = (sum, sumsq) of row r over column block cb; colpart[rb][c] likewise.  A lane keeps 8 columns of the block, a
+// wave takes every W-th row.
+//
+// Bound by the fp64 sums beside the reads: five fp64 instructions per element, and what the row sums take across the lanes.  Those
+// of 8 rows (16 numbers per lane) are halved together: every exchange leaves a lane with half as many numbers summed over
+// twice as many lanes, 63 instructions for 8 rows, where a reduction for each row by itself was 288, two thirds of them through the LDS
+// (16384 x 8192: 91 -> 64 us; the detector as a whole 120 -> 71).
+// W waves: 8 (two workgroups per compute unit), and 16 where there are fewer workgroups than compute units (371 x 12288: 48 workgroups,
+// 34 -> 14 us).
+template <int W>
+__global__ __launch_bounds__(64 * W, 4) void k_pattern_partial(const uint16_t *__restrict__ S, int64_t ld, int64_t R, int64_t C,
+                                                            double2 *__restrict__ rowpart, double2 *__restrict__ colpart)
+{
+    __shared__ double2 scol[W][PT_COLS]; // column 8 l + j of the block at 64 j + l
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t r0 = (int64_t)blockIdx.y * PT_ROWS, c0 = (int64_t)blockIdx.x * PT_COLS + lane * 8;
-    const bool cok = c0 < C; // C % 8 == 0 is not required: the tail chunk is handled element-wise
     double cs[8], cq[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) cs[j] = cq[j] = 0.0;
-    const bool whole = c0 + 8 <= C;
-    for (int i0 = 0; i0 < PT_ROWS / 4; i0 += 8) { // eight rows of the wave at a time: their loads are in flight together
+    const bool whole = c0 + 8 <= C; // C % 8 == 0 is not required: what lies behind a row counts as 0
+    const int mine = (int)min((int64_t)PT_ROWS, R - r0); // rows of this block
+    for (int i0 = 0; i0 < PT_ROWS / W; i0 += 8) { // eight rows of the wave at a time: their loads are in flight together
+        if (w + W * i0 >= mine) break;
         uint4 u[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const int64_t r = r0 + w + 4 * (i0 + t);
-            u[t] = (r < R && whole) ? load_once16(S + r * ld + c0) : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int64_t r = r0 + w + 4 * (i0 + t);
-            double rs = 0.0, rq = 0.0;
-            if (r < R && cok) {
-                float e[8];
-                if (whole) {
-                    e[0] = bf16_lo(u[t].x); e[1] = bf16_hi(u[t].x); e[2] = bf16_lo(u[t].y); e[3] = bf16_hi(u[t].y);
-                    e[4] = bf16_lo(u[t].z); e[5] = bf16_hi(u[t].z); e[6] = bf16_lo(u[t].w); e[7] = bf16_hi(u[t].w);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) e[j] = c0 + j < C ? bf16_one(S[r * ld + c0 + j]) : 0.0f;
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const double x = (double)e[j], x2 = x * x;
-                    rs += x;
-                    rq += x2;
-                    cs[j] += x;
-                    cq[j] += x2;
+            const int r = w + W * (i0 + t);
+            u[t] = make_uint4(0, 0, 0, 0);
+            if (r < mine) {
+                const uint16_t *p = S + (r0 + r) * ld + c0;
+                if (whole || (c0 < C && r0 + r + 1 < R)) { // (behind a row there is the next one, or what its stride leaves)
+                    u[t] = load_once16(p);
+                } else if (c0 < C) { // the last chunk of the last row
+                    uint64_t lo = 0, hi = 0;
+#pragma nounroll
+                    for (int j = (int)(C - c0) - 1; j >= 0; --j) {
+                        hi = hi << 16 | lo >> 48;
+                        lo = lo << 16 | p[j];
+                    }
+                    u[t] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
                 }
             }
-            rs = wave_sum(rs);
-            rq = wave_sum(rq);
-            if (lane == 0 && r < R) rowpart[(int64_t)blockIdx.x * R + r] = make_double2(rs, rq);
         }
+        // number 2 t of the 16: the sum of row t, 2 t + 1: its sum of squares.  Rows t and t + 4 one after the other, their numbers
+        // halved at once, and no row begun before: more rows under way take more registers than two workgroups have.
+        double v[8];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            double n4[2][2];
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                uint32_t word[4] = {u[t + 4 * y].x, u[t + 4 * y].y, u[t + 4 * y].z, u[t + 4 * y].w};
+                if (!whole) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) word[j] &= (c0 + 2 * j < C ? 0xffffu : 0u) | (c0 + 2 * j + 1 < C ? 0xffff0000u : 0u);
+                }
+                asm volatile("" : "+v"(word[0]), "+v"(word[1]), "+v"(word[2]), "+v"(word[3]));
+                __builtin_amdgcn_sched_barrier(0);
+                double rs = 0.0, rq = 0.0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const double x = (double)(j & 1 ? bf16_hi(word[j >> 1]) : bf16_lo(word[j >> 1]));
+                    rs += x;
+                    rq = __builtin_fma(x, x, rq); // (the square is exact: fused or not, the same sums)
+                    cs[j] += x;
+                    cq[j] = __builtin_fma(x, x, cq[j]);
+                }
+                // (here, not at the end of the loop body, where the compiler would add a whole iteration's elements, kept in registers)
+                asm volatile("" : "+v"(cs[0]), "+v"(cs[1]), "+v"(cs[2]), "+v"(cs[3]), "+v"(cs[4]), "+v"(cs[5]), "+v"(cs[6]), "+v"(cs[7]));
+                asm volatile("" : "+v"(cq[0]), "+v"(cq[1]), "+v"(cq[2]), "+v"(cq[3]), "+v"(cq[4]), "+v"(cq[5]), "+v"(cq[6]), "+v"(cq[7]));
+                n4[y][0] = rs;
+                n4[y][1] = rq;
+            }
+            v[2 * t] = halve<32>(n4[0][0], n4[1][0]);
+            v[2 * t + 1] = halve<32>(n4[0][1], n4[1][1]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = halve<16>(v[k], v[k + 4]);
+        const bool b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) // lane ^ 8
+            v[k] = (b3 ? v[k + 2] : v[k]) + dpp_double<0x128>(b3 ? v[k] : v[k + 2]);
+        double s = (b2 ? v[1] : v[0]) + dpp_double<0x141>(b2 ? v[0] : v[1]); // lane ^ 7
+        s += dpp_double<0xB1>(s);                                            // lane ^ 1
+        s += dpp_double<0x4E>(s);                                            // lane ^ 2
+        // the quad q = lane / 4 holds number q of the 16
+        const int r = w + W * (i0 + (lane >> 3));
+        if ((lane & 3) == 0 && r < mine)
+            reinterpret_cast<double *>(rowpart + (int64_t)blockIdx.x * R + r0 + r)[(lane >> 2) & 1] = s;
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) scol[w][lane * 8 + j] = make_double2(cs[j], cq[j]);
+    for (int j = 0; j < 8; ++j) scol[w][64 * j + lane] = make_double2(cs[j], cq[j]);
     __syncthreads();
-    for (int c = tid; c < PT_COLS; c += 256) {
-        const int64_t cg = (int64_t)blockIdx.x * PT_COLS + c;
+    for (int k = tid; k < PT_COLS; k += 64 * W) {
+        const int64_t cg = (int64_t)blockIdx.x * PT_COLS + 8 * (k & 63) + (k >> 6);
         if (cg < C) {
-            double2 a = scol[0][c];
-            for (int v = 1; v < 4; ++v) {
-                a.x += scol[v][c].x;
-                a.y += scol[v][c].y;
+            double2 a = scol[0][k];
+#pragma unroll
+            for (int x = 1; x < W; ++x) {
+                a.x += scol[x][k].x;
+                a.y += scol[x][k].y;
             }
             colpart[(int64_t)blockIdx.y * C + cg] = a;
         }
     }
 }
 
-// part[i] <- sum over p of part[p * n + i], p ascending, for the rows (i < R, row_parts partials) and the columns.
-// One thread per index, over the whole chip: left to the one workgroup of k_pattern_finish this sum was most of
-// the detector's time (112 partials x 8192 columns x 16 bytes through one compute unit).
+// The variances of FOLD_N rows or columns: their partials part[p * n + i] added in a fixed order, eight threads per index, and the
+// block's sums of the variances and of their squares, which go to the place of the block's first partial (nobody else reads the
+// partials of these indices).  Each variance is taken over `samples` elements.  Over the whole chip: in the one workgroup of
+// k_pattern_finish these sums were most of the detector's time, and with one thread per index that walks up to 64 partials,
+// 17 us (and 17 more for the statistics of 24576 sums in one workgroup; now 5 and 4).
+constexpr int FOLD_N = 32;
 __global__ __launch_bounds__(256) void k_pattern_fold(double2 *__restrict__ rowpart, int row_parts, double2 *__restrict__ colpart,
-                                                      int col_parts, int64_t R, int64_t C)
+                                                      int col_parts, int64_t R, int64_t C, int row_blocks)
 {
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double2 *part = g < R ? rowpart : colpart;
-    const int64_t n = g < R ? R : C, i = g < R ? g : g - R;
-    const int parts = g < R ? row_parts : col_parts;
-    if (i >= n) return;
+    __shared__ double2 sums[8][FOLD_N];
+    const bool rows = (int)blockIdx.x < row_blocks;
+    double2 *part = rows ? rowpart : colpart;
+    const int64_t n = rows ? R : C, first = (int64_t)(rows ? blockIdx.x : blockIdx.x - row_blocks) * FOLD_N;
+    const double samples = (double)(rows ? C : R);
+    const int parts = rows ? row_parts : col_parts, x = threadIdx.x & (FOLD_N - 1), g = threadIdx.x / FOLD_N;
+    const int64_t i = first + x;
     double s = 0.0, q = 0.0;
-    for (int p = 0; p < parts; ++p) {
-        const double2 v = part[(int64_t)p * n + i];
-        s += v.x;
-        q += v.y;
-    }
-    part[i] = make_double2(s, q);
-}
-
-// Statistics of the variance vector of one axis: n entries, entry i = sum over `parts` partials of
-// part[p * n + i], each variance taken over `samples` elements.  Returns (mean, mean of squares) of
-// the variances through sh (block reduction, fixed order).
-__device__ void variance_stats(const double2 *__restrict__ part, int parts, int64_t n, int64_t samples, double *sh,
-                               double &mean_v, double &mean_v2)
-{
-    double a = 0.0, b = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-        double s = 0.0, q = 0.0;
-        for (int p = 0; p < parts; ++p) {
+    if (i < n) {
+#pragma unroll 4
+        for (int p = g; p < parts; p += 8) {
             const double2 v = part[(int64_t)p * n + i];
             s += v.x;
             q += v.y;
         }
-        const double m = s / (double)samples;
-        double var = q / (double)samples - m * m;
+    }
+    sums[g][x] = make_double2(s, q);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    double a = 0.0, b = 0.0;
+    if (threadIdx.x < FOLD_N && i < n) {
+#pragma unroll
+        for (int k = 1; k < 8; ++k) {
+            s += sums[k][x].x;
+            q += sums[k][x].y;
+        }
+        const double m = s / samples;
+        double var = q / samples - m * m;
         if (var < 0.0) var = 0.0;
-        a += var;
-        b += var * var;
+        a = var;
+        b = var * var;
+    }
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if (threadIdx.x == 0) part[first] = make_double2(a, b);
+}
+
+// (mean, mean of squares) of the n variances of one axis from the sums that k_pattern_fold left (block reduction through sh,
+// fixed order).
+__device__ void variance_stats(const double2 *__restrict__ part, int64_t n, double *sh, double &mean_v, double &mean_v2)
+{
+    double a = 0.0, b = 0.0;
+    for (int64_t i = (int64_t)threadIdx.x * FOLD_N; i < n; i += (int64_t)blockDim.x * FOLD_N) {
+        const double2 v = part[i];
+        a += v.x;
+        b += v.y;
     }
     a = wave_sum(a);
     b = wave_sum(b);
@@ -160,15 +246,15 @@ __device__ __forceinline__ double ratio_or_inf(double a, double b)
 }
 
 // stats_out: CV_outer, CV_k, CV^_outer, CV^_k.  rows_are_outer: the stored rows are the outer indices.
-__global__ __launch_bounds__(1024) void k_pattern_finish(const double2 *__restrict__ rowpart, int row_parts,
-                                                         const double2 *__restrict__ colpart, int col_parts, int64_t R,
+__global__ __launch_bounds__(512) void k_pattern_finish(const double2 *__restrict__ rowpart,
+                                                         const double2 *__restrict__ colpart, int64_t R,
                                                          int64_t C, int rows_are_outer, double tau, double eps,
                                                          int32_t *__restrict__ pattern_out, double *__restrict__ stats_out)
 {
     __shared__ double sh[32];
     double mr, mr2, mc, mc2;
-    variance_stats(rowpart, row_parts, R, C, sh, mr, mr2); // row variances: over the C columns
-    variance_stats(colpart, col_parts, C, R, sh, mc, mc2); // column variances: over the R rows
+    variance_stats(rowpart, R, sh, mr, mr2); // row variances: over the C columns
+    variance_stats(colpart, C, sh, mc, mc2); // column variances: over the R rows
     if (threadIdx.x == 0) {
         double sr = mr2 - mr * mr, sc = mc2 - mc * mc;
         sr = sr > 0.0 ? sqrt(sr) : 0.0;
@@ -214,15 +300,20 @@ int launch_detect_pattern(const adahop_operand_t &x, double tau, double eps, int
     pattern_geometry(x, R, C, rb, cb);
     double2 *rowpart = static_cast<double2 *>(workspace);
     double2 *colpart = reinterpret_cast<double2 *>(static_cast<char *>(workspace) + align_up((size_t)cb * R * sizeof(double2), 256));
-    hipLaunchKernelGGL(k_pattern_partial, dim3((unsigned)cb, (unsigned)rb), dim3(256), 0, st,
-                       static_cast<const uint16_t *>(x.data), x.ld, R, C, rowpart, colpart);
+    const dim3 grid((unsigned)cb, (unsigned)rb);
+    const uint16_t *d = static_cast<const uint16_t *>(x.data);
+    if (cb * rb < 256)
+        hipLaunchKernelGGL(k_pattern_partial<16>, grid, dim3(1024), 0, st, d, x.ld, R, C, rowpart, colpart);
+    else
+        hipLaunchKernelGGL(k_pattern_partial<8>, grid, dim3(512), 0, st, d, x.ld, R, C, rowpart, colpart);
     int rc = check_launch();
     if (rc != ADAHOP_OK) return rc;
-    hipLaunchKernelGGL(k_pattern_fold, dim3((unsigned)ceil_div(R + C, 256)), dim3(256), 0, st, rowpart, (int)cb, colpart, (int)rb,
-                       R, C);
+    const int row_blocks = (int)ceil_div(R, FOLD_N);
+    hipLaunchKernelGGL(k_pattern_fold, dim3((unsigned)(row_blocks + ceil_div(C, FOLD_N))), dim3(256), 0, st, rowpart, (int)cb, colpart,
+                       (int)rb, R, C, row_blocks);
     rc = check_launch();
     if (rc != ADAHOP_OK) return rc;
-    hipLaunchKernelGGL(k_pattern_finish, dim3(1), dim3(1024), 0, st, rowpart, 1, colpart, 1, R, C, x.k_contig ? 1 : 0, tau, eps,
+    hipLaunchKernelGGL(k_pattern_finish, dim3(1), dim3(512), 0, st, rowpart, colpart, R, C, x.k_contig ? 1 : 0, tau, eps,
                        pattern_out, stats_out);
     return check_launch();
 }

@@ -538,6 +538,24 @@ def test_oe_gemm_bf16_standalone(ah, M, N, K, k_row, k_col, k_k):
 
 # ----------------------------------------------------------------------------- pattern detection (App. A)
 
+@pytest.mark.parametrize("shape", [(2, 32), (37, 544), (9, 4128), (289, 1024), (4102, 8224)])
+@pytest.mark.parametrize("k_contig", [True, False])
+def test_detect_pattern_at_block_edges(ah, shape, k_contig):
+    """Fewer rows than a workgroup has waves, rows one past a block, a chunk of one column, both workgroup sizes; what lies
+    behind the rows of the stored matrix is not a number.  The bounds of the test below."""
+    outer, K = shape
+    logical = inputs.matrix(outer, K, 1.0, 9100, col_outliers=(2, 50.0, 50.0))
+    arr, width = stored(logical, k_contig)
+    wide = np.full((arr.shape[0], (width + 7) // 8 * 8 + 8), 0x7fc0, dtype=np.uint16)
+    wide[:, :width] = arr[:, :width]
+    say("detect_pattern, block edges", shape, k_contig)
+    p, st = ah.adahop_detect_pattern(ah.Operand(torch.from_numpy(wide.view(np.int16)).cuda()[:, :width], k_contig))
+    torch.cuda.synchronize()
+    want_p, want_st = orc.detect_pattern(logical, True)
+    assert int(host(p)[0]) == want_p
+    assert np.allclose(host(st), want_st, rtol=1e-9, atol=1e-12), (host(st), want_st)
+
+
 @pytest.mark.parametrize("shape", [(600, 1056), (256, 512), (1030, 288)])
 @pytest.mark.parametrize("k_contig", [True, False])
 def test_detect_pattern_matches_oracle(ah, shape, k_contig):
