@@ -93,8 +93,8 @@ static int iht_quantize_checked(const adahop_operand_t *x, int iht_block, const 
     if (!codes || !scales || !valid_iht_block(iht_block)) return ADAHOP_E_INVALID_ARG;
     if (iht_block > 0 && x->K % iht_block != 0) return ADAHOP_E_INVALID_ARG;
     if (!aligned(codes, 16) || (zero_k && !aligned(zero_k, 8))) return ADAHOP_E_INVALID_ARG;
-    return launch_iht_quantize(*x, iht_block, zero_outer, zero_k, codes, scales, static_cast<hipStream_t>(stream),
-                               sr_seed);
+    const quant_job_t job = {x, zero_outer, zero_k, codes, scales, sr_seed, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}};
+    return launch_iht_quantize(iht_block, job, static_cast<hipStream_t>(stream));
 }
 
 int adahop_iht_quantize(const adahop_operand_t *x, int iht_block, const uint8_t *zero_outer, const uint8_t *zero_k,
@@ -337,8 +337,9 @@ int adahop_pack_operand(const adahop_operand_t *x, int is_b, adahop_strategy_t s
         rc = launch_mask_from_idx(idx, k, mask_ws, dim, st);
         if (rc != ADAHOP_OK) return rc;
     }
-    return launch_iht_quantize(*x, b, masked && kind == 1 ? mask_ws : nullptr, masked && kind == 2 ? mask_ws : nullptr,
-                               codes, scales, st);
+    const quant_job_t job = {x, masked && kind == 1 ? mask_ws : nullptr, masked && kind == 2 ? mask_ws : nullptr, codes, scales,
+                             nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}};
+    return launch_iht_quantize(b, job, st);
 }
 
 int adahop_oht_quantize(const adahop_operand_t *x, int oht_block, uint8_t *codes, uint8_t *scales, void *stream)
@@ -400,16 +401,28 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     float *scores = reinterpret_cast<float *>(ws + L.scores);
 
     // 1. which rows / columns / K-channels leave the MXFP4 path (App. F item 1)
+    const bool oe_k = oe && strategy == ADAHOP_IHT_OE_K;
+    const int kpad_planned = oe_k ? kpad_of(k) : 0;
+    // The quantiser that reads an extracted operand anyway also copies the extracted part out for the bf16 product; the position of
+    // a row or channel in the index list comes from a 16-bit table that the selection leaves in the place of the scores, which
+    // nobody reads after it.  Only for indices selected here, which are distinct: a repeated index in a caller's list would
+    // leave a position of the copy unwritten, where the separate gather reads the row twice.
+    const bool fuse = oe && !use_given_idx && foid_writes_positions(dim, k);
+    const bool a_gathers_k = fuse && oe_k && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
+    const bool b_gathers_k = fuse && oe_k && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
+    const bool a_gathers_rows = fuse && strategy == ADAHOP_IHT_OE_ROW && !a_given;
+    const bool b_gathers_rows = fuse && strategy == ADAHOP_IHT_OE_COL && !b_given;
+    uint16_t *pos1 = a_gathers_k || b_gathers_k || a_gathers_rows || b_gathers_rows ? reinterpret_cast<uint16_t *>(scores) : nullptr;
     if (oe) {
         const bool mask_used = (!a_given && a_kind) || (!b_given && b_kind);
         if (use_given_idx) {
             rc = mask_used ? launch_mask_from_idx(idx_inout, k, mask, dim, st) : ADAHOP_OK;
         } else if (strategy == ADAHOP_IHT_OE_ROW) {
-            rc = launch_foid_topk(*A, 0, k, idx_inout, mask, scores, st);
+            rc = launch_foid_topk(*A, 0, k, idx_inout, mask, scores, st, pos1);
         } else if (strategy == ADAHOP_IHT_OE_COL) {
-            rc = launch_foid_topk(*B, 0, k, idx_inout, mask, scores, st);
+            rc = launch_foid_topk(*B, 0, k, idx_inout, mask, scores, st, pos1);
         } else {
-            rc = launch_foid_topk(*A, 1, k, idx_inout, mask, scores, st);
+            rc = launch_foid_topk(*A, 1, k, idx_inout, mask, scores, st, pos1);
         }
         if (rc != ADAHOP_OK) return rc;
     }
@@ -420,50 +433,34 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const uint8_t *b_scales = b_given ? opts->b_scales : reinterpret_cast<uint8_t *>(ws + L.b_scales);
     // The GEMM kernels read the scales in a stage-major copy; the quantisers that run here write it
     // beside the canonical one, which saves the product its two re-ordering launches.
-    const int kpad_planned = oe && strategy == ADAHOP_IHT_OE_K ? kpad_of(k) : 0;
-    const bool sm_wanted = !oht;
-    // K-channel extraction: a quantiser that runs here on a K-contiguous operand also copies the extracted channels
-    // out (it has the row in registers); the position of a channel in the index list comes from a 16-bit table that
-    // takes the place of the scores, which nobody reads after the selection.
-    // Only for indices selected here, which are distinct: a repeated index in a caller's list would leave a position
-    // of the copy unwritten, where the separate gather reads the channel twice.
-    const bool oe_k = oe && strategy == ADAHOP_IHT_OE_K, fuse = oe_k && !use_given_idx;
-    const bool a_gathers = fuse && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
-    const bool b_gathers = fuse && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
-    k_gather_t ga = {nullptr, nullptr, 0, 0}, gb = ga;
-    if (a_gathers || b_gathers) {
-        uint16_t *pos1 = reinterpret_cast<uint16_t *>(scores);
-        rc = launch_k_positions(idx_inout, k, mask, K, pos1, st);
-        if (rc != ADAHOP_OK) return rc;
-        if (a_gathers) ga = k_gather_t{pos1, reinterpret_cast<uint16_t *>(ws + L.gather_a), k, kpad_planned};
-        if (b_gathers) gb = k_gather_t{pos1, reinterpret_cast<uint16_t *>(ws + L.gather_b), k, kpad_planned};
+    uint16_t *gather_a = reinterpret_cast<uint16_t *>(ws + L.gather_a), *gather_b = reinterpret_cast<uint16_t *>(ws + L.gather_b);
+    const k_gather_t no_k = {nullptr, nullptr, 0, 0};
+    const row_gather_t no_rows = {nullptr, nullptr}, rows = {pos1, gather_a}; // (the row / column product has one workspace)
+    const quant_job_t ja = {A, a_kind == 1 ? mask : nullptr, a_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.a_codes),
+                            reinterpret_cast<uint8_t *>(ws + L.a_scales), opts && opts->sr_a ? &opts->sr_seed_a : nullptr,
+                            {gemm_mx_scales_sm(ws + L.gemm, M, K, 0), M},
+                            a_gathers_k ? k_gather_t{pos1, gather_a, k, kpad_planned} : no_k, a_gathers_rows ? rows : no_rows};
+    const quant_job_t jb = {B, b_kind == 1 ? mask : nullptr, b_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.b_codes),
+                            reinterpret_cast<uint8_t *>(ws + L.b_scales), opts && opts->sr_b ? &opts->sr_seed_b : nullptr,
+                            {gemm_mx_scales_sm(ws + L.gemm, M, K, 1), N},
+                            b_gathers_k ? k_gather_t{pos1, gather_b, k, kpad_planned} : no_k, b_gathers_rows ? rows : no_rows};
+    const int sm_ready = oht ? 0 : (a_given ? 0 : 1) | (b_given ? 0 : 2);
+    if (oht) {
+        if (!a_given) rc = launch_oht_quantize(*A, b, ja.codes, ja.scales, st);
+        if (rc == ADAHOP_OK && !b_given) rc = launch_oht_quantize(*B, b, jb.codes, jb.scales, st);
+    } else if (!a_given && !b_given) {
+        rc = launch_iht_quantize_two(b, ja, jb, st);
+    } else if (!a_given || !b_given) {
+        rc = launch_iht_quantize(b, a_given ? jb : ja, st);
     }
-    int sm_ready = 0;
-    if (!a_given) {
-        uint8_t *c = reinterpret_cast<uint8_t *>(ws + L.a_codes), *s = reinterpret_cast<uint8_t *>(ws + L.a_scales);
-        const scales_sm_t sm = {sm_wanted ? gemm_mx_scales_sm(ws + L.gemm, M, K, 0) : nullptr, M};
-        rc = oht ? launch_oht_quantize(*A, b, c, s, st)
-                 : launch_iht_quantize(*A, b, a_kind == 1 ? mask : nullptr, a_kind == 2 ? mask : nullptr, c, s, st,
-                                       opts && opts->sr_a ? &opts->sr_seed_a : nullptr, &sm, &ga);
-        if (rc != ADAHOP_OK) return rc;
-        if (sm.out) sm_ready |= 1;
-    }
-    if (!b_given) {
-        uint8_t *c = reinterpret_cast<uint8_t *>(ws + L.b_codes), *s = reinterpret_cast<uint8_t *>(ws + L.b_scales);
-        const scales_sm_t sm = {sm_wanted ? gemm_mx_scales_sm(ws + L.gemm, M, K, 1) : nullptr, N};
-        rc = oht ? launch_oht_quantize(*B, b, c, s, st)
-                 : launch_iht_quantize(*B, b, b_kind == 1 ? mask : nullptr, b_kind == 2 ? mask : nullptr, c, s, st,
-                                       opts && opts->sr_b ? &opts->sr_seed_b : nullptr, &sm, &gb);
-        if (rc != ADAHOP_OK) return rc;
-        if (sm.out) sm_ready |= 2;
-    }
+    if (rc != ADAHOP_OK) return rc;
     // 3. MXFP4 product, with the K-channel BF16 product fused in front; 4. row / column BF16 product
     if (oe_k) {
         const int kpad = kpad_planned;
-        uint16_t *Ag = reinterpret_cast<uint16_t *>(ws + L.gather_a), *Bg = reinterpret_cast<uint16_t *>(ws + L.gather_b);
-        rc = a_gathers ? ADAHOP_OK : launch_gather_k(*A, idx_inout, k, kpad, Ag, st);
+        uint16_t *Ag = gather_a, *Bg = gather_b;
+        rc = a_gathers_k ? ADAHOP_OK : launch_gather_k(*A, idx_inout, k, kpad, Ag, st);
         if (rc != ADAHOP_OK) return rc;
-        rc = b_gathers ? ADAHOP_OK : launch_gather_k(*B, idx_inout, k, kpad, Bg, st);
+        rc = b_gathers_k ? ADAHOP_OK : launch_gather_k(*B, idx_inout, k, kpad, Bg, st);
         if (rc != ADAHOP_OK) return rc;
         return launch_gemm_mx(M, N, K, a_codes, a_scales, b_codes, b_scales, C, ldc, c_bf16, Ag, Bg, kpad, ws + L.gemm, st,
                               sm_ready);
@@ -472,7 +469,7 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
                         sm_ready);
     if (rc != ADAHOP_OK) return rc;
     if (oht) return launch_oht_inverse(static_cast<float *>(C), M, N, ldc, b, st); // the rotations after the product (Eq. 6)
-    if (oe) rc = launch_oe_rowcol(*A, *B, strategy, idx_inout, k, C, ldc, c_bf16, ws + L.gather_a, st);
+    if (oe) rc = launch_oe_rowcol(*A, *B, strategy, idx_inout, k, C, ldc, c_bf16, gather_a, st, a_gathers_rows || b_gathers_rows);
     return rc;
 }
 

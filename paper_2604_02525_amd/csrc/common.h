@@ -51,18 +51,31 @@ struct k_gather_t {
     uint16_t *out;        // nullptr: no copy
     int k, kpad;
 };
-// Whether launch_iht_quantize honours a k_gather_t for this operand (K-contiguous, whole passes of a workgroup
-// along K, a copy that fits its LDS staging).
+// The extracted rows of an operand (outer indices), copied out in the same way: out[pos1[o] - 1, :] = x(o, :) for every o with
+// pos1[o] != 0, which count as zero in the quantisation.  out is [k, K] bf16.
+struct row_gather_t {
+    const uint16_t *pos1; // per outer index
+    uint16_t *out;        // nullptr: no copy
+};
+// Whether launch_iht_quantize honours a k_gather_t for this operand (K-contiguous, a copy that fits its LDS staging).
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad);
-// pos1[c] = t + 1 where c = idx[t], 0 where mask[c] == 0 (mask as launch_foid_topk / launch_mask_from_idx leave it).
-int launch_k_positions(const int32_t *idx, int k, const uint8_t *mask, int64_t K, uint16_t *pos1, hipStream_t st);
-// sr_seed: NULL = round to nearest even; else the elements are rounded stochastically under that seed.
-int launch_iht_quantize(const adahop_operand_t &x, int iht_block, const uint8_t *zero_outer,
-                        const uint8_t *zero_k, uint8_t *codes, uint8_t *scales, hipStream_t st,
-                        const uint64_t *sr_seed = nullptr, const scales_sm_t *sm = nullptr,
-                        const k_gather_t *gather = nullptr);
+// One operand to quantise.
+struct quant_job_t {
+    const adahop_operand_t *x;
+    const uint8_t *zero_outer, *zero_k; // byte masks or nullptr; gk goes with the zero_k of the same channels, gr takes the place of zero_outer
+    uint8_t *codes, *scales;
+    const uint64_t *sr_seed;            // nullptr = round to nearest even; else the elements are rounded stochastically under that seed
+    scales_sm_t sm;                     // out = nullptr: no second copy
+    k_gather_t gk;
+    row_gather_t gr;
+};
+int launch_iht_quantize(int iht_block, const quant_job_t &job, hipStream_t st);
+int launch_iht_quantize_two(int iht_block, const quant_job_t &a, const quant_job_t &b, hipStream_t st); // both of a product
+// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere; it may lie where scores lies.  Only where
+// foid_writes_positions holds.
+bool foid_writes_positions(int64_t dim, int k);
 int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, uint8_t *mask, float *scores,
-                     hipStream_t st);
+                     hipStream_t st, uint16_t *pos1 = nullptr);
 // Device address, on the current device, of the library's built-in score scratch (ADAHOP_FOID_NOALLOC_MAX_DIM floats).
 int foid_static_scores(float **out);
 int launch_mask_from_idx(const int32_t *idx, int k, uint8_t *mask, int64_t dim, hipStream_t st);
@@ -93,8 +106,9 @@ int launch_gather_k(const adahop_operand_t &x, const int32_t *idx, int k, int kp
 // C is float[M, ldc], or bf16[M, ldc] when c_bf16 is set (here and in launch_oe_rowcol).
 // Row / column outlier product; workspace of oe_rowcol_workspace_bytes() bytes, 256-byte aligned.
 size_t oe_rowcol_workspace_bytes(int64_t M, int64_t N, int64_t K, int kind, int k);
+// gathered: the extracted rows lie at the start of the workspace already, [k, K] (a quantiser has copied them out).
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
-                     void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st);
+                     void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered = false);
 int launch_oe_k_accumulate(int64_t M, int64_t N, const uint16_t *Ag, const uint16_t *Bg, int kpad, float *C,
                            int64_t ldc, hipStream_t st);
 

@@ -244,8 +244,10 @@ constexpr int topk_per_wave(int n) { return ((n + TOPK_WAVES - 1) / TOPK_WAVES +
 constexpr size_t topk_lds_bytes(int dim) { return (size_t)topk_per_wave(dim) * TOPK_WAVES * 4 + sizeof(topk_shared_t); }
 static_assert(topk_lds_bytes(TOPK_LDS_KEYS) <= 160 * 1024, "keys, histograms and candidates share one compute unit's LDS");
 
-__global__ __launch_bounds__(TOPK_THREADS) void k_topk_lds(const float *__restrict__ scores, int dim, int k,
-                                                           int32_t *__restrict__ idx, uint8_t *__restrict__ mask)
+// pos1 (or nullptr): the position in idx + 1 of every selected index, 0 for the others; it may lie in the memory of the scores,
+// which nobody reads any more once the keys are in LDS.
+__global__ __launch_bounds__(TOPK_THREADS) void k_topk_lds(const float *scores, int dim, int k, int32_t *__restrict__ idx,
+                                                           uint8_t *__restrict__ mask, uint16_t *pos1)
 {
     extern __shared__ __align__(16) uint32_t skeys[]; // per * TOPK_WAVES keys, then topk_shared_t
     const int tid = threadIdx.x, lane = tid & 63;
@@ -317,6 +319,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk_lds(const float *__restri
     if (maxima) sh.cand[tid] = tmax;
     if (tid < 512) sh.hist[0][tid] = 0; // (both histograms)
     __syncthreads();
+    if (pos1) // every wave has its keys
+        for (int i = tid; i < (dim + 1) / 2; i += TOPK_THREADS) reinterpret_cast<uint32_t *>(pos1)[i] = 0u;
     int pass = 0;
     uint32_t T = 0, T0 = 0, remaining = (uint32_t)k;
     const uint64_t below = ((uint64_t)1 << lane) - 1;
@@ -466,8 +470,10 @@ __global__ __launch_bounds__(TOPK_THREADS) void k_topk_lds(const float *__restri
         // selected entries before this one: every greater key, and the equal keys that were taken
         if (is_gt || (is_eq && my_eq < remaining)) {
             const int index = direct ? i : (int)sh.cand_i[i];
-            idx[my_gt + min(my_eq, remaining)] = index;
+            const uint32_t at = my_gt + min(my_eq, remaining);
+            idx[at] = index;
             mask[index] = 1;
+            if (pos1) pos1[index] = (uint16_t)(at + 1);
         }
         gt_before += (uint32_t)__popcll(m_gt);
         eq_before += (uint32_t)__popcll(m_eq);
@@ -502,8 +508,10 @@ int configure_foid()
     return ADAHOP_OK;
 }
 
+bool foid_writes_positions(int64_t dim, int k) { return dim <= (int64_t)TOPK_LDS_KEYS && k > 0 && k <= 0xffff; }
+
 int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, uint8_t *mask, float *scores,
-                     hipStream_t st)
+                     hipStream_t st, uint16_t *pos1)
 {
     const int64_t dim = axis == 0 ? x.outer : x.K;
     const int64_t len = axis == 0 ? x.K : x.outer;
@@ -518,7 +526,7 @@ int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, u
         rc = configure_foid(); // more LDS than a launch may ask for by default: allowed once per device
         if (rc != ADAHOP_OK) return rc;
         hipLaunchKernelGGL(k_topk_lds, dim3(1), dim3(TOPK_THREADS), topk_lds_bytes((int)dim), st, scores, (int)dim, k, idx,
-                           mask);
+                           mask, pos1);
     } else {
         hipLaunchKernelGGL(k_topk, dim3(1), dim3(TOPK_THREADS), 0, st, scores, (int)dim, k, idx, mask);
     }

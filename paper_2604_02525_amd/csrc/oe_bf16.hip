@@ -476,25 +476,6 @@ __global__ __launch_bounds__(256) void k_gather_k_strided(const uint16_t *__rest
 
 } // namespace
 
-// The first K threads clear the entries of the channels that stay, the next k set those of the extracted ones:
-// no entry is written twice.
-__global__ __launch_bounds__(256) void k_positions(const int32_t *__restrict__ idx, int k, const uint8_t *__restrict__ mask,
-                                                   int64_t K, uint16_t *__restrict__ pos1)
-{
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g < K) {
-        if (!mask[g]) pos1[g] = 0;
-    } else if (g < K + k) {
-        pos1[idx[g - K]] = (uint16_t)(g - K + 1);
-    }
-}
-
-int launch_k_positions(const int32_t *idx, int k, const uint8_t *mask, int64_t K, uint16_t *pos1, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_positions, dim3((unsigned)ceil_div(K + k, 256)), dim3(256), 0, st, idx, k, mask, K, pos1);
-    return check_launch();
-}
-
 int launch_gather_k(const adahop_operand_t &x, const int32_t *idx, int k, int kpad, uint16_t *out, hipStream_t st)
 {
     const int64_t n = x.outer * kpad;
@@ -533,7 +514,7 @@ size_t oe_rowcol_workspace_bytes(int64_t M, int64_t N, int64_t K, int kind, int 
 }
 
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
-                     void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st)
+                     void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered)
 {
     const int64_t M = A.outer, N = B.outer, K = A.K;
     if (k == 0 || M == 0 || N == 0) return ADAHOP_OK;
@@ -544,7 +525,11 @@ int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int k
     uint16_t *Sg = static_cast<uint16_t *>(workspace);
     float *P = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.sg_bytes);
 
-    if (S.k_contig)
+    // (rows of Sg past the k extracted ones may hold anything: row t of the product depends on row t alone, and the reduction
+    // reads the first k)
+    if (gathered)
+        ;
+    else if (S.k_contig)
         hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)ceil_div(p.rows_all * (K >> 3), 256)), dim3(256), 0, st,
                            static_cast<const uint16_t *>(S.data), S.ld, K, idx, k, (int)p.rows_all, Sg);
     else // rows_all is a multiple of 64: whole tiles of extracted columns

@@ -322,65 +322,91 @@ __device__ __forceinline__ void store_codes_scales(uint8_t *codes, uint8_t *scal
     }
 }
 
-// K-contiguous operand: 16 lanes per 256 K-elements of a row.  FLAT = 0: blockIdx.x is the row, blockIdx.y and the
-// thread its units; FLAT = 1 (short rows): the units of all rows are numbered consecutively.  TAIL: K % 256 != 0 (an
-// instance of its own, because the conditions of a shorter last unit cost the others 2 %).
-template <int B, int FLAT, bool SR, bool TAIL>
-__global__ __launch_bounds__(256) void k_quant_kc16(const uint16_t *__restrict__ x, int64_t outer, int64_t K,
-                                                    int64_t ld, const uint8_t *__restrict__ zero_outer,
-                                                    const uint8_t *__restrict__ zero_k,
-                                                    uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
-                                                    sr_key_t key, scales_sm_t sm)
+__device__ __forceinline__ uint32_t row_of_unit(uint32_t u, uint32_t upr, uint32_t magic)
 {
-    const uint32_t upr = (uint32_t)((K + 255) >> 8); // 256-element units per row
-    int64_t row;
-    uint32_t unit;
-    bool active;
-    if constexpr (FLAT) {
-        const uint32_t u = (blockIdx.x * 256u + threadIdx.x) >> 4;
-        const uint32_t r = u / upr;
-        row = r;
-        unit = u - r * upr;
-        active = row < outer;
-    } else {
-        row = blockIdx.x;
-        unit = (blockIdx.y * 256u + threadIdx.x) >> 4;
-        active = unit < upr;
-    }
+    return upr == 1 ? u : __umulhi(u, magic); // u / upr, exact for u upr < 2^32
+}
+
+// One operand's quantisation: what is read, which entries count as zero and where the results go.
+struct quant_t {
+    const uint16_t *x;
+    int64_t outer, K, ld;
+    const uint8_t *zero_outer, *zero_k;
+    uint8_t *codes, *scales;
+    sr_key_t key;
+    scales_sm_t sm;
+    k_gather_t gk;
+    row_gather_t gr;
+    uint32_t upr, magic;  // 256-element units per row (K-strided: K-blocks); ceil(2^32 / upr)
+    uint32_t rows_per_wg; // of the kernel that copies K-channels
+    uint32_t col_tiles, tile_magic, group; // K-strided: workgroups along the outer index, ceil(2^32 / col_tiles); order, see there
+};
+
+// K-contiguous operand: 16 lanes per 256 K-elements of a row, unit `unit` of row `row`.  TAIL: K % 256 != 0 (an instance of
+// its own, because the conditions of a shorter last unit cost the others 2 %).
+// An outer index that is extracted (q.gr) leaves the quantiser as it came, for the bf16 product of the extracted rows, and
+// counts as zero here: the copy is made where the row is in registers anyway, in place of a launch that reads it again.
+template <int B, bool SR, bool TAIL>
+__device__ __forceinline__ void quant_kc_unit(const quant_t &q, int64_t row, uint32_t unit, bool active)
+{
+    const int64_t K = q.K;
     const lane_plan_t plan = make_plan<B>(threadIdx.x & 63);
     const int64_t k0 = (int64_t)unit * 256, kk = k0 + plan.chunk * 8;
     const bool in0 = active && (!TAIL || kk < K), in1 = active && (!TAIL || kk + 128 < K);
 
     uint4 r0 = make_uint4(0, 0, 0, 0), r1 = make_uint4(0, 0, 0, 0);
-    if (active) { // the row's mask byte travels with the data (1 % of the rows are read for nothing) instead of ahead of it
-        const uint16_t *src = x + row * ld + kk;
+    if (active) { // the row's mask travels with the data (1 % of the rows are read for nothing) instead of ahead of it
+        const uint16_t *src = q.x + row * q.ld + kk;
         if (!TAIL || in0) r0 = load_once16(src);
         if (!TAIL || in1) r1 = load_once16(src + 128);
-        if (zero_outer && zero_outer[row]) r0 = r1 = make_uint4(0, 0, 0, 0);
+        if (q.gr.out) {
+            const uint32_t p = q.gr.pos1[row];
+            if (p) {
+                uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + kk;
+                if (!TAIL || in0) *reinterpret_cast<uint4 *>(dst) = r0;
+                if (!TAIL || in1) *reinterpret_cast<uint4 *>(dst + 128) = r1;
+                r0 = r1 = make_uint4(0, 0, 0, 0);
+            }
+        } else if (q.zero_outer && q.zero_outer[row]) {
+            r0 = r1 = make_uint4(0, 0, 0, 0);
+        }
     }
     float w0[8] = {bf16_lo(r0.x), bf16_hi(r0.x), bf16_lo(r0.y), bf16_hi(r0.y),
                    bf16_lo(r0.z), bf16_hi(r0.z), bf16_lo(r0.w), bf16_hi(r0.w)};
     float w1[8] = {bf16_lo(r1.x), bf16_hi(r1.x), bf16_lo(r1.y), bf16_hi(r1.y),
                    bf16_lo(r1.z), bf16_hi(r1.z), bf16_lo(r1.w), bf16_hi(r1.w)};
-    if (zero_k && active) {
+    if (q.zero_k && active) {
         uint64_t z0 = 0, z1 = 0;
-        if (!TAIL || in0) z0 = *reinterpret_cast<const uint64_t *>(zero_k + kk);
-        if (!TAIL || in1) z1 = *reinterpret_cast<const uint64_t *>(zero_k + kk + 128);
+        if (!TAIL || in0) z0 = *reinterpret_cast<const uint64_t *>(q.zero_k + kk);
+        if (!TAIL || in1) z1 = *reinterpret_cast<const uint64_t *>(q.zero_k + kk + 128);
         apply_k_mask(w0, z0);
         apply_k_mask(w1, z1);
     }
     uint32_t c0, c1;
     int s0, s1;
-    transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, key, row, kk, kk + 128);
-    if (active) store_codes_scales<TAIL>(codes, scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, sm);
+    transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, q.key, row, kk, kk + 128);
+    if (active) store_codes_scales<TAIL>(q.codes, q.scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, q.sm);
+}
+
+// FLAT = 0: blockIdx.x is the row, blockIdx.y and the thread its units; FLAT = 1 (short rows): the units of all rows are
+// numbered consecutively.
+template <int B, int FLAT, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_quant_kc16(quant_t q)
+{
+    if constexpr (FLAT) {
+        const uint32_t u = (blockIdx.x * 256u + threadIdx.x) >> 4, r = u / q.upr;
+        quant_kc_unit<B, SR, TAIL>(q, r, u - r * q.upr, r < q.outer);
+    } else {
+        const uint32_t unit = (blockIdx.y * 256u + threadIdx.x) >> 4;
+        quant_kc_unit<B, SR, TAIL>(q, blockIdx.x, unit, unit < q.upr);
+    }
 }
 
 // The same with the extracted K-channels copied out on the way (Eq. 7 with S a set of K-channels).  One workgroup
-// takes a whole row, 4096 K-elements per pass.  In place of the byte mask it reads a 16-bit table, position in the
-// index list + 1 for an extracted channel and 0 for the others, with the operand (one more coalesced load, no
-// dependent look-ups); the extracted elements it meets go to those positions of a copy of the row's extracted part
-// in LDS, which leaves for memory at the end in whole 16-byte pieces; they are cleared in the raw bf16 pairs with three
-// packed 16-bit instructions per pair.
+// takes whole rows, 4096 K-elements per pass: one row, or as many shorter ones as fill a pass.  In place of the byte mask it reads
+// a 16-bit table, position in the index list + 1 for an extracted channel and 0 for the others, with the operand (one more
+// coalesced load, no dependent look-ups); the extracted elements it meets go to those positions of a copy of the row's
+// extracted part in LDS, which leaves for memory at the end in whole 16-byte pieces; they are cleared in the raw bf16 pairs
+// with three packed 16-bit instructions per pair.
 // (Two variants were measured on 16384 x 28672 at 1 % and made the quantiser half again as slow, more than the
 // separate gather kernel costs: 2-byte stores straight into the copy, and a look-up of the position in a 32-bit
 // table under the branch that an extracted element takes -- a chain of dependent loads in nearly every wave.
@@ -388,28 +414,36 @@ __global__ __launch_bounds__(256) void k_quant_kc16(const uint16_t *__restrict__
 // with the next pass's loads issued ahead, it took the same time; without the table loads 4 .. 37 us of the 14 .. 50
 // go away, most on the 57 KB table of K = 28672, which every workgroup reads whole.)
 constexpr int KC_GATHER_MAX_KPAD = 4096;
+constexpr int KC_GATHER_LDS = (8 + KC_GATHER_MAX_KPAD) * 2; // bytes: the copies of the rows, kpad + 8 elements each
 
-template <int B, bool SR>
-__global__ __launch_bounds__(256) void k_quant_kc16_gather(const uint16_t *__restrict__ x, int64_t K, int64_t ld,
-                                                           uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
-                                                           sr_key_t key, scales_sm_t sm, k_gather_t gk)
+template <int B, bool SR, bool TAIL>
+__device__ __forceinline__ void quant_kc_gather_rows(const quant_t &q, uint32_t block, uint8_t *lds_bytes)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t lds[8 + KC_GATHER_MAX_KPAD];
-    uint16_t *slot = lds + KC_GATHER_SLOT0, *part = lds + 8; // part[t] = slot[t + 1]
-    const uint32_t upr = (uint32_t)(K >> 8);
-    const int64_t row = blockIdx.x;
+    uint16_t *lds = reinterpret_cast<uint16_t *>(lds_bytes);
+    const k_gather_t gk = q.gk;
+    const int64_t K = q.K, row0 = (int64_t)block * q.rows_per_wg;
+    const int nrows = (int)min((int64_t)q.rows_per_wg, q.outer - row0), per = gk.kpad + 8;
     const lane_plan_t plan = make_plan<B>(threadIdx.x & 63);
-    for (int p = gk.k + threadIdx.x; p < gk.kpad; p += 256) part[p] = 0;
-    for (uint32_t u0 = 0; u0 < upr; u0 += 16) {
-        const uint32_t unit = u0 + (threadIdx.x >> 4);
-        const bool active = unit < upr;
-        const int64_t k0 = (int64_t)unit * 256, kk = k0 + plan.chunk * 8;
+    for (int r = 0; r < nrows; ++r)
+        for (int p = gk.k + threadIdx.x; p < gk.kpad; p += 256) lds[r * per + 8 + p] = 0;
+    for (uint32_t u0 = 0; u0 < q.upr; u0 += 16) {
+        uint32_t unit = u0 + (threadIdx.x >> 4), r = 0;
+        if (q.rows_per_wg > 1) { // (one pass)
+            r = row_of_unit(unit, q.upr, q.magic);
+            unit -= r * q.upr;
+        }
+        const bool active = (int)r < nrows && unit < q.upr;
+        const int64_t row = row0 + r, k0 = (int64_t)unit * 256, kk = k0 + plan.chunk * 8;
+        const bool in0 = active && (!TAIL || kk < K), in1 = active && (!TAIL || kk + 128 < K);
+        uint16_t *slot = lds + r * per + KC_GATHER_SLOT0;
         uint4 r0 = make_uint4(0, 0, 0, 0), r1 = r0, p0 = r0, p1 = r0;
-        if (active) {
-            const uint16_t *src = x + row * ld + kk;
+        const uint16_t *src = q.x + row * q.ld + kk;
+        if (in0) {
             r0 = load_once16(src);
-            r1 = load_once16(src + 128);
             p0 = *reinterpret_cast<const uint4 *>(gk.pos1 + kk);
+        }
+        if (in1) {
+            r1 = load_once16(src + 128);
             p1 = *reinterpret_cast<const uint4 *>(gk.pos1 + kk + 128);
         }
         if (p0.x | p0.y | p0.z | p0.w) scatter_extracted(r0, p0, slot);
@@ -422,13 +456,21 @@ __global__ __launch_bounds__(256) void k_quant_kc16_gather(const uint16_t *__res
                        bf16_lo(r1.z), bf16_hi(r1.z), bf16_lo(r1.w), bf16_hi(r1.w)};
         uint32_t c0, c1;
         int s0, s1;
-        transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, key, row, kk, kk + 128);
-        if (active) store_codes_scales<false>(codes, scales, row, K, k0, plan.chunk, true, true, c0, c1, s0, s1, sm);
+        transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, q.key, row, kk, kk + 128);
+        if (active) store_codes_scales<TAIL>(q.codes, q.scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, q.sm);
     }
     __syncthreads();
-    uint16_t *dst = gk.out + row * gk.kpad;
-    for (int p = threadIdx.x * 8; p < gk.kpad; p += 256 * 8)
-        *reinterpret_cast<uint4 *>(dst + p) = *reinterpret_cast<const uint4 *>(part + p);
+    for (int r = 0; r < nrows; ++r) {
+        uint16_t *dst = gk.out + (row0 + r) * gk.kpad;
+        for (int p = threadIdx.x * 8; p < gk.kpad; p += 256 * 8)
+            *reinterpret_cast<uint4 *>(dst + p) = *reinterpret_cast<const uint4 *>(lds + r * per + 8 + p);
+    }
+}
+
+template <int B, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_quant_kc16_gather(quant_t q)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[KC_GATHER_LDS];
+    quant_kc_gather_rows<B, SR, TAIL>(q, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -491,38 +533,19 @@ template <bool XOR7> __device__ __forceinline__ void cross_stage64(float (&w)[64
 
 __device__ __forceinline__ uint32_t rot16(uint32_t v) { return __builtin_amdgcn_alignbit(v, v, 16); }
 
+constexpr int KS_LDS = 256 * KT_PITCH + 256; // bytes: the tile and the K-mask of its rows
+
 template <int B, bool SR>
-__global__ __launch_bounds__(256) void k_quant_ks16(const uint16_t *__restrict__ x, int64_t outer, int64_t K,
-                                                    int64_t ld, const uint8_t *__restrict__ zero_outer,
-                                                    const uint8_t *__restrict__ zero_k,
-                                                    uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
-                                                    sr_key_t key, scales_sm_t sm, unsigned group)
+__device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uint32_t by, uint8_t *lds)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t tile[256 * KT_PITCH];
-    __shared__ uint8_t kmask[256];
+    uint8_t *tile = lds, *kmask = lds + 256 * KT_PITCH;
+    const uint16_t *x = q.x;
+    const int64_t outer = q.outer, K = q.K, ld = q.ld;
+    const uint8_t *zero_outer = q.gr.out ? nullptr : q.zero_outer, *zero_k = q.zero_k;
+    uint8_t *codes = q.codes, *scales = q.scales;
+    const scales_sm_t sm = q.sm;
+    const sr_key_t key = q.key;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // Workgroups start in the order of their linear index, x fastest.  Taken as it is, that order runs all column
-    // tiles of one K-block before the next K-block: the workgroups in flight together then write 128-byte pieces of
-    // thousands of different output rows.  Instead the index walks KS_GROUP neighbouring column tiles through all
-    // K-blocks before it moves to the next group: the reads still come in pieces of KS_GROUP x 128 bytes of a K-row, and
-    // an output row is written in one go.  Measured: operands with rows of 28672 elements (448 column tiles: the
-    // about 1000 workgroups in flight span two K-blocks, 300 bytes of an output row) 292 -> 237 us ([16384][28672])
-    // and 133 -> 122 us ([8192][28672]); 384, 320 and 224 column tiles 11 .. 13 % faster; 256 column tiles 7 % faster
-    // or 5 % slower by K; with 192 column tiles and fewer the plain order is as fast or up to 10 % faster and is kept
-    // (group == 0).
-    unsigned bx = blockIdx.x, by = blockIdx.y;
-    if (group) {
-        const uint64_t nx = gridDim.x, ny = gridDim.y, L = by * nx + bx, full = nx / group * group;
-        if (L < full * ny) {
-            const uint64_t r = L % (group * ny);
-            bx = (unsigned)(L / (group * ny) * group + r % group);
-            by = (unsigned)(r / group);
-        } else { // the last, narrower group
-            const uint64_t r = L - full * ny, wdt = nx - full;
-            bx = (unsigned)(full + r % wdt);
-            by = (unsigned)(r / wdt);
-        }
-    }
     const int64_t o0 = (int64_t)bx * KS_COLS, k0 = (int64_t)by * 256;
 
     // ---- global -> LDS: a pass is 32 K-rows x 64 columns; lane: 8 columns (cg) of one of the wave's 8 rows.  A group
@@ -593,6 +616,26 @@ __global__ __launch_bounds__(256) void k_quant_ks16(const uint16_t *__restrict__
     const int col = 16 * w + 4 * g + ((m & 1) ? 3 - e : e);
     const int64_t o = o0 + col;
     const bool active = o < outer;
+
+    // ---- an extracted column leaves as it came and counts as zero here: the lane has 64 of its K-elements in a row
+    // (as a launch of its own that reads two bytes of every K-row, this copy took 31 us for 64 columns x 32768)
+    if (q.gr.out) {
+        const uint32_t p = active ? q.gr.pos1[o] : 0u;
+        if (p) {
+            uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + k0 + 64 * m;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (k0 + 64 * m + 8 * i < K) {
+                    uint32_t d[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        d[j] = __builtin_amdgcn_perm(__float_as_uint(wv[8 * i + 2 * j + 1]), __float_as_uint(wv[8 * i + 2 * j]), 0x07060302u);
+                    *reinterpret_cast<uint4 *>(dst + 8 * i) = make_uint4(d[0], d[1], d[2], d[3]);
+                }
+#pragma unroll
+            for (int i = 0; i < 64; ++i) wv[i] = 0.0f;
+        }
+    }
 
     // ---- transform
     if constexpr (B > 0) {
@@ -686,86 +729,207 @@ __global__ __launch_bounds__(256) void k_quant_ks16(const uint16_t *__restrict__
     }
 }
 
-template <int B, bool SR>
-int launch_kc(const adahop_operand_t &x, const uint8_t *zo, const uint8_t *zk, uint8_t *codes, uint8_t *scales,
-              sr_key_t key, scales_sm_t sm, k_gather_t gk, hipStream_t st)
+template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(quant_t q)
 {
-    const uint16_t *d = static_cast<const uint16_t *>(x.data);
-    if (gk.out) {
-        hipLaunchKernelGGL((k_quant_kc16_gather<B, SR>), dim3((unsigned)x.outer), dim3(256), 0, st, d, x.K, x.ld, codes,
-                           scales, key, sm, gk);
-        return check_launch();
+    __shared__ __attribute__((aligned(16))) uint8_t lds[KS_LDS];
+    // Workgroups start in the order of their linear index, x fastest.  Taken as it is, that order runs all column
+    // tiles of one K-block before the next K-block: the workgroups in flight together then write 128-byte pieces of
+    // thousands of different output rows.  Instead the index walks KS_GROUP neighbouring column tiles through all
+    // K-blocks before it moves to the next group: the reads still come in pieces of KS_GROUP x 128 bytes of a K-row, and
+    // an output row is written in one go.  Measured: operands with rows of 28672 elements (448 column tiles: the
+    // about 1000 workgroups in flight span two K-blocks, 300 bytes of an output row) 292 -> 237 us ([16384][28672])
+    // and 133 -> 122 us ([8192][28672]); 384, 320 and 224 column tiles 11 .. 13 % faster; 256 column tiles 7 % faster
+    // or 5 % slower by K; with 192 column tiles and fewer the plain order is as fast or up to 10 % faster and is kept
+    // (group == 0).
+    unsigned bx = blockIdx.x, by = blockIdx.y;
+    if (q.group) {
+        const uint64_t nx = gridDim.x, ny = gridDim.y, L = by * nx + bx, full = nx / q.group * q.group;
+        if (L < full * ny) {
+            const uint64_t r = L % (q.group * ny);
+            bx = (unsigned)(L / (q.group * ny) * q.group + r % q.group);
+            by = (unsigned)(r / q.group);
+        } else { // the last, narrower group
+            const uint64_t r = L - full * ny, wdt = nx - full;
+            bx = (unsigned)(full + r % wdt);
+            by = (unsigned)(r / wdt);
+        }
     }
-    const int64_t tpr = ceil_div(x.K, 256) * 16; // threads per row
-    auto launch = [&](auto flat, auto tail, dim3 grid) {
-        hipLaunchKernelGGL((k_quant_kc16<B, decltype(flat)::value, SR, decltype(tail)::value>), grid, dim3(256), 0, st, d,
-                           x.outer, x.K, x.ld, zo, zk, codes, scales, key, sm);
-        return check_launch();
-    };
-    auto pick_tail = [&](auto flat, dim3 grid) {
-        return x.K % 256 ? launch(flat, std::true_type(), grid) : launch(flat, std::false_type(), grid);
-    };
-    if (tpr >= 128) return pick_tail(std::integral_constant<int, 0>(), dim3((unsigned)x.outer, (unsigned)ceil_div(tpr, 256)));
-    return pick_tail(std::integral_constant<int, 1>(), dim3((unsigned)ceil_div(x.outer * tpr, 256)));
+    quant_ks_tile<B, SR>(q, bx, by, lds);
 }
 
-template <int B, bool SR>
-int launch_ks(const adahop_operand_t &x, const uint8_t *zo, const uint8_t *zk, uint8_t *codes, uint8_t *scales,
-              sr_key_t key, scales_sm_t sm, hipStream_t st)
+// Both operands of a product in one launch: the workgroups below `na` take the first, the others the second.  A launch costs at
+// least 4 us next to its neighbours (the last workgroups of one kernel run alone, and so do the first of the next), half of
+// what an operand of 8 M elements takes.
+enum quant_kind_t { KC, KC_GATHER, KS };
+template <quant_kind_t OP> constexpr int quant_lds() { return OP == KS ? KS_LDS : OP == KC_GATHER ? KC_GATHER_LDS : 16; }
+
+template <int B, quant_kind_t OP, bool TAIL>
+__device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, uint8_t *lds)
 {
-    dim3 grid((unsigned)ceil_div(x.outer, KS_COLS), (unsigned)ceil_div(x.K, 256));
-    const unsigned group = grid.x > KS_GROUP_FROM ? KS_GROUP : 0u;
-    hipLaunchKernelGGL((k_quant_ks16<B, SR>), grid, dim3(256), 0, st, static_cast<const uint16_t *>(x.data), x.outer, x.K,
-                       x.ld, zo, zk, codes, scales, key, sm, group);
+    if constexpr (OP == KS) {
+        const uint32_t by = row_of_unit(block, q.col_tiles, q.tile_magic);
+        quant_ks_tile<B, false>(q, block - by * q.col_tiles, by, lds);
+    } else if constexpr (OP == KC_GATHER) {
+        quant_kc_gather_rows<B, false, TAIL>(q, block, lds);
+    } else {
+        const uint32_t u = (block * 256u + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
+        quant_kc_unit<B, false, TAIL>(q, r, u - r * q.upr, r < q.outer);
+    }
+}
+
+template <int B, quant_kind_t OPA, quant_kind_t OPB, bool TAIL>
+__global__ __launch_bounds__(256) void k_quant_two(quant_t qa, quant_t qb, uint32_t na)
+{
+    constexpr int LDS = quant_lds<OPA>() > quant_lds<OPB>() ? quant_lds<OPA>() : quant_lds<OPB>();
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS];
+    if (blockIdx.x < na)
+        quant_block<B, OPA, TAIL>(qa, blockIdx.x, lds);
+    else
+        quant_block<B, OPB, TAIL>(qb, blockIdx.x - na, lds);
+}
+
+// The descriptor of an operand and the kernel kind that takes it.
+quant_kind_t describe(const quant_job_t &j, quant_t &q)
+{
+    const adahop_operand_t &x = *j.x;
+    q.x = static_cast<const uint16_t *>(x.data);
+    q.outer = x.outer, q.K = x.K, q.ld = x.ld;
+    q.zero_outer = j.zero_outer, q.zero_k = j.zero_k;
+    q.codes = j.codes, q.scales = j.scales;
+    q.key = j.sr_seed ? sr_key_t{(uint32_t)*j.sr_seed, (uint32_t)(*j.sr_seed >> 32)} : sr_key_t{0, 0};
+    q.sm = j.sm;
+    q.gk = j.gk;
+    q.gr = j.gr;
+    q.upr = (uint32_t)ceil_div(x.K, 256);
+    auto magic_of = [](uint32_t d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
+    q.magic = magic_of(q.upr);
+    q.rows_per_wg = 1;
+    q.col_tiles = (uint32_t)ceil_div(x.outer, KS_COLS);
+    q.tile_magic = magic_of(q.col_tiles);
+    q.group = q.col_tiles > KS_GROUP_FROM ? KS_GROUP : 0;
+    if (!x.k_contig) return KS;
+    if (!q.gk.out) return KC;
+    const uint32_t fit = 16 / q.upr, room = (uint32_t)(KC_GATHER_LDS / 2 / (q.gk.kpad + 8)); // rows per pass, and in LDS
+    const uint32_t rows = fit < room ? fit : room;
+    if (rows > 1) q.rows_per_wg = rows;
+    return KC_GATHER;
+}
+
+uint32_t blocks_of(quant_kind_t kind, const quant_t &q)
+{
+    if (kind == KS) return q.col_tiles * q.upr;
+    if (kind == KC_GATHER) return (uint32_t)ceil_div(q.outer, q.rows_per_wg);
+    return (uint32_t)ceil_div(q.outer * q.upr, 16);
+}
+
+template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, hipStream_t st)
+{
+    const bool tail = q.K % 256 != 0;
+    if (kind == KS) {
+        hipLaunchKernelGGL((k_quant_ks16<B, SR>), dim3(q.col_tiles, q.upr), dim3(256), 0, st, q);
+    } else if (kind == KC_GATHER) {
+        const dim3 grid(blocks_of(KC_GATHER, q));
+        if (tail)
+            hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, true>), grid, dim3(256), 0, st, q);
+        else
+            hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, false>), grid, dim3(256), 0, st, q);
+    } else if (q.upr >= 8) {
+        const dim3 grid((unsigned)q.outer, (unsigned)ceil_div(q.upr, 16));
+        if (tail)
+            hipLaunchKernelGGL((k_quant_kc16<B, 0, SR, true>), grid, dim3(256), 0, st, q);
+        else
+            hipLaunchKernelGGL((k_quant_kc16<B, 0, SR, false>), grid, dim3(256), 0, st, q);
+    } else {
+        const dim3 grid(blocks_of(KC, q));
+        if (tail)
+            hipLaunchKernelGGL((k_quant_kc16<B, 1, SR, true>), grid, dim3(256), 0, st, q);
+        else
+            hipLaunchKernelGGL((k_quant_kc16<B, 1, SR, false>), grid, dim3(256), 0, st, q);
+    }
     return check_launch();
 }
 
-template <bool SR>
-int dispatch_block(const adahop_operand_t &x, int b, const uint8_t *zo, const uint8_t *zk, uint8_t *codes,
-                   uint8_t *scales, sr_key_t key, scales_sm_t sm, k_gather_t gk, hipStream_t st)
+template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const quant_t &qb, hipStream_t st)
 {
-#define ADAHOP_DISPATCH(BB)                                                                  \
-    case BB:                                                                                 \
-        return x.k_contig ? launch_kc<BB, SR>(x, zo, zk, codes, scales, key, sm, gk, st)     \
-                          : launch_ks<BB, SR>(x, zo, zk, codes, scales, key, sm, st);
-    switch (b) {
-        ADAHOP_DISPATCH(0)
-        ADAHOP_DISPATCH(32)
-        ADAHOP_DISPATCH(64)
-        ADAHOP_DISPATCH(128)
-        ADAHOP_DISPATCH(256)
-    default:
-        return ADAHOP_E_INVALID_ARG;
-    }
-#undef ADAHOP_DISPATCH
+    const uint32_t na = blocks_of(ka, qa), nb = blocks_of(kb, qb);
+    auto go = [&](auto a, auto b, auto tail) {
+        hipLaunchKernelGGL((k_quant_two<B, decltype(a)::value, decltype(b)::value, decltype(tail)::value>), dim3(na + nb), dim3(256),
+                           0, st, qa, qb, na);
+    };
+    typedef std::integral_constant<quant_kind_t, KC> kc_t;
+    typedef std::integral_constant<quant_kind_t, KC_GATHER> kg_t;
+    typedef std::integral_constant<quant_kind_t, KS> ks_t;
+    auto pick = [&](auto tail) {
+        if (ka == KC && kb == KC) go(kc_t(), kc_t(), tail);
+        if (ka == KC && kb == KS) go(kc_t(), ks_t(), tail);
+        if (ka == KC_GATHER && kb == KC_GATHER) go(kg_t(), kg_t(), tail);
+        if (ka == KC_GATHER && kb == KS) go(kg_t(), ks_t(), tail);
+    };
+    if (ka == KS)
+        go(ks_t(), ks_t(), std::false_type()); // (no kernel of a K-strided operand depends on it)
+    else if (qa.K % 256)
+        pick(std::true_type());
+    else
+        pick(std::false_type());
+    return check_launch();
 }
+
+#define ADAHOP_DISPATCH(b, CALL)            \
+    switch (b) {                            \
+    case 0: return CALL(0);                 \
+    case 32: return CALL(32);               \
+    case 64: return CALL(64);               \
+    case 128: return CALL(128);             \
+    case 256: return CALL(256);             \
+    default: return ADAHOP_E_INVALID_ARG;   \
+    }
+
+int launch_one(int b, bool sr, quant_kind_t kind, const quant_t &q, hipStream_t st)
+{
+#define ADAHOP_ONE(BB) (sr ? launch_one_b<BB, true>(kind, q, st) : launch_one_b<BB, false>(kind, q, st))
+    ADAHOP_DISPATCH(b, ADAHOP_ONE)
+#undef ADAHOP_ONE
+}
+
+int launch_two(int b, quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const quant_t &qb, hipStream_t st)
+{
+#define ADAHOP_TWO(BB) launch_two_b<BB>(ka, qa, kb, qb, st)
+    ADAHOP_DISPATCH(b, ADAHOP_TWO)
+#undef ADAHOP_TWO
+}
+#undef ADAHOP_DISPATCH
 
 } // namespace
 
-// sr_seed: NULL for round-to-nearest-even, else the seed of the stochastic rounding of the elements.
-// sm: NULL, or where a stage-major copy of the scales goes.
-// A whole row per workgroup pays from 4096 K-elements on (one pass of all its lanes); the copy is staged in LDS.
+// The copy of a row's extracted channels is staged in LDS.
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad)
 {
-    return x.k_contig && x.K % 4096 == 0 && kpad <= KC_GATHER_MAX_KPAD && kpad % 8 == 0 && x.outer <= 0x7fffffff;
+    return x.k_contig && kpad <= KC_GATHER_MAX_KPAD && kpad % 8 == 0 && x.outer <= 0x7fffffff;
 }
 
-// gather: NULL, or where the extracted channels are copied to and the table that names them (it must describe the
-// same channels as zk); honoured only where iht_quantize_gathers_k holds and zk is given.
-int launch_iht_quantize(const adahop_operand_t &x, int b, const uint8_t *zo, const uint8_t *zk, uint8_t *codes,
-                        uint8_t *scales, hipStream_t st, const uint64_t *sr_seed, const scales_sm_t *sm,
-                        const k_gather_t *gather)
+int launch_iht_quantize(int b, const quant_job_t &job, hipStream_t st)
 {
-    if (x.outer == 0 || x.K == 0) return ADAHOP_OK;
-    const scales_sm_t smv = sm ? *sm : scales_sm_t{nullptr, 0};
-    const k_gather_t gk = gather && gather->out && zk && !zo && iht_quantize_gathers_k(x, gather->kpad)
-                              ? *gather
-                              : k_gather_t{nullptr, nullptr, 0, 0};
-    if (sr_seed) {
-        const sr_key_t key = {(uint32_t)*sr_seed, (uint32_t)(*sr_seed >> 32)};
-        return dispatch_block<true>(x, b, zo, zk, codes, scales, key, smv, gk, st);
-    }
-    return dispatch_block<false>(x, b, zo, zk, codes, scales, sr_key_t{0, 0}, smv, gk, st);
+    if (job.x->outer == 0 || job.x->K == 0) return ADAHOP_OK;
+    quant_t q;
+    const quant_kind_t kind = describe(job, q);
+    return launch_one(b, job.sr_seed != nullptr, kind, q, st);
+}
+
+// Operands of up to 64 M elements together share a launch: 16.8 -> 12.9 us on 8192 x 2048 with 2048 x 2048 (K-contiguous),
+// 27.0 -> 25.3 on 8192 x 4096 with 4096 x 4096, K-strided 24.3 -> 20.4 and 39.2 -> 37.4.  A K-contiguous operand beside a K-strided
+// one runs with the registers and the LDS of the latter, half as many waves per compute unit: 17.5 -> 16.9 us on 8192 x 2048 with
+// 2048 x 2048, but 29.2 -> 30.7 on the larger pair, so that the line lies at 24 M there.
+int launch_iht_quantize_two(int b, const quant_job_t &ja, const quant_job_t &jb, hipStream_t st)
+{
+    quant_t qa, qb;
+    const quant_kind_t ka = describe(ja, qa), kb = describe(jb, qb);
+    const int64_t together = (ka == KS) == (kb == KS) ? 64ll << 20 : 24ll << 20;
+    const bool copies_differ = ka != kb && kb != KS && ka != KS; // one K-contiguous operand with its channels copied out, one without
+    if (qa.K == qb.K && !copies_differ && !ja.sr_seed && !jb.sr_seed && !(ka == KS && qa.group) && !(kb == KS && qb.group) &&
+        (qa.outer + qb.outer) * qa.K <= together)
+        return ka == KS && kb != KS ? launch_two(b, kb, qb, ka, qa, st) : launch_two(b, ka, qa, kb, qb, st);
+    const int rc = launch_one(b, ja.sr_seed != nullptr, ka, qa, st);
+    return rc != ADAHOP_OK ? rc : launch_one(b, jb.sr_seed != nullptr, kb, qb, st);
 }
 
 } // namespace adahop

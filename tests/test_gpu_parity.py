@@ -572,3 +572,39 @@ def test_detect_pattern_matches_oracle(ah, shape, k_contig):
         want_p, want_st = orc.detect_pattern(logical, True)
         assert int(host(p)[0]) == want_p
         assert np.allclose(host(st), want_st, rtol=1e-9, atol=1e-12), (host(st), want_st)
+
+
+# ----------------------------------------------------- extracted parts copied out by the quantisers
+
+@pytest.mark.parametrize("layouts", [(True, True), (True, False), (False, False), (False, True)])
+@pytest.mark.parametrize("M,N,K,b", [(70, 40, 256, 256), (300, 130, 288, 32), (64, 520, 1056, 32), (130, 72, 2304, 128),
+                                     (33, 41, 8480, 32), (2100, 6000, 4224, 64)])
+@pytest.mark.parametrize("strategy", [inputs.IHT, inputs.IHT_OE_ROW, inputs.IHT_OE_COL, inputs.IHT_OE_K])
+def test_quantisers_of_both_operands(ah, layouts, M, N, K, b, strategy):
+    """Rows of one unit, of a shorter last unit, of several rows per workgroup and of more than one pass; both operands in
+    one launch and (the largest pair beside a K-strided operand) in two.  Codes and scales are the oracle's bits; with the
+    indices handed in, so that the extracted parts are gathered by kernels of their own, C has the same bits."""
+    k = {inputs.IHT: 0, inputs.IHT_OE_ROW: max(1, M // 50), inputs.IHT_OE_COL: max(1, N // 50), inputs.IHT_OE_K: max(1, K // 50)}[strategy]
+    A = inputs.matrix(M, K, 1.0, 9200, row_outliers=(2, 60.0, 60.0), col_outliers=(3, 30.0, 30.0))
+    B = inputs.matrix(N, K, 0.02, 9201, row_outliers=(2, 50.0, 50.0))
+    say("quantisers of both operands", layouts, (M, N, K, b), inputs.STRATEGY_NAMES[strategy], k)
+    ops = []
+    for bits, kc in ((A, layouts[0]), (B, layouts[1])):
+        arr, width = stored(bits, kc)
+        ops.append(ah.Operand(torch.from_numpy(arr.view(np.int16)).cuda()[:, :width], kc))
+    out = ah.adahop_gemm(*ops, strategy, b, k)
+    again = ah.adahop_gemm(*ops, strategy, b, k, idx=out["idx"].clone()) if k else out
+    torch.cuda.synchronize()
+    assert torch.equal(out["C"].view(torch.int32), again["C"].view(torch.int32))
+    idx = np.sort(host(out["idx"])) if k else None
+    mask_a = mask_b = mask_k = None
+    if strategy == inputs.IHT_OE_ROW:
+        mask_a = np.zeros(M, np.uint8); mask_a[idx] = 1
+    if strategy == inputs.IHT_OE_COL:
+        mask_b = np.zeros(N, np.uint8); mask_b[idx] = 1
+    if strategy == inputs.IHT_OE_K:
+        mask_k = np.zeros(K, np.uint8); mask_k[idx] = 1
+    for name, bits, zo in (("a", A, mask_a), ("b", B, mask_b)):
+        rc, rs = orc.iht_quantize(bits, True, b, zo, mask_k)
+        assert np.array_equal(host(out[name + "_scales"]), rs), name
+        assert np.array_equal(host(out[name + "_codes"]), rc), name
