@@ -89,10 +89,11 @@ size_t gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // product lets the quantiser write that copy as well (scales_sm_t above) and says so with sm_ready (bit 0: A, bit 1: B);
 // otherwise launch_gemm_mx re-orders the canonical scales itself where the chosen kernel needs that.
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which);
-// The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): fp32 C, no gathered K-channels, K > 1792.
-bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K);
+// The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): fp32 C, at most 128 gathered K-channels, K > 1792.
+bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K, int kpad);
 int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
-                        const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, hipStream_t st);
+                        const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg,
+                        int kpad, hipStream_t st);
 // Any shape, tiles of 32 .. 128 (gemm_mx_small.hip).  a_sm / b_sm: the scales are the stage-major copy, else the canonical
 // array (only for K % 256 == 0 and 4-byte aligned).
 int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,

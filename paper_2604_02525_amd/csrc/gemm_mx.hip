@@ -612,15 +612,17 @@ void gemm_mx_force_kernel(int which)
     g_force_walk.store(which >= 3 && which <= 6 ? which - 3 : -1);
 }
 
-// Which of the two kernels with tiles of 256 rows (fp32 C, no gathered K-channels; otherwise always the 256 x 256 kernel).  The
+// Which of the two kernels with tiles of 256 rows (fp32 C and at most 128 gathered K-channels; otherwise always the 256 x 256 kernel).  The
 // 256 x 128 kernel with two accumulator sets hides the C stores behind the next tile but moves 1.5 times the operand
 // bytes per flop from L2 into LDS and out of LDS; measured on MI355X it wins where the stores are a large part of a
 // tile's time -- K = 2048: 1.2x; K = 4096: 1.04 .. 1.13x up to about 90 M elements of C, 0.97x at 8192 x 12288 -- and
 // loses 4 .. 15 % from K = 8192 on, except where the 256 x 256 tiles fill the last round of the compute units badly
-// (14336 x 4096: 896 tiles on 256 units, 3.5 rounds; 1.1x with 7 rounds of the smaller tiles).
+// (14336 x 4096: 896 tiles on 256 units, 3.5 rounds; 1.1x with 7 rounds of the smaller tiles).  With K-channels in front the
+// same line holds: whole products with 1 % of the channels, 8192 x 8192 x 2048 146 -> 124 us, 8192 x 4096 x 4096 126 -> 120,
+// 2016 x 11008 x 4096 110 -> 100, 16384 x 4096 x 4096 210 / 210.
 static bool takes_dual_kernel(int64_t M, int64_t N, int64_t K, int kpad)
 {
-    if (kpad > 0 || !gemm_mx_dual_eligible(M, N, K)) return false;
+    if (!gemm_mx_dual_eligible(M, N, K, kpad)) return false;
     const int forced = g_kernel_choice.load();
     if (forced == 1) return false;
     if (forced == 2) return true;
@@ -739,7 +741,7 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
                                     b_canonical ? b_scales : b_sm, !b_canonical, C, ldc, sizeof(OUT) == 2, Ag, Bg, kpad, st);
     if constexpr (sizeof(OUT) == 4) {
         if (c.dual)
-            return launch_gemm_mx_dual(M, N, K, a_codes, a_sm, b_codes, b_sm, reinterpret_cast<float *>(C), ldc, st);
+            return launch_gemm_mx_dual(M, N, K, a_codes, a_sm, b_codes, b_sm, reinterpret_cast<float *>(C), ldc, Ag, Bg, kpad, st);
     }
 
     int ncu = 0;

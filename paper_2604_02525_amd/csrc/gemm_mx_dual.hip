@@ -49,6 +49,7 @@ struct scales_t {
 // Wave-uniform bases of this wave's share of stage 0 of a tile.
 struct src_t {
     const uint8_t *ga, *gb, *gs;
+    const uint8_t *gga, *ggb; // gathered bf16 operands
 };
 
 struct state_t {
@@ -62,8 +63,10 @@ struct state_t {
     int last_step;     // bytes from the last stage but one to the last, which ends with the row (TKB if K % 256 == 0)
     uint32_t cbuf;     // byte offset of the cursor's LDS buffer
     src_t nxt;         // the tile after the cursor's
-    int n;             // stages per tile
-    uint32_t v_even, v_odd, vs, pitch;
+    src_t cur;         // the cursor's tile (only with gathered K-channels)
+    int n, nfp;        // stages per tile, and the FP4 ones among them
+    uint32_t v_even, v_odd, vs, pitch; // (pitch and the offsets made of it: of the cursor's stage)
+    uint32_t lrow, c_even, fp_pitch, g_pitch; // only with gathered K-channels
     int64_t s_stride;
     uint32_t lds_a, lds_b, lds_s; // LDS addresses, in buffer 0, of the rows this wave copies
 };
@@ -95,9 +98,27 @@ __device__ __forceinline__ const uint8_t *pick(bool c, const uint8_t *a, const u
     return reinterpret_cast<const uint8_t *>(c ? reinterpret_cast<uintptr_t>(a) : reinterpret_cast<uintptr_t>(b));
 }
 
-__device__ __forceinline__ void advance(state_t &t)
+__device__ __forceinline__ uint32_t pick32(bool c, uint32_t a, uint32_t b) { return c ? a : b; }
+
+// NBF: a tile begins with that many stages of gathered bf16 K-channels, 64 each, whose rows have a pitch of their own.
+template <int NBF> __device__ __forceinline__ void advance(state_t &t)
 {
     const bool wrap = t.left == 1;
+    if constexpr (NBF > 0) {
+        const bool to_fp4 = t.left == t.nfp + 1, in_bf = t.left > t.nfp; // (in_bf: the stage that has just been issued)
+        const int ahead = t.left == 2 ? t.last_step : TKB;
+        t.pa = pick(wrap, t.nxt.gga, pick(to_fp4, t.cur.ga, t.pa + ahead));
+        t.pb = pick(wrap, t.nxt.ggb, pick(to_fp4, t.cur.gb, t.pb + ahead));
+        t.ps = pick(wrap, t.nxt.gs, t.ps + (in_bf ? 0 : t.s_stride)); // (bf16 stages copy the scales of the first FP4 stage)
+        t.cur.ga = pick(wrap, t.nxt.ga, t.cur.ga);
+        t.cur.gb = pick(wrap, t.nxt.gb, t.cur.gb);
+        t.pitch = pick32(wrap, t.g_pitch, pick32(to_fp4, t.fp_pitch, t.pitch));
+        t.v_even = __umul24(t.lrow, t.pitch) + t.c_even;
+        t.v_odd = __umul24(t.lrow, t.pitch) + (t.c_even ^ 64);
+        t.left = wrap ? t.n : t.left - 1;
+        t.cbuf = next_buf(t.cbuf);
+        return;
+    }
     const int ahead = t.left == 2 ? t.last_step : TKB;
     t.pa = pick(wrap, t.nxt.ga, t.pa + ahead);
     t.pb = pick(wrap, t.nxt.gb, t.pb + ahead);
@@ -137,7 +158,8 @@ template <int SET, int ST> __device__ __forceinline__ void store_one(const state
 // other set (ST < 0: none).  A wave issues in order and is alone on its SIMD: single instructions fit into the
 // shadow of the matrix-core instruction before them, bursts would hold the matrix core up.  Written as a
 // compile-time recursion over the instruction index Q (no loop: the order written is the order that runs).
-template <int SET, int S, bool ZC, int RS, bool RSC, int C0, int C1, int ST, int R0, int R1, int Q = 0>
+// BF: the stage holds gathered bf16 K-channels.
+template <bool BF, int SET, int S, bool ZC, int RS, bool RSC, int C0, int C1, int ST, int R0, int R1, int Q = 0>
 __device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t *rbuf, frags_t &rf, float *cprev,
                                      int64_t ldc)
 {
@@ -145,9 +167,13 @@ __device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t
         constexpr int i = Q >> 1, j = Q & 1, NC = C1 - C0;
         const v16f zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         const v16f c = ZC ? zero : t.acc[SET][i][j];
-        v8i av = {(int)f.a[i].x, (int)f.a[i].y, (int)f.a[i].z, (int)f.a[i].w, 0, 0, 0, 0};
-        v8i bv = {(int)f.b[j].x, (int)f.b[j].y, (int)f.b[j].z, (int)f.b[j].w, 0, 0, 0, 0};
-        t.acc[SET][i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 4, S, t.sc.a[i], S, t.sc.b[j]);
+        if constexpr (BF) {
+            t.acc[SET][i][j] = mfma_bf16(f.a[i], f.b[j], c);
+        } else {
+            v8i av = {(int)f.a[i].x, (int)f.a[i].y, (int)f.a[i].z, (int)f.a[i].w, 0, 0, 0, 0};
+            v8i bv = {(int)f.b[j].x, (int)f.b[j].y, (int)f.b[j].z, (int)f.b[j].w, 0, 0, 0, 0};
+            t.acc[SET][i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 4, S, t.sc.a[i], S, t.sc.b[j]);
+        }
         ADAHOP_PIN();
         if constexpr (RS >= 0 && Q < 6) {
             read_item(rbuf, t, RS, Q, rf);
@@ -169,14 +195,14 @@ __device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t
             store_one<1 - SET, ST>(t, cprev, ldc, R0 + Q);
             ADAHOP_PIN();
         }
-        step<SET, S, ZC, RS, RSC, C0, C1, ST, R0, R1, Q + 1>(f, t, rbuf, rf, cprev, ldc);
+        step<BF, SET, S, ZC, RS, RSC, C0, C1, ST, R0, R1, Q + 1>(f, t, rbuf, rf, cprev, ldc);
     }
 }
 
 // One pipeline stage: four matrix-core steps on the fragments of the LDS buffer at byte offset rb (advanced to
 // the next buffer on return).  ST: the accumulator tile of the previous tile's set stored during this stage
 // (-1: none).  ZC: first stage of a tile (its first step starts the accumulators from 0).
-template <int SET, int ST, bool ZC>
+template <int NBF, bool BF, int SET, int ST, bool ZC>
 __device__ __forceinline__ void run_stage(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
 {
     const uint8_t *st = smem + rb;
@@ -184,39 +210,43 @@ __device__ __forceinline__ void run_stage(state_t &t, const uint8_t *smem, uint3
     const uint8_t *sn = smem + rn;
     // the copies of a stage: PART1 during the last step of the stage two before it (after that stage's barrier),
     // the rest during the first three steps of the stage before it
-    step<SET, 0, ZC, 1, false, PART1, PART1 + 3, ST, 0, 6>(t.f0, t, st, t.f1, cprev, ldc);
-    step<SET, 1, false, 2, false, PART1 + 3, PART1 + 6, ST, 6, 11>(t.f1, t, st, t.f0, cprev, ldc);
-    step<SET, 2, false, 3, false, PART1 + 6, NCOPY, ST, 11, 16>(t.f0, t, st, t.f1, cprev, ldc);
-    advance(t);
+    step<BF, SET, 0, ZC, 1, false, PART1, PART1 + 3, ST, 0, 6>(t.f0, t, st, t.f1, cprev, ldc);
+    step<BF, SET, 1, false, 2, false, PART1 + 3, PART1 + 6, ST, 6, 11>(t.f1, t, st, t.f0, cprev, ldc);
+    step<BF, SET, 2, false, 3, false, PART1 + 6, NCOPY, ST, 11, 16>(t.f0, t, st, t.f1, cprev, ldc);
+    advance<NBF>(t);
     // Younger than the last copy of the next stage: the NCOPY copies of the stage after it and this stage's stores.
     constexpr int X = NCOPY + (ST >= 0 ? STORES_PER_STAGE : 0);
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(X) : "memory");
-    step<SET, 3, false, 0, true, 0, PART1, -1, 0, 0>(t.f1, t, sn, t.f0, cprev, ldc);
+    step<BF, SET, 3, false, 0, true, 0, PART1, -1, 0, 0>(t.f1, t, sn, t.f0, cprev, ldc);
     t.sc = t.scn;
     rb = rn;
 }
 
-template <int SET, int ST> __device__ __forceinline__ void store_stages(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
+template <int NBF, int SET, int ST> __device__ __forceinline__ void store_stages(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
 {
     if constexpr (ST < STORE_STAGES) {
-        run_stage<SET, ST, ST == 0>(t, smem, rb, cprev, ldc);
-        store_stages<SET, ST + 1>(t, smem, rb, cprev, ldc);
+        run_stage<NBF, (ST < NBF), SET, ST, ST == 0>(t, smem, rb, cprev, ldc);
+        store_stages<NBF, SET, ST + 1>(t, smem, rb, cprev, ldc);
     }
 }
 
 // All stages of one tile into set SET; STORES: the other set holds a finished tile, whose stores go along.
-template <int SET, bool STORES>
+template <int NBF, int SET, bool STORES>
 __device__ __forceinline__ void run_tile(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
 {
     int l;
     if constexpr (STORES) {
-        store_stages<SET, 0>(t, smem, rb, cprev, ldc);
+        store_stages<NBF, SET, 0>(t, smem, rb, cprev, ldc);
         l = STORE_STAGES;
     } else {
-        run_stage<SET, -1, true>(t, smem, rb, cprev, ldc);
+        run_stage<NBF, (NBF > 0), SET, -1, true>(t, smem, rb, cprev, ldc);
         l = 1;
+        if constexpr (NBF == 2) {
+            run_stage<NBF, true, SET, -1, false>(t, smem, rb, cprev, ldc);
+            l = 2;
+        }
     }
-    for (; l < t.n; ++l) run_stage<SET, -1, false>(t, smem, rb, cprev, ldc);
+    for (; l < t.n; ++l) run_stage<NBF, false, SET, -1, false>(t, smem, rb, cprev, ldc);
 }
 
 template <int SET> __device__ __forceinline__ void store_all(const state_t &t, float *c, int64_t ldc)
@@ -235,12 +265,15 @@ template <int SET> __device__ __forceinline__ void store_all(const state_t &t, f
 // Persistent kernel, one workgroup per compute unit walking the tile sequence with the stride of the grid.
 // M >= 256, N >= 128, K % 32 == 0, K > 1792 (host side).  The last tile of a ragged dimension ends with it and overlaps
 // its neighbour, and so does the last stage of a ragged K (see the 256 x 256 kernel).
+// NBF: stages of gathered bf16 K-channels in front of the FP4 stages of a tile (kpad = 64 NBF; 0, 1 or 2: they lie among the
+// stages that carry the stores of the tile before, each of them an instance of the stage's code).
+template <int NBF>
 __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *__restrict__ a_codes,
                                                       const uint8_t *__restrict__ a_scales_sm,
                                                       const uint8_t *__restrict__ b_codes,
                                                       const uint8_t *__restrict__ b_scales_sm, int64_t M, int64_t N,
-                                                      float *__restrict__ C, int64_t ldc, int tiles_m, int tiles_n,
-                                                      int group_m)
+                                                      float *__restrict__ C, int64_t ldc, const uint16_t *__restrict__ Ag,
+                                                      const uint16_t *__restrict__ Bg, int tiles_m, int tiles_n, int group_m)
 {
     using namespace dual;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -289,14 +322,25 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
         t.lds_b = base + A_SLAB + w * 32 * TKB;
         t.lds_s = base + (w == 0 ? SA_OFF : (w == 1 ? SA_OFF + 1024 : SB_OFF)); // waves 2 and 3 both bring B's scales
     }
-    t.n = (int)((K + 255) >> 8);
-    t.last_step = (int)(K >> 1) - TKB - (t.n - 2) * TKB;
+    t.nfp = (int)((K + 255) >> 8);
+    t.n = t.nfp + NBF;
+    t.last_step = (int)(K >> 1) - TKB - (t.nfp - 2) * TKB;
+    if constexpr (NBF > 0) {
+        t.lrow = lane >> 3;
+        t.c_even = ((lane & 7) ^ (lane >> 4)) * 16;
+        t.fp_pitch = t.pitch;
+        t.g_pitch = NBF * TKB;
+    }
     auto tile_source = [&](int64_t m0, int64_t n0) {
-        const int64_t pitch = t.pitch;
+        const int64_t pitch = (int64_t)(uint32_t)(K >> 1); // (not t.pitch, which is that of the cursor's stage)
         src_t c;
         c.ga = uniform_ptr(a_codes + (m0 + w * 64) * pitch);
         c.gb = uniform_ptr(b_codes + (n0 + w * 32) * pitch);
         c.gs = uniform_ptr(w < 2 ? a_scales_sm + (m0 + w * 128) * 8 : b_scales_sm + n0 * 8);
+        if constexpr (NBF > 0) {
+            c.gga = uniform_ptr(reinterpret_cast<const uint8_t *>(Ag) + (m0 + w * 64) * (NBF * TKB));
+            c.ggb = uniform_ptr(reinterpret_cast<const uint8_t *>(Bg) + (n0 + w * 32) * (NBF * TKB));
+        }
         return c;
     };
     // fragment reads: row l32 (+32 i) of the wave's rows, logical chunk 4h + s
@@ -319,10 +363,16 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
     tile_origin(v, m0, n0);
     {
         const src_t cur = tile_source(m0, n0);
-        t.pa = cur.ga;
-        t.pb = cur.gb;
+        t.pa = pick(NBF > 0, cur.gga, cur.ga);
+        t.pb = pick(NBF > 0, cur.ggb, cur.gb);
         t.ps = cur.gs;
         t.nxt = cur;
+        if constexpr (NBF > 0) {
+            t.cur = cur;
+            t.pitch = t.g_pitch;
+            t.v_even = t.lrow * t.pitch + t.c_even;
+            t.v_odd = t.lrow * t.pitch + (t.c_even ^ 64);
+        }
     }
     t.left = t.n;
     t.cbuf = 0;
@@ -340,9 +390,9 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
     int64_t m0n, n0n;
     look_ahead(more, m0n, n0n);
     issue<0, NCOPY>(t);
-    advance(t);
+    advance<NBF>(t);
     issue<0, NCOPY>(t);
-    advance(t);
+    advance<NBF>(t);
     issue<0, PART1>(t);
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NCOPY + PART1) : "memory");
     uint32_t rb = 0;
@@ -351,7 +401,7 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
     read_scales(smem, t, t.sc);
 
     float *cprev = c_of(m0, n0);
-    run_tile<0, false>(t, smem, rb, cprev, ldc);
+    run_tile<NBF, 0, false>(t, smem, rb, cprev, ldc);
     for (;;) {
         cprev = c_of(m0, n0); // the tile just finished, in set 0
         if (!more) {
@@ -360,7 +410,7 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
         }
         v += grid, m0 = m0n, n0 = n0n;
         look_ahead(more, m0n, n0n);
-        run_tile<1, true>(t, smem, rb, cprev, ldc);
+        run_tile<NBF, 1, true>(t, smem, rb, cprev, ldc);
         cprev = c_of(m0, n0); // in set 1
         if (!more) {
             store_all<1>(t, cprev, ldc);
@@ -368,16 +418,16 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
         }
         v += grid, m0 = m0n, n0 = n0n;
         look_ahead(more, m0n, n0n);
-        run_tile<0, true>(t, smem, rb, cprev, ldc);
+        run_tile<NBF, 0, true>(t, smem, rb, cprev, ldc);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the copies begun for a tile that does not follow
 }
 
 } // namespace
 
-bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K)
+bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K, int kpad)
 {
-    return K > 256 * (dual::STORE_STAGES - 1) && M >= dual::TM && N >= dual::TN;
+    return kpad % 64 == 0 && kpad <= 128 && K > 256 * (dual::STORE_STAGES - 1) && M >= dual::TM && N >= dual::TN;
 }
 
 // Once per device: the compute-unit count and the kernel's LDS size.  Host-side calls, nothing queued.
@@ -392,9 +442,12 @@ int configure_gemm_mx_dual(int *ncu_out)
     if (once.need(dev) || ncu == 0) {
         rc = check_hip(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
         if (rc != ADAHOP_OK) return rc;
-        rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_mx_dual),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, dual::LDS_BYTES));
-        if (rc != ADAHOP_OK) return rc;
+        const void *kernels[3] = {reinterpret_cast<const void *>(&k_gemm_mx_dual<0>), reinterpret_cast<const void *>(&k_gemm_mx_dual<1>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_dual<2>)};
+        for (const void *f : kernels) {
+            rc = check_hip(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dual::LDS_BYTES));
+            if (rc != ADAHOP_OK) return rc;
+        }
         if (dev >= 0 && dev < 64) cu_count[dev].store(ncu, std::memory_order_relaxed);
         once.mark(dev);
     }
@@ -403,7 +456,8 @@ int configure_gemm_mx_dual(int *ncu_out)
 }
 
 int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
-                        const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, hipStream_t st)
+                        const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg,
+                        int kpad, hipStream_t st)
 {
     int ncu = 0;
     int rc = configure_gemm_mx_dual(&ncu);
@@ -414,9 +468,12 @@ int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
     const int ntiles = tiles_m * tiles_n;
     const int group_m = tiles_m < 4 ? tiles_m : 4; // the 32 tiles an XCD runs at a time: 4 x 8, a 1024 x 1024 block of C
     const dim3 grid((unsigned)(ntiles < ncu ? ntiles : ncu));
-    hipLaunchKernelGGL(k_gemm_mx_dual, grid, dim3(256), dual::LDS_BYTES, st, K, a_codes, a_sm, b_codes, b_sm, M, N, C, ldc,
-                       tiles_m, tiles_n, group_m);
-    return check_launch();
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), dual::LDS_BYTES, st, K, a_codes, a_sm, b_codes, b_sm, M, N, C, ldc, Ag, Bg,
+                           tiles_m, tiles_n, group_m);
+        return check_launch();
+    };
+    return kpad == 0 ? launch(&k_gemm_mx_dual<0>) : kpad == 64 ? launch(&k_gemm_mx_dual<1>) : launch(&k_gemm_mx_dual<2>);
 }
 
 } // namespace adahop

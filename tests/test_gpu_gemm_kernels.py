@@ -198,3 +198,18 @@ def test_bf16_output_of_any_alignment(ah, force, kernel, M, N, K, k, gap):
     torch.cuda.synchronize()
     assert torch.equal(room[:, :N].view(torch.int16), full.view(torch.int16))
     assert bool((room[:, N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K,k", [(256, 128, 2048, 8), (520, 264, 2080, 100), (1000, 650, 2304, 128), (4352, 4100, 2048, 70)])
+def test_two_set_kernel_with_k_channels(ah, force, M, N, K, k):
+    """One and two gathered bf16 stages in front of eight and more FP4 stages, one tile and several (both accumulator sets)
+    per workgroup: the bits of the 256 x 256 kernel, which adds in the same order (and is compared with the oracle elsewhere)."""
+    A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 95, col_outliers=(5, 50.0, 50.0)), True)
+    B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 96), True)
+    say("two accumulator sets with K-channels", (M, N, K, k))
+    force(DUAL)
+    got = ah.adahop_gemm(A, B, inputs.IHT_OE_K, 32, k)["C"]
+    force(TILE256 if N >= 256 else 8)
+    want = ah.adahop_gemm(A, B, inputs.IHT_OE_K, 32, k)["C"]
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
