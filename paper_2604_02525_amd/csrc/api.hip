@@ -65,7 +65,7 @@ int adahop_prepare_device(void)
     if ((rc = configure_gemm_mx(nullptr)) != ADAHOP_OK || (rc = configure_gemm_mx_dual(nullptr)) != ADAHOP_OK ||
         (rc = configure_gemm_mx_small()) != ADAHOP_OK ||
         (rc = configure_oe_rowcol()) != ADAHOP_OK || (rc = configure_oht()) != ADAHOP_OK ||
-        (rc = configure_foid()) != ADAHOP_OK)
+        (rc = configure_foid()) != ADAHOP_OK || (rc = configure_iht_quantize()) != ADAHOP_OK)
         return rc;
     float *scores = nullptr;
     return foid_static_scores(&scores); // the address of the built-in score scratch, looked up once per device
@@ -413,19 +413,6 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const bool a_gathers_rows = fuse && strategy == ADAHOP_IHT_OE_ROW && !a_given;
     const bool b_gathers_rows = fuse && strategy == ADAHOP_IHT_OE_COL && !b_given;
     uint16_t *pos1 = a_gathers_k || b_gathers_k || a_gathers_rows || b_gathers_rows ? reinterpret_cast<uint16_t *>(scores) : nullptr;
-    if (oe) {
-        const bool mask_used = (!a_given && a_kind) || (!b_given && b_kind);
-        if (use_given_idx) {
-            rc = mask_used ? launch_mask_from_idx(idx_inout, k, mask, dim, st) : ADAHOP_OK;
-        } else if (strategy == ADAHOP_IHT_OE_ROW) {
-            rc = launch_foid_topk(*A, 0, k, idx_inout, mask, scores, st, pos1);
-        } else if (strategy == ADAHOP_IHT_OE_COL) {
-            rc = launch_foid_topk(*B, 0, k, idx_inout, mask, scores, st, pos1);
-        } else {
-            rc = launch_foid_topk(*A, 1, k, idx_inout, mask, scores, st, pos1);
-        }
-        if (rc != ADAHOP_OK) return rc;
-    }
     // 2. residual -> transform -> MXFP4 (App. F item 2), for the operands the caller has not packed
     const uint8_t *a_codes = a_given ? opts->a_codes : reinterpret_cast<uint8_t *>(ws + L.a_codes);
     const uint8_t *a_scales = a_given ? opts->a_scales : reinterpret_cast<uint8_t *>(ws + L.a_scales);
@@ -444,8 +431,33 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
                             reinterpret_cast<uint8_t *>(ws + L.b_scales), opts && opts->sr_b ? &opts->sr_seed_b : nullptr,
                             {gemm_mx_scales_sm(ws + L.gemm, M, K, 1), N},
                             b_gathers_k ? k_gather_t{pos1, gather_b, k, kpad_planned} : no_k, b_gathers_rows ? rows : no_rows};
+    // Row and column extraction: the operand that nothing is extracted from does not wait for the selection, one workgroup of
+    // which the rest of the chip would watch (9 us for 8192 rows); its quantiser runs beside it.
+    const quant_job_t &free_job = strategy == ADAHOP_IHT_OE_ROW ? jb : ja, &masked_job = strategy == ADAHOP_IHT_OE_ROW ? ja : jb;
+    const bool beside = fuse && !oe_k && !a_given && !b_given && topk_beside_quant(dim, free_job);
+    if (beside) {
+        const topk_job_t topk = {scores, (int)dim, k, idx_inout, mask, pos1};
+        rc = launch_foid_scores(*masked_job.x, 0, scores, st);
+        if (rc == ADAHOP_OK) rc = launch_topk_beside_quant(topk, b, free_job, st);
+        if (rc == ADAHOP_OK) rc = launch_iht_quantize(b, masked_job, st);
+        if (rc != ADAHOP_OK) return rc;
+    } else if (oe) {
+        const bool mask_used = (!a_given && a_kind) || (!b_given && b_kind);
+        if (use_given_idx) {
+            rc = mask_used ? launch_mask_from_idx(idx_inout, k, mask, dim, st) : ADAHOP_OK;
+        } else if (strategy == ADAHOP_IHT_OE_ROW) {
+            rc = launch_foid_topk(*A, 0, k, idx_inout, mask, scores, st, pos1);
+        } else if (strategy == ADAHOP_IHT_OE_COL) {
+            rc = launch_foid_topk(*B, 0, k, idx_inout, mask, scores, st, pos1);
+        } else {
+            rc = launch_foid_topk(*A, 1, k, idx_inout, mask, scores, st, pos1);
+        }
+        if (rc != ADAHOP_OK) return rc;
+    }
     const int sm_ready = oht ? 0 : (a_given ? 0 : 1) | (b_given ? 0 : 2);
-    if (oht) {
+    if (beside) {
+        ;
+    } else if (oht) {
         if (!a_given) rc = launch_oht_quantize(*A, b, ja.codes, ja.scales, st);
         if (rc == ADAHOP_OK && !b_given) rc = launch_oht_quantize(*B, b, jb.codes, jb.scales, st);
     } else if (!a_given && !b_given) {

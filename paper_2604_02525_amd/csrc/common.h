@@ -36,6 +36,7 @@ int configure_gemm_mx_small();
 int configure_oe_rowcol();
 int configure_oht();
 int configure_foid();
+int configure_iht_quantize();
 
 // Launchers (one per kernel family); each validates nothing and returns a status.
 // Stage-major copy of the scales for the tiled GEMM kernels [ceil(K/256)][rows][8].
@@ -71,9 +72,21 @@ struct quant_job_t {
 };
 int launch_iht_quantize(int iht_block, const quant_job_t &job, hipStream_t st);
 int launch_iht_quantize_two(int iht_block, const quant_job_t &a, const quant_job_t &b, hipStream_t st); // both of a product
+// The selection from `scores` (launch_foid_scores) in the first workgroup of a launch whose others quantise an operand that does
+// not depend on it; topk_beside_quant says whether that can be done.
+struct topk_job_t {
+    const float *scores;
+    int dim, k;
+    int32_t *idx;
+    uint8_t *mask;
+    uint16_t *pos1; // may lie where scores lies
+};
+bool topk_beside_quant(int64_t dim, const quant_job_t &job);
+int launch_topk_beside_quant(const topk_job_t &topk, int iht_block, const quant_job_t &job, hipStream_t st);
 // pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere; it may lie where scores lies.  Only where
 // foid_writes_positions holds.
 bool foid_writes_positions(int64_t dim, int k);
+int launch_foid_scores(const adahop_operand_t &x, int axis, float *scores, hipStream_t st);
 int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, uint8_t *mask, float *scores,
                      hipStream_t st, uint16_t *pos1 = nullptr);
 // Device address, on the current device, of the library's built-in score scratch (ADAHOP_FOID_NOALLOC_MAX_DIM floats).

@@ -14,6 +14,7 @@
 // One kernel per storage order of the operand (k_quant_kc16, k_quant_ks16, for every K % 32 == 0) and a variant of the
 // first that also copies the extracted K-channels out; what bounds them and how the work is split stands at each.
 #include "common.h"
+#include "foid_topk.h"
 
 #include <type_traits>
 
@@ -777,6 +778,17 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
     }
 }
 
+// The top-k selection in workgroup 0, an operand that does not depend on it in the others.
+constexpr int TOPK_BESIDE_DIM = 8192;
+template <int B, quant_kind_t OP, bool TAIL> __global__ __launch_bounds__(256) void k_topk_and_quant(topk_job_t t, quant_t q)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
+    if (blockIdx.x == 0)
+        topk_lds<256>(t.scores, t.dim, t.k, t.idx, t.mask, t.pos1, reinterpret_cast<uint32_t *>(dyn));
+    else
+        quant_block<B, OP, TAIL>(q, blockIdx.x - 1, dyn);
+}
+
 template <int B, quant_kind_t OPA, quant_kind_t OPB, bool TAIL>
 __global__ __launch_bounds__(256) void k_quant_two(quant_t qa, quant_t qb, uint32_t na)
 {
@@ -874,6 +886,33 @@ template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind
     return check_launch();
 }
 
+template <int B, quant_kind_t OP, bool TAIL> int allow_topk_lds()
+{
+    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_topk_and_quant<B, OP, TAIL>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)(topk_lds_bytes<256>(TOPK_BESIDE_DIM) > KS_LDS ? topk_lds_bytes<256>(TOPK_BESIDE_DIM) : KS_LDS)));
+}
+
+template <int B> int launch_topk_b(const topk_job_t &t, quant_kind_t kind, const quant_t &q, hipStream_t st)
+{
+    const size_t topk = topk_lds_bytes<256>(t.dim), own = kind == KS ? (size_t)KS_LDS : 0, lds = topk > own ? topk : own;
+    const dim3 grid(1 + blocks_of(kind, q));
+    if (kind == KS)
+        hipLaunchKernelGGL((k_topk_and_quant<B, KS, false>), grid, dim3(256), lds, st, t, q);
+    else if (q.K % 256)
+        hipLaunchKernelGGL((k_topk_and_quant<B, KC, true>), grid, dim3(256), lds, st, t, q);
+    else
+        hipLaunchKernelGGL((k_topk_and_quant<B, KC, false>), grid, dim3(256), lds, st, t, q);
+    return check_launch();
+}
+
+template <int B> int allow_topk_b()
+{
+    int rc;
+    if ((rc = allow_topk_lds<B, KS, false>()) != ADAHOP_OK || (rc = allow_topk_lds<B, KC, true>()) != ADAHOP_OK) return rc;
+    return allow_topk_lds<B, KC, false>();
+}
+
 #define ADAHOP_DISPATCH(b, CALL)            \
     switch (b) {                            \
     case 0: return CALL(0);                 \
@@ -896,6 +935,12 @@ int launch_two(int b, quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const
 #define ADAHOP_TWO(BB) launch_two_b<BB>(ka, qa, kb, qb, st)
     ADAHOP_DISPATCH(b, ADAHOP_TWO)
 #undef ADAHOP_TWO
+}
+int launch_topk(int b, const topk_job_t &t, quant_kind_t kind, const quant_t &q, hipStream_t st)
+{
+#define ADAHOP_TOPK(BB) launch_topk_b<BB>(t, kind, q, st)
+    ADAHOP_DISPATCH(b, ADAHOP_TOPK)
+#undef ADAHOP_TOPK
 }
 #undef ADAHOP_DISPATCH
 
@@ -930,6 +975,43 @@ int launch_iht_quantize_two(int b, const quant_job_t &ja, const quant_job_t &jb,
         return ka == KS && kb != KS ? launch_two(b, kb, qb, ka, qa, st) : launch_two(b, ka, qa, kb, qb, st);
     const int rc = launch_one(b, ja.sr_seed != nullptr, ka, qa, st);
     return rc != ADAHOP_OK ? rc : launch_one(b, jb.sr_seed != nullptr, kb, qb, st);
+}
+
+// Every instance of the kernel that selects beside a quantiser, once per device (host-side calls, nothing queued).
+int configure_iht_quantize()
+{
+    static device_once_t once;
+    int dev = 0;
+    int rc = check_hip(hipGetDevice(&dev));
+    if (rc != ADAHOP_OK || !once.need(dev)) return rc;
+    if ((rc = allow_topk_b<0>()) != ADAHOP_OK || (rc = allow_topk_b<32>()) != ADAHOP_OK || (rc = allow_topk_b<64>()) != ADAHOP_OK ||
+        (rc = allow_topk_b<128>()) != ADAHOP_OK || (rc = allow_topk_b<256>()) != ADAHOP_OK)
+        return rc;
+    once.mark(dev);
+    return ADAHOP_OK;
+}
+
+// The selection by 256 threads, the workgroup size of the quantisers, takes up to 15 us in place of the 9 us of 1024 threads (8192
+// keys), but then 9 us less of everything else: 9 + 31 -> 16 + 19 us for 8192 x 4096 beside a K-strided 4096 x 4096, 9 + 44 -> 22 +
+// 24 for two K-strided operands of 8192 tokens x 4096.  Not for operands that are rounded stochastically (no such instance) or whose
+// K-strided order is a special one, and above 64 M elements only where the keys fit into the LDS that every workgroup of the
+// launch has anyway: more of it costs waves in flight.
+bool topk_beside_quant(int64_t dim, const quant_job_t &job)
+{
+    quant_t q;
+    const quant_kind_t kind = describe(job, q);
+    if (dim > TOPK_BESIDE_DIM || job.sr_seed || kind == KC_GATHER || (kind == KS && q.group)) return false;
+    const bool fits = kind == KS && topk_lds_bytes<256>((int)dim) <= (size_t)KS_LDS;
+    return q.outer * q.K <= (fits ? 1ll << 31 : 64ll << 20);
+}
+
+int launch_topk_beside_quant(const topk_job_t &topk, int b, const quant_job_t &job, hipStream_t st)
+{
+    int rc = configure_iht_quantize();
+    if (rc != ADAHOP_OK) return rc;
+    quant_t q;
+    const quant_kind_t kind = describe(job, q);
+    return launch_topk(b, topk, kind, q, st);
 }
 
 } // namespace adahop

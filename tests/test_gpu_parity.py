@@ -608,3 +608,26 @@ def test_quantisers_of_both_operands(ah, layouts, M, N, K, b, strategy):
         rc, rs = orc.iht_quantize(bits, True, b, zo, mask_k)
         assert np.array_equal(host(out[name + "_scales"]), rs), name
         assert np.array_equal(host(out[name + "_codes"]), rc), name
+
+
+@pytest.mark.parametrize("dim,k", [(40, 40), (257, 3), (1024, 200), (1025, 256), (4099, 257), (8192, 82), (8192, 5000), (8193, 82)])
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+@pytest.mark.parametrize("ties", [False, True])
+def test_selection_beside_a_quantiser(ah, dim, k, strategy, ties):
+    """Fewer and more keys than threads, k up to and past what the threads' maxima can bound, the largest count the joint
+    launch takes and one more; equal scores.  Indices and mask are those of the selection by itself, codes the oracle's."""
+    K, other = 96, 200
+    bits = inputs.matrix(dim, K, 1.0, 9300, row_outliers=(3, 60.0, 60.0))
+    if ties:
+        bits[:] = bits[np.arange(dim) % 7]
+    free = inputs.matrix(other, K, 0.02, 9301)
+    say("selection beside a quantiser", dim, k, inputs.STRATEGY_NAMES[strategy], "ties" if ties else "")
+    x, y = ah.Operand.from_bits(bits, True), ah.Operand.from_bits(free, True)
+    want_idx, want_mask, _ = ah.adahop_foid_topk(x, 0, k)
+    row = strategy == inputs.IHT_OE_ROW
+    out = ah.adahop_gemm(*((x, y) if row else (y, x)), strategy, 32, k)
+    torch.cuda.synchronize()
+    assert torch.equal(out["idx"], want_idx) and torch.equal(out["mask"], want_mask)
+    for name, b, zo in (("a" if row else "b", bits, host(want_mask)), ("b" if row else "a", free, None)):
+        rc, rs = orc.iht_quantize(b, True, 32, zo, None)
+        assert np.array_equal(host(out[name + "_scales"]), rs) and np.array_equal(host(out[name + "_codes"]), rc), name
