@@ -119,21 +119,43 @@ constexpr int STAGE_BYTES = SLAB_BYTES + (TM + TN) * 8; // + 8 scale bytes per r
 constexpr int TILED_LDS_BYTES = NSTAGE * STAGE_BYTES;
 
 // out[s][row][0..7] = in[row][8s .. 8s+7]; of a last stage with t < 8 blocks the last t bytes, behind zeros (see above).
-// WORDS: K % 256 == 0 and the scales 8-byte aligned, so that a row's eight bytes are one word.
+// A workgroup turns 32 rows x 32 stages in LDS: reads are 256-byte pieces of rows, writes 256-byte runs of rows.  (One thread per row
+// and stage, eight bytes at a time down the rows, took 12 us for the 11008 rows of K = 6016, now 5.)
+// WORDS: KB % 4 == 0 and the scales 4-byte aligned, so that a row is whole words.
+constexpr int SMS_ROWS = 32, SMS_STAGES = 32 /* 256 bytes of a row */, SMS_PITCH = SMS_STAGES * 8 + 4;
 template <bool WORDS>
 __global__ __launch_bounds__(256) void k_stage_major_scales(const uint8_t *__restrict__ in, uint64_t *__restrict__ out,
                                                             int64_t rows, int64_t KB)
 {
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x, stages = (KB + 7) >> 3;
-    if (g >= rows * stages) return;
-    const int64_t s = g / rows, r = g - s * rows; // consecutive threads: consecutive rows (coalesced writes)
-    if constexpr (WORDS) {
-        out[g] = reinterpret_cast<const uint64_t *>(in)[r * stages + s];
-    } else {
-        const int t = (int)(KB - 8 * s < 8 ? KB - 8 * s : 8);
-        uint64_t v = 0;
-        for (int j = 0; j < t; ++j) v |= (uint64_t)in[r * KB + 8 * s + j] << (8 * (j + 8 - t));
-        out[g] = v;
+    __shared__ __attribute__((aligned(4))) uint8_t tile[SMS_ROWS * SMS_PITCH];
+    const int64_t r0 = (int64_t)blockIdx.x * SMS_ROWS, s0 = (int64_t)blockIdx.y * SMS_STAGES, stages = (KB + 7) >> 3;
+    // (all loads of a thread in flight together)
+    if constexpr (WORDS) { // 64 words of a row, four rows per pass
+        constexpr int PASSES = SMS_ROWS / 4;
+        const int d = threadIdx.x & 63, r = threadIdx.x >> 6;
+        uint32_t v[PASSES];
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) {
+            const int64_t row = r0 + r + 4 * i, blk = 8 * s0 + 4 * d;
+            v[i] = row < rows && blk < KB ? *reinterpret_cast<const uint32_t *>(in + row * KB + blk) : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < PASSES; ++i) *reinterpret_cast<uint32_t *>(tile + (r + 4 * i) * SMS_PITCH + 4 * d) = v[i];
+    } else { // a row per pass
+        const int64_t blk = 8 * s0 + threadIdx.x;
+        uint8_t v[SMS_ROWS];
+#pragma unroll
+        for (int i = 0; i < SMS_ROWS; ++i) v[i] = r0 + i < rows && blk < KB ? in[(r0 + i) * KB + blk] : (uint8_t)0;
+#pragma unroll
+        for (int i = 0; i < SMS_ROWS; ++i) tile[i * SMS_PITCH + threadIdx.x] = v[i];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < SMS_ROWS * SMS_STAGES; i += 256) {
+        const int r = i % SMS_ROWS, s = i / SMS_ROWS;
+        if (r0 + r >= rows || s0 + s >= stages) continue;
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(tile + r * SMS_PITCH + 8 * s);
+        const int64_t left = KB - 8 * (s0 + s);
+        out[(s0 + s) * rows + r0 + r] = ((uint64_t)w[1] << 32 | w[0]) << (left < 8 ? 8 * (8 - (int)left) : 0);
     }
 }
 
@@ -723,8 +745,8 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
     uint8_t *a_sm = gemm_mx_scales_sm(workspace, M, K, 0), *b_sm = gemm_mx_scales_sm(workspace, M, K, 1);
     const int64_t KB = K / 32;
     auto reorder = [&](const uint8_t *in, uint8_t *out, int64_t rows) {
-        const dim3 g((unsigned)ceil_div(rows * ceil_div(KB, 8), 256));
-        if (KB % 8 == 0 && aligned(in, 8))
+        const dim3 g((unsigned)ceil_div(rows, SMS_ROWS), (unsigned)ceil_div(KB, 8 * SMS_STAGES));
+        if (KB % 4 == 0 && aligned(in, 4))
             hipLaunchKernelGGL(k_stage_major_scales<true>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
         else
             hipLaunchKernelGGL(k_stage_major_scales<false>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
