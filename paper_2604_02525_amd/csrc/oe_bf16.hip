@@ -35,13 +35,15 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 //                      slice writes its own partial tile (no atomics: the result does not depend on scheduling);
 //   3. k_oe_reduce     adds the slices in a fixed order and writes the rows / columns of C.
 // ------------------------------------------------------------------------------------------------
-constexpr int SK_LCOLS = 256;  // rows of L per workgroup
+constexpr int SK_LCOLS = 256;  // rows of L per workgroup (NCW = 2; half of them with NCW = 1)
 constexpr int SK_KSTAGE = 64;  // K-elements per pipeline stage
 constexpr int SK_PITCH = 72;   // LDS row pitch in bf16 of the [row][64 K] layout (144 bytes: 16-byte fragment
                                // reads of 16 consecutive rows then cover the 64 banks exactly once)
-constexpr int SK_TPITCH = 288; // pitch in bf16 of the [K][256 rows] layout (576 bytes: the four K-rows of one
-                               // transposing read of 32 lanes start 16 banks apart)
-constexpr int SK_L_ELEMS = SK_LCOLS * SK_PITCH; // = SK_KSTAGE * SK_TPITCH: either layout of a stage of L
+// Pitch in bf16 of the [K][128 NCW rows] layout (576 or 320 bytes: the four K-rows of one transposing read of 32 lanes start
+// 16 banks apart), and the elements of a stage of L in either layout.
+template <int NCW> constexpr int sk_tpitch() { return NCW == 2 ? 288 : 160; }
+template <int NCW> constexpr int sk_l_elems() { return NCW == 2 ? 256 * SK_PITCH : SK_KSTAGE * 160; }
+static_assert(sk_l_elems<2>() == SK_KSTAGE * sk_tpitch<2>() && sk_l_elems<1>() >= 128 * SK_PITCH, "either layout fits");
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
@@ -86,15 +88,19 @@ __global__ __launch_bounds__(256) void k_gather_rows_strided(const uint16_t *__r
     }
 }
 
-template <int RT, bool LONG_KC>
+// NCW: column tiles of 32 rows of L per wave.  2, and 1 where the products' workgroups then fill no more than half of the compute
+// units (a short L, or a K of few slices): 82 rows x 4096 x 4096 16.4 -> 14.1 us, 82 x 2048 x 2048 13.0 -> 8.8, 41 x 2048 x 8192
+// 14.5 -> 11.1, 41 columns x 320 x 4096 10.3 -> 6.9.
+template <int RT, bool LONG_KC, int NCW>
 __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict__ Sg, const uint16_t *__restrict__ L,
                                                       int64_t ldl, int64_t Lo, int64_t K, int stages_per_slice,
                                                       float *__restrict__ P, int64_t rows_all)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[]; // 2 x (stage of Sg, stage of L)
-    constexpr int S_ELEMS = RT * 32 * SK_PITCH, BUF_ELEMS = S_ELEMS + SK_L_ELEMS;
+    constexpr int S_ELEMS = RT * 32 * SK_PITCH, BUF_ELEMS = S_ELEMS + sk_l_elems<NCW>(), SK_TPITCH = sk_tpitch<NCW>();
+    constexpr int NL = 4 * NCW, KPP = NCW == 2 ? 8 : 16; // pieces of L per lane and stage; K-rows per pass of a K-strided L
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-    const int64_t l0 = (int64_t)blockIdx.x * SK_LCOLS;
+    const int64_t l0 = (int64_t)blockIdx.x * (128 * NCW);
     const int nstage_all = (int)((K + SK_KSTAGE - 1) / SK_KSTAGE);
     const int s0 = blockIdx.y * stages_per_slice, s1 = min(s0 + stages_per_slice, nstage_all);
     Sg += (int64_t)blockIdx.z * RT * 32 * K;
@@ -106,15 +112,15 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     // 256 rows of at most 2^21 elements).  Rows of L past the end are replaced by the last row (their results are
     // not stored); in a last stage of 32 K-elements the upper half reads the lower half again and the Sg side is
     // zero there.
-    const int c8 = tid & 7, r32 = tid >> 3, c32 = tid & 31, k8 = tid >> 5;
+    const int c8 = tid & 7, r32 = tid >> 3, c32 = tid & (16 * NCW - 1), k8 = tid / (16 * NCW);
     const int64_t last_row = Lo - 1 - l0; // >= 0
     const char *const Lb = reinterpret_cast<const char *>(L + (LONG_KC ? l0 * ldl : 0));
     const char *const Sb = reinterpret_cast<const char *>(Sg);
     const uint32_t voff_s = (uint32_t)(((int64_t)r32 * K + c8 * 8) * 2);
-    uint32_t voff_l[LONG_KC ? 8 : 1];
+    uint32_t voff_l[LONG_KC ? NL : 1];
     if constexpr (LONG_KC) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < NL; ++i) {
             const int64_t r = r32 + 32 * i;
             voff_l[i] = (uint32_t)(((r < last_row ? r : last_row) * ldl + c8 * 8) * 2);
         }
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
         const int64_t kk0 = (int64_t)(ghost ? s1 - 1 : stage) * SK_KSTAGE;
         return (ghost || (kk0 + SK_KSTAGE > K && c8 >= 4)) ? 0u : 0xffffffffu;
     };
-    auto fetch = [&](int stage, uint4 (&fs)[RT], uint4 (&fl)[8], auto quarter) {
+    auto fetch = [&](int stage, uint4 (&fs)[RT], uint4 (&fl)[NL], auto quarter) {
         constexpr int Q = decltype(quarter)::value;
         const bool ghost = stage >= s1;
         const int64_t kk0 = (int64_t)(ghost ? s1 - 1 : stage) * SK_KSTAGE;
@@ -148,15 +154,15 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             fs[i] = *reinterpret_cast<const uint4 *>(Sb + ((int64_t)32 * i * K + kk0) * 2 + (voff_s - back));
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (Q >= 0 && (i >> 1) != Q) continue;
+        for (int i = 0; i < NL; ++i) {
+            if (Q >= 0 && i / NCW != Q) continue;
             if constexpr (LONG_KC)
                 fl[i] = load_once16(Lb + kk0 * 2 + (voff_l[i] - back));
             else
-                fl[i] = load_once16(Lb + (kk0 + (half ? (8 * i) & 31 : 8 * i)) * ldl * 2 + voff_l[0]);
+                fl[i] = load_once16(Lb + (kk0 + (half ? (KPP * i) & 31 : KPP * i)) * ldl * 2 + voff_l[0]);
         }
     };
-    auto stash = [&](uint16_t *buf, const uint4 (&fs)[RT], const uint4 (&fl)[8], uint32_t keep, auto quarter) {
+    auto stash = [&](uint16_t *buf, const uint4 (&fs)[RT], const uint4 (&fl)[NL], uint32_t keep, auto quarter) {
         constexpr int Q = decltype(quarter)::value;
         uint16_t *sS = buf, *sL = buf + S_ELEMS;
 #pragma unroll
@@ -166,28 +172,28 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
                 make_uint4(fs[i].x & keep, fs[i].y & keep, fs[i].z & keep, fs[i].w & keep);
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (Q >= 0 && (i >> 1) != Q) continue;
+        for (int i = 0; i < NL; ++i) {
+            if (Q >= 0 && i / NCW != Q) continue;
             if constexpr (LONG_KC)
                 *reinterpret_cast<uint4 *>(sL + (r32 + 32 * i) * SK_PITCH + c8 * 8) = fl[i];
             else
-                *reinterpret_cast<uint4 *>(sL + (k8 + 8 * i) * SK_TPITCH + 8 * c32) = fl[i];
+                *reinterpret_cast<uint4 *>(sL + (k8 + KPP * i) * SK_TPITCH + 8 * c32) = fl[i];
         }
     };
     typedef std::integral_constant<int, -1> all_t;
 
-    v16f acc[RT][2];
+    v16f acc[RT][NCW];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < NCW; ++c)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][c][r] = 0.0f;
 
     // As supplier of addresses for the transposing read, lane s of a group of 16 points at 4 consecutive rows of L
     // (4 (s % 4) ..) in K-row s / 4; lane n of the group then receives K-rows 0 .. 3 of row n.  The four groups of a
     // wave are (rows 0-15 | 16-31 of the 32-row tile) x (K-half h) as the matrix cores want them.
-    const int tr_elem = ((lane & 15) >> 2) * SK_TPITCH + 64 * w + 16 * ((lane >> 4) & 1) + 4 * (lane & 3) + 8 * h * SK_TPITCH;
+    const int tr_elem = ((lane & 15) >> 2) * SK_TPITCH + 32 * NCW * w + 16 * ((lane >> 4) & 1) + 4 * (lane & 3) + 8 * h * SK_TPITCH;
 
     // One stage: multiply from `cur`; meanwhile write the stage that has arrived in (fs, fl) into `oth` (every wave
     // left that buffer before the last barrier) and refill (fs, fl) with stage `next`.  A wave issues in order and
@@ -196,16 +202,16 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     // the matrix-core instructions of K-step ks (scheduling groups), and a scheduling barrier after every K-step
     // keeps the compiler from reading a whole stage's fragments (128 registers) ahead.
     // (fs, fl) hold stage next - 2 on entry.
-    auto stage_body = [&](const uint16_t *cur, uint16_t *oth, uint4 (&fs)[RT], uint4 (&fl)[8], int next) {
+    auto stage_body = [&](const uint16_t *cur, uint16_t *oth, uint4 (&fs)[RT], uint4 (&fl)[NL], int next) {
         const uint32_t keep = stage_keep(next - 2);
         const uint16_t *sS = cur, *sL = cur + S_ELEMS;
         uint4 a[2][RT];
-        v8bf b[2][2];
-        auto fragments = [&](int ks, uint4 (&fa)[RT], v8bf (&fb)[2]) {
+        v8bf b[2][NCW];
+        auto fragments = [&](int ks, uint4 (&fa)[RT], v8bf (&fb)[NCW]) {
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
+            for (int c = 0; c < NCW; ++c) {
                 if constexpr (LONG_KC) {
-                    const uint4 v = *reinterpret_cast<const uint4 *>(sL + (64 * w + 32 * c + l32) * SK_PITCH + 16 * ks + 8 * h);
+                    const uint4 v = *reinterpret_cast<const uint4 *>(sL + (32 * NCW * w + 32 * c + l32) * SK_PITCH + 16 * ks + 8 * h);
                     fb[c] = __builtin_bit_cast(v8bf, v);
                 } else {
                     const uint16_t *q = sL + tr_elem + 16 * ks * SK_TPITCH + 32 * c;
@@ -223,19 +229,19 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
         };
         auto step = [&](auto ks_c) {
             constexpr int ks = decltype(ks_c)::value;
-            constexpr int n_read = ks + 1 < SK_KSTAGE / 16 ? RT + (LONG_KC ? 2 : 4) : 0;
-            constexpr int n_move = 2 + (ks < RT ? 1 : 0) + (ks + 4 < RT ? 1 : 0); // LDS writes = loads of this quarter
+            constexpr int n_read = ks + 1 < SK_KSTAGE / 16 ? RT + (LONG_KC ? NCW : 2 * NCW) : 0;
+            constexpr int n_move = NCW + (ks < RT ? 1 : 0) + (ks + 4 < RT ? 1 : 0); // LDS writes = loads of this quarter
             if constexpr (ks + 1 < SK_KSTAGE / 16) fragments(ks + 1, a[(ks + 1) & 1], b[(ks + 1) & 1]);
             stash(oth, fs, fl, keep, ks_c);
             fetch(next, fs, fl, ks_c);
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int c = 0; c < NCW; ++c)
                     acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a[ks & 1][i]), b[ks & 1][c],
                                                                         acc[i][c], 0, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 2 * RT; ++j) {
+            for (int j = 0; j < NCW * RT; ++j) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // one matrix-core instruction
                 if (j < n_read) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); // one LDS read
                 if (j < n_move) {
@@ -255,7 +261,7 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
 
     // Register set (stage - s0) & 1 carries a stage from memory to LDS buffer (stage - s0) & 1.  While a stage is
     // multiplied, the next one is written into the other buffer and the two after that are in flight.
-    uint4 ps[2][RT], pl[2][8];
+    uint4 ps[2][RT], pl[2][NL];
     uint16_t *buf0 = smem, *buf1 = smem + BUF_ELEMS;
     fetch(s0, ps[0], pl[0], all_t());
     fetch(s0 + 1, ps[1], pl[1], all_t());
@@ -270,8 +276,8 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     }
 
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const int64_t l = l0 + 64 * w + 32 * c + l32;
+    for (int c = 0; c < NCW; ++c) {
+        const int64_t l = l0 + 32 * NCW * w + 32 * c + l32;
         if (l < Lo) {
 #pragma unroll
             for (int i = 0; i < RT; ++i)
@@ -349,7 +355,7 @@ __global__ __launch_bounds__(256) void k_oe_reduce4(const float *__restrict__ P,
 }
 
 struct skinny_plan_t {
-    int rt, groups, nslice, stages_per_slice;
+    int rt, groups, nslice, stages_per_slice, ncw;
     int64_t rows_all;
     size_t sg_bytes, p_bytes;
 };
@@ -370,38 +376,50 @@ skinny_plan_t plan_skinny(int64_t Lo, int64_t K, int k)
                               // partly filled round costs more than idle compute units do
     if (want > nstage / 8) want = nstage / 8;
     if (want < 1) want = 1;
-    p.stages_per_slice = (int)ceil_div(nstage, want);
-    p.nslice = (int)ceil_div(nstage, p.stages_per_slice);
+    auto slice = [&](int64_t n) {
+        p.stages_per_slice = (int)ceil_div(nstage, n);
+        p.nslice = (int)ceil_div(nstage, p.stages_per_slice);
+    };
+    slice(want);
     p.sg_bytes = align_up((size_t)p.rows_all * K * 2, 256);
     p.p_bytes = align_up((size_t)p.nslice * p.rows_all * Lo * 4, 256);
+    p.ncw = 2;
+    if (wgs * want <= 128) { // half of L per workgroup; never more slices (and scratch) than with the whole of it
+        p.ncw = 1;
+        const int64_t most = 256 / (ceil_div(Lo, SK_LCOLS / 2) * p.groups);
+        if (want > most) slice(most < 1 ? 1 : most);
+    }
     return p;
 }
 
-template <int RT, bool LONG_KC> constexpr size_t skinny_lds_bytes() { return 2 * (RT * 32 * SK_PITCH + SK_L_ELEMS) * sizeof(uint16_t); }
+template <int RT, int NCW> constexpr size_t skinny_lds_bytes() { return 2 * (RT * 32 * SK_PITCH + sk_l_elems<NCW>()) * sizeof(uint16_t); }
 
-template <int RT, bool LONG_KC> int allow_skinny_lds()
+template <int RT, bool LONG_KC, int NCW> int allow_skinny_lds()
 {
-    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_oe_skinny<RT, LONG_KC>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)skinny_lds_bytes<RT, LONG_KC>()));
+    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_oe_skinny<RT, LONG_KC, NCW>),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)skinny_lds_bytes<RT, NCW>()));
 }
 
-template <int RT, bool LONG_KC>
+template <int RT, bool LONG_KC, int NCW>
 int launch_skinny_as(dim3 grid, hipStream_t st, const uint16_t *Sg, const uint16_t *L, int64_t ldl, int64_t Lo, int64_t K,
                      int sps, float *P, int64_t rows_all)
 {
     const int rc = configure_oe_rowcol(); // more LDS than a launch may ask for by default: allowed once per device
     if (rc != ADAHOP_OK) return rc;
-    constexpr size_t lds = skinny_lds_bytes<RT, LONG_KC>();
-    hipLaunchKernelGGL((k_oe_skinny<RT, LONG_KC>), grid, dim3(256), lds, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    constexpr size_t lds = skinny_lds_bytes<RT, NCW>();
+    hipLaunchKernelGGL((k_oe_skinny<RT, LONG_KC, NCW>), grid, dim3(256), lds, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
     return check_launch();
 }
 
 template <int RT>
-int launch_skinny(bool long_kc, dim3 grid, hipStream_t st, const uint16_t *Sg, const uint16_t *L, int64_t ldl, int64_t Lo,
+int launch_skinny(bool long_kc, int ncw, dim3 grid, hipStream_t st, const uint16_t *Sg, const uint16_t *L, int64_t ldl, int64_t Lo,
                   int64_t K, int sps, float *P, int64_t rows_all)
 {
-    return long_kc ? launch_skinny_as<RT, true>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all)
-                   : launch_skinny_as<RT, false>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    if (ncw == 1)
+        return long_kc ? launch_skinny_as<RT, true, 1>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all)
+                       : launch_skinny_as<RT, false, 1>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    return long_kc ? launch_skinny_as<RT, true, 2>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all)
+                   : launch_skinny_as<RT, false, 2>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
 }
 
 // out[o, t] = x(o, idx[t]) for t < k, 0 for k <= t < kpad.  out is [outer, kpad] bf16.
@@ -498,9 +516,12 @@ int configure_oe_rowcol()
     int dev = 0;
     int rc = check_hip(hipGetDevice(&dev));
     if (rc != ADAHOP_OK || !once.need(dev)) return rc;
-    if ((rc = allow_skinny_lds<2, true>()) != ADAHOP_OK || (rc = allow_skinny_lds<2, false>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<4, true>()) != ADAHOP_OK || (rc = allow_skinny_lds<4, false>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<6, true>()) != ADAHOP_OK || (rc = allow_skinny_lds<6, false>()) != ADAHOP_OK)
+    if ((rc = allow_skinny_lds<2, true, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds<2, false, 1>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds<4, true, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds<4, false, 1>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds<6, true, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds<6, false, 1>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds<2, true, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds<2, false, 2>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds<4, true, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds<4, false, 2>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds<6, true, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds<6, false, 2>()) != ADAHOP_OK)
         return rc;
     once.mark(dev);
     return ADAHOP_OK;
@@ -538,12 +559,12 @@ int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int k
     int rc = check_launch();
     if (rc != ADAHOP_OK) return rc;
 
-    const dim3 grid((unsigned)ceil_div(Lo, SK_LCOLS), (unsigned)p.nslice, (unsigned)p.groups);
+    const dim3 grid((unsigned)ceil_div(Lo, SK_LCOLS / 2 * p.ncw), (unsigned)p.nslice, (unsigned)p.groups);
     const uint16_t *l = static_cast<const uint16_t *>(L.data);
     switch (p.rt) {
-    case 2: rc = launch_skinny<2>(L.k_contig, grid, st, Sg, l, L.ld, Lo, K, p.stages_per_slice, P, p.rows_all); break;
-    case 4: rc = launch_skinny<4>(L.k_contig, grid, st, Sg, l, L.ld, Lo, K, p.stages_per_slice, P, p.rows_all); break;
-    default: rc = launch_skinny<6>(L.k_contig, grid, st, Sg, l, L.ld, Lo, K, p.stages_per_slice, P, p.rows_all); break;
+    case 2: rc = launch_skinny<2>(L.k_contig, p.ncw, grid, st, Sg, l, L.ld, Lo, K, p.stages_per_slice, P, p.rows_all); break;
+    case 4: rc = launch_skinny<4>(L.k_contig, p.ncw, grid, st, Sg, l, L.ld, Lo, K, p.stages_per_slice, P, p.rows_all); break;
+    default: rc = launch_skinny<6>(L.k_contig, p.ncw, grid, st, Sg, l, L.ld, Lo, K, p.stages_per_slice, P, p.rows_all); break;
     }
     if (rc != ADAHOP_OK) return rc;
 
