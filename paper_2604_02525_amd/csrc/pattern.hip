@@ -20,6 +20,8 @@
 //   k_pattern_finish   one workgroup adds these and writes the class and the four CV figures.
 #include "common.h"
 
+#include <type_traits>
+
 namespace adahop {
 
 namespace {
@@ -64,7 +66,7 @@ template <int CTRL> __device__ __forceinline__ double dpp_double(double v)
 // Bound by the fp64 sums beside the reads: five fp64 instructions per element, and what the row sums take across the lanes.  Those
 // of 8 rows (16 numbers per lane) are halved together: every exchange leaves a lane with half as many numbers summed over
 // twice as many lanes, 63 instructions for 8 rows, where a reduction for each row by itself was 288, two thirds of them through the LDS
-// (16384 x 8192: 91 -> 64 us; the detector as a whole 120 -> 71).
+// (16384 x 8192: 91 -> 64 us).
 // W waves: 8 (two workgroups per compute unit), and 16 where there are fewer workgroups than compute units (371 x 12288: 48 workgroups,
 // 34 -> 14 us).
 template <int W>
@@ -79,75 +81,99 @@ __global__ __launch_bounds__(64 * W, 4) void k_pattern_partial(const uint16_t *_
     for (int j = 0; j < 8; ++j) cs[j] = cq[j] = 0.0;
     const bool whole = c0 + 8 <= C; // C % 8 == 0 is not required: what lies behind a row counts as 0
     const int mine = (int)min((int64_t)PT_ROWS, R - r0); // rows of this block
-    for (int i0 = 0; i0 < PT_ROWS / W; i0 += 8) { // eight rows of the wave at a time: their loads are in flight together
-        if (w + W * i0 >= mine) break;
-        uint4 u[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int r = w + W * (i0 + t);
-            u[t] = make_uint4(0, 0, 0, 0);
+    // Every 16-byte piece of the block lies inside the matrix, from its first element to its last one: all but the last rows of the
+    // last columns where C % 8 != 0.
+    const int64_t cb = (int64_t)blockIdx.x * PT_COLS, cend = min(cb + PT_COLS, (C + 7) / 8 * 8), end = (R - 1) * ld + C;
+    const bool clean = (r0 + mine - 1) * ld + cend <= end;
+    const uint16_t *const mycol = S + (c0 < C ? c0 : cb);
+
+    // A clean block's loads have no condition (rows behind the last one read that again and are cleared at their use): of loads under a
+    // lane's condition the compiler waits for some before it asks for the next.  Eight are in flight now, and each is waited for
+    // where it is used: 64 -> 58 us on 16384 x 8192.  Each row's successor asked for as soon as the row is read, an iteration ahead, was
+    // slower (64 us): the registers that holds are copied at the end of the loop, behind a wait for all.
+    const auto load_row = [&](auto is_clean, int i) {
+        const int r = w + W * i;
+        if constexpr (decltype(is_clean)::value) {
+            return load_once16(mycol + (r0 + min(r, mine - 1)) * ld);
+        } else {
+            uint4 u = make_uint4(0, 0, 0, 0);
             if (r < mine) {
                 const uint16_t *p = S + (r0 + r) * ld + c0;
-                if (whole || (c0 < C && r0 + r + 1 < R)) { // (behind a row there is the next one, or what its stride leaves)
-                    u[t] = load_once16(p);
+                if (c0 < C && (r0 + r) * ld + c0 + 8 <= end) { // (behind a row there is the next one, or what its stride leaves)
+                    u = load_once16(p);
                 } else if (c0 < C) { // the last chunk of the last row
                     uint64_t lo = 0, hi = 0;
 #pragma nounroll
-                    for (int j = (int)(C - c0) - 1; j >= 0; --j) {
+                    for (int j = (int)min((int64_t)8, C - c0) - 1; j >= 0; --j) {
                         hi = hi << 16 | lo >> 48;
                         lo = lo << 16 | p[j];
                     }
-                    u[t] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+                    u = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
                 }
             }
+            return u;
         }
-        // number 2 t of the 16: the sum of row t, 2 t + 1: its sum of squares.  Rows t and t + 4 one after the other, their numbers
-        // halved at once, and no row begun before: more rows under way take more registers than two workgroups have.
-        double v[8];
+    };
+    const auto all_rows = [&](auto is_clean) {
+        for (int i0 = 0; i0 < PT_ROWS / W; i0 += 8) {
+            if (w + W * i0 >= mine) break;
+            uint4 u[8]; // eight rows of the wave are in flight together, asked for in the order of their use
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            double n4[2][2];
-#pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                uint32_t word[4] = {u[t + 4 * y].x, u[t + 4 * y].y, u[t + 4 * y].z, u[t + 4 * y].w};
-                if (!whole) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) word[j] &= (c0 + 2 * j < C ? 0xffffu : 0u) | (c0 + 2 * j + 1 < C ? 0xffff0000u : 0u);
-                }
-                asm volatile("" : "+v"(word[0]), "+v"(word[1]), "+v"(word[2]), "+v"(word[3]));
-                __builtin_amdgcn_sched_barrier(0);
-                double rs = 0.0, rq = 0.0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const double x = (double)(j & 1 ? bf16_hi(word[j >> 1]) : bf16_lo(word[j >> 1]));
-                    rs += x;
-                    rq = __builtin_fma(x, x, rq); // (the square is exact: fused or not, the same sums)
-                    cs[j] += x;
-                    cq[j] = __builtin_fma(x, x, cq[j]);
-                }
-                // (here, not at the end of the loop body, where the compiler would add a whole iteration's elements, kept in registers)
-                asm volatile("" : "+v"(cs[0]), "+v"(cs[1]), "+v"(cs[2]), "+v"(cs[3]), "+v"(cs[4]), "+v"(cs[5]), "+v"(cs[6]), "+v"(cs[7]));
-                asm volatile("" : "+v"(cq[0]), "+v"(cq[1]), "+v"(cq[2]), "+v"(cq[3]), "+v"(cq[4]), "+v"(cq[5]), "+v"(cq[6]), "+v"(cq[7]));
-                n4[y][0] = rs;
-                n4[y][1] = rq;
+            for (int t = 0; t < 4; ++t) {
+                u[t] = load_row(is_clean, i0 + t);
+                u[t + 4] = load_row(is_clean, i0 + t + 4);
             }
-            v[2 * t] = halve<32>(n4[0][0], n4[1][0]);
-            v[2 * t + 1] = halve<32>(n4[0][1], n4[1][1]);
+            // number 2 t of the 16: the sum of row t, 2 t + 1: its sum of squares.  Rows t and t + 4 one after the other, their numbers
+            // halved at once, and no row begun before: more rows under way take more registers than two workgroups have.
+            double v[8];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                double n4[2][2];
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    uint32_t word[4] = {u[t + 4 * y].x, u[t + 4 * y].y, u[t + 4 * y].z, u[t + 4 * y].w};
+                    if (w + W * (i0 + t + 4 * y) >= mine) word[0] = word[1] = word[2] = word[3] = 0;
+                    if (!whole) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) word[j] &= (c0 + 2 * j < C ? 0xffffu : 0u) | (c0 + 2 * j + 1 < C ? 0xffff0000u : 0u);
+                    }
+                    asm volatile("" : "+v"(word[0]), "+v"(word[1]), "+v"(word[2]), "+v"(word[3]));
+                    __builtin_amdgcn_sched_barrier(0);
+                    double rs = 0.0, rq = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const double x = (double)(j & 1 ? bf16_hi(word[j >> 1]) : bf16_lo(word[j >> 1]));
+                        rs += x;
+                        rq = __builtin_fma(x, x, rq); // (the square is exact: fused or not, the same sums)
+                        cs[j] += x;
+                        cq[j] = __builtin_fma(x, x, cq[j]);
+                    }
+                    // (here, not at the end of the loop body, where the compiler would add a whole iteration's elements, kept in registers)
+                    asm volatile("" : "+v"(cs[0]), "+v"(cs[1]), "+v"(cs[2]), "+v"(cs[3]), "+v"(cs[4]), "+v"(cs[5]), "+v"(cs[6]), "+v"(cs[7]));
+                    asm volatile("" : "+v"(cq[0]), "+v"(cq[1]), "+v"(cq[2]), "+v"(cq[3]), "+v"(cq[4]), "+v"(cq[5]), "+v"(cq[6]), "+v"(cq[7]));
+                    n4[y][0] = rs;
+                    n4[y][1] = rq;
+                }
+                v[2 * t] = halve<32>(n4[0][0], n4[1][0]);
+                v[2 * t + 1] = halve<32>(n4[0][1], n4[1][1]);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = halve<16>(v[k], v[k + 4]);
+            const bool b3 = lane & 8, b2 = lane & 4;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) // lane ^ 8
+                v[k] = (b3 ? v[k + 2] : v[k]) + dpp_double<0x128>(b3 ? v[k] : v[k + 2]);
+            double s = (b2 ? v[1] : v[0]) + dpp_double<0x141>(b2 ? v[0] : v[1]); // lane ^ 7
+            s += dpp_double<0xB1>(s);                                            // lane ^ 1
+            s += dpp_double<0x4E>(s);                                            // lane ^ 2
+            // the quad q = lane / 4 holds number q of the 16
+            const int r = w + W * (i0 + (lane >> 3));
+            if ((lane & 3) == 0 && r < mine)
+                reinterpret_cast<double *>(rowpart + (int64_t)blockIdx.x * R + r0 + r)[(lane >> 2) & 1] = s;
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = halve<16>(v[k], v[k + 4]);
-        const bool b3 = lane & 8, b2 = lane & 4;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) // lane ^ 8
-            v[k] = (b3 ? v[k + 2] : v[k]) + dpp_double<0x128>(b3 ? v[k] : v[k + 2]);
-        double s = (b2 ? v[1] : v[0]) + dpp_double<0x141>(b2 ? v[0] : v[1]); // lane ^ 7
-        s += dpp_double<0xB1>(s);                                            // lane ^ 1
-        s += dpp_double<0x4E>(s);                                            // lane ^ 2
-        // the quad q = lane / 4 holds number q of the 16
-        const int r = w + W * (i0 + (lane >> 3));
-        if ((lane & 3) == 0 && r < mine)
-            reinterpret_cast<double *>(rowpart + (int64_t)blockIdx.x * R + r0 + r)[(lane >> 2) & 1] = s;
-    }
+    };
+    if (clean) all_rows(std::true_type{});
+    else all_rows(std::false_type{});
 #pragma unroll
     for (int j = 0; j < 8; ++j) scol[w][64 * j + lane] = make_double2(cs[j], cq[j]);
     __syncthreads();

@@ -574,6 +574,24 @@ def test_detect_pattern_matches_oracle(ah, shape, k_contig):
         assert np.allclose(host(st), want_st, rtol=1e-9, atol=1e-12), (host(st), want_st)
 
 
+@pytest.mark.parametrize("shape", [(3, 256), (521, 1056), (513, 288), (1031, 32)])
+def test_detect_pattern_where_the_memory_ends_with_the_matrix(ah, shape):
+    """Rows of no whole number of 16-byte pieces, the last of which ends with the memory: the last rows' workgroups read their
+    last pieces by halves, the others do not.  The bounds of the test above."""
+    outer, K = shape
+    logical = inputs.matrix(outer, K, 1.0, 9110, row_outliers=(1, 50.0, 50.0))
+    ld = (outer + 7) // 8 * 8
+    flat = np.full((K - 1) * ld + outer, 0x7fc0, dtype=np.uint16)
+    np.lib.stride_tricks.as_strided(flat, (K, outer), (2 * ld, 2))[:] = logical.T
+    x = torch.from_numpy(flat.view(np.int16)).cuda().as_strided((K, outer), (ld, 1))
+    say("detect_pattern, end of memory", shape)
+    p, st = ah.adahop_detect_pattern(ah.Operand(x, False))
+    torch.cuda.synchronize()
+    want_p, want_st = orc.detect_pattern(logical, True)
+    assert int(host(p)[0]) == want_p
+    assert np.allclose(host(st), want_st, rtol=1e-9, atol=1e-12), (host(st), want_st)
+
+
 # ----------------------------------------------------- extracted parts copied out by the quantisers
 
 @pytest.mark.parametrize("layouts", [(True, True), (True, False), (False, False), (False, True)])
