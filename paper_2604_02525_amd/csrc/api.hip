@@ -404,15 +404,24 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const bool oe_k = oe && strategy == ADAHOP_IHT_OE_K;
     const int kpad_planned = oe_k ? kpad_of(k) : 0;
     // The quantiser that reads an extracted operand anyway also copies the extracted part out for the bf16 product; the position of
-    // a row or channel in the index list comes from a 16-bit table that the selection leaves in the place of the scores, which
-    // nobody reads after it.  Only for indices selected here, which are distinct: a repeated index in a caller's list would
-    // leave a position of the copy unwritten, where the separate gather reads the row twice.
-    const bool fuse = oe && !use_given_idx && foid_writes_positions(dim, k);
-    const bool a_gathers_k = fuse && oe_k && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
-    const bool b_gathers_k = fuse && oe_k && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
-    const bool a_gathers_rows = fuse && strategy == ADAHOP_IHT_OE_ROW && !a_given;
-    const bool b_gathers_rows = fuse && strategy == ADAHOP_IHT_OE_COL && !b_given;
-    uint16_t *pos1 = a_gathers_k || b_gathers_k || a_gathers_rows || b_gathers_rows ? reinterpret_cast<uint16_t *>(scores) : nullptr;
+    // a row or channel in the index list comes from a 16-bit table that the selection leaves beside the mask.  Only for indices selected
+    // here, which are distinct: a repeated index in a caller's list would leave a position of the copy unwritten, where the separate
+    // gather reads the row twice.
+    // The table of K-channels takes the place of the scores.  That of rows and columns lies where the bf16 product keeps its partial sums,
+    // which nobody writes before the quantisers are done: a caller finds the scores in the workspace afterwards.  Where it does not fit
+    // there (more than 128 rows to choose from for each of the other operand's), the rows are gathered by themselves.
+    uint16_t *pos1 = nullptr;
+    if (oe && !use_given_idx && foid_writes_positions(dim, k)) {
+        size_t room = (size_t)dim * sizeof(float);
+        pos1 = oe_k ? reinterpret_cast<uint16_t *>(scores)
+                    : reinterpret_cast<uint16_t *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &room));
+        if (align_up((size_t)dim * sizeof(uint16_t), 4) > room) pos1 = nullptr;
+    }
+    const bool a_gathers_k = pos1 && oe_k && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
+    const bool b_gathers_k = pos1 && oe_k && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
+    const bool a_gathers_rows = pos1 && strategy == ADAHOP_IHT_OE_ROW && !a_given;
+    const bool b_gathers_rows = pos1 && strategy == ADAHOP_IHT_OE_COL && !b_given;
+    if (!(a_gathers_k || b_gathers_k || a_gathers_rows || b_gathers_rows)) pos1 = nullptr;
     // 2. residual -> transform -> MXFP4 (App. F item 2), for the operands the caller has not packed
     const uint8_t *a_codes = a_given ? opts->a_codes : reinterpret_cast<uint8_t *>(ws + L.a_codes);
     const uint8_t *a_scales = a_given ? opts->a_scales : reinterpret_cast<uint8_t *>(ws + L.a_scales);
@@ -434,7 +443,7 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // Row and column extraction: the operand that nothing is extracted from does not wait for the selection, one workgroup of
     // which the rest of the chip would watch (9 us for 8192 rows); its quantiser runs beside it.
     const quant_job_t &free_job = strategy == ADAHOP_IHT_OE_ROW ? jb : ja, &masked_job = strategy == ADAHOP_IHT_OE_ROW ? ja : jb;
-    const bool beside = fuse && !oe_k && !a_given && !b_given && topk_beside_quant(dim, free_job);
+    const bool beside = oe && !oe_k && !use_given_idx && !a_given && !b_given && topk_beside_quant(dim, free_job);
     if (beside) {
         const topk_job_t topk = {scores, (int)dim, k, idx_inout, mask, pos1};
         rc = launch_foid_scores(*masked_job.x, 0, scores, st);

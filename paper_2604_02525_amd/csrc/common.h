@@ -120,6 +120,8 @@ int launch_gather_k(const adahop_operand_t &x, const int32_t *idx, int k, int kp
 // C is float[M, ldc], or bf16[M, ldc] when c_bf16 is set (here and in launch_oe_rowcol).
 // Row / column outlier product; workspace of oe_rowcol_workspace_bytes() bytes, 256-byte aligned.
 size_t oe_rowcol_workspace_bytes(int64_t M, int64_t N, int64_t K, int kind, int k);
+// Offset in it of the partial sums, and their size: free until launch_oe_rowcol.
+size_t oe_rowcol_partials_at(int64_t M, int64_t N, int64_t K, int kind, int k, size_t *bytes);
 // gathered: the extracted rows lie at the start of the workspace already, [k, K] (a quantiser has copied them out).
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
                      void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered = false);

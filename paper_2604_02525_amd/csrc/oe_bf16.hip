@@ -547,6 +547,13 @@ size_t oe_rowcol_workspace_bytes(int64_t M, int64_t N, int64_t K, int kind, int 
     return p.sg_bytes + p.p_bytes;
 }
 
+size_t oe_rowcol_partials_at(int64_t M, int64_t N, int64_t K, int kind, int k, size_t *bytes)
+{
+    const skinny_plan_t p = plan_skinny(kind == ADAHOP_IHT_OE_ROW ? N : M, K, k);
+    *bytes = p.p_bytes;
+    return p.sg_bytes;
+}
+
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
                      void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered)
 {

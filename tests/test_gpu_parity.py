@@ -649,3 +649,22 @@ def test_selection_beside_a_quantiser(ah, dim, k, strategy, ties):
     for name, b, zo in (("a" if row else "b", bits, host(want_mask)), ("b" if row else "a", free, None)):
         rc, rs = orc.iht_quantize(b, True, 32, zo, None)
         assert np.array_equal(host(out[name + "_scales"]), rs) and np.array_equal(host(out[name + "_codes"]), rc), name
+
+
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+@pytest.mark.parametrize("dim,other,k", [(40, 200, 3), (8192, 256, 82), (8192, 40, 82), (8193, 264, 20), (8200, 40, 9)])
+def test_scores_left_in_the_workspace(ah, strategy, dim, other, k):
+    """Row and column extraction leave the scores of all rows in the workspace, as the header says: selected beside the other
+    operand's quantiser and not, with and without room for the table of positions beside the partial sums of the outlier product."""
+    K = 96
+    x = ah.Operand.from_bits(inputs.matrix(dim, K, 1.0, 9400, row_outliers=(3, 60.0, 60.0)), True)
+    y = ah.Operand.from_bits(inputs.matrix(other, K, 0.02, 9401), True)
+    say("scores in the workspace", inputs.STRATEGY_NAMES[strategy], dim, other, k)
+    out = ah.adahop_gemm(*((x, y) if strategy == inputs.IHT_OE_ROW else (y, x)), strategy, 32, k)
+    idx, mask, scores = ah.adahop_foid_topk(x, 0, k)
+    again = ah.adahop_gemm(*((x, y) if strategy == inputs.IHT_OE_ROW else (y, x)), strategy, 32, k, idx=idx.clone())
+    torch.cuda.synchronize()
+    at = out["layout"].scores
+    assert torch.equal(out["workspace"][at:at + 4 * dim].view(torch.int32), scores.view(torch.int32))
+    assert torch.equal(out["idx"], idx) and torch.equal(out["mask"], mask)
+    assert torch.equal(out["C"].view(torch.int32), again["C"].view(torch.int32))
