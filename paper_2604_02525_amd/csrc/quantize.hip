@@ -72,7 +72,7 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, sr_key_
 //
 // Code plus fraction as one number is f(a) = idx + frac = min(2 a, a + 2, a / 2 + 4, 7), the magnitudes' steps of 1/2, 1, 2 being
 // a concave line, and "up iff r / 65536 < frac" is code = ceil(f(a) - r / 65536) = floor((F - r + 65535) / 65536) with
-// F = ceil(65536 f(a)).  With G = ceil(2^17 a) a whole number below 2^20, the four lines in G are exact in fp32 (a quarter is
+// F = ceil(65536 f(a)).  With G = ceil(2^17 a) a whole number of at most 2^20, the four lines in G are exact in fp32 (a quarter is
 // the finest fraction; + 65535.75 rounds up to whole numbers under the truncating conversion), so every decision is the
 // one that real arithmetic makes.  Nine instructions per element in place of about 25 (six compares, a selected
 // step and draw); with the generator's products taken whole, 8192 x 11008 takes 155 -> 82 us (46 rounded to nearest even),
@@ -81,7 +81,8 @@ __device__ __forceinline__ uint32_t e2m1_bits16_sr(float v, float inv, uint32_t 
 {
     const float G = __builtin_ceilf(fabsf(v) * inv * 0x1p17f);
     const float f1 = G + 65535.75f, f2 = __builtin_fmaf(G, 0.5f, 131072.0f + 65535.75f), f3 = __builtin_fmaf(G, 0.25f, 262144.0f + 65535.75f);
-    const float F = fminf(fminf(fminf(f1, f2), f3), 458752.0f + 65535.75f);
+    // (the median of three in place of a fourth minimum: an element that is no number gets code 0, for the same instructions)
+    const float F = __builtin_amdgcn_fmed3f(fminf(fminf(f1, f2), f3), 65535.75f, 458752.0f + 65535.75f);
     return insert_bits(0x80000u, __float_as_uint(v) >> 12, (uint32_t)F - r);
 }
 

@@ -55,6 +55,27 @@ def test_sr_quantiser_at_the_edges_of_the_range(ah, k_contig):
     assert np.array_equal(host(codes), rc)
 
 
+@pytest.mark.parametrize("seed", [None, 78])
+@pytest.mark.parametrize("K", [256, 288])
+@pytest.mark.parametrize("k_contig", [True, False])
+def test_elements_that_are_no_number(ah, k_contig, K, seed):
+    """No transform: such an element does not count for its block's scale; rounded to nearest it takes the largest magnitude, rounded
+    stochastically code 0, with its sign, as the oracle's comparisons have it.  Quiet ones, as arithmetic makes them: a signalling
+    one (0x7f81) comes out of the hardware's maximum as a quiet one and does count, in every kernel."""
+    rng = np.random.default_rng(6)
+    bits = inputs.matrix(72, K, 1.0, 720)
+    at = rng.random(bits.shape) < 0.02
+    bits[at] = rng.choice(np.array([0x7fc0, 0xffc0, 0x7fe1, 0xffff], dtype=np.uint16), size=int(at.sum()))
+    bits[3, :32] = 0xffc0
+    stored = bits if k_contig else np.ascontiguousarray(bits.T)
+    say("elements that are no number", "K-contiguous" if k_contig else "K-strided", K, seed)
+    codes, scales = ah.adahop_iht_quantize(ah.Operand(torch.from_numpy(stored.view(np.int16)).cuda(), k_contig), 0, sr_seed=seed)
+    torch.cuda.synchronize()
+    rc, rs = orc.iht_quantize(stored, k_contig, 0, sr_seed=seed)
+    assert np.array_equal(host(scales), rs)
+    assert np.array_equal(host(codes), rc)
+
+
 @pytest.mark.parametrize("k_contig", [True, False])
 @pytest.mark.parametrize("b,outer,K", [(0, 70, 96), (32, 130, 160), (64, 67, 448), (128, 200, 512), (256, 131, 1024),
                                        (32, 300, 2048), (0, 9, 256)])
