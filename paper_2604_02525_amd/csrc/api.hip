@@ -407,11 +407,12 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // a row or channel in the index list comes from a 16-bit table that the selection leaves beside the mask.  Only for indices selected
     // here, which are distinct: a repeated index in a caller's list would leave a position of the copy unwritten, where the separate
     // gather reads the row twice.
-    // The table of K-channels takes the place of the scores.  That of rows and columns lies where the bf16 product keeps its partial sums,
+    // The table of K-channels takes the place of the scores; above the selection's own limit it costs a launch, less than the separate
+    // gather of a K-contiguous operand (4096 x 4096 x 65536, 655 channels: the whole call 4 % faster).  That of rows and columns lies where the bf16 product keeps its partial sums,
     // which nobody writes before the quantisers are done: a caller finds the scores in the workspace afterwards.  Where it does not fit
     // there (more than 128 rows to choose from for each of the other operand's), the rows are gathered by themselves.
     uint16_t *pos1 = nullptr;
-    if (oe && !use_given_idx && foid_writes_positions(dim, k)) {
+    if (oe && !use_given_idx && k <= 0xffff && (oe_k || foid_writes_positions(dim))) {
         size_t room = (size_t)dim * sizeof(float);
         pos1 = oe_k ? reinterpret_cast<uint16_t *>(scores)
                     : reinterpret_cast<uint16_t *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &room));

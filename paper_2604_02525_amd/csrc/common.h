@@ -83,9 +83,9 @@ struct topk_job_t {
 };
 bool topk_beside_quant(int64_t dim, const quant_job_t &job);
 int launch_topk_beside_quant(const topk_job_t &topk, int iht_block, const quant_job_t &job, hipStream_t st);
-// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere; it may lie where scores lies.  Only where
-// foid_writes_positions holds.
-bool foid_writes_positions(int64_t dim, int k);
+// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere, for k <= 0xffff; it may lie where scores lies.  The selection
+// writes it on the way where foid_writes_positions holds, else a launch after it does.
+bool foid_writes_positions(int64_t dim);
 int launch_foid_scores(const adahop_operand_t &x, int axis, float *scores, hipStream_t st);
 int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, uint8_t *mask, float *scores,
                      hipStream_t st, uint16_t *pos1 = nullptr);

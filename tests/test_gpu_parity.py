@@ -668,3 +668,22 @@ def test_scores_left_in_the_workspace(ah, strategy, dim, other, k):
     assert torch.equal(out["workspace"][at:at + 4 * dim].view(torch.int32), scores.view(torch.int32))
     assert torch.equal(out["idx"], idx) and torch.equal(out["mask"], mask)
     assert torch.equal(out["C"].view(torch.int32), again["C"].view(torch.int32))
+
+
+def test_k_channels_copied_by_the_quantisers_of_many_channels(ah):
+    """More K-channels than the selection that writes the table of their positions takes: the copies are those of the separate gather
+    (indices handed in), K-contiguous beside K-contiguous and beside K-strided."""
+    M, N, K, k = 70, 40, 33024, 330
+    A = inputs.matrix(M, K, 1.0, 9500, col_outliers=(9, 30.0, 30.0))
+    B = inputs.matrix(N, K, 0.02, 9501)
+    say("K-channels copied by the quantisers", M, N, K, k)
+    opa = ah.Operand.from_bits(A, True)
+    for opb in (ah.Operand.from_bits(B, True), ah.Operand.from_bits(np.ascontiguousarray(B.T), False)):
+        out = ah.adahop_gemm(opa, opb, inputs.IHT_OE_K, 128, k)
+        got = {n: out[n].clone() for n in ("C", "idx", "a_codes", "a_scales", "b_codes", "b_scales")}
+        want_idx, _, _ = ah.adahop_foid_topk(opa, 1, k)
+        again = ah.adahop_gemm(opa, opb, inputs.IHT_OE_K, 128, k, idx=got["idx"].clone())
+        torch.cuda.synchronize()
+        assert torch.equal(got["idx"], want_idx)
+        for name, t in got.items():
+            assert torch.equal(t, again[name]), name
