@@ -389,13 +389,29 @@ template <int NBFC> __device__ __forceinline__ void run_tile(tile_state_t &t, co
 
 // The accumulators of a finished tile -> C.  The two stage buffers may already hold the next tile, so the
 // bf16 path, which has to transpose through LDS, uses a small patch private to the wave beyond them; LDS
-// operations of one wave execute in order, so the patch needs no barrier.  VEC (bf16): the host side found a 16-byte
-// aligned C, ldc % 8 == 0 and N % 8 == 0; any other C is stored element by element as fp32 is, 64-byte row segments
-// (8752 x 4025 x 4096: 536 us by a kernel without LDS, now 145, with aligned rows 94).
+// operations of one wave execute in order, so the patch needs no barrier.
+//
+// How the stores go, by the alignment of the rows of C (host side: launch_gemm_mx_t):
+//   STREAMED  rows begin at multiples of 64 bytes: non-temporal stores, every one of which fills 64-byte pieces of cache lines;
+//   CACHED    any other: plain stores.  The pieces of a line then come from two or more stores, which the L2 puts together
+//             before the line leaves; streamed, each of them goes to memory by itself (fp32, 3297 x 11770 x 576 131 -> 60 us, 8752 x
+//             4025 x 4096 162 -> 106, at rows of 32-byte alignment 136 -> 104; rows of 64 or 128 bytes: within 10 % either way, K = 8192 2 %
+//             for streaming);
+//   ELEMENTS  bf16 with rows of less than 16-byte alignment (C, ldc % 8 or N % 8): plain stores, element by element as fp32 is,
+//             64-byte row segments (8752 x 4025 x 4096 by a kernel without LDS 536 us).
+enum store_t { STREAMED, CACHED, ELEMENTS };
+template <store_t ST, typename V> __device__ __forceinline__ void store_as(V v, V *p)
+{
+    if constexpr (ST == STREAMED)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 constexpr int PATCH_BYTES = 5120;                                  // per wave
 constexpr int KERNEL_LDS_BYTES = TILED_LDS_BYTES + 4 * PATCH_BYTES; // 159744 of the 163840 of a compute unit
 
-template <typename OUT, bool VEC>
+template <typename OUT, store_t ST>
 __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *__restrict__ C, int64_t ldc, int64_t m0,
                                            int64_t n0, int w, int lane)
 {
@@ -410,9 +426,8 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    __builtin_nontemporal_store(t.acc[i][j][r],
-                                                &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
-    } else if constexpr (!VEC) {
+                    store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+    } else if constexpr (ST == ELEMENTS) {
         OUT *crow = C + (m0 + wm * 128 + h * 4) * ldc + n0 + wn * 128 + l32;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -420,8 +435,8 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    __builtin_nontemporal_store(__builtin_bit_cast(uint16_t, (__bf16)t.acc[i][j][r]),
-                                                &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+                    store_as<ST>(__builtin_bit_cast(uint16_t, (__bf16)t.acc[i][j][r]),
+                                 &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
     } else {
         // bf16: a lane converts two consecutive accumulator rows into one packed pair, trades pairs with its
         // neighbour and keeps, as one dword, two adjacent columns of one row (even lane: the low halves =
@@ -456,8 +471,7 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
                 for (int q = 0; q < 4; ++q) {
                     const int prow = q * 8 + (lane >> 3);
                     const u32x4 v = *reinterpret_cast<const u32x4 *>(patch + prow * BP + (lane & 7) * 16);
-                    __builtin_nontemporal_store(
-                        v, reinterpret_cast<u32x4 *>(cbase + (int64_t)(i * 32 + prow) * ldc + jp * 64 + (lane & 7) * 8));
+                    store_as<ST>(v, reinterpret_cast<u32x4 *>(cbase + (int64_t)(i * 32 + prow) * ldc + jp * 64 + (lane & 7) * 8));
                 }
             }
     }
@@ -470,7 +484,7 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
 // Host side guarantees K > 256 (two FP4 stages), so that every bf16 stage has two successors and the
 // last two stages of a tile are FP4 stages, and at least three stages per tile (K > 512 when there are
 // no bf16 stages).
-template <bool OEK, typename OUT, bool VEC>
+template <bool OEK, typename OUT, store_t ST>
 __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_t *__restrict__ a_codes,
                                                          const uint8_t *__restrict__ a_scales_sm,
                                                          const uint8_t *__restrict__ b_codes,
@@ -597,7 +611,7 @@ __global__ __launch_bounds__(256) void k_gemm_mx_tile256(int64_t K, const uint8_
             tile_origin(more ? vn : v, m0n, n0n);
             t.nxt = tile_source(m0n, n0n);
             run_tile<decltype(nbfc)::value>(t, smem, f);
-            store_tile<OUT, VEC>(t, smem, C, ldc, m0, n0, w, lane);
+            store_tile<OUT, ST>(t, smem, C, ldc, m0, n0, w, lane);
             if (!more) break;
             v = vn;
             m0 = m0n;
@@ -706,12 +720,16 @@ int configure_gemm_mx(int *ncu_out)
     if (once.need(dev) || ncu == 0) {
         rc = check_hip(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
         if (rc != ADAHOP_OK) return rc;
-        const void *kernels[6] = {reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, float, true>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, float, true>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, true>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, true>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, false>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, false>)};
+        const void *kernels[10] = {reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, float, STREAMED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, float, STREAMED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, float, CACHED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, float, CACHED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, STREAMED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, STREAMED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, CACHED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, CACHED>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<false, uint16_t, ELEMENTS>),
+                                   reinterpret_cast<const void *>(&k_gemm_mx_tile256<true, uint16_t, ELEMENTS>)};
         for (const void *f : kernels) {
             rc = check_hip(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, KERNEL_LDS_BYTES));
             if (rc != ADAHOP_OK) return rc;
@@ -799,18 +817,24 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
         const bool ok = !(forced & 1) || (grid.x == 256 && (fb ? tiles_n : tiles_m) % 8 == 0 && (fb ? tiles_m : tiles_n) % 32 == 0);
         order = ok ? forced : (forced & 2);
     }
-    auto launch = [&](auto oek, auto vec) {
-        hipLaunchKernelGGL((k_gemm_mx_tile256<decltype(oek)::value, OUT, decltype(vec)::value>), grid, dim3(256), KERNEL_LDS_BYTES,
+    auto launch = [&](auto oek, auto kind) {
+        hipLaunchKernelGGL((k_gemm_mx_tile256<decltype(oek)::value, OUT, decltype(kind)::value>), grid, dim3(256), KERNEL_LDS_BYTES,
                            st, K, a_codes, a_sm, b_codes, b_sm, M, N, C, ldc, Ag, Bg, kpad, tiles_m, tiles_n, group_m, order);
     };
-    auto launch_vec = [&](auto vec) { kpad > 0 ? launch(std::true_type(), vec) : launch(std::false_type(), vec); };
+    auto launch_kind = [&](auto kind) { kpad > 0 ? launch(std::true_type(), kind) : launch(std::false_type(), kind); };
+    const bool streamed = c_rows_streamed(C, ldc * (int64_t)sizeof(OUT));
     if constexpr (sizeof(OUT) == 2) {
         if (!(aligned(C, 16) && ldc % 8 == 0 && N % 8 == 0))
-            launch_vec(std::false_type());
+            launch_kind(std::integral_constant<store_t, ELEMENTS>());
+        else if (streamed)
+            launch_kind(std::integral_constant<store_t, STREAMED>());
         else
-            launch_vec(std::true_type());
+            launch_kind(std::integral_constant<store_t, CACHED>());
     } else {
-        launch_vec(std::true_type());
+        if (streamed)
+            launch_kind(std::integral_constant<store_t, STREAMED>());
+        else
+            launch_kind(std::integral_constant<store_t, CACHED>());
     }
     return check_launch();
 }

@@ -146,10 +146,20 @@ __device__ __forceinline__ void read_scales(const uint8_t *buf, const state_t &t
 
 // Store r of accumulator tile ST (tile row ST / 2, column ST % 2) of set SET; cprev is the lane's pointer to
 // C[tile row 4 * (lane / 32)][lane % 32] of the wave's 128 x 64 part of that tile.
-template <int SET, int ST> __device__ __forceinline__ void store_one(const state_t &t, float *cprev, int64_t ldc, int r)
+// STREAM: rows of C begin at multiples of 64 bytes and leave by non-temporal stores, else by plain ones (see store_tile of the 256 x 256
+// kernel; 8752 x 4025 x 4096 121 -> 92 us, 8192 x 8192 x 2048 with ldc = 8193 210 -> 104).
+template <bool STREAM> __device__ __forceinline__ void put_c(float v, float *p)
+{
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
+template <bool STREAM, int SET, int ST> __device__ __forceinline__ void store_one(const state_t &t, float *cprev, int64_t ldc, int r)
 {
     constexpr int i = ST >> 1, j = ST & 1;
-    __builtin_nontemporal_store(t.acc[SET][i][j][r], &cprev[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+    put_c<STREAM>(t.acc[SET][i][j][r], &cprev[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
 }
 
 // One matrix-core step (8 instructions on fragments f, step S of the stage, into set SET) and, one after each
@@ -159,7 +169,7 @@ template <int SET, int ST> __device__ __forceinline__ void store_one(const state
 // shadow of the matrix-core instruction before them, bursts would hold the matrix core up.  Written as a
 // compile-time recursion over the instruction index Q (no loop: the order written is the order that runs).
 // BF: the stage holds gathered bf16 K-channels.
-template <bool BF, int SET, int S, bool ZC, int RS, bool RSC, int C0, int C1, int ST, int R0, int R1, int Q = 0>
+template <bool STREAM, bool BF, int SET, int S, bool ZC, int RS, bool RSC, int C0, int C1, int ST, int R0, int R1, int Q = 0>
 __device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t *rbuf, frags_t &rf, float *cprev,
                                      int64_t ldc)
 {
@@ -192,17 +202,17 @@ __device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t
             }
         }
         if constexpr (ST >= 0 && R0 + Q < R1 && Q < 6) {
-            store_one<1 - SET, ST>(t, cprev, ldc, R0 + Q);
+            store_one<STREAM, 1 - SET, ST>(t, cprev, ldc, R0 + Q);
             ADAHOP_PIN();
         }
-        step<BF, SET, S, ZC, RS, RSC, C0, C1, ST, R0, R1, Q + 1>(f, t, rbuf, rf, cprev, ldc);
+        step<STREAM, BF, SET, S, ZC, RS, RSC, C0, C1, ST, R0, R1, Q + 1>(f, t, rbuf, rf, cprev, ldc);
     }
 }
 
 // One pipeline stage: four matrix-core steps on the fragments of the LDS buffer at byte offset rb (advanced to
 // the next buffer on return).  ST: the accumulator tile of the previous tile's set stored during this stage
 // (-1: none).  ZC: first stage of a tile (its first step starts the accumulators from 0).
-template <int NBF, bool BF, int SET, int ST, bool ZC>
+template <int NBF, bool STREAM, bool BF, int SET, int ST, bool ZC>
 __device__ __forceinline__ void run_stage(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
 {
     const uint8_t *st = smem + rb;
@@ -210,46 +220,47 @@ __device__ __forceinline__ void run_stage(state_t &t, const uint8_t *smem, uint3
     const uint8_t *sn = smem + rn;
     // the copies of a stage: PART1 during the last step of the stage two before it (after that stage's barrier),
     // the rest during the first three steps of the stage before it
-    step<BF, SET, 0, ZC, 1, false, PART1, PART1 + 3, ST, 0, 6>(t.f0, t, st, t.f1, cprev, ldc);
-    step<BF, SET, 1, false, 2, false, PART1 + 3, PART1 + 6, ST, 6, 11>(t.f1, t, st, t.f0, cprev, ldc);
-    step<BF, SET, 2, false, 3, false, PART1 + 6, NCOPY, ST, 11, 16>(t.f0, t, st, t.f1, cprev, ldc);
+    step<STREAM, BF, SET, 0, ZC, 1, false, PART1, PART1 + 3, ST, 0, 6>(t.f0, t, st, t.f1, cprev, ldc);
+    step<STREAM, BF, SET, 1, false, 2, false, PART1 + 3, PART1 + 6, ST, 6, 11>(t.f1, t, st, t.f0, cprev, ldc);
+    step<STREAM, BF, SET, 2, false, 3, false, PART1 + 6, NCOPY, ST, 11, 16>(t.f0, t, st, t.f1, cprev, ldc);
     advance<NBF>(t);
     // Younger than the last copy of the next stage: the NCOPY copies of the stage after it and this stage's stores.
     constexpr int X = NCOPY + (ST >= 0 ? STORES_PER_STAGE : 0);
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(X) : "memory");
-    step<BF, SET, 3, false, 0, true, 0, PART1, -1, 0, 0>(t.f1, t, sn, t.f0, cprev, ldc);
+    step<STREAM, BF, SET, 3, false, 0, true, 0, PART1, -1, 0, 0>(t.f1, t, sn, t.f0, cprev, ldc);
     t.sc = t.scn;
     rb = rn;
 }
 
-template <int NBF, int SET, int ST> __device__ __forceinline__ void store_stages(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
+template <int NBF, bool STREAM, int SET, int ST>
+__device__ __forceinline__ void store_stages(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
 {
     if constexpr (ST < STORE_STAGES) {
-        run_stage<NBF, (ST < NBF), SET, ST, ST == 0>(t, smem, rb, cprev, ldc);
-        store_stages<NBF, SET, ST + 1>(t, smem, rb, cprev, ldc);
+        run_stage<NBF, STREAM, (ST < NBF), SET, ST, ST == 0>(t, smem, rb, cprev, ldc);
+        store_stages<NBF, STREAM, SET, ST + 1>(t, smem, rb, cprev, ldc);
     }
 }
 
 // All stages of one tile into set SET; STORES: the other set holds a finished tile, whose stores go along.
-template <int NBF, int SET, bool STORES>
+template <int NBF, bool STREAM, int SET, bool STORES>
 __device__ __forceinline__ void run_tile(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
 {
     int l;
     if constexpr (STORES) {
-        store_stages<NBF, SET, 0>(t, smem, rb, cprev, ldc);
+        store_stages<NBF, STREAM, SET, 0>(t, smem, rb, cprev, ldc);
         l = STORE_STAGES;
     } else {
-        run_stage<NBF, (NBF > 0), SET, -1, true>(t, smem, rb, cprev, ldc);
+        run_stage<NBF, STREAM, (NBF > 0), SET, -1, true>(t, smem, rb, cprev, ldc);
         l = 1;
         if constexpr (NBF == 2) {
-            run_stage<NBF, true, SET, -1, false>(t, smem, rb, cprev, ldc);
+            run_stage<NBF, STREAM, true, SET, -1, false>(t, smem, rb, cprev, ldc);
             l = 2;
         }
     }
-    for (; l < t.n; ++l) run_stage<NBF, false, SET, -1, false>(t, smem, rb, cprev, ldc);
+    for (; l < t.n; ++l) run_stage<NBF, STREAM, false, SET, -1, false>(t, smem, rb, cprev, ldc);
 }
 
-template <int SET> __device__ __forceinline__ void store_all(const state_t &t, float *c, int64_t ldc)
+template <bool STREAM, int SET> __device__ __forceinline__ void store_all(const state_t &t, float *c, int64_t ldc)
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -257,7 +268,7 @@ template <int SET> __device__ __forceinline__ void store_all(const state_t &t, f
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                __builtin_nontemporal_store(t.acc[SET][i][j][r], &c[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+                put_c<STREAM>(t.acc[SET][i][j][r], &c[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
 }
 
 } // namespace dual
@@ -267,7 +278,7 @@ template <int SET> __device__ __forceinline__ void store_all(const state_t &t, f
 // its neighbour, and so does the last stage of a ragged K (see the 256 x 256 kernel).
 // NBF: stages of gathered bf16 K-channels in front of the FP4 stages of a tile (kpad = 64 NBF; 0, 1 or 2: they lie among the
 // stages that carry the stores of the tile before, each of them an instance of the stage's code).
-template <int NBF>
+template <int NBF, bool STREAM>
 __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *__restrict__ a_codes,
                                                       const uint8_t *__restrict__ a_scales_sm,
                                                       const uint8_t *__restrict__ b_codes,
@@ -401,24 +412,24 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
     read_scales(smem, t, t.sc);
 
     float *cprev = c_of(m0, n0);
-    run_tile<NBF, 0, false>(t, smem, rb, cprev, ldc);
+    run_tile<NBF, STREAM, 0, false>(t, smem, rb, cprev, ldc);
     for (;;) {
         cprev = c_of(m0, n0); // the tile just finished, in set 0
         if (!more) {
-            store_all<0>(t, cprev, ldc);
+            store_all<STREAM, 0>(t, cprev, ldc);
             break;
         }
         v += grid, m0 = m0n, n0 = n0n;
         look_ahead(more, m0n, n0n);
-        run_tile<NBF, 1, true>(t, smem, rb, cprev, ldc);
+        run_tile<NBF, STREAM, 1, true>(t, smem, rb, cprev, ldc);
         cprev = c_of(m0, n0); // in set 1
         if (!more) {
-            store_all<1>(t, cprev, ldc);
+            store_all<STREAM, 1>(t, cprev, ldc);
             break;
         }
         v += grid, m0 = m0n, n0 = n0n;
         look_ahead(more, m0n, n0n);
-        run_tile<NBF, 0, true>(t, smem, rb, cprev, ldc);
+        run_tile<NBF, STREAM, 0, true>(t, smem, rb, cprev, ldc);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the copies begun for a tile that does not follow
 }
@@ -442,8 +453,9 @@ int configure_gemm_mx_dual(int *ncu_out)
     if (once.need(dev) || ncu == 0) {
         rc = check_hip(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
         if (rc != ADAHOP_OK) return rc;
-        const void *kernels[3] = {reinterpret_cast<const void *>(&k_gemm_mx_dual<0>), reinterpret_cast<const void *>(&k_gemm_mx_dual<1>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_dual<2>)};
+        const void *kernels[6] = {reinterpret_cast<const void *>(&k_gemm_mx_dual<0, true>), reinterpret_cast<const void *>(&k_gemm_mx_dual<0, false>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_dual<1, true>), reinterpret_cast<const void *>(&k_gemm_mx_dual<1, false>),
+                                  reinterpret_cast<const void *>(&k_gemm_mx_dual<2, true>), reinterpret_cast<const void *>(&k_gemm_mx_dual<2, false>)};
         for (const void *f : kernels) {
             rc = check_hip(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dual::LDS_BYTES));
             if (rc != ADAHOP_OK) return rc;
@@ -473,7 +485,9 @@ int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                            tiles_m, tiles_n, group_m);
         return check_launch();
     };
-    return kpad == 0 ? launch(&k_gemm_mx_dual<0>) : kpad == 64 ? launch(&k_gemm_mx_dual<1>) : launch(&k_gemm_mx_dual<2>);
+    if (c_rows_streamed(C, ldc * 4))
+        return kpad == 0 ? launch(&k_gemm_mx_dual<0, true>) : kpad == 64 ? launch(&k_gemm_mx_dual<1, true>) : launch(&k_gemm_mx_dual<2, true>);
+    return kpad == 0 ? launch(&k_gemm_mx_dual<0, false>) : kpad == 64 ? launch(&k_gemm_mx_dual<1, false>) : launch(&k_gemm_mx_dual<2, false>);
 }
 
 } // namespace adahop

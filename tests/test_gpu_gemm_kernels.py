@@ -200,6 +200,27 @@ def test_bf16_output_of_any_alignment(ah, force, kernel, M, N, K, k, gap):
     assert bool((room[:, N:] == 7.0).all())
 
 
+@pytest.mark.parametrize("kernel", [TILE256, DUAL])
+@pytest.mark.parametrize("M,N,K,k", [(520, 520, 2048, 0), (300, 264, 2080, 20)])
+def test_rows_of_c_at_any_alignment(ah, force, kernel, M, N, K, k):
+    """Rows of C that are whole 64-byte pieces (streamed) and that begin at 32, 16 and 4 (bf16: 2) bytes, or all of them behind
+    such a first element: the bits of a C without gaps, and the gaps as they were."""
+    A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 92, col_outliers=(5, 50.0, 50.0)), True)
+    B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 93), True)
+    strategy = inputs.IHT_OE_K if k else inputs.IHT
+    force(kernel)
+    for dtype in (torch.float32, torch.bfloat16):
+        want = ah.adahop_gemm(A, B, strategy, 32, k, Cout=torch.empty((M, N), dtype=dtype, device="cuda"))["C"]
+        for ld, first in ((576, 0), (584, 0), (580, 0), (577, 0), (576, 8), (576, 4), (576, 1)):
+            say("rows of C", kernel, (M, N, K, k), dtype, ld, first)
+            room = torch.full((M * ld + first,), 7.0, dtype=dtype, device="cuda")
+            C = room[first:].view(M, ld)
+            ah.adahop_gemm(A, B, strategy, 32, k, Cout=C[:, :N])
+            torch.cuda.synchronize()
+            assert torch.equal(C[:, :N], want), (dtype, ld, first)
+            assert bool((C[:, N:] == 7.0).all()) and bool((room[:first] == 7.0).all())
+
+
 @pytest.mark.parametrize("M,N,K,k", [(256, 128, 2048, 8), (520, 264, 2080, 100), (1000, 650, 2304, 128), (4352, 4100, 2048, 70)])
 def test_two_set_kernel_with_k_channels(ah, force, M, N, K, k):
     """One and two gathered bf16 stages in front of eight and more FP4 stages, one tile and several (both accumulator sets)
