@@ -107,10 +107,11 @@ bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K, int kpad);
 int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
                         const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg,
                         int kpad, hipStream_t st);
-// Whether the kernels with tiles of 256 rows stream C past the caches: rows of whole 64-byte pieces (see store_tile in gemm_mx.hip).
+// Rows of C of whole 64-byte pieces: the kernels with tiles of 256 rows then stream C past the caches (see store_tile in gemm_mx.hip).
 inline bool c_rows_streamed(const void *C, int64_t row_bytes) { return aligned(C, 64) && row_bytes % 64 == 0; }
 // Any shape, tiles of 32 .. 128 (gemm_mx_small.hip).  a_sm / b_sm: the scales are the stage-major copy, else the canonical
-// array (only for K % 256 == 0 and 4-byte aligned).
+// array (only for K % 256 == 0 and 4-byte aligned, or where gemm_mx_small_takes_canonical holds).
+bool gemm_mx_small_takes_canonical(int64_t K);
 int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,
                          const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
                          const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);

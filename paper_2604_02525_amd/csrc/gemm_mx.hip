@@ -121,16 +121,24 @@ constexpr int TILED_LDS_BYTES = NSTAGE * STAGE_BYTES;
 // out[s][row][0..7] = in[row][8s .. 8s+7]; of a last stage with t < 8 blocks the last t bytes, behind zeros (see above).
 // A workgroup turns 32 rows x 32 stages in LDS: reads are 256-byte pieces of rows, writes 256-byte runs of rows.  (One thread per row
 // and stage, eight bytes at a time down the rows, took 12 us for the 11008 rows of K = 6016, now 5.)
-// WORDS: KB % 4 == 0 and the scales 4-byte aligned, so that a row is whole words.
+// Both operands of a product in one launch: the first a_blocks workgroups in x take a, the others b.
+struct stage_major_t {
+    const uint8_t *in;
+    uint64_t *out;
+    int64_t rows;
+    int words; // KB % 4 == 0 and the scales 4-byte aligned, so that a row is whole words
+};
 constexpr int SMS_ROWS = 32, SMS_STAGES = 32 /* 256 bytes of a row */, SMS_PITCH = SMS_STAGES * 8 + 4;
-template <bool WORDS>
-__global__ __launch_bounds__(256) void k_stage_major_scales(const uint8_t *__restrict__ in, uint64_t *__restrict__ out,
-                                                            int64_t rows, int64_t KB)
+__global__ __launch_bounds__(256) void k_stage_major_scales(stage_major_t a, stage_major_t b, uint32_t a_blocks, int64_t KB)
 {
     __shared__ __attribute__((aligned(4))) uint8_t tile[SMS_ROWS * SMS_PITCH];
-    const int64_t r0 = (int64_t)blockIdx.x * SMS_ROWS, s0 = (int64_t)blockIdx.y * SMS_STAGES, stages = (KB + 7) >> 3;
+    const bool is_a = blockIdx.x < a_blocks;
+    const uint8_t *__restrict__ in = is_a ? a.in : b.in;
+    uint64_t *__restrict__ out = is_a ? a.out : b.out;
+    const int64_t rows = is_a ? a.rows : b.rows;
+    const int64_t r0 = (int64_t)(is_a ? blockIdx.x : blockIdx.x - a_blocks) * SMS_ROWS, s0 = (int64_t)blockIdx.y * SMS_STAGES, stages = (KB + 7) >> 3;
     // (all loads of a thread in flight together)
-    if constexpr (WORDS) { // 64 words of a row, four rows per pass
+    if (is_a ? a.words : b.words) { // 64 words of a row, four rows per pass
         constexpr int PASSES = SMS_ROWS / 4;
         const int d = threadIdx.x & 63, r = threadIdx.x >> 6;
         uint32_t v[PASSES];
@@ -673,7 +681,10 @@ static bool takes_dual_kernel(int64_t M, int64_t N, int64_t K, int kpad)
 // Which kernel takes a product: one of the two with tiles of 256 rows (LARGE; they need at least three pipeline stages of
 // 64 gathered channels or 256 K-elements each, two of them FP4 stages) or a variant of the one with small tiles (gemm_mx_small.hip).
 // Both sides' times are estimated from the rounds of tiles on the 256 compute units: a round of 256 x 256 (256 x 128) tiles takes
-// 6.2 + 1.21 (5.3 + 0.66) us per stage of K, as fitted to the products that gemm_mx_small.hip names.  The line lies where less
+// 6.2 + 1.21 (5.3 + 0.66) us per stage of K, as fitted to the products that gemm_mx_small.hip names, and the large tiles have to
+// be ahead by 1.25 us: over 358 products on both sides of the line (M 256 .. 16000, N 130 .. 16000, K 544 .. 8192) the choice is then within 0.3 %
+// of the faster side in the mean and 11 % at worst; without that lead 0.9 and 26 % (536 x 7180 x 768, large 17.9, small 14.2 us), with
+// 2 us 0.3 and 21 %.  The line lies where less
 // than about half of the chip gets a tile, or the last round is short: measured, large against small tiles, 256 x 4096 x 4096 13.4
 // / 8.2 us, 1000 x 11008 x 4096 31 / 37 us, 594 x 4096 x 28672 71 / 57 us, 2016 x 20000 x 4096 78 / 137 us.
 // The output type has no part in it: a product has the same sums, bit for bit, whichever type they are rounded to.
@@ -696,7 +707,7 @@ static kernel_choice_t choose_kernel(int64_t M, int64_t N, int64_t K, int kpad)
     } else if (can) {
         const double rounds = (double)ceil_div(ceil_div(M, TM) * ceil_div(N, dual ? 128 : TN), 256);
         const double us_large = rounds * (dual ? 5.3 + 0.66 * (double)stages : 6.2 + 1.21 * (double)stages);
-        c.large = forced == 1 || forced == 2 || us_large <= us_small;
+        c.large = forced == 1 || forced == 2 || us_large + 1.25 <= us_small;
     }
     return c;
 }
@@ -762,19 +773,20 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
     // re-ordering them takes a launch, 3 us.
     uint8_t *a_sm = gemm_mx_scales_sm(workspace, M, K, 0), *b_sm = gemm_mx_scales_sm(workspace, M, K, 1);
     const int64_t KB = K / 32;
-    auto reorder = [&](const uint8_t *in, uint8_t *out, int64_t rows) {
-        const dim3 g((unsigned)ceil_div(rows, SMS_ROWS), (unsigned)ceil_div(KB, 8 * SMS_STAGES));
-        if (KB % 4 == 0 && aligned(in, 4))
-            hipLaunchKernelGGL(k_stage_major_scales<true>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
-        else
-            hipLaunchKernelGGL(k_stage_major_scales<false>, g, dim3(256), 0, st, in, reinterpret_cast<uint64_t *>(out), rows, KB);
-    };
-    const bool canonical_ok = !c.large && KB % 8 == 0 && KB <= 8 * 24;
-    const bool a_canonical = !(sm_ready & 1) && canonical_ok && aligned(a_scales, 4);
-    const bool b_canonical = !(sm_ready & 2) && canonical_ok && aligned(b_scales, 4);
-    if (!(sm_ready & 1) && !a_canonical) reorder(a_scales, a_sm, M);
-    if (!(sm_ready & 2) && !b_canonical) reorder(b_scales, b_sm, N);
-    int rc = check_launch();
+    const bool canonical_ok = !c.large && KB % 8 == 0 && KB <= 8 * 24, any_ok = !c.large && gemm_mx_small_takes_canonical(K);
+    const bool a_canonical = !(sm_ready & 1) && (any_ok || (canonical_ok && aligned(a_scales, 4)));
+    const bool b_canonical = !(sm_ready & 2) && (any_ok || (canonical_ok && aligned(b_scales, 4)));
+    const bool a_turned = !(sm_ready & 1) && !a_canonical, b_turned = !(sm_ready & 2) && !b_canonical;
+    int rc = ADAHOP_OK;
+    if (a_turned || b_turned) {
+        auto job = [&](const uint8_t *in, uint8_t *out, int64_t rows) {
+            return stage_major_t{in, reinterpret_cast<uint64_t *>(out), rows, KB % 4 == 0 && aligned(in, 4)};
+        };
+        const uint32_t na = a_turned ? (uint32_t)ceil_div(M, SMS_ROWS) : 0u, nb = b_turned ? (uint32_t)ceil_div(N, SMS_ROWS) : 0u;
+        hipLaunchKernelGGL(k_stage_major_scales, dim3(na + nb, (unsigned)ceil_div(KB, 8 * SMS_STAGES)), dim3(256), 0, st,
+                           job(a_scales, a_sm, M), job(b_scales, b_sm, N), na, KB);
+        rc = check_launch();
+    }
     if (rc != ADAHOP_OK) return rc;
     if (!c.large)
         return launch_gemm_mx_small(c.variant, M, N, K, a_codes, a_canonical ? a_scales : a_sm, !a_canonical, b_codes,

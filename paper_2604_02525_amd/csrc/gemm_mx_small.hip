@@ -22,7 +22,8 @@
 //     63 us on 128 x 11008 x 4096 (15) and 78 us on 4096 x 11008 x 512 (50); 256 rows of 4096 x 4096 took 13.4 us in tiles of
 //     256 x 128 (now 7.8);
 //   - the scales come from the stage-major copy or, where K % 256 == 0, straight from the canonical array (8 bytes per row
-//     and stage: two 4-byte copies), which saves a product of packed operands the launch that re-orders them.
+//     and stage: two 4-byte copies), which saves a product of packed operands the launch that re-orders them; up to
+//     PRE_STAGES stages they may be canonical at any K: see there.
 #include "common.h"
 #include "gemm_mx_common.h"
 
@@ -40,7 +41,15 @@ constexpr int TKB = 128; // bytes of K per row and stage
 struct scale_src_t {
     const uint8_t *p;
     int64_t row, stage;
+    uint32_t canonical; // (only for PRE) 0: stage-major, else ceil(2^20 / (K / 32)), which turns bytes of the canonical array into rows
 };
+
+// PRE: the scales of all stages lie in LDS from the start, brought through registers: at a K that is no multiple of 256 the canonical
+// array cannot be copied straight into stages (no piece of it is aligned, and the last stage wants zeros in front).  The
+// K / 32 bytes of a tile's rows are one run of bytes; the threads read them side by side and put each where its stage wants
+// it.  For short products of packed operands, of which the launch that re-orders the scales and its gap would be the larger part:
+// 1 x 16716 x 96 9.7 -> 4.1 us, 665 x 852 x 320 11.3 -> 5.5.  At more stages than PRE_STAGES the bytes to place grow and the launch is the smaller part.
+constexpr int PRE_STAGES = 4;
 
 __device__ __forceinline__ void dma4(const uint8_t *base, uint32_t voff, uint32_t lds_addr)
 { // as dma16, 4 bytes per lane
@@ -73,23 +82,25 @@ __device__ __forceinline__ void put(uint16_t *p, float v)
     *p = __builtin_bit_cast(uint16_t, b);
 }
 
-template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct shape_t {
+template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool PRE> struct shape_t {
     static constexpr int TM = 32 * TMB * WM, TN = 32 * TNB * WN;
-    static constexpr int SLAB = (TM + TN) * TKB, STAGE = SLAB + (TM + TN) * 8;
+    static constexpr int SLAB = (TM + TN) * TKB, SCALES = (TM + TN) * 8; // bytes of a stage
+    static constexpr int STAGE = SLAB + (PRE ? 0 : SCALES);              // bytes of a buffer
     static constexpr int RED = WK > 1 ? 4 * TMB * TNB * 16 * 64 * 4 : 0;
-    static constexpr int LDS = NST * STAGE > RED ? NST * STAGE : RED;
+    static constexpr int ALL = NST * STAGE + (PRE ? PRE_STAGES * SCALES : 0);
+    static constexpr int LDS = ALL > RED ? ALL : RED;
     static constexpr int NC = (TM + TN) / 32;      // 16-byte copies per wave and stage (a copy: 8 rows; 4 waves)
-    static constexpr int NS = ((TM + TN) / 32 + 3) / 4; // 4-byte copies of scales per wave and stage (a copy: 32 rows)
+    static constexpr int NS = PRE ? 0 : ((TM + TN) / 32 + 3) / 4; // 4-byte copies of scales per wave and stage (a copy: 32 rows)
 };
 
-template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool OEK, typename OUT>
+template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool PRE, bool OEK, typename OUT>
 __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8_t *__restrict__ a_codes, scale_src_t a_sc,
                                                           const uint8_t *__restrict__ b_codes, scale_src_t b_sc, int64_t M,
                                                           int64_t N, OUT *__restrict__ C, int64_t ldc,
                                                           const uint16_t *__restrict__ Ag, const uint16_t *__restrict__ Bg,
                                                           int kpad, int tiles_m)
 {
-    typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU> S;
+    typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU, PRE> S;
     constexpr int TM = S::TM, TN = S::TN, NC = S::NC, NS = S::NS, CPS = NC + NS; // CPS: copies per wave and stage
     static_assert(WM * WN * WK == 4 && TM % 32 == 0 && TN % 32 == 0 && 4 % WK == 0, "four waves");
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -122,9 +133,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
         const uint32_t row = (uint32_t)min((int64_t)(d < TM / 32 ? r : r - TM), left);
         vo[d] = OEK ? row : row * pitch + chunk_fp4;
     }
-    uint32_t so[NS];      // scales: lane i copies half i % 2 of row i / 2 of 32
-    bool s_is_a[NS];      // (wave-uniform)
-    int s_at[NS];
+    constexpr int NS1 = NS > 0 ? NS : 1;
+    uint32_t so[NS1];     // scales: lane i copies half i % 2 of row i / 2 of 32
+    bool s_is_a[NS1];     // (wave-uniform)
+    int s_at[NS1];
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         const int q = (w + 4 * j) % ((TM + TN) / 32); // (a wave without a copy of its own repeats another's: same bytes)
@@ -137,8 +149,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
     const uint64_t ga = reinterpret_cast<uint64_t>(a_codes) + m0 * pitch, gb = reinterpret_cast<uint64_t>(b_codes) + n0 * pitch;
     const uint64_t gga = reinterpret_cast<uint64_t>(Ag) + m0 * gpitch, ggb = reinterpret_cast<uint64_t>(Bg) + n0 * gpitch;
     // scale copies: base and stage stride of the operand that copy j of this wave serves
-    const uint8_t *sp[NS];
-    int64_t sstep[NS];
+    const uint8_t *sp[NS1];
+    int64_t sstep[NS1];
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         sp[j] = s_is_a[j] ? a_sc.p + m0 * a_sc.row : b_sc.p + n0 * b_sc.row;
@@ -178,7 +190,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
     // ---- fragment reads: row l32 (+ 32 i) of the wave's part, logical chunk 4 h + s in step s
     const int rx = (l32 >> 1) & 7;
     const int a_row = (wm * TMB * 32 + l32) * TKB, b_row = (TM + wn * TNB * 32 + l32) * TKB;
-    const int sa_row = S::SLAB + (wm * TMB * 32 + l32) * 8 + 4 * h, sb_row = S::SLAB + (TM + wn * TNB * 32 + l32) * 8 + 4 * h;
+    const int sa_row = (wm * TMB * 32 + l32) * 8 + 4 * h, sb_row = (TM + wn * TNB * 32 + l32) * 8 + 4 * h;
+    auto scales_of = [&](int t, int b) { return smem + (PRE ? NST * S::STAGE + (t - nbf) * S::SCALES : b * S::STAGE + S::SLAB); };
+
+    // (PRE) the last stage's first `zeros` scales of a row, which stand for blocks that it lacks, count as 0
+    const int zeros = PRE ? -(int)(K >> 5) & 7 : 0, behind = min(max(zeros - 4 * h, 0), 4);
+    const uint32_t keep_last = behind == 4 ? 0u : ~0u << (8 * behind);
+    const uint8_t *const last_scales = smem + NST * S::STAGE + (nfp - 1) * S::SCALES;
 
     v16f acc[TMB][TNB];
 #pragma unroll
@@ -192,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
     // (ISSUE) the copies of stage `which` into buffer `wb`, spread evenly: a wave issues in order, and all copies at the head
     // of the stage kept it from the matrix cores for half of its time (0.67 us per stage of 128 x 128 where the matrix
     // cores need 0.2).
-    auto stage = [&](const uint8_t *st, auto bf_c, auto issue_c, int which, int wb) {
+    auto stage = [&](const uint8_t *st, const uint8_t *ss, auto bf_c, auto issue_c, int which, int wb) {
         constexpr bool BF = decltype(bf_c)::value, ISSUE = decltype(issue_c)::value;
         constexpr int STEPS = 4 / WK, T = TMB * TNB * STEPS;
         int sa[TMB], sb[TNB];
@@ -206,12 +224,19 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
         };
         if constexpr (!BF) {
 #pragma unroll
-            for (int i = 0; i < TMB; ++i) sa[i] = *reinterpret_cast<const int *>(st + sa_row + i * 256);
+            for (int i = 0; i < TMB; ++i) sa[i] = *reinterpret_cast<const int *>(ss + sa_row + i * 256);
 #pragma unroll
-            for (int j = 0; j < TNB; ++j) sb[j] = *reinterpret_cast<const int *>(st + sb_row + j * 256);
+            for (int j = 0; j < TNB; ++j) sb[j] = *reinterpret_cast<const int *>(ss + sb_row + j * 256);
         }
         read(0);
         ADAHOP_PIN();
+        if constexpr (!BF && PRE) {
+            const int keep = ss == last_scales ? (int)keep_last : -1;
+#pragma unroll
+            for (int i = 0; i < TMB; ++i) sa[i] &= keep;
+#pragma unroll
+            for (int j = 0; j < TNB; ++j) sb[j] &= keep;
+        }
         if constexpr (!BF && WK > 1) {
 #pragma unroll
             for (int i = 0; i < TMB; ++i) sa[i] >>= 8 * STEPS * wk;
@@ -243,12 +268,78 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
     auto run = [&](int t, int b, auto issue_c, int which, int wb) {
         const uint8_t *st = smem + b * S::STAGE;
         if (OEK && t < nbf)
-            stage(st, std::true_type(), issue_c, which, wb);
+            stage(st, st, std::true_type(), issue_c, which, wb);
         else
-            stage(st, std::false_type(), issue_c, which, wb);
+            stage(st, scales_of(t, b), std::false_type(), issue_c, which, wb);
     };
 
-    for (int s = 0; s < NST - PU && s < n; ++s) issue_all(s, s);
+    constexpr int AHEAD = NST - PU; // stages whose copies are asked for here
+    if constexpr (PRE) {
+        // A run is read in aligned words (at most 128 x 32 bytes: four per thread) and the bytes in front of the first and behind the
+        // last of them.  The loads of both operands go ahead of the stages' copies, so that the wait for them is the wait that the
+        // first stage needs anyway.
+        uint8_t *const all = smem + NST * S::STAGE;
+        const int KB = (int)(K >> 5);
+        struct run_t {
+            const uint8_t *p;
+            int rows, head, words, edge; // edge: the byte in front of or behind the words that this thread takes, if it lies in the run
+            uint32_t v[4], e;
+        };
+        auto fetch = [&](const scale_src_t &sc, int64_t first, int64_t left, int most) {
+            run_t r;
+            r.rows = (int)min((int64_t)most, left);
+            r.p = sc.p + first * KB;
+            const int total = r.rows * KB;
+            r.head = min((int)(-(uint32_t)reinterpret_cast<uintptr_t>(r.p) & 3u), total);
+            r.words = sc.canonical ? (total - r.head) >> 2 : 0;
+            r.edge = tid < r.head ? tid : 4 * r.words + tid;
+            r.e = 0;
+            if (sc.canonical && r.edge < total) r.e = r.p[r.edge];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                r.v[j] = 0;
+                if (256 * j < r.words) r.v[j] = *reinterpret_cast<const uint32_t *>(r.p + r.head + 4 * min(tid + 256 * j, r.words - 1));
+            }
+            return r;
+        };
+        auto place = [&](const scale_src_t &sc, const run_t &r, int64_t first, int to) {
+            if (!sc.canonical) { // stage-major: eight bytes per row and stage as they are
+                for (int s = 0; s < nfp; ++s)
+                    if (tid < r.rows)
+                        *reinterpret_cast<uint64_t *>(all + s * S::SCALES + (to + tid) * 8) =
+                            *reinterpret_cast<const uint64_t *>(sc.p + (first + tid) * 8 + s * sc.stage);
+                return;
+            }
+            auto put_byte = [&](int row, int blk, uint32_t x) {
+                const int s = blk >> 3;
+                all[s * S::SCALES + (to + row) * 8 + (blk & 7) + (s == nfp - 1 ? zeros : 0)] = (uint8_t)x;
+            };
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (256 * j < r.words) {
+                    const int i = r.head + 4 * (tid + 256 * j);
+                    int row = (int)((uint32_t)i * sc.canonical >> 20), blk = i - row * KB;
+                    if (tid + 256 * j < r.words) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            put_byte(row, blk, r.v[j] >> (8 * q));
+                            const bool over = ++blk == KB;
+                            row += over, blk = over ? 0 : blk;
+                        }
+                    }
+                }
+            if (r.edge < r.rows * KB) {
+                const int row = (int)((uint32_t)r.edge * sc.canonical >> 20);
+                put_byte(row, r.edge - row * KB, r.e);
+            }
+        };
+        const run_t ra = fetch(a_sc, m0, M - m0, TM), rb = fetch(b_sc, n0, N - n0, TN);
+        for (int s = 0; s < AHEAD && s < n; ++s) issue_all(s, s);
+        place(a_sc, ra, m0, 0);
+        place(b_sc, rb, n0, TM); // (the barrier at the head of the first stage stands between these and their readers)
+    } else {
+        for (int s = 0; s < AHEAD && s < n; ++s) issue_all(s, s);
+    }
     int t = 0, b = 0; // stage t lies in buffer b = t % NST
     auto at = [&](int x) { return x < NST ? x : x - NST; };
     // PU stages with the copies of PU more, into the buffers of stages t - PU .. t - 1, which every wave has left
@@ -262,10 +353,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
     const std::true_type yes;
     const std::false_type no;
     if constexpr (OEK) { // loops of their own: a branch around the matrix-core instructions moves the accumulators at every stage
-        while (t + NST <= n && t + PU <= nbf) full([&](int, int rb, int which, int wb) { stage(smem + rb * S::STAGE, yes, yes, which, wb); });
+        while (t + NST <= n && t + PU <= nbf) full([&](int, int rb, int which, int wb) { stage(smem + rb * S::STAGE, smem, yes, yes, which, wb); });
         if (PU > 1 && t + NST <= n && t < nbf) full([&](int s, int rb, int which, int wb) { run(s, rb, yes, which, wb); });
     }
-    while (t + NST <= n) full([&](int, int rb, int which, int wb) { stage(smem + rb * S::STAGE, no, yes, which, wb); });
+    while (t + NST <= n) full([&](int s, int rb, int which, int wb) { stage(smem + rb * S::STAGE, scales_of(s, rb), no, yes, which, wb); });
     for (; t < n; t += PU, b = at(b + PU)) {
         wait_and_meet<0>();
 #pragma unroll
@@ -315,33 +406,46 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
 }
 
 template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct variant_t {
-    typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU> S;
-    template <bool OEK, typename OUT> static int allow()
+    template <bool PRE, bool OEK, typename OUT> static int allow()
     {
-        return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, OEK, OUT>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS));
+        return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, OEK, OUT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             shape_t<TMB, TNB, WM, WN, WK, NST, PU, PRE>::LDS));
+    }
+    template <bool PRE> static int configure_as()
+    {
+        int rc;
+        if ((rc = allow<PRE, false, float>()) != ADAHOP_OK || (rc = allow<PRE, false, uint16_t>()) != ADAHOP_OK) return rc;
+        if ((rc = allow<PRE, true, float>()) != ADAHOP_OK || (rc = allow<PRE, true, uint16_t>()) != ADAHOP_OK) return rc;
+        return ADAHOP_OK;
     }
     static int configure()
     {
-        int rc;
-        if ((rc = allow<false, float>()) != ADAHOP_OK || (rc = allow<true, float>()) != ADAHOP_OK ||
-            (rc = allow<false, uint16_t>()) != ADAHOP_OK)
-            return rc;
-        return allow<true, uint16_t>();
+        const int rc = configure_as<false>();
+        return rc != ADAHOP_OK ? rc : configure_as<true>();
+    }
+    template <bool PRE, typename OUT>
+    static int launch_as(int64_t M, int64_t N, int64_t K, const uint8_t *a, scale_src_t as, const uint8_t *b, scale_src_t bs, OUT *C,
+                         int64_t ldc, const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st)
+    {
+        typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU, PRE> S;
+        const int64_t tm = ceil_div(M, S::TM), tn = ceil_div(N, S::TN);
+        const dim3 grid((unsigned)(tm * tn));
+        if (kpad > 0) {
+            hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, true, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b,
+                               bs, M, N, C, ldc, Ag, Bg, kpad, (int)tm);
+            return check_launch();
+        }
+        hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, false, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b, bs,
+                           M, N, C, ldc, Ag, Bg, kpad, (int)tm);
+        return check_launch();
     }
     template <typename OUT>
     static int launch(int64_t M, int64_t N, int64_t K, const uint8_t *a, scale_src_t as, const uint8_t *b, scale_src_t bs, OUT *C,
                       int64_t ldc, const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st)
     {
-        const int64_t tm = ceil_div(M, S::TM), tn = ceil_div(N, S::TN);
-        const dim3 grid((unsigned)(tm * tn));
-        if (kpad > 0)
-            hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, true, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b, bs,
-                               M, N, C, ldc, Ag, Bg, kpad, (int)tm);
-        else
-            hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, false, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b, bs,
-                               M, N, C, ldc, Ag, Bg, kpad, (int)tm);
-        return check_launch();
+        return as.canonical || bs.canonical ? launch_as<true>(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st)
+                                            : launch_as<false>(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     }
 };
 
@@ -416,6 +520,8 @@ int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us)
     return best;
 }
 
+bool gemm_mx_small_takes_canonical(int64_t K) { return ceil_div(K, 256) <= small::PRE_STAGES; }
+
 int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,
                          const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
                          const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st)
@@ -423,7 +529,11 @@ int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uin
     const int rc = configure_gemm_mx_small();
     if (rc != ADAHOP_OK) return rc;
     const int64_t KB = K / 32;
-    const small::scale_src_t as = {a_scales, a_sm ? 8 : KB, a_sm ? M * 8 : 8}, bs = {b_scales, b_sm ? 8 : KB, b_sm ? N * 8 : 8};
+    // canonical scales that cannot be copied stage by stage: 8 bytes of every row, 4-byte aligned
+    const bool any = KB % 8 != 0 || !aligned(a_sm ? nullptr : a_scales, 4) || !aligned(b_sm ? nullptr : b_scales, 4);
+    const uint32_t rows_of = any ? (uint32_t)(((1 << 20) + KB - 1) / KB) : 0u;
+    const small::scale_src_t as = {a_scales, a_sm ? 8 : KB, a_sm ? M * 8 : 8, a_sm ? 0u : rows_of},
+                             bs = {b_scales, b_sm ? 8 : KB, b_sm ? N * 8 : 8, b_sm ? 0u : rows_of};
     if (c_bf16)
         return launch_small_t(variant, M, N, K, a_codes, as, b_codes, bs, static_cast<uint16_t *>(C), ldc, Ag, Bg, kpad, st);
     return launch_small_t(variant, M, N, K, a_codes, as, b_codes, bs, static_cast<float *>(C), ldc, Ag, Bg, kpad, st);

@@ -136,16 +136,24 @@ def test_ragged_whole_path(ah, layouts, M, N, K, strategy, k):
     check_c(host(out["C"]), ref["C"], g, extracted=ref["idx"] if k else None, tol=1e-5)
 
 
+def shifted(t, by):
+    """The same bytes `by` bytes behind the start of an allocation, which ends with them."""
+    room = torch.empty(t.numel() + by, dtype=torch.uint8, device="cuda")
+    room[by:] = t.flatten()
+    return room[by:].view(t.shape)
+
+
 SMALL = (7, 8, 9, 10, 11)           # 128 x 128 shallow and deep, 64 x 64, 32 x 64, 32 x 32
 
 
 @pytest.mark.parametrize("kernel", SMALL)
 @pytest.mark.parametrize("shape", [(1, 1, 32), (31, 33, 64), (33, 65, 224), (64, 64, 256), (65, 127, 288), (129, 130, 512),
-                                   (96, 1000, 1056), (300, 257, 2304), (130, 640, 4064), (17, 4100, 768)])
+                                   (96, 1000, 1056), (300, 257, 2304), (130, 640, 4064), (17, 4100, 768), (300, 270, 96),
+                                   (131, 261, 992)])
 def test_small_tiles(ah, force, kernel, shape):
     """Rows and columns one past and one short of a tile, K from one block over less than a stage to more stages than
-    rotate in LDS, an odd and an even count of them, canonical (K % 256 == 0) and re-ordered scales, a C with a gap behind
-    its rows that must stay as it was; both output types.  The allowance is the one above, plus half a bf16 step."""
+    rotate in LDS, an odd and an even count of them, canonical (K % 256 == 0, or up to 1024 at any address) and re-ordered scales, a C
+    with a gap behind its rows that must stay as it was; both output types.  The allowance is the one above, plus half a bf16 step."""
     M, N, K = shape
     rng = np.random.default_rng(M + 5 * N + 11 * K)
     a_codes = rng.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
@@ -157,9 +165,10 @@ def test_small_tiles(ah, force, kernel, shape):
     ref = orc.mx_gemm(a_codes, a_scales, b_codes, b_scales)
     bar = 2.0 ** -20 * np.outer(dequant_norms(a_codes, a_scales), dequant_norms(b_codes, b_scales))
     dev = [torch.from_numpy(t).cuda() for t in (a_codes, a_scales, b_codes, b_scales)]
-    for dtype in (torch.float32, torch.bfloat16):
+    off = [dev[0], shifted(dev[1], 1), dev[2], shifted(dev[3], 3)]      # scales at odd addresses
+    for dtype, ops in ((torch.float32, dev), (torch.bfloat16, dev), (torch.float32, off)):
         room = torch.full((M + 1, N + 3), 7.0, dtype=dtype, device="cuda")
-        ah.adahop_gemm_mx(*dev, Cout=room[:M, :N])
+        ah.adahop_gemm_mx(*ops, Cout=room[:M, :N])
         torch.cuda.synchronize()
         got = host(room.float()).astype(np.float64)
         assert (got[M] == 7.0).all() and (got[:, N:] == 7.0).all()
