@@ -93,12 +93,26 @@ template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool PRE> s
     static constexpr int NS = PRE ? 0 : ((TM + TN) / 32 + 3) / 4; // 4-byte copies of scales per wave and stage (a copy: 32 rows)
 };
 
+// The order of the tiles (launch_as).  A C that the Infinity Cache holds: down the columns of tiles, in runs per XCD, so that the
+// workgroups that read the same rows of B share an L2.  A larger one leaves for memory while the product runs, and what counts is that
+// what lies together is written together: along the rows of tiles, in runs per XCD, which also puts the pieces of a line that two
+// tiles share into one L2; without the runs where the rows of C are whole 4-KiB pages, of which the runs would write eight times as many in
+// different places, but on the same memory channels (with one stage of K in fp32: of whole 64-byte pieces, 8569 x 8576 x 96 49 along, 57 in
+// runs).  Where K is one stage there is little to share, and the line lies lower: 8454 x 10175 x 192 in bf16 (164 MB) 54 / 43 / 43, but 2541 x
+// 13392 x 96 (130 MB) 26.6 / 27.2 / 27.3.  128 x 128 tiles, us, down in runs / along / along in runs:
+//   9687 x 14001 x 64 (517 MB, ldc 14001)  203 / 185 / 133      8192 x 16384 x 64 (512 MB)     153 / 109 / 110
+//   24515 x 9536 x 320 (891 MB)            234 / 249 / 214      8192 x 16384 x 1024           231 / 166 / 190
+//   6000 x 9001 x 64 (206 MB, ldc 9001)     47 /  47 /  43      30000 x 4096 x 512 (468 MB)    116 / 118 / 147
+//   4001 x 12001 x 512 (183 MB, ldc 12001)  47 /  53 /  49      4096 x 11008 x 512 (172 MB)     40 /  42 /  44
+enum walk_t { DOWN = 0, ALONG_ROWS = 1, RUNS = 2 };
+constexpr int64_t C_STAYS = 192ll << 20, C_STAYS_SHORT = 136ll << 20; // bytes of C; the latter for K <= 256
+
 template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool PRE, bool OEK, typename OUT>
-__global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8_t *__restrict__ a_codes, scale_src_t a_sc,
+__global__ __launch_bounds__(256, NST == 1 ? 4 : 2) void k_gemm_mx_small(int64_t K, const uint8_t *__restrict__ a_codes, scale_src_t a_sc,
                                                           const uint8_t *__restrict__ b_codes, scale_src_t b_sc, int64_t M,
                                                           int64_t N, OUT *__restrict__ C, int64_t ldc,
                                                           const uint16_t *__restrict__ Ag, const uint16_t *__restrict__ Bg,
-                                                          int kpad, int tiles_m)
+                                                          int kpad, int walk, int tiles_fast)
 {
     typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU, PRE> S;
     constexpr int TM = S::TM, TN = S::TN, NC = S::NC, NS = S::NS, CPS = NC + NS; // CPS: copies per wave and stage
@@ -108,14 +122,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wk = w % WK, wmn = w / WK, wm = wmn / WN, wn = wmn % WN;
 
-    // Workgroup v -> tile, row tiles fastest: consecutive ids land on the 8 XCDs in turn, and every XCD takes a contiguous run,
-    // so that the workgroups that read the same rows of B share an L2.
+    // Workgroup v -> tile.  Consecutive ids land on the 8 XCDs in turn; RUNS: every XCD takes a contiguous run of the tiles.
     int tix = blockIdx.x;
-    {
+    if (walk & RUNS) {
         const int nt = gridDim.x, per = nt >> 3, rest = nt & 7, x = tix & 7;
         tix = x * per + min(x, rest) + (tix >> 3);
     }
-    const int64_t m0 = (int64_t)(tix % tiles_m) * TM, n0 = (int64_t)(tix / tiles_m) * TN;
+    const int fast = tix % tiles_fast, slow = tix / tiles_fast;
+    const int64_t m0 = (int64_t)(walk & ALONG_ROWS ? slow : fast) * TM, n0 = (int64_t)(walk & ALONG_ROWS ? fast : slow) * TN;
 
     // ---- copy engine.  Copy d of wave w: rows 8 (w + 4 d) .. + 7 of the tile's TM rows of A and TN rows of B; lane i writes
     // LDS row i / 8 of them, chunk position i % 8, which holds logical chunk (i % 8) ^ ((row / 2) & 7).
@@ -177,7 +191,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
                 if (d < NC) {
                     uint32_t v = vo[d];
                     if constexpr (OEK) v = __umul24(v, rp) + ch;
-                    dma16(d < TM / 32 ? pa : pb, v, buf + (uint32_t)(w + 4 * d) * 1024);
+                    if (NST > 1 || (int)chunk16 >= short_by) dma16(d < TM / 32 ? pa : pb, v, buf + (uint32_t)(w + 4 * d) * 1024);
                 } else {
                     const int j = d - NC;
                     dma4(sp[j] + fs * sstep[j], so[j], buf + S::SLAB + s_at[j] * 256);
@@ -228,6 +242,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
 #pragma unroll
             for (int j = 0; j < TNB; ++j) sb[j] = *reinterpret_cast<const int *>(ss + sb_row + j * 256);
         }
+        const int absent = NST == 1 ? max(4 - (int)(K >> 5), 0) : 0; // steps of a stage of K < 128 that hold none of its blocks
         read(0);
         ADAHOP_PIN();
         if constexpr (!BF && PRE) {
@@ -245,6 +260,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
         }
         auto one = [&](auto k_c) { // matrix-core instruction k of the stage: step k / (TMB TNB), row-major over the wave's tiles
             constexpr int k = decltype(k_c)::value, q = k / (TMB * TNB), e = k % (TMB * TNB), i = e / TNB, j = e % TNB;
+            if (NST == 1 && q < absent) return; // (only blocks of scale 0)
+            if constexpr (e == 0 && NST == 1 && q > 0) {
+                if (q == absent) read(q); // (the first step that is there)
+            }
             if constexpr (e == 0 && q + 1 < STEPS) {
                 read(q + 1);
                 ADAHOP_PIN();
@@ -273,7 +292,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
             stage(st, scales_of(t, b), std::false_type(), issue_c, which, wb);
     };
 
-    constexpr int AHEAD = NST - PU; // stages whose copies are asked for here
+    constexpr int AHEAD = NST > 1 ? NST - PU : 1; // stages whose copies are asked for here
     if constexpr (PRE) {
         // A run is read in aligned words (at most 128 x 32 bytes: four per thread) and the bytes in front of the first and behind the
         // last of them.  The loads of both operands go ahead of the stages' copies, so that the wait for them is the wait that the
@@ -356,12 +375,12 @@ __global__ __launch_bounds__(256, 2) void k_gemm_mx_small(int64_t K, const uint8
         while (t + NST <= n && t + PU <= nbf) full([&](int, int rb, int which, int wb) { stage(smem + rb * S::STAGE, smem, yes, yes, which, wb); });
         if (PU > 1 && t + NST <= n && t < nbf) full([&](int s, int rb, int which, int wb) { run(s, rb, yes, which, wb); });
     }
-    while (t + NST <= n) full([&](int s, int rb, int which, int wb) { stage(smem + rb * S::STAGE, scales_of(s, rb), no, yes, which, wb); });
+    while (NST > 1 && t + NST <= n) full([&](int s, int rb, int which, int wb) { stage(smem + rb * S::STAGE, scales_of(s, rb), no, yes, which, wb); });
     for (; t < n; t += PU, b = at(b + PU)) {
         wait_and_meet<0>();
 #pragma unroll
         for (int u = 0; u < PU; ++u)
-            if (t + NST - PU + u < n) issue_all(t + NST - PU + u, at(b + NST - PU + u));
+            if (NST > 1 && t + NST - PU + u < n) issue_all(t + NST - PU + u, at(b + NST - PU + u));
         run(t, b, std::false_type(), 0, 0);
 #pragma unroll
         for (int u = 1; u < PU; ++u)
@@ -416,7 +435,9 @@ template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct vari
     {
         int rc;
         if ((rc = allow<PRE, false, float>()) != ADAHOP_OK || (rc = allow<PRE, false, uint16_t>()) != ADAHOP_OK) return rc;
-        if ((rc = allow<PRE, true, float>()) != ADAHOP_OK || (rc = allow<PRE, true, uint16_t>()) != ADAHOP_OK) return rc;
+        if constexpr (NST > 1) { // (K-channels and a stage of K are two stages)
+            if ((rc = allow<PRE, true, float>()) != ADAHOP_OK || (rc = allow<PRE, true, uint16_t>()) != ADAHOP_OK) return rc;
+        }
         return ADAHOP_OK;
     }
     static int configure()
@@ -431,13 +452,19 @@ template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct vari
         typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU, PRE> S;
         const int64_t tm = ceil_div(M, S::TM), tn = ceil_div(N, S::TN);
         const dim3 grid((unsigned)(tm * tn));
-        if (kpad > 0) {
-            hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, true, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b,
-                               bs, M, N, C, ldc, Ag, Bg, kpad, (int)tm);
-            return check_launch();
+        const bool leaves = M * N * (int64_t)sizeof(OUT) >= (K <= 256 ? C_STAYS_SHORT : C_STAYS);
+        const int64_t whole = NST == 1 && sizeof(OUT) == 4 ? 64 : 4096;
+        const int walk = !leaves ? DOWN | RUNS : ldc * (int64_t)sizeof(OUT) % whole == 0 ? ALONG_ROWS : ALONG_ROWS | RUNS;
+        const int fast = (int)(leaves ? tn : tm);
+        if constexpr (NST > 1) {
+            if (kpad > 0) {
+                hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, true, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b,
+                                   bs, M, N, C, ldc, Ag, Bg, kpad, walk, fast);
+                return check_launch();
+            }
         }
         hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, false, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b, bs,
-                           M, N, C, ldc, Ag, Bg, kpad, (int)tm);
+                           M, N, C, ldc, Ag, Bg, kpad, walk, fast);
         return check_launch();
     }
     template <typename OUT>
@@ -450,6 +477,11 @@ template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct vari
 };
 
 typedef variant_t<2, 2, 2, 2, 1, 2, 1> v128_t;    // 128 x 128, two workgroups per compute unit
+// 128 x 128 for a K of one stage: one buffer, half the registers, four workgroups.  Such a product is its stores, which three other
+// workgroups' loads then run beside: 2541 x 13392 x 96 30.4 -> 26.8 us, in bf16 26.5 -> 20.5, 16384 x 16384 x 96 217 -> 190.
+// Not for more than 64 MB of fp32 off the 64-byte grid, where twice the tiles in flight cost more line pieces than they hide (9687 x
+// 14001 x 64 133 / 203 us, 6000 x 9001 x 64 43 / 46; 3324 x 2547 x 32, 32 MB, 13.8 / 12.1), and not for K = 256, where it gains nothing.
+typedef variant_t<2, 2, 2, 2, 1, 1, 1> v128one_t;
 typedef variant_t<2, 2, 2, 2, 1, 3, 1> v128deep_t; // 128 x 128, one workgroup, two stages on the way
 typedef variant_t<2, 2, 1, 1, 4, 4, 1> v64_t;     // 64 x 64
 typedef variant_t<1, 2, 1, 1, 4, 4, 1> v32x64_t;  // 32 x 64
@@ -479,7 +511,7 @@ int configure_gemm_mx_small()
     int rc = check_hip(hipGetDevice(&dev));
     if (rc != ADAHOP_OK || !once.need(dev)) return rc;
     using namespace small;
-    if ((rc = v128_t::configure()) != ADAHOP_OK || (rc = v128deep_t::configure()) != ADAHOP_OK ||
+    if ((rc = v128_t::configure()) != ADAHOP_OK || (rc = v128one_t::configure()) != ADAHOP_OK || (rc = v128deep_t::configure()) != ADAHOP_OK ||
         (rc = v64_t::configure()) != ADAHOP_OK || (rc = v32x64_t::configure()) != ADAHOP_OK ||
         (rc = v32_t::configure()) != ADAHOP_OK)
         return rc;
@@ -494,7 +526,10 @@ static int launch_small_t(int variant, int64_t M, int64_t N, int64_t K, const ui
 {
     using namespace small;
     switch (variant) {
-    case 0: return v128_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    case 0:
+        if (K <= 192 && kpad == 0 && (sizeof(OUT) == 2 || c_rows_streamed(C, ldc * 4) || M * N <= (16 << 20)))
+            return v128one_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+        return v128_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 1: return v128deep_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 2: return v64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 3: return v32x64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);

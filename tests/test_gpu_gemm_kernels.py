@@ -176,6 +176,31 @@ def test_small_tiles(ah, force, kernel, shape):
         assert float((np.abs(got[:M, :N] - ref) - step * np.abs(ref) - bar * (1.0 + step)).max()) <= 0.0
 
 
+@pytest.mark.parametrize("M,N,K,ld,dtype", [(4250, 8450, 96, 8452, torch.float32), (4250, 8450, 192, 8464, torch.float32),
+                                            (8400, 8500, 64, 8501, torch.bfloat16), (6200, 8150, 288, 8192, torch.float32),
+                                            (6200, 8150, 480, 8151, torch.float32), (4000, 3900, 32, 3901, torch.float32)])
+def test_short_products_with_a_large_c(ah, M, N, K, ld, dtype):
+    """The orders in which tiles are walked where C is larger than the Infinity Cache (rows of whole pages, of whole 64-byte pieces and of
+    neither), with the 128 x 128 tiles of a single stage of K and of more: rows at every tile's edges against the oracle, and the gap behind
+    the rows as it was.  The allowance is the one above, plus half a bf16 step."""
+    rng = np.random.default_rng(M + N + K)
+    a_codes = rng.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
+    b_codes = rng.integers(0, 256, size=(N, K // 2), dtype=np.uint8)
+    a_scales = rng.integers(117, 137, size=(M, K // 32), dtype=np.uint8)
+    b_scales = rng.integers(100, 120, size=(N, K // 32), dtype=np.uint8)
+    say("large C", (M, N, K, ld), dtype)
+    room = torch.full((M, ld), 7.0, dtype=dtype, device="cuda")
+    ah.adahop_gemm_mx(*(torch.from_numpy(t).cuda() for t in (a_codes, a_scales, b_codes, b_scales)), Cout=room[:, :N])
+    torch.cuda.synchronize()
+    assert bool((room[:, N:] == 7.0).all())
+    rows = np.unique(np.concatenate([np.arange(0, M, 128), np.arange(127, M, 128), [M - 1]]))
+    ref = orc.mx_gemm(a_codes[rows], a_scales[rows], b_codes, b_scales)
+    bar = 2.0 ** -20 * np.outer(dequant_norms(a_codes[rows], a_scales[rows]), dequant_norms(b_codes, b_scales))
+    got = host(room[torch.from_numpy(rows).cuda(), :N].float()).astype(np.float64)
+    step = 0.0 if dtype == torch.float32 else 2.0 ** -8
+    assert float((np.abs(got - ref) - step * np.abs(ref) - bar * (1.0 + step)).max()) <= 0.0
+
+
 @pytest.mark.parametrize("kernel", SMALL)
 @pytest.mark.parametrize("M,N,K,k", [(40, 70, 96, 9), (96, 264, 1120, 70), (150, 129, 2048, 200)])
 def test_small_tiles_with_k_channels(ah, force, kernel, M, N, K, k):
