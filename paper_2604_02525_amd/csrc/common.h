@@ -168,11 +168,18 @@ __device__ __forceinline__ uint4 load_once16(const void *p)
     const u32x4 v = __builtin_nontemporal_load(static_cast<const u32x4 *>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ uint32_t load_once4(const void *p)
-{
-    return __builtin_nontemporal_load(static_cast<const uint32_t *>(p));
-}
 __device__ __forceinline__ uint16_t load_once2(const uint16_t *p) { return __builtin_nontemporal_load(p); }
+// The first n < 8 elements of a 16-byte piece, zeros behind them: where a matrix ends inside the piece.
+__device__ __forceinline__ uint4 load_part16(const uint16_t *p, int n)
+{
+    uint64_t lo = 0, hi = 0;
+#pragma nounroll
+    for (int j = n - 1; j >= 0; --j) {
+        hi = hi << 16 | lo >> 48;
+        lo = lo << 16 | load_once2(p + j);
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
 
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xffff0000u); }

@@ -91,7 +91,9 @@ __global__ __launch_bounds__(256) void k_gather_rows_strided(const uint16_t *__r
 // NCW: column tiles of 32 rows of L per wave.  2, and 1 where the products' workgroups then fill no more than half of the compute
 // units (a short L, or a K of few slices): 82 rows x 4096 x 4096 16.4 -> 14.1 us, 82 x 2048 x 2048 13.0 -> 8.8, 41 x 2048 x 8192
 // 14.5 -> 11.1, 41 columns x 320 x 4096 10.3 -> 6.9.
-template <int RT, bool LONG_KC, int NCW>
+// EDGE (K-strided L of a number of rows that is no multiple of 8): the matrix ends inside the last 16-byte piece of its last K-row.  The
+// lanes of that piece read the K-row above in its place and write the elements that exist, read one by one at the start.
+template <int RT, bool LONG_KC, int NCW, bool EDGE>
 __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict__ Sg, const uint16_t *__restrict__ L,
                                                       int64_t ldl, int64_t Lo, int64_t K, int stages_per_slice,
                                                       float *__restrict__ P, int64_t rows_all)
@@ -128,6 +130,14 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
         const int64_t l = l0 + 8 * c32, l_last = (Lo - 1) / 8 * 8; // whole 16-byte pieces: ld is a multiple of 8
         voff_l[0] = (uint32_t)(((int64_t)k8 * ldl) * 2) + (uint32_t)((l < l_last ? l : l_last) * 2);
     }
+    static_assert(!(EDGE && LONG_KC), "rows of a K-contiguous operand are whole pieces");
+    uint4 end_piece = make_uint4(0, 0, 0, 0);
+    const bool last_piece = EDGE && l0 + 8 * c32 >= Lo / 8 * 8;
+    if (last_piece) end_piece = load_part16(L + (K - 1) * ldl + Lo / 8 * 8, (int)(Lo & 7));
+    // whether piece i of a stage is that piece (kk0: the stage's first K-row)
+    auto is_end = [&](int64_t kk0, int i) {
+        return last_piece && kk0 + k8 + (kk0 + SK_KSTAGE > K ? (KPP * i) & 31 : KPP * i) == K - 1;
+    };
 
     // A stage past the end of the slice (the loop below works on pairs of stages) reads the slice's last stage
     // again with the Sg side cleared.  No branches: the loop body stays one block, which the interleaving of
@@ -137,15 +147,13 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     // QUARTER = -1: all of them.
     // (The clearing of the Sg side happens when the registers are written to LDS, stage_keep below: touching a
     // loaded value here would make the wave wait for the load it has just issued.)
+    auto first_row = [&](int stage) { return (int64_t)(stage >= s1 ? s1 - 1 : stage) * SK_KSTAGE; };
     auto stage_keep = [&](int stage) -> uint32_t {
-        const bool ghost = stage >= s1;
-        const int64_t kk0 = (int64_t)(ghost ? s1 - 1 : stage) * SK_KSTAGE;
-        return (ghost || (kk0 + SK_KSTAGE > K && c8 >= 4)) ? 0u : 0xffffffffu;
+        return (stage >= s1 || (first_row(stage) + SK_KSTAGE > K && c8 >= 4)) ? 0u : 0xffffffffu;
     };
     auto fetch = [&](int stage, uint4 (&fs)[RT], uint4 (&fl)[NL], auto quarter) {
         constexpr int Q = decltype(quarter)::value;
-        const bool ghost = stage >= s1;
-        const int64_t kk0 = (int64_t)(ghost ? s1 - 1 : stage) * SK_KSTAGE;
+        const int64_t kk0 = first_row(stage);
         const bool half = kk0 + SK_KSTAGE > K; // K is a multiple of 32: the last stage may hold 32 K-elements
         const uint32_t back = half && c8 >= 4 ? 64u : 0u;
 #pragma unroll
@@ -159,10 +167,11 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             if constexpr (LONG_KC)
                 fl[i] = load_once16(Lb + kk0 * 2 + (voff_l[i] - back));
             else
-                fl[i] = load_once16(Lb + (kk0 + (half ? (KPP * i) & 31 : KPP * i)) * ldl * 2 + voff_l[0]);
+                fl[i] = load_once16(Lb + (kk0 + (half ? (KPP * i) & 31 : KPP * i)) * ldl * 2 + voff_l[0] -
+                                    (EDGE && is_end(kk0, i) ? 2 * ldl : 0));
         }
     };
-    auto stash = [&](uint16_t *buf, const uint4 (&fs)[RT], const uint4 (&fl)[NL], uint32_t keep, auto quarter) {
+    auto stash = [&](int stage, uint16_t *buf, const uint4 (&fs)[RT], const uint4 (&fl)[NL], uint32_t keep, auto quarter) {
         constexpr int Q = decltype(quarter)::value;
         uint16_t *sS = buf, *sL = buf + S_ELEMS;
 #pragma unroll
@@ -177,7 +186,8 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             if constexpr (LONG_KC)
                 *reinterpret_cast<uint4 *>(sL + (r32 + 32 * i) * SK_PITCH + c8 * 8) = fl[i];
             else
-                *reinterpret_cast<uint4 *>(sL + (k8 + KPP * i) * SK_TPITCH + 8 * c32) = fl[i];
+                *reinterpret_cast<uint4 *>(sL + (k8 + KPP * i) * SK_TPITCH + 8 * c32) =
+                    EDGE && is_end(first_row(stage), i) ? end_piece : fl[i];
         }
     };
     typedef std::integral_constant<int, -1> all_t;
@@ -232,7 +242,7 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             constexpr int n_read = ks + 1 < SK_KSTAGE / 16 ? RT + (LONG_KC ? NCW : 2 * NCW) : 0;
             constexpr int n_move = NCW + (ks < RT ? 1 : 0) + (ks + 4 < RT ? 1 : 0); // LDS writes = loads of this quarter
             if constexpr (ks + 1 < SK_KSTAGE / 16) fragments(ks + 1, a[(ks + 1) & 1], b[(ks + 1) & 1]);
-            stash(oth, fs, fl, keep, ks_c);
+            stash(next - 2, oth, fs, fl, keep, ks_c);
             fetch(next, fs, fl, ks_c);
 #pragma unroll
             for (int i = 0; i < RT; ++i)
@@ -265,7 +275,7 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     uint16_t *buf0 = smem, *buf1 = smem + BUF_ELEMS;
     fetch(s0, ps[0], pl[0], all_t());
     fetch(s0 + 1, ps[1], pl[1], all_t());
-    stash(buf0, ps[0], pl[0], stage_keep(s0), all_t());
+    stash(s0, buf0, ps[0], pl[0], stage_keep(s0), all_t());
     fetch(s0 + 2, ps[0], pl[0], all_t());
     __syncthreads();
     for (int stage = s0; stage < s1; stage += 2) { // no branch around a multiply: the accumulators stay where they are
@@ -407,20 +417,32 @@ skinny_plan_t plan_skinny(int64_t Lo, int64_t K, int k)
 
 template <int RT, int NCW> constexpr size_t skinny_lds_bytes() { return 2 * (RT * 32 * SK_PITCH + sk_l_elems<NCW>()) * sizeof(uint16_t); }
 
-template <int RT, bool LONG_KC, int NCW> int allow_skinny_lds()
+template <int RT, bool LONG_KC, int NCW, bool EDGE> int allow_skinny_lds()
 {
-    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_oe_skinny<RT, LONG_KC, NCW>),
+    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_oe_skinny<RT, LONG_KC, NCW, EDGE>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)skinny_lds_bytes<RT, NCW>()));
 }
 
-template <int RT, bool LONG_KC, int NCW>
-int launch_skinny_as(dim3 grid, hipStream_t st, const uint16_t *Sg, const uint16_t *L, int64_t ldl, int64_t Lo, int64_t K,
+template <int RT, int NCW> int allow_skinny_lds_all()
+{
+    int rc;
+    if ((rc = allow_skinny_lds<RT, true, NCW, false>()) != ADAHOP_OK || (rc = allow_skinny_lds<RT, false, NCW, false>()) != ADAHOP_OK) return rc;
+    return allow_skinny_lds<RT, false, NCW, true>();
+}
+
+template <int RT, int NCW>
+int launch_skinny_as(bool long_kc, dim3 grid, hipStream_t st, const uint16_t *Sg, const uint16_t *L, int64_t ldl, int64_t Lo, int64_t K,
                      int sps, float *P, int64_t rows_all)
 {
     const int rc = configure_oe_rowcol(); // more LDS than a launch may ask for by default: allowed once per device
     if (rc != ADAHOP_OK) return rc;
     constexpr size_t lds = skinny_lds_bytes<RT, NCW>();
-    hipLaunchKernelGGL((k_oe_skinny<RT, LONG_KC, NCW>), grid, dim3(256), lds, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    if (long_kc)
+        hipLaunchKernelGGL((k_oe_skinny<RT, true, NCW, false>), grid, dim3(256), lds, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    else if (Lo % 8 == 0)
+        hipLaunchKernelGGL((k_oe_skinny<RT, false, NCW, false>), grid, dim3(256), lds, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    else
+        hipLaunchKernelGGL((k_oe_skinny<RT, false, NCW, true>), grid, dim3(256), lds, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
     return check_launch();
 }
 
@@ -428,11 +450,8 @@ template <int RT>
 int launch_skinny(bool long_kc, int ncw, dim3 grid, hipStream_t st, const uint16_t *Sg, const uint16_t *L, int64_t ldl, int64_t Lo,
                   int64_t K, int sps, float *P, int64_t rows_all)
 {
-    if (ncw == 1)
-        return long_kc ? launch_skinny_as<RT, true, 1>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all)
-                       : launch_skinny_as<RT, false, 1>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
-    return long_kc ? launch_skinny_as<RT, true, 2>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all)
-                   : launch_skinny_as<RT, false, 2>(grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
+    return ncw == 1 ? launch_skinny_as<RT, 1>(long_kc, grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all)
+                    : launch_skinny_as<RT, 2>(long_kc, grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
 }
 
 // out[o, t] = x(o, idx[t]) for t < k, 0 for k <= t < kpad.  out is [outer, kpad] bf16.
@@ -529,12 +548,9 @@ int configure_oe_rowcol()
     int dev = 0;
     int rc = check_hip(hipGetDevice(&dev));
     if (rc != ADAHOP_OK || !once.need(dev)) return rc;
-    if ((rc = allow_skinny_lds<2, true, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds<2, false, 1>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<4, true, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds<4, false, 1>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<6, true, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds<6, false, 1>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<2, true, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds<2, false, 2>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<4, true, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds<4, false, 2>()) != ADAHOP_OK ||
-        (rc = allow_skinny_lds<6, true, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds<6, false, 2>()) != ADAHOP_OK)
+    if ((rc = allow_skinny_lds_all<2, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds_all<4, 1>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds_all<6, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds_all<2, 2>()) != ADAHOP_OK ||
+        (rc = allow_skinny_lds_all<4, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds_all<6, 2>()) != ADAHOP_OK)
         return rc;
     once.mark(dev);
     return ADAHOP_OK;

@@ -102,13 +102,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_pattern_partial(const uint16_t *_
                 if (c0 < C && (r0 + r) * ld + c0 + 8 <= end) { // (behind a row there is the next one, or what its stride leaves)
                     u = load_once16(p);
                 } else if (c0 < C) { // the last chunk of the last row
-                    uint64_t lo = 0, hi = 0;
-#pragma nounroll
-                    for (int j = (int)min((int64_t)8, C - c0) - 1; j >= 0; --j) {
-                        hi = hi << 16 | lo >> 48;
-                        lo = lo << 16 | p[j];
-                    }
-                    u = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+                    u = load_part16(p, (int)min((int64_t)8, C - c0));
                 }
             }
             return u;

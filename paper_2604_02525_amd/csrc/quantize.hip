@@ -591,10 +591,22 @@ __device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uin
         // byte loads per lane, one for each of its K-rows, made the masked call 15 % slower than the plain one)
         uint8_t my_kz = 0;
         if (zero_k && k0 + tid < K) my_kz = zero_k[k0 + tid];
+        // The matrix ends with its last element: of the last K-row's last piece only the columns that exist are read (behind any other
+        // K-row there is the next one, or what its stride leaves).  The same way for the whole workgroup, so that the
+        // others' loads have no condition of their own.
+        if ((outer & 7) && k0 + 256 >= K && o0 + KS_COLS > outer) {
 #pragma unroll
-        for (int it = 0; it < 8; ++it) { // (a pass is one MX block of K: inside the operand or not as a whole)
-            const int64_t kk = k0 + it * 32 + rw;
-            v[it] = ok && k0 + it * 32 < K ? load_once16(x + kk * ld + oc) : make_uint4(0, 0, 0, 0);
+            for (int it = 0; it < 8; ++it) {
+                const int64_t kk = k0 + it * 32 + rw;
+                v[it] = make_uint4(0, 0, 0, 0);
+                if (ok && kk < K) v[it] = kk == K - 1 && oc + 8 > outer ? load_part16(x + kk * ld + oc, (int)(outer - oc)) : load_once16(x + kk * ld + oc);
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < 8; ++it) { // (a pass is one MX block of K: inside the operand or not as a whole)
+                const int64_t kk = k0 + it * 32 + rw;
+                v[it] = ok && k0 + it * 32 < K ? load_once16(x + kk * ld + oc) : make_uint4(0, 0, 0, 0);
+            }
         }
         uint32_t zk = 0; // bit it: the lane's K-row of pass it is masked out
         if (zero_k) {    // (uniform: a kernel argument)

@@ -592,6 +592,52 @@ def test_detect_pattern_where_the_memory_ends_with_the_matrix(ah, shape):
     assert np.allclose(host(st), want_st, rtol=1e-9, atol=1e-12), (host(st), want_st)
 
 
+def ending_with_its_last_element(ah, bits):
+    """K-strided operand of logical [outer, K] bits with nothing of its own behind the last element: NaNs follow there."""
+    outer, K = bits.shape
+    ld = (outer + 7) // 8 * 8
+    flat = np.full(K * ld + 8, 0x7fc0, dtype=np.uint16)
+    np.lib.stride_tricks.as_strided(flat, (K, outer), (2 * ld, 2))[:] = bits.T
+    return ah.Operand(torch.from_numpy(flat.view(np.int16)).cuda().as_strided((K, outer), (ld, 1)), False)
+
+
+@pytest.mark.parametrize("outer", [1, 7, 65, 130, 187])
+@pytest.mark.parametrize("K,b", [(32, 32), (96, 0), (256, 256), (544, 32)])
+def test_quantiser_where_the_memory_ends_with_the_matrix(ah, outer, K, b):
+    """K-strided rows of no whole number of 16-byte pieces: the last one's last piece is read element by element, with one, some and
+    seven of them in it, in a tile of its own and beside whole pieces, and with K-rows behind the last one in its tile."""
+    bits = inputs.matrix(outer, K, 1.0, 9600)
+    x = ending_with_its_last_element(ah, bits)
+    say("quantiser, end of memory", outer, K, b)
+    for seed in (None, 31):
+        codes, scales = ah.adahop_iht_quantize(x, b, sr_seed=seed)
+        torch.cuda.synchronize()
+        rc, rs = orc.iht_quantize(bits, True, b, sr_seed=seed)
+        assert np.array_equal(host(scales), rs) and np.array_equal(host(codes), rc), seed
+
+
+@pytest.mark.parametrize("N,K,k", [(41, 32, 3), (263, 96, 70), (129, 1600, 130), (4097, 576, 20), (8190, 512, 180)])
+@pytest.mark.parametrize("col", [False, True])
+def test_row_and_column_product_where_the_memory_ends_with_the_matrix(ah, N, K, k, col):
+    """The same for the long operand of the BF16 product, of which a workgroup takes 128 rows (short L) or 256, in stages of 64 K-rows,
+    the last of 32 or 64.  The allowance of the module docstring."""
+    S = inputs.matrix(200, K, 1.0, 9610, row_outliers=(3, 40.0, 40.0))
+    L = inputs.matrix(N, K, 0.02, 9611)
+    idx = np.sort(np.random.default_rng(N + K).permutation(200)[:k]).astype(np.int32)
+    s, l = ah.Operand.from_bits(S, True), ending_with_its_last_element(ah, L)
+    say("row / column product, end of memory", N, K, k, col)
+    C = torch.zeros((N, 200) if col else (200, N), dtype=torch.float32, device="cuda")
+    a, b = (l, s) if col else (s, l)
+    ah.adahop_oe_gemm_bf16(a, b, inputs.IHT_OE_COL if col else inputs.IHT_OE_ROW, torch.from_numpy(idx).cuda(), C)
+    torch.cuda.synchronize()
+    got = host(C).astype(np.float64)
+    got = (got.T if col else got)[idx]
+    sf, lf = (orc.bf16_to_double(x) for x in (S[idx], L))
+    ref = sf @ lf.T
+    bar = 2.0 ** -20 * np.outer(np.linalg.norm(sf, axis=1), np.linalg.norm(lf, axis=1))
+    assert float((np.abs(got - ref) - bar).max()) <= 0.0
+
+
 # ----------------------------------------------------- extracted parts copied out by the quantisers
 
 @pytest.mark.parametrize("layouts", [(True, True), (True, False), (False, False), (False, True)])
