@@ -128,16 +128,17 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
         }
     } else {
         const int64_t l = l0 + 8 * c32, l_last = (Lo - 1) / 8 * 8; // whole 16-byte pieces: ld is a multiple of 8
-        voff_l[0] = (uint32_t)(((int64_t)k8 * ldl) * 2) + (uint32_t)((l < l_last ? l : l_last) * 2);
+        voff_l[0] = (uint32_t)(((int64_t)(k8 + EDGE) * ldl) * 2) + (uint32_t)((l < l_last ? l : l_last) * 2);
     }
     static_assert(!(EDGE && LONG_KC), "rows of a K-contiguous operand are whole pieces");
     uint4 end_piece = make_uint4(0, 0, 0, 0);
-    const bool last_piece = EDGE && l0 + 8 * c32 >= Lo / 8 * 8;
-    if (last_piece) end_piece = load_part16(L + (K - 1) * ldl + Lo / 8 * 8, (int)(Lo & 7));
+    int end_row = -1; // the K-row whose piece this lane must not read (selects, no branches: see below)
+    if (EDGE && l0 + 8 * c32 >= Lo / 8 * 8) {
+        end_piece = load_part16(L + (K - 1) * ldl + Lo / 8 * 8, (int)(Lo & 7));
+        end_row = (int)K - 1;
+    }
     // whether piece i of a stage is that piece (kk0: the stage's first K-row)
-    auto is_end = [&](int64_t kk0, int i) {
-        return last_piece && kk0 + k8 + (kk0 + SK_KSTAGE > K ? (KPP * i) & 31 : KPP * i) == K - 1;
-    };
+    auto is_end = [&](int64_t kk0, int i) { return (int)kk0 + k8 + (kk0 + SK_KSTAGE > K ? (KPP * i) & 31 : KPP * i) == end_row; };
 
     // A stage past the end of the slice (the loop below works on pairs of stages) reads the slice's last stage
     // again with the Sg side cleared.  No branches: the loop body stays one block, which the interleaving of
@@ -167,8 +168,8 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             if constexpr (LONG_KC)
                 fl[i] = load_once16(Lb + kk0 * 2 + (voff_l[i] - back));
             else
-                fl[i] = load_once16(Lb + (kk0 + (half ? (KPP * i) & 31 : KPP * i)) * ldl * 2 + voff_l[0] -
-                                    (EDGE && is_end(kk0, i) ? 2 * ldl : 0));
+                fl[i] = load_once16(Lb + (kk0 - EDGE + (half ? (KPP * i) & 31 : KPP * i)) * ldl * 2 +
+                                    (voff_l[0] - (EDGE && is_end(kk0, i) ? (uint32_t)(2 * ldl) : 0u)));
         }
     };
     auto stash = [&](int stage, uint16_t *buf, const uint4 (&fs)[RT], const uint4 (&fl)[NL], uint32_t keep, auto quarter) {
@@ -186,8 +187,14 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             if constexpr (LONG_KC)
                 *reinterpret_cast<uint4 *>(sL + (r32 + 32 * i) * SK_PITCH + c8 * 8) = fl[i];
             else
-                *reinterpret_cast<uint4 *>(sL + (k8 + KPP * i) * SK_TPITCH + 8 * c32) =
-                    EDGE && is_end(first_row(stage), i) ? end_piece : fl[i];
+            {
+                uint4 v = fl[i];
+                if constexpr (EDGE) {
+                    const bool end = is_end(first_row(stage), i);
+                    v = make_uint4(end ? end_piece.x : v.x, end ? end_piece.y : v.y, end ? end_piece.z : v.z, end ? end_piece.w : v.w);
+                }
+                *reinterpret_cast<uint4 *>(sL + (k8 + KPP * i) * SK_TPITCH + 8 * c32) = v;
+            }
         }
     };
     typedef std::integral_constant<int, -1> all_t;
