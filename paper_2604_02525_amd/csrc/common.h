@@ -116,7 +116,7 @@ int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uin
                          const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
                          const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);
 int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us); // the variant for a shape and its expected time
-// Diagnostics: 0 = choose by shape, 1 = always the 256 x 256 kernel, 2 = the 256 x 128 kernel wherever it can run,
+// Diagnostics: 0 = choose by shape, 1 = the 256 x 256 kernel and 2 = the 256 x 128 kernel, each wherever it can run,
 // 3 .. 6 = by shape with a forced tile walk, 7 .. 11 = a variant of the kernel with small tiles.
 void gemm_mx_force_kernel(int which);
 int launch_gather_k(const adahop_operand_t &x, const int32_t *idx, int k, int kpad, uint16_t *out, hipStream_t st);

@@ -203,8 +203,8 @@ __global__ __launch_bounds__(256) void k_mark(const int32_t *__restrict__ idx, i
     if (t < k) mask[idx[t]] = 1;
 }
 
-// The table of positions where the selection does not write it (k_topk reads its scores, where the table may lie, to the end): the first dim threads clear the entries of what stays, the next k set
-// those of what is extracted: no entry is written twice.
+// The table of positions where the selection does not write it (k_topk reads its scores, where the table may lie, to the end): the first
+// dim threads clear the entries of what stays, the next k set those of what is extracted; no entry is written twice.
 __global__ __launch_bounds__(256) void k_positions(const int32_t *__restrict__ idx, int k, const uint8_t *__restrict__ mask,
                                                    int64_t dim, uint16_t *__restrict__ pos1)
 {

@@ -17,15 +17,15 @@ constexpr int TOPK_THREADS = 1024, TOPK_WAVES = TOPK_THREADS / 64; // of the ker
 // a version of this kernel with the keys in registers and every loop unrolled spent most of its 12-18 us there) and,
 // second, the number of passes over all keys.  So every pass is a rolled loop over keys in LDS, the select and the
 // compaction exist once each (they run over a list described by a few numbers), and the passes over all keys are light:
-//   1. every thread takes the maximum of the keys it loads; the k-th largest of these 1024 maxima, cut down to its
+//   1. every thread takes the maximum of the keys it loads; the k-th largest of these NT maxima, cut down to its
 //      upper 16 bits (two radix passes over ONE value per thread), is a threshold T0 that at least k keys reach -- so
 //      the k largest keys, and every key tied with the k-th, are among the keys >= T0 -- and that few others reach
 //      (about 1.2 k of them for scores without structure).  With fewer than k threads that own a key the threshold
 //      comes out as 0 and step 2 finds too many candidates, which is handled there;
 //   2. the keys >= T0 are counted per wave and then copied, with their indices, to a list in index order (a compare
 //      per key in each of the two passes);
-//   3. radix select and ordered compaction run over this list (at most two entries per thread).
-// If k > 1024, or more than TOPK_CAND keys reach T0, or there are no more keys than four per thread, the list is
+//   3. radix select and ordered compaction run over this list (at most TOPK_CAND / NT entries per thread).
+// If k > NT, or more than TOPK_CAND keys reach T0, or there are no more keys than four per thread, the list is
 // the keys themselves.
 constexpr int TOPK_LDS_KEYS = 32768;
 constexpr int TOPK_CAND = 2048;

@@ -11,10 +11,12 @@
 //   - WK waves share a part of C and take the four matrix-core steps of every stage between them (WK = 2: two steps
 //     each, WK = 4: one); their sums are added through LDS at the end, in wave order.  A tile of 64 x 64 by four waves then reads
 //     every operand byte from LDS once, and four times as many workgroups share a product of few tiles;
-//   - NST stages of 256 K-elements rotate in LDS, NST - 1 of them on the way: such a product is bound by the latency of
+//   - NST stages of 256 K-elements rotate in LDS, NST - PU of them on the way: such a product is bound by the latency of
 //     its operands (a tile's own share of the copy rate is 64 bytes per cycle and compute unit, reached with 64 .. 96 KiB
-//     in flight), not by the matrix cores.  One barrier per stage, at its head: the stage has landed (a counted
-//     wait for all but the copies of the younger stages) and every wave has left the buffer that is refilled next;
+//     in flight), not by the matrix cores.  One barrier per PU stages, at the head of the first: they have landed (a counted
+//     wait for all but the copies of the younger stages) and every wave has left the buffers that are refilled next.  PU is 1, and 2
+//     for 32 x 32, where a wave has one matrix-core instruction per stage and a barrier for each would be most of its time; NST =
+//     1 is for products of a single stage;
 //   - rows past the end of an operand repeat its last row and are not stored.  A last stage of K that is no multiple of
 //     256 starts at K - 256 as in the 256 x 256 kernel, its leading blocks with scale 0; of a K below 256 the missing
 //     blocks are the first block again, with scale 0.

@@ -23,13 +23,13 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // OE-col) and L the other, "long" operand, both products are  P[t, l] = sum_kk S(idx[t], kk) L(l, kk),
 // a skinny product: a few hundred rows against a whole operand, bound by reading L once.
 //
-//   1. k_gather_rows   copies the extracted rows into a K-contiguous staging matrix Sg, zero padded to
-//                      whole 32-row matrix-core tiles;
-//   2. k_oe_skinny     workgroup = (RT x 32 rows of Sg) x (256 rows of L) x (one slice of K), a wave = all the rows
-//                      of Sg x 64 rows of L.  Stages of 64 K-elements travel memory -> registers -> LDS; two are
+//   1. the operand's quantiser (quantize.hip), or k_gather_rows, copies the extracted rows into a K-contiguous staging
+//                      matrix Sg of whole 32-row matrix-core tiles; rows past the k extracted ones may hold anything;
+//   2. k_oe_skinny     workgroup = (RT x 32 rows of Sg) x (128 NCW rows of L) x (one slice of K), a wave = all the rows
+//                      of Sg x 32 NCW rows of L.  Stages of 64 K-elements travel memory -> registers -> LDS; two are
 //                      on their way in registers while a third is multiplied from one LDS buffer and a fourth is
 //                      being written into the other (one barrier per stage).  Sg and a K-contiguous L lie in LDS
-//                      as [row][64 K]; a K-strided L lies there as it lies in memory, [K][256 rows], and the
+//                      as [row][64 K]; a K-strided L lies there as it lies in memory, [K][128 NCW rows], and the
 //                      transposing LDS read hands the matrix cores their 8 consecutive K-elements of a row.  K
 //                      is split over workgroups so that the chip is full although there are few tiles; every
 //                      slice writes its own partial tile (no atomics: the result does not depend on scheduling);
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     P += ((int64_t)blockIdx.y * rows_all + (int64_t)blockIdx.z * RT * 32) * Lo;
 
     // loader geometry.  [row][K] sources: 16-byte chunk c8 of rows r32 + 32 i.  K-strided L: chunk c32 (8 rows of
-    // L) of K-rows k8 + 8 i, so that a wave reads two whole 512-byte pieces of K-rows.  Every address is a base that
+    // L) of K-rows k8 + 8 i (16 i with NCW = 1), so that a wave reads whole pieces of K-rows.  Every address is a base that
     // is the same for the whole workgroup plus a 32-bit byte offset of the lane (the offsets stay below 2^31: at most
     // 256 rows of at most 2^21 elements).  Rows of L past the end are replaced by the last row (their results are
     // not stored); in a last stage of 32 K-elements the upper half reads the lower half again and the Sg side is

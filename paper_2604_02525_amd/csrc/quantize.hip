@@ -975,7 +975,7 @@ int launch_topk(int b, const topk_job_t &t, quant_kind_t kind, const quant_t &q,
 // The copy of a row's extracted channels is staged in LDS.
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad)
 {
-    return x.k_contig && kpad <= KC_GATHER_MAX_KPAD && kpad % 8 == 0 && x.outer <= 0x7fffffff;
+    return x.k_contig && kpad <= KC_GATHER_MAX_KPAD;
 }
 
 int launch_iht_quantize(int b, const quant_job_t &job, hipStream_t st)

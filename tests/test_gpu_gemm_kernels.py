@@ -216,11 +216,13 @@ def test_small_tiles_with_k_channels(ah, force, kernel, M, N, K, k):
     check_c(host(out["C"]), ref["C"], inputs.Gemm("small", A, B, inputs.IHT_OE_K, 32, k), extracted=ref["idx"], tol=1e-5)
 
 
-@pytest.mark.parametrize("kernel", [0, TILE256])
+@pytest.mark.parametrize("kernel", [0, TILE256, DUAL])
 @pytest.mark.parametrize("M,N,K,k,gap", [(2305, 1027, 4096, 0, 0), (2048, 2048, 2048, 0, 1), (1024, 1001, 1024, 20, 0),
-                                         (300, 130, 2080, 0, 3)])
+                                         (300, 130, 2080, 0, 3), (520, 200, 2304, 100, 1)])
 def test_bf16_output_of_any_alignment(ah, force, kernel, M, N, K, k, gap):
-    """Widths and row strides that are no multiples of 16 bytes: the bits of the fp32 product rounded to nearest even."""
+    """Widths and row strides that are no multiples of 16 bytes: the bits of the fp32 product rounded to nearest even.  Chosen by shape
+    these products are taken by small tiles for either type; with the two-set kernel forced, which has no bf16 form, the bf16 product goes to
+    the 256 x 256 tiles, or with N < 256 to 128 x 128 tiles, and is compared with the fp32 product of the two-set kernel."""
     A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 90, col_outliers=(5, 50.0, 50.0)), True)
     B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 91), True)
     say("bf16 output of any alignment", kernel, (M, N, K, k, gap))

@@ -134,10 +134,11 @@ def test_whole_path_with_stochastically_rounded_gradient_operand(ah, strategy, k
     assert torch.equal(det["b_codes"], out["b_codes"]) and not torch.equal(det["a_codes"], out["a_codes"])
 
 
-def test_stochastic_rounding_in_the_quantiser_that_copies_k_channels(ah):
-    """OE-K on K-contiguous operands with K a whole number of 4096-element passes takes the quantiser that also
-    copies the extracted channels out; its stochastic-rounding instance must draw as every other quantiser does."""
-    M, N, K, k, b = 136, 72, 4096, 37, 128
+@pytest.mark.parametrize("K,k,b", [(4096, 37, 128), (288, 9, 32), (4384, 70, 32)])
+def test_stochastic_rounding_in_the_quantiser_that_copies_k_channels(ah, K, k, b):
+    """OE-K on K-contiguous operands takes the quantiser that also copies the extracted channels out, one row per workgroup and several, K
+    a whole number of 256-element units and not; its stochastic-rounding instance must draw as every other quantiser does."""
+    M, N = 136, 72
     A = inputs.Operand(inputs.matrix(M, K, 1.0, 720, col_outliers=(12, 40.0, 80.0)), True)
     B = inputs.Operand(inputs.matrix(N, K, 0.02, 721), True)
     say("whole path, SR on both operands, channels copied by the quantiser")
@@ -152,3 +153,31 @@ def test_stochastic_rounding_in_the_quantiser_that_copies_k_channels(ah):
     say(f"  vs oracle {err:.2e}")
     assert err < 1e-3
 
+
+@pytest.mark.parametrize("K,b", [(512, 256), (544, 32), (96, 32)])
+@pytest.mark.parametrize("layouts", [(True, False), (False, True), (False, False)])
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+def test_stochastic_rounding_in_the_quantiser_that_copies_rows(ah, strategy, layouts, K, b):
+    """The rounded operand is the one that rows / columns are extracted from, and its quantiser copies them out: K-contiguous and K-strided, K
+    a whole number of 256-element units and not.  With the indices handed in, so that a kernel of its own gathers them, C has the same bits."""
+    M, N, k = 131, 72, 5
+    A = inputs.matrix(M, K, 1e-3, 730, row_outliers=(4, 100.0, 100.0))
+    B = inputs.matrix(N, K, 0.02, 731, row_outliers=(4, 50.0, 50.0))
+    say("SR, rows copied by the quantiser", inputs.STRATEGY_NAMES[strategy], layouts, K, b)
+    ops, host_ops = [], []
+    for bits, kc in ((A, layouts[0]), (B, layouts[1])):
+        arr = bits if kc else np.ascontiguousarray(bits.T)
+        wide = np.zeros((arr.shape[0], (arr.shape[1] + 7) // 8 * 8), dtype=np.uint16)
+        wide[:, :arr.shape[1]] = arr
+        ops.append(ah.Operand(torch.from_numpy(wide.view(np.int16)).cuda()[:, :arr.shape[1]], kc))
+        host_ops += [arr, kc]
+    seeds = dict(sr_seed_a=77) if strategy == inputs.IHT_OE_ROW else dict(sr_seed_b=78)
+    out = ah.adahop_gemm(*ops, strategy, b, k, **seeds)
+    again = ah.adahop_gemm(*ops, strategy, b, k, idx=out["idx"].clone(), **seeds)
+    torch.cuda.synchronize()
+    ref = orc.adahop_gemm(*host_ops, strategy, b, k, **seeds)
+    for name in ("a_scales", "b_scales", "a_codes", "b_codes"):
+        assert np.array_equal(host(out[name]), ref[name]), name
+    assert np.array_equal(np.sort(host(out["idx"])), ref["idx"])
+    assert torch.equal(out["C"].view(torch.int32), again["C"].view(torch.int32))
+    assert np.linalg.norm(host(out["C"]).astype(np.float64) - ref["C"]) / np.linalg.norm(ref["C"]) < 1e-3
