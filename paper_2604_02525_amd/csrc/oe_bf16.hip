@@ -148,13 +148,15 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     // QUARTER = -1: all of them.
     // (The clearing of the Sg side happens when the registers are written to LDS, stage_keep below: touching a
     // loaded value here would make the wave wait for the load it has just issued.)
-    auto first_row = [&](int stage) { return (int64_t)(stage >= s1 ? s1 - 1 : stage) * SK_KSTAGE; };
     auto stage_keep = [&](int stage) -> uint32_t {
-        return (stage >= s1 || (first_row(stage) + SK_KSTAGE > K && c8 >= 4)) ? 0u : 0xffffffffu;
+        const bool ghost = stage >= s1;
+        const int64_t kk0 = (int64_t)(ghost ? s1 - 1 : stage) * SK_KSTAGE;
+        return (ghost || (kk0 + SK_KSTAGE > K && c8 >= 4)) ? 0u : 0xffffffffu;
     };
     auto fetch = [&](int stage, uint4 (&fs)[RT], uint4 (&fl)[NL], auto quarter) {
         constexpr int Q = decltype(quarter)::value;
-        const int64_t kk0 = first_row(stage);
+        const bool ghost = stage >= s1;
+        const int64_t kk0 = (int64_t)(ghost ? s1 - 1 : stage) * SK_KSTAGE;
         const bool half = kk0 + SK_KSTAGE > K; // K is a multiple of 32: the last stage may hold 32 K-elements
         const uint32_t back = half && c8 >= 4 ? 64u : 0u;
 #pragma unroll
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
             {
                 uint4 v = fl[i];
                 if constexpr (EDGE) {
-                    const bool end = is_end(first_row(stage), i);
+                    const bool end = is_end((int64_t)(stage >= s1 ? s1 - 1 : stage) * SK_KSTAGE, i);
                     v = make_uint4(end ? end_piece.x : v.x, end ? end_piece.y : v.y, end ? end_piece.z : v.z, end ? end_piece.w : v.w);
                 }
                 *reinterpret_cast<uint4 *>(sL + (k8 + KPP * i) * SK_TPITCH + 8 * c32) = v;
