@@ -429,7 +429,7 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const uint8_t *b_codes = b_given ? opts->b_codes : reinterpret_cast<uint8_t *>(ws + L.b_codes);
     const uint8_t *b_scales = b_given ? opts->b_scales : reinterpret_cast<uint8_t *>(ws + L.b_scales);
     // The GEMM kernels read the scales in a stage-major copy; the quantisers that run here write it
-    // beside the canonical one, which saves the product its two re-ordering launches.
+    // beside the canonical one, which saves the product its re-ordering launch.
     uint16_t *gather_a = reinterpret_cast<uint16_t *>(ws + L.gather_a), *gather_b = reinterpret_cast<uint16_t *>(ws + L.gather_b);
     const k_gather_t no_k = {nullptr, nullptr, 0, 0};
     const row_gather_t no_rows = {nullptr, nullptr}, rows = {pos1, gather_a}; // (the row / column product has one workspace)

@@ -20,8 +20,8 @@
 //   - rows past the end of an operand repeat its last row and are not stored.  A last stage of K that is no multiple of
 //     256 starts at K - 256 as in the 256 x 256 kernel, its leading blocks with scale 0; of a K below 256 the missing
 //     blocks are the first block again, with scale 0.
-//   - what it replaced, a kernel that read its operands straight from global memory, took 420 us on 128 x 1248 x 28672 (now 28),
-//     63 us on 128 x 11008 x 4096 (15) and 78 us on 4096 x 11008 x 512 (50); 256 rows of 4096 x 4096 took 13.4 us in tiles of
+//   - what it replaced, a kernel that read its operands straight from global memory, took 420 us on 128 x 1248 x 28672 (now 19),
+//     63 us on 128 x 11008 x 4096 (10) and 78 us on 4096 x 11008 x 512 (40); 256 rows of 4096 x 4096 took 13.4 us in tiles of
 //     256 x 128 (now 7.8);
 //   - the scales come from the stage-major copy or, where K % 256 == 0, straight from the canonical array (8 bytes per row
 //     and stage: two 4-byte copies), which saves a product of packed operands the launch that re-orders them; up to
@@ -490,8 +490,9 @@ typedef variant_t<1, 2, 1, 1, 4, 4, 1> v32x64_t;  // 32 x 64
 typedef variant_t<1, 1, 1, 1, 4, 8, 2> v32_t;     // 32 x 32
 
 // What a variant takes, in us: start + stages max(alone, busy L) + tile L, L = tiles on the fullest of the 256 compute units.
-// Fitted on MI355X to 330 products (16 .. 4096 rows, 320 .. 20000 columns, K 512 .. 28672; mean error 8 .. 15 %); the choice that
-// the figures give is within 2 % of the fastest variant in the geometric mean over them.
+// Fitted on MI355X to 330 products (16 .. 4096 rows, 320 .. 20000 columns, K 512 .. 28672; mean error 8 .. 15 %).  On 240 others
+// (profiles/gemm_mx_kernel_choice.txt: 16 .. 8192 rows, K 256 .. 28672, every variant's time) the estimate of the chosen variant is off by 10 % in
+// the mean, and the choice is 0.9 % behind the fastest variant in the geometric mean, 19 % at worst.
 struct cost_t {
     int tm, tn;
     double start, alone, busy, tile;

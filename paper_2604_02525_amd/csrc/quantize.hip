@@ -986,10 +986,14 @@ int launch_iht_quantize(int b, const quant_job_t &job, hipStream_t st)
     return launch_one(b, job.sr_seed != nullptr, kind, q, st);
 }
 
-// Operands of up to 64 M elements together share a launch: 16.8 -> 12.9 us on 8192 x 2048 with 2048 x 2048 (K-contiguous),
-// 27.0 -> 25.3 on 8192 x 4096 with 4096 x 4096, K-strided 24.3 -> 20.4 and 39.2 -> 37.4.  A K-contiguous operand beside a K-strided
-// one runs with the registers and the LDS of the latter, half as many waves per compute unit: 17.5 -> 16.9 us on 8192 x 2048 with
-// 2048 x 2048, but 29.2 -> 30.7 on the larger pair, so that the line lies at 24 M there.
+// Operands of up to 64 M elements together share a launch; rows of both x K, us in two launches / in one, both K-contiguous | both K-strided:
+//   2048 + 2048 x 2048 (8 M)     8.3 /  5.7 | 10.1 /  6.8      8192 +  8192 x 4096 (64 M)     35.7 / 33.1 | 40.4 / 37.2
+//   8192 + 2048 x 2048 (20 M)   16.1 / 11.7 | 16.3 / 12.5     16384 +  8192 x 4096 (96 M)     50.1 / 47.2 | 58.7 / 59.0
+//   8192 + 4096 x 4096 (48 M)   28.0 / 25.3 | 31.8 / 27.2      8192 + 12288 x 8192 (160 M)    80.9 / 74.7 | 97.5 / 91.7
+// What is gained is a launch and its gap, whatever the size; the line lies where every measured pair gains.  A K-contiguous operand beside a
+// K-strided one runs with the registers and the LDS of the latter, half as many waves per compute unit: 8 M 8.8 / 6.7 us, 20 M 16.9 /
+// 15.7, 4096 + 4096 x 3040 (24 M) 16.9 / 17.1, 48 M 29.7 / 30.7, 96 M 53.0 / 55.2, so that the line lies at 24 M there (one pair above it
+// still gains: 8192 + 11008 x 2048, 37.5 M, 25.3 / 23.2).
 int launch_iht_quantize_two(int b, const quant_job_t &ja, const quant_job_t &jb, hipStream_t st)
 {
     quant_t qa, qb;
@@ -1021,7 +1025,12 @@ int configure_iht_quantize()
 // keys), but then 9 us less of everything else: 9 + 31 -> 16 + 19 us for 8192 x 4096 beside a K-strided 4096 x 4096, 9 + 44 -> 22 +
 // 24 for two K-strided operands of 8192 tokens x 4096.  Not for operands that are rounded stochastically (no such instance) or whose
 // K-strided order is a special one, and above 64 M elements only where the keys fit into the LDS that every workgroup of the
-// launch has anyway: more of it costs waves in flight.
+// launch has anyway: more of it costs waves in flight.  Whole calls with 1 % of the rows extracted (M x N x K), selection first / beside, the
+// other operand K-strided | K-contiguous:
+//   8192 x 4096 x 4096 (16 M)    132.8 / 128.4 | 130.4 / 128.2      8192 x  8192 x 8192 (64 M)   380.7 / 372.9 | 373.4 / 375.1
+//   4096 x 11008 x 4096 (43 M)   173.6 / 163.0 | 170.6 / 164.7      8192 x 12288 x 8192 (96 M)   511.6 / 504.2 | 502.6 / 509.2
+// and columns, 4096 x 4096 x 32768 (128 M, K-strided), 444.5 / 436.1.  An operand that is done before the selection gains nothing:
+// 8192 x 2048 x 2048 71.1 / 69.9 | 67.1 / 69.4.
 bool topk_beside_quant(int64_t dim, const quant_job_t &job)
 {
     quant_t q;
