@@ -106,8 +106,15 @@ template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool PRE> s
 //   24515 x 9536 x 320 (891 MB)            234 / 249 / 214      8192 x 16384 x 1024           231 / 166 / 190
 //   6000 x 9001 x 64 (206 MB, ldc 9001)     47 /  47 /  43      30000 x 4096 x 512 (468 MB)    116 / 118 / 147
 //   4001 x 12001 x 512 (183 MB, ldc 12001)  47 /  53 /  49      4096 x 11008 x 512 (172 MB)     40 /  42 /  44
+// Below those lines, along the rows in runs from 24 MB of C and 16 rows of tiles on, for K up to 192, off the 64-byte grid 512: as much is shared as down the columns, and the
+// pieces of C's lines meet in one L2.  Down / along in runs: 10911 x 2828 x 64 (118 MB) 29.2 / 26.9, 5345 x 8125 x 384 (166 MB)
+// 52.1 / 44.1, 9187 x 2427 x 320 (85 MB) 27.5 / 24.9, 4096 x 2048 x 64 (32 MB) 10.8 / 9.7, 6374 x 2200 x 64 in bf16 (27 MB) 14.8 / 11.7,
+// 2743 x 11808 x 192 (124 MB) 30.0 / 28.6; fewer rows of tiles do not spread over the XCDs: 1158 x 6892 x 64 11.1 / 11.6, 1356 x 12198 x 192
+// 19.8 / 20.3.  On the grid, where two tiles share no line, more K takes it back: 3378 x 10976 x 512 (141 MB) 32 / 38, and of the lines above
+// 3360 x 11416 x 256 (146 MB, ldc 11424) 28 / 31.
 enum walk_t { DOWN = 0, ALONG_ROWS = 1, RUNS = 2 };
-constexpr int64_t C_STAYS = 192ll << 20, C_STAYS_SHORT = 136ll << 20; // bytes of C; the latter for K <= 256
+constexpr int64_t C_STAYS = 192ll << 20, C_STAYS_SHORT = 136ll << 20; // bytes of C; the latter for K <= 192, off the 64-byte grid 256
+constexpr int64_t C_ALONG = 24ll << 20;
 
 template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU, bool PRE, bool OEK, typename OUT>
 __global__ __launch_bounds__(256, NST == 1 ? 4 : 2) void k_gemm_mx_small(int64_t K, const uint8_t *__restrict__ a_codes, scale_src_t a_sc,
@@ -454,10 +461,13 @@ template <int TMB, int TNB, int WM, int WN, int WK, int NST, int PU> struct vari
         typedef shape_t<TMB, TNB, WM, WN, WK, NST, PU, PRE> S;
         const int64_t tm = ceil_div(M, S::TM), tn = ceil_div(N, S::TN);
         const dim3 grid((unsigned)(tm * tn));
-        const bool leaves = M * N * (int64_t)sizeof(OUT) >= (K <= 256 ? C_STAYS_SHORT : C_STAYS);
+        const int64_t c_bytes = M * N * (int64_t)sizeof(OUT);
+        const bool off = !c_rows_streamed(C, ldc * (int64_t)sizeof(OUT)); // rows off the 64-byte grid
+        const bool leaves = c_bytes >= (K <= 192 || (K <= 256 && off) ? C_STAYS_SHORT : C_STAYS);
+        const bool stores = c_bytes >= C_ALONG && tm >= 16 && K <= (off ? 512 : 192);
         const int64_t whole = NST == 1 && sizeof(OUT) == 4 ? 64 : 4096;
-        const int walk = !leaves ? DOWN | RUNS : ldc * (int64_t)sizeof(OUT) % whole == 0 ? ALONG_ROWS : ALONG_ROWS | RUNS;
-        const int fast = (int)(leaves ? tn : tm);
+        const int walk = leaves ? (ldc * (int64_t)sizeof(OUT) % whole == 0 ? ALONG_ROWS : ALONG_ROWS | RUNS) : stores ? ALONG_ROWS | RUNS : DOWN | RUNS;
+        const int fast = (int)(walk & ALONG_ROWS ? tn : tm);
         if constexpr (NST > 1) {
             if (kpad > 0) {
                 hipLaunchKernelGGL((k_gemm_mx_small<TMB, TNB, WM, WN, WK, NST, PU, PRE, true, OUT>), grid, dim3(256), S::LDS, st, K, a, as, b,

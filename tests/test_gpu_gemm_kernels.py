@@ -178,10 +178,12 @@ def test_small_tiles(ah, force, kernel, shape):
 
 @pytest.mark.parametrize("M,N,K,ld,dtype", [(4250, 8450, 96, 8452, torch.float32), (4250, 8450, 192, 8464, torch.float32),
                                             (8400, 8500, 64, 8501, torch.bfloat16), (6200, 8150, 288, 8192, torch.float32),
-                                            (6200, 8150, 480, 8151, torch.float32), (4000, 3900, 32, 3901, torch.float32)])
+                                            (6200, 8150, 480, 8151, torch.float32), (4000, 3900, 32, 3901, torch.float32),
+                                            (1930, 3300, 32, 3301, torch.float32), (1800, 3900, 64, 3900, torch.float32),
+                                            (3400, 3750, 512, 3752, torch.bfloat16)])
 def test_short_products_with_a_large_c(ah, M, N, K, ld, dtype):
     """The orders in which tiles are walked where C is larger than the Infinity Cache (rows of whole pages, of whole 64-byte pieces and of
-    neither), with the 128 x 128 tiles of a single stage of K and of more: rows at every tile's edges against the oracle, and the gap behind
+    neither) and where it is larger than 24 MB, with the 128 x 128 tiles of a single stage of K and of more: rows at every tile's edges against the oracle, and the gap behind
     the rows as it was.  The allowance is the one above, plus half a bf16 step."""
     rng = np.random.default_rng(M + N + K)
     a_codes = rng.integers(0, 256, size=(M, K // 2), dtype=np.uint8)
