@@ -411,8 +411,29 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // gather of a K-contiguous operand (4096 x 4096 x 65536, 655 channels: the whole call 4 % faster).  That of rows and columns lies where the bf16 product keeps its partial sums,
     // which nobody writes before the quantisers are done: a caller finds the scores in the workspace afterwards.  Where it does not fit
     // there (more than 128 rows to choose from for each of the other operand's), the rows are gathered by themselves.
+    const bool oe_rc = oe && !oe_k;
+    const bool from_a = strategy == ADAHOP_IHT_OE_ROW; // (row / column extraction: of which operand)
+    const adahop_operand_t &short_op = from_a ? *A : *B, &long_op = from_a ? *B : *A;
+    outlier_job_t outliers = {};
+    // Row and column extraction: the bf16 products are formed by the quantiser of the other operand where that is K-strided
+    // (k_quant_ks16_outliers), whether the indices are selected here or given.  Where that operand comes packed, or is rounded stochastically, the
+    // same kernel forms them without quantising, up to a size at which it is as fast as the kernel for the products alone (41 rows x 11008 x 2016 13.7 /
+    // 14.5 us, 82 x 4096 x 4096 15.5 / 14.6, 33 x 512 x 4096 6.5 / 7, but 54 x 8192 x 5024, whole call, 229 / 225, 64 x 4096 x 32768 73 / 50):
+    // a product has the same bits then, packed operands or not.
+    const bool short_given = from_a ? a_given : b_given, long_given = from_a ? b_given : a_given;
+    const bool products_only = long_given || (opts && (from_a ? opts->sr_b : opts->sr_a));
+    bool on_the_way = oe_rc && !long_op.k_contig && (!products_only || long_op.outer * K <= 32ll << 20) &&
+                      oe_rowcol_on_the_way(long_op.outer, K, k, &outliers);
+    // Where that quantiser then has to wait for a selection that could stand beside it, and so does that of the operand of the
+    // extracted rows, it takes some work for that to pay: 416 x 4096 (128 tiles), 55 columns, whole call 45 us beside, 48 on the way; 32 x 1440
+    // (23) 36.9 / 38.1; 96 x 8992 (141) 78.7 / 79.3; 32 x 17376 (272) 52.7 / 49.5; 32 x 20608 (322) 77.2 / 74.3.
+    if (on_the_way && !short_op.k_contig && iht_quantize_beside_topk(dim, long_op) && ceil_div(long_op.outer, 64) * ceil_div(K, 256) < 192)
+        on_the_way = false;
+    // ... and where they are rows of a K-contiguous operand, it reads them where they are
+    const bool in_place = on_the_way && short_op.k_contig;
     uint16_t *pos1 = nullptr;
-    if (oe && !use_given_idx && k <= 0xffff && (oe_k || foid_writes_positions(dim))) {
+    size_t partials = 0;
+    if (oe && !use_given_idx && !in_place && k <= 0xffff && (oe_k || foid_writes_positions(dim))) {
         size_t room = (size_t)dim * sizeof(float);
         pos1 = oe_k ? reinterpret_cast<uint16_t *>(scores)
                     : reinterpret_cast<uint16_t *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &room));
@@ -433,20 +454,43 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     uint16_t *gather_a = reinterpret_cast<uint16_t *>(ws + L.gather_a), *gather_b = reinterpret_cast<uint16_t *>(ws + L.gather_b);
     const k_gather_t no_k = {nullptr, nullptr, 0, 0};
     const row_gather_t no_rows = {nullptr, nullptr}, rows = {pos1, gather_a}; // (the row / column product has one workspace)
-    const quant_job_t ja = {A, a_kind == 1 ? mask : nullptr, a_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.a_codes),
+    const bool unmasked = in_place && !use_given_idx; // (the extracted rows are set to zero afterwards)
+    const quant_job_t ja = {A, a_kind == 1 && !unmasked ? mask : nullptr, a_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.a_codes),
                             reinterpret_cast<uint8_t *>(ws + L.a_scales), opts && opts->sr_a ? &opts->sr_seed_a : nullptr,
                             {gemm_mx_scales_sm(ws + L.gemm, M, K, 0), M},
                             a_gathers_k ? k_gather_t{pos1, gather_a, k, kpad_planned} : no_k, a_gathers_rows ? rows : no_rows};
-    const quant_job_t jb = {B, b_kind == 1 ? mask : nullptr, b_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.b_codes),
+    const quant_job_t jb = {B, b_kind == 1 && !unmasked ? mask : nullptr, b_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.b_codes),
                             reinterpret_cast<uint8_t *>(ws + L.b_scales), opts && opts->sr_b ? &opts->sr_seed_b : nullptr,
                             {gemm_mx_scales_sm(ws + L.gemm, M, K, 1), N},
                             b_gathers_k ? k_gather_t{pos1, gather_b, k, kpad_planned} : no_k, b_gathers_rows ? rows : no_rows};
     // Row and column extraction: the operand that nothing is extracted from does not wait for the selection, one workgroup of
     // which the rest of the chip would watch (9 us for 8192 rows); its quantiser runs beside it.
-    const quant_job_t &free_job = strategy == ADAHOP_IHT_OE_ROW ? jb : ja, &masked_job = strategy == ADAHOP_IHT_OE_ROW ? ja : jb;
-    const bool beside = oe && !oe_k && !use_given_idx && !a_given && !b_given && topk_beside_quant(dim, free_job);
-    if (beside) {
-        const topk_job_t topk = {scores, (int)dim, k, idx_inout, mask, pos1};
+    const quant_job_t &free_job = from_a ? jb : ja, &masked_job = from_a ? ja : jb;
+    const bool beside = !on_the_way && oe_rc && !use_given_idx && !a_given && !b_given && topk_beside_quant(dim, free_job);
+    const topk_job_t topk = {scores, (int)dim, k, idx_inout, mask, pos1};
+    if (on_the_way) {
+        // The quantiser of the other operand needs the selection; where the extracted rows are read in place, that of the operand they
+        // come from does not: it takes them along, and their codes and scales are set to zero behind it.
+        if (unmasked && topk_beside_quant(dim, masked_job)) {
+            rc = launch_foid_scores(short_op, 0, scores, st);
+            if (rc == ADAHOP_OK) rc = launch_topk_beside_quant(topk, b, masked_job, st);
+        } else {
+            if (!use_given_idx)
+                rc = launch_foid_topk(short_op, 0, k, idx_inout, mask, scores, st, pos1);
+            else if (!short_given)
+                rc = launch_mask_from_idx(idx_inout, k, mask, dim, st);
+            if (rc == ADAHOP_OK && !short_given) rc = launch_iht_quantize(b, masked_job, st);
+            if (rc == ADAHOP_OK && !in_place && !masked_job.gr.out) rc = launch_gather_rows(short_op, idx_inout, k, gather_a, st);
+        }
+        outliers.rows = in_place ? static_cast<const uint16_t *>(short_op.data) : gather_a;
+        outliers.ld = in_place ? short_op.ld : K;
+        outliers.idx = in_place ? idx_inout : nullptr;
+        outliers.p = reinterpret_cast<float *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &partials));
+        if (unmasked) outliers.codes = masked_job.codes, outliers.scales = masked_job.scales, outliers.sm = masked_job.sm;
+        if (rc == ADAHOP_OK && products_only && !long_given) rc = launch_iht_quantize(b, free_job, st);
+        if (rc == ADAHOP_OK) rc = launch_iht_quantize_outliers(products_only ? -1 : b, free_job, outliers, st);
+        if (rc != ADAHOP_OK) return rc;
+    } else if (beside) {
         rc = launch_foid_scores(*masked_job.x, 0, scores, st);
         if (rc == ADAHOP_OK) rc = launch_topk_beside_quant(topk, b, free_job, st);
         if (rc == ADAHOP_OK) rc = launch_iht_quantize(b, masked_job, st);
@@ -465,7 +509,7 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
         if (rc != ADAHOP_OK) return rc;
     }
     const int sm_ready = oht ? 0 : (a_given ? 0 : 1) | (b_given ? 0 : 2);
-    if (beside) {
+    if (beside || on_the_way) {
         ;
     } else if (oht) {
         if (!a_given) rc = launch_oht_quantize(*A, b, ja.codes, ja.scales, st);
@@ -491,6 +535,8 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
                         sm_ready);
     if (rc != ADAHOP_OK) return rc;
     if (oht) return launch_oht_inverse(static_cast<float *>(C), M, N, ldc, b, st); // the rotations after the product (Eq. 6)
+    if (on_the_way)
+        return launch_oe_reduce(outliers.p, outliers.nslice, k, long_op.outer, from_a, idx_inout, k, C, ldc, c_bf16, st);
     if (oe) rc = launch_oe_rowcol(*A, *B, strategy, idx_inout, k, C, ldc, c_bf16, gather_a, st, a_gathers_rows || b_gathers_rows);
     return rc;
 }

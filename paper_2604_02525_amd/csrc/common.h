@@ -72,6 +72,22 @@ struct quant_job_t {
 };
 int launch_iht_quantize(int iht_block, const quant_job_t &job, hipStream_t st);
 int launch_iht_quantize_two(int iht_block, const quant_job_t &a, const quant_job_t &b, hipStream_t st); // both of a product
+// One K-strided operand (nothing extracted from it, rounded to nearest), and on the way its products with the k rows extracted from the
+// other one: slice s of p is [k, outer] and holds the sums over the 256-element blocks s, s + nslice, ... of K.
+struct outlier_job_t {
+    const uint16_t *rows; // extracted row t begins at rows + (idx ? idx[t] : t) * ld
+    int64_t ld;
+    const int32_t *idx;
+    float *p;
+    int k, tiles, nslice; // tiles: of 16 rows
+    // the rows idx[t] of the other operand's codes and scales, to be set to zero (codes = nullptr: they are)
+    uint8_t *codes, *scales;
+    scales_sm_t sm;
+};
+constexpr int OUTLIER_TILES = 6; // at most
+bool iht_quantize_takes_outliers(int tiles);
+// iht_block = -1: the products without the quantisation.
+int launch_iht_quantize_outliers(int iht_block, const quant_job_t &job, const outlier_job_t &e, hipStream_t st);
 // The selection from `scores` (launch_foid_scores) in the first workgroup of a launch whose others quantise an operand that does
 // not depend on it; topk_beside_quant says whether that can be done.
 struct topk_job_t {
@@ -82,6 +98,7 @@ struct topk_job_t {
     uint16_t *pos1; // may lie where scores lies
 };
 bool topk_beside_quant(int64_t dim, const quant_job_t &job);
+bool iht_quantize_beside_topk(int64_t dim, const adahop_operand_t &x); // the same for an operand rounded to nearest, no K-channels copied out
 int launch_topk_beside_quant(const topk_job_t &topk, int iht_block, const quant_job_t &job, hipStream_t st);
 // pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere, for k <= 0xffff; it may lie where scores lies.  The selection
 // writes it on the way where foid_writes_positions holds, else a launch after it does.
@@ -128,6 +145,13 @@ size_t oe_rowcol_partials_at(int64_t M, int64_t N, int64_t K, int kind, int k, s
 // gathered: the extracted rows lie at the start of the workspace already, [k, K] (a quantiser has copied them out).
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
                      void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered = false);
+// The same with the products formed by the quantiser of the long operand: false where that is not worth while or does not fit into the
+// region of the partial sums above, which then takes outlier_job_t::p.
+bool oe_rowcol_on_the_way(int64_t Lo, int64_t K, int k, outlier_job_t *e);
+int launch_gather_rows(const adahop_operand_t &x, const int32_t *idx, int k, uint16_t *out, hipStream_t st); // out[t, :] = x(idx[t], :)
+// C[idx[t], l] (rows) or C[l, idx[t]] = the sum over the slices of p[slice][t][l], p being [nslice][rows_all][Lo].
+int launch_oe_reduce(const float *p, int nslice, int64_t rows_all, int64_t Lo, bool rows, const int32_t *idx, int k, void *C, int64_t ldc,
+                     int c_bf16, hipStream_t st);
 int launch_oe_k_accumulate(int64_t M, int64_t N, const uint16_t *Ag, const uint16_t *Bg, int kpad, float *C,
                            int64_t ldc, hipStream_t st);
 

@@ -33,6 +33,7 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 //                      transposing LDS read hands the matrix cores their 8 consecutive K-elements of a row.  K
 //                      is split over workgroups so that the chip is full although there are few tiles; every
 //                      slice writes its own partial tile (no atomics: the result does not depend on scheduling);
+//      (where L is K-strided and there are at most 96 rows, L's quantiser forms the products instead: k_quant_ks16_outliers);
 //   3. k_oe_reduce     adds the slices in a fixed order and writes the rows / columns of C.
 // ------------------------------------------------------------------------------------------------
 constexpr int SK_LCOLS = 256;  // rows of L per workgroup (NCW = 2; half of them with NCW = 1)
@@ -48,15 +49,12 @@ static_assert(sk_l_elems<2>() == SK_KSTAGE * sk_tpitch<2>() && sk_l_elems<1>() >
 typedef short v4s __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t *__restrict__ x, int64_t ld, int64_t K,
-                                                     const int32_t *__restrict__ idx, int k, int rows_alloc,
-                                                     uint16_t *__restrict__ out)
+                                                     const int32_t *__restrict__ idx, int k, uint16_t *__restrict__ out)
 { // K-contiguous source: one thread = 8 consecutive K-elements of one row
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x, per_row = K >> 3;
-    if (g >= rows_alloc * per_row) return;
+    if (g >= k * per_row) return;
     const int64_t t = g / per_row, c = g - t * per_row;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (t < k) v = load_once16(x + (int64_t)idx[t] * ld + c * 8);
-    *reinterpret_cast<uint4 *>(out + t * K + c * 8) = v;
+    *reinterpret_cast<uint4 *>(out + t * K + c * 8) = load_once16(x + (int64_t)idx[t] * ld + c * 8);
 }
 
 // K-strided source (element (o, kk) at x[kk * ld + o]): a workgroup takes 64 K-rows x 64 extracted columns.  It reads
@@ -579,6 +577,69 @@ size_t oe_rowcol_partials_at(int64_t M, int64_t N, int64_t K, int kind, int k, s
     return p.sg_bytes;
 }
 
+// Whole groups of 64 rows of out are written at most.  (Rows past the k extracted ones may hold anything: row t of the product depends on
+// row t alone, and the reduction reads the first k.)
+int launch_gather_rows(const adahop_operand_t &S, const int32_t *idx, int k, uint16_t *out, hipStream_t st)
+{
+    const int64_t K = S.K;
+    if (S.k_contig)
+        hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)ceil_div(k * (K >> 3), 256)), dim3(256), 0, st,
+                           static_cast<const uint16_t *>(S.data), S.ld, K, idx, k, out);
+    else
+        hipLaunchKernelGGL(k_gather_rows_strided, dim3((unsigned)ceil_div(K, 64), (unsigned)ceil_div(k, 64)), dim3(256), 0, st,
+                           static_cast<const uint16_t *>(S.data), S.ld, K, idx, k, out);
+    return check_launch();
+}
+
+int launch_oe_reduce(const float *P, int nslice, int64_t rows_all, int64_t Lo, bool rows, const int32_t *idx, int k, void *C, int64_t ldc,
+                     int c_bf16, hipStream_t st)
+{
+    const unsigned rblocks = (unsigned)ceil_div((int64_t)k * Lo, 256);
+    auto reduce = [&](auto *c) {
+        typedef typename std::remove_pointer<decltype(c)>::type out_t;
+        // four long-side indices per thread where rows of the partials (and, for rows of C, of C) are 16-byte pieces
+        if (Lo % 4 == 0 && (!rows || (ldc % 4 == 0 && aligned(c, 4 * sizeof(out_t))))) {
+            const unsigned b4 = (unsigned)ceil_div((int64_t)k * (Lo >> 2), 256);
+            if (rows)
+                hipLaunchKernelGGL((k_oe_reduce4<true, out_t>), dim3(b4), dim3(256), 0, st, P, nslice, rows_all, Lo, idx, k, c,
+                                   ldc);
+            else
+                hipLaunchKernelGGL((k_oe_reduce4<false, out_t>), dim3(b4), dim3(256), 0, st, P, nslice, rows_all, Lo, idx, k,
+                                   c, ldc);
+            return;
+        }
+        if (rows)
+            hipLaunchKernelGGL((k_oe_reduce<true, out_t>), dim3(rblocks), dim3(256), 0, st, P, nslice, rows_all, Lo, idx,
+                               k, c, ldc);
+        else // (a variant that turns 32 x 64 blocks in LDS so that a wave's stores fall into two rows of C was measured
+             // and is slower, 42 against 33 us on 123 x 8192: the k x Lo partial-sector writes cost the same either way)
+            hipLaunchKernelGGL((k_oe_reduce<false, out_t>), dim3(rblocks), dim3(256), 0, st, P, nslice, rows_all, Lo, idx,
+                               k, c, ldc);
+    };
+    if (c_bf16)
+        reduce(static_cast<uint16_t *>(C));
+    else
+        reduce(static_cast<float *>(C));
+    return check_launch();
+}
+
+// As many 256-element blocks of K per workgroup as leave four workgroups for each of the 256 compute units (4096 x 32768 with 64 rows, whole
+// call: two for each 421, four 416, eight 416 us), and more where the sums would not fit otherwise.
+bool oe_rowcol_on_the_way(int64_t Lo, int64_t K, int k, outlier_job_t *e)
+{
+    e->tiles = (k + 15) / 16;
+    while (e->tiles <= OUTLIER_TILES && !iht_quantize_takes_outliers(e->tiles)) ++e->tiles;
+    if (e->tiles > OUTLIER_TILES) return false;
+    const size_t room = plan_skinny(Lo, K, k).p_bytes;
+    const int64_t upr = ceil_div(K, 256), tiles = ceil_div(Lo, 64) * upr;
+    int64_t blocks = tiles / 1024;
+    if (blocks < 1) blocks = 1;
+    while (blocks < upr && (size_t)ceil_div(upr, blocks) * k * Lo * 4 > room) ++blocks;
+    e->k = k;
+    e->nslice = (int)ceil_div(upr, blocks);
+    return (size_t)e->nslice * k * Lo * 4 <= room;
+}
+
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
                      void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered)
 {
@@ -591,17 +652,7 @@ int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int k
     uint16_t *Sg = static_cast<uint16_t *>(workspace);
     float *P = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.sg_bytes);
 
-    // (rows of Sg past the k extracted ones may hold anything: row t of the product depends on row t alone, and the reduction
-    // reads the first k)
-    if (gathered)
-        ;
-    else if (S.k_contig)
-        hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)ceil_div(p.rows_all * (K >> 3), 256)), dim3(256), 0, st,
-                           static_cast<const uint16_t *>(S.data), S.ld, K, idx, k, (int)p.rows_all, Sg);
-    else // rows_all is a multiple of 64: whole tiles of extracted columns
-        hipLaunchKernelGGL(k_gather_rows_strided, dim3((unsigned)ceil_div(K, 64), (unsigned)(p.rows_all / 64)), dim3(256), 0,
-                           st, static_cast<const uint16_t *>(S.data), S.ld, K, idx, k, Sg);
-    int rc = check_launch();
+    int rc = gathered ? ADAHOP_OK : launch_gather_rows(S, idx, k, Sg, st);
     if (rc != ADAHOP_OK) return rc;
 
     const dim3 grid((unsigned)ceil_div(Lo, SK_LCOLS / 2 * p.ncw), (unsigned)p.nslice, (unsigned)p.groups);
@@ -613,33 +664,7 @@ int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int k
     }
     if (rc != ADAHOP_OK) return rc;
 
-    const unsigned rblocks = (unsigned)ceil_div((int64_t)k * Lo, 256);
-    auto reduce = [&](auto *c) {
-        typedef typename std::remove_pointer<decltype(c)>::type out_t;
-        // four long-side indices per thread where rows of the partials (and, for rows of C, of C) are 16-byte pieces
-        if (Lo % 4 == 0 && (!rows || (ldc % 4 == 0 && aligned(c, 4 * sizeof(out_t))))) {
-            const unsigned b4 = (unsigned)ceil_div((int64_t)k * (Lo >> 2), 256);
-            if (rows)
-                hipLaunchKernelGGL((k_oe_reduce4<true, out_t>), dim3(b4), dim3(256), 0, st, P, p.nslice, p.rows_all, Lo, idx, k, c,
-                                   ldc);
-            else
-                hipLaunchKernelGGL((k_oe_reduce4<false, out_t>), dim3(b4), dim3(256), 0, st, P, p.nslice, p.rows_all, Lo, idx, k,
-                                   c, ldc);
-            return;
-        }
-        if (rows)
-            hipLaunchKernelGGL((k_oe_reduce<true, out_t>), dim3(rblocks), dim3(256), 0, st, P, p.nslice, p.rows_all, Lo, idx,
-                               k, c, ldc);
-        else // (a variant that turns 32 x 64 blocks in LDS so that a wave's stores fall into two rows of C was measured
-             // and is slower, 42 against 33 us on 123 x 8192: the k x Lo partial-sector writes cost the same either way)
-            hipLaunchKernelGGL((k_oe_reduce<false, out_t>), dim3(rblocks), dim3(256), 0, st, P, p.nslice, p.rows_all, Lo, idx,
-                               k, c, ldc);
-    };
-    if (c_bf16)
-        reduce(static_cast<uint16_t *>(C));
-    else
-        reduce(static_cast<float *>(C));
-    return check_launch();
+    return launch_oe_reduce(P, p.nslice, p.rows_all, Lo, rows, idx, k, C, ldc, c_bf16, st);
 }
 
 } // namespace adahop

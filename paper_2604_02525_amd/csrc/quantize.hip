@@ -496,169 +496,166 @@ template <int B, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_qu
 //
 // The transposing read works on groups of 16 lanes: lane s supplies the address of 4 consecutive 16-bit elements
 // (a piece of one K-row), and lane n of the group receives, as element j, the element n % 4 of the piece that lane
-// 4 j + n / 4 supplied.  With lane s pointing at K-row 64 (s % 4) + 4 t + s / 4 of 4 neighbouring columns, lane n
-// receives K-rows 64 (n / 4) + 4 t .. + 3 of column n % 4: after 16 reads (t = 0 .. 15) a group of 16 lanes holds
-// 4 columns x 256 K, lane n the 64 consecutive K-elements [64 m, 64 m + 64), m = n / 4, of its column.
+// 4 j + n / 4 supplied.  With lane s of group g pointing at K-row 64 g + 4 t + s / 4 of the columns 4 (s % 4) .. + 3 of
+// the wave's 16, lane n receives K-rows 64 g + 4 t .. + 3 of column n: after 16 reads (t = 0 .. 15) it holds the 64
+// consecutive K-elements [64 g, 64 g + 64) of its column.  That is also how the BF16 matrix cores want an operand of 16
+// columns (v_mfma_f32_16x16x32_bf16: 8 consecutive K-elements of a column per lane, a quarter of the K-elements in each group of 16
+// lanes), which the kernel that forms the outlier product on the way makes use of (k_quant_ks16_outlier).
 //
-// Work split, then: strides 1 .. 32 of the transform are butterflies inside a lane's 64 registers, stride 64 pairs
-// the lanes m and m ^ 1, stride 128 m and m ^ 2 of a column.  A gfx9 DPP row offers lane ^ 8 (row_ror:8) and lane ^ 7
-// (row_half_mirror) but not lane ^ 4, so the K-rows with bit 6 set are stored in LDS with every aligned group of 4
-// columns reversed: lane n then holds column 3 - n % 4 when m is odd, and lane n ^ 7 is its stride-64 partner in
-// the same column.  The two MX blocks of a lane lie entirely in its registers (no cross-lane maximum).
+// Strides 1 .. 32 of the transform are butterflies inside a lane's 64 registers.  Strides 64 and 128 are between lanes 16
+// and 32 apart: v_permlane16_swap (v_permlane32_swap) exchanges the odd rows of 16 lanes (the upper half) of one register with
+// the even rows (the lower half) of another.  Given the registers of K-elements 32 apart, it leaves both terms of a
+// butterfly in one lane: afterwards the register's place stands for K bit 6 (7) and the lane's for bit 5 (6).  The two MX
+// blocks of a lane lie entirely in its registers (no cross-lane maximum).
 //
-// (A variant with 128 columns per workgroup, 256-byte pieces of the operand's K-rows, runs at the same speed: the
-// kernel is bound by its vector instructions, about 15 per element, as much as by memory.)
+// (A variant with 128 columns per workgroup, 256-byte pieces of the operand's K-rows, runs at the same speed, and so do plain and
+// write-through stores of the codes in whole 128-byte rows, other orders of the workgroups, and the kernel without its transform: what it
+// waits for is the memory, 46 us of 73 on 4096 x 32768 for the reads and the rest for the writes of 128-byte pieces of many rows.)
 //
-// LDS layout: K-row kk at row index 4 (kk % 64) + kk / 64, 144 bytes per row (128 of data).  The 16 pieces of one
-// transposing read of a half wave (two groups: 16 bytes per row) then start 4 banks apart and cover the 64 banks
-// exactly once; the 16-byte writes of a 16-lane group go to two rows whose banks do not overlap either.
+// LDS layout: K-row kk at kk * 128 bytes, its four pieces of 32 bytes exchanged by kk's bits 1 and 6: the eight rows that the
+// half wave of a transposing read touches then lie in eight different eighths of the 64 banks.
 // ------------------------------------------------------------------------------------------------
-constexpr int KS_COLS = 64, KT_PITCH = 144;
+constexpr int KS_COLS = 64, KT_PITCH = 128;
 constexpr unsigned KS_GROUP = 32, KS_GROUP_FROM = 200; // column tiles that walk the K-blocks together; from how many on
 
 typedef short v4s __attribute__((ext_vector_type(4)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
-#define ADAHOP_FMAC_DPP16_AT(W, O, CTRL, T)                                                                    \
-    asm volatile("s_nop 1\n\t"                                                                                \
-                 "v_fmac_f32_dpp %0, %0, %16 " CTRL "\n\tv_fmac_f32_dpp %1, %1, %16 " CTRL "\n\t"             \
-                 "v_fmac_f32_dpp %2, %2, %16 " CTRL "\n\tv_fmac_f32_dpp %3, %3, %16 " CTRL "\n\t"             \
-                 "v_fmac_f32_dpp %4, %4, %16 " CTRL "\n\tv_fmac_f32_dpp %5, %5, %16 " CTRL "\n\t"             \
-                 "v_fmac_f32_dpp %6, %6, %16 " CTRL "\n\tv_fmac_f32_dpp %7, %7, %16 " CTRL "\n\t"             \
-                 "v_fmac_f32_dpp %8, %8, %16 " CTRL "\n\tv_fmac_f32_dpp %9, %9, %16 " CTRL "\n\t"             \
-                 "v_fmac_f32_dpp %10, %10, %16 " CTRL "\n\tv_fmac_f32_dpp %11, %11, %16 " CTRL "\n\t"         \
-                 "v_fmac_f32_dpp %12, %12, %16 " CTRL "\n\tv_fmac_f32_dpp %13, %13, %16 " CTRL "\n\t"         \
-                 "v_fmac_f32_dpp %14, %14, %16 " CTRL "\n\tv_fmac_f32_dpp %15, %15, %16 " CTRL "\n\t"         \
-                 "s_nop 1"                                                                                    \
-                 : "+v"(W[O + 0]), "+v"(W[O + 1]), "+v"(W[O + 2]), "+v"(W[O + 3]), "+v"(W[O + 4]), "+v"(W[O + 5]),    \
-                   "+v"(W[O + 6]), "+v"(W[O + 7]), "+v"(W[O + 8]), "+v"(W[O + 9]), "+v"(W[O + 10]), "+v"(W[O + 11]),  \
-                   "+v"(W[O + 12]), "+v"(W[O + 13]), "+v"(W[O + 14]), "+v"(W[O + 15])                             \
-                 : "v"(T))
-
-// w <- partner(w) * t + w on all 64 values of the lane; XOR7: the partner is lane ^ 7, else lane ^ 8.
-template <bool XOR7> __device__ __forceinline__ void cross_stage64(float (&w)[64], float t)
+__device__ __forceinline__ uint4 pieces(v4s a, v4s b)
 {
-#pragma unroll
-    for (int o = 0; o < 64; o += 16) {
-        if constexpr (XOR7)
-            ADAHOP_FMAC_DPP16_AT(w, o, "row_half_mirror row_mask:0xf bank_mask:0xf", t);
-        else
-            ADAHOP_FMAC_DPP16_AT(w, o, "row_ror:8 row_mask:0xf bank_mask:0xf", t);
-    }
+    const v2u x = __builtin_bit_cast(v2u, a), y = __builtin_bit_cast(v2u, b);
+    return make_uint4(x.x, x.y, y.x, y.y);
 }
-
-__device__ __forceinline__ uint32_t rot16(uint32_t v) { return __builtin_amdgcn_alignbit(v, v, 16); }
 
 constexpr int KS_LDS = 256 * KT_PITCH + 256; // bytes: the tile and the K-mask of its rows
 
-template <int B, bool SR>
-__device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uint32_t by, uint8_t *lds)
+__device__ __forceinline__ int ks_swizzle(int kk) { return ((kk >> 1) & 1) | ((kk >> 5) & 2); } // of a row's 32-byte pieces
+
+// a + b and a - b of the lanes that hold the two terms: (x of K-element e, y of e + 32) -> see above.
+template <bool HALVES> __device__ __forceinline__ void swap_butterfly(float &x, float &y)
 {
-    uint8_t *tile = lds, *kmask = lds + 256 * KT_PITCH;
+    v2u r;
+    if constexpr (HALVES)
+        r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    else
+        r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    const float a = __uint_as_float(r.x), b = __uint_as_float(r.y);
+    x = a + b;
+    y = a - b;
+}
+
+// A tile on its way to LDS: a pass is 32 K-rows x 64 columns; lane: 8 columns (cg) of one of the wave's 8 rows.
+struct ks_tile_t {
+    uint4 v[8], last;
+    uint8_t kz;
+};
+
+__device__ __forceinline__ bool ks_at_end(const quant_t &q, int64_t o0, int64_t k0)
+{
+    return (q.outer & 7) && k0 + 256 >= q.K && o0 + KS_COLS > q.outer;
+}
+
+__device__ __forceinline__ void ks_fetch_tile(const quant_t &q, int tid, int64_t o0, int64_t k0, ks_tile_t &f)
+{
     const uint16_t *x = q.x;
     const int64_t outer = q.outer, K = q.K, ld = q.ld;
-    const uint8_t *zero_outer = q.gr.out ? nullptr : q.zero_outer, *zero_k = q.zero_k;
-    uint8_t *codes = q.codes, *scales = q.scales;
-    const scales_sm_t sm = q.sm;
-    const sr_key_t key = q.key;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t o0 = (int64_t)bx * KS_COLS, k0 = (int64_t)by * 256;
-
-    // ---- global -> LDS: a pass is 32 K-rows x 64 columns; lane: 8 columns (cg) of one of the wave's 8 rows.  A group
-    // of 16 lanes takes two rows two apart (their banks do not overlap: consecutive K-rows are 16 banks apart).
-    {
-        const int cg = lane & 7, q = lane >> 4;
-        const int rw = w * 8 + (q >> 1) * 4 + (q & 1) + 2 * ((lane >> 3) & 1);
-        const int64_t oc = o0 + cg * 8;
-        const bool ok = oc < outer;
-        uint32_t cm[4] = {~0u, ~0u, ~0u, ~0u}; // keeps the columns that are not masked out
-        if (zero_outer && ok) {
-            // the 8 mask bytes of the lane's columns in one load where that is possible (eight dependent byte loads
-            // at the head of every workgroup cost the masked call a third more time)
-            uint64_t z = 0;
-            if ((reinterpret_cast<uintptr_t>(zero_outer) & 7) == 0 && oc + 8 <= outer) {
-                z = *reinterpret_cast<const uint64_t *>(zero_outer + oc);
-            } else {
+    const int cg = tid & 7, rw = tid >> 3;
+    const int64_t oc = o0 + cg * 8;
+    const bool ok = oc < outer;
+    // K-mask: one byte of the tile's 256 per thread, loaded ahead of the data and handed round through LDS (eight
+    // byte loads per lane, one for each of its K-rows, made the masked call 15 % slower than the plain one)
+    f.kz = 0;
+    if (q.zero_k && k0 + tid < K) f.kz = q.zero_k[k0 + tid];
+    // The matrix ends with its last element.  Where that lies inside a piece, the workgroup takes the last pass by itself, the part
+    // of a piece with the elements that exist.  (Behind any other K-row there is the next one, or what its stride leaves.)  A
+    // condition more on the loads of every pass cost 8192 rows x 4096 0.7 of 20.3 us.
+    const bool at_end = ks_at_end(q, o0, k0);
+    const int64_t k_end = at_end ? K - 32 : K;
 #pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    if (oc + c < outer && zero_outer[oc + c]) z |= (uint64_t)1 << (8 * c);
-            }
+    for (int it = 0; it < 8; ++it) { // (a pass is one MX block of K: inside the operand or not as a whole)
+        const int64_t kk = k0 + it * 32 + rw;
+        f.v[it] = ok && k0 + it * 32 < k_end ? load_once16(x + kk * ld + oc) : make_uint4(0, 0, 0, 0);
+    }
+    f.last = make_uint4(0, 0, 0, 0);
+    if (at_end && ok) {
+        const uint16_t *p = x + (k_end + rw) * ld + oc;
+        f.last = rw == 31 && oc + 8 > outer ? load_part16(p, (int)(outer - oc)) : load_once16(p);
+    }
+}
+
+__device__ __forceinline__ void ks_put_tile(const quant_t &q, int tid, int64_t o0, int64_t k0, uint8_t *lds, const ks_tile_t &f)
+{
+    uint8_t *tile = lds, *kmask = lds + 256 * KT_PITCH;
+    const int64_t outer = q.outer;
+    const uint8_t *zero_outer = q.gr.out ? nullptr : q.zero_outer;
+    const int cg = tid & 7, rw = tid >> 3;
+    const int64_t oc = o0 + cg * 8;
+    uint32_t cm[4] = {~0u, ~0u, ~0u, ~0u}; // keeps the columns that are not masked out
+    if (zero_outer && oc < outer) {
+        // the 8 mask bytes of the lane's columns in one load where that is possible (eight dependent byte loads
+        // at the head of every workgroup cost the masked call a third more time)
+        uint64_t z = 0;
+        if ((reinterpret_cast<uintptr_t>(zero_outer) & 7) == 0 && oc + 8 <= outer) {
+            z = *reinterpret_cast<const uint64_t *>(zero_outer + oc);
+        } else {
 #pragma unroll
             for (int c = 0; c < 8; ++c)
-                if ((z >> (8 * c)) & 0xffu) cm[c >> 1] &= (c & 1) ? 0x0000ffffu : 0xffff0000u;
+                if (oc + c < outer && zero_outer[oc + c]) z |= (uint64_t)1 << (8 * c);
         }
-        uint4 v[8];
-        // K-mask: one byte of the tile's 256 per thread, loaded ahead of the data and handed round through LDS (eight
-        // byte loads per lane, one for each of its K-rows, made the masked call 15 % slower than the plain one)
-        uint8_t my_kz = 0;
-        if (zero_k && k0 + tid < K) my_kz = zero_k[k0 + tid];
-        // The matrix ends with its last element.  Where that lies inside a piece, the workgroup takes the last pass by itself, the part
-        // of a piece with the elements that exist.  (Behind any other K-row there is the next one, or what its stride leaves.)  A
-        // condition more on the loads of every pass cost 8192 rows x 4096 0.7 of 20.3 us.
-        const bool at_end = (outer & 7) && k0 + 256 >= K && o0 + KS_COLS > outer;
-        const int64_t k_end = at_end ? K - 32 : K;
 #pragma unroll
-        for (int it = 0; it < 8; ++it) { // (a pass is one MX block of K: inside the operand or not as a whole)
-            const int64_t kk = k0 + it * 32 + rw;
-            v[it] = ok && k0 + it * 32 < k_end ? load_once16(x + kk * ld + oc) : make_uint4(0, 0, 0, 0);
-        }
-        uint4 last = make_uint4(0, 0, 0, 0);
-        if (at_end && ok) {
-            const uint16_t *p = x + (k_end + rw) * ld + oc;
-            last = rw == 31 && oc + 8 > outer ? load_part16(p, (int)(outer - oc)) : load_once16(p);
-        }
-        uint32_t zk = 0; // bit it: the lane's K-row of pass it is masked out
-        if (zero_k) {    // (uniform: a kernel argument)
-            kmask[tid] = my_kz;
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < 8; ++it) zk |= (kmask[it * 32 + rw] ? 1u : 0u) << it;
-        }
-        auto put = [&](int it, uint4 p) {
-            const int row = it * 32 + rw; // K-row within the tile; bit 6 = bit 1 of it
-            const uint32_t kz = ((zk >> it) & 1u) ? 0u : ~0u;
-            uint4 u = make_uint4(p.x & cm[0] & kz, p.y & cm[1] & kz, p.z & cm[2] & kz, p.w & cm[3] & kz);
-            if (it & 2) u = make_uint4(rot16(u.y), rot16(u.x), rot16(u.w), rot16(u.z)); // groups of 4 columns reversed
-            *reinterpret_cast<uint4 *>(tile + (4 * (row & 63) + (row >> 6)) * KT_PITCH + cg * 16) = u;
-        };
-#pragma unroll
-        for (int it = 0; it < 8; ++it) put(it, v[it]);
-        if (at_end) put((int)(K - 1 - k0) >> 5, last);
+        for (int c = 0; c < 8; ++c)
+            if ((z >> (8 * c)) & 0xffu) cm[c >> 1] &= (c & 1) ? 0x0000ffffu : 0xffff0000u;
     }
-    __syncthreads();
+    uint32_t zk = 0;   // bit it: the lane's K-row of pass it is masked out
+    if (q.zero_k) {    // (uniform: a kernel argument)
+        kmask[tid] = f.kz;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < 8; ++it) zk |= (kmask[it * 32 + rw] ? 1u : 0u) << it;
+    }
+    auto put = [&](int it, uint4 p) {
+        const int row = it * 32 + rw; // K-row within the tile
+        const uint32_t kz = ((zk >> it) & 1u) ? 0u : ~0u;
+        *reinterpret_cast<uint4 *>(tile + row * KT_PITCH + ((cg * 16) ^ (ks_swizzle(row) * 32))) =
+            make_uint4(p.x & cm[0] & kz, p.y & cm[1] & kz, p.z & cm[2] & kz, p.w & cm[3] & kz);
+    };
+#pragma unroll
+    for (int it = 0; it < 8; ++it) put(it, f.v[it]);
+    if (ks_at_end(q, o0, k0)) put((int)(q.K - 1 - k0) >> 5, f.last);
+}
 
-    // ---- LDS -> registers, transposed: wave w takes columns [16 w, 16 w + 16)
-    const int n = lane & 15, g = lane >> 4, m = n >> 2, e = n & 3;
-    float wv[64];
-    {
-        // as the supplier of addresses this lane is s = n: K-row 64 (s % 4) + 4 t + s / 4, i.e. row index 16 t + 4 (s / 4) + s % 4
-        const uint8_t *src = tile + (4 * (n >> 2) + (n & 3)) * KT_PITCH + 32 * w + 8 * g;
+// LDS -> registers, transposed: wave w takes columns [16 w, 16 w + 16); d[t]: K-elements 64 g + 4 t .. + 3 of the lane's column.
+__device__ __forceinline__ void ks_read_tile(int tid, const uint8_t *lds, v4s (&d)[16])
+{
+    const int lane = tid & 63, w = tid >> 6, g = lane >> 4, j = (lane >> 2) & 3, c = lane & 3;
+    const uint8_t *src = lds + (64 * g + j) * KT_PITCH + ((w ^ ks_swizzle(64 * g + j)) * 32) + 8 * c;
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            const v4s d = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (__attribute__((address_space(3))) v4s *)(src + t * 16 * KT_PITCH));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) wv[4 * t + j] = bf16_one((uint16_t)d[j]);
-        }
-    }
-    const int col = 16 * w + 4 * g + ((m & 1) ? 3 - e : e);
-    const int64_t o = o0 + col;
+    for (int t = 0; t < 16; ++t)
+        d[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)(src + t * 4 * KT_PITCH));
+}
+
+// The column of the lane from its raw elements on: copied out if it is extracted, transformed, quantised and stored.
+template <int B, bool SR> __device__ __forceinline__ void ks_finish(const quant_t &q, int tid, int64_t o0, int64_t k0, const v4s (&d)[16])
+{
+    const int64_t outer = q.outer, K = q.K;
+    const int lane = tid & 63, w = tid >> 6, g = lane >> 4, b4 = g & 1, b5 = g >> 1;
+    const int64_t o = o0 + 16 * w + (lane & 15);
     const bool active = o < outer;
+    float wv[64];
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wv[4 * t + j] = bf16_one((uint16_t)d[t][j]);
 
     // ---- an extracted column leaves as it came and counts as zero here: the lane has 64 of its K-elements in a row
     // (as a launch of its own that reads two bytes of every K-row, this copy took 31 us for 64 columns x 32768)
     if (q.gr.out) {
         const uint32_t p = active ? q.gr.pos1[o] : 0u;
         if (p) {
-            uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + k0 + 64 * m;
+            uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + k0 + 64 * g;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (k0 + 64 * m + 8 * i < K) {
-                    uint32_t d[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        d[j] = __builtin_amdgcn_perm(__float_as_uint(wv[8 * i + 2 * j + 1]), __float_as_uint(wv[8 * i + 2 * j]), 0x07060302u);
-                    *reinterpret_cast<uint4 *>(dst + 8 * i) = make_uint4(d[0], d[1], d[2], d[3]);
-                }
+                if (k0 + 64 * g + 8 * i < K) *reinterpret_cast<uint4 *>(dst + 8 * i) = pieces(d[2 * i], d[2 * i + 1]);
 #pragma unroll
             for (int i = 0; i < 64; ++i) wv[i] = 0.0f;
         }
@@ -677,111 +674,234 @@ __device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uin
                     wv[j] = a + b;
                     wv[j + h] = a - b;
                 }
-        float sign = 1.0f;
-        if constexpr (B >= 128) { // stride 64: lanes m and m ^ 1 of the column (lane ^ 7)
-            const bool upper = (m & 1) != 0;
-            cross_stage64<true>(wv, upper ? -1.0f : 1.0f);
-            if (upper) sign = -sign;
+        if constexpr (B >= 128) {
+#pragma unroll
+            for (int i = 0; i < 32; ++i) swap_butterfly<false>(wv[i], wv[i + 32]); // stride 64
         }
-        if constexpr (B == 256) { // stride 128: lanes m and m ^ 2 (lane ^ 8)
-            const bool upper = (m & 2) != 0;
-            cross_stage64<false>(wv, upper ? -1.0f : 1.0f);
-            if (upper) sign = -sign;
+        if constexpr (B == 256) {
+#pragma unroll
+            for (int i = 0; i < 32; ++i) swap_butterfly<true>(wv[i], wv[i + 32]); // stride 128
         }
-        // the sign left over from the stages goes into the normalisation; "+ 0" stores exact zeros unsigned
-        const float fin = sign * hadamard_norm<B>();
+        // "+ 0" stores exact zeros unsigned
+        const float fin = hadamard_norm<B>();
 #pragma unroll
         for (int i = 0; i < 64; ++i) wv[i] = __builtin_fmaf(wv[i], fin, 0.0f);
     }
 
-    // ---- the lane's two MX blocks
+    // ---- the lane's two MX blocks; at[i]: which of the tile's eight
+    const int at[2] = {B == 256 ? b4 + 2 * b5 : B == 128 ? b4 + 4 * b5 : 2 * g, B == 256 ? 4 + b4 + 2 * b5 : B == 128 ? 2 + b4 + 4 * b5 : 2 * g + 1};
     uint32_t c[8];
-    int sc[2];
+    uint32_t sc[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
         float amax = 0.0f;
 #pragma unroll
         for (int i = 0; i < 32; ++i) amax = fmaxf(amax, fabsf(wv[32 * blk + i]));
         const int s = e8m0_of_amax(amax);
-        sc[blk] = s;
+        sc[blk] = (uint32_t)s;
         if constexpr (SR) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q4 = 0; q4 < 4; ++q4) {
                 float t8[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) t8[i] = wv[32 * blk + 8 * q + i];
-                c[4 * blk + q] = pack8_sr(t8, s, key, o, k0 + 64 * m + 32 * blk + 8 * q);
+                for (int i = 0; i < 8; ++i) t8[i] = wv[32 * blk + 8 * q4 + i];
+                c[4 * blk + q4] = pack8_sr(t8, s, q.key, o, k0 + 32 * at[blk] + 8 * q4);
             }
         } else {
             const float X = __uint_as_float((uint32_t)s << 23);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q4 = 0; q4 < 4; ++q4) {
                 uint32_t p = 0;
-                const float *v8 = wv + 32 * blk + 8 * q;
+                const float *v8 = wv + 32 * blk + 8 * q4;
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[0], v8[1], X, 0);
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[2], v8[3], X, 1);
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[4], v8[5], X, 2);
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[6], v8[7], X, 3);
-                c[4 * blk + q] = p;
+                c[4 * blk + q4] = p;
             }
         }
     }
     if (active) {
-        uint8_t *crow = codes + o * (K >> 1) + ((k0 + 64 * m) >> 1);
-        if (k0 + 64 * m < K) *reinterpret_cast<uint4 *>(crow) = make_uint4(c[0], c[1], c[2], c[3]);
-        if (k0 + 64 * m + 32 < K) *reinterpret_cast<uint4 *>(crow + 16) = make_uint4(c[4], c[5], c[6], c[7]);
+        uint8_t *crow = q.codes + o * (K >> 1) + (k0 >> 1);
+        if (k0 + 32 * at[0] < K) *reinterpret_cast<uint4 *>(crow + 16 * at[0]) = make_uint4(c[0], c[1], c[2], c[3]);
+        if (k0 + 32 * at[1] < K) *reinterpret_cast<uint4 *>(crow + 16 * at[1]) = make_uint4(c[4], c[5], c[6], c[7]);
     }
-    // The column's 8 scale bytes of this tile sit in the four lanes m = 0 .. 3 of the column, which are 4 apart in
-    // the row of 16 lanes: the lane m = 0 collects them (two DPP shifts) and stores them at once.  Byte stores, four
-    // per lane, were three quarters of the kernel's write requests.
-    // (Lanes with odd m hold the columns of their quad in reverse order: they take their neighbour's bytes first.)
-    const uint32_t own = (uint32_t)sc[0] | ((uint32_t)sc[1] << 8);
-    const uint32_t mirrored = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0x1B /* quad_perm:[3,2,1,0] */, 0xf, 0xf, true);
-    const uint32_t mine = (m & 1) ? mirrored : own;
-    const uint32_t pair = mine | ((uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0x104 /* row_shl:4 */, 0xf, 0xf, true) << 16);
-    const uint32_t upper = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)pair, 0x108 /* row_shl:8 */, 0xf, 0xf, true);
-    if (active && m == 0) {
-        uint8_t *srow = scales + o * (K >> 5) + (k0 >> 5);
-        const int rot = tail_rotation(K, k0);
+    // The column's 8 scale bytes of this tile sit in its four lanes, two each: two exchanges give every lane all of them, and one lane
+    // stores them at once, another the second copy.  Byte stores, four per lane, were three quarters of the kernel's write requests.
+    const uint32_t own = sc[0] | sc[1] << 8;
+    const v2u r16 = __builtin_amdgcn_permlane16_swap(own, own, false, false); // of the even and the odd row of 16 lanes
+    // bytes of half a column: in the order of the blocks (B < 128), else first blocks of both lanes, then second ones
+    const uint32_t four = __builtin_amdgcn_perm(r16.y, r16.x, B >= 128 ? 0x05010400u : 0x05040100u);
+    const v2u r32 = __builtin_amdgcn_permlane32_swap(four, four, false, false);
+    const uint32_t lower = B == 256 ? __builtin_amdgcn_perm(r32.y, r32.x, 0x05040100u) : r32.x;
+    const uint32_t upper = B == 256 ? __builtin_amdgcn_perm(r32.y, r32.x, 0x07060302u) : r32.y;
+    const int rot = tail_rotation(K, k0);
+    if (active && g == 0) {
+        uint8_t *srow = q.scales + o * (K >> 5) + (k0 >> 5);
         if (rot == 0 && (reinterpret_cast<uintptr_t>(srow) & 7) == 0) {
-            *reinterpret_cast<uint2 *>(srow) = make_uint2(pair, upper);
+            *reinterpret_cast<uint2 *>(srow) = make_uint2(lower, upper);
         } else { // the canonical array has no alignment rule, and the last tile may hold fewer blocks
-            const uint64_t all = (uint64_t)upper << 32 | pair;
+            const uint64_t all = (uint64_t)upper << 32 | lower;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (i < 8 - rot) srow[i] = (uint8_t)(all >> (8 * i));
         }
-        if (sm.out)
-            *reinterpret_cast<uint64_t *>(sm.out + ((k0 >> 8) * sm.rows + o) * 8) = ((uint64_t)upper << 32 | pair) << (8 * rot);
+    }
+    if (q.sm.out && active && g == 1)
+        *reinterpret_cast<uint64_t *>(q.sm.out + ((k0 >> 8) * q.sm.rows + o) * 8) = ((uint64_t)upper << 32 | lower) << (8 * rot);
+}
+
+template <int B, bool SR>
+__device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uint32_t by, uint8_t *lds)
+{
+    const int64_t o0 = (int64_t)bx * KS_COLS, k0 = (int64_t)by * 256;
+    const int tid = threadIdx.x;
+    ks_tile_t f;
+    ks_fetch_tile(q, tid, o0, k0, f);
+    ks_put_tile(q, tid, o0, k0, lds, f);
+    __syncthreads();
+    v4s d[16];
+    ks_read_tile(tid, lds, d);
+    ks_finish<B, SR>(q, tid, o0, k0, d);
+}
+
+// Workgroups start in the order of their linear index, x fastest.  Taken as it is, that order runs all column
+// tiles of one K-block before the next K-block: the workgroups in flight together then write 128-byte pieces of
+// thousands of different output rows.  Instead the index walks KS_GROUP neighbouring column tiles through all
+// K-blocks before it moves to the next group: the reads still come in pieces of KS_GROUP x 128 bytes of a K-row, and
+// an output row is written in one go.  Measured: operands with rows of 28672 elements (448 column tiles: the
+// about 1000 workgroups in flight span two K-blocks, 300 bytes of an output row) 292 -> 237 us ([16384][28672])
+// and 133 -> 122 us ([8192][28672]); 384, 320 and 224 column tiles 11 .. 13 % faster; 256 column tiles 7 % faster
+// or 5 % slower by K; with 192 column tiles and fewer the plain order is as fast or up to 10 % faster and is kept
+// (group == 0).
+__device__ __forceinline__ void ks_order(unsigned group, uint64_t ny, unsigned &bx, unsigned &by)
+{
+    if (!group) return;
+    const uint64_t nx = gridDim.x, L = by * nx + bx, full = nx / group * group;
+    if (L < full * ny) {
+        const uint64_t r = L % (group * ny);
+        bx = (unsigned)(L / (group * ny) * group + r % group);
+        by = (unsigned)(r / group);
+    } else { // the last, narrower group
+        const uint64_t r = L - full * ny, wdt = nx - full;
+        bx = (unsigned)(full + r % wdt);
+        by = (unsigned)(r / wdt);
     }
 }
 
 template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(quant_t q)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[KS_LDS];
-    // Workgroups start in the order of their linear index, x fastest.  Taken as it is, that order runs all column
-    // tiles of one K-block before the next K-block: the workgroups in flight together then write 128-byte pieces of
-    // thousands of different output rows.  Instead the index walks KS_GROUP neighbouring column tiles through all
-    // K-blocks before it moves to the next group: the reads still come in pieces of KS_GROUP x 128 bytes of a K-row, and
-    // an output row is written in one go.  Measured: operands with rows of 28672 elements (448 column tiles: the
-    // about 1000 workgroups in flight span two K-blocks, 300 bytes of an output row) 292 -> 237 us ([16384][28672])
-    // and 133 -> 122 us ([8192][28672]); 384, 320 and 224 column tiles 11 .. 13 % faster; 256 column tiles 7 % faster
-    // or 5 % slower by K; with 192 column tiles and fewer the plain order is as fast or up to 10 % faster and is kept
-    // (group == 0).
     unsigned bx = blockIdx.x, by = blockIdx.y;
-    if (q.group) {
-        const uint64_t nx = gridDim.x, ny = gridDim.y, L = by * nx + bx, full = nx / q.group * q.group;
-        if (L < full * ny) {
-            const uint64_t r = L % (q.group * ny);
-            bx = (unsigned)(L / (q.group * ny) * q.group + r % q.group);
-            by = (unsigned)(r / q.group);
-        } else { // the last, narrower group
-            const uint64_t r = L - full * ny, wdt = nx - full;
-            bx = (unsigned)(full + r % wdt);
-            by = (unsigned)(r / wdt);
-        }
-    }
+    ks_order(q.group, gridDim.y, bx, by);
     quant_ks_tile<B, SR>(q, bx, by, lds);
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+// A K-strided operand (nothing extracted from it), and on the way its bf16 products with the k <= 16 RT rows extracted from the other
+// one (second term of Eq. 7 / 8): the operand's tile is in registers in the matrix cores' layout anyway, and reading it once more for these products by
+// themselves is what they cost.  Quantiser and products, us in two kernels / here: 4096 x 32768 with 64 rows 73 + 50 / 92, 4096 x 11008 with 21
+// 26.5 + 22.5 / 31, 8192 x 4096 with 41 20 + 19 / 27, 4096 x 4096 with 82 11.5 + 13.7 / 21.5; the partial sums are added by k_oe_reduce as before.
+//
+// A workgroup takes every nslice-th tile along K, so that the sums leave once per slice and not once per tile; four of them per compute unit
+// hide each other's loads.  The extracted rows' 256 K-elements of the tile come with its loads and take its place in LDS once it is in
+// registers (each wave reading its fragments from memory: 103 in place of 92 us in the first example; the matrix cores' own time is a tenth).
+//
+// The extracted rows are those that the other operand's quantiser has copied out, or (idx) lie in that operand where it is
+// K-contiguous: then its quantiser need not know the selection, and the workgroups of one row more of the grid set the codes and scales of
+// the extracted rows to zero.  B = -1: an operand that is packed already, the same products by themselves.
+template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_ks16_outliers(quant_t q, outlier_job_t e)
+{
+    constexpr int TILE_LDS = RT * 8192 > KS_LDS ? RT * 8192 : KS_LDS;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS + RT * 16 * 8];
+    int64_t *const row_at = reinterpret_cast<int64_t *>(lds + TILE_LDS);
+    const int64_t K = q.K;
+    unsigned bx = blockIdx.x, slice = blockIdx.y;
+    if ((int)slice == e.nslice) { // the extracted rows of the other operand's codes and scales
+        for (int t = (int)bx; t < e.k; t += (int)gridDim.x) {
+            const int64_t o = e.idx[t];
+            for (int64_t i = threadIdx.x; i < K / 32; i += 256) {
+                *reinterpret_cast<uint4 *>(e.codes + o * (K >> 1) + i * 16) = make_uint4(0, 0, 0, 0);
+                e.scales[o * (K >> 5) + i] = 0;
+            }
+            if (e.sm.out)
+                for (int64_t i = threadIdx.x; i < q.upr; i += 256) *reinterpret_cast<uint64_t *>(e.sm.out + (i * e.sm.rows + o) * 8) = 0;
+        }
+        return;
+    }
+    ks_order(q.group, (uint64_t)e.nslice, bx, slice);
+    const int64_t o0 = (int64_t)bx * KS_COLS;
+    for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
+        const int r = min(t, e.k - 1);
+        row_at[t] = (e.idx ? e.idx[r] : r) * e.ld;
+    }
+    __syncthreads();
+    v4f acc[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr bool AHEAD = B < 0 && RT <= 3; // (registers that a tile's quantisation needs: with it three workgroups fit, and nothing is gained)
+    ks_tile_t tile;
+    if constexpr (AHEAD) ks_fetch_tile(q, threadIdx.x, o0, (int64_t)slice * 256, tile);
+    for (int by = (int)slice; by < (int)q.upr; by += e.nslice) {
+        // What depends on the lane alone is formed anew for every tile: kept across the tiles it took 40 registers too many.
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int64_t k0 = (int64_t)by * 256;
+        if constexpr (!AHEAD) ks_fetch_tile(q, tid, o0, k0, tile);
+        // the extracted rows' 256 K-elements: piece c (8 elements) of row r0 + 8 i
+        const int c = tid & 31, r0 = tid >> 5;
+        uint4 f[2 * RT];
+#pragma unroll
+        for (int i = 0; i < 2 * RT; ++i) {
+            f[i] = make_uint4(0, 0, 0, 0);
+            if (k0 + 8 * c < K) f[i] = *reinterpret_cast<const uint4 *>(e.rows + row_at[r0 + 8 * i] + k0 + 8 * c);
+        }
+        ks_put_tile(q, tid, o0, k0, lds, tile);
+        __syncthreads();
+        v4s d[16];
+        ks_read_tile(tid, lds, d);
+        if constexpr (AHEAD) {
+            if (by + e.nslice < (int)q.upr) ks_fetch_tile(q, tid, o0, k0 + 256ll * e.nslice, tile);
+        }
+        __syncthreads(); // the tile is in registers: its place takes the extracted rows
+        // A tile of 16 rows as 8 x 64 pieces: at (i, 16 g + r) the K-elements 64 g + 8 i .. + 7 of row r, what lane 16 g + r hands to
+        // matrix-core instruction i.  Row r at r ^ (8 (g & 1) + i): the 16 pieces that 16 lanes write then cover the banks once.
+        uint4 *const s = reinterpret_cast<uint4 *>(lds);
+        {
+            const int at = (c & 7) * 64 + (c >> 3) * 16, x = c & 15;
+#pragma unroll
+            for (int i = 0; i < 2 * RT; ++i) s[(i >> 1) * 512 + at + ((r0 + 8 * (i & 1)) ^ x)] = f[i];
+        }
+        __syncthreads();
+        {
+            const int lane = tid & 63, g16 = lane & 48, x = 8 * ((lane >> 4) & 1), r = lane & 15;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { // (the sums of different rows in turn: none waits for the one before)
+                const v8bf column = __builtin_bit_cast(v8bf, pieces(d[2 * i], d[2 * i + 1]));
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, s[rt * 512 + i * 64 + g16 + (r ^ (x + i))]), column,
+                                                                      acc[rt], 0, 0, 0);
+                if (i & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (by + e.nslice < (int)q.upr) __syncthreads(); // (the next tile may be written)
+        if constexpr (B >= 0) ks_finish<B, false>(q, tid, o0, k0, d);
+    }
+    const int g = (threadIdx.x >> 4) & 3;
+    const int64_t o = o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
+    if (o < q.outer) {
+        float *p = e.p + (int64_t)slice * e.k * q.outer + o;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = 16 * rt + 4 * g + r;
+                if (t < e.k) p[(int64_t)t * q.outer] = acc[rt][r];
+            }
+    }
 }
 
 // Both operands of a product in one launch: the workgroups below `na` take the first, the others the second.  A launch costs at
@@ -790,7 +910,7 @@ template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(qu
 enum quant_kind_t { KC, KC_GATHER, KS };
 template <quant_kind_t OP> constexpr int quant_lds() { return OP == KS ? KS_LDS : OP == KC_GATHER ? KC_GATHER_LDS : 16; }
 
-template <int B, quant_kind_t OP, bool TAIL>
+template <int B, quant_kind_t OP, bool TAIL, int NT = 256>
 __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, uint8_t *lds)
 {
     if constexpr (OP == KS) {
@@ -799,20 +919,25 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
     } else if constexpr (OP == KC_GATHER) {
         quant_kc_gather_rows<B, false, TAIL>(q, block, lds);
     } else {
-        const uint32_t u = (block * 256u + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
+        const uint32_t u = (block * (uint32_t)NT + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
         quant_kc_unit<B, false, TAIL>(q, r, u - r * q.upr, r < q.outer);
     }
 }
 
-// The top-k selection in workgroup 0, an operand that does not depend on it in the others.
-constexpr int TOPK_BESIDE_DIM = 8192;
-template <int B, quant_kind_t OP, bool TAIL> __global__ __launch_bounds__(256) void k_topk_and_quant(topk_job_t t, quant_t q)
+// The top-k selection in workgroup 0, an operand that does not depend on it in the others.  Every workgroup of the launch gets the LDS that
+// the selection needs (46 KB for 8192 keys).  Beside a K-contiguous operand, whose own kernel needs none, the workgroups have 512 threads, so that
+// more waves share it: whole calls with 1 % of the rows extracted, M x N x K, us with 256 / 512 / 1024 threads: 8192 x 4096 x 4096 121.5 / 117.9 / 119.0,
+// 16384 x 1024 x 4096 97.3 (selection by itself) / 94.4 / 91.2, 2016 x 4096 x 11008 98.9 / 99.7 / 100.9, 1024 x 2048 x 8192 44.7 / 45.0 / 45.9.
+constexpr int TOPK_BESIDE_DIM = 8192, TOPK_BESIDE_DIM_KC = 16384;
+template <quant_kind_t OP> constexpr int topk_threads() { return OP == KC ? 512 : 256; }
+template <int B, quant_kind_t OP, bool TAIL>
+__global__ __launch_bounds__(topk_threads<OP>()) void k_topk_and_quant(topk_job_t t, quant_t q)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
     if (blockIdx.x == 0)
-        topk_lds<256>(t.scores, t.dim, t.k, t.idx, t.mask, t.pos1, reinterpret_cast<uint32_t *>(dyn));
+        topk_lds<topk_threads<OP>()>(t.scores, t.dim, t.k, t.idx, t.mask, t.pos1, reinterpret_cast<uint32_t *>(dyn));
     else
-        quant_block<B, OP, TAIL>(q, blockIdx.x - 1, dyn);
+        quant_block<B, OP, TAIL, topk_threads<OP>()>(q, blockIdx.x - 1, dyn);
 }
 
 template <int B, quant_kind_t OPA, quant_kind_t OPB, bool TAIL>
@@ -887,6 +1012,19 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
     return check_launch();
 }
 
+template <int B> int launch_outliers_b(const quant_t &q, const outlier_job_t &e, hipStream_t st)
+{
+    const dim3 grid(q.col_tiles, (unsigned)(e.nslice + (e.codes ? 1 : 0)));
+    switch (e.tiles) {
+    case 1: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 1>), grid, dim3(256), 0, st, q, e); break;
+    case 2: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 2>), grid, dim3(256), 0, st, q, e); break;
+    case 3: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 3>), grid, dim3(256), 0, st, q, e); break;
+    case 4: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 4>), grid, dim3(256), 0, st, q, e); break;
+    case 6: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 6>), grid, dim3(256), 0, st, q, e); break;
+    }
+    return check_launch();
+}
+
 template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const quant_t &qb, hipStream_t st)
 {
     const uint32_t na = blocks_of(ka, qa), nb = blocks_of(kb, qb);
@@ -912,23 +1050,30 @@ template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind
     return check_launch();
 }
 
+template <quant_kind_t OP> size_t topk_quant_lds(int dim)
+{
+    const size_t topk = topk_lds_bytes<topk_threads<OP>()>(dim), own = OP == KS ? (size_t)KS_LDS : 0;
+    return topk > own ? topk : own;
+}
+
 template <int B, quant_kind_t OP, bool TAIL> int allow_topk_lds()
 {
     return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_topk_and_quant<B, OP, TAIL>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)(topk_lds_bytes<256>(TOPK_BESIDE_DIM) > KS_LDS ? topk_lds_bytes<256>(TOPK_BESIDE_DIM) : KS_LDS)));
+                                         (int)topk_quant_lds<OP>(OP == KC ? TOPK_BESIDE_DIM_KC : TOPK_BESIDE_DIM)));
 }
 
 template <int B> int launch_topk_b(const topk_job_t &t, quant_kind_t kind, const quant_t &q, hipStream_t st)
 {
-    const size_t topk = topk_lds_bytes<256>(t.dim), own = kind == KS ? (size_t)KS_LDS : 0, lds = topk > own ? topk : own;
-    const dim3 grid(1 + blocks_of(kind, q));
     if (kind == KS)
-        hipLaunchKernelGGL((k_topk_and_quant<B, KS, false>), grid, dim3(256), lds, st, t, q);
-    else if (q.K % 256)
-        hipLaunchKernelGGL((k_topk_and_quant<B, KC, true>), grid, dim3(256), lds, st, t, q);
-    else
-        hipLaunchKernelGGL((k_topk_and_quant<B, KC, false>), grid, dim3(256), lds, st, t, q);
+        hipLaunchKernelGGL((k_topk_and_quant<B, KS, false>), dim3(1 + blocks_of(kind, q)), dim3(256), topk_quant_lds<KS>(t.dim), st, t, q);
+    else {
+        const dim3 grid((unsigned)(1 + ceil_div(q.outer * q.upr, topk_threads<KC>() / 16)));
+        if (q.K % 256)
+            hipLaunchKernelGGL((k_topk_and_quant<B, KC, true>), grid, dim3(topk_threads<KC>()), topk_quant_lds<KC>(t.dim), st, t, q);
+        else
+            hipLaunchKernelGGL((k_topk_and_quant<B, KC, false>), grid, dim3(topk_threads<KC>()), topk_quant_lds<KC>(t.dim), st, t, q);
+    }
     return check_launch();
 }
 
@@ -976,6 +1121,22 @@ int launch_topk(int b, const topk_job_t &t, quant_kind_t kind, const quant_t &q,
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad)
 {
     return x.k_contig && kpad <= KC_GATHER_MAX_KPAD;
+}
+
+bool iht_quantize_takes_outliers(int tiles) { return (tiles >= 1 && tiles <= 4) || tiles == 6; }
+
+int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_job_t &e, hipStream_t st)
+{
+    quant_t q;
+    if (describe(job, q) != KS || (b >= 0 && job.sr_seed) || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
+    switch (b) {
+    case -1: return launch_outliers_b<-1>(q, e, st);
+    case 32: return launch_outliers_b<32>(q, e, st);
+    case 64: return launch_outliers_b<64>(q, e, st);
+    case 128: return launch_outliers_b<128>(q, e, st);
+    case 256: return launch_outliers_b<256>(q, e, st);
+    }
+    return ADAHOP_E_INVALID_ARG;
 }
 
 int launch_iht_quantize(int b, const quant_job_t &job, hipStream_t st)
@@ -1035,9 +1196,16 @@ bool topk_beside_quant(int64_t dim, const quant_job_t &job)
 {
     quant_t q;
     const quant_kind_t kind = describe(job, q);
-    if (dim > TOPK_BESIDE_DIM || job.sr_seed || kind == KC_GATHER || (kind == KS && q.group)) return false;
-    const bool fits = kind == KS && topk_lds_bytes<256>((int)dim) <= (size_t)KS_LDS;
+    if (job.sr_seed || kind == KC_GATHER || (kind == KS && q.group)) return false;
+    if (kind == KC) return dim <= TOPK_BESIDE_DIM_KC;
+    if (dim > TOPK_BESIDE_DIM) return false;
+    const bool fits = topk_lds_bytes<256>((int)dim) <= (size_t)KS_LDS;
     return q.outer * q.K <= (fits ? 1ll << 31 : 64ll << 20);
+}
+
+bool iht_quantize_beside_topk(int64_t dim, const adahop_operand_t &x)
+{
+    return topk_beside_quant(dim, {&x, nullptr, nullptr, nullptr, nullptr, nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}});
 }
 
 int launch_topk_beside_quant(const topk_job_t &topk, int b, const quant_job_t &job, hipStream_t st)

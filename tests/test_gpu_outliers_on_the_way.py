@@ -1,0 +1,110 @@
+"""Row / column extraction whose bf16 products are formed by the quantiser of the K-strided operand: against the oracle, and the
+extracted rows / columns against fp64 products, at the edges of its tiles (64 columns, 256 K-elements, 16 extracted rows)."""
+import numpy as np
+import pytest
+
+from oracle import reference as orc
+from paper_2604_02525_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def bits(rng, outer, K, rows):
+    """bf16 bits of an [outer, K] operand, some rows amplified."""
+    x = rng.standard_normal((outer, K)).astype(np.float32)
+    x[rng.permutation(outer)[:rows]] *= 30.0
+    return torch.from_numpy(x).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+
+
+def values(b):
+    return (b.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+
+
+def operand(ah, logical, k_contig, pad):
+    """(device operand with `pad` elements more per stored row, all NaN; the stored array for the oracle)"""
+    a = logical if k_contig else np.ascontiguousarray(logical.T)
+    wide = np.full((a.shape[0], (a.shape[1] + 7) // 8 * 8 + pad), 0x7FC0, dtype=np.uint16)
+    wide[:, :a.shape[1]] = a
+    return ah.Operand(torch.from_numpy(wide.view(np.int16)).cuda()[:, :a.shape[1]], k_contig), a
+
+
+# (extracted operand's rows, the other's, K, k, block, extracted operand K-contiguous)
+CASES = [
+    (40, 64, 32, 1, 32, True),          # one tile, an eighth of its K
+    (64, 65, 256, 16, 256, True),       # a whole tile and one column of the next
+    (97, 200, 288, 17, 32, True),       # second tile of 32 K-elements, second tile of rows with one row
+    (130, 72, 544, 33, 32, True),
+    (200, 136, 1024, 64, 128, True),
+    (300, 1000, 1056, 96, 32, True),    # the most rows; columns that end inside a 16-byte piece
+    (300, 256, 512, 97, 64, True),      # one more: the separate kernel
+    (5000, 512, 4096, 48, 128, True),
+    (64, 12808, 256, 5, 128, True),     # more than 200 column tiles: their own order
+    (100, 12801, 512, 20, 256, False),
+    (1030, 4100, 1312, 49, 32, False),
+    (72, 20000, 32, 3, 32, False),
+    (9000, 8192, 512, 90, 64, False),   # selection too wide to stand beside a K-strided operand
+]
+
+
+@pytest.mark.parametrize("short,long,K,k,block,short_kc", CASES)
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+def test_products_on_the_way(short, long, K, k, block, short_kc, strategy):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_02525_amd import binding as ah
+    print("[case]", short, long, K, k, block, short_kc, strategy, flush=True)
+    rng = np.random.default_rng(short + long + K + k)
+    row = strategy == inputs.IHT_OE_ROW
+    S, L = bits(rng, short, K, k), bits(rng, long, K, 2)
+    (s, s_st), (l, l_st) = operand(ah, S, short_kc, 8), operand(ah, L, False, 16)
+    A, B, a_st, b_st = (s, l, s_st, l_st) if row else (l, s, l_st, s_st)
+    out = ah.adahop_gemm(A, B, strategy, block, k)
+    torch.cuda.synchronize()
+    small = short * long * K < 1 << 31
+    idx = np.sort(out["idx"].cpu().numpy())
+    mask = np.zeros(short, dtype=np.uint8)
+    mask[idx] = 1
+    assert len(set(idx.tolist())) == k and np.array_equal(out["mask"].cpu().numpy(), mask)
+    ref = orc.adahop_gemm(a_st, A.k_contig, b_st, B.k_contig, strategy, block, k) if small else None
+    if ref:
+        assert np.array_equal(idx, ref["idx"])
+        for name in ("a_codes", "b_codes", "a_scales", "b_scales"):
+            assert np.array_equal(out[name].cpu().numpy(), ref[name]), name
+    codes, scales = (out["a_codes"], out["a_scales"]) if row else (out["b_codes"], out["b_scales"])
+    # the same bits with the indices handed in, and with the other operand packed beforehand
+    other = {"b_packed" if row else "a_packed": ah.adahop_pack_operand(l, row, strategy, block)}
+    for again in (ah.adahop_gemm(A, B, strategy, block, k, idx=out["idx"].clone()), ah.adahop_gemm(A, B, strategy, block, k, **other)):
+        assert torch.equal(again["C"].view(torch.int32), out["C"].view(torch.int32))
+    assert not codes.cpu().numpy()[idx].any() and not scales.cpu().numpy()[idx].any()
+    C = out["C"].cpu().numpy().astype(np.float64)
+    got = C[idx] if row else C[:, idx].T
+    a, b = values(S[idx]), values(L)
+    # products of bf16 values are exact in fp32; a sum of K of them in fp32, in any order, is off by at most K 2^-24 of the sum of magnitudes
+    assert (np.abs(got - a @ b.T) <= K * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T)).all()
+    if ref:
+        rest = np.delete(C - ref["C"], idx, axis=0 if row else 1)
+        assert np.linalg.norm(rest) <= 1e-3 * np.linalg.norm(np.delete(ref["C"], idx, axis=0 if row else 1))
+
+
+@pytest.mark.parametrize("sr", ["short", "long"])
+def test_rounding_option(sr):
+    """A stochastically rounded operand: extracted rows still count as zero, and the products of a rounded long operand are formed
+    by themselves."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_02525_amd import binding as ah
+    print("[case] rounding", sr, flush=True)
+    rng = np.random.default_rng(7)
+    S, L = bits(rng, 300, 544, 9), bits(rng, 264, 544, 0)
+    (s, _), (l, _) = operand(ah, S, True, 0), operand(ah, L, False, 0)
+    out = ah.adahop_gemm(s, l, inputs.IHT_OE_ROW, 32, 9, **{"sr_seed_a" if sr == "short" else "sr_seed_b": 77})
+    idx = np.sort(out["idx"].cpu().numpy())
+    zero = torch.zeros(300, dtype=torch.uint8)
+    zero[torch.from_numpy(idx).long()] = 1
+    for op, key, z, seed in ((s, "a", zero.cuda(), 77 if sr == "short" else None), (l, "b", None, 77 if sr == "long" else None)):
+        codes, scales = ah.adahop_iht_quantize(op, 32, zero_outer=z, sr_seed=seed)
+        assert torch.equal(codes, out[key + "_codes"]) and torch.equal(scales, out[key + "_scales"])
+    a, b = values(S[idx]), values(L)
+    assert (np.abs(out["C"].cpu().numpy()[idx] - a @ b.T) <= 544 * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T)).all()
