@@ -119,20 +119,21 @@ size_t gemm_mx_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // product lets the quantiser write that copy as well (scales_sm_t above) and says so with sm_ready (bit 0: A, bit 1: B);
 // otherwise launch_gemm_mx re-orders the canonical scales itself where the chosen kernel needs that.
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which);
-// The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): fp32 C, at most 128 gathered K-channels, K > 1792.
+// The 256 x 128 kernel with two accumulator sets (gemm_mx_dual.hip): at most 128 gathered K-channels, K > 1792; a bf16 C of whole 4-byte
+// pairs (dual_takes_bf16).
 bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K, int kpad);
-int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
-                        const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg,
-                        int kpad, hipStream_t st);
+int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm, const uint8_t *b_codes, const uint8_t *b_sm,
+                        void *C, int64_t ldc, int c_bf16, const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);
 // Rows of C of whole 64-byte pieces: the kernels with tiles of 256 rows then stream C past the caches (see store_tile in gemm_mx.hip).
 inline bool c_rows_streamed(const void *C, int64_t row_bytes) { return aligned(C, 64) && row_bytes % 64 == 0; }
+inline bool dual_takes_bf16(const void *C, int64_t N, int64_t ldc) { return aligned(C, 4) && ldc % 2 == 0 && N % 2 == 0; }
 // Any shape, tiles of 32 .. 128 (gemm_mx_small.hip).  a_sm / b_sm: the scales are the stage-major copy, else the canonical
 // array (only for K % 256 == 0 and 4-byte aligned, or where gemm_mx_small_takes_canonical holds).
 bool gemm_mx_small_takes_canonical(int64_t K);
 int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,
                          const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
                          const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);
-int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us); // the variant for a shape and its expected time
+int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us, int variants = 5); // the variant for a shape and its expected time
 // Diagnostics: 0 = choose by shape, 1 = the 256 x 256 kernel and 2 = the 256 x 128 kernel, each wherever it can run,
 // 3 .. 6 = by shape with a forced tile walk, 7 .. 11 = a variant of the kernel with small tiles.
 void gemm_mx_force_kernel(int which);

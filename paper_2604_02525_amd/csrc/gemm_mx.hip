@@ -656,7 +656,7 @@ void gemm_mx_force_kernel(int which)
     g_force_walk.store(which >= 3 && which <= 6 ? which - 3 : -1);
 }
 
-// Which of the two kernels with tiles of 256 rows (fp32 C and at most 128 gathered K-channels; otherwise always the 256 x 256 kernel).  The
+// Which of the two kernels with tiles of 256 rows (at most 128 gathered K-channels; otherwise always the 256 x 256 kernel).  The
 // 256 x 128 kernel with two accumulator sets hides the C stores behind the next tile but moves 1.5 times the operand
 // bytes per flop from L2 into LDS and out of LDS; measured on MI355X it wins where the stores are a large part of a
 // tile's time -- K = 2048: 1.2x; K = 4096: 1.04 .. 1.13x up to about 90 M elements of C, 0.97x at 8192 x 12288 -- and
@@ -693,6 +693,12 @@ struct kernel_choice_t {
     int variant;
 };
 
+static double us_large_tiles(int64_t M, int64_t N, int64_t stages, bool dual)
+{
+    const double rounds = (double)ceil_div(ceil_div(M, TM) * ceil_div(N, dual ? 128 : TN), 256);
+    return rounds * (dual ? 5.3 + 0.66 * (double)stages : 6.2 + 1.21 * (double)stages);
+}
+
 static kernel_choice_t choose_kernel(int64_t M, int64_t N, int64_t K, int kpad)
 {
     const int forced = g_kernel_choice.load();
@@ -705,9 +711,7 @@ static kernel_choice_t choose_kernel(int64_t M, int64_t N, int64_t K, int kpad)
     if (forced >= 7) {
         c.variant = forced - 7;
     } else if (can) {
-        const double rounds = (double)ceil_div(ceil_div(M, TM) * ceil_div(N, dual ? 128 : TN), 256);
-        const double us_large = rounds * (dual ? 5.3 + 0.66 * (double)stages : 6.2 + 1.21 * (double)stages);
-        c.large = forced == 1 || forced == 2 || us_large + 1.25 <= us_small;
+        c.large = forced == 1 || forced == 2 || us_large_tiles(M, N, stages, dual) + 1.25 <= us_small;
     }
     return c;
 }
@@ -761,11 +765,23 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
 {
     if (M == 0 || N == 0) return ADAHOP_OK;
     kernel_choice_t c = choose_kernel(M, N, K, kpad);
-    if (c.large && c.dual && sizeof(OUT) == 2) { // (the kernel with two accumulator sets stores fp32 only)
-        c.dual = false;
-        if (N < TN) { // its sums are those of the 128 x 128 tiles, which add in the same order
-            c.large = false;
-            c.variant = 1;
+    // bf16 with a choice of 256 x 128 tiles: there is less of C to hide, and what is stored has to leave the accumulator registers first,
+    // so that the tiles of the fewest rounds win (all of these add in the same order).  256 x 256 / 256 x 128 / the choice between 256 x 256 and 128 x 128 where rows
+    // of C are no whole pairs, us: 1000 x 5000 x 3040 28.3 / 20.6 / 21.8, 1024 x 8192 x 8192 46.3 / 40.7, 2016 x 11008 x 4096 60.7 / 55.9, 700 x 200 x
+    // 4096 8.7 / 6.9, but 8192 x 4096 x 4096 73.1 / 76.6, 16384 x 4096 x 4096 137 / 144, 4096 x 4096 x 2048 26.9 / 28.8 (and 8192 x 8192 x 2048 93 / 86,
+    // with ldc = 8200 82 / 84).
+    if (c.large && c.dual && sizeof(OUT) == 2) {
+        const int64_t stages = ceil_div(K, 256) + kpad / 64;
+        const double us256 = us_large_tiles(M, N, stages, false);
+        const bool forced = g_kernel_choice.load() == 2;
+        if (!dual_takes_bf16(C, N, ldc) || (!forced && N >= TN && us256 <= us_large_tiles(M, N, stages, true))) {
+            double us_small = 0.0;
+            const int variant = gemm_mx_small_pick(M, N, stages, &us_small, 2); // (of 128 x 128)
+            c.dual = false;
+            if (N < TN || (!forced && us_small < us256)) {
+                c.large = false;
+                c.variant = variant;
+            }
         }
     }
     // Stage-major scales in the caller's workspace (sm_ready bit 0 / 1: the quantiser of A / B has already written them).
@@ -791,10 +807,8 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
     if (!c.large)
         return launch_gemm_mx_small(c.variant, M, N, K, a_codes, a_canonical ? a_scales : a_sm, !a_canonical, b_codes,
                                     b_canonical ? b_scales : b_sm, !b_canonical, C, ldc, sizeof(OUT) == 2, Ag, Bg, kpad, st);
-    if constexpr (sizeof(OUT) == 4) {
-        if (c.dual)
-            return launch_gemm_mx_dual(M, N, K, a_codes, a_sm, b_codes, b_sm, reinterpret_cast<float *>(C), ldc, Ag, Bg, kpad, st);
-    }
+    if (c.dual)
+        return launch_gemm_mx_dual(M, N, K, a_codes, a_sm, b_codes, b_sm, C, ldc, sizeof(OUT) == 2, Ag, Bg, kpad, st);
 
     int ncu = 0;
     rc = configure_gemm_mx(&ncu); // once per device: the compute-unit count and the kernels' LDS size

@@ -36,7 +36,6 @@ constexpr int LDS_BYTES = NBUF * STAGE_BYTES; // 156672 of the 163840 of a compu
 constexpr int NCOPY = 13;                     // copies per wave and stage: 8 of A, 4 of B, 1 of scales
 constexpr int PART1 = 4;                      // of which issued in the last step of a stage, the rest in the next three
 constexpr int STORE_STAGES = 8;               // stages of a tile that carry the stores of the previous tile
-constexpr int STORES_PER_STAGE = 16;
 
 struct frags_t {
     uint4 a[4], b[2];
@@ -144,11 +143,17 @@ __device__ __forceinline__ void read_scales(const uint8_t *buf, const state_t &t
     for (int j = 0; j < 2; ++j) sc.b[j] = *reinterpret_cast<const int *>(buf + t.sb_row + j * 32 * 8);
 }
 
-// Store r of accumulator tile ST (tile row ST / 2, column ST % 2) of set SET; cprev is the lane's pointer to
-// C[tile row 4 * (lane / 32)][lane % 32] of the wave's 128 x 64 part of that tile.
+// Where a lane's share of the wave's 128 x 64 part of a tile begins in C, and the row stride.  fp32: C[4 (lane / 32)][lane % 32].
+// bf16: a lane trades with its neighbour, so that each holds two columns of one of two rows: C[4 (lane / 32) + lane % 2][lane % 32 - lane % 2].
+template <typename OUT> struct dest_t {
+    OUT *c;
+    int64_t ldc;
+    uint32_t sel; // (bf16) byte permutation of the trade
+};
+
 // STREAM: rows of C begin at multiples of 64 bytes and leave by non-temporal stores, else by plain ones (see store_tile of the 256 x 256
 // kernel; 8752 x 4025 x 4096 121 -> 92 us, 8192 x 8192 x 2048 with ldc = 8193 210 -> 104).
-template <bool STREAM> __device__ __forceinline__ void put_c(float v, float *p)
+template <bool STREAM, typename T> __device__ __forceinline__ void put_c(T v, T *p)
 {
     if constexpr (STREAM)
         __builtin_nontemporal_store(v, p);
@@ -156,10 +161,26 @@ template <bool STREAM> __device__ __forceinline__ void put_c(float v, float *p)
         *p = v;
 }
 
-template <bool STREAM, int SET, int ST> __device__ __forceinline__ void store_one(const state_t &t, float *cprev, int64_t ldc, int r)
+// Stores of an accumulator tile per lane: 16 of one row and column each, or 8 of two columns.
+template <typename OUT> constexpr int stores_of_tile() { return sizeof(OUT) == 4 ? 16 : 8; }
+
+// Store n of accumulator tile ST (tile row ST / 2, column ST % 2) of set SET.
+template <bool STREAM, int SET, int ST> __device__ __forceinline__ void store_one(const state_t &t, const dest_t<float> &d, int n)
 {
     constexpr int i = ST >> 1, j = ST & 1;
-    put_c<STREAM>(t.acc[SET][i][j][r], &cprev[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+    put_c<STREAM>(t.acc[SET][i][j][n], &d.c[(int64_t)(i * 32 + (n >> 2) * 8 + (n & 3)) * d.ldc + j * 32]);
+}
+
+template <bool STREAM, int SET, int ST> __device__ __forceinline__ void store_one(const state_t &t, const dest_t<uint16_t> &d, int n)
+{
+    constexpr int i = ST >> 1, j = ST & 1;
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    const v2bf two = {(__bf16)t.acc[SET][i][j][2 * n], (__bf16)t.acc[SET][i][j][2 * n + 1]}; // (one instruction, nearest even)
+    const uint32_t own = __builtin_bit_cast(uint32_t, two);
+    const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1 /* quad_perm:[1,0,3,2] */, 0xf, 0xf, true);
+    const int r = 2 * n;
+    put_c<STREAM>(__builtin_amdgcn_perm(other, own, d.sel),
+                  reinterpret_cast<uint32_t *>(&d.c[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * d.ldc + j * 32]));
 }
 
 // One matrix-core step (8 instructions on fragments f, step S of the stage, into set SET) and, one after each
@@ -169,9 +190,8 @@ template <bool STREAM, int SET, int ST> __device__ __forceinline__ void store_on
 // shadow of the matrix-core instruction before them, bursts would hold the matrix core up.  Written as a
 // compile-time recursion over the instruction index Q (no loop: the order written is the order that runs).
 // BF: the stage holds gathered bf16 K-channels.
-template <bool STREAM, bool BF, int SET, int S, bool ZC, int RS, bool RSC, int C0, int C1, int ST, int R0, int R1, int Q = 0>
-__device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t *rbuf, frags_t &rf, float *cprev,
-                                     int64_t ldc)
+template <bool STREAM, bool BF, int SET, int S, bool ZC, int RS, bool RSC, int C0, int C1, int ST, int R0, int R1, int Q = 0, typename OUT>
+__device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t *rbuf, frags_t &rf, const dest_t<OUT> &prev)
 {
     if constexpr (Q < 8) {
         constexpr int i = Q >> 1, j = Q & 1, NC = C1 - C0;
@@ -202,73 +222,72 @@ __device__ __forceinline__ void step(const frags_t &f, state_t &t, const uint8_t
             }
         }
         if constexpr (ST >= 0 && R0 + Q < R1 && Q < 6) {
-            store_one<STREAM, 1 - SET, ST>(t, cprev, ldc, R0 + Q);
+            store_one<STREAM, 1 - SET, ST>(t, prev, R0 + Q);
             ADAHOP_PIN();
         }
-        step<STREAM, BF, SET, S, ZC, RS, RSC, C0, C1, ST, R0, R1, Q + 1>(f, t, rbuf, rf, cprev, ldc);
+        step<STREAM, BF, SET, S, ZC, RS, RSC, C0, C1, ST, R0, R1, Q + 1>(f, t, rbuf, rf, prev);
     }
 }
 
 // One pipeline stage: four matrix-core steps on the fragments of the LDS buffer at byte offset rb (advanced to
 // the next buffer on return).  ST: the accumulator tile of the previous tile's set stored during this stage
 // (-1: none).  ZC: first stage of a tile (its first step starts the accumulators from 0).
-template <int NBF, bool STREAM, bool BF, int SET, int ST, bool ZC>
-__device__ __forceinline__ void run_stage(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
+template <int NBF, bool STREAM, bool BF, int SET, int ST, bool ZC, typename OUT>
+__device__ __forceinline__ void run_stage(state_t &t, const uint8_t *smem, uint32_t &rb, const dest_t<OUT> &prev)
 {
+    constexpr int PER = stores_of_tile<OUT>(), A = (PER + 2) / 3, B = (2 * PER + 1) / 3; // spread over three steps
     const uint8_t *st = smem + rb;
     const uint32_t rn = next_buf(rb);
     const uint8_t *sn = smem + rn;
     // the copies of a stage: PART1 during the last step of the stage two before it (after that stage's barrier),
     // the rest during the first three steps of the stage before it
-    step<STREAM, BF, SET, 0, ZC, 1, false, PART1, PART1 + 3, ST, 0, 6>(t.f0, t, st, t.f1, cprev, ldc);
-    step<STREAM, BF, SET, 1, false, 2, false, PART1 + 3, PART1 + 6, ST, 6, 11>(t.f1, t, st, t.f0, cprev, ldc);
-    step<STREAM, BF, SET, 2, false, 3, false, PART1 + 6, NCOPY, ST, 11, 16>(t.f0, t, st, t.f1, cprev, ldc);
+    step<STREAM, BF, SET, 0, ZC, 1, false, PART1, PART1 + 3, ST, 0, A>(t.f0, t, st, t.f1, prev);
+    step<STREAM, BF, SET, 1, false, 2, false, PART1 + 3, PART1 + 6, ST, A, B>(t.f1, t, st, t.f0, prev);
+    step<STREAM, BF, SET, 2, false, 3, false, PART1 + 6, NCOPY, ST, B, PER>(t.f0, t, st, t.f1, prev);
     advance<NBF>(t);
     // Younger than the last copy of the next stage: the NCOPY copies of the stage after it and this stage's stores.
-    constexpr int X = NCOPY + (ST >= 0 ? STORES_PER_STAGE : 0);
+    constexpr int X = NCOPY + (ST >= 0 ? PER : 0);
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"(X) : "memory");
-    step<STREAM, BF, SET, 3, false, 0, true, 0, PART1, -1, 0, 0>(t.f1, t, sn, t.f0, cprev, ldc);
+    step<STREAM, BF, SET, 3, false, 0, true, 0, PART1, -1, 0, 0>(t.f1, t, sn, t.f0, prev);
     t.sc = t.scn;
     rb = rn;
 }
 
-template <int NBF, bool STREAM, int SET, int ST>
-__device__ __forceinline__ void store_stages(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
+template <int NBF, bool STREAM, int SET, int ST, typename OUT>
+__device__ __forceinline__ void store_stages(state_t &t, const uint8_t *smem, uint32_t &rb, const dest_t<OUT> &prev)
 {
     if constexpr (ST < STORE_STAGES) {
-        run_stage<NBF, STREAM, (ST < NBF), SET, ST, ST == 0>(t, smem, rb, cprev, ldc);
-        store_stages<NBF, STREAM, SET, ST + 1>(t, smem, rb, cprev, ldc);
+        run_stage<NBF, STREAM, (ST < NBF), SET, ST, ST == 0>(t, smem, rb, prev);
+        store_stages<NBF, STREAM, SET, ST + 1>(t, smem, rb, prev);
     }
 }
 
 // All stages of one tile into set SET; STORES: the other set holds a finished tile, whose stores go along.
-template <int NBF, bool STREAM, int SET, bool STORES>
-__device__ __forceinline__ void run_tile(state_t &t, const uint8_t *smem, uint32_t &rb, float *cprev, int64_t ldc)
+template <int NBF, bool STREAM, int SET, bool STORES, typename OUT>
+__device__ __forceinline__ void run_tile(state_t &t, const uint8_t *smem, uint32_t &rb, const dest_t<OUT> &prev)
 {
     int l;
     if constexpr (STORES) {
-        store_stages<NBF, STREAM, SET, 0>(t, smem, rb, cprev, ldc);
+        store_stages<NBF, STREAM, SET, 0>(t, smem, rb, prev);
         l = STORE_STAGES;
     } else {
-        run_stage<NBF, STREAM, (NBF > 0), SET, -1, true>(t, smem, rb, cprev, ldc);
+        run_stage<NBF, STREAM, (NBF > 0), SET, -1, true>(t, smem, rb, prev);
         l = 1;
         if constexpr (NBF == 2) {
-            run_stage<NBF, STREAM, true, SET, -1, false>(t, smem, rb, cprev, ldc);
+            run_stage<NBF, STREAM, true, SET, -1, false>(t, smem, rb, prev);
             l = 2;
         }
     }
-    for (; l < t.n; ++l) run_stage<NBF, STREAM, false, SET, -1, false>(t, smem, rb, cprev, ldc);
+    for (; l < t.n; ++l) run_stage<NBF, STREAM, false, SET, -1, false>(t, smem, rb, prev);
 }
 
-template <bool STREAM, int SET> __device__ __forceinline__ void store_all(const state_t &t, float *c, int64_t ldc)
+template <bool STREAM, int SET, int ST = 0, typename OUT> __device__ __forceinline__ void store_all(const state_t &t, const dest_t<OUT> &d)
 {
+    if constexpr (ST < 8) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                put_c<STREAM>(t.acc[SET][i][j][r], &c[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+        for (int n = 0; n < stores_of_tile<OUT>(); ++n) store_one<STREAM, SET, ST>(t, d, n);
+        store_all<STREAM, SET, ST + 1>(t, d);
+    }
 }
 
 } // namespace dual
@@ -278,12 +297,12 @@ template <bool STREAM, int SET> __device__ __forceinline__ void store_all(const 
 // its neighbour, and so does the last stage of a ragged K (see the 256 x 256 kernel).
 // NBF: stages of gathered bf16 K-channels in front of the FP4 stages of a tile (kpad = 64 NBF; 0, 1 or 2: they lie among the
 // stages that carry the stores of the tile before, each of them an instance of the stage's code).
-template <int NBF, bool STREAM>
+template <int NBF, bool STREAM, typename OUT>
 __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *__restrict__ a_codes,
                                                       const uint8_t *__restrict__ a_scales_sm,
                                                       const uint8_t *__restrict__ b_codes,
                                                       const uint8_t *__restrict__ b_scales_sm, int64_t M, int64_t N,
-                                                      float *__restrict__ C, int64_t ldc, const uint16_t *__restrict__ Ag,
+                                                      OUT *__restrict__ C, int64_t ldc, const uint16_t *__restrict__ Ag,
                                                       const uint16_t *__restrict__ Bg, int tiles_m, int tiles_n, int group_m)
 {
     using namespace dual;
@@ -388,7 +407,9 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
     t.left = t.n;
     t.cbuf = 0;
 
-    auto c_of = [&](int64_t mm, int64_t nn) { return C + (mm + wm * 128 + h * 4) * ldc + nn + wn * 64 + l32; };
+    const int odd = sizeof(OUT) == 2 ? lane & 1 : 0;
+    const int64_t c_lane = (int64_t)(wm * 128 + h * 4 + odd) * ldc + wn * 64 + l32 - odd;
+    auto c_of = [&](int64_t mm, int64_t nn) { return dest_t<OUT>{C + mm * ldc + nn + c_lane, ldc, odd ? 0x03020706u : 0x05040100u}; };
     auto look_ahead = [&](bool &more, int64_t &m0n, int64_t &n0n) {
         const int vn = v + grid;
         more = vn < ntiles; // the same for the whole workgroup
@@ -411,25 +432,25 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
     for (int q = 0; q < 6; ++q) read_item(smem, t, 0, q, t.f0);
     read_scales(smem, t, t.sc);
 
-    float *cprev = c_of(m0, n0);
-    run_tile<NBF, STREAM, 0, false>(t, smem, rb, cprev, ldc);
+    dest_t<OUT> prev = c_of(m0, n0);
+    run_tile<NBF, STREAM, 0, false>(t, smem, rb, prev);
     for (;;) {
-        cprev = c_of(m0, n0); // the tile just finished, in set 0
+        prev = c_of(m0, n0); // the tile just finished, in set 0
         if (!more) {
-            store_all<STREAM, 0>(t, cprev, ldc);
+            store_all<STREAM, 0>(t, prev);
             break;
         }
         v += grid, m0 = m0n, n0 = n0n;
         look_ahead(more, m0n, n0n);
-        run_tile<NBF, STREAM, 1, true>(t, smem, rb, cprev, ldc);
-        cprev = c_of(m0, n0); // in set 1
+        run_tile<NBF, STREAM, 1, true>(t, smem, rb, prev);
+        prev = c_of(m0, n0); // in set 1
         if (!more) {
-            store_all<STREAM, 1>(t, cprev, ldc);
+            store_all<STREAM, 1>(t, prev);
             break;
         }
         v += grid, m0 = m0n, n0 = n0n;
         look_ahead(more, m0n, n0n);
-        run_tile<NBF, STREAM, 0, true>(t, smem, rb, cprev, ldc);
+        run_tile<NBF, STREAM, 0, true>(t, smem, rb, prev);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the copies begun for a tile that does not follow
 }
@@ -439,6 +460,17 @@ __global__ __launch_bounds__(256) void k_gemm_mx_dual(int64_t K, const uint8_t *
 bool gemm_mx_dual_eligible(int64_t M, int64_t N, int64_t K, int kpad)
 {
     return kpad % 64 == 0 && kpad <= 128 && K > 256 * (dual::STORE_STAGES - 1) && M >= dual::TM && N >= dual::TN;
+}
+
+template <typename OUT> static int allow_dual_lds()
+{
+    const void *kernels[6] = {reinterpret_cast<const void *>(&k_gemm_mx_dual<0, true, OUT>), reinterpret_cast<const void *>(&k_gemm_mx_dual<0, false, OUT>),
+                              reinterpret_cast<const void *>(&k_gemm_mx_dual<1, true, OUT>), reinterpret_cast<const void *>(&k_gemm_mx_dual<1, false, OUT>),
+                              reinterpret_cast<const void *>(&k_gemm_mx_dual<2, true, OUT>), reinterpret_cast<const void *>(&k_gemm_mx_dual<2, false, OUT>)};
+    int rc = ADAHOP_OK;
+    for (const void *f : kernels)
+        if (rc == ADAHOP_OK) rc = check_hip(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dual::LDS_BYTES));
+    return rc;
 }
 
 // Once per device: the compute-unit count and the kernel's LDS size.  Host-side calls, nothing queued.
@@ -453,13 +485,9 @@ int configure_gemm_mx_dual(int *ncu_out)
     if (once.need(dev) || ncu == 0) {
         rc = check_hip(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
         if (rc != ADAHOP_OK) return rc;
-        const void *kernels[6] = {reinterpret_cast<const void *>(&k_gemm_mx_dual<0, true>), reinterpret_cast<const void *>(&k_gemm_mx_dual<0, false>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_dual<1, true>), reinterpret_cast<const void *>(&k_gemm_mx_dual<1, false>),
-                                  reinterpret_cast<const void *>(&k_gemm_mx_dual<2, true>), reinterpret_cast<const void *>(&k_gemm_mx_dual<2, false>)};
-        for (const void *f : kernels) {
-            rc = check_hip(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dual::LDS_BYTES));
-            if (rc != ADAHOP_OK) return rc;
-        }
+        rc = allow_dual_lds<float>();
+        if (rc == ADAHOP_OK) rc = allow_dual_lds<uint16_t>();
+        if (rc != ADAHOP_OK) return rc;
         if (dev >= 0 && dev < 64) cu_count[dev].store(ncu, std::memory_order_relaxed);
         once.mark(dev);
     }
@@ -467,8 +495,9 @@ int configure_gemm_mx_dual(int *ncu_out)
     return ADAHOP_OK;
 }
 
-int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
-                        const uint8_t *b_codes, const uint8_t *b_sm, float *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg,
+template <typename OUT>
+static int launch_dual_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm,
+                        const uint8_t *b_codes, const uint8_t *b_sm, OUT *C, int64_t ldc, const uint16_t *Ag, const uint16_t *Bg,
                         int kpad, hipStream_t st)
 {
     int ncu = 0;
@@ -485,9 +514,16 @@ int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes,
                            tiles_m, tiles_n, group_m);
         return check_launch();
     };
-    if (c_rows_streamed(C, ldc * 4))
-        return kpad == 0 ? launch(&k_gemm_mx_dual<0, true>) : kpad == 64 ? launch(&k_gemm_mx_dual<1, true>) : launch(&k_gemm_mx_dual<2, true>);
-    return kpad == 0 ? launch(&k_gemm_mx_dual<0, false>) : kpad == 64 ? launch(&k_gemm_mx_dual<1, false>) : launch(&k_gemm_mx_dual<2, false>);
+    if (c_rows_streamed(C, ldc * (int64_t)sizeof(OUT)))
+        return kpad == 0 ? launch(&k_gemm_mx_dual<0, true, OUT>) : kpad == 64 ? launch(&k_gemm_mx_dual<1, true, OUT>) : launch(&k_gemm_mx_dual<2, true, OUT>);
+    return kpad == 0 ? launch(&k_gemm_mx_dual<0, false, OUT>) : kpad == 64 ? launch(&k_gemm_mx_dual<1, false, OUT>) : launch(&k_gemm_mx_dual<2, false, OUT>);
+}
+
+int launch_gemm_mx_dual(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_sm, const uint8_t *b_codes, const uint8_t *b_sm,
+                        void *C, int64_t ldc, int c_bf16, const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st)
+{
+    return c_bf16 ? launch_dual_t(M, N, K, a_codes, a_sm, b_codes, b_sm, static_cast<uint16_t *>(C), ldc, Ag, Bg, kpad, st)
+                  : launch_dual_t(M, N, K, a_codes, a_sm, b_codes, b_sm, static_cast<float *>(C), ldc, Ag, Bg, kpad, st);
 }
 
 } // namespace adahop

@@ -551,11 +551,11 @@ static int launch_small_t(int variant, int64_t M, int64_t N, int64_t K, const ui
     return ADAHOP_E_INVALID_ARG;
 }
 
-// The fastest variant for a product of `stages` pipeline stages, and what it is expected to take.
-int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us)
+// The fastest of the first `variants` variants for a product of `stages` pipeline stages, and what it is expected to take.
+int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us, int variants)
 {
     int best = 0;
-    for (int v = 0; v < 5; ++v) {
+    for (int v = 0; v < variants; ++v) {
         const small::cost_t &c = small::COST[v];
         const double L = (double)ceil_div(ceil_div(M, c.tm) * ceil_div(N, c.tn), 256);
         const double each = c.alone > c.busy * L ? c.alone : c.busy * L;

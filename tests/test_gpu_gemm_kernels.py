@@ -223,8 +223,8 @@ def test_small_tiles_with_k_channels(ah, force, kernel, M, N, K, k):
                                          (300, 130, 2080, 0, 3), (520, 200, 2304, 100, 1)])
 def test_bf16_output_of_any_alignment(ah, force, kernel, M, N, K, k, gap):
     """Widths and row strides that are no multiples of 16 bytes: the bits of the fp32 product rounded to nearest even.  Chosen by shape
-    these products are taken by small tiles for either type; with the two-set kernel forced, which has no bf16 form, the bf16 product goes to
-    the 256 x 256 tiles, or with N < 256 to 128 x 128 tiles, and is compared with the fp32 product of the two-set kernel."""
+    these products are taken by small tiles for either type; with the two-set kernel forced, which stores bf16 in pairs, the bf16 product with
+    other rows goes to the 256 x 256 tiles, or with N < 256 to 128 x 128 tiles, and is compared with the fp32 product of the two-set kernel."""
     A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 90, col_outliers=(5, 50.0, 50.0)), True)
     B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 91), True)
     say("bf16 output of any alignment", kernel, (M, N, K, k, gap))
@@ -272,3 +272,21 @@ def test_two_set_kernel_with_k_channels(ah, force, M, N, K, k):
     want = ah.adahop_gemm(A, B, inputs.IHT_OE_K, 32, k)["C"]
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("M,N,K,k,gap", [(256, 128, 2048, 0, 0), (300, 130, 1824, 0, 2), (513, 386, 2080, 20, 6), (1000, 650, 2304, 128, 0),
+                                         (4352, 4098, 2048, 70, 30), (2560, 7936, 2048, 0, 0)])
+def test_two_set_kernel_with_bf16_output(ah, force, M, N, K, k, gap):
+    """Pairs of columns from the accumulators of neighbouring lanes, with none, one and two bf16 stages, one tile and several (both
+    accumulator sets) per workgroup, streamed rows and others: the kernel's own fp32 sums rounded to nearest even."""
+    A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 97, col_outliers=(5, 50.0, 50.0)), True)
+    B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 98), True)
+    say("two accumulator sets, bf16", (M, N, K, k, gap))
+    force(DUAL)
+    strategy = inputs.IHT_OE_K if k else inputs.IHT
+    want = ah.adahop_gemm(A, B, strategy, 32, k)["C"].to(torch.bfloat16)
+    room = torch.full((M, N + gap), 7.0, dtype=torch.bfloat16, device="cuda")
+    ah.adahop_gemm(A, B, strategy, 32, k, Cout=room[:, :N])
+    torch.cuda.synchronize()
+    assert torch.equal(room[:, :N].view(torch.int16), want.view(torch.int16))
+    assert bool((room[:, N:] == 7.0).all())
