@@ -774,26 +774,26 @@ __device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uin
 // and 133 -> 122 us ([8192][28672]); 384, 320 and 224 column tiles 11 .. 13 % faster; 256 column tiles 7 % faster
 // or 5 % slower by K; with 192 column tiles and fewer the plain order is as fast or up to 10 % faster and is kept
 // (group == 0).
-__device__ __forceinline__ void ks_order(unsigned group, uint64_t ny, unsigned &bx, unsigned &by)
+// Workgroup L of nx column tiles x ny K-blocks.
+__device__ __forceinline__ void ks_order(unsigned group, uint32_t nx, uint32_t magic, uint32_t ny, uint32_t L, uint32_t &bx, uint32_t &by)
 {
-    if (!group) return;
-    const uint64_t nx = gridDim.x, L = by * nx + bx, full = nx / group * group;
-    if (L < full * ny) {
-        const uint64_t r = L % (group * ny);
-        bx = (unsigned)(L / (group * ny) * group + r % group);
-        by = (unsigned)(r / group);
-    } else { // the last, narrower group
-        const uint64_t r = L - full * ny, wdt = nx - full;
-        bx = (unsigned)(full + r % wdt);
-        by = (unsigned)(r / wdt);
+    if (!group) {
+        by = row_of_unit(L, nx, magic);
+        bx = L - by * nx;
+        return;
     }
+    const uint32_t full = nx / group * group, whole = full * ny;
+    const uint32_t per = L < whole ? group : nx - full; // (the last group may be narrower)
+    const uint32_t in = L < whole ? L : L - whole, r = in % (per * ny);
+    bx = (L < whole ? in / (per * ny) * per : full) + r % per;
+    by = r / per;
 }
 
 template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(quant_t q)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[KS_LDS];
-    unsigned bx = blockIdx.x, by = blockIdx.y;
-    ks_order(q.group, gridDim.y, bx, by);
+    uint32_t bx, by;
+    ks_order(q.group, q.col_tiles, q.tile_magic, q.upr, blockIdx.x, bx, by);
     quant_ks_tile<B, SR>(q, bx, by, lds);
 }
 
@@ -810,17 +810,17 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // registers (each wave reading its fragments from memory: 103 in place of 92 us in the first example; the matrix cores' own time is a tenth).
 //
 // The extracted rows are those that the other operand's quantiser has copied out, or (idx) lie in that operand where it is
-// K-contiguous: then its quantiser need not know the selection, and the workgroups of one row more of the grid set the codes and scales of
-// the extracted rows to zero.  B = -1: an operand that is packed already, the same products by themselves.
+// K-contiguous: then its quantiser need not know the selection, and a workgroup more for each extracted row sets its codes and scales
+// to zero.  B = -1: an operand that is packed already, the same products by themselves.
 template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_ks16_outliers(quant_t q, outlier_job_t e)
 {
     constexpr int TILE_LDS = RT * 8192 > KS_LDS ? RT * 8192 : KS_LDS;
     __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS + RT * 16 * 8];
     int64_t *const row_at = reinterpret_cast<int64_t *>(lds + TILE_LDS);
     const int64_t K = q.K;
-    unsigned bx = blockIdx.x, slice = blockIdx.y;
-    if ((int)slice == e.nslice) { // the extracted rows of the other operand's codes and scales
-        for (int t = (int)bx; t < e.k; t += (int)gridDim.x) {
+    const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
+    if (blockIdx.x >= tiles) { // the extracted rows of the other operand's codes and scales
+        for (int t = (int)(blockIdx.x - tiles); t < e.k; t += (int)(gridDim.x - tiles)) {
             const int64_t o = e.idx[t];
             for (int64_t i = threadIdx.x; i < K / 32; i += 256) {
                 *reinterpret_cast<uint4 *>(e.codes + o * (K >> 1) + i * 16) = make_uint4(0, 0, 0, 0);
@@ -831,7 +831,8 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
         }
         return;
     }
-    ks_order(q.group, (uint64_t)e.nslice, bx, slice);
+    uint32_t bx, slice;
+    ks_order(q.group, q.col_tiles, q.tile_magic, (uint32_t)e.nslice, blockIdx.x, bx, slice);
     const int64_t o0 = (int64_t)bx * KS_COLS;
     for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
         const int r = min(t, e.k - 1);
@@ -904,23 +905,25 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
     }
 }
 
-// Both operands of a product in one launch: the workgroups below `na` take the first, the others the second.  A launch costs at
+// Both operands of a product in one launch: the workgroups below `na` take the first, the others the second; a K-strided one beside a
+// K-contiguous one goes first (its workgroups take longest).  A launch costs at
 // least 4 us next to its neighbours (the last workgroups of one kernel run alone, and so do the first of the next), half of
 // what an operand of 8 M elements takes.
 enum quant_kind_t { KC, KC_GATHER, KS };
 template <quant_kind_t OP> constexpr int quant_lds() { return OP == KS ? KS_LDS : OP == KC_GATHER ? KC_GATHER_LDS : 16; }
 
-template <int B, quant_kind_t OP, bool TAIL, int NT = 256>
+template <int B, quant_kind_t OP, bool TAIL, int NT = 256, bool SR = false>
 __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, uint8_t *lds)
 {
     if constexpr (OP == KS) {
-        const uint32_t by = row_of_unit(block, q.col_tiles, q.tile_magic);
-        quant_ks_tile<B, false>(q, block - by * q.col_tiles, by, lds);
+        uint32_t bx, by;
+        ks_order(q.group, q.col_tiles, q.tile_magic, q.upr, block, bx, by);
+        quant_ks_tile<B, SR>(q, bx, by, lds);
     } else if constexpr (OP == KC_GATHER) {
-        quant_kc_gather_rows<B, false, TAIL>(q, block, lds);
+        quant_kc_gather_rows<B, SR, TAIL>(q, block, lds);
     } else {
         const uint32_t u = (block * (uint32_t)NT + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
-        quant_kc_unit<B, false, TAIL>(q, r, u - r * q.upr, r < q.outer);
+        quant_kc_unit<B, SR, TAIL>(q, r, u - r * q.upr, r < q.outer);
     }
 }
 
@@ -951,6 +954,19 @@ __global__ __launch_bounds__(256) void k_quant_two(quant_t qa, quant_t qb, uint3
         quant_block<B, OPB, TAIL>(qb, blockIdx.x - na, lds);
 }
 
+// A K-strided operand rounded to nearest and a stochastically rounded one in one launch, in this order: the second is bound by its vector
+// instructions (8192 x 11008: 79 us, of which the memory takes 46) and starts while the first, bound by the memory, ends.  Whole calls, two
+// launches / this order / the other / workgroups mixed evenly, us: dgrad 8192 x 4096 x 11008 244 / 241 / 242 / 248, 2048 x 8192 x 8192 112.8 / 107.7 / 109.8 /
+// 122.6, 2048 x 11008 x 4096 87.9 / 77.6 / 78.7 / 79.9, 47 x 4096 x 28672 87.7 / 84.1 / 84.8 / 82.6, wgrad 4096 x 4096 x 8192 105.2 / 99.6 / 102.2 / 107.9.
+template <int B, quant_kind_t OPA, bool TAIL> __global__ __launch_bounds__(256) void k_quant_two_sr(quant_t qa, quant_t qb, uint32_t nb)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[KS_LDS];
+    if (blockIdx.x < nb)
+        quant_block<B, KS, false>(qb, blockIdx.x, lds);
+    else
+        quant_block<B, OPA, TAIL, 256, true>(qa, blockIdx.x - nb, lds);
+}
+
 // The descriptor of an operand and the kernel kind that takes it.
 quant_kind_t describe(const quant_job_t &j, quant_t &q)
 {
@@ -978,6 +994,13 @@ quant_kind_t describe(const quant_job_t &j, quant_t &q)
     return KC_GATHER;
 }
 
+// Whether row_of_unit is exact for all units of a K-contiguous operand that is taken without a grid of its own (and of K-strided ones: their order
+// is another one above KS_GROUP_FROM column tiles).
+bool counts_flat(quant_kind_t kind, const quant_t &q) { return kind != KC || (uint64_t)(q.outer * q.upr + 64) * q.upr < (uint64_t)1 << 32; }
+
+// Workgroups of 256 threads that one launch takes (its threads are counted in 32 bits).
+constexpr uint64_t MAX_BLOCKS = (1u << 24) - 1;
+
 uint32_t blocks_of(quant_kind_t kind, const quant_t &q)
 {
     if (kind == KS) return q.col_tiles * q.upr;
@@ -989,7 +1012,7 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
 {
     const bool tail = q.K % 256 != 0;
     if (kind == KS) {
-        hipLaunchKernelGGL((k_quant_ks16<B, SR>), dim3(q.col_tiles, q.upr), dim3(256), 0, st, q);
+        hipLaunchKernelGGL((k_quant_ks16<B, SR>), dim3(blocks_of(KS, q)), dim3(256), 0, st, q);
     } else if (kind == KC_GATHER) {
         const dim3 grid(blocks_of(KC_GATHER, q));
         if (tail)
@@ -1014,7 +1037,7 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
 
 template <int B> int launch_outliers_b(const quant_t &q, const outlier_job_t &e, hipStream_t st)
 {
-    const dim3 grid(q.col_tiles, (unsigned)(e.nslice + (e.codes ? 1 : 0)));
+    const dim3 grid(q.col_tiles * (uint32_t)e.nslice + (uint32_t)(e.codes ? e.k : 0));
     switch (e.tiles) {
     case 1: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 1>), grid, dim3(256), 0, st, q, e); break;
     case 2: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 2>), grid, dim3(256), 0, st, q, e); break;
@@ -1037,11 +1060,11 @@ template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind
     typedef std::integral_constant<quant_kind_t, KS> ks_t;
     auto pick = [&](auto tail) {
         if (ka == KC && kb == KC) go(kc_t(), kc_t(), tail);
-        if (ka == KC && kb == KS) go(kc_t(), ks_t(), tail);
+        if (ka == KS && kb == KC) go(ks_t(), kc_t(), tail);
         if (ka == KC_GATHER && kb == KC_GATHER) go(kg_t(), kg_t(), tail);
-        if (ka == KC_GATHER && kb == KS) go(kg_t(), ks_t(), tail);
+        if (ka == KS && kb == KC_GATHER) go(ks_t(), kg_t(), tail);
     };
-    if (ka == KS)
+    if (ka == KS && kb == KS)
         go(ks_t(), ks_t(), std::false_type()); // (no kernel of a K-strided operand depends on it)
     else if (qa.K % 256)
         pick(std::true_type());
@@ -1054,6 +1077,19 @@ template <quant_kind_t OP> size_t topk_quant_lds(int dim)
 {
     const size_t topk = topk_lds_bytes<topk_threads<OP>()>(dim), own = OP == KS ? (size_t)KS_LDS : 0;
     return topk > own ? topk : own;
+}
+
+template <int B> int launch_two_sr_b(quant_kind_t ka, const quant_t &qa, const quant_t &qb, hipStream_t st)
+{
+    const uint32_t nb = blocks_of(KS, qb);
+    const dim3 grid(blocks_of(ka, qa) + nb);
+    if (ka == KS)
+        hipLaunchKernelGGL((k_quant_two_sr<B, KS, false>), grid, dim3(256), 0, st, qa, qb, nb);
+    else if (qa.K % 256)
+        hipLaunchKernelGGL((k_quant_two_sr<B, KC, true>), grid, dim3(256), 0, st, qa, qb, nb);
+    else
+        hipLaunchKernelGGL((k_quant_two_sr<B, KC, false>), grid, dim3(256), 0, st, qa, qb, nb);
+    return check_launch();
 }
 
 template <int B, quant_kind_t OP, bool TAIL> int allow_topk_lds()
@@ -1107,6 +1143,12 @@ int launch_two(int b, quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const
     ADAHOP_DISPATCH(b, ADAHOP_TWO)
 #undef ADAHOP_TWO
 }
+int launch_two_sr(int b, quant_kind_t ka, const quant_t &qa, const quant_t &qb, hipStream_t st)
+{
+#define ADAHOP_TWO_SR(BB) launch_two_sr_b<BB>(ka, qa, qb, st)
+    ADAHOP_DISPATCH(b, ADAHOP_TWO_SR)
+#undef ADAHOP_TWO_SR
+}
 int launch_topk(int b, const topk_job_t &t, quant_kind_t kind, const quant_t &q, hipStream_t st)
 {
 #define ADAHOP_TOPK(BB) launch_topk_b<BB>(t, kind, q, st)
@@ -1147,23 +1189,29 @@ int launch_iht_quantize(int b, const quant_job_t &job, hipStream_t st)
     return launch_one(b, job.sr_seed != nullptr, kind, q, st);
 }
 
-// Operands of up to 64 M elements together share a launch; rows of both x K, us in two launches / in one, both K-contiguous | both K-strided:
-//   2048 + 2048 x 2048 (8 M)     8.3 /  5.7 | 10.1 /  6.8      8192 +  8192 x 4096 (64 M)     35.7 / 33.1 | 40.4 / 37.2
-//   8192 + 2048 x 2048 (20 M)   16.1 / 11.7 | 16.3 / 12.5     16384 +  8192 x 4096 (96 M)     50.1 / 47.2 | 58.7 / 59.0
-//   8192 + 4096 x 4096 (48 M)   28.0 / 25.3 | 31.8 / 27.2      8192 + 12288 x 8192 (160 M)    80.9 / 74.7 | 97.5 / 91.7
-// What is gained is a launch and its gap, whatever the size; the line lies where every measured pair gains.  A K-contiguous operand beside a
-// K-strided one runs with the registers and the LDS of the latter, half as many waves per compute unit: 8 M 8.8 / 6.7 us, 20 M 16.9 /
-// 15.7, 4096 + 4096 x 3040 (24 M) 16.9 / 17.1, 48 M 29.7 / 30.7, 96 M 53.0 / 55.2, so that the line lies at 24 M there (one pair above it
-// still gains: 8192 + 11008 x 2048, 37.5 M, 25.3 / 23.2).
+// Both operands share a launch: what is gained is a launch and its gap, whatever the size.  Whole calls, two launches / one, us: forward, both
+// K-contiguous, 8192 x 8192 x 4096 181 / 175.8, 16384 x 8192 x 4096 338 / 335, with 82 K-channels copied out 382 / 379; weight gradient, both
+// K-strided, 4096 x 4096 x 16384 197.7 / 190.2, 11008 x 4096 x 8192 243.8 / 241.5; input gradient, one of each, 1024 x 4096 x 11008 67.3 /
+// 65.0, 512 x 8192 x 8192 69.4 / 64.6, 8192 x 4096 x 4096 107.8 / 106.  The K-contiguous one of such a pair runs with the registers and the LDS of
+// the other's kernel, half as many waves per compute unit, which costs more than the launch where it is large and the other one
+// is not: 16384 x 2048 x 4096 111 / 114.
 int launch_iht_quantize_two(int b, const quant_job_t &ja, const quant_job_t &jb, hipStream_t st)
 {
     quant_t qa, qb;
     const quant_kind_t ka = describe(ja, qa), kb = describe(jb, qb);
-    const int64_t together = (ka == KS) == (kb == KS) ? 64ll << 20 : 24ll << 20;
     const bool copies_differ = ka != kb && kb != KS && ka != KS; // one K-contiguous operand with its channels copied out, one without
-    if (qa.K == qb.K && !copies_differ && !ja.sr_seed && !jb.sr_seed && !(ka == KS && qa.group) && !(kb == KS && qb.group) &&
-        (qa.outer + qb.outer) * qa.K <= together)
-        return ka == KS && kb != KS ? launch_two(b, kb, qb, ka, qa, st) : launch_two(b, ka, qa, kb, qb, st);
+    const bool mixed = (ka == KS) != (kb == KS);
+    const int64_t n_kc = (ka == KS ? qb.outer : qa.outer) * qa.K, n_ks = (ka == KS ? qa.outer : qb.outer) * qa.K; // (mixed)
+    const bool pays = !mixed || n_kc <= 48ll << 20 || n_kc <= 2 * n_ks;
+    if (qa.K == qb.K && pays && !copies_differ && !ja.sr_seed && !jb.sr_seed && counts_flat(ka, qa) && counts_flat(kb, qb) &&
+        (uint64_t)blocks_of(ka, qa) + blocks_of(kb, qb) <= MAX_BLOCKS)
+        return kb == KS && ka != KS ? launch_two(b, kb, qb, ka, qa, st) : launch_two(b, ka, qa, kb, qb, st);
+    if (qa.K == qb.K && (ja.sr_seed != nullptr) != (jb.sr_seed != nullptr)) {
+        const bool first = ja.sr_seed != nullptr;
+        const quant_kind_t ks = first ? ka : kb, kn = first ? kb : ka;
+        const quant_t &qs = first ? qa : qb, &qn = first ? qb : qa;
+        if (kn == KS && ks != KC_GATHER && counts_flat(ks, qs) && (uint64_t)blocks_of(ka, qa) + blocks_of(kb, qb) <= MAX_BLOCKS) return launch_two_sr(b, ks, qs, qn, st);
+    }
     const int rc = launch_one(b, ja.sr_seed != nullptr, ka, qa, st);
     return rc != ADAHOP_OK ? rc : launch_one(b, jb.sr_seed != nullptr, kb, qb, st);
 }
@@ -1184,9 +1232,8 @@ int configure_iht_quantize()
 
 // The selection by 256 threads, the workgroup size of the quantisers, takes up to 15 us in place of the 9 us of 1024 threads (8192
 // keys), but then 9 us less of everything else: 9 + 31 -> 16 + 19 us for 8192 x 4096 beside a K-strided 4096 x 4096, 9 + 44 -> 22 +
-// 24 for two K-strided operands of 8192 tokens x 4096.  Not for operands that are rounded stochastically (no such instance) or whose
-// K-strided order is a special one, and above 64 M elements only where the keys fit into the LDS that every workgroup of the
-// launch has anyway: more of it costs waves in flight.  Whole calls with 1 % of the rows extracted (M x N x K), selection first / beside, the
+// 24 for two K-strided operands of 8192 tokens x 4096.  Not for operands that are rounded stochastically (no such instance), and
+// above 64 M elements of a K-strided one only where the keys fit into the LDS that every workgroup of the launch has anyway: more of it costs waves in flight.  Whole calls with 1 % of the rows extracted (M x N x K), selection first / beside, the
 // other operand K-strided | K-contiguous:
 //   8192 x 4096 x 4096 (16 M)    132.8 / 128.4 | 130.4 / 128.2      8192 x  8192 x 8192 (64 M)   380.7 / 372.9 | 373.4 / 375.1
 //   4096 x 11008 x 4096 (43 M)   173.6 / 163.0 | 170.6 / 164.7      8192 x 12288 x 8192 (96 M)   511.6 / 504.2 | 502.6 / 509.2
@@ -1196,8 +1243,8 @@ bool topk_beside_quant(int64_t dim, const quant_job_t &job)
 {
     quant_t q;
     const quant_kind_t kind = describe(job, q);
-    if (job.sr_seed || kind == KC_GATHER || (kind == KS && q.group)) return false;
-    if (kind == KC) return dim <= TOPK_BESIDE_DIM_KC;
+    if (job.sr_seed || kind == KC_GATHER) return false;
+    if (kind == KC) return dim <= TOPK_BESIDE_DIM_KC && counts_flat(kind, q);
     if (dim > TOPK_BESIDE_DIM) return false;
     const bool fits = topk_lds_bytes<256>((int)dim) <= (size_t)KS_LDS;
     return q.outer * q.K <= (fits ? 1ll << 31 : 64ll << 20);

@@ -181,3 +181,23 @@ def test_stochastic_rounding_in_the_quantiser_that_copies_rows(ah, strategy, lay
     assert np.array_equal(np.sort(host(out["idx"])), ref["idx"])
     assert torch.equal(out["C"].view(torch.int32), again["C"].view(torch.int32))
     assert np.linalg.norm(host(out["C"]).astype(np.float64) - ref["C"]) / np.linalg.norm(ref["C"]) < 1e-3
+
+
+@pytest.mark.parametrize("layouts", [(True, False), (False, True), (False, False)])
+@pytest.mark.parametrize("rounded", ["a", "b"])
+@pytest.mark.parametrize("M,N,K,b", [(3, 1, 32, 32), (70, 65, 288, 32), (130, 200, 512, 256), (64, 13001, 544, 32), (13001, 70, 320, 64)])
+def test_one_operand_rounded_beside_the_other(ah, layouts, rounded, M, N, K, b):
+    """Both operands quantised in one launch where the other one is K-strided: one workgroup of either, shorter last tiles, more than
+    200 column tiles (an order of their own).  Codes and scales are the bits of the quantisers by themselves."""
+    say("rounded beside", layouts, rounded, (M, N, K, b))
+    ops = {}
+    for key, outer, kc in (("a", M, layouts[0]), ("b", N, layouts[1])):
+        x = inputs.matrix(outer, K, 1e-3 if key == rounded else 0.02, 9700 + outer)
+        wide = np.zeros(((outer, K) if kc else (K, (outer + 7) // 8 * 8)), dtype=np.uint16)
+        wide[:, :(K if kc else outer)] = x if kc else x.T
+        ops[key] = ah.Operand(torch.from_numpy(wide.view(np.int16)).cuda()[:, :(K if kc else outer)], kc)
+    out = ah.adahop_gemm(ops["a"], ops["b"], inputs.IHT, b, 0, **{"sr_seed_" + rounded: 4711})
+    for key in ("a", "b"):
+        codes, scales = ah.adahop_iht_quantize(ops[key], b, sr_seed=4711 if key == rounded else None)
+        torch.cuda.synchronize()
+        assert torch.equal(out[key + "_codes"], codes) and torch.equal(out[key + "_scales"], scales), key
