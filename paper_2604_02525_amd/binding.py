@@ -1,6 +1,7 @@
 """Thin ctypes binding over libadahop.so (the C ABI of include/adahop.h).
 
-Argument marshalling only: every step of the path runs in the HIP kernels behind the ABI.  PyTorch is
+Argument marshalling only: every step of the path runs in the HIP kernels behind the ABI.  A product's arguments and the views that
+it returns are handled in csrc/call.cpp (_call.so), since a small product takes less time than they do in Python.  PyTorch is
 used for device memory (outputs and workspaces are torch tensors) and for the current stream.  There
 is no CPU fallback: if the library is missing, loading fails loudly.
 """
@@ -96,6 +97,23 @@ def lib():
             getattr(L, name)          # AttributeError here means the library is stale: rebuild it
         _lib = L
     return _lib
+
+
+_product_fn = None
+
+
+def _product():
+    """_call.product, with the addresses of the entry points that it calls; raises where _call.so is not built."""
+    global _product_fn
+    if _product_fn is None:
+        L = lib()
+        try:
+            from . import _call
+        except ImportError as e:
+            raise RuntimeError("_call.so is missing or stale: run `python -c 'import __graft_entry__ as g; g.build()'`") from e
+        _call.init(C.cast(L.adahop_gemm, C.c_void_p).value, C.cast(L.adahop_gemm_ex, C.c_void_p).value, Operand, C.ArgumentError)
+        _product_fn = _call.product
+    return _product_fn
 
 
 def _check(status, where):
@@ -284,31 +302,30 @@ def adahop_gemm(A, B, strategy, iht_block, k=0, idx=None, Cout=None, workspace=N
     if Cout is None:
         Cout = torch.empty((M, N), dtype=torch.bfloat16 if c_bf16 else torch.float32, device=dev)
     c_bf16 = Cout.element_size() == 2
-    use_given = idx is not None
-    if idx is None:
-        idx = torch.empty(max(k, 1), dtype=torch.int32, device=dev)
-    if a_packed is None and b_packed is None and not c_bf16 and sr_seed_a is None and sr_seed_b is None:
-        _check(lib().adahop_gemm(C.byref(A.c()), C.byref(B.c()), _ptr(Cout), Cout.stride(0), strategy, iht_block, k,
-                                 _ptr(idx), int(use_given), _ptr(workspace), workspace.numel(), _stream(stream)),
-               "adahop_gemm")
-    else:
+    opts = None
+    if a_packed is not None or b_packed is not None or c_bf16 or sr_seed_a is not None or sr_seed_b is not None:
         ac, asc = a_packed if a_packed is not None else (None, None)
         bc, bsc = b_packed if b_packed is not None else (None, None)
         opts = adahop_gemm_opts_t(_ptr(ac), _ptr(asc), _ptr(bc), _ptr(bsc), int(c_bf16), int(sr_seed_a is not None),
                                   int(sr_seed_b is not None), int(sr_seed_a or 0), int(sr_seed_b or 0))
-        _check(lib().adahop_gemm_ex(C.byref(A.c()), C.byref(B.c()), _ptr(Cout), Cout.stride(0), strategy, iht_block, k,
-                                    _ptr(idx), int(use_given), C.byref(opts), _ptr(workspace), workspace.numel(),
-                                    _stream(stream)), "adahop_gemm_ex")
-    dim = {ADAHOP_IHT_OE_ROW: M, ADAHOP_IHT_OE_COL: N, ADAHOP_IHT_OE_K: K}.get(strategy, 0)
-    return dict(C=Cout, idx=idx[:k], workspace=workspace, layout=L,
-                a_codes=_part(workspace, L.a_codes, M, K // 2), a_scales=_part(workspace, L.a_scales, M, K // 32),
-                b_codes=_part(workspace, L.b_codes, N, K // 2), b_scales=_part(workspace, L.b_scales, N, K // 32),
-                mask=_part(workspace, L.mask, dim))
+    stream = _stream(stream)
+    if not (stream is None or isinstance(stream, int)):
+        stream = C.cast(stream, C.c_void_p).value
+    given = idx
+    status, idx, a_codes, a_scales, b_codes, b_scales, mask = _product()(A, B, Cout, strategy, iht_block, k, given, workspace, stream,
+                                                                         opts, L)
+    _check(status, "adahop_gemm" if opts is None else "adahop_gemm_ex")
+    if a_codes is None:
+        dim = {ADAHOP_IHT_OE_ROW: M, ADAHOP_IHT_OE_COL: N, ADAHOP_IHT_OE_K: K}.get(strategy, 0)
+        a_codes, a_scales = _part(workspace, L.a_codes, M, K // 2), _part(workspace, L.a_scales, M, K // 32)
+        b_codes, b_scales = _part(workspace, L.b_codes, N, K // 2), _part(workspace, L.b_scales, N, K // 32)
+        mask = _part(workspace, L.mask, dim)
+    return dict(C=Cout, idx=idx if given is None else idx[:k], workspace=workspace, layout=L, a_codes=a_codes, a_scales=a_scales, b_codes=b_codes,
+                b_scales=b_scales, mask=mask)
 
 
 def _part(workspace, off, *shape):
-    """The row-major array of that shape at byte `off` of a workspace.  One call into torch (0.8 us) in place of a slice and a
-    view (1.8 us): a product of 256 x 256 x 256 is enqueued in 17 us, 8 of them its two launches, and takes 7 us on the GPU."""
+    """The row-major array of that shape at byte `off` of a workspace that is no plain one-dimensional tensor."""
     if workspace.dim() != 1 or workspace.stride(0) != 1:
         n = 1
         for extent in shape:

@@ -1,11 +1,13 @@
-"""Build libadahop.so (HIP, gfx950 only) in-tree with hipcc.  No GPU is needed to compile."""
+"""Build libadahop.so (HIP, gfx950 only) in-tree with hipcc, and the binding's native half with g++.  No GPU is needed to compile."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadahop.so")
+CALL = os.path.join(HERE, "_call.so")
 SOURCES = ["api.hip", "quantize.hip", "foid.hip", "gemm_mx.hip", "gemm_mx_dual.hip", "gemm_mx_small.hip", "oe_bf16.hip", "pattern.hip", "oht.hip", "probe.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-ffp-contract=off", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument"]
@@ -18,10 +20,20 @@ def hipcc():
     raise RuntimeError("hipcc not found")
 
 
+def call_command():
+    """The command that builds csrc/call.cpp, a Python module against torch's own headers and libraries."""
+    import torch
+    from torch.utils import cpp_extension
+    root = os.path.dirname(torch.__file__)
+    include = [f"-I{p}" for p in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+    return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+            + include + [os.path.join(CSRC, "call.cpp"), "-o", CALL, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"])
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link the shared library; always recompiles."""
+    """Compile every source and link the shared libraries; always recompiles."""
     objs = []
-    procs = []
+    procs = [("call.cpp", subprocess.Popen(call_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
     for s in SOURCES:
         obj = os.path.join(CSRC, s.replace(".hip", ".o"))
         objs.append(obj)
@@ -37,7 +49,7 @@ def build(verbose: bool = False) -> str:
             print(out, file=sys.stderr, flush=True)
         failed |= p.returncode != 0
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("a source does not compile")
     subprocess.run([hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs, check=True)
     return LIB
 
