@@ -508,6 +508,8 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
         }
         if (rc != ADAHOP_OK) return rc;
     }
+    if (!oe && !oht && !a_given && !b_given && quant_and_product_takes(ja, jb) && gemm_mx_splits_stages(M, N, K))
+        return launch_quant_and_product(b, ja, jb, C, ldc, c_bf16, st);
     const int sm_ready = oht ? 0 : (a_given ? 0 : 1) | (b_given ? 0 : 2);
     if (beside || on_the_way) {
         ;

@@ -72,6 +72,9 @@ struct quant_job_t {
 };
 int launch_iht_quantize(int iht_block, const quant_job_t &job, hipStream_t st);
 int launch_iht_quantize_two(int iht_block, const quant_job_t &a, const quant_job_t &b, hipStream_t st); // both of a product
+// Both operands of a small product, and the product, in one launch; where quant_and_product_takes them and gemm_mx_splits_stages holds.
+bool quant_and_product_takes(const quant_job_t &a, const quant_job_t &b);
+int launch_quant_and_product(int iht_block, const quant_job_t &a, const quant_job_t &b, void *C, int64_t ldc, int c_bf16, hipStream_t st);
 // One K-strided operand (nothing extracted from it, rounded to nearest), and on the way its products with the k rows extracted from the
 // other one: slice s of p is [k, outer] and holds the sums over the 256-element blocks s, s + nslice, ... of K.
 struct outlier_job_t {
@@ -134,6 +137,9 @@ int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uin
                          const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
                          const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);
 int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us, int variants = 5); // the variant for a shape and its expected time
+// Whether a product of that shape (no K-channels) goes to small tiles whose four waves share the K-elements of a stage: what
+// launch_quant_and_product computes has the same bits as that.
+bool gemm_mx_splits_stages(int64_t M, int64_t N, int64_t K);
 // Diagnostics: 0 = choose by shape, 1 = the 256 x 256 kernel and 2 = the 256 x 128 kernel, each wherever it can run,
 // 3 .. 6 = by shape with a forced tile walk, 7 .. 11 = a variant of the kernel with small tiles.
 void gemm_mx_force_kernel(int which);

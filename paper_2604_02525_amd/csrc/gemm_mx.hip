@@ -716,6 +716,13 @@ static kernel_choice_t choose_kernel(int64_t M, int64_t N, int64_t K, int kpad)
     return c;
 }
 
+bool gemm_mx_splits_stages(int64_t M, int64_t N, int64_t K)
+{
+    if (g_kernel_choice.load() != 0) return false;
+    const kernel_choice_t c = choose_kernel(M, N, K, 0);
+    return !c.large && c.variant >= 2;
+}
+
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which)
 {
     uint8_t *a_sm = static_cast<uint8_t *>(workspace);

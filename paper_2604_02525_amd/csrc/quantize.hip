@@ -15,6 +15,7 @@
 // first that also copies the extracted K-channels out; what bounds them and how the work is split stands at each.
 #include "common.h"
 #include "foid_topk.h"
+#include "gemm_mx_common.h"
 
 #include <type_traits>
 
@@ -967,6 +968,96 @@ template <int B, quant_kind_t OPA, bool TAIL> __global__ __launch_bounds__(256) 
         quant_block<B, OPA, TAIL, 256, true>(qa, blockIdx.x - nb, lds);
 }
 
+// A small product of two K-contiguous operands from which nothing is extracted, in one launch: a workgroup quantises the 32 rows of A and the
+// 32 of B that its tile of C needs, 256 K-elements at a time, into LDS, and multiplies them there.  The codes and scales of a row leave
+// with the first tile that has it.
+// Bound by the launches: 3 us of the host and 3 of the GPU for each, and quantisers and product by themselves were two.  256 x 256 x 256, whole
+// call: 10.4 us in two launches, 7.2 here, of which the host's part is 7.  A wave quantises four rows of a stage: with 256 threads, 16 rows for each wave, a
+// stage took 2.6 us, now 1.2.  The loads of the next stage are on their way meanwhile, and two buffers leave one barrier for a stage.
+// As in the product kernel of such shapes (tiles of 32 or 64 rows, gemm_mx_small.hip) four waves take a matrix-core step of each stage, their
+// sums are added in wave order, and a last stage of K that is no multiple of 256 ends with the row: the same bits.
+constexpr int TILE_THREADS = 1024;
+struct tile_product_t {
+    const uint16_t *x[2]; // A, B
+    int64_t ld[2], rows[2], K;
+    uint8_t *codes[2], *scales[2];
+    int64_t ldc;
+    int tiles_m;
+};
+__device__ __forceinline__ void put_c(float *p, float v) { *p = v; }
+__device__ __forceinline__ void put_c(uint16_t *p, float v)
+{
+    const __bf16 b = (__bf16)v; // nearest even
+    *p = __builtin_bit_cast(uint16_t, b);
+}
+template <int B, typename OUT> __global__ __launch_bounds__(TILE_THREADS) void k_quant_and_product(tile_product_t p, OUT *__restrict__ C)
+{
+    constexpr int SLAB = 64 * 128, BUF = SLAB + 64 * 8; // codes of 64 rows (rows of A, then of B), their scales
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * BUF];
+    static_assert(2 * BUF >= 4 * 16 * 64 * 4, "the waves' sums take the place of the stages");
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, h = lane >> 5;
+    const int bm = blockIdx.x % p.tiles_m, bn = blockIdx.x / p.tiles_m;
+    const int64_t K = p.K;
+    // Quantisation: 16 lanes for row r of the slab, in the first half of the waves a row of A, in the second one of B.
+    const lane_plan_t plan = make_plan<B>(lane);
+    const int side = w >> 3, r = tid >> 4, x = (r >> 1) & 7, in_chunk = (plan.chunk & 3) * 4;
+    const int64_t row = 32ll * (side ? bn : bm) + (r & 31);
+    const bool active = row < p.rows[side], leaves = active && (side ? bm : bn) == 0;
+    const uint16_t *const src = p.x[side] + row * p.ld[side] + plan.chunk * 8;
+    uint4 raw[2];
+    auto fetch = [&](int64_t k0) {
+        const int64_t kk = k0 + plan.chunk * 8;
+        raw[0] = raw[1] = make_uint4(0, 0, 0, 0);
+        if (active && kk < K) raw[0] = *reinterpret_cast<const uint4 *>(src + k0);
+        if (active && kk + 128 < K) raw[1] = *reinterpret_cast<const uint4 *>(src + k0 + 128);
+    };
+    v16f acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    fetch(0);
+    int buf = 0;
+    for (int64_t k0 = 0; k0 < K; k0 += 256, buf ^= 1) {
+        uint8_t *const slab = lds + buf * BUF;
+        const int64_t kk = k0 + plan.chunk * 8;
+        const int j0 = ((plan.chunk >> 2) + tail_rotation(K, k0)) & 7, j1 = (j0 + 4) & 7; // the lane's MX blocks in the stage
+        float w0[8] = {bf16_lo(raw[0].x), bf16_hi(raw[0].x), bf16_lo(raw[0].y), bf16_hi(raw[0].y),
+                       bf16_lo(raw[0].z), bf16_hi(raw[0].z), bf16_lo(raw[0].w), bf16_hi(raw[0].w)};
+        float w1[8] = {bf16_lo(raw[1].x), bf16_hi(raw[1].x), bf16_lo(raw[1].y), bf16_hi(raw[1].y),
+                       bf16_lo(raw[1].z), bf16_hi(raw[1].z), bf16_lo(raw[1].w), bf16_hi(raw[1].w)};
+        if (k0 + 256 < K) fetch(k0 + 256);
+        uint32_t c0, c1;
+        int s0, s1;
+        transform_quantize16<B, false>(w0, w1, plan, c0, c1, s0, s1, sr_key_t{0, 0}, 0, 0, 0);
+        *reinterpret_cast<uint32_t *>(slab + r * 128 + (j0 ^ x) * 16 + in_chunk) = c0;
+        *reinterpret_cast<uint32_t *>(slab + r * 128 + (j1 ^ x) * 16 + in_chunk) = c1;
+        if (in_chunk == 0) slab[SLAB + r * 8 + j0] = (uint8_t)s0, slab[SLAB + r * 8 + j1] = (uint8_t)s1;
+        if (leaves)
+            store_codes_scales<true>(p.codes[side], p.scales[side], row, K, k0, plan.chunk, kk < K, kk + 128 < K, c0, c1, s0, s1, {nullptr, 0});
+        __syncthreads();
+        if (w < 4) {
+            const int at = ((4 * h + w) ^ ((l32 >> 1) & 7)) * 16;
+            const uint4 a = *reinterpret_cast<const uint4 *>(slab + l32 * 128 + at), b = *reinterpret_cast<const uint4 *>(slab + (32 + l32) * 128 + at);
+            const int sa = *reinterpret_cast<const int *>(slab + SLAB + l32 * 8 + 4 * h) >> (8 * w);
+            const int sb = *reinterpret_cast<const int *>(slab + SLAB + (32 + l32) * 8 + 4 * h) >> (8 * w);
+            const v8i av = {(int)a.x, (int)a.y, (int)a.z, (int)a.w, 0, 0, 0, 0}, bv = {(int)b.x, (int)b.y, (int)b.z, (int)b.w, 0, 0, 0, 0};
+            acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc, 4, 4, 0, sa, 0, sb);
+        }
+    }
+    __syncthreads(); // every wave has read its last fragments
+    float *const red = reinterpret_cast<float *>(lds);
+    if (w < 4) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[(w * 16 + i) * 64 + lane] = acc[i];
+    }
+    __syncthreads();
+    // wave w: accumulator register w
+    float v = red[w * 64 + lane];
+#pragma unroll
+    for (int q = 1; q < 4; ++q) v += red[(q * 16 + w) * 64 + lane];
+    const int64_t m = 32ll * bm + (w >> 2) * 8 + h * 4 + (w & 3), n = 32ll * bn + l32;
+    if (m < p.rows[0] && n < p.rows[1]) put_c(C + m * p.ldc + n, v);
+}
+
 // The descriptor of an operand and the kernel kind that takes it.
 quant_kind_t describe(const quant_job_t &j, quant_t &q)
 {
@@ -1155,9 +1246,39 @@ int launch_topk(int b, const topk_job_t &t, quant_kind_t kind, const quant_t &q,
     ADAHOP_DISPATCH(b, ADAHOP_TOPK)
 #undef ADAHOP_TOPK
 }
+template <typename OUT> int launch_tiles(int b, const tile_product_t &p, OUT *C, hipStream_t st)
+{
+    const dim3 grid((unsigned)(p.tiles_m * ceil_div(p.rows[1], 32)));
+    auto go = [&](auto bb) {
+        hipLaunchKernelGGL((k_quant_and_product<decltype(bb)::value, OUT>), grid, dim3(TILE_THREADS), 0, st, p, C);
+        return check_launch();
+    };
+#define ADAHOP_TILES(BB) go(std::integral_constant<int, BB>())
+    ADAHOP_DISPATCH(b, ADAHOP_TILES)
+#undef ADAHOP_TILES
+}
 #undef ADAHOP_DISPATCH
 
 } // namespace
+
+// Up to a tile per compute unit and three stages, or two tiles and one stage.  Every tile quantises its rows once more and its stages come one after the
+// other, which then costs as much as the launch.  Two launches / one, us, in a queue and (each call waited for): 256 x 512 x 512 (128 tiles)
+// 10.0 / 7.0 (20.6 / 18.7), 256 x 1024 x 768 (256) 9.9 / 7.6 (20.7 / 20.6), 512 x 1024 x 256 (512) 9.9 / 7.1 (20.7 / 20.1); beyond the line
+// 256 x 1024 x 1024 10.0 / 9.4 (20.7 / 22.2), 512 x 1024 x 512 9.9 / 10.1 (20.7 / 23.1), 1024 x 1024 x 256 10.8 / 12.4.
+bool quant_and_product_takes(const quant_job_t &a, const quant_job_t &b)
+{
+    if (!a.x->k_contig || !b.x->k_contig || a.sr_seed || b.sr_seed) return false;
+    const int64_t tiles = ceil_div(a.x->outer, 32) * ceil_div(b.x->outer, 32), K = a.x->K;
+    return (tiles <= 256 && K <= 768) || (tiles <= 512 && K <= 256);
+}
+
+int launch_quant_and_product(int b, const quant_job_t &ja, const quant_job_t &jb, void *C, int64_t ldc, int c_bf16, hipStream_t st)
+{
+    const adahop_operand_t &A = *ja.x, &B = *jb.x;
+    const tile_product_t p = {{static_cast<const uint16_t *>(A.data), static_cast<const uint16_t *>(B.data)}, {A.ld, B.ld}, {A.outer, B.outer}, A.K,
+                              {ja.codes, jb.codes}, {ja.scales, jb.scales}, ldc, (int)ceil_div(A.outer, 32)};
+    return c_bf16 ? launch_tiles(b, p, static_cast<uint16_t *>(C), st) : launch_tiles(b, p, static_cast<float *>(C), st);
+}
 
 // The copy of a row's extracted channels is staged in LDS.
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad)
