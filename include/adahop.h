@@ -335,8 +335,8 @@ int adahop_probe_mfma_rate(int random_operands, int idle_sleeps, int workgroups,
  * 256 x 256 kernel walks its tiles in a forced order: 3 = bands of A in XCD-contiguous runs, 4 = bands of A swept
  * over B, 5 / 6 = the same two with the roles of A and B exchanged (a sweep that the shape does not allow falls back
  * to the contiguous runs).  By default the bands run along the operand with more tiles, swept where more of it would
- * be in use at a time than stays in the Infinity Cache.  7 .. 11 = always the kernel with small tiles: 128 x 128 (two
- * workgroups per compute unit), 128 x 128 (one, more stages in flight), 64 x 64, 32 x 64, 32 x 32.  Results are the same up to
+ * be in use at a time than stays in the Infinity Cache.  7 .. 12 = always the kernel with small tiles: 128 x 128 (two
+ * workgroups per compute unit), 128 x 128 (one, more stages in flight), 64 x 64, 32 x 64, 32 x 32, 96 x 64.  Results are the same up to
  * fp32 summation order (1 .. 8: the same bits).  Returns ADAHOP_E_INVALID_ARG for any other value. */
 int adahop_debug_force_gemm_kernel(int which);
 

@@ -366,7 +366,7 @@ def adahop_prepare_device():
 def adahop_debug_force_gemm_kernel(which):
     """Measurement aid: 0 = kernel chosen by shape, 1 = 256 x 256 tiles, 2 = 256 x 128 tiles with two accumulator sets,
     3 .. 6 = kernel by shape with the order of the tile walk forced (bands of A: contiguous runs / swept over B; 5, 6: of B),
-    7 .. 11 = small tiles: 128 x 128 shallow and deep, 64 x 64, 32 x 64, 32 x 32."""
+    7 .. 12 = small tiles: 128 x 128 shallow and deep, 64 x 64, 32 x 64, 32 x 32, 96 x 64."""
     _check(lib().adahop_debug_force_gemm_kernel(int(which)), "adahop_debug_force_gemm_kernel")
 
 

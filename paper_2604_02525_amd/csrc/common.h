@@ -136,12 +136,12 @@ bool gemm_mx_small_takes_canonical(int64_t K);
 int launch_gemm_mx_small(int variant, int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, const uint8_t *a_scales, int a_sm,
                          const uint8_t *b_codes, const uint8_t *b_scales, int b_sm, void *C, int64_t ldc, int c_bf16,
                          const uint16_t *Ag, const uint16_t *Bg, int kpad, hipStream_t st);
-int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us, int variants = 5); // the variant for a shape and its expected time
+int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us, int variants = 6); // the variant for a shape and its expected time
 // Whether a product of that shape (no K-channels) goes to small tiles whose four waves share the K-elements of a stage: what
 // launch_quant_and_product computes has the same bits as that.
 bool gemm_mx_splits_stages(int64_t M, int64_t N, int64_t K);
 // Diagnostics: 0 = choose by shape, 1 = the 256 x 256 kernel and 2 = the 256 x 128 kernel, each wherever it can run,
-// 3 .. 6 = by shape with a forced tile walk, 7 .. 11 = a variant of the kernel with small tiles.
+// 3 .. 6 = by shape with a forced tile walk, 7 .. 12 = a variant of the kernel with small tiles.
 void gemm_mx_force_kernel(int which);
 int launch_gather_k(const adahop_operand_t &x, const int32_t *idx, int k, int kpad, uint16_t *out, hipStream_t st);
 // C is float[M, ldc], or bf16[M, ldc] when c_bf16 is set (here and in launch_oe_rowcol).

@@ -720,7 +720,7 @@ bool gemm_mx_splits_stages(int64_t M, int64_t N, int64_t K)
 {
     if (g_kernel_choice.load() != 0) return false;
     const kernel_choice_t c = choose_kernel(M, N, K, 0);
-    return !c.large && c.variant >= 2;
+    return !c.large && c.variant >= 2 && c.variant <= 4;
 }
 
 uint8_t *gemm_mx_scales_sm(void *workspace, int64_t M, int64_t K, int which)

@@ -498,6 +498,11 @@ typedef variant_t<2, 2, 2, 2, 1, 3, 1> v128deep_t; // 128 x 128, one workgroup, 
 typedef variant_t<2, 2, 1, 1, 4, 4, 1> v64_t;     // 64 x 64
 typedef variant_t<1, 2, 1, 1, 4, 4, 1> v32x64_t;  // 32 x 64
 typedef variant_t<1, 1, 1, 1, 4, 8, 2> v32_t;     // 32 x 32
+// 96 x 64 for products that it gives one tile per compute unit and the smaller tiles two or three, us, the smaller ones / this: 96 x 11008 x 4096 14.3 / 11.4,
+// 384 x 4096 x 4096 14.9 / 11.9, 96 x 16384 x 8192 23.2 / 21.2 (with weights not in the Infinity Cache 18.9 / 17.3, 15.8 / 12.8 the first two).  Two
+// waves share a part of C: with four, each with all of it (<3, 2, 1, 1, 4>), the sums to add fill the LDS of two workgroups, 12.5 for the first; five stages in
+// place of three 11.9.
+typedef variant_t<3, 1, 1, 2, 2, 3, 1> v96x64_t;
 
 // What a variant takes, in us: start + stages max(alone, busy L) + tile L, L = tiles on the fullest of the 256 compute units.
 // Fitted on MI355X to 330 products (16 .. 4096 rows, 320 .. 20000 columns, K 512 .. 28672; mean error 8 .. 15 %).  On 240 others
@@ -507,11 +512,13 @@ struct cost_t {
     int tm, tn;
     double start, alone, busy, tile;
 };
-constexpr cost_t COST[5] = {{128, 128, 0.9, 0.743, 0.521, 3.2},
+// (96 x 64: fitted to 140 products of M 72 .. 384, N 2048 .. 16384, K 1024 .. 8192.)
+constexpr cost_t COST[6] = {{128, 128, 0.9, 0.743, 0.521, 3.2},
                             {128, 128, 0.2, 0.448, 0.500, 5.0},
                             {64, 64, 2.8, 0.138, 0.222, 1.4},
                             {32, 64, 3.0, 0.172, 0.153, 0.6},
-                            {32, 32, 2.5, 0.135, 0.111, 0.6}};
+                            {32, 32, 2.5, 0.135, 0.111, 0.6},
+                            {96, 64, 0.4, 0.390, 0.250, 4.9}};
 
 } // namespace small
 
@@ -526,7 +533,7 @@ int configure_gemm_mx_small()
     using namespace small;
     if ((rc = v128_t::configure()) != ADAHOP_OK || (rc = v128one_t::configure()) != ADAHOP_OK || (rc = v128deep_t::configure()) != ADAHOP_OK ||
         (rc = v64_t::configure()) != ADAHOP_OK || (rc = v32x64_t::configure()) != ADAHOP_OK ||
-        (rc = v32_t::configure()) != ADAHOP_OK)
+        (rc = v32_t::configure()) != ADAHOP_OK || (rc = v96x64_t::configure()) != ADAHOP_OK)
         return rc;
     once.mark(dev);
     return ADAHOP_OK;
@@ -547,6 +554,7 @@ static int launch_small_t(int variant, int64_t M, int64_t N, int64_t K, const ui
     case 2: return v64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 3: return v32x64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 4: return v32_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+    case 5: return v96x64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     }
     return ADAHOP_E_INVALID_ARG;
 }

@@ -176,6 +176,29 @@ def test_small_tiles(ah, force, kernel, shape):
         assert float((np.abs(got[:M, :N] - ref) - step * np.abs(ref) - bar * (1.0 + step)).max()) <= 0.0
 
 
+@pytest.mark.parametrize("M,N,K,k", [(1, 1, 32, 0), (95, 63, 224, 0), (97, 65, 288, 0), (96, 64, 768, 0), (193, 129, 2304, 0), (300, 257, 96, 0),
+                                     (95, 129, 1120, 70), (97, 200, 2048, 200), (96, 11008, 4096, 0), (384, 4096, 1024, 9)])
+def test_96_row_tiles(ah, force, M, N, K, k):
+    """The 96 x 64 tiles at their edges, with fewer stages than rotate in LDS and more, with and without K-channels: the sums of the 128 x 128
+    tiles in another order, against which the allowance is that of the oracle's tests on the same fp32 accumulation."""
+    A = ah.Operand.from_bits(inputs.matrix(M, K, 1.0, 82, col_outliers=(5, 50.0, 50.0)), True)
+    B = ah.Operand.from_bits(inputs.matrix(N, K, 0.02, 83), True)
+    say("96 x 64 tiles", (M, N, K, k))
+    got = {}
+    for kernel in (7, 12):
+        force(kernel)
+        for dtype in (torch.float32, torch.bfloat16):
+            room = torch.full((M + 1, N + 3), 7.0, dtype=dtype, device="cuda")
+            ah.adahop_gemm(A, B, inputs.IHT_OE_K if k else inputs.IHT, 32, k, Cout=room[:M, :N])
+            torch.cuda.synchronize()
+            assert bool((room[M] == 7.0).all()) and bool((room[:, N:] == 7.0).all())
+            got[kernel, dtype] = room[:M, :N]
+    want = got[7, torch.float32].double()
+    err = float((got[12, torch.float32].double() - want).norm() / want.norm())
+    assert err < 1e-5
+    assert torch.equal(got[12, torch.bfloat16], got[12, torch.float32].to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("M,N,K,ld,dtype", [(4250, 8450, 96, 8452, torch.float32), (4250, 8450, 192, 8464, torch.float32),
                                             (8400, 8500, 64, 8501, torch.bfloat16), (6200, 8150, 288, 8192, torch.float32),
                                             (6200, 8150, 480, 8151, torch.float32), (4000, 3900, 32, 3901, torch.float32),
