@@ -330,7 +330,7 @@ int adahop_probe_mfma_rate(int random_operands, int idle_sleeps, int workgroups,
 
 /* Measurement aid: which tiled kernel the MXFP4 product uses from now on (process-wide).  0 = chosen by shape (the
  * default), 1 = the 256 x 256 tile kernel wherever it can run (M, N >= 256, K > 512, with K-channels K > 256; the small tiles
- * elsewhere), 2 = the 256 x 128 tile kernel with two accumulator sets wherever it can run (fp32 C, M >= 256, N >= 128, K > 1792,
+ * elsewhere), 2 = the 256 x 128 tile kernel with two accumulator sets wherever it can run (fp32 C, or bf16 C of whole 4-byte pairs; M >= 256, N >= 128, K > 1792,
  * at most 128 K-channels, counted in whole stages of 64; elsewhere as 1).  3 .. 6 = kernel chosen by shape, and the
  * 256 x 256 kernel walks its tiles in a forced order: 3 = bands of A in XCD-contiguous runs, 4 = bands of A swept
  * over B, 5 / 6 = the same two with the roles of A and B exchanged (a sweep that the shape does not allow falls back
