@@ -416,19 +416,14 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const adahop_operand_t &short_op = from_a ? *A : *B, &long_op = from_a ? *B : *A;
     outlier_job_t outliers = {};
     // Row and column extraction: the bf16 products are formed by the quantiser of the other operand where that is K-strided
-    // (k_quant_ks16_outliers), whether the indices are selected here or given.  Where that operand comes packed, or is rounded stochastically, the
-    // same kernel forms them without quantising, up to a size at which it is as fast as the kernel for the products alone (41 rows x 11008 x 2016 13.7 /
-    // 14.5 us, 82 x 4096 x 4096 15.5 / 14.6, 33 x 512 x 4096 6.5 / 7, but 54 x 8192 x 5024, whole call, 229 / 225, 64 x 4096 x 32768 73 / 50):
-    // a product has the same bits then, packed operands or not.
+    // (k_quant_ks16_outliers), whether the indices are selected here or given.  Where that operand comes packed, or is rounded stochastically,
+    // they are formed by themselves in the same order (launch_outlier_products): a product has the same bits, packed operands or not, at any size.
+    // Before the MXFP4 product, beside the steps below, up to a size; above it, after the product, by launch_oe_rowcol, so that both
+    // quantisers can share a launch.  Whole calls, before / after: 8192 x 4096 x 4096, 82 rows, packed, 113.8 / 117.5 us, 1024 x 2048 x 2048, 11
+    // rows, packed, 22.7 / 27.5, 4096 x 11008 x 2016, 41 columns, rounded, 138.5 / 130.
     const bool short_given = from_a ? a_given : b_given, long_given = from_a ? b_given : a_given;
     const bool products_only = long_given || (opts && (from_a ? opts->sr_b : opts->sr_a));
-    bool on_the_way = oe_rc && !long_op.k_contig && (!products_only || long_op.outer * K <= 32ll << 20) &&
-                      oe_rowcol_on_the_way(long_op.outer, K, k, &outliers);
-    // Where that quantiser then has to wait for a selection that could stand beside it, and so does that of the operand of the
-    // extracted rows, it takes some work for that to pay: 416 x 4096 (128 tiles), 55 columns, whole call 45 us beside, 48 on the way; 32 x 1440
-    // (23) 36.9 / 38.1; 96 x 8992 (141) 78.7 / 79.3; 32 x 17376 (272) 52.7 / 49.5; 32 x 20608 (322) 77.2 / 74.3.
-    if (on_the_way && !short_op.k_contig && iht_quantize_beside_topk(dim, long_op) && ceil_div(long_op.outer, 64) * ceil_div(K, 256) < 192)
-        on_the_way = false;
+    const bool on_the_way = oe_rc && (!products_only || long_op.outer * K <= 32ll << 20) && oe_rowcol_on_the_way(short_op, long_op, k, &outliers);
     // ... and where they are rows of a K-contiguous operand, it reads them where they are
     const bool in_place = on_the_way && short_op.k_contig;
     uint16_t *pos1 = nullptr;
@@ -488,7 +483,7 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
         outliers.p = reinterpret_cast<float *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &partials));
         if (unmasked) outliers.codes = masked_job.codes, outliers.scales = masked_job.scales, outliers.sm = masked_job.sm;
         if (rc == ADAHOP_OK && products_only && !long_given) rc = launch_iht_quantize(b, free_job, st);
-        if (rc == ADAHOP_OK) rc = launch_iht_quantize_outliers(products_only ? -1 : b, free_job, outliers, st);
+        if (rc == ADAHOP_OK) rc = products_only ? launch_outlier_products(long_op, outliers, st) : launch_iht_quantize_outliers(b, free_job, outliers, st);
         if (rc != ADAHOP_OK) return rc;
     } else if (beside) {
         rc = launch_foid_scores(*masked_job.x, 0, scores, st);

@@ -89,8 +89,8 @@ struct outlier_job_t {
 };
 constexpr int OUTLIER_TILES = 6; // at most
 bool iht_quantize_takes_outliers(int tiles);
-// iht_block = -1: the products without the quantisation.
 int launch_iht_quantize_outliers(int iht_block, const quant_job_t &job, const outlier_job_t &e, hipStream_t st);
+int launch_outlier_products(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st); // the products alone
 // The selection from `scores` (launch_foid_scores) in the first workgroup of a launch whose others quantise an operand that does
 // not depend on it; topk_beside_quant says whether that can be done.
 struct topk_job_t {
@@ -152,9 +152,10 @@ size_t oe_rowcol_partials_at(int64_t M, int64_t N, int64_t K, int kind, int k, s
 // gathered: the extracted rows lie at the start of the workspace already, [k, K] (a quantiser has copied them out).
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,
                      void *C, int64_t ldc, int c_bf16, void *workspace, hipStream_t st, bool gathered = false);
-// The same with the products formed by the quantiser of the long operand: false where that is not worth while or does not fit into the
-// region of the partial sums above, which then takes outlier_job_t::p.
-bool oe_rowcol_on_the_way(int64_t Lo, int64_t K, int k, outlier_job_t *e);
+// Whether the products of the k rows extracted from S are formed on tiles of L in the quantiser's layout, by L's quantiser or by
+// launch_outlier_products: a rule on sizes and layouts alone, the same for every caller, so that a product has the same bits
+// whichever of them forms it.  The region of the partial sums above takes outlier_job_t::p.
+bool oe_rowcol_on_the_way(const adahop_operand_t &S, const adahop_operand_t &L, int k, outlier_job_t *e);
 int launch_gather_rows(const adahop_operand_t &x, const int32_t *idx, int k, uint16_t *out, hipStream_t st); // out[t, :] = x(idx[t], :)
 // C[idx[t], l] (rows) or C[l, idx[t]] = the sum over the slices of p[slice][t][l], p being [nslice][rows_all][Lo].
 int launch_oe_reduce(const float *p, int nslice, int64_t rows_all, int64_t Lo, bool rows, const int32_t *idx, int k, void *C, int64_t ldc,

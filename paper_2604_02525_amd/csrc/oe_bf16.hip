@@ -33,7 +33,8 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 //                      transposing LDS read hands the matrix cores their 8 consecutive K-elements of a row.  K
 //                      is split over workgroups so that the chip is full although there are few tiles; every
 //                      slice writes its own partial tile (no atomics: the result does not depend on scheduling);
-//      (where L is K-strided and there are at most 96 rows, L's quantiser forms the products instead: k_quant_ks16_outliers);
+//      (where L is K-strided and there are at most 96 rows, L's quantiser forms the products instead, k_quant_ks16_outliers, or
+//      k_outliers_ks16 in the same order: oe_rowcol_on_the_way);
 //   3. k_oe_reduce     adds the slices in a fixed order and writes the rows / columns of C.
 // ------------------------------------------------------------------------------------------------
 constexpr int SK_LCOLS = 256;  // rows of L per workgroup (NCW = 2; half of them with NCW = 1)
@@ -625,8 +626,14 @@ int launch_oe_reduce(const float *P, int nslice, int64_t rows_all, int64_t Lo, b
 
 // As many 256-element blocks of K per workgroup as leave four workgroups for each of the 256 compute units (4096 x 32768 with 64 rows, whole
 // call: two for each 421, four 416, eight 416 us), and more where the sums would not fit otherwise.
-bool oe_rowcol_on_the_way(int64_t Lo, int64_t K, int k, outlier_job_t *e)
+// Not where L's quantiser would then have to wait for a selection that could stand beside it, and so does that of S: it takes some
+// work for that to pay.  416 x 4096 (128 tiles), 55 columns, whole call 45 us beside, 48 on the way; 32 x 1440
+// (23) 36.9 / 38.1; 96 x 8992 (141) 78.7 / 79.3; 32 x 17376 (272) 52.7 / 49.5; 32 x 20608 (322) 77.2 / 74.3.
+bool oe_rowcol_on_the_way(const adahop_operand_t &S, const adahop_operand_t &L, int k, outlier_job_t *e)
 {
+    const int64_t Lo = L.outer, K = L.K;
+    if (L.k_contig) return false;
+    if (!S.k_contig && iht_quantize_beside_topk(S.outer, L) && ceil_div(Lo, 64) * ceil_div(K, 256) < 192) return false;
     e->tiles = (k + 15) / 16;
     while (e->tiles <= OUTLIER_TILES && !iht_quantize_takes_outliers(e->tiles)) ++e->tiles;
     if (e->tiles > OUTLIER_TILES) return false;
@@ -652,8 +659,18 @@ int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int k
     uint16_t *Sg = static_cast<uint16_t *>(workspace);
     float *P = reinterpret_cast<float *>(static_cast<char *>(workspace) + p.sg_bytes);
 
-    int rc = gathered ? ADAHOP_OK : launch_gather_rows(S, idx, k, Sg, st);
+    outlier_job_t e = {};
+    const bool as_on_the_way = oe_rowcol_on_the_way(S, L, k, &e), in_place = as_on_the_way && S.k_contig && !gathered;
+    int rc = gathered || in_place ? ADAHOP_OK : launch_gather_rows(S, idx, k, Sg, st);
     if (rc != ADAHOP_OK) return rc;
+    if (as_on_the_way) {
+        e.rows = in_place ? static_cast<const uint16_t *>(S.data) : Sg;
+        e.ld = in_place ? S.ld : K;
+        e.idx = in_place ? idx : nullptr;
+        e.p = P;
+        rc = launch_outlier_products(L, e, st);
+        return rc != ADAHOP_OK ? rc : launch_oe_reduce(P, e.nslice, k, Lo, rows, idx, k, C, ldc, c_bf16, st);
+    }
 
     const dim3 grid((unsigned)ceil_div(Lo, SK_LCOLS / 2 * p.ncw), (unsigned)p.nslice, (unsigned)p.groups);
     const uint16_t *l = static_cast<const uint16_t *>(L.data);

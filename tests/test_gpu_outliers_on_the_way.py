@@ -108,3 +108,50 @@ def test_rounding_option(sr):
         assert torch.equal(codes, out[key + "_codes"]) and torch.equal(scales, out[key + "_scales"])
     a, b = values(S[idx]), values(L)
     assert (np.abs(out["C"].cpu().numpy()[idx] - a @ b.T) <= 544 * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T)).all()
+
+
+# More than 32 Mi elements, where the products of a packed or rounded operand are formed after the MXFP4 product, 128 columns per
+# workgroup: whole and broken pairs of 64 columns, columns that end inside a 16-byte piece, K-elements that end inside a tile.
+@pytest.mark.parametrize("short,long,K,k,short_kc", [(96, 8200, 4128, 5, True), (330, 4160, 8224, 17, False), (300, 8251, 4128, 90, True),
+                                                     (200, 33000, 1056, 40, False), (64, 4096, 8224, 60, True), (90, 1088, 31008, 30, False)])
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, strategy):
+    """Extracted rows / columns of a call that quantises both operands, of one with the other operand packed beforehand, of one that
+    rounds it stochastically, and of the bf16 product by itself."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_02525_amd import binding as ah
+    print("[case] packed", short, long, K, k, short_kc, strategy, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(short + long + K)
+
+    def stored(outer, k_contig, rows):
+        x = torch.randn(outer, K, generator=gen, device="cuda")
+        x[torch.randperm(outer, generator=gen, device="cuda")[:rows]] *= 30.0
+        x = x if k_contig else x.T
+        wide = torch.full((x.shape[0], (x.shape[1] + 7) // 8 * 8 + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+        wide[:, :x.shape[1]] = x
+        return ah.Operand(wide[:, :x.shape[1]], k_contig)
+    s, l = stored(short, short_kc, k), stored(long, False, 2)
+    assert long * K > 32 << 20
+    row = strategy == inputs.IHT_OE_ROW
+    A, B = (s, l) if row else (l, s)
+    packed, seed = ("b_packed", "sr_seed_b") if row else ("a_packed", "sr_seed_a")
+    want = ah.adahop_gemm(A, B, strategy, 32, k)
+    idx = want["idx"].clone()
+    given = {packed: ah.adahop_pack_operand(l, row, strategy, 32)}
+    for again in (ah.adahop_gemm(A, B, strategy, 32, k, **given), ah.adahop_gemm(A, B, strategy, 32, k, idx=idx, **given)):
+        assert torch.equal(again["idx"], idx) and torch.equal(again["C"].view(torch.int32), want["C"].view(torch.int32))
+
+    def extracted(C):
+        return (C[idx.long()] if row else C[:, idx.long()]).contiguous().view(torch.int32)
+    rounded = ah.adahop_gemm(A, B, strategy, 32, k, **{seed: 5})
+    assert torch.equal(extracted(rounded["C"]), extracted(want["C"]))
+    alone = torch.full_like(want["C"], 3.0)
+    ah.adahop_oe_gemm_bf16(A, B, strategy, idx, alone)
+    assert torch.equal(extracted(alone), extracted(want["C"]))
+    a, b = (A, B) if row else (B, A)
+    take = a.tensor[idx.long()] if a.k_contig else a.tensor[:, idx.long()].T
+    exact = take.double() @ l.tensor.double()
+    bound = K * 2.0 ** -24 * (take.double().abs() @ l.tensor.double().abs())   # (see above)
+    got = want["C"][idx.long()] if row else want["C"][:, idx.long()].T
+    assert bool(((got.double() - exact).abs() <= bound).all())
