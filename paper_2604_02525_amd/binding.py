@@ -111,7 +111,7 @@ def _product():
             from . import _call
         except ImportError as e:
             raise RuntimeError("_call.so is missing or stale: run `python -c 'import __graft_entry__ as g; g.build()'`") from e
-        _call.init(C.cast(L.adahop_gemm, C.c_void_p).value, C.cast(L.adahop_gemm_ex, C.c_void_p).value, Operand, C.ArgumentError)
+        _call.init(C.cast(L.adahop_gemm, C.c_void_p).value, C.cast(L.adahop_gemm_ex, C.c_void_p).value, Operand)
         _product_fn = _call.product
     return _product_fn
 
@@ -308,24 +308,34 @@ def adahop_gemm(A, B, strategy, iht_block, k=0, idx=None, Cout=None, workspace=N
         bc, bsc = b_packed if b_packed is not None else (None, None)
         opts = adahop_gemm_opts_t(_ptr(ac), _ptr(asc), _ptr(bc), _ptr(bsc), int(c_bf16), int(sr_seed_a is not None),
                                   int(sr_seed_b is not None), int(sr_seed_a or 0), int(sr_seed_b or 0))
-    stream = _stream(stream)
-    if not (stream is None or isinstance(stream, int)):
-        stream = C.cast(stream, C.c_void_p).value
-    given = idx
-    status, idx, a_codes, a_scales, b_codes, b_scales, mask = _product()(A, B, Cout, strategy, iht_block, k, given, workspace, stream,
-                                                                         opts, L)
+    stream, given = _stream(stream), idx
+    done = _product()(A, B, Cout, strategy, iht_block, k, given, workspace, stream, opts, L)
+    if done is None:
+        done = _product_by_ctypes(A, B, Cout, strategy, iht_block, k, given, workspace, stream, opts, L)
+    status, idx, a_codes, a_scales, b_codes, b_scales, mask = done
     _check(status, "adahop_gemm" if opts is None else "adahop_gemm_ex")
-    if a_codes is None:
-        dim = {ADAHOP_IHT_OE_ROW: M, ADAHOP_IHT_OE_COL: N, ADAHOP_IHT_OE_K: K}.get(strategy, 0)
-        a_codes, a_scales = _part(workspace, L.a_codes, M, K // 2), _part(workspace, L.a_scales, M, K // 32)
-        b_codes, b_scales = _part(workspace, L.b_codes, N, K // 2), _part(workspace, L.b_scales, N, K // 32)
-        mask = _part(workspace, L.mask, dim)
     return dict(C=Cout, idx=idx if given is None else idx[:k], workspace=workspace, layout=L, a_codes=a_codes, a_scales=a_scales, b_codes=b_codes,
                 b_scales=b_scales, mask=mask)
 
 
+def _product_by_ctypes(A, B, Cout, strategy, iht_block, k, idx, workspace, stream, opts, L):
+    """What _call.product does, for calls that are not in the form it takes: whatever ctypes makes of the arguments."""
+    M, N, K = A.outer, B.outer, A.K
+    given = idx is not None
+    if not given:
+        idx = torch.empty(max(k, 1), dtype=torch.int32, device=A.tensor.device)[:k]
+    head = (C.byref(A.c()), C.byref(B.c()), _ptr(Cout), Cout.stride(0), strategy, iht_block, k, _ptr(idx), int(given))
+    tail = (_ptr(workspace), workspace.numel(), stream)
+    status = lib().adahop_gemm(*head, *tail) if opts is None else lib().adahop_gemm_ex(*head, C.byref(opts), *tail)
+    if status != ADAHOP_OK:
+        return (status, idx) + (None,) * 5
+    dim = {ADAHOP_IHT_OE_ROW: M, ADAHOP_IHT_OE_COL: N, ADAHOP_IHT_OE_K: K}.get(strategy, 0)
+    return (status, idx, _part(workspace, L.a_codes, M, K // 2), _part(workspace, L.a_scales, M, K // 32),
+            _part(workspace, L.b_codes, N, K // 2), _part(workspace, L.b_scales, N, K // 32), _part(workspace, L.mask, dim))
+
+
 def _part(workspace, off, *shape):
-    """The row-major array of that shape at byte `off` of a workspace that is no plain one-dimensional tensor."""
+    """The row-major array of that shape at byte `off` of a workspace."""
     if workspace.dim() != 1 or workspace.stride(0) != 1:
         n = 1
         for extent in shape:

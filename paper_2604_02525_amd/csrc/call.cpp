@@ -16,8 +16,12 @@ namespace {
 
 decltype(&adahop_gemm) gemm = nullptr;
 decltype(&adahop_gemm_ex) gemm_ex = nullptr;
-PyObject *operand_type = nullptr, *argument_error = nullptr;
-PyObject *n_tensor, *n_outer, *n_K, *n_ld, *n_k_contig, *n_c, *n_data_ptr, *n_stride, *n_numel;
+PyObject *operand_type = nullptr;
+PyObject *n_tensor, *n_outer, *n_K, *n_ld, *n_k_contig;
+
+// What is read here is the plain form of a call: int objects, tensors that are exactly torch's, the binding's own operands.  Everything else that
+// ctypes takes (an object with __index__, as numpy's integers, a c_int, _as_parameter_, an operand with a c() of its own, other objects with a
+// data_ptr()) is left to it, and so is what it refuses: these functions return false without an exception to be kept.
 
 struct object_t { // one reference
     PyObject *p;
@@ -28,22 +32,11 @@ struct object_t { // one reference
     explicit operator bool() const { return p != nullptr; }
 };
 
-// An integer as ctypes takes it: int objects only, the low bits of larger ones.
 bool integer(PyObject *o, int64_t *out)
 {
-    if (!o) return false;
-    if (!PyLong_Check(o)) {
-        PyErr_Format(argument_error, "an integer is required, not %s", Py_TYPE(o)->tp_name);
-        return false;
-    }
-    *out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
+    if (!o || !PyLong_Check(o)) return false;
+    *out = (int64_t)PyLong_AsUnsignedLongLongMask(o); // the low bits of larger ones, as ctypes
     return !PyErr_Occurred();
-}
-
-bool method_integer(PyObject *o, PyObject *name, PyObject *arg, int64_t *out)
-{
-    const object_t r(PyObject_CallMethodObjArgs(o, name, arg, nullptr));
-    return integer(r.p, out);
 }
 
 bool attribute(PyObject *o, PyObject *name, int64_t *out)
@@ -52,42 +45,25 @@ bool attribute(PyObject *o, PyObject *name, int64_t *out)
     return integer(r.p, out);
 }
 
-// data_ptr() of a tensor, or of what has such a method; None is a null pointer.
+// None is a null pointer.
 bool pointer(PyObject *o, void **out)
 {
     *out = nullptr;
-    if (!o) return false;
-    if (o == Py_None) return true;
-    if (THPVariable_CheckExact(o)) {
-        *out = THPVariable_Unpack(o).data_ptr();
-        return true;
-    }
-    int64_t v;
-    if (!method_integer(o, n_data_ptr, nullptr, &v)) return false;
-    *out = reinterpret_cast<void *>(v);
+    if (!o || (o != Py_None && !THPVariable_CheckExact(o))) return false;
+    if (o != Py_None) *out = THPVariable_Unpack(o).data_ptr();
     return true;
 }
 
 bool operand(PyObject *o, adahop_operand_t *x)
 {
-    if (reinterpret_cast<PyObject *>(Py_TYPE(o)) != operand_type) { // its own c() says what it is
-        const object_t c(PyObject_CallMethodObjArgs(o, n_c, nullptr));
-        Py_buffer b;
-        if (!c || PyObject_GetBuffer(c.p, &b, PyBUF_SIMPLE) != 0) return false;
-        const bool fits = b.len == (Py_ssize_t)sizeof *x;
-        if (fits) memcpy(x, b.buf, sizeof *x);
-        PyBuffer_Release(&b);
-        if (!fits) PyErr_SetString(argument_error, "c() of an operand is no adahop_operand_t");
-        return fits;
-    }
+    if (reinterpret_cast<PyObject *>(Py_TYPE(o)) != operand_type) return false;
     const object_t t(PyObject_GetAttr(o, n_tensor));
     void *data;
     int64_t outer, K, ld;
-    if (!pointer(t.p, &data) || !attribute(o, n_outer, &outer) || !attribute(o, n_K, &K) || !attribute(o, n_ld, &ld)) return false;
+    if (t.p == Py_None || !pointer(t.p, &data) || !attribute(o, n_outer, &outer) || !attribute(o, n_K, &K) || !attribute(o, n_ld, &ld)) return false;
     const object_t kc(PyObject_GetAttr(o, n_k_contig));
-    const int k_contig = kc ? PyObject_IsTrue(kc.p) : -1;
-    if (k_contig < 0) return false;
-    *x = {static_cast<uint16_t *>(data), outer, K, ld, k_contig};
+    if (!kc || !PyBool_Check(kc.p)) return false;
+    *x = {static_cast<uint16_t *>(data), outer, K, ld, kc.p == Py_True};
     return true;
 }
 
@@ -98,14 +74,13 @@ template <typename T> bool structure(PyObject *o, T *out)
     const bool fits = b.len == (Py_ssize_t)sizeof *out;
     if (fits) memcpy(out, b.buf, sizeof *out);
     PyBuffer_Release(&b);
-    if (!fits) PyErr_SetString(argument_error, "a structure of another size");
     return fits;
 }
 
 // product(A, B, Cout, strategy, iht_block, k, idx, workspace, stream, opts, layout)
 //   idx: the caller's list, or None: a new one of k entries on A's device (none: no memory); opts: adahop_gemm_opts_t or None.
 // -> (status, idx, a_codes, a_scales, b_codes, b_scales, mask): the list, and views of the workspace, which are None
-// where the call failed or the workspace is no plain one-dimensional tensor (the binding makes them then).
+// where the call failed; or None, nothing having been done, where the call is not in the plain form above.
 PyObject *product(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
@@ -114,37 +89,24 @@ PyObject *product(PyObject *, PyObject *const *args, Py_ssize_t n)
         return nullptr;
     }
     PyObject *const pa = args[0], *const pb = args[1], *const pc = args[2], *const pidx = args[6], *const pws = args[7];
+    const bool given = pidx != Py_None;
     adahop_operand_t A, B;
     adahop_gemm_opts_t opts;
     adahop_ws_layout_t L;
-    int64_t strategy, block, k, stream = 0, ldc, ws_bytes;
+    int64_t strategy, block, k, stream = 0;
     void *C, *ws, *idx;
-    if (!operand(pa, &A) || !operand(pb, &B) || !pointer(pc, &C) || !integer(args[3], &strategy) || !integer(args[4], &block) ||
-        !integer(args[5], &k) || !pointer(pws, &ws) || (args[8] != Py_None && !integer(args[8], &stream)) ||
-        (args[9] != Py_None && !structure(args[9], &opts)) || !structure(args[10], &L))
-        return nullptr;
-    if (THPVariable_CheckExact(pc)) {
-        ldc = THPVariable_Unpack(pc).stride(0);
-    } else {
-        const object_t zero(PyLong_FromLong(0));
-        if (!method_integer(pc, n_stride, zero.p, &ldc)) return nullptr;
+    if (!operand(pa, &A) || !operand(pb, &B) || pc == Py_None || !pointer(pc, &C) || !integer(args[3], &strategy) || !integer(args[4], &block) ||
+        !integer(args[5], &k) || k != (int)k || !pointer(pidx, &idx) || pws == Py_None || !pointer(pws, &ws) || (args[8] != Py_None && !integer(args[8], &stream)) ||
+        (args[9] != Py_None && !structure(args[9], &opts)) || !structure(args[10], &L) || THPVariable_Unpack(pc).dim() == 0 ||
+        THPVariable_Unpack(pws).dim() != 1 || THPVariable_Unpack(pws).stride(0) != 1) {
+        PyErr_Clear();
+        Py_RETURN_NONE;
     }
-    const bool plain = THPVariable_CheckExact(pws);
-    if (plain)
-        ws_bytes = THPVariable_Unpack(pws).numel();
-    else if (!method_integer(pws, n_numel, nullptr, &ws_bytes))
-        return nullptr;
+    const int64_t ldc = THPVariable_Unpack(pc).stride(0), ws_bytes = THPVariable_Unpack(pws).numel();
     at::Tensor list;
-    const bool given = pidx != Py_None;
-    if (given) {
-        if (!pointer(pidx, &idx)) return nullptr;
-    } else {
+    if (!given) {
         const object_t t(PyObject_GetAttr(pa, n_tensor));
         if (!t) return nullptr;
-        if (!THPVariable_Check(t.p)) {
-            PyErr_SetString(argument_error, "an operand that is no tensor needs an index list of its own");
-            return nullptr;
-        }
         list = at::empty({(int)k > 0 ? (int)k : 0}, at::TensorOptions().dtype(at::kInt).device(THPVariable_Unpack(t.p).device()));
         idx = list.data_ptr();
     }
@@ -163,45 +125,40 @@ PyObject *product(PyObject *, PyObject *const *args, Py_ssize_t n)
         if (o) PyTuple_SET_ITEM(result.p, i, o);
         return o != nullptr;
     };
-    auto none = [] {
-        Py_INCREF(Py_None);
-        return Py_None;
-    };
     Py_XINCREF(given ? pidx : nullptr);
     if (!set(0, PyLong_FromLong(status)) || !set(1, given ? pidx : THPVariable_Wrap(std::move(list)))) return nullptr;
-    bool views = status == ADAHOP_OK && plain;
-    if (views) {
+    if (status == ADAHOP_OK) {
         const at::Tensor &w = THPVariable_Unpack(pws);
-        views = w.dim() == 1 && w.stride(0) == 1;
-        if (views) {
-            const int64_t at0 = w.storage_offset(), M = A.outer, N = B.outer, K = A.K;
-            auto matrix = [&](int i, size_t off, int64_t rows, int64_t cols) {
-                return set(i, THPVariable_Wrap(at::as_strided(w, {rows, cols}, {cols, 1}, at0 + (int64_t)off)));
-            };
-            const int which = (int)strategy;
-            const int64_t dim = which == ADAHOP_IHT_OE_ROW ? M : which == ADAHOP_IHT_OE_COL ? N : which == ADAHOP_IHT_OE_K ? K : 0;
-            if (!matrix(2, L.a_codes, M, K / 2) || !matrix(3, L.a_scales, M, K / 32) || !matrix(4, L.b_codes, N, K / 2) ||
-                !matrix(5, L.b_scales, N, K / 32) || !set(6, THPVariable_Wrap(at::as_strided(w, {dim}, {1}, at0 + (int64_t)L.mask))))
-                return nullptr;
+        const int64_t at0 = w.storage_offset(), M = A.outer, N = B.outer, K = A.K;
+        auto matrix = [&](int i, size_t off, int64_t rows, int64_t cols) {
+            return set(i, THPVariable_Wrap(at::as_strided(w, {rows, cols}, {cols, 1}, at0 + (int64_t)off)));
+        };
+        const int which = (int)strategy;
+        const int64_t dim = which == ADAHOP_IHT_OE_ROW ? M : which == ADAHOP_IHT_OE_COL ? N : which == ADAHOP_IHT_OE_K ? K : 0;
+        if (!matrix(2, L.a_codes, M, K / 2) || !matrix(3, L.a_scales, M, K / 32) || !matrix(4, L.b_codes, N, K / 2) ||
+            !matrix(5, L.b_scales, N, K / 32) || !set(6, THPVariable_Wrap(at::as_strided(w, {dim}, {1}, at0 + (int64_t)L.mask))))
+            return nullptr;
+    } else {
+        for (int i = 2; i < 7; ++i) {
+            Py_INCREF(Py_None);
+            set(i, Py_None);
         }
     }
-    if (!views)
-        for (int i = 2; i < 7; ++i) set(i, none());
     Py_INCREF(result.p);
     return result.p;
     END_HANDLE_TH_ERRORS
 }
 
-// init(address of adahop_gemm, address of adahop_gemm_ex, the operand's type, ctypes' exception)
+// init(address of adahop_gemm, address of adahop_gemm_ex, the operand's type)
 PyObject *init(PyObject *, PyObject *args)
 {
     unsigned long long g, ge;
-    PyObject *type, *error;
-    if (!PyArg_ParseTuple(args, "KKOO", &g, &ge, &type, &error)) return nullptr;
-    Py_INCREF(type), Py_INCREF(error); // (for the life of the process)
+    PyObject *type;
+    if (!PyArg_ParseTuple(args, "KKO", &g, &ge, &type)) return nullptr;
+    Py_INCREF(type); // (for the life of the process)
     gemm = reinterpret_cast<decltype(gemm)>(g);
     gemm_ex = reinterpret_cast<decltype(gemm_ex)>(ge);
-    operand_type = type, argument_error = error;
+    operand_type = type;
     Py_RETURN_NONE;
 }
 
@@ -217,8 +174,7 @@ PyMODINIT_FUNC PyInit__call(void)
     struct {
         PyObject **name;
         const char *text;
-    } const names[] = {{&n_tensor, "tensor"}, {&n_outer, "outer"},       {&n_K, "K"},           {&n_ld, "ld"},      {&n_k_contig, "k_contig"},
-                       {&n_c, "c"},           {&n_data_ptr, "data_ptr"}, {&n_stride, "stride"}, {&n_numel, "numel"}};
+    } const names[] = {{&n_tensor, "tensor"}, {&n_outer, "outer"}, {&n_K, "K"}, {&n_ld, "ld"}, {&n_k_contig, "k_contig"}};
     for (const auto &x : names)
         if (!(*x.name = PyUnicode_InternFromString(x.text))) return nullptr;
     return PyModule_Create(&module);

@@ -1,7 +1,8 @@
-"""The native half of the binding's product call: what it refuses (before any HIP call, on CPU tensors), and that the index
-list and the views are those of the workspace whatever form that has."""
+"""The native half of the binding's product call: what it refuses and what it leaves to ctypes (before any HIP call, on CPU
+tensors), and that the index list and the views are those of the workspace whatever form that has."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -34,6 +35,61 @@ def test_refused_calls_raise_as_the_entry_point_says(cls):
         cpu_call(cls, strategy=ah.ADAHOP_IHT_OE_K, k=3, block=33, idx=[1, 2, 3])
 
 
+class Index:
+    def __init__(self, value):
+        self.value = value
+
+    def __index__(self):
+        return self.value
+
+
+class AsParameter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+class Buffer:
+    """No torch tensor, but all that the binding asks of one."""
+
+    def __init__(self, t):
+        self.t, self.device, self.shape = t, t.device, t.shape
+
+    def __getattr__(self, name):
+        if name in ("data_ptr", "dim", "stride", "element_size", "numel"):
+            return getattr(self.t, name)
+        raise AttributeError(name)
+
+
+INTEGERS = [int, np.int64, np.int32, np.uint8, Index, AsParameter, C.c_int]
+
+
+@pytest.mark.parametrize("integer", INTEGERS)
+def test_integers_are_what_ctypes_takes(integer):
+    with pytest.raises(ah.AdahopError) as e:            # the entry point was reached, and refused the block
+        cpu_call(block=integer(33))
+    assert e.value.status == ah.ADAHOP_E_INVALID_ARG
+    with pytest.raises(ah.AdahopError) as e:            # every argument accepted up to the workspace
+        cpu_call(block=integer(32), strategy=integer(ah.ADAHOP_IHT), nbytes=64)
+    assert e.value.status == ah.ADAHOP_E_WORKSPACE
+    for refused in (33.0, "33", None, C.c_long(33)):
+        with pytest.raises(C.ArgumentError):
+            cpu_call(block=refused)
+
+
+@pytest.mark.parametrize("count", [int, np.int64])
+def test_objects_with_a_data_pointer(count):
+    def buffer_op(t, kc):
+        return ah.Operand(Buffer(t), kc)
+    for strategy, k in ((ah.ADAHOP_IHT, 0), (ah.ADAHOP_IHT_OE_ROW, 3)):
+        for cls in (buffer_op, ah.Operand):
+            with pytest.raises(ah.AdahopError) as e:
+                cpu_call(cls, block=33, strategy=strategy, k=count(k))
+            assert e.value.status == ah.ADAHOP_E_INVALID_ARG
+            with pytest.raises(ah.AdahopError) as e:
+                cpu_call(cls, nbytes=64, strategy=strategy, k=count(k), idx=Buffer(torch.zeros(8, dtype=torch.int32)))
+            assert e.value.status == ah.ADAHOP_E_WORKSPACE
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("strategy,k", [(ah.ADAHOP_IHT, 0), (ah.ADAHOP_IHT_OE_ROW, 3), (ah.ADAHOP_IHT_OE_COL, 5), (ah.ADAHOP_IHT_OE_K, 7)])
 def test_index_list_and_views_in_every_form_of_the_workspace(strategy, k):
@@ -63,6 +119,14 @@ def test_index_list_and_views_in_every_form_of_the_workspace(strategy, k):
                 want = got
             for n in got:
                 assert torch.equal(got[n], want[n]), n
+    for integer in INTEGERS:
+        count = integer if integer in (int, np.int64) else int
+        r = ah.adahop_gemm(ah.Operand(x, True), ah.Operand(Buffer(w), True), count(strategy), integer(64), count(k),
+                           workspace=flat[:need],
+                           stream=C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        for n in ("C", "idx", "a_codes", "a_scales", "b_codes", "b_scales"):
+            assert torch.equal(r[n], want[n]), n
     if k:
         again = ah.adahop_gemm(ah.Operand(x, True), ah.Operand(w, True), strategy, 64, k, idx=want["idx"])
         torch.cuda.synchronize()
