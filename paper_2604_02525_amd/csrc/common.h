@@ -89,8 +89,8 @@ struct outlier_job_t {
 };
 constexpr int OUTLIER_TILES = 6; // at most
 bool iht_quantize_takes_outliers(int tiles);
+// iht_block = -1: the products without the quantisation (see launch_outlier_products).
 int launch_iht_quantize_outliers(int iht_block, const quant_job_t &job, const outlier_job_t &e, hipStream_t st);
-int launch_outlier_products(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st); // the products alone
 // The selection from `scores` (launch_foid_scores) in the first workgroup of a launch whose others quantise an operand that does
 // not depend on it; topk_beside_quant says whether that can be done.
 struct topk_job_t {
@@ -156,6 +156,7 @@ int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int k
 // launch_outlier_products: a rule on sizes and layouts alone, the same for every caller, so that a product has the same bits
 // whichever of them forms it.  The region of the partial sums above takes outlier_job_t::p.
 bool oe_rowcol_on_the_way(const adahop_operand_t &S, const adahop_operand_t &L, int k, outlier_job_t *e);
+int launch_outlier_products(const adahop_operand_t &L, const outlier_job_t &e, hipStream_t st); // the products alone
 int launch_gather_rows(const adahop_operand_t &x, const int32_t *idx, int k, uint16_t *out, hipStream_t st); // out[t, :] = x(idx[t], :)
 // C[idx[t], l] (rows) or C[l, idx[t]] = the sum over the slices of p[slice][t][l], p being [nslice][rows_all][Lo].
 int launch_oe_reduce(const float *p, int nslice, int64_t rows_all, int64_t Lo, bool rows, const int32_t *idx, int k, void *C, int64_t ldc,
@@ -212,6 +213,18 @@ __device__ __forceinline__ uint4 load_part16(const uint16_t *p, int n)
     const uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
     const uint64_t l = by < 64 ? lo >> by | hi << (64 - by) : hi >> (by - 64), h = by < 64 ? hi >> by : 0;
     return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+}
+
+// The codes and scales of the extracted row idx[t], by a workgroup of 256 threads.
+__device__ __forceinline__ void clear_extracted_row(const outlier_job_t &e, int t, int64_t K)
+{
+    const int64_t o = e.idx[t];
+    for (int64_t i = threadIdx.x; i < K / 32; i += 256) {
+        *reinterpret_cast<uint4 *>(e.codes + o * (K >> 1) + i * 16) = make_uint4(0, 0, 0, 0);
+        e.scales[o * (K >> 5) + i] = 0;
+    }
+    if (e.sm.out)
+        for (int64_t i = threadIdx.x; i < (K + 255) / 256; i += 256) *reinterpret_cast<uint64_t *>(e.sm.out + (i * e.sm.rows + o) * 8) = 0;
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }

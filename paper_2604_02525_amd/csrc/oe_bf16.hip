@@ -306,6 +306,230 @@ __global__ __launch_bounds__(256, 1) void k_oe_skinny(const uint16_t *__restrict
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same products with a K-strided L by themselves, in the order of its quantiser (k_quant_ks16_outliers), so that a product has the same bits
+// whether L is quantised in the call or not: slice s holds the 256-element blocks s, s + nslice, ... of K, and matrix-core
+// instruction i of a block (v_mfma_f32_16x16x32_bf16) the K-elements 64 g + 8 i .. + 7, g = 0 .. 3 (the groups of 16 lanes).
+// Bound by reading L.  Workgroup = 32 R extracted rows x 64 CT rows of L x one slice, a wave = all the extracted rows x 16 CT rows of L.
+//   L travels in stages of 64 K-elements as in k_oe_skinny: two on their way in registers, one in the LDS buffer that is multiplied, one
+//   being written into the other.  Stage s of a block holds what instructions 2 s and 2 s + 1 take, the K-rows 64 g + 16 s .. + 15.  K-row
+//   r = 16 g + 8 u + 4 h + j of it (u: which instruction, j < 4) lies at row j + 4 (g & 1) + 8 h + 16 u + 32 (g >> 1) of the buffer, pieces of 32
+//   bytes exchanged by the row's low three bits: the eight K-rows that a transposing read of 32 lanes touches lie in different eighths of the banks.
+//   The extracted rows' 256 K-elements of a block lie in LDS as in the quantiser; those of the next block arrive with the four stages, a
+//   quarter of the rows each, so that whole lines are read (28672 x 8192, 64 rows, whole call with 96 rows of the other operand: 142 us, with the 32 bytes
+//   of a row that each stage needs 160; k_oe_skinny, which adds in another order, 137).
+// With slices that do not fill the chip evenly k_oe_skinny, which splits K as suits it, is up to a quarter faster in such a call (20000 x 4096, 40 rows, 63.5 / 78.6;
+// 4096 x 32768, 40 rows, 107 / 110; 12288 x 8192, 64 rows, 73 / 78); bits that do not depend on who packs an operand are worth that.
+// ------------------------------------------------------------------------------------------------
+template <int CT> constexpr int op_l_bytes() { return 64 * 128 * CT; }
+template <int R> constexpr int op_s_bytes() { return R * 16384; }
+template <int R, int CT> constexpr int op_lds_bytes() { return 2 * (op_l_bytes<CT>() + op_s_bytes<R>()); }
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int R, int CT, bool EDGE>
+__global__ __launch_bounds__(256, CT == 4 || R == 3 ? 1 : 2) void k_outlier_products(const uint16_t *__restrict__ L, int64_t ldl, int64_t Lo, int64_t K,
+                                                                                     outlier_job_t e, int col_groups)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t op_smem[]; // 2 stages of L, 2 blocks of the extracted rows
+    constexpr int NL = 2 * CT, KPP = 32 / CT; // pieces of L per lane and stage, K-rows per pass of the workgroup
+    constexpr int LB = op_l_bytes<CT>(), SB = op_s_bytes<R>(), PITCH = 128 * CT;
+    static_assert(CT == 2 || CT == 4, "a pass lies within one group of 16 K-rows");
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int tiles = col_groups * e.nslice;
+    if ((int)blockIdx.x >= tiles) {
+        clear_extracted_row(e, (int)blockIdx.x - tiles, K);
+        return;
+    }
+    const int slice = (int)blockIdx.x / col_groups;
+    const int64_t l0 = (int64_t)((int)blockIdx.x - slice * col_groups) * (64 * CT);
+    const int nblock = ((int)((K + 255) / 256) - slice + e.nslice - 1) / e.nslice;
+    auto block_at = [&](int blk) { return (int64_t)(slice + e.nslice * (blk < nblock ? blk : nblock - 1)) * 256; }; // (behind the last one: loaded, not used)
+
+    // Loader of the extracted rows: piece c32 (8 K-elements) of rows 8 R q + r8 + 8 i in quarter q; rows past the last by that one (not stored).
+    const int c32 = tid & 31, r8 = tid >> 5;
+    int row_no[4][R];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int t = min(8 * (R * q + i) + r8, e.k - 1);
+            row_no[q][i] = e.idx ? e.idx[t] : t;
+        }
+    auto fetch_s = [&](int blk, const int (&rows)[R], uint4 (&fs)[R]) {
+        const int64_t k0 = block_at(blk), k = k0 + 8 * c32;
+        const uint16_t *const at = e.rows + (k < K ? k : k0);
+#pragma unroll
+        for (int i = 0; i < R; ++i) fs[i] = *reinterpret_cast<const uint4 *>(at + (int64_t)rows[i] * e.ld);
+    };
+    // tile rt of 16 rows as 8 x 64 pieces, row r of it at r ^ (8 (g & 1) + i): see k_quant_ks16_outliers
+    const int s_at = (c32 & 7) * 64 + (c32 >> 3) * 16, s_x = c32 & 15;
+    auto stash_s = [&](int blk, auto quarter, uint8_t *buf, const uint4 (&fs)[R]) {
+        constexpr int Q = decltype(quarter)::value;
+        const uint32_t keep = block_at(blk) + 8 * c32 < K ? ~0u : 0u;
+        uint4 *const s = reinterpret_cast<uint4 *>(buf);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            constexpr int first = R * Q;
+            const int n = first + i; // rows 8 n + r8
+            s[(n >> 1) * 512 + s_at + ((r8 + 8 * (n & 1)) ^ s_x)] = make_uint4(fs[i].x & keep, fs[i].y & keep, fs[i].z & keep, fs[i].w & keep);
+        }
+    };
+
+    // Loader of L: 16-byte piece cl of the K-rows kl + KPP i.  Rows of L past the end are replaced by the last piece (not stored).
+    const int cl = tid & (8 * CT - 1), kl = tid / (8 * CT);
+    const int64_t l = l0 + 8 * cl, l_last = (Lo - 1) / 8 * 8; // whole 16-byte pieces: ld is a multiple of 8
+    const uint16_t *const lrow = L + (int64_t)kl * ldl + (l < l_last ? l : l_last);
+    uint4 end_piece = make_uint4(0, 0, 0, 0);
+    int end_row = -1; // the K-row whose piece this lane must not read whole
+    if (EDGE && l >= Lo / 8 * 8) {
+        end_piece = load_part16(L + (K - 1) * ldl + Lo / 8 * 8, (int)(Lo & 7));
+        end_row = (int)K - 1;
+    }
+    // Pass i of stage s: K-rows pass(s, i) + ... of the block; behind the end of K the block's first ones, which exist, in their place, and zeros on
+    // both sides: an infinity there must not meet one of those zeros.
+    auto pass = [](int s, int i) { return 16 * s + 64 * (CT == 4 ? i >> 1 : i); };
+    auto row_of = [&](int64_t k0, int s, int i) { return (k0 + pass(s, i) < K ? k0 + pass(s, i) : k0) + (CT == 4 ? 8 * (i & 1) : 0); };
+    auto fetch_l = [&](int blk, int s, int half, uint4 (&fl)[NL]) {
+        const int64_t k0 = block_at(blk);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            if (half >= 0 && i / CT != half) continue;
+            const int64_t row = row_of(k0, s, i);
+            fl[i] = load_once16(lrow + (row - (EDGE && (int)row + kl == end_row ? 1 : 0)) * ldl);
+        }
+    };
+    const int l_unit = (cl >> 1) ^ (kl & 3);
+    auto stash_l = [&](int blk, int s, int half, uint8_t *buf, const uint4 (&fl)[NL]) {
+        const int64_t k0 = block_at(blk);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            if (half >= 0 && i / CT != half) continue;
+            const uint32_t keep = k0 + pass(s, i) < K ? ~0u : 0u;
+            uint4 v = fl[i];
+            if constexpr (EDGE) {
+                const bool end = (int)row_of(k0, s, i) + kl == end_row;
+                v = make_uint4(end ? end_piece.x : v.x, end ? end_piece.y : v.y, end ? end_piece.z : v.z, end ? end_piece.w : v.w);
+            }
+            const int g4 = 4 * (CT == 4 ? (i >> 1) & 1 : i & 1); // 4 (g & 1)
+            const int row = CT == 4 ? (kl & 3) + 8 * (kl >> 2) + 16 * (i & 1) + g4 + 32 * (i >> 2)
+                                    : (kl & 3) + 8 * ((kl >> 2) & 1) + 16 * (kl >> 3) + g4 + 32 * (i >> 1);
+            *reinterpret_cast<uint4 *>(buf + row * PITCH + (l_unit ^ g4) * 32 + 16 * (cl & 1)) = make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep);
+        }
+    };
+
+    v4f acc[2 * R][CT];
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[i][c] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // As supplier of addresses for the transposing read, lane s of a group of 16 points at 4 neighbouring rows of L (4 (s % 4) ..) in
+    // K-row s / 4; lane n of the group receives K-rows 0 .. 3 of row n.
+    const int x7 = (l16 >> 2) + 4 * (g & 1), tr = (x7 + 32 * (g >> 1)) * PITCH + 8 * (l16 & 3);
+    int tr_unit[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) tr_unit[c] = tr + ((CT * w + c) ^ x7) * 32;
+    const int s_read = 16 * g, s_row = l16 ^ (8 * (g & 1));
+
+    uint4 ps[2][R], pl[2][NL];
+    uint8_t *const lbuf = op_smem, *const sbuf = op_smem + 2 * LB;
+
+    // Stage s of block blk: multiply; meanwhile write the next stage of L, which has arrived in set (s + 1) & 1, into the other buffer and refill
+    // the set with the third one from here, and write quarter s of the next block's extracted rows, and refill its set with the quarter after the next.
+    auto stage = [&](auto s_c, int blk) {
+        constexpr int s = decltype(s_c)::value;
+        const uint8_t *const cur = lbuf + (s & 1) * LB;
+        uint8_t *const oth = lbuf + (1 - (s & 1)) * LB;
+        const uint4 *const rows = reinterpret_cast<const uint4 *>(sbuf + (blk & 1) * SB);
+        uint4 (&fl)[NL] = pl[(s + 1) & 1];
+        uint4 (&fs)[R] = ps[s & 1];
+        uint4 a[2][2 * R];
+        v8bf b[2][CT];
+        auto fragments = [&](int u) {
+            const int i = 2 * s + u;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const uint8_t *q = cur + tr_unit[c] + 16 * u * PITCH;
+                const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)q);
+                const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)(q + 8 * PITCH));
+                typedef short v8s __attribute__((ext_vector_type(8)));
+                const v8s both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+                b[u][c] = __builtin_bit_cast(v8bf, both);
+            }
+#pragma unroll
+            for (int rt = 0; rt < 2 * R; ++rt) a[u][rt] = rows[rt * 512 + i * 64 + s_read + (s_row ^ i)];
+        };
+        auto step = [&](auto u_c) {
+            constexpr int u = decltype(u_c)::value;
+            constexpr int n_read = u == 0 ? 2 * R + 2 * CT : 0, n_move = CT + (u == 1 ? R : 0), N = 2 * R * CT;
+            constexpr int reads = (n_read + N - 1) / N, moves = (n_move + N - 1) / N; // behind one instruction
+            if constexpr (u == 0) fragments(1);
+            stash_l(blk + (s == 3), (s + 1) & 3, u, oth, fl);
+            fetch_l(blk + (s >= 1), (s + 3) & 3, u, fl);
+            if constexpr (u == 1) {
+                stash_s(blk + 1, s_c, sbuf + ((blk + 1) & 1) * SB, fs);
+                fetch_s(blk + 1 + (s >= 2), row_no[(s + 2) & 3], fs);
+            }
+#pragma unroll
+            for (int i = 0; i < 2 * R; ++i)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[u][i]), b[u][c], acc[i][c], 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                             // one matrix-core instruction
+                if (j * reads < n_read) __builtin_amdgcn_sched_group_barrier(0x100, reads, 0); // LDS reads
+                if (j * moves < n_move) {
+                    __builtin_amdgcn_sched_group_barrier(0x200, moves, 0);                     // LDS writes
+                    __builtin_amdgcn_sched_group_barrier(0x020, moves, 0);                     // loads
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        fragments(0);
+        step(std::integral_constant<int, 0>());
+        step(std::integral_constant<int, 1>());
+        __syncthreads();
+    };
+
+    fetch_l(0, 0, -1, pl[0]);
+    fetch_l(0, 1, -1, pl[1]);
+    {
+        uint4 f[4][R];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) fetch_s(0, row_no[q], f[q]);
+        fetch_s(1, row_no[0], ps[0]);
+        fetch_s(1, row_no[1], ps[1]);
+        stash_l(0, 0, -1, lbuf, pl[0]);
+        fetch_l(0, 2, -1, pl[0]);
+        stash_s(0, std::integral_constant<int, 0>(), sbuf, f[0]);
+        stash_s(0, std::integral_constant<int, 1>(), sbuf, f[1]);
+        stash_s(0, std::integral_constant<int, 2>(), sbuf, f[2]);
+        stash_s(0, std::integral_constant<int, 3>(), sbuf, f[3]);
+    }
+    __syncthreads();
+    for (int blk = 0; blk < nblock; ++blk) {
+        stage(std::integral_constant<int, 0>(), blk);
+        stage(std::integral_constant<int, 1>(), blk);
+        stage(std::integral_constant<int, 2>(), blk);
+        stage(std::integral_constant<int, 3>(), blk);
+    }
+    float *p = e.p + (int64_t)slice * e.k * Lo;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const int64_t o = l0 + 16 * CT * w + 16 * c + l16;
+        if (o < Lo) {
+#pragma unroll
+            for (int i = 0; i < 2 * R; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int t = 16 * i + 4 * g + r;
+                    if (t < e.k) p[(int64_t)t * Lo + o] = acc[i][c][r];
+                }
+        }
+    }
+}
+
 // C[idx[t], l] (ROWS) or C[l, idx[t]] = sum over the K slices of P[s][t][l], in slice order.
 // C holds float, or bf16 as its 16 bits (rounded to nearest even from the fp32 sum).
 template <bool ROWS, typename OUT>
@@ -462,6 +686,29 @@ int launch_skinny(bool long_kc, int ncw, dim3 grid, hipStream_t st, const uint16
                     : launch_skinny_as<RT, 2>(long_kc, grid, st, Sg, L, ldl, Lo, K, sps, P, rows_all);
 }
 
+template <int R, int CT> int allow_products_lds()
+{
+    const int rc = check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_outlier_products<R, CT, false>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)op_lds_bytes<R, CT>()));
+    return rc != ADAHOP_OK ? rc
+                           : check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_outlier_products<R, CT, true>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)op_lds_bytes<R, CT>()));
+}
+
+template <int R, int CT> int launch_products_as(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st)
+{
+    const int64_t groups = ceil_div(x.outer, 64 * CT);
+    const dim3 grid((unsigned)(groups * e.nslice + (e.codes ? e.k : 0)));
+    const uint16_t *l = static_cast<const uint16_t *>(x.data);
+    if (x.outer % 8 == 0)
+        hipLaunchKernelGGL((k_outlier_products<R, CT, false>), grid, dim3(256), (op_lds_bytes<R, CT>()), st, l, x.ld, x.outer, x.K, e, (int)groups);
+    else
+        hipLaunchKernelGGL((k_outlier_products<R, CT, true>), grid, dim3(256), (op_lds_bytes<R, CT>()), st, l, x.ld, x.outer, x.K, e, (int)groups);
+    return check_launch();
+}
+
+constexpr int64_t LONG_SLICE = 4; // blocks of 256 K-elements
+
 // out[o, t] = x(o, idx[t]) for t < k, 0 for k <= t < kpad.  out is [outer, kpad] bf16.
 __global__ __launch_bounds__(256) void k_gather_k(const uint16_t *__restrict__ x, int64_t ld, int k_contig,
                                                   int64_t outer, const int32_t *__restrict__ idx, int k, int kpad,
@@ -560,8 +807,30 @@ int configure_oe_rowcol()
         (rc = allow_skinny_lds_all<6, 1>()) != ADAHOP_OK || (rc = allow_skinny_lds_all<2, 2>()) != ADAHOP_OK ||
         (rc = allow_skinny_lds_all<4, 2>()) != ADAHOP_OK || (rc = allow_skinny_lds_all<6, 2>()) != ADAHOP_OK)
         return rc;
+    if ((rc = allow_products_lds<1, 2>()) != ADAHOP_OK || (rc = allow_products_lds<2, 2>()) != ADAHOP_OK || (rc = allow_products_lds<1, 4>()) != ADAHOP_OK ||
+        (rc = allow_products_lds<2, 4>()) != ADAHOP_OK || (rc = allow_products_lds<3, 4>()) != ADAHOP_OK)
+        return rc;
     once.mark(dev);
     return ADAHOP_OK;
+}
+
+// Slices of up to three blocks: the quantiser's kernel without the quantisation, which takes a block at once; k_outlier_products has to fill its
+// pipeline first.  Whole calls with 96 rows of the other operand, the quantiser's kernel / this, us: one block, 11008 x 2016, 16 rows 34.7 / 39.7; two, 8192 x 5024, 16
+// rows 46.8 / 50.8; three, 14336 x 4096, 40 rows 57.3 / 61.0; four, 20000 x 4096, 1 row 69.6 / 67.0, 40 rows 81.0 / 78.6; seven, 11008 x 12000, 1 row 103 / 94.6;
+// more, 5000 x 28672, 16 rows 153 / 133, 28672 x 8192, 64 rows 185 / 144.
+// 256 columns per workgroup where these fill the chip in one round, or with more than 64 rows, where half as wide ones do not fit twice into the LDS
+// either: 17000 x 10048, 64 rows (201 workgroups) 134 / 156 with 128 columns, 90 rows (268) 175 / 183; but 12288 x 8192, 16 rows (384) 80 / 73, and
+// 20000 x 4096, 1 row (316) 70 / 67.
+int launch_outlier_products(const adahop_operand_t &L, const outlier_job_t &e, hipStream_t st)
+{
+    if (ceil_div(ceil_div(L.K, 256), e.nslice) < LONG_SLICE)
+        return launch_iht_quantize_outliers(-1, {&L, nullptr, nullptr, nullptr, nullptr, nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}}, e, st);
+    const int rc = configure_oe_rowcol();
+    if (rc != ADAHOP_OK) return rc;
+    if (e.k > 64) return launch_products_as<3, 4>(L, e, st);
+    const int64_t workgroups = ceil_div(L.outer, 256) * e.nslice;
+    if (workgroups >= 160 && workgroups <= 256) return e.k <= 32 ? launch_products_as<1, 4>(L, e, st) : launch_products_as<2, 4>(L, e, st);
+    return e.k <= 32 ? launch_products_as<1, 2>(L, e, st) : launch_products_as<2, 2>(L, e, st);
 }
 
 size_t oe_rowcol_workspace_bytes(int64_t M, int64_t N, int64_t K, int kind, int k)
@@ -638,13 +907,26 @@ bool oe_rowcol_on_the_way(const adahop_operand_t &S, const adahop_operand_t &L, 
     while (e->tiles <= OUTLIER_TILES && !iht_quantize_takes_outliers(e->tiles)) ++e->tiles;
     if (e->tiles > OUTLIER_TILES) return false;
     const size_t room = plan_skinny(Lo, K, k).p_bytes;
-    const int64_t upr = ceil_div(K, 256), tiles = ceil_div(Lo, 64) * upr;
-    int64_t blocks = tiles / 1024;
+    auto fits = [&](int64_t slices) { return (size_t)slices * k * Lo * 4 <= room; };
+    const int64_t upr = ceil_div(K, 256), cols = ceil_div(Lo, 64);
+    int64_t blocks = cols * upr / 1024;
     if (blocks < 1) blocks = 1;
-    while (blocks < upr && (size_t)ceil_div(upr, blocks) * k * Lo * 4 > room) ++blocks;
+    while (blocks < upr && !fits(ceil_div(upr, blocks))) ++blocks;
+    int64_t n = ceil_div(upr, blocks);
+    // Where that is somewhat more than four, and their slices are long, a second round is nearly empty and takes as long as the first: up to twice
+    // as many, shorter slices then, if that makes the rounds together shorter.  Quantiser with the products, whole call with 96 rows of the other
+    // operand / products alone, the same, us: 11008 x 12000, 8 rows, 7 -> 10 slices 129.9 -> 126.3 / 103 -> 100; 12288 x 8192, 8 rows, 6 -> 8 98.2 -> 89.4 /
+    // 77 -> 71, 40 rows 104.7 -> 96 / 88 -> 84; 28672 x 8192, 8 rows, 3 -> 4 186 -> 173 / 151 -> 142.  (With slices of three blocks, 6400 x 8192, 11 -> 16 slices,
+    // 53.8 / 53.8.  With more than 64 rows three workgroups fit: 12288 x 8192, 90 rows, 112 -> 115.)
+    if (e->tiles <= 4 && ceil_div(upr, n) >= LONG_SLICE) {
+        auto time = [&](int64_t slices) { return ceil_div(cols * slices, 1024) * ceil_div(upr, slices); };
+        const int64_t most = 2 * n;
+        for (int64_t s = n + 1; s <= most && fits(s); ++s)
+            if (time(s) < time(n)) n = s;
+    }
     e->k = k;
-    e->nslice = (int)ceil_div(upr, blocks);
-    return (size_t)e->nslice * k * Lo * 4 <= room;
+    e->nslice = (int)n;
+    return fits(n);
 }
 
 int launch_oe_rowcol(const adahop_operand_t &A, const adahop_operand_t &B, int kind, const int32_t *idx, int k,

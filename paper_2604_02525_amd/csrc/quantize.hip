@@ -528,7 +528,7 @@ __device__ __forceinline__ uint4 pieces(v4s a, v4s b)
     return make_uint4(x.x, x.y, y.x, y.y);
 }
 
-constexpr int KS_TILE = 256 * KT_PITCH, KS_LDS = KS_TILE + 256; // bytes: the tile, and the K-mask of its rows
+constexpr int KS_LDS = 256 * KT_PITCH + 256; // bytes: the tile and the K-mask of its rows
 
 __device__ __forceinline__ int ks_swizzle(int kk) { return ((kk >> 1) & 1) | ((kk >> 5) & 2); } // of a row's 32-byte pieces
 
@@ -801,82 +801,6 @@ template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(qu
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-// The parts of the extracted rows' bf16 products with a K-strided operand, on tiles of 64 columns x 256 K-elements.
-template <int RT, int C> constexpr int outliers_tile_lds() { return RT * 8192 > C * KS_TILE ? RT * 8192 : C * KS_TILE; }
-template <int RT, int C> constexpr int outliers_lds() { return outliers_tile_lds<RT, C>() + RT * 16 * 8; }
-
-// Where the extracted rows begin (the last row stands for those behind it, whose sums are not stored).
-template <int RT> __device__ __forceinline__ void extracted_rows(const outlier_job_t &e, int64_t *row_at)
-{
-    for (int t = threadIdx.x; t < 16 * RT; t += 256) {
-        const int r = min(t, e.k - 1);
-        row_at[t] = (e.idx ? e.idx[r] : r) * e.ld;
-    }
-}
-
-// The extracted rows' 256 K-elements: piece c (8 elements) of row r0 + 8 i.
-template <int RT> __device__ __forceinline__ void fetch_rows(const outlier_job_t &e, const int64_t *row_at, int tid, int64_t k0, int64_t K, uint4 (&f)[2 * RT])
-{
-    const int c = tid & 31, r0 = tid >> 5;
-#pragma unroll
-    for (int i = 0; i < 2 * RT; ++i) {
-        f[i] = make_uint4(0, 0, 0, 0);
-        if (k0 + 8 * c < K) f[i] = *reinterpret_cast<const uint4 *>(e.rows + row_at[r0 + 8 * i] + k0 + 8 * c);
-    }
-}
-
-// A tile of 16 rows as 8 x 64 pieces: at (i, 16 g + r) the K-elements 64 g + 8 i .. + 7 of row r, what lane 16 g + r hands to
-// matrix-core instruction i.  Row r at r ^ (8 (g & 1) + i): the 16 pieces that 16 lanes write then cover the banks once.
-template <int RT> __device__ __forceinline__ void put_rows(uint8_t *lds, int tid, const uint4 (&f)[2 * RT])
-{
-    uint4 *const s = reinterpret_cast<uint4 *>(lds);
-    const int c = tid & 31, r0 = tid >> 5, at = (c & 7) * 64 + (c >> 3) * 16, x = c & 15;
-#pragma unroll
-    for (int i = 0; i < 2 * RT; ++i) s[(i >> 1) * 512 + at + ((r0 + 8 * (i & 1)) ^ x)] = f[i];
-}
-
-// Instruction i of C tiles' columns with every 16 rows (the sums of different rows in turn: none waits for the one before).
-template <int RT, int C> __device__ __forceinline__ void multiply_rows(const uint8_t *lds, int tid, int i, const v4s (&d)[C][16], v4f (&acc)[C][RT])
-{
-    const uint4 *const s = reinterpret_cast<const uint4 *>(lds);
-    const int lane = tid & 63, g16 = lane & 48, x = 8 * ((lane >> 4) & 1), r = lane & 15;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const v8bf rows = __builtin_bit_cast(v8bf, s[rt * 512 + i * 64 + g16 + (r ^ (x + i))]);
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-            acc[c][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rows, __builtin_bit_cast(v8bf, pieces(d[c][2 * i], d[c][2 * i + 1])), acc[c][rt], 0, 0, 0);
-    }
-    if (i & 1) __builtin_amdgcn_sched_barrier(0);
-}
-
-// Row t of the extracted ones in the other operand's codes and scales.
-__device__ __forceinline__ void clear_extracted_row(const quant_t &q, const outlier_job_t &e, uint32_t t)
-{
-    const int64_t o = e.idx[t], K = q.K;
-    for (int64_t i = threadIdx.x; i < K / 32; i += 256) {
-        *reinterpret_cast<uint4 *>(e.codes + o * (K >> 1) + i * 16) = make_uint4(0, 0, 0, 0);
-        e.scales[o * (K >> 5) + i] = 0;
-    }
-    if (e.sm.out)
-        for (int64_t i = threadIdx.x; i < q.upr; i += 256) *reinterpret_cast<uint64_t *>(e.sm.out + (i * e.sm.rows + o) * 8) = 0;
-}
-
-template <int RT> __device__ __forceinline__ void store_sums(const outlier_job_t &e, int slice, int64_t o0, int64_t outer, const v4f (&acc)[RT])
-{
-    const int g = (threadIdx.x >> 4) & 3;
-    const int64_t o = o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
-    if (o >= outer) return;
-    float *p = e.p + (int64_t)slice * e.k * outer + o;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int t = 16 * rt + 4 * g + r;
-            if (t < e.k) p[(int64_t)t * outer] = acc[rt][r];
-        }
-}
-
 // A K-strided operand (nothing extracted from it), and on the way its bf16 products with the k <= 16 RT rows extracted from the other
 // one (second term of Eq. 7 / 8): the operand's tile is in registers in the matrix cores' layout anyway, and reading it once more for these products by
 // themselves is what they cost.  Quantiser and products, us in two kernels / here: 4096 x 32768 with 64 rows 73 + 50 / 92, 4096 x 11008 with 21
@@ -888,7 +812,8 @@ template <int RT> __device__ __forceinline__ void store_sums(const outlier_job_t
 //
 // The extracted rows are those that the other operand's quantiser has copied out, or (idx) lie in that operand where it is
 // K-contiguous: then its quantiser need not know the selection, and a workgroup more for each extracted row sets its codes and scales
-// to zero.
+// to zero.  B = -1: an operand that is packed already or rounded stochastically, the same products by themselves (short slices; for long
+// ones k_outlier_products).
 template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_ks16_outliers(quant_t q, outlier_job_t e)
 {
     constexpr int TILE_LDS = RT * 8192 > KS_LDS ? RT * 8192 : KS_LDS;
@@ -897,95 +822,81 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
     const int64_t K = q.K;
     const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
     if (blockIdx.x >= tiles) {
-        clear_extracted_row(q, e, blockIdx.x - tiles);
+        clear_extracted_row(e, (int)(blockIdx.x - tiles), K);
         return;
     }
     uint32_t bx, slice;
     ks_order(q.group, q.col_tiles, q.tile_magic, (uint32_t)e.nslice, blockIdx.x, bx, slice);
     const int64_t o0 = (int64_t)bx * KS_COLS;
-    extracted_rows<RT>(e, row_at);
+    for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
+        const int r = min(t, e.k - 1);
+        row_at[t] = (e.idx ? e.idx[r] : r) * e.ld;
+    }
     __syncthreads();
-    v4f acc[1][RT];
+    v4f acc[RT];
 #pragma unroll
-    for (int i = 0; i < RT; ++i) acc[0][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < RT; ++i) acc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr bool AHEAD = B < 0 && RT <= 3; // (registers that a tile's quantisation needs: with it three workgroups fit, and nothing is gained)
     ks_tile_t tile;
+    if constexpr (AHEAD) ks_fetch_tile(q, threadIdx.x, o0, (int64_t)slice * 256, tile);
     for (int by = (int)slice; by < (int)q.upr; by += e.nslice) {
         // What depends on the lane alone is formed anew for every tile: kept across the tiles it took 40 registers too many.
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const int64_t k0 = (int64_t)by * 256;
-        ks_fetch_tile(q, tid, o0, k0, tile); // (a tile ahead takes registers that the quantisation needs: three workgroups fit then, and nothing is gained)
+        if constexpr (!AHEAD) ks_fetch_tile(q, tid, o0, k0, tile);
+        // the extracted rows' 256 K-elements: piece c (8 elements) of row r0 + 8 i
+        const int c = tid & 31, r0 = tid >> 5;
         uint4 f[2 * RT];
-        fetch_rows<RT>(e, row_at, tid, k0, K, f);
+#pragma unroll
+        for (int i = 0; i < 2 * RT; ++i) {
+            f[i] = make_uint4(0, 0, 0, 0);
+            if (k0 + 8 * c < K) f[i] = *reinterpret_cast<const uint4 *>(e.rows + row_at[r0 + 8 * i] + k0 + 8 * c);
+        }
         ks_put_tile(q, tid, o0, k0, lds, tile);
         __syncthreads();
-        v4s d[1][16];
-        ks_read_tile(tid, lds, d[0]);
-        __syncthreads(); // the tile is in registers: its place takes the extracted rows
-        put_rows<RT>(lds, tid, f);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) multiply_rows<RT>(lds, tid, i, d, acc);
-        if (by + e.nslice < (int)q.upr) __syncthreads(); // (the next tile may be written)
-        ks_finish<B, false>(q, tid, o0, k0, d[0]);
-    }
-    store_sums<RT>(e, (int)slice, o0, q.outer, acc[0]);
-}
-
-// The same products of an operand that is packed already, or rounded stochastically, by themselves: the same instructions in the same order, so that
-// a product has the same bits.  Bound by reading the operand; its next tile is on the way while one is multiplied.  With 128 columns (C = 2)
-// a wave multiplies every fragment of the extracted rows with two of its own columns' tiles: the fragments' LDS reads are two thirds
-// of the LDS traffic otherwise.  k_oe_skinny, which adds in another order, is faster where the slices do not fill the chip evenly (with the
-// reduction, k_oe_skinny / here: 28672 x 8192 with 82 rows 98 / 126 us, 12288 x 8192 with 16 44 / 49) and otherwise not (4096 x 32768 with 64 60 / 61,
-// 8192 x 5024 with 54 28.2 / 28.8, 4096 x 4096 with 82 22 / 19); bits that do not depend on who packs an operand are worth that.
-template <int RT, int C> __global__ __launch_bounds__(256, C == 1 ? 3 : 2) void k_outliers_ks16(quant_t q, outlier_job_t e)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    int64_t *const row_at = reinterpret_cast<int64_t *>(lds + outliers_tile_lds<RT, C>());
-    const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
-    if (blockIdx.x >= tiles) {
-        clear_extracted_row(q, e, blockIdx.x - tiles);
-        return;
-    }
-    uint32_t bx, slice;
-    ks_order(q.group, q.col_tiles, q.tile_magic, (uint32_t)e.nslice, blockIdx.x, bx, slice);
-    const int64_t o0 = (int64_t)bx * (C * KS_COLS);
-    extracted_rows<RT>(e, row_at);
-    __syncthreads();
-    v4f acc[C][RT];
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-#pragma unroll
-        for (int i = 0; i < RT; ++i) acc[c][i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    ks_tile_t tile[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) ks_fetch_tile(q, threadIdx.x, o0 + c * KS_COLS, (int64_t)slice * 256, tile[c]);
-    for (int by = (int)slice; by < (int)q.upr; by += e.nslice) {
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid)); // (as above)
-        const int64_t k0 = (int64_t)by * 256;
-        uint4 f[2 * RT];
-        fetch_rows<RT>(e, row_at, tid, k0, q.K, f);
-#pragma unroll
-        for (int c = 0; c < C; ++c) ks_put_tile(q, tid, o0 + c * KS_COLS, k0, lds + c * KS_TILE, tile[c]);
-        __syncthreads();
-        v4s d[C][16];
-#pragma unroll
-        for (int c = 0; c < C; ++c) ks_read_tile(tid, lds + c * KS_TILE, d[c]);
-        const bool more = by + e.nslice < (int)q.upr;
-        if (more) {
-#pragma unroll
-            for (int c = 0; c < C; ++c) ks_fetch_tile(q, tid, o0 + c * KS_COLS, k0 + 256ll * e.nslice, tile[c]);
+        v4s d[16];
+        ks_read_tile(tid, lds, d);
+        if constexpr (AHEAD) {
+            if (by + e.nslice < (int)q.upr) ks_fetch_tile(q, tid, o0, k0 + 256ll * e.nslice, tile);
         }
         __syncthreads(); // the tile is in registers: its place takes the extracted rows
-        put_rows<RT>(lds, tid, f);
+        // A tile of 16 rows as 8 x 64 pieces: at (i, 16 g + r) the K-elements 64 g + 8 i .. + 7 of row r, what lane 16 g + r hands to
+        // matrix-core instruction i.  Row r at r ^ (8 (g & 1) + i): the 16 pieces that 16 lanes write then cover the banks once.
+        uint4 *const s = reinterpret_cast<uint4 *>(lds);
+        {
+            const int at = (c & 7) * 64 + (c >> 3) * 16, x = c & 15;
+#pragma unroll
+            for (int i = 0; i < 2 * RT; ++i) s[(i >> 1) * 512 + at + ((r0 + 8 * (i & 1)) ^ x)] = f[i];
+        }
         __syncthreads();
+        {
+            const int lane = tid & 63, g16 = lane & 48, x = 8 * ((lane >> 4) & 1), r = lane & 15;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) multiply_rows<RT>(lds, tid, i, d, acc);
-        if (more) __syncthreads(); // (the next tile may be written)
+            for (int i = 0; i < 8; ++i) { // (the sums of different rows in turn: none waits for the one before)
+                const v8bf column = __builtin_bit_cast(v8bf, pieces(d[2 * i], d[2 * i + 1]));
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, s[rt * 512 + i * 64 + g16 + (r ^ (x + i))]), column,
+                                                                      acc[rt], 0, 0, 0);
+                if (i & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (by + e.nslice < (int)q.upr) __syncthreads(); // (the next tile may be written)
+        if constexpr (B >= 0) ks_finish<B, false>(q, tid, o0, k0, d);
     }
+    const int g = (threadIdx.x >> 4) & 3;
+    const int64_t o = o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
+    if (o < q.outer) {
+        float *p = e.p + (int64_t)slice * e.k * q.outer + o;
 #pragma unroll
-    for (int c = 0; c < C; ++c) store_sums<RT>(e, (int)slice, o0 + c * KS_COLS, q.outer, acc[c]);
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = 16 * rt + 4 * g + r;
+                if (t < e.k) p[(int64_t)t * q.outer] = acc[rt][r];
+            }
+    }
 }
 
 // Both operands of a product in one launch: the workgroups below `na` take the first, the others the second; a K-strided one beside a
@@ -1140,8 +1051,6 @@ template <int B, typename OUT> __global__ __launch_bounds__(TILE_THREADS) void k
     if (m < p.rows[0] && n < p.rows[1]) put_c(C + m * p.ldc + n, v);
 }
 
-uint32_t magic_of(uint32_t d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
-
 // The descriptor of an operand and the kernel kind that takes it.
 quant_kind_t describe(const quant_job_t &j, quant_t &q)
 {
@@ -1155,6 +1064,7 @@ quant_kind_t describe(const quant_job_t &j, quant_t &q)
     q.gk = j.gk;
     q.gr = j.gr;
     q.upr = (uint32_t)ceil_div(x.K, 256);
+    auto magic_of = [](uint32_t d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
     q.magic = magic_of(q.upr);
     q.rows_per_wg = 1;
     q.col_tiles = (uint32_t)ceil_div(x.outer, KS_COLS);
@@ -1220,29 +1130,6 @@ template <int B> int launch_outliers_b(const quant_t &q, const outlier_job_t &e,
     case 6: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 6>), grid, dim3(256), 0, st, q, e); break;
     }
     return check_launch();
-}
-
-// 128 columns per workgroup where those of 64 would fill the chip.  64 / 128, us with the reduction: 4096 x 32768 with 64 rows 72 / 61, with 96
-// 86 / 68, 28672 x 8192 with 82 142 / 126, 8192 x 5024 with 54 31.1 / 28.8, 11008 x 16384 with 82 100 / 104.  (Workgroups of 512 threads that take 64
-// columns with each half: 61.7, 70, 127, 28.7, 103.)  Column tiles first, also above KS_GROUP_FROM: nothing of a column is written on the way (28672 x 8192
-// with 82 rows 132 -> 126, 14336 x 4096 with 41 40 -> 35.5); row_of_unit is exact for them, of which there are some 2000 or one slice's.
-template <int RT> int launch_products_of(quant_t q, const outlier_job_t &e, hipStream_t st)
-{
-    const bool wide = q.col_tiles * (uint32_t)e.nslice >= 1024;
-    if (wide) q.col_tiles = (q.col_tiles + 1) / 2, q.tile_magic = magic_of(q.col_tiles);
-    q.group = 0;
-    const dim3 grid(q.col_tiles * (uint32_t)e.nslice + (uint32_t)(e.codes ? e.k : 0));
-    if (wide)
-        hipLaunchKernelGGL((k_outliers_ks16<RT, 2>), grid, dim3(256), (outliers_lds<RT, 2>()), st, q, e);
-    else
-        hipLaunchKernelGGL((k_outliers_ks16<RT, 1>), grid, dim3(256), (outliers_lds<RT, 1>()), st, q, e);
-    return check_launch();
-}
-
-template <int RT> int allow_products_lds()
-{
-    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_outliers_ks16<RT, 2>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         outliers_lds<RT, 2>()));
 }
 
 template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const quant_t &qb, hipStream_t st)
@@ -1397,28 +1284,13 @@ bool iht_quantize_takes_outliers(int tiles) { return (tiles >= 1 && tiles <= 4) 
 int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_job_t &e, hipStream_t st)
 {
     quant_t q;
-    if (describe(job, q) != KS || job.sr_seed || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
+    if (describe(job, q) != KS || (b >= 0 && job.sr_seed) || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
     switch (b) {
+    case -1: return launch_outliers_b<-1>(q, e, st);
     case 32: return launch_outliers_b<32>(q, e, st);
     case 64: return launch_outliers_b<64>(q, e, st);
     case 128: return launch_outliers_b<128>(q, e, st);
     case 256: return launch_outliers_b<256>(q, e, st);
-    }
-    return ADAHOP_E_INVALID_ARG;
-}
-
-int launch_outlier_products(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st)
-{
-    const int rc = configure_iht_quantize();
-    if (rc != ADAHOP_OK) return rc;
-    quant_t q;
-    if (describe({&x, nullptr, nullptr, nullptr, nullptr, nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}}, q) != KS) return ADAHOP_E_INVALID_ARG;
-    switch (e.tiles) {
-    case 1: return launch_products_of<1>(q, e, st);
-    case 2: return launch_products_of<2>(q, e, st);
-    case 3: return launch_products_of<3>(q, e, st);
-    case 4: return launch_products_of<4>(q, e, st);
-    case 6: return launch_products_of<6>(q, e, st);
     }
     return ADAHOP_E_INVALID_ARG;
 }
@@ -1465,9 +1337,6 @@ int configure_iht_quantize()
     int dev = 0;
     int rc = check_hip(hipGetDevice(&dev));
     if (rc != ADAHOP_OK || !once.need(dev)) return rc;
-    if ((rc = allow_products_lds<1>()) != ADAHOP_OK || (rc = allow_products_lds<2>()) != ADAHOP_OK || (rc = allow_products_lds<3>()) != ADAHOP_OK ||
-        (rc = allow_products_lds<4>()) != ADAHOP_OK || (rc = allow_products_lds<6>()) != ADAHOP_OK)
-        return rc;
     if ((rc = allow_topk_b<0>()) != ADAHOP_OK || (rc = allow_topk_b<32>()) != ADAHOP_OK || (rc = allow_topk_b<64>()) != ADAHOP_OK ||
         (rc = allow_topk_b<128>()) != ADAHOP_OK || (rc = allow_topk_b<256>()) != ADAHOP_OK)
         return rc;

@@ -110,10 +110,14 @@ def test_rounding_option(sr):
     assert (np.abs(out["C"].cpu().numpy()[idx] - a @ b.T) <= 544 * 2.0 ** -24 * (np.abs(a) @ np.abs(b).T)).all()
 
 
-# More than 32 Mi elements, where the products of a packed or rounded operand are formed after the MXFP4 product, 128 columns per
-# workgroup: whole and broken pairs of 64 columns, columns that end inside a 16-byte piece, K-elements that end inside a tile.
-@pytest.mark.parametrize("short,long,K,k,short_kc", [(96, 8200, 4128, 5, True), (330, 4160, 8224, 17, False), (300, 8251, 4128, 90, True),
-                                                     (200, 33000, 1056, 40, False), (64, 4096, 8224, 60, True), (90, 1088, 31008, 30, False)])
+# More than 32 Mi elements, where the products of a packed or rounded operand are formed after the MXFP4 product: slices of two or three blocks
+# (the quantiser's kernel without the quantisation), and longer ones (k_outlier_products: 32, 64 and 96 rows; 128 and 256 columns
+# per workgroup; columns that end inside a workgroup's, and inside a 16-byte piece; K-elements that end inside a block).
+@pytest.mark.parametrize("short,long,K,k,short_kc", [
+    (96, 8200, 4128, 5, True), (330, 4160, 8224, 17, False), (300, 8251, 4128, 90, True), (64, 4096, 8224, 60, True), (90, 1088, 31008, 30, False),
+    (64, 12801, 8224, 17, True), (64, 16384, 8192, 32, False), (80, 16377, 8032, 1, True),          # 32 rows: 128, 256 and 256 columns
+    (200, 33000, 1056, 40, False), (96, 11000, 9248, 33, True), (96, 14337, 5152, 64, True), (96, 20008, 4320, 64, False),  # 64: 128, 128, 256, 256
+    (120, 28681, 4128, 90, False), (100, 5000, 28704, 96, True), (96, 33100, 1184, 65, True)])      # 96
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
 def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, strategy):
     """Extracted rows / columns of a call that quantises both operands, of one with the other operand packed beforehand, of one that
@@ -155,3 +159,9 @@ def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, 
     bound = K * 2.0 ** -24 * (take.double().abs() @ l.tensor.double().abs())   # (see above)
     got = want["C"][idx.long()] if row else want["C"][:, idx.long()].T
     assert bool(((got.double() - exact).abs() <= bound).all())
+    # infinities and NaN beside the end of K, where blocks are filled up with zeros
+    l.tensor[K - 1, 3], l.tensor[K - 32, long - 1], l.tensor[K - 5, 64] = float("inf"), -float("inf"), float("nan")
+    want = ah.adahop_gemm(A, B, strategy, 32, k, idx=idx)
+    again = ah.adahop_gemm(A, B, strategy, 32, k, idx=idx, **{packed: ah.adahop_pack_operand(l, row, strategy, 32)})
+    assert torch.equal(again["C"].view(torch.int32), want["C"].view(torch.int32))
+    assert bool(want["C"][idx.long()].isinf().any() if row else want["C"][:, idx.long()].isinf().any())
