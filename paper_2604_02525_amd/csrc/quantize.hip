@@ -404,12 +404,14 @@ __device__ __forceinline__ void quant_kc_unit(const quant_t &q, int64_t row, uin
     if (active) store_codes_scales<TAIL>(q.codes, q.scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, q.sm);
 }
 
-// FLAT = 0: blockIdx.x is the row, blockIdx.y and the thread its units; FLAT = 1 (short rows): the units of all rows are
-// numbered consecutively.
+// FLAT = 0: blockIdx.x is the row, blockIdx.y and the thread its units, 16 to a workgroup; FLAT = 1: the units of all rows are
+// numbered consecutively.  FLAT = 0 where a row is exactly one workgroup (and for counts above row_of_unit's): where the last of a row's
+// workgroups has fewer units the rest of it idles, and with several of them a row's parts are written far apart in time.  FLAT = 0 / 1, us: 10000 rows x
+// 4096 18.0 / 18.6, x 4256 27.2 / 19.9, x 3072 15.4 / 15.0, x 11008 53.2 / 45.4; 28672 x 8192 113 / 99; 16384 x 28672 232 / 196.
 template <int B, int FLAT, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_quant_kc16(quant_t q)
 {
     if constexpr (FLAT) {
-        const uint32_t u = (blockIdx.x * 256u + threadIdx.x) >> 4, r = u / q.upr;
+        const uint32_t u = (blockIdx.x * 256u + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
         quant_kc_unit<B, SR, TAIL>(q, r, u - r * q.upr, r < q.outer);
     } else {
         const uint32_t unit = (blockIdx.y * 256u + threadIdx.x) >> 4;
@@ -923,8 +925,11 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
 
 // The top-k selection in workgroup 0, an operand that does not depend on it in the others.  Every workgroup of the launch gets the LDS that
 // the selection needs (46 KB for 8192 keys).  Beside a K-contiguous operand, whose own kernel needs none, the workgroups have 512 threads, so that
-// more waves share it: whole calls with 1 % of the rows extracted, M x N x K, us with 256 / 512 / 1024 threads: 8192 x 4096 x 4096 121.5 / 117.9 / 119.0,
-// 16384 x 1024 x 4096 97.3 (selection by itself) / 94.4 / 91.2, 2016 x 4096 x 11008 98.9 / 99.7 / 100.9, 1024 x 2048 x 8192 44.7 / 45.0 / 45.9.
+// more waves share it: whole calls with 1 % of the rows extracted, M x N x K, us with 256 / 512 / 1024 threads: 8192 x 4096 x 4096 126.2 / 123.7 / 123.4,
+// 8192 x 2048 x 2048 67.6 / 65.2 / 64.5, 4096 x 4096 x 4096 88.9 / 87.1 / 87.8, 3000 x 8192 x 2048 74.9 / 73.0 / 74.7; with fewer keys there is little between
+// them, 2016 x 4096 x 11008 113.3 / 114.5 / 116.9, 2016 x 11008 x 4096 115.4 / 115.2 / 117.6, 1024 x 2048 x 8192 51.9 / 52.7 / 53.0, 1024 x 4096 x 4096 46.2 / 46.4 / 47.2, too
+// little for instances of their own.  256 threads hold 8192 keys at most; beyond, selection by itself / 512 / 1024: 9000 x 2624 x 4256 126.9 / 124.6 / 123.6,
+// 12000 x 2048 x 4096 113.4 / 111.3 / 110.5, 16384 x 4096 x 4096 215.3 / 210.6 / 208.4, 14000 x 512 x 4096 84.8 / 84.3 / 83.3, 16384 x 512 x 512 44.2 / 45.2 / 43.7.
 constexpr int TOPK_BESIDE_DIM = 8192, TOPK_BESIDE_DIM_KC = 16384;
 template <quant_kind_t OP> constexpr int topk_threads() { return OP == KC ? 512 : 256; }
 template <int B, quant_kind_t OP, bool TAIL>
@@ -1103,7 +1108,7 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
             hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, true>), grid, dim3(256), 0, st, q);
         else
             hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, false>), grid, dim3(256), 0, st, q);
-    } else if (q.upr >= 8) {
+    } else if (q.upr == 16 || !counts_flat(KC, q)) {
         const dim3 grid((unsigned)q.outer, (unsigned)ceil_div(q.upr, 16));
         if (tail)
             hipLaunchKernelGGL((k_quant_kc16<B, 0, SR, true>), grid, dim3(256), 0, st, q);

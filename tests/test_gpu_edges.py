@@ -175,3 +175,32 @@ def test_operands_at_the_size_limits(ah):
         ri, rm = orc.foid_topk(arr, kc, 1, 4096)
         assert np.array_equal(host(idx), ri) and np.array_equal(host(mask), rm)
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("rows", [1, 3, 17, 70])
+@pytest.mark.parametrize("K", [224, 256, 1824, 2048, 3840, 3872, 4096, 4128, 4352, 8192, 8224, 12320])
+def test_units_of_long_and_short_rows(ah, rows, K):
+    """K-contiguous quantiser on both sides of rows that are one workgroup (16 units of 256), with rows that share one and rows that
+    span several; masked rows and K-indices; rounded to nearest and stochastically."""
+    x = inputs.matrix(rows, K, 1.0, 9600, row_outliers=(1, 40.0, 40.0))
+    op = ah.Operand.from_bits(x, True)
+    rng = np.random.default_rng(rows + K)
+    zo, zk = (rng.random(rows) < 0.2).astype(np.uint8), (rng.random(K) < 0.1).astype(np.uint8)
+    for b in (0, 32):
+        for mo, mk in ((None, None), (zo, zk)):
+            for seed in (None, 11):
+                codes, scales = ah.adahop_iht_quantize(op, b, zero_outer=None if mo is None else torch.from_numpy(mo).cuda(),
+                                                       zero_k=None if mk is None else torch.from_numpy(mk).cuda(), sr_seed=seed)
+                rc, rs = orc.iht_quantize(x, True, b, mo, mk, sr_seed=seed)
+                assert np.array_equal(host(scales), rs) and np.array_equal(host(codes), rc), (b, mo is not None, seed)
+
+
+def test_units_counted_beyond_the_one_multiplication(ah):
+    """Rows x units x units of 2^32 and more: numbered row by row; the same bits as in two halves, which are numbered consecutively."""
+    rows, K = 300, 1 << 20
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(rows, K, generator=gen, device="cuda", dtype=torch.bfloat16)
+    codes, scales = ah.adahop_iht_quantize(ah.Operand(x, True), 64)
+    for at in (0, 150):
+        c, s = ah.adahop_iht_quantize(ah.Operand(x[at:at + 150], True), 64)
+        assert torch.equal(c, codes[at:at + 150]) and torch.equal(s, scales[at:at + 150])
