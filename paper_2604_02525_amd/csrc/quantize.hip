@@ -924,22 +924,19 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
 }
 
 // The top-k selection in workgroup 0, an operand that does not depend on it in the others.  Every workgroup of the launch gets the LDS that
-// the selection needs (46 KB for 8192 keys).  Beside a K-contiguous operand, whose own kernel needs none, the workgroups have 512 threads, so that
-// more waves share it: whole calls with 1 % of the rows extracted, M x N x K, us with 256 / 512 / 1024 threads: 8192 x 4096 x 4096 126.2 / 123.7 / 123.4,
-// 8192 x 2048 x 2048 67.6 / 65.2 / 64.5, 4096 x 4096 x 4096 88.9 / 87.1 / 87.8, 3000 x 8192 x 2048 74.9 / 73.0 / 74.7; with fewer keys there is little between
-// them, 2016 x 4096 x 11008 113.3 / 114.5 / 116.9, 2016 x 11008 x 4096 115.4 / 115.2 / 117.6, 1024 x 2048 x 8192 51.9 / 52.7 / 53.0, 1024 x 4096 x 4096 46.2 / 46.4 / 47.2, too
-// little for instances of their own.  256 threads hold 8192 keys at most; beyond, selection by itself / 512 / 1024: 9000 x 2624 x 4256 126.9 / 124.6 / 123.6,
-// 12000 x 2048 x 4096 113.4 / 111.3 / 110.5, 16384 x 4096 x 4096 215.3 / 210.6 / 208.4, 14000 x 512 x 4096 84.8 / 84.3 / 83.3, 16384 x 512 x 512 44.2 / 45.2 / 43.7.
+// the selection needs (46 KB for 8192 keys).  Beside a K-contiguous operand, whose own kernel needs none, workgroups of 512 threads let more waves
+// share it, and hold more keys than the 8192 of 256 threads; with few keys the smaller ones are a little faster.  Whole calls with 1 % of the rows
+// extracted, M x N x K, us with 256 / 512 / 1024 threads: 8192 x 4096 x 4096 126.2 / 123.7 / 123.4, 8192 x 2048 x 2048 67.6 / 65.2 / 64.5, 4096 x 4096 x 4096 88.9 /
+// 87.1 / 87.8, 3000 x 8192 x 2048 74.9 / 73.0 / 74.7, but 2016 x 4096 x 11008 113.3 / 114.5 / 116.9, 1024 x 2048 x 8192 51.9 / 52.7 / 53.0.
 constexpr int TOPK_BESIDE_DIM = 8192, TOPK_BESIDE_DIM_KC = 16384;
-template <quant_kind_t OP> constexpr int topk_threads() { return OP == KC ? 512 : 256; }
-template <int B, quant_kind_t OP, bool TAIL>
-__global__ __launch_bounds__(topk_threads<OP>()) void k_topk_and_quant(topk_job_t t, quant_t q)
+template <quant_kind_t OP> constexpr int topk_threads(int64_t dim) { return OP == KC && dim > 2048 ? 512 : 256; }
+template <int B, quant_kind_t OP, bool TAIL, int NT> __global__ __launch_bounds__(NT) void k_topk_and_quant(topk_job_t t, quant_t q)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
     if (blockIdx.x == 0)
-        topk_lds<topk_threads<OP>()>(t.scores, t.dim, t.k, t.idx, t.mask, t.pos1, reinterpret_cast<uint32_t *>(dyn));
+        topk_lds<NT>(t.scores, t.dim, t.k, t.idx, t.mask, t.pos1, reinterpret_cast<uint32_t *>(dyn));
     else
-        quant_block<B, OP, TAIL, topk_threads<OP>()>(q, blockIdx.x - 1, dyn);
+        quant_block<B, OP, TAIL, NT>(q, blockIdx.x - 1, dyn);
 }
 
 template <int B, quant_kind_t OPA, quant_kind_t OPB, bool TAIL>
@@ -1162,9 +1159,9 @@ template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind
     return check_launch();
 }
 
-template <quant_kind_t OP> size_t topk_quant_lds(int dim)
+template <quant_kind_t OP, int NT> size_t topk_quant_lds(int dim)
 {
-    const size_t topk = topk_lds_bytes<topk_threads<OP>()>(dim), own = OP == KS ? (size_t)KS_LDS : 0;
+    const size_t topk = topk_lds_bytes<NT>(dim), own = OP == KS ? (size_t)KS_LDS : 0;
     return topk > own ? topk : own;
 }
 
@@ -1181,32 +1178,38 @@ template <int B> int launch_two_sr_b(quant_kind_t ka, const quant_t &qa, const q
     return check_launch();
 }
 
-template <int B, quant_kind_t OP, bool TAIL> int allow_topk_lds()
+template <int B, quant_kind_t OP, bool TAIL, int NT> int allow_topk_lds()
 {
-    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_topk_and_quant<B, OP, TAIL>),
+    return check_hip(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_topk_and_quant<B, OP, TAIL, NT>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)topk_quant_lds<OP>(OP == KC ? TOPK_BESIDE_DIM_KC : TOPK_BESIDE_DIM)));
+                                         (int)topk_quant_lds<OP, NT>(OP == KC && NT == 512 ? TOPK_BESIDE_DIM_KC : TOPK_BESIDE_DIM)));
 }
 
 template <int B> int launch_topk_b(const topk_job_t &t, quant_kind_t kind, const quant_t &q, hipStream_t st)
 {
-    if (kind == KS)
-        hipLaunchKernelGGL((k_topk_and_quant<B, KS, false>), dim3(1 + blocks_of(kind, q)), dim3(256), topk_quant_lds<KS>(t.dim), st, t, q);
-    else {
-        const dim3 grid((unsigned)(1 + ceil_div(q.outer * q.upr, topk_threads<KC>() / 16)));
-        if (q.K % 256)
-            hipLaunchKernelGGL((k_topk_and_quant<B, KC, true>), grid, dim3(topk_threads<KC>()), topk_quant_lds<KC>(t.dim), st, t, q);
-        else
-            hipLaunchKernelGGL((k_topk_and_quant<B, KC, false>), grid, dim3(topk_threads<KC>()), topk_quant_lds<KC>(t.dim), st, t, q);
+    if (kind == KS) {
+        hipLaunchKernelGGL((k_topk_and_quant<B, KS, false, 256>), dim3(1 + blocks_of(kind, q)), dim3(256), (topk_quant_lds<KS, 256>(t.dim)), st, t, q);
+        return check_launch();
     }
-    return check_launch();
+    auto go = [&](auto tail, auto threads) {
+        constexpr int NT = decltype(threads)::value;
+        const dim3 grid((unsigned)(1 + ceil_div(q.outer * q.upr, NT / 16)));
+        hipLaunchKernelGGL((k_topk_and_quant<B, KC, decltype(tail)::value, NT>), grid, dim3(NT), (topk_quant_lds<KC, NT>(t.dim)), st, t, q);
+        return check_launch();
+    };
+    auto pick = [&](auto tail) {
+        return topk_threads<KC>(t.dim) == 512 ? go(tail, std::integral_constant<int, 512>()) : go(tail, std::integral_constant<int, 256>());
+    };
+    return q.K % 256 ? pick(std::true_type()) : pick(std::false_type());
 }
 
 template <int B> int allow_topk_b()
 {
     int rc;
-    if ((rc = allow_topk_lds<B, KS, false>()) != ADAHOP_OK || (rc = allow_topk_lds<B, KC, true>()) != ADAHOP_OK) return rc;
-    return allow_topk_lds<B, KC, false>();
+    if ((rc = allow_topk_lds<B, KS, false, 256>()) != ADAHOP_OK || (rc = allow_topk_lds<B, KC, true, 256>()) != ADAHOP_OK ||
+        (rc = allow_topk_lds<B, KC, false, 256>()) != ADAHOP_OK || (rc = allow_topk_lds<B, KC, true, 512>()) != ADAHOP_OK)
+        return rc;
+    return allow_topk_lds<B, KC, false, 512>();
 }
 
 #define ADAHOP_DISPATCH(b, CALL)            \
@@ -1356,14 +1359,17 @@ int configure_iht_quantize()
 // other operand K-strided | K-contiguous:
 //   8192 x 4096 x 4096 (16 M)    132.8 / 128.4 | 130.4 / 128.2      8192 x  8192 x 8192 (64 M)   380.7 / 372.9 | 373.4 / 375.1
 //   4096 x 11008 x 4096 (43 M)   173.6 / 163.0 | 170.6 / 164.7      8192 x 12288 x 8192 (96 M)   511.6 / 504.2 | 502.6 / 509.2
-// and columns, 4096 x 4096 x 32768 (128 M, K-strided), 444.5 / 436.1.  An operand that is done before the selection gains nothing:
+// and columns, 4096 x 4096 x 32768 (128 M, K-strided), 444.5 / 436.1.  With more than 8192 keys two workgroups of 512 threads fit, half the waves of
+// the quantiser by itself: beside a K-contiguous operand up to 32 Mi elements, 12288 x 4096 x 4096 167.3 / 162.9, 16384 x 8192 x 4096 380 / 375, up to 64 Mi with rows of a
+// workgroup, 16384 x 11008 x 4096 492 / 482 (16384 x 28672 x 4096 1093 / 1102), but 16384 x 4096 x 11008 481 / 512, 16384 x 8192 x 8192 634 / 676, 16384 x 12288 x
+// 8192 931 / 1000.  An operand that is done before the selection gains nothing:
 // 8192 x 2048 x 2048 71.1 / 69.9 | 67.1 / 69.4.
 bool topk_beside_quant(int64_t dim, const quant_job_t &job)
 {
     quant_t q;
     const quant_kind_t kind = describe(job, q);
     if (job.sr_seed || kind == KC_GATHER) return false;
-    if (kind == KC) return dim <= TOPK_BESIDE_DIM_KC && counts_flat(kind, q);
+    if (kind == KC) return (dim <= TOPK_BESIDE_DIM || (dim <= TOPK_BESIDE_DIM_KC && q.outer * q.K <= (q.K <= 4096 ? 64ll : 32ll) << 20)) && counts_flat(kind, q);
     if (dim > TOPK_BESIDE_DIM) return false;
     const bool fits = topk_lds_bytes<256>((int)dim) <= (size_t)KS_LDS;
     return q.outer * q.K <= (fits ? 1ll << 31 : 64ll << 20);

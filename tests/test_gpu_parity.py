@@ -674,19 +674,24 @@ def test_quantisers_of_both_operands(ah, layouts, M, N, K, b, strategy):
         assert np.array_equal(host(out[name + "_codes"]), rc), name
 
 
-@pytest.mark.parametrize("dim,k", [(40, 40), (257, 3), (1024, 200), (1025, 256), (4099, 257), (8192, 82), (8192, 5000), (8193, 82)])
+@pytest.mark.parametrize("dim,k,free_kc", [(40, 40, True), (257, 3, True), (1024, 200, True), (1025, 256, True), (2048, 30, True), (2049, 30, True),
+                                           (4099, 257, True), (8192, 82, True), (8192, 5000, True), (8193, 82, True), (16383, 164, True),
+                                           (16384, 164, True), (16384, 9000, True), (16385, 164, True),
+                                           (300, 100, False), (1024, 100, False), (1025, 100, False), (8192, 100, False), (8193, 100, False)])
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
 @pytest.mark.parametrize("ties", [False, True])
-def test_selection_beside_a_quantiser(ah, dim, k, strategy, ties):
-    """Fewer and more keys than threads, k up to and past what the threads' maxima can bound, the largest count the joint
-    launch takes and one more; equal scores.  Indices and mask are those of the selection by itself, codes the oracle's."""
+def test_selection_beside_a_quantiser(ah, dim, k, free_kc, strategy, ties):
+    """Fewer and more keys than threads, k up to and past what the threads' maxima can bound, the largest counts that the joint
+    launches take (of 256 threads 2048 beside a K-contiguous operand and 8192 beside a K-strided one, of 512 threads 16384) and one more; equal
+    scores.  Indices and mask are those of the selection by itself, codes the oracle's.  (Beside a K-strided operand more than 96 rows: fewer
+    are multiplied on the way of its quantiser, which then waits for the selection.)"""
     K, other = 96, 200
     bits = inputs.matrix(dim, K, 1.0, 9300, row_outliers=(3, 60.0, 60.0))
     if ties:
         bits[:] = bits[np.arange(dim) % 7]
     free = inputs.matrix(other, K, 0.02, 9301)
-    say("selection beside a quantiser", dim, k, inputs.STRATEGY_NAMES[strategy], "ties" if ties else "")
-    x, y = ah.Operand.from_bits(bits, True), ah.Operand.from_bits(free, True)
+    say("selection beside a quantiser", dim, k, free_kc, inputs.STRATEGY_NAMES[strategy], "ties" if ties else "")
+    x, y = ah.Operand.from_bits(bits, True), ah.Operand.from_bits(free if free_kc else np.ascontiguousarray(free.T), free_kc)
     want_idx, want_mask, _ = ah.adahop_foid_topk(x, 0, k)
     row = strategy == inputs.IHT_OE_ROW
     out = ah.adahop_gemm(*((x, y) if row else (y, x)), strategy, 32, k)
@@ -698,10 +703,10 @@ def test_selection_beside_a_quantiser(ah, dim, k, strategy, ties):
 
 
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
-@pytest.mark.parametrize("dim,other,k", [(40, 200, 3), (8192, 256, 82), (8192, 40, 82), (8193, 264, 20), (8200, 40, 9)])
+@pytest.mark.parametrize("dim,other,k", [(40, 200, 3), (8192, 256, 82), (8192, 40, 82), (8193, 264, 20), (8200, 40, 9), (16385, 264, 20), (16392, 40, 9)])
 def test_scores_left_in_the_workspace(ah, strategy, dim, other, k):
     """Row and column extraction leave the scores of all rows in the workspace, as the header says: selected beside the other
-    operand's quantiser and not, with and without room for the table of positions beside the partial sums of the outlier product."""
+    operand's quantiser (up to 16384 rows) and not, with and without room for the table of positions beside the partial sums of the outlier product."""
     K = 96
     x = ah.Operand.from_bits(inputs.matrix(dim, K, 1.0, 9400, row_outliers=(3, 60.0, 60.0)), True)
     y = ah.Operand.from_bits(inputs.matrix(other, K, 0.02, 9401), True)
