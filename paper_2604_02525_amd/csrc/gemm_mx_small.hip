@@ -501,18 +501,20 @@ typedef variant_t<1, 1, 1, 1, 4, 8, 2> v32_t;     // 32 x 32
 // 96 x 64 for products that it gives one tile per compute unit and the smaller tiles two or three, us, the smaller ones / this: 96 x 11008 x 4096 14.3 / 11.4,
 // 384 x 4096 x 4096 14.9 / 11.9, 96 x 16384 x 8192 23.2 / 21.2 (with weights not in the Infinity Cache 18.9 / 17.3, 15.8 / 12.8 the first two).  Two
 // waves share a part of C: with four, each with all of it (<3, 2, 1, 1, 4>), the sums to add fill the LDS of two workgroups, 12.5 for the first; five stages in
-// place of three 11.9.
+// place of three 11.9.  Not for products of more tiles than compute units: 261 x 15506 x 7168, 729 tiles, 40.3 / 49.1, 191 x 23746 x 9056, 744, 68.6 / 75.6.
 typedef variant_t<3, 1, 1, 2, 2, 3, 1> v96x64_t;
 
 // What a variant takes, in us: start + stages max(alone, busy L) + tile L, L = tiles on the fullest of the 256 compute units.
 // Fitted on MI355X to 330 products (16 .. 4096 rows, 320 .. 20000 columns, K 512 .. 28672; mean error 8 .. 15 %).  On 240 others
 // (profiles/gemm_mx_kernel_choice.txt: 16 .. 8192 rows, K 256 .. 28672, every variant's time) the estimate of the chosen variant is off by 10 % in
-// the mean, and the choice is 0.9 % behind the fastest variant in the geometric mean, 19 % at worst.
+// the mean, and the choice is 0.9 % behind the fastest variant in the geometric mean, 19 % at worst.  On 260 more, with 96 x 64 and weights not in the
+// Infinity Cache (40 .. 1100 rows, 800 .. 24000 columns, K 512 .. 14000), 1.9 %, 22 % at worst (K = 512).
 struct cost_t {
     int tm, tn;
     double start, alone, busy, tile;
 };
-// (96 x 64: fitted to 140 products of M 72 .. 384, N 2048 .. 16384, K 1024 .. 8192.)
+// (96 x 64: fitted to 140 products of M 72 .. 384, N 2048 .. 16384, K 1024 .. 8192.  200 products of M 40 .. 2000, N 600 .. 30000, K 512 .. 14000 that it is chosen for:
+// geometric mean 1.14 over the other variants' choice, 0.984 .. 1.40.)
 constexpr cost_t COST[6] = {{128, 128, 0.9, 0.743, 0.521, 3.2},
                             {128, 128, 0.2, 0.448, 0.500, 5.0},
                             {64, 64, 2.8, 0.138, 0.222, 1.4},
@@ -566,6 +568,7 @@ int gemm_mx_small_pick(int64_t M, int64_t N, int64_t stages, double *us, int var
     for (int v = 0; v < variants; ++v) {
         const small::cost_t &c = small::COST[v];
         const double L = (double)ceil_div(ceil_div(M, c.tm) * ceil_div(N, c.tn), 256);
+        if (v == 5 && L > 1.0) continue; // (see v96x64_t)
         const double each = c.alone > c.busy * L ? c.alone : c.busy * L;
         const double t = c.start + (double)stages * each + c.tile * L;
         if (v == 0 || t < *us) {

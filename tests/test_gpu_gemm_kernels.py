@@ -199,6 +199,27 @@ def test_96_row_tiles(ah, force, M, N, K, k):
     assert torch.equal(got[12, torch.bfloat16], got[12, torch.float32].to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("M,N,K,chosen", [(610, 1971, 5376, True), (96, 16384, 4096, True), (261, 15506, 7168, False), (191, 23746, 9056, False)])
+def test_96_row_tiles_only_one_per_compute_unit(ah, force, M, N, K, chosen):
+    """Up to 256 of the 96 x 64 tiles, and above: the chosen kernel's bits are those of the 96 x 64 tiles, whose two waves per part add in an order of
+    their own, or not (scaling blocks of very different sizes, so that the sums are rounded)."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+
+    def operand(rows):
+        sizes = torch.exp2(torch.randint(-12, 13, (rows, K // 32, 1), generator=gen, device="cuda").float())
+        return ah.Operand((torch.randn(rows, K // 32, 32, generator=gen, device="cuda") * sizes).view(rows, K).to(torch.bfloat16), True)
+    A, B = operand(M), operand(N)
+    say("choice of the 96 x 64 tiles", (M, N, K))
+    got = {}
+    for kernel in (0, 12):
+        force(kernel)
+        got[kernel] = ah.adahop_gemm(A, B, inputs.IHT, 32)["C"]
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[12]) == chosen
+    force(7)
+    assert not torch.equal(ah.adahop_gemm(A, B, inputs.IHT, 32)["C"], got[12])
+
+
 @pytest.mark.parametrize("M,N,K,ld,dtype", [(4250, 8450, 96, 8452, torch.float32), (4250, 8450, 192, 8464, torch.float32),
                                             (8400, 8500, 64, 8501, torch.bfloat16), (6200, 8150, 288, 8192, torch.float32),
                                             (6200, 8150, 480, 8151, torch.float32), (4000, 3900, 32, 3901, torch.float32),
