@@ -646,7 +646,7 @@ def test_row_and_column_product_where_the_memory_ends_with_the_matrix(ah, N, K, 
 @pytest.mark.parametrize("strategy", [inputs.IHT, inputs.IHT_OE_ROW, inputs.IHT_OE_COL, inputs.IHT_OE_K])
 def test_quantisers_of_both_operands(ah, layouts, M, N, K, b, strategy):
     """Rows of one unit, of a shorter last unit, of several rows per workgroup and of more than one pass; both operands in
-    one launch and (the largest pair beside a K-strided operand) in two.  Codes and scales are the oracle's bits; with the
+    one launch (test_quantisers_of_a_large_and_a_small_operand: in two).  Codes and scales are the oracle's bits; with the
     indices handed in, so that the extracted parts are gathered by kernels of their own, C has the same bits."""
     k = {inputs.IHT: 0, inputs.IHT_OE_ROW: max(1, M // 50), inputs.IHT_OE_COL: max(1, N // 50), inputs.IHT_OE_K: max(1, K // 50)}[strategy]
     A = inputs.matrix(M, K, 1.0, 9200, row_outliers=(2, 60.0, 60.0), col_outliers=(3, 30.0, 30.0))
@@ -672,6 +672,25 @@ def test_quantisers_of_both_operands(ah, layouts, M, N, K, b, strategy):
         rc, rs = orc.iht_quantize(bits, True, b, zo, mask_k)
         assert np.array_equal(host(out[name + "_scales"]), rs), name
         assert np.array_equal(host(out[name + "_codes"]), rc), name
+
+
+@pytest.mark.parametrize("M,N,K", [(24576, 40, 2048), (24577, 40, 2048), (24600, 12400, 2048), (900, 24601, 2080)])
+@pytest.mark.parametrize("layouts", [(True, False), (False, True)])
+def test_quantisers_of_a_large_and_a_small_operand(ah, layouts, M, N, K):
+    """A K-contiguous operand beside a K-strided one, on both sides of 48 Mi elements and of twice as many as the other's: the bits of each by itself,
+    also where one of them is rounded stochastically."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    say("quantisers of a large and a small operand", layouts, (M, N, K))
+    ops = []
+    for rows, kc in ((M, layouts[0]), (N, layouts[1])):
+        ld = K if kc else (rows + 7) // 8 * 8
+        t = torch.randn(*((rows, ld) if kc else (K, ld)), generator=gen, device="cuda").to(torch.bfloat16)
+        ops.append(ah.Operand(t if kc else t[:, :rows], kc))
+    for seeds in ((None, None), (5, None), (None, 6)):
+        out = ah.adahop_gemm(*ops, inputs.IHT, 32, sr_seed_a=seeds[0], sr_seed_b=seeds[1])
+        for name, op, seed in (("a", ops[0], seeds[0]), ("b", ops[1], seeds[1])):
+            codes, scales = ah.adahop_iht_quantize(op, 32, sr_seed=seed)
+            assert torch.equal(codes, out[name + "_codes"]) and torch.equal(scales, out[name + "_scales"]), (name, seeds)
 
 
 @pytest.mark.parametrize("dim,k,free_kc", [(40, 40, True), (257, 3, True), (1024, 200, True), (1025, 256, True), (2048, 30, True), (2049, 30, True),
