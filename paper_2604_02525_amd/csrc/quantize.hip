@@ -925,11 +925,12 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
 
 // The top-k selection in workgroup 0, an operand that does not depend on it in the others.  Every workgroup of the launch gets the LDS that
 // the selection needs (46 KB for 8192 keys).  Beside a K-contiguous operand, whose own kernel needs none, workgroups of 512 threads let more waves
-// share it, and hold more keys than the 8192 of 256 threads; with few keys the smaller ones are a little faster.  Whole calls with 1 % of the rows
-// extracted, M x N x K, us with 256 / 512 / 1024 threads: 8192 x 4096 x 4096 126.2 / 123.7 / 123.4, 8192 x 2048 x 2048 67.6 / 65.2 / 64.5, 4096 x 4096 x 4096 88.9 /
-// 87.1 / 87.8, 3000 x 8192 x 2048 74.9 / 73.0 / 74.7, but 2016 x 4096 x 11008 113.3 / 114.5 / 116.9, 1024 x 2048 x 8192 51.9 / 52.7 / 53.0.
+// share it, and hold more keys than the 8192 of 256 threads; with few keys beside a large operand, which outlasts their selection anyway, the smaller ones
+// are a little faster.  Whole calls with 1 % of the rows extracted, M x N x K, us with 256 / 512 threads: 8192 x 4096 x 4096 126.2 / 123.7, 4096 x 4096 x 4096 88.9 /
+// 87.1, 2048 x 4096 x 4096 77.4 / 76.1 (each call waited for), 1024 rows beside a K-strided operand of 1 M elements, read in place, 35.5 / 34.3 (the same), but
+// 2000 x 8192 x 8192 142.2 / 143.9, 2000 x 4096 x 11008 113.9 / 116.1, 500 x 8192 x 8192 95.3 / 97.3.
 constexpr int TOPK_BESIDE_DIM = 8192, TOPK_BESIDE_DIM_KC = 16384;
-template <quant_kind_t OP> constexpr int topk_threads(int64_t dim) { return OP == KC && dim > 2048 ? 512 : 256; }
+bool topk_by_512(int64_t dim, const quant_t &q) { return dim > 2048 || q.outer * q.K <= 16ll << 20; } // (K-contiguous)
 template <int B, quant_kind_t OP, bool TAIL, int NT> __global__ __launch_bounds__(NT) void k_topk_and_quant(topk_job_t t, quant_t q)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t dyn[];
@@ -1198,7 +1199,7 @@ template <int B> int launch_topk_b(const topk_job_t &t, quant_kind_t kind, const
         return check_launch();
     };
     auto pick = [&](auto tail) {
-        return topk_threads<KC>(t.dim) == 512 ? go(tail, std::integral_constant<int, 512>()) : go(tail, std::integral_constant<int, 256>());
+        return topk_by_512(t.dim, q) ? go(tail, std::integral_constant<int, 512>()) : go(tail, std::integral_constant<int, 256>());
     };
     return q.K % 256 ? pick(std::true_type()) : pick(std::false_type());
 }

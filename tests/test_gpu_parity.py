@@ -701,7 +701,7 @@ def test_quantisers_of_a_large_and_a_small_operand(ah, layouts, M, N, K):
 @pytest.mark.parametrize("ties", [False, True])
 def test_selection_beside_a_quantiser(ah, dim, k, free_kc, strategy, ties):
     """Fewer and more keys than threads, k up to and past what the threads' maxima can bound, the largest counts that the joint
-    launches take (of 256 threads 2048 beside a K-contiguous operand and 8192 beside a K-strided one, of 512 threads 16384) and one more; equal
+    launches take (of 256 threads 8192, beside a K-strided operand, of 512 threads 16384) and one more; equal
     scores.  Indices and mask are those of the selection by itself, codes the oracle's.  (Beside a K-strided operand more than 96 rows: fewer
     are multiplied on the way of its quantiser, which then waits for the selection.)"""
     K, other = 96, 200
@@ -719,6 +719,22 @@ def test_selection_beside_a_quantiser(ah, dim, k, free_kc, strategy, ties):
     for name, b, zo in (("a" if row else "b", bits, host(want_mask)), ("b" if row else "a", free, None)):
         rc, rs = orc.iht_quantize(b, True, 32, zo, None)
         assert np.array_equal(host(out[name + "_scales"]), rs) and np.array_equal(host(out[name + "_codes"]), rc), name
+
+
+@pytest.mark.parametrize("dim,other,K", [(2048, 4096, 4096), (2048, 4104, 4096), (2049, 4104, 4096), (1500, 8200, 2080), (8193, 8192, 4096), (8193, 4200, 8192), (8193, 8193, 8192)])
+def test_selection_beside_a_large_quantiser(ah, dim, other, K):
+    """Beside K-contiguous operands on both sides of 16 Mi elements, where workgroups of 256 threads take up to 2048 keys, and of 32 and 64 Mi,
+    above which more than 8192 keys are selected first: the bits of each step by itself."""
+    gen = torch.Generator(device="cuda").manual_seed(dim + K)
+    x, y = (ah.Operand(torch.randn(n, K, generator=gen, device="cuda").to(torch.bfloat16), True) for n in (dim, other))
+    say("selection beside a large quantiser", dim, other, K)
+    want_idx, want_mask, _ = ah.adahop_foid_topk(x, 0, 20)
+    out = ah.adahop_gemm(x, y, inputs.IHT_OE_ROW, 32, 20)
+    torch.cuda.synchronize()
+    assert torch.equal(out["idx"], want_idx) and torch.equal(out["mask"], want_mask)
+    for name, op, zo in (("a", x, want_mask), ("b", y, None)):
+        codes, scales = ah.adahop_iht_quantize(op, 32, zero_outer=zo)
+        assert torch.equal(out[name + "_codes"], codes) and torch.equal(out[name + "_scales"], scales), name
 
 
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
