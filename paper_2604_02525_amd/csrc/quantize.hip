@@ -407,7 +407,9 @@ __device__ __forceinline__ void quant_kc_unit(const quant_t &q, int64_t row, uin
 // FLAT = 0: blockIdx.x is the row, blockIdx.y and the thread its units, 16 to a workgroup; FLAT = 1: the units of all rows are
 // numbered consecutively.  FLAT = 0 where a row is exactly one workgroup (and for counts above row_of_unit's): where the last of a row's
 // workgroups has fewer units the rest of it idles, and with several of them a row's parts are written far apart in time.  FLAT = 0 / 1, us: 10000 rows x
-// 4096 18.0 / 18.6, x 4256 27.2 / 19.9, x 3072 15.4 / 15.0, x 11008 53.2 / 45.4; 28672 x 8192 113 / 99; 16384 x 28672 232 / 196.
+// 4096 18.0 / 18.6, x 4256 27.2 / 19.9, x 3072 15.4 / 15.0, x 11008 53.2 / 45.4; 28672 x 8192 113 / 99; 16384 x 28672 232 / 196.  Rounded stochastically, which is
+// bound by vector instructions, and fewer of them with a row that is the same for the workgroup, also where a row is several whole workgroups: 28672 x 8192 161
+// / 165, 8192 x 12288 67.9 / 69.8, but x 4256 33.8 / 26.5, x 2048 16.6 / 13.6.
 template <int B, int FLAT, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_quant_kc16(quant_t q)
 {
     if constexpr (FLAT) {
@@ -1106,7 +1108,7 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
             hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, true>), grid, dim3(256), 0, st, q);
         else
             hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, false>), grid, dim3(256), 0, st, q);
-    } else if (q.upr == 16 || !counts_flat(KC, q)) {
+    } else if (q.upr == 16 || (SR && q.upr % 16 == 0) || !counts_flat(KC, q)) {
         const dim3 grid((unsigned)q.outer, (unsigned)ceil_div(q.upr, 16));
         if (tail)
             hipLaunchKernelGGL((k_quant_kc16<B, 0, SR, true>), grid, dim3(256), 0, st, q);
