@@ -225,6 +225,7 @@ int adahop_oht_inverse(float *C, int64_t M, int64_t N, int64_t ldc, int oht_bloc
  *     same strategy, iht_block, k and indices, and is not quantised again; the bf16 operand is still
  *     required (FOID and the BF16 outlier product read it).  If the residual of a packed operand
  *     depends on the indices (see above) and k > 0, use_given_idx must be set: INVALID_ARG otherwise.
+ *     C has the bits that it has with that operand quantised in the call.
  *     The workspace regions of an operand packed by the caller are left untouched.
  *   c_bf16: 0: C is float [M, ldc]; 1: C is bf16 [M, ldc] (2-byte aligned), every element the fp32
  *     result rounded to nearest even once (the K-channel product is added before the rounding, the

@@ -9,8 +9,8 @@ static thread_local int g_last_hip_error = 0;
 void set_last_hip_error(int e) { g_last_hip_error = e; }
 
 // Largest operand extents.  They keep every launch legal: the second grid dimension of a launch may not exceed
-// 65535, and the kernels put K / 256 (quantisers) and stored rows / 256 (pattern detector) there.  The OHT kernels put outer / block there and check it
-// themselves (oht_grid_ok).
+// 65535, and the kernels put K / 4096 (K-contiguous quantiser) and stored rows / 256 (pattern detector) there.  The OHT kernels put outer / block there and check it
+// themselves (oht_grid_ok).  Grids of one dimension, as the K-strided quantisers', are below 2^24 workgroups: validate_operand bounds outer x K.
 static const int64_t MAX_OUTER = (int64_t)1 << 21;
 static const int64_t MAX_K = (int64_t)1 << 21;
 
@@ -408,8 +408,9 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // here, which are distinct: a repeated index in a caller's list would leave a position of the copy unwritten, where the separate
     // gather reads the row twice.
     // The table of K-channels takes the place of the scores; above the selection's own limit it costs a launch, less than the separate
-    // gather of a K-contiguous operand (4096 x 4096 x 65536, 655 channels: the whole call 4 % faster).  That of rows and columns lies where the bf16 product keeps its partial sums,
-    // which nobody writes before the quantisers are done: a caller finds the scores in the workspace afterwards.  Where it does not fit
+    // gather of a K-contiguous operand (4096 x 4096 x 65536, 655 channels: the whole call 4 % faster).  That of rows and columns lies where the bf16 product keeps its partial sums:
+    // a caller finds the scores in the workspace afterwards.  Whoever writes those sums, be it the other operand's quantiser, is queued behind the
+    // quantiser that reads the table, on the same stream.  Where it does not fit
     // there (more than 128 rows to choose from for each of the other operand's), the rows are gathered by themselves.
     const bool oe_rc = oe && !oe_k;
     const bool from_a = strategy == ADAHOP_IHT_OE_ROW; // (row / column extraction: of which operand)

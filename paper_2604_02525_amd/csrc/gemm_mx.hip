@@ -776,7 +776,7 @@ int launch_gemm_mx_t(int64_t M, int64_t N, int64_t K, const uint8_t *a_codes, co
     // so that the tiles of the fewest rounds win (all of these add in the same order).  256 x 256 / 256 x 128 / the choice between 256 x 256 and 128 x 128 where rows
     // of C are no whole pairs, us: 1000 x 5000 x 3040 28.3 / 20.6 / 21.8, 1024 x 8192 x 8192 46.3 / 40.7, 2016 x 11008 x 4096 60.7 / 55.9, 700 x 200 x
     // 4096 8.7 / 6.9, but 8192 x 4096 x 4096 73.1 / 76.6, 16384 x 4096 x 4096 137 / 144, 4096 x 4096 x 2048 26.9 / 28.8 (and 8192 x 8192 x 2048 93 / 86,
-    // with ldc = 8200 82 / 84).
+    // with ldc = 8200 82 / 84: the rounds say 256 x 256, and with so short a K the bytes of C would have a say).
     if (c.large && c.dual && sizeof(OUT) == 2) {
         const int64_t stages = ceil_div(K, 256) + kpad / 64;
         const double us256 = us_large_tiles(M, N, stages, false);
