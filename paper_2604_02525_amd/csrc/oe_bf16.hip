@@ -897,7 +897,9 @@ int launch_oe_reduce(const float *P, int nslice, int64_t rows_all, int64_t Lo, b
 // call: two for each 421, four 416, eight 416 us), and more where the sums would not fit otherwise.
 // Not where L's quantiser would then have to wait for a selection that could stand beside it, and so does that of S: it takes some
 // work for that to pay.  416 x 4096 (128 tiles), 55 columns, whole call 45 us beside, 48 on the way; 32 x 1440
-// (23) 36.9 / 38.1; 96 x 8992 (141) 78.7 / 79.3; 32 x 17376 (272) 52.7 / 49.5; 32 x 20608 (322) 77.2 / 74.3.
+// (23) 36.9 / 38.1; 96 x 8992 (141) 78.7 / 79.3; 32 x 17376 (272) 52.7 / 49.5; 32 x 20608 (322) 77.2 / 74.3.  (Extracted rows of a K-contiguous S are read
+// in place, and the selection stands beside S's quantiser: on the way at any size, 4096 rows, 40 extracted, x 416 x 4096 46.0 / 40.3, x 32 x 1440 32.9 / 27.2,
+// 1024 rows, 10 extracted, x 512 x 1024 41 / 34, each call waited for.)
 bool oe_rowcol_on_the_way(const adahop_operand_t &S, const adahop_operand_t &L, int k, outlier_job_t *e)
 {
     const int64_t Lo = L.outer, K = L.K;

@@ -165,3 +165,37 @@ def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, 
     again = ah.adahop_gemm(A, B, strategy, 32, k, idx=idx, **{packed: ah.adahop_pack_operand(l, row, strategy, 32)})
     assert torch.equal(again["C"].view(torch.int32), want["C"].view(torch.int32))
     assert bool(want["C"][idx.long()].isinf().any() if row else want["C"][:, idx.long()].isinf().any())
+
+
+@pytest.mark.parametrize("long,K,k", [(20008, 4320, 64), (4100, 8224, 9)])
+def test_products_by_themselves_under_capture(long, K, k):
+    """The products of a packed operand, long slices and short, from a graph: every replay, with new rows in place and eager calls between, has the
+    eager call's bits."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2604_02525_amd import binding as ah
+    print("[case] capture", long, K, k, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(long)
+    rows = torch.randn(3, 96, K, generator=gen, device="cuda").to(torch.bfloat16)
+    A = ah.Operand(rows[0].clone(), True)
+    B = ah.Operand(torch.randn(K, (long + 7) // 8 * 8, generator=gen, device="cuda").to(torch.bfloat16)[:, :long], False)
+    packed = ah.adahop_pack_operand(B, True, inputs.IHT_OE_ROW, 32)
+    ws = torch.empty(ah.adahop_gemm_workspace_bytes(96, long, K, inputs.IHT_OE_ROW, k), dtype=torch.uint8, device="cuda")
+    C, idx = torch.empty(96, long, device="cuda"), torch.randperm(96, generator=gen, device="cuda")[:k].to(torch.int32)
+
+    def call(out):
+        return ah.adahop_gemm(A, B, inputs.IHT_OE_ROW, 32, k, idx=idx, Cout=out, workspace=ws, b_packed=packed)
+    ah.adahop_prepare_device()
+    call(C)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(C)
+    for i in (1, 2, 0):
+        A.tensor.copy_(rows[i])
+        graph.replay()
+        got = C.clone()
+        want = torch.full_like(C, 5.0)
+        call(want)
+        torch.cuda.synchronize()
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), i
