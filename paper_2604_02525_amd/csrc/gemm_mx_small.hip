@@ -419,14 +419,17 @@ __global__ __launch_bounds__(256, NST == 1 ? 4 : 2) void k_gemm_mx_small(int64_t
             if (row < M && col < N) put(C + row * ldc + col, v);
         }
     } else {
+        // Row by row over the wave's columns: what lies together is written together, and where rows lie off the 64-byte grid the two halves of the
+        // line between two accumulator tiles meet in the L2 (tile by tile / row by row, us: 2528 x 13392 x 96 43.8 / 36.6, 6000 x 9000 x 320
+        // 72 / 60, 8192 x 9001 x 96 90 / 66, 4096 x 11008 x 480 58.7 / 53.9, 28672 x 8192 x 64 in bf16 103 / 91).
 #pragma unroll
         for (int i = 0; i < TMB; ++i)
 #pragma unroll
-            for (int j = 0; j < TNB; ++j) {
-                const int64_t col = n0 + (wn * TNB + j) * 32 + l32;
+            for (int r = 0; r < 16; ++r) {
+                const int64_t row = m0 + (wm * TMB + i) * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t row = m0 + (wm * TMB + i) * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+                for (int j = 0; j < TNB; ++j) {
+                    const int64_t col = n0 + (wn * TNB + j) * 32 + l32;
                     if (row < M && col < N) put(C + row * ldc + col, acc[i][j][r]);
                 }
             }
@@ -494,6 +497,11 @@ typedef variant_t<2, 2, 2, 2, 1, 2, 1> v128_t;    // 128 x 128, two workgroups p
 // Not for more than 64 MB of fp32 off the 64-byte grid, where twice the tiles in flight cost more line pieces than they hide (9687 x
 // 14001 x 64 133 / 203 us, 6000 x 9001 x 64 43 / 46; 3324 x 2547 x 32, 32 MB, 13.8 / 12.1), and not for K = 256, where it gains nothing.
 typedef variant_t<2, 2, 2, 2, 1, 1, 1> v128one_t;
+// The same in tiles of 64 x 256, for fp32 rows on the 64-byte grid and more than 80 MB of C: the four waves store 1 KiB of a row at about the
+// same time, and stores alone reach 5.9 TB/s in such tiles, 5.5 in 128 x 128.  128 x 128 / 64 x 256, us: 8192 x 12288 x 96 75.9 / 69.4, 16384 x 16384 x
+// 96 194 / 166, 8192 x 14336 x 192 88.7 / 80.8, 8192 x 4096 x 192 35.5 / 33.3; below that as much as they gain is lost with the rows of B that a tile reads, 5152
+// x 2912 x 64 (60 MB) 17.3 / 18.2, 2048 x 8192 x 192 (64 MB) 19.0 / 19.2; off the grid 8192 x 9001 x 96 66 (two buffers) / 70, bf16 28672 x 8192 x 64 91 / 110.
+typedef variant_t<2, 2, 1, 4, 1, 1, 1> v64x256_t;
 typedef variant_t<2, 2, 2, 2, 1, 3, 1> v128deep_t; // 128 x 128, one workgroup, two stages on the way
 typedef variant_t<2, 2, 1, 1, 4, 4, 1> v64_t;     // 64 x 64
 typedef variant_t<1, 2, 1, 1, 4, 4, 1> v32x64_t;  // 32 x 64
@@ -533,7 +541,9 @@ int configure_gemm_mx_small()
     int rc = check_hip(hipGetDevice(&dev));
     if (rc != ADAHOP_OK || !once.need(dev)) return rc;
     using namespace small;
-    if ((rc = v128_t::configure()) != ADAHOP_OK || (rc = v128one_t::configure()) != ADAHOP_OK || (rc = v128deep_t::configure()) != ADAHOP_OK ||
+    if ((rc = v128_t::configure()) != ADAHOP_OK || (rc = v128one_t::configure()) != ADAHOP_OK ||
+        (rc = v64x256_t::allow<false, false, float>()) != ADAHOP_OK || (rc = v64x256_t::allow<true, false, float>()) != ADAHOP_OK ||
+        (rc = v128deep_t::configure()) != ADAHOP_OK ||
         (rc = v64_t::configure()) != ADAHOP_OK || (rc = v32x64_t::configure()) != ADAHOP_OK ||
         (rc = v32_t::configure()) != ADAHOP_OK || (rc = v96x64_t::configure()) != ADAHOP_OK)
         return rc;
@@ -549,8 +559,14 @@ static int launch_small_t(int variant, int64_t M, int64_t N, int64_t K, const ui
     using namespace small;
     switch (variant) {
     case 0:
-        if (K <= 192 && kpad == 0 && (sizeof(OUT) == 2 || c_rows_streamed(C, ldc * 4) || M * N <= (16 << 20)))
-            return v128one_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+        if (K <= 192 && kpad == 0) {
+            const bool streamed = c_rows_streamed(C, ldc * 4);
+            if constexpr (sizeof(OUT) == 4) {
+                if (streamed && M * N > (20 << 20)) return v64x256_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+            }
+            if (sizeof(OUT) == 2 || streamed || M * N <= (16 << 20))
+                return v128one_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
+        }
         return v128_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 1: return v128deep_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);
     case 2: return v64_t::launch(M, N, K, a, as, b, bs, C, ldc, Ag, Bg, kpad, st);

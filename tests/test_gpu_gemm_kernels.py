@@ -247,6 +247,26 @@ def test_short_products_with_a_large_c(ah, M, N, K, ld, dtype):
     assert float((np.abs(got - ref) - step * np.abs(ref) - bar * (1.0 + step)).max()) <= 0.0
 
 
+@pytest.mark.parametrize("M,N,K", [(5001, 4400, 64), (330, 65552, 192), (21000, 1040, 32), (2048, 10304, 128)])
+def test_wide_tiles_of_one_stage(ah, force, M, N, K):
+    """64 x 256 tiles (fp32, one stage of K, more than 80 MB on the 64-byte grid): the bits of the 128 x 128 ones, which add in the same
+    order, with scales from the quantisers and from canonical arrays, remainders of both tile edges, and the gap behind the rows as it was."""
+    gen = torch.Generator().manual_seed(M + K)
+    A, B = (ah.Operand(torch.randn(n, K, generator=gen).to(torch.bfloat16).cuda(), True) for n in (M, N))
+    say("wide tiles", (M, N, K))
+    got = {}
+    for which in (0, 8):
+        force(which)
+        room = torch.full((M, N + 16), 7.0, device="cuda")
+        r = ah.adahop_gemm(A, B, inputs.IHT, 32, Cout=room[:, :N])
+        packed = ah.adahop_gemm_mx(r["a_codes"], r["a_scales"], r["b_codes"], r["b_scales"])
+        torch.cuda.synchronize()
+        assert bool((room[:, N:] == 7.0).all())
+        got[which] = room[:, :N].clone()
+        assert torch.equal(packed, got[which])
+    assert torch.equal(got[0], got[8])
+
+
 @pytest.mark.parametrize("kernel", SMALL)
 @pytest.mark.parametrize("M,N,K,k", [(40, 70, 96, 9), (96, 264, 1120, 70), (150, 129, 2048, 200)])
 def test_small_tiles_with_k_channels(ah, force, kernel, M, N, K, k):
