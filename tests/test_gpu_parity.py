@@ -538,10 +538,11 @@ def test_oe_gemm_bf16_standalone(ah, M, N, K, k_row, k_col, k_k):
 
 # ----------------------------------------------------------------------------- pattern detection (App. A)
 
-@pytest.mark.parametrize("shape", [(2, 32), (37, 544), (9, 4128), (289, 1024), (4102, 8224)])
+@pytest.mark.parametrize("shape", [(2, 32), (37, 544), (9, 4128), (289, 1024), (2500, 4096), (2060, 6176), (4102, 8224)])
 @pytest.mark.parametrize("k_contig", [True, False])
 def test_detect_pattern_at_block_edges(ah, shape, k_contig):
-    """Fewer rows than a workgroup has waves, rows one past a block, a chunk of one column, both workgroup sizes; what lies
+    """Fewer rows than a workgroup has waves, rows one past a block, a chunk of one column, the most blocks of the kernel with
+    small pieces, both workgroup sizes of the other; what lies
     behind the rows of the stored matrix is not a number.  The bounds of the test below."""
     outer, K = shape
     logical = inputs.matrix(outer, K, 1.0, 9100, col_outliers=(2, 50.0, 50.0))
