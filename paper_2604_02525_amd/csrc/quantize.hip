@@ -343,6 +343,14 @@ __device__ __forceinline__ uint32_t row_of_unit(uint32_t u, uint32_t upr, uint32
     return upr == 1 ? u : __umulhi(u, magic); // u / upr, exact for u upr < 2^32
 }
 
+// The order of the workgroups of a K-strided operand (ks_order).
+struct ks_order_t {
+    uint32_t run, rest; // workgroups of an XCD (of the first `rest`: one more); run = 0: the order as it is
+    uint32_t groups;    // whole groups of KS_GROUP column tiles
+    uint32_t per_group, narrow, narrow_magic; // workgroups of a group; column tiles of a last, narrower one, ceil(2^32 / narrow)
+    uint64_t magic;                           // ceil(2^44 / per_group): v / per_group is exact for v per_group < 2^44
+};
+
 // One operand's quantisation: what is read, which entries count as zero and where the results go.
 struct quant_t {
     const uint16_t *x;
@@ -355,7 +363,8 @@ struct quant_t {
     row_gather_t gr;
     uint32_t upr, magic;  // 256-element units per row (K-strided: K-blocks); ceil(2^32 / upr)
     uint32_t rows_per_wg; // of the kernel that copies K-channels
-    uint32_t col_tiles, tile_magic, group; // K-strided: workgroups along the outer index, ceil(2^32 / col_tiles); order, see there
+    uint32_t col_tiles;   // K-strided: workgroups along the outer index
+    ks_order_t order;
 };
 
 // K-contiguous operand: 16 lanes per 256 K-elements of a row, unit `unit` of row `row`.  TAIL: K % 256 != 0 (an instance of
@@ -514,14 +523,14 @@ template <int B, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_qu
 // blocks of a lane lie entirely in its registers (no cross-lane maximum).
 //
 // (A variant with 128 columns per workgroup, 256-byte pieces of the operand's K-rows, runs at the same speed, and so do plain and
-// write-through stores of the codes in whole 128-byte rows, other orders of the workgroups, and the kernel without its transform: what it
-// waits for is the memory, 46 us of 73 on 4096 x 32768 for the reads and the rest for the writes of 128-byte pieces of many rows.)
+// write-through stores of the codes in whole 128-byte rows.  What it waits for is the memory, and that depends on the order of the workgroups:
+// see ks_order.  Reads and writes alone, without the transform, take 62 of 65 us on 4096 x 32768.)
 //
 // LDS layout: K-row kk at kk * 128 bytes, its four pieces of 32 bytes exchanged by kk's bits 1 and 6: the eight rows that the
 // half wave of a transposing read touches then lie in eight different eighths of the 64 banks.
 // ------------------------------------------------------------------------------------------------
 constexpr int KS_COLS = 64, KT_PITCH = 128;
-constexpr unsigned KS_GROUP = 32, KS_GROUP_FROM = 200; // column tiles that walk the K-blocks together; from how many on
+constexpr uint32_t KS_GROUP = 16, KS_PLAIN = 2048; // column tiles that walk the K-blocks together; tiles up to which they need not
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
@@ -770,35 +779,33 @@ __device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uin
     ks_finish<B, SR>(q, tid, o0, k0, d);
 }
 
-// Workgroups start in the order of their linear index, x fastest.  Taken as it is, that order runs all column
-// tiles of one K-block before the next K-block: the workgroups in flight together then write 128-byte pieces of
-// thousands of different output rows.  Instead the index walks KS_GROUP neighbouring column tiles through all
-// K-blocks before it moves to the next group: the reads still come in pieces of KS_GROUP x 128 bytes of a K-row, and
-// an output row is written in one go.  Measured: operands with rows of 28672 elements (448 column tiles: the
-// about 1000 workgroups in flight span two K-blocks, 300 bytes of an output row) 292 -> 237 us ([16384][28672])
-// and 133 -> 122 us ([8192][28672]); 384, 320 and 224 column tiles 11 .. 13 % faster; 256 column tiles 7 % faster
-// or 5 % slower by K; with 192 column tiles and fewer the plain order is as fast or up to 10 % faster and is kept
-// (group == 0).
-// Workgroup L of nx column tiles x ny K-blocks.
-__device__ __forceinline__ void ks_order(unsigned group, uint32_t nx, uint32_t magic, uint32_t ny, uint32_t L, uint32_t &bx, uint32_t &by)
+// Workgroup L -> column tile bx, K-block by.  Consecutive workgroups go to the eight XCDs in turn; here each XCD takes a contiguous run of the
+// sequence in which KS_GROUP neighbouring column tiles walk all K-blocks together.  What an XCD's workgroups in flight touch then lies together:
+// reads in pieces of KS_GROUP x 128 bytes of a K-row, which share an L2 where the rows do not begin on 128-byte lines, and a few output rows,
+// each written in one go (their scales too, of which 16 K-blocks share a line).  In the plain order (all column tiles of a K-block, then
+// the next) eight L2s held parts of the same lines, and 128-byte pieces of thousands of output rows were written at a time.  Plain / in runs,
+// us: [32768][4096] 72.7 / 64.9, [28672][8192] 129 / 119, [8192][14336] 63.8 / 56.6, [28672][9056] 181 / 148, [28672][20976] (rows off the
+// lines) 482 / 360, [11008][4096] 27.1 / 25.3; groups of 8 and 32 within 2 % of that.  Workgroups that are nearly all in flight at once gain only where
+// rows lie off the lines ([2048][11488] 16.8 / 14.9, [4096][1000] 5.8 / 5.1, but [4096][4096] 11.1 / 12.6, [5120][6400] 18.4 / 19.4, [8192][4096] 19.5 /
+// 20.3): up to KS_PLAIN tiles take the plain order there (run = 0).
+__device__ __forceinline__ void ks_order(const ks_order_t &o, uint32_t L, uint32_t &bx, uint32_t &by)
 {
-    if (!group) {
-        by = row_of_unit(L, nx, magic);
-        bx = L - by * nx;
-        return;
+    const uint32_t xcd = L & 7, v = o.run ? xcd * o.run + min(xcd, o.rest) + (L >> 3) : L;
+    const uint32_t g = (uint32_t)(v * o.magic >> 44), r = v - g * o.per_group;
+    if (g < o.groups) {
+        by = r / KS_GROUP;
+        bx = g * KS_GROUP + r % KS_GROUP;
+    } else { // the last group is narrower
+        by = o.narrow == 1 ? r : __umulhi(r, o.narrow_magic);
+        bx = g * KS_GROUP + r - by * o.narrow;
     }
-    const uint32_t full = nx / group * group, whole = full * ny;
-    const uint32_t per = L < whole ? group : nx - full; // (the last group may be narrower)
-    const uint32_t in = L < whole ? L : L - whole, r = in % (per * ny);
-    bx = (L < whole ? in / (per * ny) * per : full) + r % per;
-    by = r / per;
 }
 
 template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(quant_t q)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[KS_LDS];
     uint32_t bx, by;
-    ks_order(q.group, q.col_tiles, q.tile_magic, q.upr, blockIdx.x, bx, by);
+    ks_order(q.order, blockIdx.x, bx, by);
     quant_ks_tile<B, SR>(q, bx, by, lds);
 }
 
@@ -830,7 +837,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
         return;
     }
     uint32_t bx, slice;
-    ks_order(q.group, q.col_tiles, q.tile_magic, (uint32_t)e.nslice, blockIdx.x, bx, slice);
+    ks_order(q.order, blockIdx.x, bx, slice);
     const int64_t o0 = (int64_t)bx * KS_COLS;
     for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
         const int r = min(t, e.k - 1);
@@ -915,7 +922,7 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
 {
     if constexpr (OP == KS) {
         uint32_t bx, by;
-        ks_order(q.group, q.col_tiles, q.tile_magic, q.upr, block, bx, by);
+        ks_order(q.order, block, bx, by);
         quant_ks_tile<B, SR>(q, bx, by, lds);
     } else if constexpr (OP == KC_GATHER) {
         quant_kc_gather_rows<B, SR, TAIL>(q, block, lds);
@@ -1056,6 +1063,16 @@ template <int B, typename OUT> __global__ __launch_bounds__(TILE_THREADS) void k
     if (m < p.rows[0] && n < p.rows[1]) put_c(C + m * p.ldc + n, v);
 }
 
+ks_order_t order_of(uint32_t nx, uint32_t ny, uint32_t blocks, int64_t ld) // column tiles x K-blocks, or slices of `blocks` K-blocks
+{
+    const uint32_t n = nx * ny, per_group = KS_GROUP * ny; // n < 2^24, ny <= 2^13
+    const bool plain = nx * blocks <= KS_PLAIN && ld % 64 == 0;
+    const uint32_t narrow = plain ? nx : nx % KS_GROUP;
+    const uint32_t narrow_magic = narrow > 1 ? (uint32_t)((((uint64_t)1 << 32) + narrow - 1) / narrow) : 0;
+    if (plain) return {0, 0, 0, per_group, narrow, narrow_magic, 0};
+    return {n >> 3, n & 7, nx / KS_GROUP, per_group, narrow, narrow_magic, (((uint64_t)1 << 44) + per_group - 1) / per_group};
+}
+
 // The descriptor of an operand and the kernel kind that takes it.
 quant_kind_t describe(const quant_job_t &j, quant_t &q)
 {
@@ -1073,9 +1090,10 @@ quant_kind_t describe(const quant_job_t &j, quant_t &q)
     q.magic = magic_of(q.upr);
     q.rows_per_wg = 1;
     q.col_tiles = (uint32_t)ceil_div(x.outer, KS_COLS);
-    q.tile_magic = magic_of(q.col_tiles);
-    q.group = q.col_tiles > KS_GROUP_FROM ? KS_GROUP : 0;
-    if (!x.k_contig) return KS;
+    if (!x.k_contig) {
+        q.order = order_of(q.col_tiles, q.upr, q.upr, x.ld);
+        return KS;
+    }
     if (!q.gk.out) return KC;
     const uint32_t fit = 16 / q.upr, room = (uint32_t)(KC_GATHER_LDS / 2 / (q.gk.kpad + 8)); // rows per pass, and in LDS
     const uint32_t rows = fit < room ? fit : room;
@@ -1084,7 +1102,7 @@ quant_kind_t describe(const quant_job_t &j, quant_t &q)
 }
 
 // Whether row_of_unit is exact for all units of a K-contiguous operand that is taken without a grid of its own (and of K-strided ones: their order
-// is another one above KS_GROUP_FROM column tiles).
+// has divisors of its own).
 bool counts_flat(quant_kind_t kind, const quant_t &q) { return kind != KC || (uint64_t)(q.outer * q.upr + 64) * q.upr < (uint64_t)1 << 32; }
 
 // Workgroups of 256 threads that one launch takes (its threads are counted in 32 bits).
@@ -1296,6 +1314,7 @@ int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_jo
 {
     quant_t q;
     if (describe(job, q) != KS || (b >= 0 && job.sr_seed) || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
+    q.order = order_of(q.col_tiles, (uint32_t)e.nslice, q.upr, q.ld);
     switch (b) {
     case -1: return launch_outliers_b<-1>(q, e, st);
     case 32: return launch_outliers_b<32>(q, e, st);

@@ -204,3 +204,20 @@ def test_units_counted_beyond_the_one_multiplication(ah):
     for at in (0, 150):
         c, s = ah.adahop_iht_quantize(ah.Operand(x[at:at + 150], True), 64)
         assert torch.equal(c, codes[at:at + 150]) and torch.equal(s, scales[at:at + 150])
+
+
+@pytest.mark.parametrize("outer,K", [(40, 32), (72, 320), (1000, 2336), (1032, 2336), (4160, 8192), (8200, 4352), (29992, 512), (6976, 7712)])
+@pytest.mark.parametrize("block", [0, 32])
+def test_orders_of_the_workgroups_of_a_k_strided_operand(ah, outer, K, block):
+    """Whole groups of 16 column tiles, a last group of one and of several, none at all, workgroups that are a multiple of eight and not, up to and
+    beyond the count that keeps the plain order, rows on 128-byte lines and off them: the bytes of the same matrix stored K-contiguous, whose
+    kernel numbers its work otherwise, with an extracted column and K-channels masked as well."""
+    gen = torch.Generator(device="cuda").manual_seed(outer + K)
+    x = torch.randn(outer, K, generator=gen, device="cuda").to(torch.bfloat16)
+    t = x.t().contiguous()
+    say("K-strided order", outer, K, block)
+    idx = torch.tensor([0, K // 2, K - 1], dtype=torch.int32, device="cuda")
+    for strategy, kw in ((inputs.IHT if block else inputs.NONE, {}), (inputs.IHT_OE_K, dict(k=3, idx=idx)) if block else (inputs.NONE, {})):
+        want, got = (ah.adahop_pack_operand(op, True, strategy, block, **kw) for op in (ah.Operand(x, True), ah.Operand(t, False)))
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
