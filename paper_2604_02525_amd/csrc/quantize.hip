@@ -638,6 +638,45 @@ __device__ __forceinline__ void ks_put_tile(const quant_t &q, int tid, int64_t o
     if (ks_at_end(q, o0, k0)) put((int)(q.K - 1 - k0) >> 5, f.last);
 }
 
+// A tile that lies inside the operand as a whole, with no column masked out (uniform), which all but those at its edges are: no condition
+// on its loads and stores, whose addresses are a scalar base and one 32-bit offset per lane.  The general code spends a third of its
+// vector instructions on these (846 -> 601 per wave and tile at B = 32, with the products of 64 rows 967 -> 671), which the kernels whose workgroups do more
+// than wait for the memory feel: kernels with products, us, 4096 x 32768, 64 rows, 103 -> 97.5, 8192 x 4096, 41 rows, 28.9 -> 27.4, 4096 x 4096, 82 rows,
+// 23.0 -> 21.5; plain ones of 2048 x 4096 9.9 -> 8.6, 8192 x 4096 24.4 -> 23.2, 4096 x 32768 74.9 -> 73.1.
+__device__ __forceinline__ bool ks_whole(const quant_t &q, int64_t o0, int64_t k0)
+{
+    return k0 + 256 <= q.K && o0 + KS_COLS <= q.outer && q.ld <= 1 << 24 && (!q.zero_outer || q.gr.out);
+}
+
+__device__ __forceinline__ uint32_t ks_load_offset(const quant_t &q, int tid) { return ((uint32_t)(tid >> 3) * (uint32_t)q.ld + (uint32_t)(tid & 7) * 8) * 2; }
+
+__device__ __forceinline__ void ks_fetch_whole(const quant_t &q, uint32_t voff, int64_t o0, int64_t k0, ks_tile_t &f)
+{
+    const uint8_t *base = reinterpret_cast<const uint8_t *>(q.x + k0 * q.ld + o0);
+    const int64_t pass = 64 * q.ld;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) f.v[it] = load_once16(base + it * pass + voff);
+}
+
+__device__ __forceinline__ void ks_put_whole(const quant_t &q, int tid, int64_t k0, uint8_t *lds, const ks_tile_t &f)
+{
+    const int cg = tid & 7, rw = tid >> 3;
+    uint8_t *const even = lds + rw * KT_PITCH + ((cg * 16) ^ (ks_swizzle(rw) * 32)), *const odd = lds + rw * KT_PITCH + ((cg * 16) ^ (ks_swizzle(rw + 64) * 32));
+    uint4 v[8];
+#pragma unroll
+    for (int it = 0; it < 8; ++it) v[it] = f.v[it];
+    if (q.zero_k) { // (uniform: a kernel argument)
+        uint8_t *kmask = lds + 256 * KT_PITCH;
+        kmask[tid] = q.zero_k[k0 + tid];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < 8; ++it)
+            if (kmask[it * 32 + rw]) v[it] = make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int it = 0; it < 8; ++it) *reinterpret_cast<uint4 *>(((it & 2) ? odd : even) + it * 32 * KT_PITCH) = v[it];
+}
+
 // LDS -> registers, transposed: wave w takes columns [16 w, 16 w + 16); d[t]: K-elements 64 g + 4 t .. + 3 of the lane's column.
 __device__ __forceinline__ void ks_read_tile(int tid, const uint8_t *lds, v4s (&d)[16])
 {
@@ -649,12 +688,14 @@ __device__ __forceinline__ void ks_read_tile(int tid, const uint8_t *lds, v4s (&
 }
 
 // The column of the lane from its raw elements on: copied out if it is extracted, transformed, quantised and stored.
-template <int B, bool SR> __device__ __forceinline__ void ks_finish(const quant_t &q, int tid, int64_t o0, int64_t k0, const v4s (&d)[16])
+// WHOLE: see ks_whole.
+template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_finish(const quant_t &q, int tid, int64_t o0, int64_t k0, const v4s (&d)[16])
 {
     const int64_t outer = q.outer, K = q.K;
     const int lane = tid & 63, w = tid >> 6, g = lane >> 4, b4 = g & 1, b5 = g >> 1;
-    const int64_t o = o0 + 16 * w + (lane & 15);
-    const bool active = o < outer;
+    const uint32_t col = 16 * w + (lane & 15);
+    const int64_t o = o0 + col;
+    const bool active = WHOLE || o < outer;
     float wv[64];
 #pragma unroll
     for (int t = 0; t < 16; ++t)
@@ -669,7 +710,7 @@ template <int B, bool SR> __device__ __forceinline__ void ks_finish(const quant_
             uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + k0 + 64 * g;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (k0 + 64 * g + 8 * i < K) *reinterpret_cast<uint4 *>(dst + 8 * i) = pieces(d[2 * i], d[2 * i + 1]);
+                if (WHOLE || k0 + 64 * g + 8 * i < K) *reinterpret_cast<uint4 *>(dst + 8 * i) = pieces(d[2 * i], d[2 * i + 1]);
 #pragma unroll
             for (int i = 0; i < 64; ++i) wv[i] = 0.0f;
         }
@@ -735,7 +776,11 @@ template <int B, bool SR> __device__ __forceinline__ void ks_finish(const quant_
             }
         }
     }
-    if (active) {
+    if constexpr (WHOLE) {
+        uint8_t *crow = q.codes + (o0 * (K >> 1) + (k0 >> 1)) + (col * (uint32_t)(K >> 1) + 16 * (uint32_t)at[0]);
+        *reinterpret_cast<uint4 *>(crow) = make_uint4(c[0], c[1], c[2], c[3]);
+        *reinterpret_cast<uint4 *>(crow + (B == 256 ? 64 : B == 128 ? 32 : 16)) = make_uint4(c[4], c[5], c[6], c[7]);
+    } else if (active) {
         uint8_t *crow = q.codes + o * (K >> 1) + (k0 >> 1);
         if (k0 + 32 * at[0] < K) *reinterpret_cast<uint4 *>(crow + 16 * at[0]) = make_uint4(c[0], c[1], c[2], c[3]);
         if (k0 + 32 * at[1] < K) *reinterpret_cast<uint4 *>(crow + 16 * at[1]) = make_uint4(c[4], c[5], c[6], c[7]);
@@ -749,9 +794,9 @@ template <int B, bool SR> __device__ __forceinline__ void ks_finish(const quant_
     const v2u r32 = __builtin_amdgcn_permlane32_swap(four, four, false, false);
     const uint32_t lower = B == 256 ? __builtin_amdgcn_perm(r32.y, r32.x, 0x05040100u) : r32.x;
     const uint32_t upper = B == 256 ? __builtin_amdgcn_perm(r32.y, r32.x, 0x07060302u) : r32.y;
-    const int rot = tail_rotation(K, k0);
+    const int rot = WHOLE ? 0 : tail_rotation(K, k0);
     if (active && g == 0) {
-        uint8_t *srow = q.scales + o * (K >> 5) + (k0 >> 5);
+        uint8_t *srow = q.scales + (o0 * (K >> 5) + (k0 >> 5)) + col * (uint32_t)(K >> 5);
         if (rot == 0 && (reinterpret_cast<uintptr_t>(srow) & 7) == 0) {
             *reinterpret_cast<uint2 *>(srow) = make_uint2(lower, upper);
         } else { // the canonical array has no alignment rule, and the last tile may hold fewer blocks
@@ -762,7 +807,7 @@ template <int B, bool SR> __device__ __forceinline__ void ks_finish(const quant_
         }
     }
     if (q.sm.out && active && g == 1)
-        *reinterpret_cast<uint64_t *>(q.sm.out + ((k0 >> 8) * q.sm.rows + o) * 8) = ((uint64_t)upper << 32 | lower) << (8 * rot);
+        *reinterpret_cast<uint64_t *>(q.sm.out + ((k0 >> 8) * q.sm.rows + o0) * 8 + col * 8) = ((uint64_t)upper << 32 | lower) << (8 * rot);
 }
 
 template <int B, bool SR>
@@ -771,12 +816,20 @@ __device__ __forceinline__ void quant_ks_tile(const quant_t &q, uint32_t bx, uin
     const int64_t o0 = (int64_t)bx * KS_COLS, k0 = (int64_t)by * 256;
     const int tid = threadIdx.x;
     ks_tile_t f;
-    ks_fetch_tile(q, tid, o0, k0, f);
-    ks_put_tile(q, tid, o0, k0, lds, f);
-    __syncthreads();
     v4s d[16];
-    ks_read_tile(tid, lds, d);
-    ks_finish<B, SR>(q, tid, o0, k0, d);
+    if (ks_whole(q, o0, k0)) { // (uniform)
+        ks_fetch_whole(q, ks_load_offset(q, tid), o0, k0, f);
+        ks_put_whole(q, tid, k0, lds, f);
+        __syncthreads();
+        ks_read_tile(tid, lds, d);
+        ks_finish<B, SR, true>(q, tid, o0, k0, d);
+    } else {
+        ks_fetch_tile(q, tid, o0, k0, f);
+        ks_put_tile(q, tid, o0, k0, lds, f);
+        __syncthreads();
+        ks_read_tile(tid, lds, d);
+        ks_finish<B, SR, false>(q, tid, o0, k0, d);
+    }
 }
 
 // Workgroup L -> column tile bx, K-block by.  Consecutive workgroups go to the eight XCDs in turn; here each XCD takes a contiguous run of the
@@ -811,6 +864,7 @@ template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(qu
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A K-strided operand (nothing extracted from it), and on the way its bf16 products with the k <= 16 RT rows extracted from the other
 // one (second term of Eq. 7 / 8): the operand's tile is in registers in the matrix cores' layout anyway, and reading it once more for these products by
@@ -829,7 +883,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
 {
     constexpr int TILE_LDS = RT * 8192 > KS_LDS ? RT * 8192 : KS_LDS;
     __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS + RT * 16 * 8];
-    int64_t *const row_at = reinterpret_cast<int64_t *>(lds + TILE_LDS);
+    const uint16_t **const row_at = reinterpret_cast<const uint16_t **>(lds + TILE_LDS);
     const int64_t K = q.K;
     const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
     if (blockIdx.x >= tiles) {
@@ -841,35 +895,51 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
     const int64_t o0 = (int64_t)bx * KS_COLS;
     for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
         const int r = min(t, e.k - 1);
-        row_at[t] = (e.idx ? e.idx[r] : r) * e.ld;
+        row_at[t] = e.rows + (e.idx ? e.idx[r] : r) * e.ld;
     }
     __syncthreads();
     v4f acc[RT];
 #pragma unroll
     for (int i = 0; i < RT; ++i) acc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     constexpr bool AHEAD = B < 0 && RT <= 3; // (registers that a tile's quantisation needs: with it three workgroups fit, and nothing is gained)
-    ks_tile_t tile;
-    if constexpr (AHEAD) ks_fetch_tile(q, threadIdx.x, o0, (int64_t)slice * 256, tile);
-    for (int by = (int)slice; by < (int)q.upr; by += e.nslice) {
+    const int upr = (int)q.upr, nslice = e.nslice;
+    int by = (int)slice;
+    ks_tile_t ahead;
+    auto fetch = [&](auto whole, int tid, int64_t k0, ks_tile_t &tile) {
+        if constexpr (decltype(whole)::value)
+            ks_fetch_whole(q, ks_load_offset(q, tid), o0, k0, tile);
+        else
+            ks_fetch_tile(q, tid, o0, k0, tile);
+    };
+    // The tile at K-block by (AHEAD: which lies in `ahead`; the next one follows it there).
+    auto take = [&](auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
         // What depends on the lane alone is formed anew for every tile: kept across the tiles it took 40 registers too many.
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const int64_t k0 = (int64_t)by * 256;
-        if constexpr (!AHEAD) ks_fetch_tile(q, tid, o0, k0, tile);
+        ks_tile_t tile;
+        if constexpr (AHEAD)
+            tile = ahead;
+        else
+            fetch(whole, tid, k0, tile);
         // the extracted rows' 256 K-elements: piece c (8 elements) of row r0 + 8 i
         const int c = tid & 31, r0 = tid >> 5;
-        uint4 f[2 * RT];
+        u32x4 f[2 * RT];
 #pragma unroll
         for (int i = 0; i < 2 * RT; ++i) {
-            f[i] = make_uint4(0, 0, 0, 0);
-            if (k0 + 8 * c < K) f[i] = *reinterpret_cast<const uint4 *>(e.rows + row_at[r0 + 8 * i] + k0 + 8 * c);
+            f[i] = u32x4{0, 0, 0, 0};
+            if (WHOLE || k0 + 8 * c < K) f[i] = *reinterpret_cast<const u32x4 *>(row_at[r0 + 8 * i] + (k0 + 8 * c));
         }
-        ks_put_tile(q, tid, o0, k0, lds, tile);
+        if constexpr (WHOLE)
+            ks_put_whole(q, tid, k0, lds, tile);
+        else
+            ks_put_tile(q, tid, o0, k0, lds, tile);
         __syncthreads();
         v4s d[16];
         ks_read_tile(tid, lds, d);
         if constexpr (AHEAD) {
-            if (by + e.nslice < (int)q.upr) ks_fetch_tile(q, tid, o0, k0 + 256ll * e.nslice, tile);
+            if (by + nslice < upr) fetch(whole, tid, k0 + 256ll * nslice, ahead);
         }
         __syncthreads(); // the tile is in registers: its place takes the extracted rows
         // A tile of 16 rows as 8 x 64 pieces: at (i, 16 g + r) the K-elements 64 g + 8 i .. + 7 of row r, what lane 16 g + r hands to
@@ -878,7 +948,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
         {
             const int at = (c & 7) * 64 + (c >> 3) * 16, x = c & 15;
 #pragma unroll
-            for (int i = 0; i < 2 * RT; ++i) s[(i >> 1) * 512 + at + ((r0 + 8 * (i & 1)) ^ x)] = f[i];
+            for (int i = 0; i < 2 * RT; ++i) *reinterpret_cast<u32x4 *>(s + (i >> 1) * 512 + at + ((r0 + 8 * (i & 1)) ^ x)) = f[i];
         }
         __syncthreads();
         {
@@ -893,8 +963,17 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
                 if (i & 1) __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (by + e.nslice < (int)q.upr) __syncthreads(); // (the next tile may be written)
-        if constexpr (B >= 0) ks_finish<B, false>(q, tid, o0, k0, d);
+        if (by + nslice < upr) __syncthreads(); // (the next tile may be written)
+        if constexpr (B >= 0) ks_finish<B, false, WHOLE>(q, tid, o0, k0, d);
+    };
+    if constexpr (AHEAD) {
+        fetch(std::false_type{}, threadIdx.x, (int64_t)by * 256, ahead);
+        for (; by < upr; by += nslice) take(std::false_type{});
+    } else {
+        const int whole = ks_whole(q, o0, 0) ? (int)(K >> 8) : 0;
+        for (; by < whole; by += nslice) take(std::true_type{});
+#pragma unroll 1
+        for (; by < upr; by += nslice) take(std::false_type{});
     }
     const int g = (threadIdx.x >> 4) & 3;
     const int64_t o = o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);

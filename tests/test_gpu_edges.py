@@ -221,3 +221,25 @@ def test_orders_of_the_workgroups_of_a_k_strided_operand(ah, outer, K, block):
         want, got = (ah.adahop_pack_operand(op, True, strategy, block, **kw) for op in (ah.Operand(x, True), ah.Operand(t, False)))
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("outer,K,pad", [(64, 256, 0), (63, 256, 1), (65, 288, 7), (128, 224, 8), (200, 768, 0), (192, 1056, 64), (328, 2048, 24)])
+@pytest.mark.parametrize("block", [0, 32, 128, 256])
+def test_tiles_of_a_k_strided_operand_at_and_off_its_edges(ah, outer, K, pad, block):
+    """Tiles of 256 K x 64 columns that lie inside the operand as a whole and ones that do not, rows with and without a gap behind them, K-channels
+    and columns masked, rounded to nearest and stochastically: the bytes of the same matrix stored K-contiguous."""
+    if block and K % block:
+        pytest.skip("the transform's block has to divide K")
+    gen = torch.Generator(device="cuda").manual_seed(outer * K + pad)
+    x = torch.randn(outer, K, generator=gen, device="cuda").to(torch.bfloat16)
+    wide = torch.full((K, (outer + pad + 7) // 8 * 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:, :outer] = x.t()
+    ops = (ah.Operand(x, True), ah.Operand(wide[:, :outer], False))
+    zk, zo = torch.zeros(K, dtype=torch.uint8, device="cuda"), torch.zeros(outer, dtype=torch.uint8, device="cuda")
+    zk[[0, K // 2, K - 1]] = 1
+    zo[[0, outer // 2, outer - 1]] = 1
+    say("K-strided tiles", outer, K, pad, block)
+    for kw in ({}, {"zero_k": zk}, {"zero_outer": zo}, {"sr_seed": 5}):
+        want, got = (ah.adahop_iht_quantize(op, block, **kw) for op in ops)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), list(kw)
