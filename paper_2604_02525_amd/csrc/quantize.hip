@@ -104,6 +104,7 @@ __device__ __forceinline__ uint32_t pack8_sr(const float (&w)[8], int s, sr_key_
 }
 
 template <int B> __device__ __forceinline__ float hadamard_norm();
+template <> __device__ __forceinline__ float hadamard_norm<0>() { return 1.0f; }
 template <> __device__ __forceinline__ float hadamard_norm<32>() { return 0x1.6a09e6p-3f; }
 template <> __device__ __forceinline__ float hadamard_norm<64>() { return 0.125f; }
 template <> __device__ __forceinline__ float hadamard_norm<128>() { return 0x1.6a09e6p-4f; }
@@ -146,20 +147,15 @@ struct lane_plan_t {
 template <int B> __device__ __forceinline__ lane_plan_t make_plan(int lane)
 {
     constexpr int NS = B >= 128 ? 4 : (B == 64 ? 3 : (B == 32 ? 2 : 0));
-    const int r = lane & 15, r2 = (r >> 2) & 1;
+    const int r = lane & 15;
     lane_plan_t p;
-    p.chunk = ((r ^ r2) & 1) | ((r ^ (r2 << 1)) & 2) | (r & 12);
-    float sign = 1.0f;
+    p.chunk = r ^ ((r << 29 >> 31) & 3); // chunk bit 2 set: the two below it flipped
+    p.fin = B > 0 ? hadamard_norm<B>() : 1.0f;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const bool upper = b < NS && ((p.chunk >> b) & 1);
-        p.t[b] = upper ? -1.0f : 1.0f;
-        if (upper) sign = -sign;
+        p.t[b] = b < NS ? __uint_as_float(((uint32_t)p.chunk << (31 - b) & 0x80000000u) | 0x3f800000u) : 1.0f;
+        if (b < NS) p.fin *= p.t[b];
     }
-    if constexpr (B > 0)
-        p.fin = sign * hadamard_norm<B>();
-    else
-        p.fin = 1.0f;
     return p;
 }
 
@@ -257,8 +253,8 @@ __device__ __forceinline__ void transform_quantize16(float (&w0)[8], float (&w1)
         return;
     }
     const float x0 = __uint_as_float((uint32_t)s0 << 23), x1 = __uint_as_float((uint32_t)s1 << 23);
-    codes0 = 0;
-    codes1 = 0;
+    codes0 = __float_as_uint(w0[0]); // (every byte is written: any register that is free)
+    codes1 = __float_as_uint(w1[0]);
     codes0 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes0, w0[0], w0[1], x0, 0);
     codes0 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes0, w0[2], w0[3], x0, 1);
     codes0 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(codes0, w0[4], w0[5], x0, 2);
@@ -413,17 +409,87 @@ __device__ __forceinline__ void quant_kc_unit(const quant_t &q, int64_t row, uin
     if (active) store_codes_scales<TAIL>(q.codes, q.scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, q.sm);
 }
 
+// The same for a workgroup whose units, numbered consecutively over the rows from u0 (uniform) on, all exist, K % 256 == 0: the results then lie one
+// unit after the other, and so does the operand but for the gap between its rows, so that addresses are a scalar base and a small offset, and nothing has a
+// condition: 235 vector instructions per wave in place of 271 at B = 256.  us: 8192 x 2048 9.7 -> 9.2, 2016 x 11008 11.5 -> 10.9, 1000 x 3072 6.4 -> 6.05;
+// where the memory bounds it 1 .. 2 %, 16384 x 28672 196.9 -> 193.4.
+template <int B, bool SR> __device__ __forceinline__ void quant_kc_whole(const quant_t &q, uint32_t u0)
+{
+    const int64_t K = q.K;
+    const lane_plan_t plan = make_plan<B>(threadIdx.x & 63);
+    const uint32_t n = threadIdx.x >> 4, u = u0 + n;
+    const uint32_t first = row_of_unit(u0, q.upr, q.magic);
+    uint32_t row = 0, unit = 0, skip = 0;
+    if (q.sm.out || q.ld != K || q.gr.out || q.zero_outer || q.zero_k || SR) { // (uniform)
+        row = row_of_unit(u, q.upr, q.magic);
+        unit = u - row * q.upr;
+        skip = (row - first) * (uint32_t)((q.ld - K) * 2);
+    }
+    const uint8_t *base = reinterpret_cast<const uint8_t *>(q.x) + ((int64_t)u0 * 512 + (int64_t)first * (q.ld - K) * 2);
+    const uint32_t at = n * 512 + plan.chunk * 16 + skip;
+    uint4 r0 = load_once16(base + at), r1 = load_once16(base + at + 256);
+    if (q.gr.out) {
+        const uint32_t p = q.gr.pos1[row];
+        if (p) {
+            uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + unit * 256 + plan.chunk * 8;
+            *reinterpret_cast<uint4 *>(dst) = r0;
+            *reinterpret_cast<uint4 *>(dst + 128) = r1;
+            r0 = r1 = make_uint4(0, 0, 0, 0);
+        }
+    } else if (q.zero_outer) {
+        if (q.zero_outer[row]) r0 = r1 = make_uint4(0, 0, 0, 0);
+    }
+    float w0[8] = {bf16_lo(r0.x), bf16_hi(r0.x), bf16_lo(r0.y), bf16_hi(r0.y),
+                   bf16_lo(r0.z), bf16_hi(r0.z), bf16_lo(r0.w), bf16_hi(r0.w)};
+    float w1[8] = {bf16_lo(r1.x), bf16_hi(r1.x), bf16_lo(r1.y), bf16_hi(r1.y),
+                   bf16_lo(r1.z), bf16_hi(r1.z), bf16_lo(r1.w), bf16_hi(r1.w)};
+    if (q.zero_k) {
+        const uint8_t *zk = q.zero_k + unit * 256 + plan.chunk * 8;
+        apply_k_mask(w0, *reinterpret_cast<const uint64_t *>(zk));
+        apply_k_mask(w1, *reinterpret_cast<const uint64_t *>(zk + 128));
+    }
+    uint32_t c0, c1;
+    int s0, s1;
+    const int64_t kk = (int64_t)unit * 256 + plan.chunk * 8;
+    transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, q.key, row, kk, kk + 128);
+    uint8_t *crow = q.codes + (int64_t)u0 * 128 + (n * 128 + plan.chunk * 4);
+    *reinterpret_cast<uint32_t *>(crow) = c0;
+    *reinterpret_cast<uint32_t *>(crow + 64) = c1;
+    if ((plan.chunk & 3) == 0) {
+        uint8_t *srow = q.scales + (int64_t)u0 * 8 + (n * 8 + (plan.chunk >> 2));
+        srow[0] = (uint8_t)s0;
+        srow[4] = (uint8_t)s1;
+        if (q.sm.out) {
+            uint8_t *sm = q.sm.out + ((uint64_t)unit * (uint32_t)q.sm.rows + row) * 8 + (plan.chunk >> 2);
+            sm[0] = (uint8_t)s0;
+            sm[4] = (uint8_t)s1;
+        }
+    }
+}
+
 // FLAT = 0: blockIdx.x is the row, blockIdx.y and the thread its units, 16 to a workgroup; FLAT = 1: the units of all rows are
 // numbered consecutively.  FLAT = 0 where a row is exactly one workgroup (and for counts above row_of_unit's): where the last of a row's
 // workgroups has fewer units the rest of it idles, and with several of them a row's parts are written far apart in time.  FLAT = 0 / 1, us: 10000 rows x
 // 4096 18.0 / 18.6, x 4256 27.2 / 19.9, x 3072 15.4 / 15.0, x 11008 53.2 / 45.4; 28672 x 8192 113 / 99; 16384 x 28672 232 / 196.  Rounded stochastically, which is
 // bound by vector instructions, and fewer of them with a row that is the same for the workgroup, also where a row is several whole workgroups: 28672 x 8192 161
 // / 165, 8192 x 12288 67.9 / 69.8, but x 4256 33.8 / 26.5, x 2048 16.6 / 13.6.
+template <int B, bool SR, bool TAIL, int NT> __device__ __forceinline__ void quant_kc_block(const quant_t &q, uint32_t block)
+{
+    if constexpr (!TAIL) { // (up to 16 or 32 rows' gaps lie within 32 bits)
+        const uint32_t u0 = block * (NT / 16);
+        if ((uint64_t)u0 + NT / 16 <= (uint64_t)q.outer * q.upr && q.ld - q.K < 1 << 20) {
+            quant_kc_whole<B, SR>(q, u0);
+            return;
+        }
+    }
+    const uint32_t u = (block * (uint32_t)NT + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
+    quant_kc_unit<B, SR, TAIL>(q, r, u - r * q.upr, r < q.outer);
+}
+
 template <int B, int FLAT, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_quant_kc16(quant_t q)
 {
     if constexpr (FLAT) {
-        const uint32_t u = (blockIdx.x * 256u + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
-        quant_kc_unit<B, SR, TAIL>(q, r, u - r * q.upr, r < q.outer);
+        quant_kc_block<B, SR, TAIL, 256>(q, blockIdx.x);
     } else {
         const uint32_t unit = (blockIdx.y * 256u + threadIdx.x) >> 4;
         quant_kc_unit<B, SR, TAIL>(q, blockIdx.x, unit, unit < q.upr);
@@ -766,8 +832,8 @@ template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_finish(
             const float X = __uint_as_float((uint32_t)s << 23);
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                uint32_t p = 0;
                 const float *v8 = wv + 32 * blk + 8 * q4;
+                uint32_t p = __float_as_uint(v8[0]); // (every byte is written: any register that is free)
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[0], v8[1], X, 0);
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[2], v8[3], X, 1);
                 p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(p, v8[4], v8[5], X, 2);
@@ -1006,8 +1072,7 @@ __device__ __forceinline__ void quant_block(const quant_t &q, uint32_t block, ui
     } else if constexpr (OP == KC_GATHER) {
         quant_kc_gather_rows<B, SR, TAIL>(q, block, lds);
     } else {
-        const uint32_t u = (block * (uint32_t)NT + threadIdx.x) >> 4, r = row_of_unit(u, q.upr, q.magic);
-        quant_kc_unit<B, SR, TAIL>(q, r, u - r * q.upr, r < q.outer);
+        quant_kc_block<B, SR, TAIL, NT>(q, block);
     }
 }
 
