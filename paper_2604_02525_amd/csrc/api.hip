@@ -403,12 +403,10 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // 1. which rows / columns / K-channels leave the MXFP4 path (App. F item 1)
     const bool oe_k = oe && strategy == ADAHOP_IHT_OE_K;
     const int kpad_planned = oe_k ? kpad_of(k) : 0;
-    // The quantiser that reads an extracted operand anyway also copies the extracted part out for the bf16 product; the position of
-    // a row or channel in the index list comes from a 16-bit table that the selection leaves beside the mask.  Only for indices selected
-    // here, which are distinct: a repeated index in a caller's list would leave a position of the copy unwritten, where the separate
-    // gather reads the row twice.
-    // The table of K-channels takes the place of the scores; above the selection's own limit it costs a launch, less than the separate
-    // gather of a K-contiguous operand (4096 x 4096 x 65536, 655 channels: the whole call 4 % faster).  That of rows and columns lies where the bf16 product keeps its partial sums:
+    // The quantiser that reads an extracted operand anyway also copies the extracted part out for the bf16 product: K-channels by the
+    // list of indices, which has to ascend, rows and columns by a 16-bit table of positions that the selection leaves beside the mask.  Only for indices selected
+    // here, which are distinct and ascend.
+    // The table lies where the bf16 product keeps its partial sums:
     // a caller finds the scores in the workspace afterwards.  Whoever writes those sums, be it the other operand's quantiser, is queued behind the
     // quantiser that reads the table, on the same stream.  Where it does not fit
     // there (more than 128 rows to choose from for each of the other operand's), the rows are gathered by themselves.
@@ -429,17 +427,16 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const bool in_place = on_the_way && short_op.k_contig;
     uint16_t *pos1 = nullptr;
     size_t partials = 0;
-    if (oe && !use_given_idx && !in_place && k <= 0xffff && (oe_k || foid_writes_positions(dim))) {
-        size_t room = (size_t)dim * sizeof(float);
-        pos1 = oe_k ? reinterpret_cast<uint16_t *>(scores)
-                    : reinterpret_cast<uint16_t *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &room));
+    if (oe_rc && !use_given_idx && !in_place && k <= 0xffff && foid_writes_positions(dim)) {
+        size_t room = 0;
+        pos1 = reinterpret_cast<uint16_t *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &room));
         if (align_up((size_t)dim * sizeof(uint16_t), 4) > room) pos1 = nullptr;
     }
-    const bool a_gathers_k = pos1 && oe_k && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
-    const bool b_gathers_k = pos1 && oe_k && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
+    const bool a_gathers_k = oe_k && !use_given_idx && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
+    const bool b_gathers_k = oe_k && !use_given_idx && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
     const bool a_gathers_rows = pos1 && strategy == ADAHOP_IHT_OE_ROW && !a_given;
     const bool b_gathers_rows = pos1 && strategy == ADAHOP_IHT_OE_COL && !b_given;
-    if (!(a_gathers_k || b_gathers_k || a_gathers_rows || b_gathers_rows)) pos1 = nullptr;
+    if (!(a_gathers_rows || b_gathers_rows)) pos1 = nullptr;
     // 2. residual -> transform -> MXFP4 (App. F item 2), for the operands the caller has not packed
     const uint8_t *a_codes = a_given ? opts->a_codes : reinterpret_cast<uint8_t *>(ws + L.a_codes);
     const uint8_t *a_scales = a_given ? opts->a_scales : reinterpret_cast<uint8_t *>(ws + L.a_scales);
@@ -454,11 +451,11 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const quant_job_t ja = {A, a_kind == 1 && !unmasked ? mask : nullptr, a_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.a_codes),
                             reinterpret_cast<uint8_t *>(ws + L.a_scales), opts && opts->sr_a ? &opts->sr_seed_a : nullptr,
                             {gemm_mx_scales_sm(ws + L.gemm, M, K, 0), M},
-                            a_gathers_k ? k_gather_t{pos1, gather_a, k, kpad_planned} : no_k, a_gathers_rows ? rows : no_rows};
+                            a_gathers_k ? k_gather_t{idx_inout, gather_a, k, kpad_planned} : no_k, a_gathers_rows ? rows : no_rows};
     const quant_job_t jb = {B, b_kind == 1 && !unmasked ? mask : nullptr, b_kind == 2 ? mask : nullptr, reinterpret_cast<uint8_t *>(ws + L.b_codes),
                             reinterpret_cast<uint8_t *>(ws + L.b_scales), opts && opts->sr_b ? &opts->sr_seed_b : nullptr,
                             {gemm_mx_scales_sm(ws + L.gemm, M, K, 1), N},
-                            b_gathers_k ? k_gather_t{pos1, gather_b, k, kpad_planned} : no_k, b_gathers_rows ? rows : no_rows};
+                            b_gathers_k ? k_gather_t{idx_inout, gather_b, k, kpad_planned} : no_k, b_gathers_rows ? rows : no_rows};
     // Row and column extraction: the operand that nothing is extracted from does not wait for the selection, one workgroup of
     // which the rest of the chip would watch (9 us for 8192 rows); its quantiser runs beside it.
     const quant_job_t &free_job = from_a ? jb : ja, &masked_job = from_a ? ja : jb;

@@ -45,10 +45,10 @@ struct scales_sm_t {
     int64_t rows; // rows of the operand
 };
 // The extracted K-channels of an operand, copied out by the quantiser that reads the operand anyway (Eq. 7 with
-// S a set of K-channels): out[o, pos1[c] - 1] = x(o, c) for every channel c with pos1[c] != 0, out[o, k .. kpad) = 0.
-// out is [outer, kpad] bf16; pos1[c] = t + 1 for the channel c = idx[t], 0 for a channel that is not extracted.
+// S a set of K-channels): out[o, t] = x(o, idx[t]), out[o, k .. kpad) = 0.
+// out is [outer, kpad] bf16; idx ascends, as the selection leaves it.
 struct k_gather_t {
-    const uint16_t *pos1; // per K-channel, 16-byte aligned
+    const int32_t *idx;
     uint16_t *out;        // nullptr: no copy
     int k, kpad;
 };
@@ -58,7 +58,7 @@ struct row_gather_t {
     const uint16_t *pos1; // per outer index
     uint16_t *out;        // nullptr: no copy
 };
-// Whether launch_iht_quantize honours a k_gather_t for this operand (K-contiguous, a copy that fits its LDS staging).
+// Whether launch_iht_quantize honours a k_gather_t for this operand (K-contiguous, up to 4096 channels).
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad);
 // One operand to quantise.
 struct quant_job_t {
@@ -103,8 +103,7 @@ struct topk_job_t {
 bool topk_beside_quant(int64_t dim, const quant_job_t &job);
 bool iht_quantize_beside_topk(int64_t dim, const adahop_operand_t &x); // the same for an operand rounded to nearest, no K-channels copied out
 int launch_topk_beside_quant(const topk_job_t &topk, int iht_block, const quant_job_t &job, hipStream_t st);
-// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere, for k <= 0xffff; it may lie where scores lies.  The selection
-// writes it on the way where foid_writes_positions holds, else a launch after it does.
+// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere, for k <= 0xffff, where foid_writes_positions holds; it may lie where scores lies.
 bool foid_writes_positions(int64_t dim);
 int launch_foid_scores(const adahop_operand_t &x, int axis, float *scores, hipStream_t st);
 int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, uint8_t *mask, float *scores,

@@ -203,19 +203,6 @@ __global__ __launch_bounds__(256) void k_mark(const int32_t *__restrict__ idx, i
     if (t < k) mask[idx[t]] = 1;
 }
 
-// The table of positions where the selection does not write it (k_topk reads its scores, where the table may lie, to the end): the first
-// dim threads clear the entries of what stays, the next k set those of what is extracted; no entry is written twice.
-__global__ __launch_bounds__(256) void k_positions(const int32_t *__restrict__ idx, int k, const uint8_t *__restrict__ mask,
-                                                   int64_t dim, uint16_t *__restrict__ pos1)
-{
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g < dim) {
-        if (!mask[g]) pos1[g] = 0;
-    } else if (g < dim + k) {
-        pos1[idx[g - dim]] = (uint16_t)(g - dim + 1);
-    }
-}
-
 } // namespace
 
 // The one-workgroup selection keeps up to TOPK_LDS_KEYS keys in LDS: allowed once per device (host-side call).
@@ -259,11 +246,6 @@ int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, u
                            mask, pos1);
     } else {
         hipLaunchKernelGGL(k_topk, dim3(1), dim3(TOPK_THREADS), 0, st, scores, (int)dim, k, idx, mask);
-        if (pos1) {
-            rc = check_launch();
-            if (rc != ADAHOP_OK) return rc;
-            hipLaunchKernelGGL(k_positions, dim3((unsigned)ceil_div(dim + k, 256)), dim3(256), 0, st, idx, k, mask, dim, pos1);
-        }
     }
     return check_launch();
 }

@@ -272,34 +272,6 @@ __device__ __forceinline__ void apply_k_mask(float (&w)[8], uint64_t zm)
         if ((zm >> (8 * i)) & 0xffu) w[i] = 0.0f;
 }
 
-// Of 8 consecutive K-elements (raw bf16 in r), all go to slot[pos1] of the row's copy, pos1 being position + 1 for an
-// extracted element and 0 for one that stays: slot 0 takes what is not extracted and is never read, so that no
-// store needs a condition of its own (eight predicated stores cost three times the instructions).
-constexpr int KC_GATHER_SLOT0 = 7; // index of slot 0 in the LDS array: the copy proper starts 16-byte aligned behind it
-
-__device__ __forceinline__ void scatter_extracted(uint4 r, uint4 pos, uint16_t *slot)
-{
-    const uint32_t e[4] = {r.x, r.y, r.z, r.w}, q[4] = {pos.x, pos.y, pos.z, pos.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        slot[q[j] & 0xffffu] = (uint16_t)e[j];
-        slot[q[j] >> 16] = (uint16_t)(e[j] >> 16);
-    }
-}
-
-// The raw bf16 pairs with the extracted elements (pos1 != 0) cleared to +0: per 16-bit half, min(pos1, 1) - 1 is
-// 0xffff for an element that stays and 0 for an extracted one.
-__device__ __forceinline__ uint4 clear_extracted(uint4 r, uint4 pos)
-{
-    const uint32_t ones = 0x00010001u;
-    auto keep = [&](uint32_t q) { // (the compiler's own code for this is a compare and a select per half)
-        uint32_t t;
-        asm("v_pk_min_u16 %0, %1, %2\n\tv_pk_sub_u16 %0, %0, %2" : "=&v"(t) : "v"(q), "v"(ones));
-        return t;
-    };
-    return make_uint4(r.x & keep(pos.x), r.y & keep(pos.y), r.z & keep(pos.z), r.w & keep(pos.w));
-}
-
 // Slot of MX block j (0 .. 7) of unit u in the stage-major copy of the scales: the last unit of a row holds
 // t = K / 32 - 8 u blocks if K is no multiple of 256, and the tiled GEMM kernels read that stage so that it ends with the
 // row (see there): its blocks then are the last t of 8, and the slots before them, which stand for blocks that the
@@ -496,70 +468,113 @@ template <int B, int FLAT, bool SR, bool TAIL> __global__ __launch_bounds__(256)
     }
 }
 
-// The same with the extracted K-channels copied out on the way (Eq. 7 with S a set of K-channels).  One workgroup
-// takes whole rows, 4096 K-elements per pass: one row, or as many shorter ones as fill a pass.  In place of the byte mask it reads
-// a 16-bit table, position in the index list + 1 for an extracted channel and 0 for the others, with the operand (one more
-// coalesced load, no dependent look-ups); the extracted elements it meets go to those positions of a copy of the row's
-// extracted part in LDS, which leaves for memory at the end in whole 16-byte pieces; they are cleared in the raw bf16 pairs
-// with three packed 16-bit instructions per pair.
-// (Two variants were measured on 16384 x 28672 at 1 % and made the quantiser half again as slow, more than the
-// separate gather kernel costs: 2-byte stores straight into the copy, and a look-up of the position in a 32-bit
-// table under the branch that an extracted element takes -- a chain of dependent loads in nearly every wave.
-// What the kernel costs over the plain one, 10 .. 20 %, is not its instructions: with a fifth fewer of them, and
-// with the next pass's loads issued ahead, it took the same time; without the table loads 4 .. 37 us of the 14 .. 50
-// go away, most on the 57 KB table of K = 28672, which every workgroup reads whole.)
+// The same with the extracted K-channels copied out on the way (Eq. 7 with S a set of K-channels).  One workgroup takes whole rows, 4096 K-elements
+// per pass: one row, or as many shorter ones as fill a pass.  The 16 lanes of a unit leave its elements in LDS as they came, look up the indices that
+// fall into it (the list ascends: two loads of 16 entries, one of them the same for all units, or three for a long list), take those elements out, to a copy
+// in LDS and to zero, and read their own back: no barrier, since it all stays within a wave.  The copies leave for memory at the end in whole 16-byte pieces.
+//
+// What bounds it is the issue of vector instructions (the more so beside a large product, whose power budget it shares) and, where a workgroup has one pass, its chain of
+// loads.  With a 16-bit table of positions read beside the elements, all of them scattered in LDS and cleared by it, it issued 325 per wave and 16 elements of a lane, here 244 (the plain
+// kernel 235): both operands, us, 16384 + 28672 rows x 8192, 82 channels, 226.7 -> 188.7; 8192 + 8192 x 2048, 8, 25.1 -> 23.6; 8192 + 4096 x 4096, 41, 33.4 ->
+// 31.1; 2016 + 11008 x 4096, 41, 32.9 -> 32.2; 1000 + 5000 x 3040, 31, 15.4 -> 15.25.  The elements taken out by the whole workgroup between two
+// barriers: 203, 27.4, 37.5, 35.9, 15.5; the same with the next row's loads on their way and one .. eight rows per workgroup 196 .. 212, 21 .. 28, 32.6 .. 36,
+// 32.6 .. 37, 16 .. 21.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 lds16_t __attribute__((may_alias)); // (a unit's elements are written and read in pieces and one by one)
 constexpr int KC_GATHER_MAX_KPAD = 4096;
-constexpr int KC_GATHER_LDS = (8 + KC_GATHER_MAX_KPAD) * 2; // bytes: the copies of the rows, kpad + 8 elements each
+constexpr int KC_GATHER_COPY = KC_GATHER_MAX_KPAD * 2, KC_GATHER_LDS = KC_GATHER_COPY + 4096 * 2; // bytes: the copies of the rows, and a pass
 
 template <int B, bool SR, bool TAIL>
-__device__ __forceinline__ void quant_kc_gather_rows(const quant_t &q, uint32_t block, uint8_t *lds_bytes)
+__device__ __forceinline__ void quant_kc_gather_rows(const quant_t &q, uint32_t block, uint8_t *lds)
 {
-    uint16_t *lds = reinterpret_cast<uint16_t *>(lds_bytes);
     const k_gather_t gk = q.gk;
     const int64_t K = q.K, row0 = (int64_t)block * q.rows_per_wg;
-    const int nrows = (int)min((int64_t)q.rows_per_wg, q.outer - row0), per = gk.kpad + 8;
-    const lane_plan_t plan = make_plan<B>(threadIdx.x & 63);
-    for (int r = 0; r < nrows; ++r)
-        for (int p = gk.k + threadIdx.x; p < gk.kpad; p += 256) lds[r * per + 8 + p] = 0;
-    for (uint32_t u0 = 0; u0 < q.upr; u0 += 16) {
-        uint32_t unit = u0 + (threadIdx.x >> 4), r = 0;
+    const int tid = threadIdx.x, l16 = tid & 15, none = 0x7fffffff;
+    const int nrows = (int)min((int64_t)q.rows_per_wg, q.outer - row0);
+    uint16_t *const copy = reinterpret_cast<uint16_t *>(lds), *const raw = reinterpret_cast<uint16_t *>(lds + KC_GATHER_COPY) + (tid >> 4) * 256;
+    const lane_plan_t plan = make_plan<B>(tid & 63);
+    // The list at 16 places, and at 16 places between two of those.  Loads without a condition, at places that exist: a wait can then be for one of them.
+    const int last = gk.k - 1, step = (gk.k + 15) >> 4, fine = (step + 15) >> 4;
+    auto load = [&](int t) { return gk.idx[min(t, last)]; };
+    auto entry = [&](int t) {
+        const int at = load(t);
+        return t <= last ? at : none;
+    };
+    auto of_unit = [&](bool hit) { return (int)__popc((uint32_t)(__ballot(hit) >> (tid & 48)) & 0xffffu); }; // of its 16 lanes, how many
+    const int coarse = entry(l16 * step);
+    if (tid < gk.kpad - gk.k) {
+#pragma clang loop vectorize(disable) unroll(disable)
+        for (int r = 0; r < nrows; ++r) copy[r * gk.kpad + gk.k + tid] = 0;
+    }
+    // the lane's place in the pass that begins with unit u0, its elements, and the first entries of the list that may lie in its unit
+    struct part_t {
+        u32x4 r0, r1;
+        int64_t row;
+        int from, r, t, at;
+        bool active;
+    };
+    auto fetch = [&](uint32_t u0) {
+        part_t f;
+        uint32_t unit = u0 + (tid >> 4), r = 0;
         if (q.rows_per_wg > 1) { // (one pass)
             r = row_of_unit(unit, q.upr, q.magic);
             unit -= r * q.upr;
         }
-        const bool active = (int)r < nrows && unit < q.upr;
-        const int64_t row = row0 + r, k0 = (int64_t)unit * 256, kk = k0 + plan.chunk * 8;
-        const bool in0 = active && (!TAIL || kk < K), in1 = active && (!TAIL || kk + 128 < K);
-        uint16_t *slot = lds + r * per + KC_GATHER_SLOT0;
-        uint4 r0 = make_uint4(0, 0, 0, 0), r1 = r0, p0 = r0, p1 = r0;
-        const uint16_t *src = q.x + row * q.ld + kk;
-        if (in0) {
-            r0 = load_once16(src);
-            p0 = *reinterpret_cast<const uint4 *>(gk.pos1 + kk);
+        f.active = (int)r < nrows && unit < q.upr;
+        r = min(r, (uint32_t)nrows - 1), unit = min(unit, q.upr - 1);
+        f.r = (int)r, f.row = row0 + r, f.from = (int)unit * 256;
+        const uint16_t *const src = q.x + f.row * q.ld;
+        const int kk = f.from + plan.chunk * 8, end = (int)K - 8;
+        f.r0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + (TAIL ? min(kk, end) : kk)));
+        f.r1 = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + (TAIL ? min(kk + 128, end) : kk + 128)));
+        const int before = of_unit(coarse < f.from);
+        f.t = (before > 0 ? before - 1 : 0) * step;
+        if (fine > 1) {
+            const int more = of_unit(entry(f.t + l16 * fine) < f.from);
+            f.t += (more > 0 ? more - 1 : 0) * fine;
         }
-        if (in1) {
-            r1 = load_once16(src + 128);
-            p1 = *reinterpret_cast<const uint4 *>(gk.pos1 + kk + 128);
+        f.t += l16;
+        f.at = load(f.t); // (looked at when it is needed)
+        return f;
+    };
+    part_t f = fetch(0);
+    for (uint32_t u0 = 16;; u0 += 16) {
+        const int kk = f.from + plan.chunk * 8;
+        const bool in0 = !TAIL || kk < K, in1 = !TAIL || kk + 128 < K;
+        lds16_t *const own = reinterpret_cast<lds16_t *>(raw + plan.chunk * 8);
+        own[0] = in0 ? f.r0 : u32x4{0, 0, 0, 0};
+        own[16] = in1 ? f.r1 : u32x4{0, 0, 0, 0};
+        int t = f.t, at = f.active && t <= last ? f.at : none;
+        for (;;) {
+            if (at >= f.from && at < f.from + 256) {
+                uint16_t *const e = raw + (at - f.from);
+                copy[f.r * gk.kpad + t] = *e;
+                *e = 0;
+            }
+            const uint64_t again = __ballot(l16 == 15 && at < f.from + 256); // (few waves)
+            if (!again) break;
+            t += 16;
+            at = again >> (tid & 48) & 0x8000 ? entry(t) : none;
         }
-        if (p0.x | p0.y | p0.z | p0.w) scatter_extracted(r0, p0, slot);
-        if (p1.x | p1.y | p1.z | p1.w) scatter_extracted(r1, p1, slot);
-        r0 = clear_extracted(r0, p0);
-        r1 = clear_extracted(r1, p1);
-        float w0[8] = {bf16_lo(r0.x), bf16_hi(r0.x), bf16_lo(r0.y), bf16_hi(r0.y),
-                       bf16_lo(r0.z), bf16_hi(r0.z), bf16_lo(r0.w), bf16_hi(r0.w)};
-        float w1[8] = {bf16_lo(r1.x), bf16_hi(r1.x), bf16_lo(r1.y), bf16_hi(r1.y),
-                       bf16_lo(r1.z), bf16_hi(r1.z), bf16_lo(r1.w), bf16_hi(r1.w)};
+        const u32x4 e0 = own[0], e1 = own[16];
+        float w0[8] = {bf16_lo(e0.x), bf16_hi(e0.x), bf16_lo(e0.y), bf16_hi(e0.y),
+                       bf16_lo(e0.z), bf16_hi(e0.z), bf16_lo(e0.w), bf16_hi(e0.w)};
+        float w1[8] = {bf16_lo(e1.x), bf16_hi(e1.x), bf16_lo(e1.y), bf16_hi(e1.y),
+                       bf16_lo(e1.z), bf16_hi(e1.z), bf16_lo(e1.w), bf16_hi(e1.w)};
+        const int64_t row = f.row, k0 = f.from;
+        const bool active = f.active, more = u0 < q.upr;
+        if (more) f = fetch(u0); // the next pass's, on their way while this one's are transformed
         uint32_t c0, c1;
         int s0, s1;
         transform_quantize16<B, SR>(w0, w1, plan, c0, c1, s0, s1, q.key, row, kk, kk + 128);
         if (active) store_codes_scales<TAIL>(q.codes, q.scales, row, K, k0, plan.chunk, in0, in1, c0, c1, s0, s1, q.sm);
+        if (!more) break;
     }
     __syncthreads();
-    for (int r = 0; r < nrows; ++r) {
-        uint16_t *dst = gk.out + (row0 + r) * gk.kpad;
-        for (int p = threadIdx.x * 8; p < gk.kpad; p += 256 * 8)
-            *reinterpret_cast<uint4 *>(dst + p) = *reinterpret_cast<const uint4 *>(lds + r * per + 8 + p);
-    }
+    // (the rows' copies lie one after the other, here and there)
+#pragma clang loop unroll(disable)
+    for (int p = tid * 8; p < nrows * gk.kpad; p += 256 * 8)
+        *reinterpret_cast<lds16_t *>(gk.out + row0 * gk.kpad + p) = *reinterpret_cast<const lds16_t *>(copy + p);
 }
 
 template <int B, bool SR, bool TAIL> __global__ __launch_bounds__(256) void k_quant_kc16_gather(quant_t q)
@@ -930,7 +945,6 @@ template <int B, bool SR> __global__ __launch_bounds__(256) void k_quant_ks16(qu
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A K-strided operand (nothing extracted from it), and on the way its bf16 products with the k <= 16 RT rows extracted from the other
 // one (second term of Eq. 7 / 8): the operand's tile is in registers in the matrix cores' layout anyway, and reading it once more for these products by
@@ -1239,7 +1253,7 @@ quant_kind_t describe(const quant_job_t &j, quant_t &q)
         return KS;
     }
     if (!q.gk.out) return KC;
-    const uint32_t fit = 16 / q.upr, room = (uint32_t)(KC_GATHER_LDS / 2 / (q.gk.kpad + 8)); // rows per pass, and in LDS
+    const uint32_t fit = 16 / q.upr, room = (uint32_t)(KC_GATHER_MAX_KPAD / q.gk.kpad); // rows per pass, and in LDS
     const uint32_t rows = fit < room ? fit : room;
     if (rows > 1) q.rows_per_wg = rows;
     return KC_GATHER;
@@ -1446,7 +1460,6 @@ int launch_quant_and_product(int b, const quant_job_t &ja, const quant_job_t &jb
     return c_bf16 ? launch_tiles(b, p, static_cast<uint16_t *>(C), st) : launch_tiles(b, p, static_cast<float *>(C), st);
 }
 
-// The copy of a row's extracted channels is staged in LDS.
 bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad)
 {
     return x.k_contig && kpad <= KC_GATHER_MAX_KPAD;

@@ -243,3 +243,27 @@ def test_tiles_of_a_k_strided_operand_at_and_off_its_edges(ah, outer, K, pad, bl
         want, got = (ah.adahop_iht_quantize(op, block, **kw) for op in ops)
         torch.cuda.synchronize()
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), list(kw)
+
+
+@pytest.mark.parametrize("K,at,k", [(32, 0, 32), (64, 63, 1), (288, 4, 280), (512, 255, 2), (768, 250, 270), (4096, 512, 300), (8192, 0, 1), (8192, 8191, 1), (8192, 4090, 17),
+                                    (3040, 300, 2500), (11008, 6000, 4096), (9000 // 32 * 32, 0, 257)])
+def test_runs_of_k_channels_copied_by_the_quantisers(ah, K, at, k):
+    """The extracted K-channels next to each other: units of 256 with none of them, a few, more than 16 and nothing else, before, between and behind the
+    units with any, lists of one entry up to the longest that the quantisers take; several rows per workgroup and several passes.  Codes, scales, and C
+    as with the same indices handed in, where the mask and the separate gather are used; and codes of zero where all of a block is extracted."""
+    M, N, b = 37, 70, 32
+    gen = torch.Generator(device="cuda").manual_seed(K + k)
+    A = torch.randn(M, K, generator=gen, device="cuda")
+    A[:, at:at + k] *= 100.0
+    A, B = A.to(torch.bfloat16), torch.randn(N, K, generator=gen, device="cuda").to(torch.bfloat16)
+    say("runs of K-channels", K, at, k)
+    opa, opb = ah.Operand(A, True), ah.Operand(B, True)
+    out = ah.adahop_gemm(opa, opb, inputs.IHT_OE_K, b, k)
+    got = {n: out[n].clone() for n in ("C", "idx", "a_codes", "a_scales", "b_codes", "b_scales")}
+    again = ah.adahop_gemm(opa, opb, inputs.IHT_OE_K, b, k, idx=got["idx"].clone())
+    torch.cuda.synchronize()
+    assert torch.equal(got["idx"], torch.arange(at, at + k, dtype=torch.int32, device="cuda"))
+    for name, t in got.items():
+        assert torch.equal(t, again[name]), name
+    first, last = -(-at // b), (at + k) // b
+    assert not got["a_codes"][:, first * b // 2:max(first, last) * b // 2].any() and not got["b_codes"][:, first * b // 2:max(first, last) * b // 2].any()
