@@ -426,17 +426,17 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
     const int l32 = lane & 31, h = lane >> 5, wm = w >> 1, wn = w & 1;
     if constexpr (sizeof(OUT) == 4) {
         // fp32: straight from the accumulator registers, 128-byte row segments (staging through LDS as below
-        // and storing whole rows, 16 bytes per lane, was measured and is no faster), row by row over the wave's columns, so
-        // that off the 64-byte grid the halves of a line meet in the L2: tile by tile / row by row 6000 x 12001 x 1024 120 / 107 us, 16384 x 14337 x 8192
-        // 1190 / 1134; on the grid the same
+        // and storing whole rows, 16 bytes per lane, was measured and is no faster).  Off the 64-byte grid row by row over the wave's columns, so
+        // that the halves of a line meet in the L2: tile by tile / row by row 6000 x 12001 x 1024 120 / 107 us, 16384 x 14337 x 8192
+        // 1190 / 1134; on the grid tile by tile: 12288 x 8192 x 1568 158 / 164, 4096 x 4096 x 8192 70.3 / 71.1
         float *crow = C + (m0 + wm * 128 + h * 4) * ldc + n0 + wn * 128 + l32;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+            for (int n = 0; n < 64; ++n) {
+                const int j = ST == STREAMED ? n >> 4 : n & 3, r = ST == STREAMED ? n & 15 : n >> 2;
+                store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+            }
     } else if constexpr (ST == ELEMENTS) {
         OUT *crow = C + (m0 + wm * 128 + h * 4) * ldc + n0 + wn * 128 + l32;
 #pragma unroll
