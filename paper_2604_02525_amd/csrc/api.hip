@@ -403,9 +403,9 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     // 1. which rows / columns / K-channels leave the MXFP4 path (App. F item 1)
     const bool oe_k = oe && strategy == ADAHOP_IHT_OE_K;
     const int kpad_planned = oe_k ? kpad_of(k) : 0;
-    // The quantiser that reads an extracted operand anyway also copies the extracted part out for the bf16 product: K-channels by the
-    // list of indices, which has to ascend, rows and columns by a 16-bit table of positions that the selection leaves beside the mask.  Only for indices selected
-    // here, which are distinct and ascend.
+    // The launch that quantises an extracted operand also copies the extracted part out for the bf16 product: K-channels by the list of indices, which
+    // for a K-contiguous operand has to ascend as the selection leaves it, rows and columns by a 16-bit table of positions that the selection leaves beside
+    // the mask, for indices selected here, which are distinct (a repeated index in a caller's list would leave a position of the copy unwritten).
     // The table lies where the bf16 product keeps its partial sums:
     // a caller finds the scores in the workspace afterwards.  Whoever writes those sums, be it the other operand's quantiser, is queued behind the
     // quantiser that reads the table, on the same stream.  Where it does not fit
@@ -432,8 +432,8 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
         pos1 = reinterpret_cast<uint16_t *>(ws + L.gather_a + oe_rowcol_partials_at(M, N, K, strategy, k, &room));
         if (align_up((size_t)dim * sizeof(uint16_t), 4) > room) pos1 = nullptr;
     }
-    const bool a_gathers_k = oe_k && !use_given_idx && !a_given && iht_quantize_gathers_k(*A, kpad_planned);
-    const bool b_gathers_k = oe_k && !use_given_idx && !b_given && iht_quantize_gathers_k(*B, kpad_planned);
+    const bool a_gathers_k = oe_k && !a_given && iht_quantize_gathers_k(*A, kpad_planned, !use_given_idx);
+    const bool b_gathers_k = oe_k && !b_given && iht_quantize_gathers_k(*B, kpad_planned, !use_given_idx);
     const bool a_gathers_rows = pos1 && strategy == ADAHOP_IHT_OE_ROW && !a_given;
     const bool b_gathers_rows = pos1 && strategy == ADAHOP_IHT_OE_COL && !b_given;
     if (!(a_gathers_rows || b_gathers_rows)) pos1 = nullptr;

@@ -46,7 +46,7 @@ struct scales_sm_t {
 };
 // The extracted K-channels of an operand, copied out by the quantiser that reads the operand anyway (Eq. 7 with
 // S a set of K-channels): out[o, t] = x(o, idx[t]), out[o, k .. kpad) = 0.
-// out is [outer, kpad] bf16; idx ascends, as the selection leaves it.
+// out is [outer, kpad] bf16.
 struct k_gather_t {
     const int32_t *idx;
     uint16_t *out;        // nullptr: no copy
@@ -58,8 +58,8 @@ struct row_gather_t {
     const uint16_t *pos1; // per outer index
     uint16_t *out;        // nullptr: no copy
 };
-// Whether launch_iht_quantize honours a k_gather_t for this operand (K-contiguous, up to 4096 channels).
-bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad);
+// Whether launch_iht_quantize honours a k_gather_t for this operand: up to 4096 channels of a K-contiguous one, whose list has to ascend.
+bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad, bool ascending);
 // One operand to quantise.
 struct quant_job_t {
     const adahop_operand_t *x;

@@ -51,11 +51,19 @@ __global__ __launch_bounds__(256) void k_foid_scores(const uint16_t *__restrict_
             v = __builtin_fmaf(d, d, v);
         }
     } else {
-        for (int j = 0; j < L; ++j) s = s + bf16_one(x[base + j * step]);
+        // fewer: the last one in place of those that are missing, so that all loads are on their way together here too (one after the other 12288 scores of 32
+        // samples took 16.3 us, so 4.6; 8192 of 45 23 and 4.3)
+        float e[64];
+#pragma unroll
+        for (int j = 0; j < 64; ++j) e[j] = bf16_one(x[base + min(j, L - 1) * step]);
+#pragma unroll
+        for (int j = 0; j < 64; ++j)
+            if (j < L) s = s + e[j];
         const float mean = s * inv_L;
-        for (int j = 0; j < L; ++j) {
-            const float d = bf16_one(x[base + j * step]) - mean;
-            v = __builtin_fmaf(d, d, v);
+#pragma unroll
+        for (int j = 0; j < 64; ++j) {
+            const float d = e[j] - mean;
+            if (j < L) v = __builtin_fmaf(d, d, v);
         }
     }
     scores[i] = v;

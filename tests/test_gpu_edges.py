@@ -267,3 +267,47 @@ def test_runs_of_k_channels_copied_by_the_quantisers(ah, K, at, k):
         assert torch.equal(t, again[name]), name
     first, last = -(-at // b), (at + k) // b
     assert not got["a_codes"][:, first * b // 2:max(first, last) * b // 2].any() and not got["b_codes"][:, first * b // 2:max(first, last) * b // 2].any()
+
+
+@pytest.mark.parametrize("outer,K,axis", [(1, 64, 1), (2, 288, 1), (45, 512, 1), (63, 320, 1), (65, 320, 1), (300, 32, 0), (72, 64, 0)])
+@pytest.mark.parametrize("k_contig", [True, False])
+def test_scores_of_few_samples(ah, outer, K, axis, k_contig):
+    """Fewer than 64 samples per scored index (and 64), along the rows of the stored array and across them: the oracle's scores bit for bit."""
+    rng = np.random.default_rng(outer + K)
+    bits = bf16(rng.standard_normal((outer, K)) * np.exp(rng.standard_normal((outer, K))))
+    t, a = stored(bits, k_contig)
+    say("scores of few samples", outer, K, axis, k_contig)
+    k = max((outer if axis == 0 else K) // 5, 1)
+    idx, mask, scores = ah.adahop_foid_topk(ah.Operand(t, k_contig), axis, k)
+    torch.cuda.synchronize()
+    want = orc.foid_scores(a, k_contig, axis)
+    assert np.array_equal(host(scores).view(np.uint32), want.view(np.uint32))
+    assert np.array_equal(host(idx), np.flatnonzero(host(mask)))
+
+
+@pytest.mark.parametrize("M,N,K,k", [(8, 63, 64, 3), (65, 200, 288, 64), (1000, 72, 1056, 65), (129, 4104, 2048, 200)])
+@pytest.mark.parametrize("a_kc,b_kc", [(False, False), (True, False), (False, True)])
+@pytest.mark.parametrize("given,sr", [(False, False), (True, False), (False, True)])
+def test_k_channels_of_k_strided_operands_copied_beside_their_tiles(ah, M, N, K, k, a_kc, b_kc, given, sr):
+    """The copies of K-strided operands (by workgroups ahead of their tiles) and of K-contiguous ones give the same product, indices selected and handed
+    in, rounded to nearest and stochastically: ragged outer sizes, one to four groups of 64 channels."""
+    gen = torch.Generator(device="cuda").manual_seed(M * N + k)
+    A = torch.randn(M, K, generator=gen, device="cuda")
+    A[:, torch.randperm(K, generator=gen, device="cuda")[:k]] *= 50.0
+    A, B = A.to(torch.bfloat16), torch.randn(N, K, generator=gen, device="cuda").to(torch.bfloat16)
+    say("K-channels beside the tiles", (M, N, K), k, a_kc, b_kc, given, sr)
+
+    def strided(x):
+        wide = torch.zeros((K, (x.shape[0] + 7) // 8 * 8), dtype=torch.bfloat16, device="cuda")
+        wide[:, :x.shape[0]] = x.t()
+        return ah.Operand(wide[:, :x.shape[0]], False)
+
+    kw = {"sr_seed_a": 11} if sr else {}
+    want = ah.adahop_gemm(ah.Operand(A, True), ah.Operand(B, True), inputs.IHT_OE_K, 32, k, **kw)
+    keep = {n: want[n].clone() for n in ("C", "idx", "a_codes", "b_codes", "a_scales", "b_scales")}
+    if given:
+        kw["idx"] = keep["idx"].clone()
+    got = ah.adahop_gemm(ah.Operand(A, True) if a_kc else strided(A), ah.Operand(B, True) if b_kc else strided(B), inputs.IHT_OE_K, 32, k, **kw)
+    torch.cuda.synchronize()
+    for n, t in keep.items():
+        assert torch.equal(got[n], t), n
