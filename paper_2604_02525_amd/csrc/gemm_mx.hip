@@ -431,12 +431,21 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
         // 1190 / 1134; on the grid tile by tile: 12288 x 8192 x 1568 158 / 164, 4096 x 4096 x 8192 70.3 / 71.1
         float *crow = C + (m0 + wm * 128 + h * 4) * ldc + n0 + wn * 128 + l32;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (ST == STREAMED) {
 #pragma unroll
-            for (int n = 0; n < 64; ++n) {
-                const int j = ST == STREAMED ? n >> 4 : n & 3, r = ST == STREAMED ? n & 15 : n >> 2;
-                store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
             }
+        }
     } else if constexpr (ST == ELEMENTS) {
         OUT *crow = C + (m0 + wm * 128 + h * 4) * ldc + n0 + wn * 128 + l32;
 #pragma unroll
