@@ -33,8 +33,8 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 //                      transposing LDS read hands the matrix cores their 8 consecutive K-elements of a row.  K
 //                      is split over workgroups so that the chip is full although there are few tiles; every
 //                      slice writes its own partial tile (no atomics: the result does not depend on scheduling);
-//      (where L is K-strided and there are at most 96 rows, L's quantiser forms the products instead, k_quant_ks16_outliers, or
-//      k_outliers_ks16 in the same order: oe_rowcol_on_the_way);
+//      (with at most 96 rows L's quantiser forms the products instead, k_quant_ks16_outliers and k_quant_kc16_outliers, or
+//      launch_outlier_products in the same order: oe_rowcol_on_the_way);
 //   3. k_oe_reduce     adds the slices in a fixed order and writes the rows / columns of C.
 // ------------------------------------------------------------------------------------------------
 constexpr int SK_LCOLS = 256;  // rows of L per workgroup (NCW = 2; half of them with NCW = 1)
@@ -823,7 +823,7 @@ int configure_oe_rowcol()
 // 20000 x 4096, 1 row (316) 70 / 67.
 int launch_outlier_products(const adahop_operand_t &L, const outlier_job_t &e, hipStream_t st)
 {
-    if (ceil_div(ceil_div(L.K, 256), e.nslice) < LONG_SLICE)
+    if (L.k_contig || ceil_div(ceil_div(L.K, 256), e.nslice) < LONG_SLICE)
         return launch_iht_quantize_outliers(-1, {&L, nullptr, nullptr, nullptr, nullptr, nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}}, e, st);
     const int rc = configure_oe_rowcol();
     if (rc != ADAHOP_OK) return rc;
@@ -903,7 +903,6 @@ int launch_oe_reduce(const float *P, int nslice, int64_t rows_all, int64_t Lo, b
 bool oe_rowcol_on_the_way(const adahop_operand_t &S, const adahop_operand_t &L, int k, outlier_job_t *e)
 {
     const int64_t Lo = L.outer, K = L.K;
-    if (L.k_contig) return false;
     if (!S.k_contig && iht_quantize_beside_topk(S.outer, L) && ceil_div(Lo, 64) * ceil_div(K, 256) < 192) return false;
     e->tiles = (k + 15) / 16;
     while (e->tiles <= OUTLIER_TILES && !iht_quantize_takes_outliers(e->tiles)) ++e->tiles;

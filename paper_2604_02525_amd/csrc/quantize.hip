@@ -770,40 +770,13 @@ __device__ __forceinline__ void ks_read_tile(int tid, const uint8_t *lds, v4s (&
         d[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)(src + t * 4 * KT_PITCH));
 }
 
-// The column of the lane from its raw elements on: copied out if it is extracted, transformed, quantised and stored.
-// WHOLE: see ks_whole.
-template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_finish(const quant_t &q, int tid, int64_t o0, int64_t k0, const v4s (&d)[16])
+// The transform's strides from FROM on, of a lane that holds the 64 consecutive K-elements [64 g, 64 g + 64) of its column, and the factor.
+template <int B, int FROM> __device__ __forceinline__ void ks_transform(float (&wv)[64])
 {
-    const int64_t outer = q.outer, K = q.K;
-    const int lane = tid & 63, w = tid >> 6, g = lane >> 4, b4 = g & 1, b5 = g >> 1;
-    const uint32_t col = 16 * w + (lane & 15);
-    const int64_t o = o0 + col;
-    const bool active = WHOLE || o < outer;
-    float wv[64];
-#pragma unroll
-    for (int t = 0; t < 16; ++t)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) wv[4 * t + j] = bf16_one((uint16_t)d[t][j]);
-
-    // ---- an extracted column leaves as it came and counts as zero here: the lane has 64 of its K-elements in a row
-    // (as a launch of its own that reads two bytes of every K-row, this copy took 31 us for 64 columns x 32768)
-    if (q.gr.out) {
-        const uint32_t p = active ? q.gr.pos1[o] : 0u;
-        if (p) {
-            uint16_t *dst = q.gr.out + (int64_t)(p - 1) * K + k0 + 64 * g;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (WHOLE || k0 + 64 * g + 8 * i < K) *reinterpret_cast<uint4 *>(dst + 8 * i) = pieces(d[2 * i], d[2 * i + 1]);
-#pragma unroll
-            for (int i = 0; i < 64; ++i) wv[i] = 0.0f;
-        }
-    }
-
-    // ---- transform
     if constexpr (B > 0) {
         constexpr int HMAX = B >= 64 ? 32 : 16;
 #pragma unroll
-        for (int h = 1; h <= HMAX; h *= 2)
+        for (int h = FROM; h <= HMAX; h *= 2)
 #pragma unroll
             for (int i = 0; i < 64; i += 2 * h)
 #pragma unroll
@@ -825,7 +798,16 @@ template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_finish(
 #pragma unroll
         for (int i = 0; i < 64; ++i) wv[i] = __builtin_fmaf(wv[i], fin, 0.0f);
     }
+}
 
+// The lane's column, transformed: quantised and stored.  WHOLE: see ks_whole.
+template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_pack(const quant_t &q, int tid, int64_t o0, int64_t k0, const float (&wv)[64])
+{
+    const int64_t outer = q.outer, K = q.K;
+    const int lane = tid & 63, w = tid >> 6, g = lane >> 4, b4 = g & 1, b5 = g >> 1;
+    const uint32_t col = 16 * w + (lane & 15);
+    const int64_t o = o0 + col;
+    const bool active = WHOLE || o < outer;
     // ---- the lane's two MX blocks; at[i]: which of the tile's eight
     const int at[2] = {B == 256 ? b4 + 2 * b5 : B == 128 ? b4 + 4 * b5 : 2 * g, B == 256 ? 4 + b4 + 2 * b5 : B == 128 ? 2 + b4 + 4 * b5 : 2 * g + 1};
     uint32_t c[8];
@@ -891,6 +873,34 @@ template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_finish(
     }
     if (q.sm.out && active && g == 1)
         *reinterpret_cast<uint64_t *>(q.sm.out + ((k0 >> 8) * q.sm.rows + o0) * 8 + col * 8) = ((uint64_t)upper << 32 | lower) << (8 * rot);
+}
+
+// The column of the lane from its raw elements on: copied out if it is extracted, transformed, quantised and stored.
+template <int B, bool SR, bool WHOLE> __device__ __forceinline__ void ks_finish(const quant_t &q, int tid, int64_t o0, int64_t k0, const v4s (&d)[16])
+{
+    float wv[64];
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wv[4 * t + j] = bf16_one((uint16_t)d[t][j]);
+
+    // ---- an extracted column leaves as it came and counts as zero here: the lane has 64 of its K-elements in a row
+    // (as a launch of its own that reads two bytes of every K-row, this copy took 31 us for 64 columns x 32768)
+    if (q.gr.out) {
+        const int lane = tid & 63, g = lane >> 4;
+        const int64_t o = o0 + 16 * (tid >> 6) + (lane & 15);
+        const uint32_t p = WHOLE || o < q.outer ? q.gr.pos1[o] : 0u;
+        if (p) {
+            uint16_t *dst = q.gr.out + (int64_t)(p - 1) * q.K + k0 + 64 * g;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (WHOLE || k0 + 64 * g + 8 * i < q.K) *reinterpret_cast<uint4 *>(dst + 8 * i) = pieces(d[2 * i], d[2 * i + 1]);
+#pragma unroll
+            for (int i = 0; i < 64; ++i) wv[i] = 0.0f;
+        }
+    }
+    ks_transform<B, 1>(wv);
+    ks_pack<B, SR, WHOLE>(q, tid, o0, k0, wv);
 }
 
 template <int B, bool SR>
@@ -1111,6 +1121,134 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
 #pragma unroll 1
         for (; by < upr; by += nslice) take(std::false_type{});
     }
+    const int g = (threadIdx.x >> 4) & 3;
+    const int64_t o = o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
+    if (o < q.outer) {
+        float *p = e.p + (int64_t)slice * e.k * q.outer + o;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int t = 16 * rt + 4 * g + r;
+                if (t < e.k) p[(int64_t)t * q.outer] = acc[rt][r];
+            }
+    }
+}
+
+// The same for a K-contiguous operand.  A workgroup takes tiles of 64 rows x 256 K-elements, 16 rows to a wave: lane 16 g + r loads the eight pieces 32 i + 8 g
+// .. + 7 of row r, which is what it hands to matrix-core instruction i, and after the strides 1, 2, 4 in registers and 8, 16 between lanes (each exchange
+// leaves a lane with the halves of the next pair of K bits, see swap_butterfly) it holds 64 consecutive K-elements as the K-strided kernel's lanes do.
+// In place of a second pass over the operand.  Quantiser and products, us in two kernels / here: 12296 x 6368 with 2 rows 40 + 45 / 52, 9152 x 16672 with 2 73
+// + 56 / 105, 11008 x 4096 with 21 25 + 24 / 32, 4096 x 4096 with 82 14 + 15 / 21, 2048 x 544 with 7 4 + 7 / 5.
+//
+// What bounds it is how the memory takes pieces of 64 bytes of 16 rows: an operand up to KEEP_LONG is read through the caches, which fetch both halves of a line at
+// once (56 / 52, 36 / 32, 11.5 / 9.3 us); a larger one past them, or the product finds the packed operands gone (9152 x 16672: 105 / 97, but the product 61 / 89; 5632 x
+// 16384 71 / 71 and 193 / 208; 11008 x 8192 67 / 62 and 107 / 108).  The slices of a tile of rows are neighbours on an XCD and take every nslice-th K-block, so that what is read at a time lies
+// together; each slice a run of K-blocks, its workgroups on all XCDs: 60, 109, 37.  The next tile's loads ahead: the same.
+template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_kc16_outliers(quant_t q, outlier_job_t e)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[RT * 8192 + RT * 16 * 8];
+    const uint16_t **const row_at = reinterpret_cast<const uint16_t **>(lds + RT * 8192);
+    const int64_t K = q.K;
+    const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
+    if (blockIdx.x >= tiles) {
+        clear_extracted_row(e, (int)(blockIdx.x - tiles), K);
+        return;
+    }
+    // Each XCD takes a run of the workgroups, the slices of a tile of rows next to each other.
+    const uint32_t xcd = blockIdx.x & 7, rest = tiles & 7, at = xcd * (tiles >> 3) + min(xcd, rest) + (blockIdx.x >> 3), bx = at / (uint32_t)e.nslice;
+    const int upr = (int)q.upr, nslice = e.nslice, slice = (int)(at - bx * (uint32_t)nslice);
+    const int64_t o0 = (int64_t)bx * KS_COLS;
+    for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
+        const int r = min(t, e.k - 1);
+        row_at[t] = e.rows + (e.idx ? e.idx[r] : r) * e.ld;
+    }
+    __syncthreads();
+    v4f acc[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) acc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    // (rows past the end repeat the last one; what comes of them is not stored)
+    const uint16_t *const src = q.x + min(o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15), q.outer - 1) * q.ld + ((threadIdx.x >> 4) & 3) * 8;
+    auto take = [&](int by, auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int64_t k0 = (int64_t)by * 256;
+        u32x4 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = u32x4{0, 0, 0, 0};
+        if (e.keep_long) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (WHOLE || k0 + 32 * i < K) v[i] = *reinterpret_cast<const u32x4 *>(src + k0 + 32 * i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (WHOLE || k0 + 32 * i < K) v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + k0 + 32 * i));
+        }
+        // the extracted rows' 256 K-elements: piece c (8 elements) of row r0 + 8 i
+        const int c = tid & 31, r0 = tid >> 5;
+        u32x4 f[2 * RT];
+#pragma unroll
+        for (int i = 0; i < 2 * RT; ++i) {
+            f[i] = u32x4{0, 0, 0, 0};
+            if (WHOLE || k0 + 8 * c < K) f[i] = *reinterpret_cast<const u32x4 *>(row_at[r0 + 8 * i] + (k0 + 8 * c));
+        }
+        // A tile of 16 rows as 8 x 64 pieces: at (i, 16 g + r) piece 4 i + g of row r, at r ^ (4 i + g): the 16 pieces that 16 lanes write then cover the banks once.
+        u32x4 *const s = reinterpret_cast<u32x4 *>(lds);
+        {
+            const int at = (c >> 2) * 64 + (c & 3) * 16, x = c & 15;
+#pragma unroll
+            for (int i = 0; i < 2 * RT; ++i) s[(i >> 1) * 512 + at + ((r0 + 8 * (i & 1)) ^ x)] = f[i];
+        }
+        __syncthreads();
+        {
+            const int g = (tid >> 4) & 3, r = tid & 15;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { // (the sums of different rows in turn: none waits for the one before)
+                const v8bf row = __builtin_bit_cast(v8bf, v[i]);
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, s[rt * 512 + i * 64 + g * 16 + (r ^ ((4 * i + g) & 15))]), row, acc[rt], 0, 0, 0);
+                if (i & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads(); // (the next tile's rows may be written)
+        if constexpr (B > 0) {
+            float wv[64]; // K bits 0 .. 2, then of the piece's number i: bit 1 and bit 2 (after the exchanges K bits 3 and 4), bit 0 (K bit 5)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int at = 8 * ((i >> 1) & 1) + 16 * (i >> 2) + 32 * (i & 1);
+                const uint32_t p[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) wv[at + 2 * j] = bf16_lo(p[j]), wv[at + 2 * j + 1] = bf16_hi(p[j]);
+            }
+#pragma unroll
+            for (int h = 1; h <= 4; h *= 2)
+#pragma unroll
+                for (int i = 0; i < 64; i += 2 * h)
+#pragma unroll
+                    for (int j = i; j < i + h; ++j) {
+                        const float a = wv[j], b = wv[j + h];
+                        wv[j] = a + b;
+                        wv[j + h] = a - b;
+                    }
+#pragma unroll
+            for (int i = 0; i < 64; ++i)
+                if (!(i & 8)) swap_butterfly<false>(wv[i], wv[i + 8]); // stride 8
+#pragma unroll
+            for (int i = 0; i < 64; ++i)
+                if (!(i & 16)) swap_butterfly<true>(wv[i], wv[i + 16]); // stride 16
+            ks_transform<B, 32>(wv);
+            ks_pack<B, false, WHOLE>(q, tid, o0, k0, wv);
+        }
+    };
+    const int whole = o0 + KS_COLS <= q.outer ? (int)(K >> 8) : 0;
+    int by = slice;
+#pragma unroll 1
+    for (; by < whole; by += nslice) take(by, std::true_type{});
+#pragma unroll 1
+    for (; by < upr; by += nslice) take(by, std::false_type{});
     const int g = (threadIdx.x >> 4) & 3;
     const int64_t o = o0 + 16 * (threadIdx.x >> 6) + (threadIdx.x & 15);
     if (o < q.outer) {
@@ -1355,17 +1493,24 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
     return check_launch();
 }
 
-template <int B> int launch_outliers_b(const quant_t &q, const outlier_job_t &e, hipStream_t st)
+template <int B> int launch_outliers_b(quant_kind_t kind, const quant_t &q, const outlier_job_t &e, hipStream_t st)
 {
     const dim3 grid(q.col_tiles * (uint32_t)e.nslice + (uint32_t)(e.codes ? e.k : 0));
+    auto go = [&](auto tiles) {
+        if (kind == KS)
+            hipLaunchKernelGGL((k_quant_ks16_outliers<B, decltype(tiles)::value>), grid, dim3(256), 0, st, q, e);
+        else
+            hipLaunchKernelGGL((k_quant_kc16_outliers<B, decltype(tiles)::value>), grid, dim3(256), 0, st, q, e);
+        return check_launch();
+    };
     switch (e.tiles) {
-    case 1: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 1>), grid, dim3(256), 0, st, q, e); break;
-    case 2: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 2>), grid, dim3(256), 0, st, q, e); break;
-    case 3: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 3>), grid, dim3(256), 0, st, q, e); break;
-    case 4: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 4>), grid, dim3(256), 0, st, q, e); break;
-    case 6: hipLaunchKernelGGL((k_quant_ks16_outliers<B, 6>), grid, dim3(256), 0, st, q, e); break;
+    case 1: return go(std::integral_constant<int, 1>());
+    case 2: return go(std::integral_constant<int, 2>());
+    case 3: return go(std::integral_constant<int, 3>());
+    case 4: return go(std::integral_constant<int, 4>());
+    case 6: return go(std::integral_constant<int, 6>());
     }
-    return check_launch();
+    return ADAHOP_E_INVALID_ARG;
 }
 
 template <int B> int launch_two_b(quant_kind_t ka, const quant_t &qa, quant_kind_t kb, const quant_t &qb, hipStream_t st)
@@ -1523,17 +1668,23 @@ bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad, bool ascending)
 
 bool iht_quantize_takes_outliers(int tiles) { return (tiles >= 1 && tiles <= 4) || tiles == 6; }
 
-int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_job_t &e, hipStream_t st)
+// Elements of a K-contiguous operand up to which the caches keep it (see k_quant_kc16_outliers).
+constexpr int64_t KEEP_LONG = 80ll << 20;
+
+int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_job_t &job_e, hipStream_t st)
 {
     quant_t q;
-    if (describe(job, q) != KS || (b >= 0 && job.sr_seed) || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
+    const quant_kind_t kind = describe(job, q);
+    outlier_job_t e = job_e;
+    e.keep_long = q.outer * q.ld <= KEEP_LONG;
+    if (kind == KC_GATHER || (b >= 0 && job.sr_seed) || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
     q.order = order_of(q.col_tiles, (uint32_t)e.nslice, q.upr, q.ld);
     switch (b) {
-    case -1: return launch_outliers_b<-1>(q, e, st);
-    case 32: return launch_outliers_b<32>(q, e, st);
-    case 64: return launch_outliers_b<64>(q, e, st);
-    case 128: return launch_outliers_b<128>(q, e, st);
-    case 256: return launch_outliers_b<256>(q, e, st);
+    case -1: return launch_outliers_b<-1>(kind, q, e, st);
+    case 32: return launch_outliers_b<32>(kind, q, e, st);
+    case 64: return launch_outliers_b<64>(kind, q, e, st);
+    case 128: return launch_outliers_b<128>(kind, q, e, st);
+    case 256: return launch_outliers_b<256>(kind, q, e, st);
     }
     return ADAHOP_E_INVALID_ARG;
 }

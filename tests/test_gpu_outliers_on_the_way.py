@@ -50,7 +50,7 @@ CASES = [
 
 @pytest.mark.parametrize("short,long,K,k,block,short_kc", CASES)
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
-def test_products_on_the_way(short, long, K, k, block, short_kc, strategy):
+def test_products_on_the_way(short, long, K, k, block, short_kc, strategy, long_kc=False):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2604_02525_amd import binding as ah
@@ -58,7 +58,7 @@ def test_products_on_the_way(short, long, K, k, block, short_kc, strategy):
     rng = np.random.default_rng(short + long + K + k)
     row = strategy == inputs.IHT_OE_ROW
     S, L = bits(rng, short, K, k), bits(rng, long, K, 2)
-    (s, s_st), (l, l_st) = operand(ah, S, short_kc, 8), operand(ah, L, False, 16)
+    (s, s_st), (l, l_st) = operand(ah, S, short_kc, 8), operand(ah, L, long_kc, 16)
     A, B, a_st, b_st = (s, l, s_st, l_st) if row else (l, s, l_st, s_st)
     out = ah.adahop_gemm(A, B, strategy, block, k)
     torch.cuda.synchronize()
@@ -86,6 +86,16 @@ def test_products_on_the_way(short, long, K, k, block, short_kc, strategy):
     if ref:
         rest = np.delete(C - ref["C"], idx, axis=0 if row else 1)
         assert np.linalg.norm(rest) <= 1e-3 * np.linalg.norm(np.delete(ref["C"], idx, axis=0 if row else 1))
+
+
+@pytest.mark.parametrize("short,long,K,k,block,short_kc", CASES + [
+    (70, 127, 96, 33, 32, True), (70, 63, 2048, 9, 256, False), (600, 191, 4416, 70, 64, True),
+    (300, 20504, 4128, 5, 32, True),    # an operand that is streamed past the caches
+])
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+def test_products_on_the_way_of_a_k_contiguous_operand(short, long, K, k, block, short_kc, strategy):
+    """The same by the quantiser of a K-contiguous operand (tiles of 64 rows x 256 K-elements)."""
+    test_products_on_the_way(short, long, K, k, block, short_kc, strategy, long_kc=True)
 
 
 @pytest.mark.parametrize("sr", ["short", "long"])
