@@ -83,7 +83,6 @@ struct outlier_job_t {
     const int32_t *idx;
     float *p;
     int k, tiles, nslice; // tiles: of 16 rows
-    int keep_long;        // (set at the launch)
     // the rows idx[t] of the other operand's codes and scales, to be set to zero (codes = nullptr: they are)
     uint8_t *codes, *scales;
     scales_sm_t sm;

@@ -1145,7 +1145,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
 // once (56 / 52, 36 / 32, 11.5 / 9.3 us); a larger one past them, or the product finds the packed operands gone (9152 x 16672: 105 / 97, but the product 61 / 89; 5632 x
 // 16384 71 / 71 and 193 / 208; 11008 x 8192 67 / 62 and 107 / 108).  The slices of a tile of rows are neighbours on an XCD and take every nslice-th K-block, so that what is read at a time lies
 // together; each slice a run of K-blocks, its workgroups on all XCDs: 60, 109, 37.  The next tile's loads ahead: the same.
-template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_kc16_outliers(quant_t q, outlier_job_t e)
+template <int B, int RT, bool KEEP> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_kc16_outliers(quant_t q, outlier_job_t e)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[RT * 8192 + RT * 16 * 8];
     const uint16_t **const row_at = reinterpret_cast<const uint16_t **>(lds + RT * 8192);
@@ -1177,15 +1177,12 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
         u32x4 v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = u32x4{0, 0, 0, 0};
-        if (e.keep_long) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (WHOLE || k0 + 32 * i < K) v[i] = *reinterpret_cast<const u32x4 *>(src + k0 + 32 * i);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (WHOLE || k0 + 32 * i < K) v[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + k0 + 32 * i));
-        }
+        for (int i = 0; i < 8; ++i)
+            if (WHOLE || k0 + 32 * i < K) {
+                const u32x4 *p = reinterpret_cast<const u32x4 *>(src + k0 + 32 * i);
+                v[i] = KEEP ? *p : __builtin_nontemporal_load(p);
+            }
         // the extracted rows' 256 K-elements: piece c (8 elements) of row r0 + 8 i
         const int c = tid & 31, r0 = tid >> 5;
         u32x4 f[2 * RT];
@@ -1493,14 +1490,19 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
     return check_launch();
 }
 
+// Elements of a K-contiguous operand up to which the caches keep it (see k_quant_kc16_outliers).
+constexpr int64_t KEEP_LONG = 80ll << 20;
+
 template <int B> int launch_outliers_b(quant_kind_t kind, const quant_t &q, const outlier_job_t &e, hipStream_t st)
 {
     const dim3 grid(q.col_tiles * (uint32_t)e.nslice + (uint32_t)(e.codes ? e.k : 0));
     auto go = [&](auto tiles) {
         if (kind == KS)
             hipLaunchKernelGGL((k_quant_ks16_outliers<B, decltype(tiles)::value>), grid, dim3(256), 0, st, q, e);
-        else
-            hipLaunchKernelGGL((k_quant_kc16_outliers<B, decltype(tiles)::value>), grid, dim3(256), 0, st, q, e);
+        else if (B < 0 || q.outer * q.ld <= KEEP_LONG)
+            hipLaunchKernelGGL((k_quant_kc16_outliers<B, decltype(tiles)::value, true>), grid, dim3(256), 0, st, q, e);
+        else if constexpr (B >= 0)
+            hipLaunchKernelGGL((k_quant_kc16_outliers<B, decltype(tiles)::value, false>), grid, dim3(256), 0, st, q, e);
         return check_launch();
     };
     switch (e.tiles) {
@@ -1668,15 +1670,10 @@ bool iht_quantize_gathers_k(const adahop_operand_t &x, int kpad, bool ascending)
 
 bool iht_quantize_takes_outliers(int tiles) { return (tiles >= 1 && tiles <= 4) || tiles == 6; }
 
-// Elements of a K-contiguous operand up to which the caches keep it (see k_quant_kc16_outliers).
-constexpr int64_t KEEP_LONG = 80ll << 20;
-
-int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_job_t &job_e, hipStream_t st)
+int launch_iht_quantize_outliers(int b, const quant_job_t &job, const outlier_job_t &e, hipStream_t st)
 {
     quant_t q;
     const quant_kind_t kind = describe(job, q);
-    outlier_job_t e = job_e;
-    e.keep_long = q.outer * q.ld <= KEEP_LONG;
     if (kind == KC_GATHER || (b >= 0 && job.sr_seed) || !iht_quantize_takes_outliers(e.tiles)) return ADAHOP_E_INVALID_ARG;
     q.order = order_of(q.col_tiles, (uint32_t)e.nslice, q.upr, q.ld);
     switch (b) {
