@@ -214,6 +214,15 @@ __device__ __forceinline__ uint4 load_part16(const uint16_t *p, int n)
     return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
 }
 
+// Between what lanes of a wave write to LDS and what other lanes of the same wave read there.  A wave's LDS operations take effect in their
+// order, so this is no instruction; but the compiler looks at one lane at a time: without it a lane whose own code did not change what it
+// had stored may be handed that on in place of what another lane has put there since.
+__device__ __forceinline__ void lds_between_lanes()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // The codes and scales of the extracted row idx[t], by a workgroup of 256 threads.
 __device__ __forceinline__ void clear_extracted_row(const outlier_job_t &e, int t, int64_t K)
 {

@@ -546,6 +546,7 @@ __device__ __forceinline__ void quant_kc_gather_rows(const quant_t &q, uint32_t 
         lds16_t *const own = reinterpret_cast<lds16_t *>(raw + plan.chunk * 8);
         own[0] = in0 ? f.r0 : u32x4{0, 0, 0, 0};
         own[16] = in1 ? f.r1 : u32x4{0, 0, 0, 0};
+        lds_between_lanes();
         int t = f.t, at = f.active && t <= last ? f.at : none;
         for (;;) {
             if (at >= f.from && at < f.from + 256) {
@@ -558,6 +559,7 @@ __device__ __forceinline__ void quant_kc_gather_rows(const quant_t &q, uint32_t 
             t += 16;
             at = again >> (tid & 48) & 0x8000 ? entry(t) : none;
         }
+        lds_between_lanes();
         const u32x4 e0 = own[0], e1 = own[16];
         float w0[8] = {bf16_lo(e0.x), bf16_hi(e0.x), bf16_lo(e0.y), bf16_hi(e0.y),
                        bf16_lo(e0.z), bf16_hi(e0.z), bf16_lo(e0.w), bf16_hi(e0.w)};
