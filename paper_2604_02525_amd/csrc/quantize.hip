@@ -482,6 +482,9 @@ template <int B, int FLAT, bool SR, bool TAIL> __global__ __launch_bounds__(256)
 // 32.6 .. 37, 16 .. 21.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 lds16_t __attribute__((may_alias)); // (a unit's elements are written and read in pieces and one by one)
+// What a pointer kept in LDS points to: of one that does not say so the compiler makes flat loads, which are waited for together with all others.
+typedef __attribute__((address_space(1))) uint16_t global_u16;
+typedef __attribute__((address_space(1))) u32x4 global_u32x4;
 constexpr int KC_GATHER_MAX_KPAD = 4096;
 constexpr int KC_GATHER_COPY = KC_GATHER_MAX_KPAD * 2, KC_GATHER_LDS = KC_GATHER_COPY + 4096 * 2; // bytes: the copies of the rows, and a pass
 
@@ -1031,7 +1034,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
 {
     constexpr int TILE_LDS = RT * 8192 > KS_LDS ? RT * 8192 : KS_LDS;
     __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS + RT * 16 * 8];
-    const uint16_t **const row_at = reinterpret_cast<const uint16_t **>(lds + TILE_LDS);
+    const global_u16 **const row_at = reinterpret_cast<const global_u16 **>(lds + TILE_LDS);
     const int64_t K = q.K;
     const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
     if (blockIdx.x >= tiles) {
@@ -1043,7 +1046,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
     const int64_t o0 = (int64_t)bx * KS_COLS;
     for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
         const int r = min(t, e.k - 1);
-        row_at[t] = e.rows + (e.idx ? e.idx[r] : r) * e.ld;
+        row_at[t] = (const global_u16 *)(e.rows + (e.idx ? e.idx[r] : r) * e.ld);
     }
     __syncthreads();
     v4f acc[RT];
@@ -1077,7 +1080,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
 #pragma unroll
         for (int i = 0; i < 2 * RT; ++i) {
             f[i] = u32x4{0, 0, 0, 0};
-            if (WHOLE || k0 + 8 * c < K) f[i] = *reinterpret_cast<const u32x4 *>(row_at[r0 + 8 * i] + (k0 + 8 * c));
+            if (WHOLE || k0 + 8 * c < K) f[i] = *reinterpret_cast<const global_u32x4 *>(row_at[r0 + 8 * i] + (k0 + 8 * c));
         }
         if constexpr (WHOLE)
             ks_put_whole(q, tid, k0, lds, tile);
@@ -1150,7 +1153,7 @@ template <int B, int RT> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void
 template <int B, int RT, bool KEEP> __global__ __launch_bounds__(256, RT <= 4 ? 4 : 3) void k_quant_kc16_outliers(quant_t q, outlier_job_t e)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[RT * 8192 + RT * 16 * 8];
-    const uint16_t **const row_at = reinterpret_cast<const uint16_t **>(lds + RT * 8192);
+    const global_u16 **const row_at = reinterpret_cast<const global_u16 **>(lds + RT * 8192);
     const int64_t K = q.K;
     const uint32_t tiles = q.col_tiles * (uint32_t)e.nslice;
     if (blockIdx.x >= tiles) {
@@ -1163,7 +1166,7 @@ template <int B, int RT, bool KEEP> __global__ __launch_bounds__(256, RT <= 4 ? 
     const int64_t o0 = (int64_t)bx * KS_COLS;
     for (int t = threadIdx.x; t < 16 * RT; t += 256) { // (the last row stands for those behind it, whose sums are not stored)
         const int r = min(t, e.k - 1);
-        row_at[t] = e.rows + (e.idx ? e.idx[r] : r) * e.ld;
+        row_at[t] = (const global_u16 *)(e.rows + (e.idx ? e.idx[r] : r) * e.ld);
     }
     __syncthreads();
     v4f acc[RT];
@@ -1191,7 +1194,7 @@ template <int B, int RT, bool KEEP> __global__ __launch_bounds__(256, RT <= 4 ? 
 #pragma unroll
         for (int i = 0; i < 2 * RT; ++i) {
             f[i] = u32x4{0, 0, 0, 0};
-            if (WHOLE || k0 + 8 * c < K) f[i] = *reinterpret_cast<const u32x4 *>(row_at[r0 + 8 * i] + (k0 + 8 * c));
+            if (WHOLE || k0 + 8 * c < K) f[i] = *reinterpret_cast<const global_u32x4 *>(row_at[r0 + 8 * i] + (k0 + 8 * c));
         }
         // A tile of 16 rows as 8 x 64 pieces: at (i, 16 g + r) piece 4 i + g of row r, at r ^ (4 i + g): the 16 pieces that 16 lanes write then cover the banks once.
         u32x4 *const s = reinterpret_cast<u32x4 *>(lds);
