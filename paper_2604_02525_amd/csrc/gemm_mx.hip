@@ -424,6 +424,12 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
                                            int64_t n0, int w, int lane)
 {
     const int l32 = lane & 31, h = lane >> 5, wm = w >> 1, wn = w & 1;
+    // The row of accumulator r of tile row i, where rows are stored one after the other; its offset is formed here and now.
+    auto row_of = [&](OUT *crow, int i, int r) {
+        int64_t pitch = ldc;
+        asm volatile("" : "+s"(pitch)); // (the compiler made the offsets of all 64 rows beforehand and spilled 190 scalar registers)
+        return crow + (int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * pitch;
+    };
     if constexpr (sizeof(OUT) == 4) {
         // fp32: straight from the accumulator registers, 128-byte row segments (staging through LDS as below
         // and storing whole rows, 16 bytes per lane, was measured and is no faster).  Off the 64-byte grid row by row over the wave's columns, so
@@ -440,10 +446,11 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
                         store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
             } else {
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
+                for (int r = 0; r < 16; ++r) {
+                    OUT *const row = row_of(crow, i, r);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        store_as<ST>(t.acc[i][j][r], &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+                    for (int j = 0; j < 4; ++j) store_as<ST>(t.acc[i][j][r], row + j * 32);
+                }
             }
         }
     } else if constexpr (ST == ELEMENTS) {
@@ -451,11 +458,11 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
+            for (int r = 0; r < 16; ++r) {
+                OUT *const row = row_of(crow, i, r);
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    store_as<ST>(__builtin_bit_cast(uint16_t, (__bf16)t.acc[i][j][r]),
-                                 &crow[(int64_t)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc + j * 32]);
+                for (int j = 0; j < 4; ++j) store_as<ST>(__builtin_bit_cast(uint16_t, (__bf16)t.acc[i][j][r]), row + j * 32);
+            }
     } else {
         // bf16: a lane converts two consecutive accumulator rows into one packed pair, trades pairs with its
         // neighbour and keeps, as one dword, two adjacent columns of one row (even lane: the low halves =
