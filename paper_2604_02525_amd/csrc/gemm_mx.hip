@@ -397,7 +397,7 @@ template <int NBFC> __device__ __forceinline__ void run_tile(tile_state_t &t, co
 
 // The accumulators of a finished tile -> C.  The two stage buffers may already hold the next tile, so the
 // bf16 path, which has to transpose through LDS, uses a small patch private to the wave beyond them; LDS
-// operations of one wave execute in order, so the patch needs no barrier.
+// operations of one wave execute in order, so the patch needs no barrier, but what tells the compiler that lanes exchange there (lds_between_lanes).
 //
 // How the stores go, by the alignment of the rows of C (host side: launch_gemm_mx_t):
 //   STREAMED  rows begin at multiples of 64 bytes: non-temporal stores, every one of which fills 64-byte pieces of cache lines;
@@ -493,12 +493,14 @@ __device__ __forceinline__ void store_tile(tile_state_t &t, uint8_t *smem, OUT *
                         *reinterpret_cast<uint32_t *>(patch + row * BP + (jj * 32 + (l32 & ~1)) * 2) =
                             __builtin_amdgcn_perm(q, p, sel);
                     }
+                lds_between_lanes();
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int prow = q * 8 + (lane >> 3);
                     const u32x4 v = *reinterpret_cast<const u32x4 *>(patch + prow * BP + (lane & 7) * 16);
                     store_as<ST>(v, reinterpret_cast<u32x4 *>(cbase + (int64_t)(i * 32 + prow) * ldc + jp * 64 + (lane & 7) * 8));
                 }
+                lds_between_lanes(); // (the patch may be written again)
             }
     }
 }

@@ -51,3 +51,10 @@ def test_the_quantiser_that_takes_k_channels_out_says_so():
         seen = "".join("c" if "lds_between_lanes" in m else m[0] for m in re.findall(r"(?:load|store) <4 x i32>[^\n]*!tbaa|call void @\S*lds_between_lanes", b))
         seen = seen[seen.index("c") - 4:]       # l s l s: the two pieces, read from the loaded ones or zero and stored
         assert seen[:6] == "lslscc" and seen[6] == "l" and seen[8] == "l", seen
+
+
+def test_the_store_of_a_bf16_tile_says_so():
+    """Both instances that turn the tile through a wave's patch: between its writes and reads, and before it is written again."""
+    code = intermediate(os.path.join(build.CSRC, "gemm_mx.hip"), "-Xclang", "-disable-llvm-passes")
+    bodies = re.findall(r"\ndefine [^\n]*@_ZN6adahop12_GLOBAL__N_110store_tileItLNS0_7store_tE[01]E[^\n]*\n.*?\n}", code, re.S)
+    assert [len(re.findall(r"call void @\S*lds_between_lanes", b)) for b in bodies] == [2, 2]
