@@ -530,6 +530,152 @@ __global__ __launch_bounds__(256, CT == 4 || R == 3 ? 1 : 2) void k_outlier_prod
     }
 }
 
+// The same for a K-contiguous L, in the order of k_quant_kc16_outliers: slices as above, a block's K-elements in ascending chunks of 32, one instruction
+// each.  Bound by reading L, and by the extracted rows beside it where they are many (12288 x 8192, 90 rows: 66 us, 50 without its loads of L).
+//   Workgroup = T tiles of 16 extracted rows x 128 rows of L x one slice, a wave = all the extracted rows x 32 rows of L.
+//   L goes from memory to the matrix cores' operands without the LDS.  A load takes whole lines, 8 rows x 64 K-elements: lane 16 g + 8 u + r piece 4 u + g of
+//   row r.  Of two of them, rows 0 .. 7 and 8 .. 15 of a tile, an exchange of the lanes 8 apart makes the operands of two instructions, u = 0 and 1.  Two chunks of 64
+//   K-elements are on their way in registers while a third is multiplied (four: 16384 x 4096, 64 rows, 39 -> 44 us; through the LDS as in k_oe_skinny: the same,
+//   9152 x 16672, 2 rows, 72 / 66; 256 rows of L per workgroup, 20000 x 4096, 40 rows, 46 / 56).
+//   The extracted rows travel in stages of 128 K-elements through two buffers, one barrier per stage; in a buffer as 4 x 64 pieces for each 16 rows, as in
+//   the quantiser.
+//   A tile's slices are neighbours on an XCD, as in the quantiser, and each XCD begins its run of the workgroups three tiles further than the one before: begun alike,
+//   the XCDs read a power of two apart (16384 x 4096, 10 rows 35.7 -> 30.5 us, 64 rows 47 -> 40; 8192 x 8192 29.6 -> 27.7).
+constexpr int OPK_ROWS = 128, OPK_STAGE = 128;
+
+template <int T>
+__global__ __launch_bounds__(256, 2) void k_outlier_products_kc(const uint16_t *__restrict__ L, int64_t ldl, int64_t Lo, int64_t K, outlier_job_t e, int row_groups)
+{
+    constexpr int CT = OPK_ROWS / 64, NS = 2 * ((T + 1) / 2), SB = OPK_STAGE * 2 * 16 * NS; // tiles of a wave; pieces of the extracted rows per lane and stage; bytes of a stage
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * SB];
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int tiles = row_groups * e.nslice;
+    if ((int)blockIdx.x >= tiles) {
+        clear_extracted_row(e, (int)blockIdx.x - tiles, K);
+        return;
+    }
+    const int xcd = blockIdx.x & 7, rest = tiles & 7, run = (tiles >> 3) + (xcd < rest ? 1 : 0);
+    const int at = xcd * (tiles >> 3) + min(xcd, rest) + (((int)blockIdx.x >> 3) + 3 * e.nslice * xcd) % run;
+    const int group = at / e.nslice, slice = at - group * e.nslice;
+    const int64_t l0 = (int64_t)group * OPK_ROWS + 16 * CT * w;
+    const int nblock = ((int)((K + 255) / 256) - slice + e.nslice - 1) / e.nslice;
+    const int64_t last = (int64_t)(slice + e.nslice * (nblock - 1)) * 256;
+    const int nstage = 2 * (nblock - 1) + (K - last > OPK_STAGE ? 2 : 1);
+    auto k_of = [&](int chunk) { return (int64_t)(slice + e.nslice * (chunk >> 2)) * 256 + 64 * (chunk & 3); }; // (behind the slice's last block: past the end of K)
+
+    // Rows past the last one by that one (not stored).
+    const uint16_t *lrows[2 * CT];
+    const int lk = 32 * (lane >> 3 & 1) + 8 * g;
+#pragma unroll
+    for (int i = 0; i < 2 * CT; ++i) lrows[i] = L + min(l0 + 8 * i + (lane & 7), Lo - 1) * ldl;
+    // (past the end of K: the row's first piece, which exists, and zeros on both sides: an infinity there must not meet one of those zeros)
+    auto fetch_l = [&](int chunk, uint4 (&f)[2 * CT]) {
+        const int64_t k = k_of(chunk) + lk, there = k < K ? k : 0;
+#pragma unroll
+        for (int i = 0; i < 2 * CT; ++i) f[i] = load_once16(lrows[i] + there);
+    };
+    // Piece sc of the rows sr + 16 i.
+    const int sc = tid & 15, sr = tid >> 4;
+    const uint16_t *srows[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const int t = min(sr + 16 * i, e.k - 1);
+        srows[i] = e.rows + (e.idx ? e.idx[t] : t) * e.ld;
+    }
+    uint4 ps[NS];
+    auto fetch_s = [&](int stage) {
+        const int64_t k = k_of(2 * stage) + 8 * sc, there = k < K ? k : 0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) ps[i] = *reinterpret_cast<const uint4 *>(srows[i] + there);
+    };
+    auto stash_s = [&](int stage) {
+        const uint32_t keep = k_of(2 * stage) + 8 * sc < K ? ~0u : 0u;
+        uint4 *const s = reinterpret_cast<uint4 *>(lds + (stage & 1) * SB) + (sc >> 2) * 64 + (sc & 3) * 16 + (sr ^ sc);
+#pragma unroll
+        for (int i = 0; i < NS; ++i) s[i * 256] = make_uint4(ps[i].x & keep, ps[i].y & keep, ps[i].z & keep, ps[i].w & keep);
+    };
+
+    v4f acc[T][CT];
+#pragma unroll
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[i][c] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    uint4 set[2][2 * CT];
+    v8bf a[2][T], b[2][CT];
+
+    // Half h of a stage: chunk 2 stage + h, which has arrived in set h; the set is refilled with the chunk after the next one.
+    auto half = [&](auto h_c, int stage) {
+        constexpr int h = decltype(h_c)::value;
+        const uint4 *const rows = reinterpret_cast<const uint4 *>(lds + (stage & 1) * SB) + 16 * g;
+        auto fragments = [&](int i) { // instruction i of the stage
+#pragma unroll
+            for (int t = 0; t < T; ++t) a[i & 1][t] = __builtin_bit_cast(v8bf, rows[t * 256 + i * 64 + (l16 ^ (4 * i + g))]);
+        };
+        if constexpr (h == 0) fragments(0);
+        const uint32_t keep = k_of(2 * stage + h) + lk < K ? ~0u : 0u;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const uint4 p = set[h][2 * c], q = set[h][2 * c + 1];
+            const uint32_t lo[4] = {p.x & keep, p.y & keep, p.z & keep, p.w & keep}, hi[4] = {q.x & keep, q.y & keep, q.z & keep, q.w & keep};
+            uint32_t v[2][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { // (row_ror:8, into the lanes 8 .. 15 or 0 .. 7 of each 16)
+                v[0][j] = __builtin_amdgcn_update_dpp(lo[j], hi[j], 0x128, 0xf, 0xc, false);
+                v[1][j] = __builtin_amdgcn_update_dpp(hi[j], lo[j], 0x128, 0xf, 0x3, false);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) b[u][c] = __builtin_bit_cast(v8bf, make_uint4(v[u][0], v[u][1], v[u][2], v[u][3]));
+        }
+        fetch_l(2 * stage + h + 2, set[h]);
+        if constexpr (h == 1) {
+            stash_s(stage + 1);
+            fetch_s(stage + 2);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = 2 * h + u;
+            if (i < 3) fragments(i + 1);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i & 1][t], b[u][c], acc[t][c], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // (in this order, and into a loop that is entered without a condition: its waits count the loads behind the one that is needed, on either way into it)
+    fetch_s(0);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_l(0, set[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_l(1, set[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    stash_s(0);
+    fetch_s(1);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    int stage = 0;
+    do {
+        half(std::integral_constant<int, 0>(), stage);
+        half(std::integral_constant<int, 1>(), stage);
+        __syncthreads();
+    } while (++stage < nstage);
+    float *p = e.p + (int64_t)slice * e.k * Lo;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const int64_t o = l0 + 16 * c + l16;
+        if (o < Lo) {
+#pragma unroll
+            for (int i = 0; i < T; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int t = 16 * i + 4 * g + r;
+                    if (t < e.k) p[(int64_t)t * Lo + o] = acc[i][c][r];
+                }
+        }
+    }
+}
+
 // C[idx[t], l] (ROWS) or C[l, idx[t]] = sum over the K slices of P[s][t][l], in slice order.
 // C holds float, or bf16 as its 16 bits (rounded to nearest even from the fp32 sum).
 template <bool ROWS, typename OUT>
@@ -707,7 +853,16 @@ template <int R, int CT> int launch_products_as(const adahop_operand_t &x, const
     return check_launch();
 }
 
+template <int T> int launch_products_kc_as(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st)
+{
+    const int64_t groups = ceil_div(x.outer, OPK_ROWS);
+    hipLaunchKernelGGL((k_outlier_products_kc<T>), dim3((unsigned)(groups * e.nslice + (e.codes ? e.k : 0))), dim3(256), 0, st,
+                       static_cast<const uint16_t *>(x.data), x.ld, x.outer, x.K, e, (int)groups);
+    return check_launch();
+}
+
 constexpr int64_t LONG_SLICE = 4; // blocks of 256 K-elements
+constexpr int64_t LONG_KC = 32ll << 20; // elements of a K-contiguous operand
 
 // out[o, t] = x(o, idx[t]) for t < k, 0 for k <= t < kpad.  out is [outer, kpad] bf16.
 __global__ __launch_bounds__(256) void k_gather_k(const uint16_t *__restrict__ x, int64_t ld, int k_contig,
@@ -814,17 +969,32 @@ int configure_oe_rowcol()
     return ADAHOP_OK;
 }
 
-// Slices of up to three blocks: the quantiser's kernel without the quantisation, which takes a block at once; k_outlier_products has to fill its
+// K-strided, slices of up to three blocks: the quantiser's kernel without the quantisation, which takes a block at once; k_outlier_products has to fill its
 // pipeline first.  Whole calls with 96 rows of the other operand, the quantiser's kernel / this, us: one block, 11008 x 2016, 16 rows 34.7 / 39.7; two, 8192 x 5024, 16
 // rows 46.8 / 50.8; three, 14336 x 4096, 40 rows 57.3 / 61.0; four, 20000 x 4096, 1 row 69.6 / 67.0, 40 rows 81.0 / 78.6; seven, 11008 x 12000, 1 row 103 / 94.6;
 // more, 5000 x 28672, 16 rows 153 / 133, 28672 x 8192, 64 rows 185 / 144.
 // 256 columns per workgroup where these fill the chip in one round, or with more than 64 rows, where half as wide ones do not fit twice into the LDS
 // either: 17000 x 10048, 64 rows (201 workgroups) 134 / 156 with 128 columns, 90 rows (268) 175 / 183; but 12288 x 8192, 16 rows (384) 80 / 73, and
 // 20000 x 4096, 1 row (316) 70 / 67.
+// K-contiguous, fewer than LONG_KC elements: the quantiser's kernel, which leaves the operand in the caches; a larger one takes the place of the packed operands there,
+// which the next product reads.  Whole calls on operands used in turn, the quantiser's kernel / k_outlier_products_kc, us: 6144 x 4096, 10 rows 44 / 48.5;
+// 8192 x 4096, 41 rows 82 / 83; 4096 x 8192, 10 rows 58.5 / 56; 2048 x 16384, 10 rows 71 / 67; 9216 x 4096, 41 rows 101 / 97; 16384 x 4096, 10 rows 98 / 87;
+// 11008 x 8192, 40 rows 187 / 167; 28672 x 2048, 82 rows 246 / 199; 28672 x 8192, 41 rows 384 / 375.  (k_oe_skinny, which adds in another order, is up to 8 % faster in
+// such a call with many rows and short slices: 16384 x 4096, 64 rows 92 / 96, 20000 x 4096, 40 rows 109 / 116, 12288 x 8192, 90 rows 128 / 138; elsewhere as fast, or up to 9 % slower.)
 int launch_outlier_products(const adahop_operand_t &L, const outlier_job_t &e, hipStream_t st)
 {
-    if (L.k_contig || ceil_div(ceil_div(L.K, 256), e.nslice) < LONG_SLICE)
+    if (L.k_contig ? L.outer * L.K < LONG_KC : ceil_div(ceil_div(L.K, 256), e.nslice) < LONG_SLICE)
         return launch_iht_quantize_outliers(-1, {&L, nullptr, nullptr, nullptr, nullptr, nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}}, e, st);
+    if (L.k_contig) {
+        switch (e.tiles) {
+        case 1: return launch_products_kc_as<1>(L, e, st);
+        case 2: return launch_products_kc_as<2>(L, e, st);
+        case 3: return launch_products_kc_as<3>(L, e, st);
+        case 4: return launch_products_kc_as<4>(L, e, st);
+        case 6: return launch_products_kc_as<6>(L, e, st);
+        }
+        return ADAHOP_E_INVALID_ARG;
+    }
     const int rc = configure_oe_rowcol();
     if (rc != ADAHOP_OK) return rc;
     if (e.k > 64) return launch_products_as<3, 4>(L, e, st);

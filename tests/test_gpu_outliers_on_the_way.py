@@ -129,7 +129,7 @@ def test_rounding_option(sr):
     (200, 33000, 1056, 40, False), (96, 11000, 9248, 33, True), (96, 14337, 5152, 64, True), (96, 20008, 4320, 64, False),  # 64: 128, 128, 256, 256
     (120, 28681, 4128, 90, False), (100, 5000, 28704, 96, True), (96, 33100, 1184, 65, True)])      # 96
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
-def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, strategy):
+def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, strategy, long_kc=False):
     """Extracted rows / columns of a call that quantises both operands, of one with the other operand packed beforehand, of one that
     rounds it stochastically, and of the bf16 product by itself."""
     if not torch.cuda.is_available():
@@ -145,7 +145,8 @@ def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, 
         wide = torch.full((x.shape[0], (x.shape[1] + 7) // 8 * 8 + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
         wide[:, :x.shape[1]] = x
         return ah.Operand(wide[:, :x.shape[1]], k_contig)
-    s, l = stored(short, short_kc, k), stored(long, False, 2)
+    s, l = stored(short, short_kc, k), stored(long, long_kc, 2)
+    at = l.tensor.T if long_kc else l.tensor    # [K, long]
     assert long * K > 32 << 20
     row = strategy == inputs.IHT_OE_ROW
     A, B = (s, l) if row else (l, s)
@@ -165,20 +166,35 @@ def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, 
     assert torch.equal(extracted(alone), extracted(want["C"]))
     a, b = (A, B) if row else (B, A)
     take = a.tensor[idx.long()] if a.k_contig else a.tensor[:, idx.long()].T
-    exact = take.double() @ l.tensor.double()
-    bound = K * 2.0 ** -24 * (take.double().abs() @ l.tensor.double().abs())   # (see above)
+    exact = take.double() @ at.double()
+    bound = K * 2.0 ** -24 * (take.double().abs() @ at.double().abs())   # (see above)
     got = want["C"][idx.long()] if row else want["C"][:, idx.long()].T
     assert bool(((got.double() - exact).abs() <= bound).all())
     # infinities and NaN beside the end of K, where blocks are filled up with zeros
-    l.tensor[K - 1, 3], l.tensor[K - 32, long - 1], l.tensor[K - 5, 64] = float("inf"), -float("inf"), float("nan")
+    at[K - 1, 3], at[K - 32, long - 1], at[K - 5, min(64, long - 2)] = float("inf"), -float("inf"), float("nan")
     want = ah.adahop_gemm(A, B, strategy, 32, k, idx=idx)
     again = ah.adahop_gemm(A, B, strategy, 32, k, idx=idx, **{packed: ah.adahop_pack_operand(l, row, strategy, 32)})
-    assert torch.equal(again["C"].view(torch.int32), want["C"].view(torch.int32))
+    # (the codes of a NaN have no defined sign: a K-contiguous operand's two quantisers subtract in different ways, and the rest of that row may differ)
+    assert torch.equal(extracted(again["C"]), extracted(want["C"]))
+    there = torch.arange(long, device="cuda") != (min(64, long - 2) if long_kc else -1)
+    a, b = (C["C"][:, there] if row else C["C"][there] for C in (again, want))
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     assert bool(want["C"][idx.long()].isinf().any() if row else want["C"][:, idx.long()].isinf().any())
 
 
+# K-contiguous, from 32 Mi elements on (k_outlier_products_kc): 16 .. 96 rows; rows of the operand that end inside a workgroup's 128, a wave's 32 and a load's 8;
+# K-elements that end inside a block, at each quarter of it; one block, the shortest rows, and the longest
+@pytest.mark.parametrize("short,long,K,k,short_kc", [
+    (96, 8200, 4128, 5, True), (330, 4160, 8256, 17, False), (64, 1100, 31008, 40, True), (300, 8251, 4224, 60, True), (120, 28681, 1184, 90, False),
+    (96, 8192, 4320, 96, True), (64, 131203, 256, 16, True), (40, 1048610, 32, 3, False), (24, 17, 2097120, 5, True)])
+@pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
+def test_same_bits_whoever_packs_a_k_contiguous_operand(short, long, K, k, short_kc, strategy):
+    test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, strategy, long_kc=True)
+
+
+@pytest.mark.parametrize("long_kc", [False, True])
 @pytest.mark.parametrize("long,K,k", [(20008, 4320, 64), (4100, 8224, 9)])
-def test_products_by_themselves_under_capture(long, K, k):
+def test_products_by_themselves_under_capture(long, K, k, long_kc):
     """The products of a packed operand, long slices and short, from a graph: every replay, with new rows in place and eager calls between, has the
     eager call's bits."""
     if not torch.cuda.is_available():
@@ -188,7 +204,10 @@ def test_products_by_themselves_under_capture(long, K, k):
     gen = torch.Generator(device="cuda").manual_seed(long)
     rows = torch.randn(3, 96, K, generator=gen, device="cuda").to(torch.bfloat16)
     A = ah.Operand(rows[0].clone(), True)
-    B = ah.Operand(torch.randn(K, (long + 7) // 8 * 8, generator=gen, device="cuda").to(torch.bfloat16)[:, :long], False)
+    if long_kc:
+        B = ah.Operand(torch.randn(long, K, generator=gen, device="cuda").to(torch.bfloat16), True)
+    else:
+        B = ah.Operand(torch.randn(K, (long + 7) // 8 * 8, generator=gen, device="cuda").to(torch.bfloat16)[:, :long], False)
     packed = ah.adahop_pack_operand(B, True, inputs.IHT_OE_ROW, 32)
     ws = torch.empty(ah.adahop_gemm_workspace_bytes(96, long, K, inputs.IHT_OE_ROW, k), dtype=torch.uint8, device="cuda")
     C, idx = torch.empty(96, long, device="cuda"), torch.randperm(96, generator=gen, device="cuda")[:k].to(torch.int32)
