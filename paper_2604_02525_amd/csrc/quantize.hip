@@ -441,11 +441,13 @@ template <int B, bool SR> __device__ __forceinline__ void quant_kc_whole(const q
 }
 
 // FLAT = 0: blockIdx.x is the row, blockIdx.y and the thread its units, 16 to a workgroup; FLAT = 1: the units of all rows are
-// numbered consecutively.  FLAT = 0 where a row is exactly one workgroup (and for counts above row_of_unit's): where the last of a row's
-// workgroups has fewer units the rest of it idles, and with several of them a row's parts are written far apart in time.  FLAT = 0 / 1, us: 10000 rows x
-// 4096 18.0 / 18.6, x 4256 27.2 / 19.9, x 3072 15.4 / 15.0, x 11008 53.2 / 45.4; 28672 x 8192 113 / 99; 16384 x 28672 232 / 196.  Rounded stochastically, which is
-// bound by vector instructions, and fewer of them with a row that is the same for the workgroup, also where a row is several whole workgroups: 28672 x 8192 161
-// / 165, 8192 x 12288 67.9 / 69.8, but x 4256 33.8 / 26.5, x 2048 16.6 / 13.6.
+// numbered consecutively.  FLAT = 1 where it is free to choose: of a row that is no whole number of workgroups FLAT = 0 leaves a part of the last one idle,
+// with several of them a row's parts are written far apart in time, and whole workgroups of consecutive units have fewer instructions (quant_kc_whole).
+// FLAT = 0 / 1, us: 10000 rows x 4256 27.2 / 19.9, x 3072 15.4 / 15.0, x 11008 53.2 / 45.4; 28672 x 8192 113 / 99; 16384 x 28672 232 / 196; rows of
+// exactly one workgroup 2016 x 4096 6.0 / 5.8, 4096 x 4096 9.5 / 9.2, 8192 x 4096 16.2 / 15.7, 32768 x 4096 54.1 / 54.1.  FLAT = 0 for counts above row_of_unit's, and where
+// it is the faster one by 1 .. 2 %: such rows that are few or end inside their last unit (500 x 4096 4.7 / 4.8, 10000 x 4064 21.0 / 21.2), and,
+// rounded stochastically, which has fewer vector instructions with a row that is the same for the workgroup, rows of whole workgroups (28672 x 8192 165.8 /
+// 167.0, 8192 x 12288 73.5 / 73.9, 2048 x 8192 15.0 / 15.3, but x 4256 33.8 / 26.5, x 2048 16.6 / 13.6).
 template <int B, bool SR, bool TAIL, int NT> __device__ __forceinline__ void quant_kc_block(const quant_t &q, uint32_t block)
 {
     if constexpr (!TAIL) { // (up to 16 or 32 rows' gaps lie within 32 bits)
@@ -1479,7 +1481,7 @@ template <int B, bool SR> int launch_one_b(quant_kind_t kind, const quant_t &q, 
             hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, true>), grid, dim3(256), 0, st, q);
         else
             hipLaunchKernelGGL((k_quant_kc16_gather<B, SR, false>), grid, dim3(256), 0, st, q);
-    } else if (q.upr == 16 || (SR && q.upr % 16 == 0) || !counts_flat(KC, q)) {
+    } else if ((q.upr == 16 && (tail || q.outer < 1024)) || (SR && q.upr % 16 == 0) || !counts_flat(KC, q)) {
         const dim3 grid((unsigned)q.outer, (unsigned)ceil_div(q.upr, 16));
         if (tail)
             hipLaunchKernelGGL((k_quant_kc16<B, 0, SR, true>), grid, dim3(256), 0, st, q);

@@ -206,6 +206,26 @@ def test_units_counted_beyond_the_one_multiplication(ah):
         assert torch.equal(c, codes[at:at + 150]) and torch.equal(s, scales[at:at + 150])
 
 
+@pytest.mark.parametrize("outer,K,pad", [(500, 4096, 0), (1023, 4096, 8), (1024, 4096, 0), (1030, 4096, 8), (1030, 4064, 0), (1030, 3840, 0)])
+@pytest.mark.parametrize("block", [0, 32])
+def test_rows_of_exactly_one_workgroup(ah, outer, K, pad, block):
+    """K-contiguous rows of 16 units, of whole ones and with a shorter last one, and of 15, numbered row by row and over all rows: the bytes of the
+    same matrix stored K-strided; rows and K-channels masked, rounded to nearest and stochastically."""
+    gen = torch.Generator(device="cuda").manual_seed(outer * K + pad)
+    x = torch.full((outer, K + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    x[:, :K] = torch.randn(outer, K, generator=gen, device="cuda")
+    t = torch.zeros(K, (outer + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")
+    t[:, :outer] = x[:, :K].t()
+    zk, zo = torch.zeros(K, dtype=torch.uint8, device="cuda"), torch.zeros(outer, dtype=torch.uint8, device="cuda")
+    zk[[0, K // 2, K - 1]] = 1
+    zo[[0, outer // 2, outer - 1]] = 1
+    say("rows of one workgroup", outer, K, pad, block)
+    for kw in ({}, {"zero_k": zk}, {"zero_outer": zo}, {"sr_seed": 5}):
+        got, want = (ah.adahop_iht_quantize(op, block, **kw) for op in (ah.Operand(x[:, :K], True), ah.Operand(t[:, :outer], False)))
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), list(kw)
+
+
 @pytest.mark.parametrize("outer,K", [(40, 32), (72, 320), (1000, 2336), (1032, 2336), (4160, 8192), (8200, 4352), (29992, 512), (6976, 7712)])
 @pytest.mark.parametrize("block", [0, 32])
 def test_orders_of_the_workgroups_of_a_k_strided_operand(ah, outer, K, block):
