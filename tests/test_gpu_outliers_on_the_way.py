@@ -40,7 +40,7 @@ CASES = [
     (300, 1000, 1056, 96, 32, True),    # the most rows; columns that end inside a 16-byte piece
     (300, 256, 512, 97, 64, True),      # one more: the separate kernel
     (5000, 512, 4096, 48, 128, True),
-    (64, 12808, 256, 5, 128, True),     # more than 200 column tiles: their own order
+    (64, 12808, 256, 5, 128, True),     # rows off the 128-byte lines: an order of the column tiles of their own
     (100, 12801, 512, 20, 256, False),
     (1030, 4100, 1312, 49, 32, False),
     (72, 20000, 32, 3, 32, False),
@@ -90,7 +90,10 @@ def test_products_on_the_way(short, long, K, k, block, short_kc, strategy, long_
 
 @pytest.mark.parametrize("short,long,K,k,block,short_kc", CASES + [
     (70, 127, 96, 33, 32, True), (70, 63, 2048, 9, 256, False), (600, 191, 4416, 70, 64, True),
-    (300, 20504, 4128, 5, 32, True),    # an operand that is streamed past the caches
+    # an operand that is streamed past the caches, 16 .. 96 extracted rows
+    (300, 20504, 4128, 5, 32, True), (300, 20504, 4352, 17, 64, True), (300, 20504, 4352, 33, 128, True), (300, 20504, 4352, 49, 256, True),
+    (300, 20504, 4352, 90, 256, True), (300, 20488, 4352, 96, 64, False), (300, 20504, 4352, 16, 256, False), (300, 20504, 4352, 32, 128, False),
+    (300, 20504, 4352, 48, 64, False), (300, 20504, 4352, 64, 32, False), (300, 20504, 4352, 65, 128, True),
 ])
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
 def test_products_on_the_way_of_a_k_contiguous_operand(short, long, K, k, block, short_kc, strategy):

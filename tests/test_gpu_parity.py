@@ -136,8 +136,8 @@ def test_iht_quantize_bit_exact(ah, b, k_contig):
 
 @pytest.mark.parametrize("b", [256, 32])
 def test_iht_quantize_k_strided_long_rows_bit_exact(ah, b):
-    """K-strided operand with more than 256 tiles of 64 columns (the quantiser then starts its workgroups in groups of
-    32 column tiles that walk the K-blocks together): a whole number of groups plus a narrower last one plus a ragged
+    """K-strided operand with 278 tiles of 64 columns, rows off the 128-byte lines (the quantiser then starts its workgroups in groups of
+    16 column tiles that walk the K-blocks together): a whole number of groups plus a narrower last one with a ragged
     last tile, three K-blocks, with both masks."""
     outer, K = (8 * 32 + 21) * 64 + 40, 768
     rng = np.random.default_rng(300 + b)

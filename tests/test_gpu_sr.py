@@ -187,8 +187,8 @@ def test_stochastic_rounding_in_the_quantiser_that_copies_rows(ah, strategy, lay
 @pytest.mark.parametrize("rounded", ["a", "b"])
 @pytest.mark.parametrize("M,N,K,b", [(3, 1, 32, 32), (70, 65, 288, 32), (130, 200, 512, 256), (64, 13001, 544, 32), (13001, 70, 320, 64)])
 def test_one_operand_rounded_beside_the_other(ah, layouts, rounded, M, N, K, b):
-    """Both operands quantised in one launch where the other one is K-strided: one workgroup of either, shorter last tiles, more than
-    200 column tiles (an order of their own).  Codes and scales are the bits of the quantisers by themselves."""
+    """Both operands quantised in one launch where the other one is K-strided: one workgroup of either, shorter last tiles, rows
+    off the 128-byte lines (an order of their own).  Codes and scales are the bits of the quantisers by themselves."""
     say("rounded beside", layouts, rounded, (M, N, K, b))
     ops = {}
     for key, outer, kc in (("a", M, layouts[0]), ("b", N, layouts[1])):
