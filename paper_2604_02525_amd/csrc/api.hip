@@ -414,8 +414,8 @@ static int gemm_whole_path(const adahop_operand_t *A, const adahop_operand_t *B,
     const bool from_a = strategy == ADAHOP_IHT_OE_ROW; // (row / column extraction: of which operand)
     const adahop_operand_t &short_op = from_a ? *A : *B, &long_op = from_a ? *B : *A;
     outlier_job_t outliers = {};
-    // Row and column extraction: the bf16 products are formed by the quantiser of the other operand where that is K-strided
-    // (k_quant_ks16_outliers), whether the indices are selected here or given.  Where that operand comes packed, or is rounded stochastically,
+    // Row and column extraction: the bf16 products are formed by the quantiser of the other operand (k_quant_ks16_outliers where that is K-strided,
+    // k_quant_kc16_outliers where it is K-contiguous), whether the indices are selected here or given.  Where that operand comes packed, or is rounded stochastically,
     // they are formed by themselves in the same order (launch_outlier_products): a product has the same bits, packed operands or not, at any size.
     // Before the MXFP4 product, beside the steps below, up to a size; above it, after the product, by launch_oe_rowcol, so that both
     // quantisers can share a launch.  Whole calls, before / after: 8192 x 4096 x 4096, 82 rows, packed, 113.8 / 117.5 us, 1024 x 2048 x 2048, 11

@@ -75,8 +75,8 @@ int launch_iht_quantize_two(int iht_block, const quant_job_t &a, const quant_job
 // Both operands of a small product, and the product, in one launch; where quant_and_product_takes them and gemm_mx_splits_stages holds.
 bool quant_and_product_takes(const quant_job_t &a, const quant_job_t &b);
 int launch_quant_and_product(int iht_block, const quant_job_t &a, const quant_job_t &b, void *C, int64_t ldc, int c_bf16, hipStream_t st);
-// One K-strided operand (nothing extracted from it, rounded to nearest), and on the way its products with the k rows extracted from the
-// other one: slice s of p is [k, outer] and holds the sums over the 256-element blocks s, s + nslice, ... of K.
+// One operand of either storage order (nothing extracted from it, rounded to nearest), and on the way its products with the k rows extracted from the
+// other one (k_quant_ks16_outliers, k_quant_kc16_outliers): slice s of p is [k, outer] and holds the sums over the 256-element blocks s, s + nslice, ... of K.
 struct outlier_job_t {
     const uint16_t *rows; // extracted row t begins at rows + (idx ? idx[t] : t) * ld
     int64_t ld;
@@ -98,12 +98,13 @@ struct topk_job_t {
     int dim, k;
     int32_t *idx;
     uint8_t *mask;
-    uint16_t *pos1; // may lie where scores lies
+    uint16_t *pos1; // (or nullptr) not where scores lies: a caller finds the scores afterwards
 };
 bool topk_beside_quant(int64_t dim, const quant_job_t &job);
 bool iht_quantize_beside_topk(int64_t dim, const adahop_operand_t &x); // the same for an operand rounded to nearest, no K-channels copied out
 int launch_topk_beside_quant(const topk_job_t &topk, int iht_block, const quant_job_t &job, hipStream_t st);
-// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere, for k <= 0xffff, where foid_writes_positions holds; it may lie where scores lies.
+// pos1 (may be nullptr): pos1[c] = t + 1 where c = idx[t], 0 elsewhere, for k <= 0xffff, where foid_writes_positions holds; not where
+// scores lies, which a caller finds afterwards.
 bool foid_writes_positions(int64_t dim);
 int launch_foid_scores(const adahop_operand_t &x, int axis, float *scores, hipStream_t st);
 int launch_foid_topk(const adahop_operand_t &x, int axis, int k, int32_t *idx, uint8_t *mask, float *scores,

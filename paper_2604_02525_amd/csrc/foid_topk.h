@@ -69,8 +69,8 @@ template <int NT> constexpr int topk_per_wave(int n) { return ((n + NT / 64 - 1)
 template <int NT> constexpr size_t topk_lds_bytes(int dim) { return (size_t)topk_per_wave<NT>(dim) * (NT / 64) * 4 + sizeof(topk_shared_t); }
 static_assert(topk_lds_bytes<TOPK_THREADS>(TOPK_LDS_KEYS) <= 160 * 1024, "keys, histograms and candidates share one compute unit's LDS");
 
-// pos1 (or nullptr): the position in idx + 1 of every selected index, 0 for the others; it may lie in the memory of the scores,
-// which nobody reads any more once the keys are in LDS.  skeys: topk_lds_bytes<NT>(dim) of LDS, per * NW keys, then topk_shared_t.
+// pos1 (or nullptr): the position in idx + 1 of every selected index, 0 for the others; not in the memory of the scores,
+// which a caller finds there afterwards.  skeys: topk_lds_bytes<NT>(dim) of LDS, per * NW keys, then topk_shared_t.
 // dim <= 2048 NT / 64 (eight 16-byte loads per lane).
 template <int NT>
 __device__ __forceinline__ void topk_lds(const float *scores, int dim, int k, int32_t *__restrict__ idx, uint8_t *__restrict__ mask,

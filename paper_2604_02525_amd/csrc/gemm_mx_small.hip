@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256, NST == 1 ? 4 : 2) void k_gemm_mx_small(int64_t
 
     constexpr int AHEAD = NST > 1 ? NST - PU : 1; // stages whose copies are asked for here
     if constexpr (PRE) {
-        // A run is read in aligned words (at most 128 x 32 bytes: four per thread) and the bytes in front of the first and behind the
+        // A run is read in aligned words (four per thread) and the bytes in front of the first and behind the
         // last of them.  The loads of both operands go ahead of the stages' copies, so that the wait for them is the wait that the
         // first stage needs anyway.
         uint8_t *const all = smem + NST * S::STAGE;
@@ -320,6 +320,8 @@ __global__ __launch_bounds__(256, NST == 1 ? 4 : 2) void k_gemm_mx_small(int64_t
             const int total = r.rows * KB;
             r.head = min((int)(-(uint32_t)reinterpret_cast<uintptr_t>(r.p) & 3u), total);
             r.words = sc.canonical ? (total - r.head) >> 2 : 0;
+            // (one buffer: one stage)
+            static_assert((S::TM > S::TN ? S::TM : S::TN) * 8 * (NST == 1 ? 1 : PRE_STAGES) <= 4 * 4 * 256, "four words per thread hold an operand's run");
             r.edge = tid < r.head ? tid : 4 * r.words + tid;
             r.e = 0;
             if (sc.canonical && r.edge < total) r.e = r.p[r.edge];
@@ -497,7 +499,7 @@ typedef variant_t<2, 2, 2, 2, 1, 2, 1> v128_t;    // 128 x 128, two workgroups p
 // Not for more than 64 MB of fp32 off the 64-byte grid, where twice the tiles in flight cost more line pieces than they hide (9687 x
 // 14001 x 64 133 / 203 us, 6000 x 9001 x 64 43 / 46; 3324 x 2547 x 32, 32 MB, 13.8 / 12.1), and not for K = 256, where it gains nothing.
 typedef variant_t<2, 2, 2, 2, 1, 1, 1> v128one_t;
-// The same in tiles of 64 x 256, for fp32 rows on the 64-byte grid and more than 80 MB of C: the four waves store 1 KiB of a row at about the
+// The same in tiles of 64 x 256, three workgroups (50 KB of LDS), for fp32 rows on the 64-byte grid and more than 80 MB of C: the four waves store 1 KiB of a row at about the
 // same time, and stores alone reach 5.9 TB/s in such tiles, 5.5 in 128 x 128.  128 x 128 / 64 x 256, us: 8192 x 12288 x 96 75.9 / 69.4, 16384 x 16384 x
 // 96 194 / 166, 8192 x 14336 x 192 88.7 / 80.8, 8192 x 4096 x 192 35.5 / 33.3; below that as much as they gain is lost with the rows of B that a tile reads, 5152
 // x 2912 x 64 (60 MB) 17.3 / 18.2, 2048 x 8192 x 192 (64 MB) 19.0 / 19.2; off the grid 8192 x 9001 x 96 66 (two buffers) / 70, bf16 28672 x 8192 x 64 91 / 110.
