@@ -77,6 +77,8 @@ typedef struct {
  * E2M1 code: bit 3 = sign, bits 0..2 index {0, .5, 1, 1.5, 2, 3, 4, 6}; round to nearest even,
  * saturating at 6.  Scale = 127 + floor(log2(amax)) - 2, clamped to [0, 254]; 0 for an all-zero
  * block (OCP Microscaling v1.0; the paper names the format in Sec. 1 and App. F item 2).
+ * E2M1 has no NaN: the codes that stand for one, and for opposite infinities in one transform block, are
+ * left open, and differ in sign between the ways to quantise an operand.
  * Requires K % 32 == 0.
  * ------------------------------------------------------------------------------------------- */
 
