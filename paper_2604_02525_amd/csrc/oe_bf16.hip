@@ -531,22 +531,22 @@ __global__ __launch_bounds__(256, CT == 4 || R == 3 ? 1 : 2) void k_outlier_prod
 }
 
 // The same for a K-contiguous L, in the order of k_quant_kc16_outliers: slices as above, a block's K-elements in ascending chunks of 32, one instruction
-// each.  Bound by reading L, and by the extracted rows beside it where they are many (12288 x 8192, 90 rows: 66 us, 50 without its loads of L).
-//   Workgroup = T tiles of 16 extracted rows x 128 rows of L x one slice, a wave = all the extracted rows x 32 rows of L.
+// each.  Bound by reading L, and by the extracted rows beside it where they are many (12288 x 8192, 90 rows, 128 rows of L per workgroup: 66 us, 50 without its loads of L).
+//   Workgroup = T tiles of 16 extracted rows x 64 CT rows of L x one slice, a wave = all the extracted rows x 16 CT rows of L.
 //   L goes from memory to the matrix cores' operands without the LDS.  A load takes whole lines, 8 rows x 64 K-elements: lane 16 g + 8 u + r piece 4 u + g of
 //   row r.  Of two of them, rows 0 .. 7 and 8 .. 15 of a tile, an exchange of the lanes 8 apart makes the operands of two instructions, u = 0 and 1.  Two chunks of 64
 //   K-elements are on their way in registers while a third is multiplied (four: 16384 x 4096, 64 rows, 39 -> 44 us; through the LDS as in k_oe_skinny: the same,
-//   9152 x 16672, 2 rows, 72 / 66; 256 rows of L per workgroup, 20000 x 4096, 40 rows, 46 / 56).
+//   9152 x 16672, 2 rows, 72 / 66).
 //   The extracted rows travel in stages of 128 K-elements through two buffers, one barrier per stage; in a buffer as 4 x 64 pieces for each 16 rows, as in
 //   the quantiser.
 //   A tile's slices are neighbours on an XCD, as in the quantiser, and each XCD begins its run of the workgroups three tiles further than the one before: begun alike,
 //   the XCDs read a power of two apart (16384 x 4096, 10 rows 35.7 -> 30.5 us, 64 rows 47 -> 40; 8192 x 8192 29.6 -> 27.7).
-constexpr int OPK_ROWS = 128, OPK_STAGE = 128;
+constexpr int OPK_STAGE = 128;
 
-template <int T>
+template <int T, int CT>
 __global__ __launch_bounds__(256, 2) void k_outlier_products_kc(const uint16_t *__restrict__ L, int64_t ldl, int64_t Lo, int64_t K, outlier_job_t e, int row_groups)
 {
-    constexpr int CT = OPK_ROWS / 64, NS = 2 * ((T + 1) / 2), SB = OPK_STAGE * 2 * 16 * NS; // tiles of a wave; pieces of the extracted rows per lane and stage; bytes of a stage
+    constexpr int NS = 2 * ((T + 1) / 2), SB = OPK_STAGE * 2 * 16 * NS; // pieces of the extracted rows per lane and stage; bytes of a stage
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * SB];
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int tiles = row_groups * e.nslice;
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(256, 2) void k_outlier_products_kc(const uint16_t *
     const int xcd = blockIdx.x & 7, rest = tiles & 7, run = (tiles >> 3) + (xcd < rest ? 1 : 0);
     const int at = xcd * (tiles >> 3) + min(xcd, rest) + (((int)blockIdx.x >> 3) + 3 * e.nslice * xcd) % run;
     const int group = at / e.nslice, slice = at - group * e.nslice;
-    const int64_t l0 = (int64_t)group * OPK_ROWS + 16 * CT * w;
+    const int64_t l0 = (int64_t)group * (64 * CT) + 16 * CT * w;
     const int nblock = ((int)((K + 255) / 256) - slice + e.nslice - 1) / e.nslice;
     const int64_t last = (int64_t)(slice + e.nslice * (nblock - 1)) * 256;
     const int nstage = 2 * (nblock - 1) + (K - last > OPK_STAGE ? 2 : 1);
@@ -853,10 +853,10 @@ template <int R, int CT> int launch_products_as(const adahop_operand_t &x, const
     return check_launch();
 }
 
-template <int T> int launch_products_kc_as(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st)
+template <int T, int CT> int launch_products_kc_as(const adahop_operand_t &x, const outlier_job_t &e, hipStream_t st)
 {
-    const int64_t groups = ceil_div(x.outer, OPK_ROWS);
-    hipLaunchKernelGGL((k_outlier_products_kc<T>), dim3((unsigned)(groups * e.nslice + (e.codes ? e.k : 0))), dim3(256), 0, st,
+    const int64_t groups = ceil_div(x.outer, 64 * CT);
+    hipLaunchKernelGGL((k_outlier_products_kc<T, CT>), dim3((unsigned)(groups * e.nslice + (e.codes ? e.k : 0))), dim3(256), 0, st,
                        static_cast<const uint16_t *>(x.data), x.ld, x.outer, x.K, e, (int)groups);
     return check_launch();
 }
@@ -979,19 +979,35 @@ int configure_oe_rowcol()
 // K-contiguous, fewer than LONG_KC elements: the quantiser's kernel, which leaves the operand in the caches; a larger one takes the place of the packed operands there,
 // which the next product reads.  Whole calls on operands used in turn, the quantiser's kernel / k_outlier_products_kc, us: 6144 x 4096, 10 rows 44 / 48.5;
 // 8192 x 4096, 41 rows 82 / 83; 4096 x 8192, 10 rows 58.5 / 56; 2048 x 16384, 10 rows 71 / 67; 9216 x 4096, 41 rows 101 / 97; 16384 x 4096, 10 rows 98 / 87;
-// 11008 x 8192, 40 rows 187 / 167; 28672 x 2048, 82 rows 246 / 199; 28672 x 8192, 41 rows 384 / 375.  (k_oe_skinny, which adds in another order, is up to 8 % faster in
-// such a call with many rows and short slices: 16384 x 4096, 64 rows 92 / 96, 20000 x 4096, 40 rows 109 / 116, 12288 x 8192, 90 rows 128 / 138; elsewhere as fast, or up to 9 % slower.)
+// 11008 x 8192, 40 rows 187 / 167; 28672 x 2048, 82 rows 246 / 199; 28672 x 8192, 41 rows 384 / 375.
+// There 128 rows of L per workgroup, but 192 or 64 where the fullest compute unit then has fewer rows, 64 with up to 48 extracted rows (each workgroup moves all of
+// them), and of 192 and 128 alike 192 with more than 64.  Products alone, us, 128 / 192 rows: 36000 x 2048, 70 rows 59 / 48, 40 rows 50.5 / 39.4; 35008 x 3072, 48 rows
+// 68 / 53; 24000 x 4096, 60 rows 55.5 / 48; alike 12288 x 8192, 90 rows 71 / 66, 20000 x 4096, 40 rows 45.4 / 44.0, 14336 x 4096, 40 rows 36.8 / 37.7; more 16384 x
+// 4096, 80 rows 42 / 49.  128 / 64 rows: 18000 x 4096, 10 rows 36.6 / 33.2, 40 rows 44.3 / 43.5; 9000 x 11008, 30 rows 56.5 / 52.7; 28672 x 8192, 10 rows 90 / 82; 20000 x 8192, 70 rows
+// 84 (192) / 92; alike 9152 x 16672, 2 rows 66.6 / 68.4, 14336 x 4096, 40 rows 36.4 / 40.5.
+// (k_oe_skinny, which adds in another order and splits K as suits it, is up to 6 % faster in such a call with many rows and short slices: 16384 x 4096, 64 rows 92 / 96, 12288 x
+// 8192, 90 rows 127 / 135, 14336 x 4096, 40 rows 82 / 87; elsewhere as fast, or up to 20 % slower.)
 int launch_outlier_products(const adahop_operand_t &L, const outlier_job_t &e, hipStream_t st)
 {
     if (L.k_contig ? L.outer * L.K < LONG_KC : ceil_div(ceil_div(L.K, 256), e.nslice) < LONG_SLICE)
         return launch_iht_quantize_outliers(-1, {&L, nullptr, nullptr, nullptr, nullptr, nullptr, {nullptr, 0}, {nullptr, nullptr, 0, 0}, {nullptr, nullptr}}, e, st);
     if (L.k_contig) {
+        // the rows of L, in 64, that the fullest compute unit takes
+        auto most = [&](int64_t ct) { return ct * ceil_div(ceil_div(L.outer, 64 * ct) * e.nslice, 256); };
+        auto go = [&](auto tiles) {
+            constexpr int T = decltype(tiles)::value;
+            const int64_t two = most(2), three = most(3);
+            if constexpr (T <= 3) {
+                if (most(1) < (two < three ? two : three)) return launch_products_kc_as<T, 1>(L, e, st);
+            }
+            return three < two || (T == 6 && three == two) ? launch_products_kc_as<T, 3>(L, e, st) : launch_products_kc_as<T, 2>(L, e, st);
+        };
         switch (e.tiles) {
-        case 1: return launch_products_kc_as<1>(L, e, st);
-        case 2: return launch_products_kc_as<2>(L, e, st);
-        case 3: return launch_products_kc_as<3>(L, e, st);
-        case 4: return launch_products_kc_as<4>(L, e, st);
-        case 6: return launch_products_kc_as<6>(L, e, st);
+        case 1: return go(std::integral_constant<int, 1>());
+        case 2: return go(std::integral_constant<int, 2>());
+        case 3: return go(std::integral_constant<int, 3>());
+        case 4: return go(std::integral_constant<int, 4>());
+        case 6: return go(std::integral_constant<int, 6>());
         }
         return ADAHOP_E_INVALID_ARG;
     }

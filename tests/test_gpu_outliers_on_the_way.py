@@ -185,11 +185,13 @@ def test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, 
     assert bool(want["C"][idx.long()].isinf().any() if row else want["C"][:, idx.long()].isinf().any())
 
 
-# K-contiguous, from 32 Mi elements on (k_outlier_products_kc): 16 .. 96 rows; rows of the operand that end inside a workgroup's 128, a wave's 32 and a load's 8;
-# K-elements that end inside a block, at each quarter of it; one block, the shortest rows, and the longest
+# K-contiguous, from 32 Mi elements on (k_outlier_products_kc): 16 .. 96 rows, each with every width that a workgroup may have; rows of the operand that end inside
+# a workgroup's, a wave's and a load's 8; K-elements that end inside a block, at each quarter of it; one block, the shortest rows, and the longest
 @pytest.mark.parametrize("short,long,K,k,short_kc", [
     (96, 8200, 4128, 5, True), (330, 4160, 8256, 17, False), (64, 1100, 31008, 40, True), (300, 8251, 4224, 60, True), (120, 28681, 1184, 90, False),
-    (96, 8192, 4320, 96, True), (64, 131203, 256, 16, True), (40, 1048610, 32, 3, False), (24, 17, 2097120, 5, True)])
+    (96, 8192, 4320, 96, True), (64, 131203, 256, 16, True), (40, 1048610, 32, 3, False), (24, 17, 2097120, 5, True),
+    (64, 31452, 1184, 16, True), (64, 131203, 256, 20, True), (64, 64487, 544, 25, False), (96, 9423, 4128, 45, True), (64, 33199, 1184, 45, True),
+    (96, 4293, 8224, 60, True), (64, 64370, 544, 49, True), (120, 68578, 544, 96, True), (80, 3486, 11040, 45, True)])
 @pytest.mark.parametrize("strategy", [inputs.IHT_OE_ROW, inputs.IHT_OE_COL])
 def test_same_bits_whoever_packs_a_k_contiguous_operand(short, long, K, k, short_kc, strategy):
     test_same_bits_whoever_packs_the_other_operand(short, long, K, k, short_kc, strategy, long_kc=True)
